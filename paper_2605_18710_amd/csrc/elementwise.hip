@@ -1,7 +1,7 @@
 // Bandwidth-bound kernels of the module step: LayerNorm / RMSNorm forward and backward
 // (with fused residual add and fixed-order column reductions), GELU / SwiGLU forward and
 // backward, MSE loss and gradient, column sums for bias gradients, and the stem kernels
-// (patch unfold, position table, embedding gather / owner-computes scatter).
+// (patch unfold, position table).
 //
 // All reductions run in an order fixed by the problem shape alone: persistent grids only
 // decide which workgroup handles a work item, so results are bit-identical for any quota.
@@ -599,110 +599,6 @@ __global__ __launch_bounds__(kThreads) void pos_grad_kernel(const T* __restrict_
   }
 }
 
-// Token ids and image-token counts.  Without per-sample counts every sample has n_img image
-// tokens and ids holds the N - n_img text ids of a sample, [B, N - n_img].  With counts
-// (int32 [B], clamped to [0, n_img]) sample b takes its first counts[b] image tokens and ids
-// holds one id per sequence position, [B, N], read at positions counts[b] .. N-1.
-__device__ __forceinline__ int stem_n_img(const int32_t* counts, int b, int n_img) {
-  if (!counts) return n_img;
-  const int c = counts[b];
-  return c < 0 ? 0 : (c > n_img ? n_img : c);
-}
-__device__ __forceinline__ int stem_id(const int32_t* ids, const int32_t* counts, int b, int t, int N, int n_img, int vocab) {
-  // an id outside the table is clamped rather than followed out of bounds (forward and backward alike)
-  const int id = counts ? ids[(int64_t)b * N + t] : ids[(int64_t)b * (N - n_img) + (t - n_img)];
-  return id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kThreads) void text_stem_fwd_kernel(const T* __restrict__ img_tok, const int32_t* __restrict__ ids,
-                                                                 const int32_t* __restrict__ counts,
-                                                                 const T* __restrict__ table, T* __restrict__ out,
-                                                                 int B, int N, int n_img, int h, int vocab) {
-  const int64_t total = (int64_t)B * N * h;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += (int64_t)gridDim.x * kThreads) {
-    const int c = (int)(i % h);
-    const int64_t row = i / h;
-    const int t = (int)(row % N), b = (int)(row / N);
-    if (t < stem_n_img(counts, b, n_img)) out[i] = img_tok[((int64_t)b * n_img + t) * h + c];
-    else out[i] = table[(int64_t)stem_id(ids, counts, b, t, N, n_img, vocab) * h + c];
-  }
-}
-
-// gradient of the image tokens: rows the sample did not use get zero
-template <typename T>
-__global__ __launch_bounds__(kThreads) void split_img_kernel(const T* __restrict__ dy, const int32_t* __restrict__ counts,
-                                                             T* __restrict__ d_img, int B, int N, int n_img, int h) {
-  const int64_t total = (int64_t)B * n_img * h;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += (int64_t)gridDim.x * kThreads) {
-    const int c = (int)(i % h);
-    const int64_t row = i / h;
-    const int t = (int)(row % n_img), b = (int)(row / n_img);
-    d_img[i] = t < stem_n_img(counts, b, n_img) ? dy[((int64_t)b * N + t) * h + c] : from_f32<T>(0.f);
-  }
-}
-
-// Embedding gradient, owner computes: the workgroup that owns table row v walks all token
-// positions once, 256 at a time, and gathers the positions that hold v into a list in LDS in
-// ascending order (waves in order, lanes in order, by ballot and prefix count); whenever the
-// list is nearly full, and at the end, every thread adds the listed rows of dy to the column
-// sums it keeps in registers, in list order.  The sum of a row is therefore taken over its
-// occurrences in ascending position whatever the grid, repeated ids need no atomics, and a
-// row nobody uses costs one pass over the ids and a zero fill.
-constexpr int kEmbedList = 1024;                     // positions gathered before they are summed
-constexpr int kEmbedMaxCols = 32;                    // columns per thread: rows of up to 8192 elements
-template <typename T>
-__global__ __launch_bounds__(kThreads) void embed_grad_kernel(const T* __restrict__ dy, const int32_t* __restrict__ ids,
-                                                              const int32_t* __restrict__ counts,
-                                                              T* __restrict__ dtable, int B, int N, int n_img, int h, int vocab) {
-  __shared__ int list[kEmbedList];
-  __shared__ int wave_hits[kWaves];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int total = B * N;
-  for (int v = blockIdx.x; v < vocab; v += gridDim.x) {
-    float acc[kEmbedMaxCols];
-#pragma unroll
-    for (int j = 0; j < kEmbedMaxCols; ++j) acc[j] = 0.f;
-    int n_list = 0;                                  // the same in every thread
-    auto add_listed = [&]() {
-      for (int e = 0; e < n_list; ++e) {
-        const T* row = dy + (int64_t)list[e] * h;
-#pragma unroll
-        for (int j = 0; j < kEmbedMaxCols; ++j) {
-          const int c = j * kThreads + threadIdx.x;
-          if (c < h) acc[j] += to_f32(row[c]);
-        }
-      }
-      __syncthreads();                               // everybody is done with the list
-      n_list = 0;
-    };
-    for (int p0 = 0; p0 < total; p0 += kThreads) {
-      const int p = p0 + threadIdx.x;
-      bool hit = false;
-      if (p < total) {
-        const int b = p / N, t = p - b * N;
-        hit = t >= stem_n_img(counts, b, n_img) && stem_id(ids, counts, b, t, N, n_img, vocab) == v;
-      }
-      const unsigned long long m = __ballot(hit);
-      if (lane == 0) wave_hits[wave] = __popcll(m);
-      __syncthreads();
-      int before = n_list, all = 0;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) { if (w < wave) before += wave_hits[w]; all += wave_hits[w]; }
-      if (hit) list[before + __popcll(m & ((1ull << lane) - 1ull))] = p;
-      n_list += all;
-      __syncthreads();                               // list entries visible; wave_hits free for the next chunk
-      if (n_list > kEmbedList - kThreads) add_listed();
-    }
-    if (n_list > 0) add_listed();
-#pragma unroll
-    for (int j = 0; j < kEmbedMaxCols; ++j) {
-      const int c = j * kThreads + threadIdx.x;
-      if (c < h) dtable[(int64_t)v * h + c] = from_f32<T>(acc[j]);
-    }
-  }
-}
-
 int pick_nv(int need) {
   const int opts[] = {1, 2, 3, 4, 5, 6, 8, 10};
   for (int o : opts) if (o >= need) return o;
@@ -1003,33 +899,4 @@ mosaic_status launch_pos_grad(hipStream_t s, int quota, int dtype, int B, int N,
 #define ARGS(TT) ((const TT*)dy, (TT*)dpos, B, N, h)
   EW_LAUNCH(pos_grad_kernel, total, ARGS);
 #undef ARGS
-}
-
-mosaic_status launch_text_stem_fwd(hipStream_t s, int quota, int dtype, int B, int N, int n_img, int h, int vocab,
-                                   const void* img_tok, const int32_t* ids, const int32_t* counts, const void* table, void* out) {
-  const int64_t total = (int64_t)B * N * h;
-#define ARGS(TT) ((const TT*)img_tok, ids, counts, (const TT*)table, (TT*)out, B, N, n_img, h, vocab)
-  EW_LAUNCH(text_stem_fwd_kernel, total, ARGS);
-#undef ARGS
-}
-
-mosaic_status launch_text_stem_bwd(hipStream_t s, int quota, int dtype, int B, int N, int n_img, int h, int vocab,
-                                   const void* dy, const int32_t* ids, const int32_t* counts, void* d_img, void* dtable) {
-  if (d_img != nullptr && n_img > 0) {
-    const int64_t total = (int64_t)B * n_img * h;
-    const int grid = grid_for(quota, 8, ceil_div(total, kThreads));
-    if (dtype == MOSAIC_BF16) split_img_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)dy, counts, (bf16*)d_img, B, N, n_img, h);
-    else split_img_kernel<float><<<grid, kThreads, 0, s>>>((const float*)dy, counts, (float*)d_img, B, N, n_img, h);
-    MOSAIC_LAUNCH_CHECK();
-  }
-  if (vocab > 0) {
-    if (h > kEmbedMaxCols * kThreads) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "embedding rows of %d elements; the gradient kernel holds up to %d", h, kEmbedMaxCols * kThreads);
-    const int grid = grid_for(quota, 8, vocab);
-    if (dtype == MOSAIC_BF16)
-      embed_grad_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)dy, ids, counts, (bf16*)dtable, B, N, n_img, h, vocab);
-    else
-      embed_grad_kernel<float><<<grid, kThreads, 0, s>>>((const float*)dy, ids, counts, (float*)dtable, B, N, n_img, h, vocab);
-    MOSAIC_LAUNCH_CHECK();
-  }
-  return MOSAIC_OK;
 }

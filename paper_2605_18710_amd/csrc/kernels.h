@@ -101,7 +101,8 @@ mosaic_status launch_text_stem_fwd(hipStream_t s, int quota, int dtype, int B, i
                                    int h, int vocab, const void* img_tok, const int32_t* ids,
                                    const int32_t* counts, const void* table, void* out);
 // d_img rows from dy (zero for image tokens a sample did not use); dtable[v] = sum over
-// occurrences of v (ascending position)
+// occurrences of v in an order that the ids alone fix.  scratch: text_stem_scratch_bytes, 256-byte aligned
+size_t text_stem_scratch_bytes(int64_t T, int64_t h);
 mosaic_status launch_text_stem_bwd(hipStream_t s, int quota, int dtype, int B, int N, int n_img,
                                    int h, int vocab, const void* dy, const int32_t* ids,
-                                   const int32_t* counts, void* d_img, void* dtable);
+                                   const int32_t* counts, void* d_img, void* dtable, void* scratch);

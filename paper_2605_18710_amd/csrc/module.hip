@@ -43,6 +43,7 @@ struct mosaic_module {
   // scratch byte offsets
   size_t s_dA, s_dZ, s_dU, s_dX1, s_dO, s_dQKV, s_delta, s_g0, s_g1, s_norm, s_colsum, s_mse, s_dyloss, s_splitk;
   size_t s_patches;
+  size_t s_embed = 0;    // sorted positions and run pieces of the embedding gradient
   size_t s_rope = 0;     // (cos, sin) table of the rotary embedding, when on
   size_t c_p1 = 0, c_z1 = 0, c_a1 = 0, c_p2 = 0, c_z2 = 0, c_dz2 = 0, c_dp2 = 0, c_da1 = 0, c_dz1 = 0, c_dp1 = 0;   // conv stem
   // bound buffers
@@ -245,6 +246,7 @@ void build_layout(mosaic_module* m) {
     LayerParams q;
     q.w_1 = add_tensor(m, "table", d.vocab, h);
     m->lp.push_back(q);
+    m->s_embed = take(&cur, text_stem_scratch_bytes(T, h));
   }
   m->s_mse = take(&cur, mse_scratch_bytes());
   m->s_dyloss = take(&cur, mosaic_module_output_elems(m) * es);
@@ -567,7 +569,8 @@ mosaic_status mosaic_module_backward(mosaic_module* m, int32_t quota, const mosa
     case MOSAIC_PATCH_STEM: return patch_stem_backward(m, s, q, dy, dx);
     case MOSAIC_CONV_STEM: return conv_stem_backward(m, s, q, dy, dx);
     default:
-      return launch_text_stem_bwd(s, q, m->d.dtype, m->d.batch, m->d.seq, m->d.n_img, m->d.hidden, m->d.vocab, dy, m->ids, m->img_counts, dx, G(m, m->lp[0].w_1));
+      return launch_text_stem_bwd(s, q, m->d.dtype, m->d.batch, m->d.seq, m->d.n_img, m->d.hidden, m->d.vocab, dy, m->ids, m->img_counts, dx, G(m, m->lp[0].w_1),
+                                  W(m, m->s_embed));
   }
 }
 

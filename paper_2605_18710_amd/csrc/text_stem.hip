@@ -1,0 +1,421 @@
+// Text stem: image-token rows and embedding rows assembled into sequences, and the way back.
+//
+// Forward and the image-token gradient are row copies (HBM-bound).  The embedding gradient
+// needs, for every table row, the sum of the output gradients at the positions that hold it:
+//   1. the T positions are sorted by id with a stable radix sort (8 bits a pass, two launches a
+//      pass), so the occurrences of an id are one run in ascending position;
+//   2. the sorted list is cut into segments of kSeg entries; a workgroup requests all rows of
+//      its segment at once and adds them run by run, so the work is balanced however often an
+//      id occurs; runs inside a segment go straight to the table, pieces of longer runs to scratch;
+//   3. the pieces of a run are added by the segment it starts in.  Rows that nobody used are
+//      found by bisection in the sorted list and filled with zeros beside step 2.
+// Every sum has one owner and an order fixed by the ids alone: repeated ids need no atomics and
+// the bits do not depend on the grid.
+//
+// What bounds it: the table is written whole (V x h; 131 MB at V 32000, h 2048) and dy read once;
+// the sort moves a few bytes per position and is six short launches.  A whole step (forward and
+// backward) at B8 N1024 h2048 V32000, ids with the frequencies of running text: 99 us = 2.5 TB/s of
+// the bytes it cannot do without, against 2098 us when the owner of every table row walked all
+// positions (V x T id reads).
+#include "kernels.h"
+
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / 64;
+
+// V consecutive elements as one access: 16 bytes, or a single element for rows that do not
+// start on 16-byte boundaries (a caller's tensor may be a slice of a larger buffer)
+template <typename T, int V> struct Pack { typedef T type __attribute__((ext_vector_type(V))); };
+template <typename T> struct Pack<T, 1> { typedef T type; };
+
+// Token ids and image-token counts.  Without per-sample counts every sample has n_img image
+// tokens and ids holds the N - n_img text ids of a sample, [B, N - n_img].  With counts
+// (int32 [B], clamped to [0, n_img]) sample b takes its first counts[b] image tokens and ids
+// holds one id per sequence position, [B, N], read at positions counts[b] .. N-1.
+__device__ __forceinline__ int stem_n_img(const int32_t* counts, int b, int n_img) {
+  if (!counts) return n_img;
+  const int c = counts[b];
+  return c < 0 ? 0 : (c > n_img ? n_img : c);
+}
+__device__ __forceinline__ int stem_id(const int32_t* ids, const int32_t* counts, int b, int t, int N, int n_img, int vocab) {
+  // an id outside the table is clamped rather than followed out of bounds (forward and backward alike)
+  const int id = counts ? ids[(int64_t)b * N + t] : ids[(int64_t)b * (N - n_img) + (t - n_img)];
+  return id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);
+}
+
+// One wave per row: one division per row, 16 bytes per lane and access.  (A kernel with one element
+// per thread spent its time on three 64-bit divisions per element: 51 us at B8 N1024 h2048.)
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void text_stem_fwd_kernel(const T* __restrict__ img_tok, const int32_t* __restrict__ ids,
+                                                                 const int32_t* __restrict__ counts,
+                                                                 const T* __restrict__ table, T* __restrict__ out,
+                                                                 int B, int N, int n_img, int h, int vocab) {
+  typedef typename Pack<T, V>::type vec;
+  const int lane = threadIdx.x & 63;
+  const int64_t rows = (int64_t)B * N;
+  for (int64_t row = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); row < rows; row += (int64_t)gridDim.x * kWaves) {
+    const int b = (int)(row / N), t = (int)(row - (int64_t)b * N);
+    const T* src = t < stem_n_img(counts, b, n_img) ? img_tok + ((int64_t)b * n_img + t) * h
+                                                     : table + (int64_t)stem_id(ids, counts, b, t, N, n_img, vocab) * h;
+    T* dst = out + row * h;
+    for (int c = lane * V; c < h; c += 64 * V) *reinterpret_cast<vec*>(dst + c) = *reinterpret_cast<const vec*>(src + c);
+  }
+}
+
+// gradient of the image tokens: rows the sample did not use get zero
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void split_img_kernel(const T* __restrict__ dy, const int32_t* __restrict__ counts,
+                                                             T* __restrict__ d_img, int B, int N, int n_img, int h) {
+  typedef typename Pack<T, V>::type vec;
+  const int lane = threadIdx.x & 63;
+  const int64_t rows = (int64_t)B * n_img;
+  for (int64_t row = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); row < rows; row += (int64_t)gridDim.x * kWaves) {
+    const int b = (int)(row / n_img), t = (int)(row - (int64_t)b * n_img);
+    const bool used = t < stem_n_img(counts, b, n_img);
+    const T* src = dy + ((int64_t)b * N + t) * h;
+    T* dst = d_img + row * h;
+    for (int c = lane * V; c < h; c += 64 * V) *reinterpret_cast<vec*>(dst + c) = used ? *reinterpret_cast<const vec*>(src + c) : vec{};
+  }
+}
+
+// --------------------------------------------------------------------- sort by id
+constexpr int kDigit = 8, kBins = 1 << kDigit;       // a thread per bin
+constexpr int kRounds = 8;                            // keys per thread
+constexpr int kChunk = kThreads * kRounds;            // keys per workgroup
+static_assert(kBins == kThreads, "the scatter kernel gives every bin a thread");
+
+// where a sort pass takes its keys from: the token ids (first pass; positions that hold an
+// image token get the key `vocab`, beyond every id), or the pass before
+struct SortInput {
+  const int32_t *key, *pos;                           // null key: the token ids
+  const int32_t *ids, *counts;
+  int N, n_img, vocab;
+  __device__ __forceinline__ int key_of(int e) const {
+    if (key) return key[e];
+    const int b = e / N, t = e - b * N;
+    return t >= stem_n_img(counts, b, n_img) ? stem_id(ids, counts, b, t, N, n_img, vocab) : vocab;
+  }
+  __device__ __forceinline__ int pos_of(int e) const { return key ? pos[e] : e; }
+};
+
+// digit counts of every chunk: hist[chunk][bin]
+__global__ __launch_bounds__(kThreads) void sort_hist_kernel(SortInput in, int shift, int total, int chunks, int* __restrict__ hist) {
+  __shared__ int cnt[kBins];
+  for (int c = blockIdx.x; c < chunks; c += gridDim.x) {
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      const int e = c * kChunk + r * kThreads + threadIdx.x;
+      if (e < total) atomicAdd(&cnt[(in.key_of(e) >> shift) & (kBins - 1)], 1);
+    }
+    __syncthreads();
+    hist[c * kBins + threadIdx.x] = cnt[threadIdx.x];
+    __syncthreads();
+  }
+}
+
+// A chunk's keys go to their places: entries with a smaller digit, the same digit in earlier
+// chunks, in earlier waves of the chunk (a wave owns 512 consecutive entries), in earlier rounds
+// of the wave, in earlier lanes of the round.
+__global__ __launch_bounds__(kThreads) void sort_scatter_kernel(SortInput in, int shift, int total, int chunks,
+                                                                const int* __restrict__ hist, int32_t* __restrict__ key_out,
+                                                                int32_t* __restrict__ pos_out) {
+  __shared__ int place[kWaves][kBins];
+  __shared__ int wave_total[kWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int c = blockIdx.x; c < chunks; c += gridDim.x) {
+    int key[kRounds];
+    const int first = c * kChunk + wave * (64 * kRounds) + lane;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) place[w][threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      const int e = first + 64 * r;
+      key[r] = e < total ? in.key_of(e) : -1;
+      if (e < total) atomicAdd(&place[wave][(key[r] >> shift) & (kBins - 1)], 1);
+    }
+    // this thread's bin: entries in all chunks, and in the chunks before this one
+    int all = 0, before = 0;
+    for (int k = 0; k < chunks; ++k) {
+      const int v = hist[k * kBins + threadIdx.x];
+      if (k < c) before += v;
+      all += v;
+    }
+    int scan = all;                                   // inclusive over the bins
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(scan, o, 64);
+      if (lane >= o) scan += v;
+    }
+    if (lane == 63) wave_total[wave] = scan;
+    __syncthreads();
+    int at = scan - all + before;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) if (w < wave) at += wave_total[w];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) { const int v = place[w][threadIdx.x]; place[w][threadIdx.x] = at; at += v; }
+    __syncthreads();
+    volatile int* mine = place[wave];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      const int e = first + 64 * r;
+      const bool live = e < total;
+      const int dgt = (key[r] >> shift) & (kBins - 1);
+      unsigned long long same = __ballot(live);       // lanes of this round with the same digit
+#pragma unroll
+      for (int b = 0; b < kDigit; ++b) {
+        const unsigned long long m = __ballot((dgt >> b) & 1);
+        same &= ((dgt >> b) & 1) ? m : ~m;
+      }
+      const int rank = __popcll(same & ((1ull << lane) - 1ull));
+      const int base = live ? mine[dgt] : 0;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();                // every lane has read its base before a leader moves it
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (live) {
+        if (rank == 0) mine[dgt] = base + __popcll(same);
+        key_out[base + rank] = key[r];
+        pos_out[base + rank] = in.pos_of(e);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------- sums over the runs
+constexpr int kSeg = 16;         // entries of a segment: as many rows as a thread holds in registers at once
+constexpr int kFillRows = 16;    // table rows a wave looks up and, where nobody used them, fills
+
+template <typename T, int V>
+__device__ __forceinline__ void store_row(T* dst, const float* acc) {
+  typename Pack<T, V>::type o;
+  if constexpr (V == 1) o = from_f32<T>(acc[0]);
+  else {
+#pragma unroll
+    for (int k = 0; k < V; ++k) o[k] = from_f32<T>(acc[k]);
+  }
+  *reinterpret_cast<typename Pack<T, V>::type*>(dst) = o;
+}
+
+// Items [0, segs * ctiles): segment x tile of kThreads * V columns.  Items after that: fills.
+// part[segment][0][h] is the piece of the run that reaches into the segment from the one before,
+// part[segment][1][h] the piece of a run that starts in it and goes on in the next.
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void embed_sum_kernel(const T* __restrict__ dy, const int32_t* __restrict__ key,
+                                                             const int32_t* __restrict__ pos, T* __restrict__ dtable,
+                                                             float* __restrict__ part, int total, int h, int vocab,
+                                                             int segs, int ctiles, int fills) {
+  typedef typename Pack<T, V>::type vec;
+  const int sums = segs * ctiles;
+  const int lane = threadIdx.x & 63;
+  for (int item = blockIdx.x; item < sums + fills; item += gridDim.x) {
+    if (item >= sums) {
+      const int r0 = ((item - sums) * kWaves + (threadIdx.x >> 6)) * kFillRows;
+      const int row = r0 + lane;
+      bool empty = false;
+      if (lane < kFillRows && row < vocab) {
+        int lo = 0, hi = total;                        // first entry whose key is not below `row`
+        while (lo < hi) { const int mid = (lo + hi) >> 1; if (key[mid] < row) lo = mid + 1; else hi = mid; }
+        empty = lo >= total || key[lo] != row;
+      }
+      unsigned long long m = __ballot(empty);
+      while (m) {
+        const int r = r0 + __ffsll(m) - 1;
+        m &= m - 1;
+        for (int c = lane * V; c < h; c += 64 * V) *reinterpret_cast<vec*>(dtable + (int64_t)r * h + c) = vec{};
+      }
+      continue;
+    }
+    const int seg = item / ctiles, c = ((item - seg * ctiles) * kThreads + (int)threadIdx.x) * V;
+    const int e0 = seg * kSeg, e1 = min(e0 + kSeg, total);
+    int k[kSeg + 2];                                   // keys of the entry before, the segment, the entry after; -1: none
+#pragma unroll
+    for (int i = 0; i < kSeg + 2; ++i) {
+      const int e = e0 + i - 1;
+      k[i] = e >= 0 && e < total && e <= e1 ? key[e] : -1;
+    }
+    if (c >= h) continue;
+    vec v[kSeg];
+#pragma unroll
+    for (int i = 0; i < kSeg; ++i) {
+      v[i] = vec{};
+      if (k[i + 1] >= 0 && k[i + 1] < vocab) v[i] = *reinterpret_cast<const vec*>(dy + (int64_t)pos[e0 + i] * h + c);
+    }
+    float acc[V];
+#pragma unroll
+    for (int q = 0; q < V; ++q) acc[q] = 0.f;
+    bool from_before = k[0] == k[1];
+#pragma unroll
+    for (int i = 0; i < kSeg; ++i) {
+      if (k[i + 1] < 0 || k[i + 1] >= vocab) continue;  // past the list, or an image token
+      if constexpr (V == 1) acc[0] += to_f32(v[i]);
+      else {
+#pragma unroll
+        for (int q = 0; q < V; ++q) acc[q] += (float)v[i][q];
+      }
+      if (i + 1 < kSeg && k[i + 2] == k[i + 1]) continue;
+      const bool goes_on = i + 1 == kSeg && k[i + 2] == k[i + 1];
+      if (from_before || goes_on) {
+        float* dst = part + ((int64_t)seg * 2 + (from_before ? 0 : 1)) * h + c;
+#pragma unroll
+        for (int q = 0; q < V; ++q) dst[q] = acc[q];
+      } else {
+        store_row<T, V>(dtable + (int64_t)k[i + 1] * h + c, acc);
+      }
+      from_before = false;
+#pragma unroll
+      for (int q = 0; q < V; ++q) acc[q] = 0.f;
+    }
+  }
+}
+
+// Runs that leave the segment they start in: the first piece plus the head pieces of the
+// segments that follow, each wave a quarter of those in ascending order, the waves added in
+// order.  Item = segment x 64 columns.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void embed_join_kernel(const int32_t* __restrict__ key, const float* __restrict__ part,
+                                                              T* __restrict__ dtable, int total, int h, int vocab, int segs,
+                                                              int ctiles) {
+  __shared__ float red[kWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int item = blockIdx.x; item < segs * ctiles; item += gridDim.x) {
+    const int seg = item / ctiles, c = (item - seg * ctiles) * 64 + lane;
+    const int last = seg * kSeg + kSeg - 1;
+    if (last + 1 >= total) continue;
+    const int id = key[last];
+    if (id >= vocab || key[last + 1] != id) continue;                                   // ends here
+    if (key[seg * kSeg] == id && seg > 0 && key[seg * kSeg - 1] == id) continue;        // started earlier
+    int lo = last + 1, hi = total;                                                      // end of the run
+    while (lo < hi) { const int mid = (lo + hi) >> 1; if (key[mid] == id) lo = mid + 1; else hi = mid; }
+    const int n = (lo - 1) / kSeg - seg;                                                // segments that follow
+    const int per = (n + kWaves - 1) / kWaves;
+    const int s0 = seg + 1 + wave * per, s1 = min(s0 + per, seg + 1 + n);
+    float acc = 0.f;
+    if (c < h) {
+      if (wave == 0) acc = part[((int64_t)seg * 2 + 1) * h + c];
+      int s = s0;
+      for (; s + 8 <= s1; s += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(s + u) * 2 * h + c];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += v[u];
+      }
+      for (; s < s1; ++s) acc += part[(int64_t)s * 2 * h + c];
+    }
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && c < h) {
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) acc += red[w][lane];
+      dtable[(int64_t)id * h + c] = from_f32<T>(acc);
+    }
+    __syncthreads();
+  }
+}
+
+struct EmbedScratch {
+  size_t key[2], pos[2], hist, part, bytes;
+  EmbedScratch(int64_t total, int64_t h) {
+    size_t cur = 0;
+    auto take = [&](size_t n) { const size_t at = cur; cur = align_up(cur + n, 256); return at; };
+    for (int i = 0; i < 2; ++i) { key[i] = take(total * 4); pos[i] = take(total * 4); }
+    hist = take((size_t)ceil_div(total, kChunk) * kBins * 4);
+    part = take((size_t)ceil_div(total, kSeg) * 2 * h * 4);
+    bytes = cur;
+  }
+};
+
+template <typename T, int V>
+mosaic_status embed_grad_t(hipStream_t s, int quota, int B, int N, int n_img, int h, int vocab, const T* dy,
+                           const int32_t* ids, const int32_t* counts, T* dtable, char* scratch) {
+  const int total = B * N;
+  const EmbedScratch sc(total, h);
+  const int chunks = (int)ceil_div(total, kChunk);
+  int32_t* key[2] = {(int32_t*)(scratch + sc.key[0]), (int32_t*)(scratch + sc.key[1])};
+  int32_t* pos[2] = {(int32_t*)(scratch + sc.pos[0]), (int32_t*)(scratch + sc.pos[1])};
+  int* hist = (int*)(scratch + sc.hist);
+  float* part = (float*)(scratch + sc.part);
+  int cur = 1;
+  const int grid = grid_for(quota, 4, chunks);
+  for (int shift = 0; shift == 0 || (shift < 32 && (vocab >> shift) > 0); shift += kDigit) {      // the largest key is `vocab`
+    SortInput in = {shift ? key[cur] : nullptr, shift ? pos[cur] : nullptr, ids, counts, N, n_img, vocab};
+    cur ^= 1;
+    sort_hist_kernel<<<grid, kThreads, 0, s>>>(in, shift, total, chunks, hist);
+    MOSAIC_LAUNCH_CHECK();
+    sort_scatter_kernel<<<grid, kThreads, 0, s>>>(in, shift, total, chunks, hist, key[cur], pos[cur]);
+    MOSAIC_LAUNCH_CHECK();
+  }
+  const int segs = (int)ceil_div(total, kSeg), ctiles = (int)ceil_div(h, kThreads * V);
+  const int fills = (int)ceil_div(vocab, kWaves * kFillRows);
+  const int jtiles = (int)ceil_div(h, 64);
+  if ((int64_t)segs * jtiles + fills > INT32_MAX) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "embedding gradient over %d positions", total);
+  embed_sum_kernel<T, V><<<grid_for(quota, 8, (int64_t)segs * ctiles + fills), kThreads, 0, s>>>(dy, key[cur], pos[cur], dtable, part, total, h,
+                                                                                                vocab, segs, ctiles, fills);
+  MOSAIC_LAUNCH_CHECK();
+  embed_join_kernel<T><<<grid_for(quota, 8, (int64_t)segs * jtiles), kThreads, 0, s>>>(key[cur], part, dtable, total, h, vocab, segs, jtiles);
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
+
+// 16-byte accesses where every row of every tensor starts on a 16-byte boundary (the width is a
+// multiple of 16 bytes in a module); single elements for a caller's tensor that does not
+template <typename T>
+bool wide_rows(int h, const void* a, const void* b, const void* c) {
+  return h % Vec16<T>::N == 0 && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15) == 0;
+}
+
+template <typename T>
+mosaic_status text_stem_fwd_t(hipStream_t s, int quota, int B, int N, int n_img, int h, int vocab, const T* img_tok,
+                              const int32_t* ids, const int32_t* counts, const T* table, T* out) {
+  const int64_t rows = (int64_t)B * N;
+  if (rows == 0 || h == 0) return MOSAIC_OK;
+  const int grid = grid_for(quota, 8, ceil_div(rows, kWaves));
+  if (wide_rows<T>(h, img_tok, table, out))
+    text_stem_fwd_kernel<T, Vec16<T>::N><<<grid, kThreads, 0, s>>>(img_tok, ids, counts, table, out, B, N, n_img, h, vocab);
+  else
+    text_stem_fwd_kernel<T, 1><<<grid, kThreads, 0, s>>>(img_tok, ids, counts, table, out, B, N, n_img, h, vocab);
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
+
+template <typename T>
+mosaic_status text_stem_bwd_t(hipStream_t s, int quota, int B, int N, int n_img, int h, int vocab, const T* dy,
+                              const int32_t* ids, const int32_t* counts, T* d_img, T* dtable, char* scratch) {
+  const bool wide = wide_rows<T>(h, dy, d_img, dtable);
+  if (d_img != nullptr && n_img > 0) {
+    const int grid = grid_for(quota, 8, ceil_div((int64_t)B * n_img, kWaves));
+    if (wide) split_img_kernel<T, Vec16<T>::N><<<grid, kThreads, 0, s>>>(dy, counts, d_img, B, N, n_img, h);
+    else split_img_kernel<T, 1><<<grid, kThreads, 0, s>>>(dy, counts, d_img, B, N, n_img, h);
+    MOSAIC_LAUNCH_CHECK();
+  }
+  if (wide) return embed_grad_t<T, Vec16<T>::N>(s, quota, B, N, n_img, h, vocab, dy, ids, counts, dtable, scratch);
+  return embed_grad_t<T, 1>(s, quota, B, N, n_img, h, vocab, dy, ids, counts, dtable, scratch);
+}
+
+constexpr int kEmbedMaxWidth = 8192;
+
+}  // namespace
+
+size_t text_stem_scratch_bytes(int64_t T, int64_t h) { return EmbedScratch(T, h).bytes; }
+
+mosaic_status launch_text_stem_fwd(hipStream_t s, int quota, int dtype, int B, int N, int n_img, int h, int vocab,
+                                   const void* img_tok, const int32_t* ids, const int32_t* counts, const void* table, void* out) {
+  if (dtype == MOSAIC_BF16)
+    return text_stem_fwd_t<bf16>(s, quota, B, N, n_img, h, vocab, (const bf16*)img_tok, ids, counts, (const bf16*)table, (bf16*)out);
+  return text_stem_fwd_t<float>(s, quota, B, N, n_img, h, vocab, (const float*)img_tok, ids, counts, (const float*)table, (float*)out);
+}
+
+mosaic_status launch_text_stem_bwd(hipStream_t s, int quota, int dtype, int B, int N, int n_img, int h, int vocab,
+                                   const void* dy, const int32_t* ids, const int32_t* counts, void* d_img, void* dtable, void* scratch) {
+  if (h > kEmbedMaxWidth) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "embedding rows of %d elements; the gradient takes up to %d", h, kEmbedMaxWidth);
+  if (dtype == MOSAIC_BF16)
+    return text_stem_bwd_t<bf16>(s, quota, B, N, n_img, h, vocab, (const bf16*)dy, ids, counts, (bf16*)d_img, (bf16*)dtable, (char*)scratch);
+  return text_stem_bwd_t<float>(s, quota, B, N, n_img, h, vocab, (const float*)dy, ids, counts, (float*)d_img, (float*)dtable, (char*)scratch);
+}
