@@ -92,6 +92,19 @@ template <> struct Vec16<bf16> {
   __device__ __forceinline__ void set(int i, float f) { v[i] = (bf16)f; }
 };
 
+// V consecutive elements as one access: 16 bytes, or a single element for rows that do not start
+// on 16-byte boundaries (a caller's tensor may be a slice of a larger buffer).
+template <typename T, int V> struct Pack { typedef T type __attribute__((ext_vector_type(V))); };
+template <typename T> struct Pack<T, 1> { typedef T type; };
+template <typename T, int V> __device__ __forceinline__ float pack_get(const typename Pack<T, V>::type& v, int i) {
+  if constexpr (V == 1) return to_f32(v);
+  else return (float)v[i];
+}
+template <typename T, int V> __device__ __forceinline__ void pack_set(typename Pack<T, V>::type& v, int i, float f) {
+  if constexpr (V == 1) v = from_f32<T>(f);
+  else v[i] = (T)f;
+}
+
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);

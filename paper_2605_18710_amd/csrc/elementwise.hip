@@ -565,37 +565,77 @@ __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(const T* __res
 }
 
 // ------------------------------------------------------------------------------- stems
-// Patch vector index = (c*p + i)*p + j; patches row-major over the image.
-template <typename T>
+// Patch vector index = (c*p + i)*p + j; patches row-major over the image.  Rows are `ld` >= 3*p*p
+// elements apart; what lies between is filled with zeros, so that rows of 588 elements (14 x 14
+// patches) start on 16-byte boundaries and the matrix-core product takes them.  A thread writes one
+// 16-byte piece of a row; its pixels are neighbours, so the 2-byte reads hit the cache.  I: index
+// type (32 bits where they hold every piece: a 64-bit division per element took the 26 us that
+// this pass spent on 16 images of 336 x 336; with it in 32 bits, once per piece, it takes 10).
+template <typename T, typename I>
 __global__ __launch_bounds__(kThreads) void unfold_kernel(const T* __restrict__ img, T* __restrict__ out,
-                                                          int B, int side, int patch) {
-  const int g = side / patch, pd = 3 * patch * patch;
-  const int64_t total = (int64_t)B * g * g * pd;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += (int64_t)gridDim.x * kThreads) {
-    const int e = (int)(i % pd);
-    const int64_t tok = i / pd;
-    const int px = (int)(tok % g), py = (int)((tok / g) % g), b = (int)(tok / ((int64_t)g * g));
-    const int jj = e % patch, ii = (e / patch) % patch, c = e / (patch * patch);
-    out[i] = img[(((int64_t)b * 3 + c) * side + (py * patch + ii)) * side + (px * patch + jj)];
+                                                          int B, int side, int patch, int ld) {
+  constexpr int VN = Vec16<T>::N;
+  const int g = side / patch, pd = 3 * patch * patch, pieces = ld / VN;
+  const I total = (I)B * g * g * pieces;
+  for (I v = (I)blockIdx.x * kThreads + threadIdx.x; v < total; v += (I)gridDim.x * kThreads) {
+    const I tok = v / pieces;
+    int e = (int)(v - tok * pieces) * VN;
+    const I prow = tok / g;
+    const int px = (int)(tok - prow * g), py = (int)(prow % g), b = (int)(prow / g);
+    int c = e / (patch * patch), ij = e - c * patch * patch, i = ij / patch, j = ij - i * patch;
+    Vec16<T> o;
+#pragma unroll
+    for (int k = 0; k < VN; ++k, ++e) {
+      o.set(k, e < pd ? to_f32(img[(((int64_t)b * 3 + c) * side + (py * patch + i)) * side + (px * patch + j)]) : 0.f);
+      if (++j == patch) { j = 0; if (++i == patch) { i = 0; ++c; } }
+    }
+    o.store(out + (int64_t)tok * ld + (int64_t)(v - tok * pieces) * VN);
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void add_pos_kernel(const T* __restrict__ pos, T* __restrict__ y,
-                                                           int B, int N, int h) {
-  const int64_t total = (int64_t)B * N * h, per = (int64_t)N * h;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += (int64_t)gridDim.x * kThreads)
-    y[i] = from_f32<T>(to_f32(y[i]) + to_f32(pos[i % per]));
+// y[b, t, :] += pos[t, :].  Work item = (sample, block of kThreads pieces of the N x h table): one
+// division per item.  V elements per access: 16 bytes, or one for tensors that are not 16-byte aligned.
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void add_pos_kernel(const T* __restrict__ pos, T* __restrict__ y, int B, int64_t per, int blocks) {
+  typedef typename Pack<T, V>::type vec;
+  for (int64_t it = blockIdx.x; it < (int64_t)B * blocks; it += gridDim.x) {
+    const int64_t b = it / blocks, i = ((it - b * blocks) * kThreads + threadIdx.x) * V;
+    if (i >= per) continue;
+    const vec p = *reinterpret_cast<const vec*>(pos + i);
+    vec v = *reinterpret_cast<const vec*>(y + b * per + i);
+#pragma unroll
+    for (int k = 0; k < V; ++k) pack_set<T, V>(v, k, pack_get<T, V>(v, k) + pack_get<T, V>(p, k));
+    *reinterpret_cast<vec*>(y + b * per + i) = v;
+  }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void pos_grad_kernel(const T* __restrict__ dy, T* __restrict__ dpos,
-                                                            int B, int N, int h) {
-  const int64_t per = (int64_t)N * h;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < per; i += (int64_t)gridDim.x * kThreads) {
-    float acc = 0.f;
-    for (int b = 0; b < B; ++b) acc += to_f32(dy[(int64_t)b * per + i]);
-    dpos[i] = from_f32<T>(acc);
+// dpos[t, :] = sum over samples in ascending order; four samples' pieces are requested together
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void pos_grad_kernel(const T* __restrict__ dy, T* __restrict__ dpos, int B, int64_t per) {
+  typedef typename Pack<T, V>::type vec;
+  for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * V; i < per; i += (int64_t)gridDim.x * kThreads * V) {
+    float acc[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) acc[k] = 0.f;
+    int b = 0;
+    for (; b + 4 <= B; b += 4) {
+      vec v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const vec*>(dy + (int64_t)(b + u) * per + i);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int k = 0; k < V; ++k) acc[k] += pack_get<T, V>(v[u], k);
+    }
+    for (; b < B; ++b) {
+      const vec v = *reinterpret_cast<const vec*>(dy + (int64_t)b * per + i);
+#pragma unroll
+      for (int k = 0; k < V; ++k) acc[k] += pack_get<T, V>(v, k);
+    }
+    vec o = {};
+#pragma unroll
+    for (int k = 0; k < V; ++k) pack_set<T, V>(o, k, acc[k]);
+    *reinterpret_cast<vec*>(dpos + i) = o;
   }
 }
 
@@ -869,34 +909,54 @@ mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_
   return MOSAIC_OK;
 }
 
-#define EW_LAUNCH(KERNEL, total, ...)                                                        \
-  do {                                                                                       \
-    if ((total) == 0) return MOSAIC_OK;                                                      \
-    const int grid = grid_for(quota, 8, ceil_div((total), kThreads));                        \
-    if (dtype == MOSAIC_BF16) KERNEL<bf16><<<grid, kThreads, 0, s>>> __VA_ARGS__(bf16);      \
-    else KERNEL<float><<<grid, kThreads, 0, s>>> __VA_ARGS__(float);                         \
-    MOSAIC_LAUNCH_CHECK();                                                                   \
-    return MOSAIC_OK;                                                                        \
-  } while (0)
+// 16-byte accesses where every row of both tensors starts on a 16-byte boundary
+static inline bool wide_access(int64_t n, int dtype, const void* a, const void* b) {
+  return n % (dtype == MOSAIC_BF16 ? 8 : 4) == 0 && (((uintptr_t)a | (uintptr_t)b) & 15) == 0;
+}
 
-mosaic_status launch_unfold(hipStream_t s, int quota, int dtype, int B, int side, int patch, const void* img, void* out) {
+mosaic_status launch_unfold(hipStream_t s, int quota, int dtype, int B, int side, int patch, const void* img, void* out, int ld) {
   if (patch <= 0 || side % patch) MOSAIC_FAIL(MOSAIC_EINVAL, "image side %d is not a multiple of patch %d", side, patch);
-  const int64_t total = (int64_t)B * 3 * side * side;
-#define ARGS(TT) ((const TT*)img, (TT*)out, B, side, patch)
-  EW_LAUNCH(unfold_kernel, total, ARGS);
-#undef ARGS
+  const int vn = dtype == MOSAIC_BF16 ? 8 : 4;
+  if (ld < 3 * patch * patch || ld % vn || ((uintptr_t)out & 15)) MOSAIC_FAIL(MOSAIC_EINVAL, "patch rows must start on 16-byte boundaries");
+  const int64_t g = side / patch, pieces = (int64_t)B * g * g * (ld / vn);
+  if (pieces == 0) return MOSAIC_OK;
+  const int grid = grid_for(quota, 8, ceil_div(pieces, kThreads));
+  const bool small = pieces + (int64_t)grid * kThreads < INT32_MAX;
+#define UNFOLD(TT, II) unfold_kernel<TT, II><<<grid, kThreads, 0, s>>>((const TT*)img, (TT*)out, B, side, patch, ld)
+  if (dtype == MOSAIC_BF16) { if (small) UNFOLD(bf16, int32_t); else UNFOLD(bf16, int64_t); }
+  else { if (small) UNFOLD(float, int32_t); else UNFOLD(float, int64_t); }
+#undef UNFOLD
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
+
+template <typename T, int V>
+static void add_pos_t(hipStream_t s, int quota, int B, int64_t per, const void* pos, void* y) {
+  const int blocks = (int)ceil_div(per, (int64_t)kThreads * V);
+  add_pos_kernel<T, V><<<grid_for(quota, 8, (int64_t)B * blocks), kThreads, 0, s>>>((const T*)pos, (T*)y, B, per, blocks);
 }
 
 mosaic_status launch_add_pos(hipStream_t s, int quota, int dtype, int B, int N, int h, const void* pos, void* y) {
-  const int64_t total = (int64_t)B * N * h;
-#define ARGS(TT) ((const TT*)pos, (TT*)y, B, N, h)
-  EW_LAUNCH(add_pos_kernel, total, ARGS);
-#undef ARGS
+  const int64_t per = (int64_t)N * h;
+  if (per == 0 || B == 0) return MOSAIC_OK;
+  const bool wide = wide_access(per, dtype, pos, y);
+  if (dtype == MOSAIC_BF16) { if (wide) add_pos_t<bf16, 8>(s, quota, B, per, pos, y); else add_pos_t<bf16, 1>(s, quota, B, per, pos, y); }
+  else { if (wide) add_pos_t<float, 4>(s, quota, B, per, pos, y); else add_pos_t<float, 1>(s, quota, B, per, pos, y); }
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
+
+template <typename T, int V>
+static void pos_grad_t(hipStream_t s, int quota, int B, int64_t per, const void* dy, void* dpos) {
+  pos_grad_kernel<T, V><<<grid_for(quota, 8, ceil_div(per, (int64_t)kThreads * V)), kThreads, 0, s>>>((const T*)dy, (T*)dpos, B, per);
 }
 
 mosaic_status launch_pos_grad(hipStream_t s, int quota, int dtype, int B, int N, int h, const void* dy, void* dpos) {
-  const int64_t total = (int64_t)N * h;
-#define ARGS(TT) ((const TT*)dy, (TT*)dpos, B, N, h)
-  EW_LAUNCH(pos_grad_kernel, total, ARGS);
-#undef ARGS
+  const int64_t per = (int64_t)N * h;
+  if (per == 0) return MOSAIC_OK;
+  const bool wide = wide_access(per, dtype, dy, dpos);
+  if (dtype == MOSAIC_BF16) { if (wide) pos_grad_t<bf16, 8>(s, quota, B, per, dy, dpos); else pos_grad_t<bf16, 1>(s, quota, B, per, dy, dpos); }
+  else { if (wide) pos_grad_t<float, 4>(s, quota, B, per, dy, dpos); else pos_grad_t<float, 1>(s, quota, B, per, dy, dpos); }
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
 }

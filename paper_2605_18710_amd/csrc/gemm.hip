@@ -1421,19 +1421,20 @@ size_t gemm_splitk_scratch_bytes(int64_t M, int64_t N, int64_t K) {
 static mosaic_status launch_gemm_impl(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int64_t M, int64_t N,
                           int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
                           int64_t ldc, const void* bias, const void* R, void* splitk_scratch,
-                          int act, void* C2, int64_t ldc2, bool* fused) {
+                          int64_t b_rows, int act, void* C2, int64_t ldc2, bool* fused) {
   if (fused) *fused = false;
+  if (b_rows < 0 || b_kc) b_rows = K;
   if (M < 0 || N < 0 || K < 0) MOSAIC_FAIL(MOSAIC_EINVAL, "negative GEMM size");
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "GEMM dimension too large");
   if (M == 0 || N == 0) return MOSAIC_OK;
   const bool vec_ok = (lda % 8 == 0) && (ldb % 8 == 0) && (K % 8 == 0 || (!a_kc && !b_kc)) &&
-                      (a_kc || M % 8 == 0) && (b_kc || N % 8 == 0) &&
+                      (a_kc || M % 8 == 0 || lda >= ceil_div(M, 8) * 8) && (b_kc || N % 8 == 0) &&
                       ((uintptr_t)A % 16 == 0) && ((uintptr_t)B % 16 == 0) && ((uintptr_t)C % 16 == 0) &&
                       (ldc % 8 == 0) && (N % 8 == 0) && K > 0 &&
                       (R == nullptr || (uintptr_t)R % 16 == 0) && (bias == nullptr || (uintptr_t)bias % 16 == 0);
   // extents in bytes as seen by the buffer descriptors (dense rows: ld >= logical width)
-  const int64_t a_ext = a_kc ? ((M - 1) * lda + K) * 2 : ((K - 1) * lda + M) * 2;
-  const int64_t b_ext = b_kc ? ((N - 1) * ldb + K) * 2 : ((K - 1) * ldb + N) * 2;
+  const int64_t a_ext = a_kc ? ((M - 1) * lda + K) * 2 : ((K - 1) * lda + std::min(ceil_div(M, 8) * 8, lda)) * 2;
+  const int64_t b_ext = b_kc ? ((N - 1) * ldb + K) * 2 : ((b_rows - 1) * ldb + N) * 2;
   const int64_t c_ext = ((M - 1) * ldc + N) * 2;
   const int64_t lim = (int64_t)1 << 31;
   if (dtype == MOSAIC_BF16 && vec_ok && a_ext < lim && b_ext < lim && c_ext < lim) {
@@ -1466,18 +1467,18 @@ static mosaic_status launch_gemm_impl(hipStream_t s, int quota, int dtype, bool 
   const int grid = grid_for(quota, 8, (int64_t)tiles_m * tiles_n);
   if (dtype == MOSAIC_BF16)
     gemm_generic_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)A, (const bf16*)B, (bf16*)C, (const bf16*)bias,
-                                                   (const bf16*)R, (int)M, (int)N, (int)K, sam, sak, sbk, sbn, ldc, tiles_m, tiles_n);
+                                                   (const bf16*)R, (int)M, (int)N, (int)b_rows, sam, sak, sbk, sbn, ldc, tiles_m, tiles_n);
   else
     gemm_generic_kernel<float><<<grid, 256, 0, s>>>((const float*)A, (const float*)B, (float*)C, (const float*)bias,
-                                                    (const float*)R, (int)M, (int)N, (int)K, sam, sak, sbk, sbn, ldc, tiles_m, tiles_n);
+                                                    (const float*)R, (int)M, (int)N, (int)b_rows, sam, sak, sbk, sbn, ldc, tiles_m, tiles_n);
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;
 }
 
 mosaic_status launch_gemm(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int64_t M, int64_t N,
                           int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
-                          int64_t ldc, const void* bias, const void* R, void* splitk_scratch) {
-  return launch_gemm_impl(s, quota, dtype, a_kc, b_kc, M, N, K, A, lda, B, ldb, C, ldc, bias, R, splitk_scratch, 0, nullptr, 0, nullptr);
+                          int64_t ldc, const void* bias, const void* R, void* splitk_scratch, int64_t b_rows) {
+  return launch_gemm_impl(s, quota, dtype, a_kc, b_kc, M, N, K, A, lda, B, ldb, C, ldc, bias, R, splitk_scratch, b_rows, 0, nullptr, 0, nullptr);
 }
 
 mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act, int64_t T, int64_t k, int64_t n,
@@ -1486,7 +1487,7 @@ mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act
   if (act == MOSAIC_SWIGLU && (n % 2)) MOSAIC_FAIL(MOSAIC_EINVAL, "SwiGLU needs an even output width, got %lld", (long long)n);
   const int64_t na = act == MOSAIC_SWIGLU ? n / 2 : n;
   bool fused = false;
-  MOSAIC_TRY(launch_gemm_impl(s, quota, dtype, true, false, T, n, k, X, k, W, n, Z, n, bias, nullptr, nullptr, act, Aout, na,
+  MOSAIC_TRY(launch_gemm_impl(s, quota, dtype, true, false, T, n, k, X, k, W, n, Z, n, bias, nullptr, nullptr, -1, act, Aout, na,
                               act == MOSAIC_GELU_TANH ? nullptr : &fused));
   if (fused || T == 0 || n == 0) return MOSAIC_OK;
   if (act == MOSAIC_SWIGLU) return launch_swiglu_fwd(s, quota, dtype, T, na, Z, Aout);

@@ -13,7 +13,10 @@
 mosaic_status launch_gemm(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc,
                           int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
                           const void* B, int64_t ldb, void* C, int64_t ldc,
-                          const void* bias, const void* R, void* splitk_scratch = nullptr);
+                          const void* bias, const void* R, void* splitk_scratch = nullptr, int64_t b_rows = -1);
+// Padded rows: with lda >= M rounded up to 8, a K-strided A may have any M (its rows must be
+// readable up to that width).  b_rows >= 0: a K-strided B has only that many of its K rows; the
+// columns of A past them must hold zeros.
 // Z[T,n] = X[T,k] W[k,n] (+ bias[n]) and A = act(Z): GELU / tanh GELU give A[T,n]; SwiGLU reads Z
 // as [gate | up] halves and gives A[T,n/2] = silu(gate) * up.  Where the bf16 matrix-core kernel
 // takes the product, the activation is applied in its epilogue (same bits as the separate pass);
@@ -86,8 +89,9 @@ mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int6
                             const void* X, void* out, void* scratch);
 
 // ----------------------------------------------------------------------------- stems
+// rows of `out` are ld elements apart (whole 16-byte pieces), zeros past 3*patch*patch
 mosaic_status launch_unfold(hipStream_t s, int quota, int dtype, int B, int side, int patch,
-                            const void* img, void* out);
+                            const void* img, void* out, int ld);
 // y[b*N+t, :] += pos[t, :]
 mosaic_status launch_add_pos(hipStream_t s, int quota, int dtype, int B, int N, int h,
                              const void* pos, void* y);

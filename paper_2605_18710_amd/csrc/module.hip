@@ -130,6 +130,10 @@ inline int64_t qkv_width(const mosaic_module_desc& d) {
 }
 inline int kv_heads_of(const mosaic_module_desc& d) { return d.kv_heads > 0 ? d.kv_heads : d.heads; }
 
+// distance between unfolded patches: whole 16-byte pieces, so that the matrix-core product takes
+// patches of 588 elements too (14 x 14); tokens that the caller brings (patch = 0) are dense
+inline int64_t patch_ld(const mosaic_module_desc& d) { return d.patch > 0 ? ceil_div(d.in_dim, 8) * 8 : d.in_dim; }
+
 void build_layout(mosaic_module* m) {
   const mosaic_module_desc& d = m->d;
   const int64_t T = m->T, h = d.hidden, f = d.mlp;
@@ -218,7 +222,7 @@ void build_layout(mosaic_module* m) {
     q.b_1 = add_tensor(m, "b_stem", 1, h);
     q.w_2 = add_tensor(m, "pos", d.seq, h);
     m->lp.push_back(q);
-    m->s_patches = take(&cur, T * d.in_dim * es);
+    m->s_patches = take(&cur, T * patch_ld(d) * es);
     m->s_colsum = take(&cur, colsum_scratch_bytes(h));
     m->s_splitk = take(&cur, gemm_splitk_scratch_bytes(d.in_dim, h, T));
   } else if (d.kind == MOSAIC_CONV_STEM) {
@@ -386,10 +390,11 @@ mosaic_status patch_stem_forward(mosaic_module* m, hipStream_t s, int q, const v
   const void* tokens = x;
   if (d.patch > 0) {
     const int side = (int)lround(sqrt((double)d.seq)) * d.patch;
-    MOSAIC_TRY(launch_unfold(s, q, d.dtype, d.batch, side, d.patch, x, W(m, m->s_patches)));
+    MOSAIC_TRY(launch_unfold(s, q, d.dtype, d.batch, side, d.patch, x, W(m, m->s_patches), (int)patch_ld(d)));
     tokens = W(m, m->s_patches);
   }
-  MOSAIC_TRY(launch_gemm(s, q, d.dtype, true, false, m->T, d.hidden, d.in_dim, tokens, d.in_dim, P(m, p.w_1), d.hidden, y, d.hidden, P(m, p.b_1), nullptr));
+  MOSAIC_TRY(launch_gemm(s, q, d.dtype, true, false, m->T, d.hidden, patch_ld(d), tokens, patch_ld(d), P(m, p.w_1), d.hidden, y, d.hidden, P(m, p.b_1), nullptr,
+                         nullptr, d.in_dim));
   MOSAIC_TRY(launch_add_pos(s, q, d.dtype, d.batch, d.seq, d.hidden, P(m, p.w_2), y));
   return MOSAIC_OK;
 }
@@ -399,7 +404,7 @@ mosaic_status patch_stem_backward(mosaic_module* m, hipStream_t s, int q, const 
   const LayerParams& p = m->lp[0];
   if (dx) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "the patch stem has no input gradient");
   const void* tokens = d.patch > 0 ? W(m, m->s_patches) : m->last_x;
-  MOSAIC_TRY(launch_gemm(s, q, d.dtype, false, false, d.in_dim, d.hidden, m->T, tokens, d.in_dim, dy, d.hidden, G(m, p.w_1), d.hidden, nullptr, nullptr, W(m, m->s_splitk)));
+  MOSAIC_TRY(launch_gemm(s, q, d.dtype, false, false, d.in_dim, d.hidden, m->T, tokens, patch_ld(d), dy, d.hidden, G(m, p.w_1), d.hidden, nullptr, nullptr, W(m, m->s_splitk)));
   MOSAIC_TRY(launch_colsum(s, q, d.dtype, m->T, d.hidden, dy, G(m, p.b_1), W(m, m->s_colsum)));
   MOSAIC_TRY(launch_pos_grad(s, q, d.dtype, d.batch, d.seq, d.hidden, dy, G(m, p.w_2)));
   return MOSAIC_OK;

@@ -24,11 +24,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 
-// V consecutive elements as one access: 16 bytes, or a single element for rows that do not
-// start on 16-byte boundaries (a caller's tensor may be a slice of a larger buffer)
-template <typename T, int V> struct Pack { typedef T type __attribute__((ext_vector_type(V))); };
-template <typename T> struct Pack<T, 1> { typedef T type; };
-
 // Token ids and image-token counts.  Without per-sample counts every sample has n_img image
 // tokens and ids holds the N - n_img text ids of a sample, [B, N - n_img].  With counts
 // (int32 [B], clamped to [0, n_img]) sample b takes its first counts[b] image tokens and ids
@@ -194,12 +189,9 @@ constexpr int kFillRows = 16;    // table rows a wave looks up and, where nobody
 
 template <typename T, int V>
 __device__ __forceinline__ void store_row(T* dst, const float* acc) {
-  typename Pack<T, V>::type o;
-  if constexpr (V == 1) o = from_f32<T>(acc[0]);
-  else {
+  typename Pack<T, V>::type o = {};
 #pragma unroll
-    for (int k = 0; k < V; ++k) o[k] = from_f32<T>(acc[k]);
-  }
+  for (int k = 0; k < V; ++k) pack_set<T, V>(o, k, acc[k]);
   *reinterpret_cast<typename Pack<T, V>::type*>(dst) = o;
 }
 
@@ -254,11 +246,8 @@ __global__ __launch_bounds__(kThreads) void embed_sum_kernel(const T* __restrict
 #pragma unroll
     for (int i = 0; i < kSeg; ++i) {
       if (k[i + 1] < 0 || k[i + 1] >= vocab) continue;  // past the list, or an image token
-      if constexpr (V == 1) acc[0] += to_f32(v[i]);
-      else {
 #pragma unroll
-        for (int q = 0; q < V; ++q) acc[q] += (float)v[i][q];
-      }
+      for (int q = 0; q < V; ++q) acc[q] += pack_get<T, V>(v[i], q);
       if (i + 1 < kSeg && k[i + 2] == k[i + 1]) continue;
       const bool goes_on = i + 1 == kSeg && k[i + 2] == k[i + 1];
       if (from_before || goes_on) {
