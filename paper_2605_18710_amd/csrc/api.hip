@@ -1,16 +1,14 @@
 // C-ABI wrappers of the single operations, and the dispatch between the MFMA attention
-// kernels and the plain FMA ones.
+// kernels for bf16 and the fp32 ones.
 #include <mutex>
 #include "kernels.h"
 
-mosaic_status launch_attention_fwd_simple(hipStream_t s, int quota, int dtype, int B, int N, int H, int Hkv, int d,
+mosaic_status launch_attention_fwd_f32(hipStream_t s, int quota, int dtype, int B, int N, int H, int Hkv, int d,
                                           int causal, const void* qkv, void* O, float* lse);
-mosaic_status launch_attention_bwd_simple(hipStream_t s, int quota, int dtype, int B, int N, int H, int Hkv, int d,
+mosaic_status launch_attention_bwd_f32(hipStream_t s, int quota, int dtype, int B, int N, int H, int Hkv, int d,
                                           int causal, const void* qkv, const void* O, const float* lse,
                                           const void* dO, void* dqkv, float* delta);
 
-mosaic_status launch_attention_delta(hipStream_t s, int quota, int dtype, int B, int N, int H, int d,
-                                     const void* O, const void* dO, float* delta);
 bool attention_mfma_supported(int dtype, int d);
 mosaic_status launch_attention_fwd_mfma(hipStream_t s, int quota, int B, int N, int H, int Hkv, int d, int causal,
                                         const void* qkv, void* O, float* lse);
@@ -21,8 +19,8 @@ mosaic_status launch_attention_bwd_mfma(hipStream_t s, int quota, int B, int N, 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // The MFMA kernels address one sample's packed q|k|v rows with 32-bit byte offsets (buffer
-// descriptors); a tile may start up to 63 rows past the end.  Longer slices take the plain
-// kernels, which index with 64 bits.
+// descriptors); a tile may start up to 63 rows past the end.  Longer slices take the
+// fp32 kernels, which index with 64 bits.
 static bool attn_slice_fits32(int N, int H, int Hkv, int d) {
   return ((int64_t)N + 64) * ((int64_t)H + 2 * Hkv) * d * 2 < ((int64_t)1 << 32);
 }
@@ -39,7 +37,7 @@ mosaic_status launch_attention_fwd(hipStream_t s, int quota, int dtype, int B, i
   MOSAIC_TRY(check_attn(B, N, H, Hkv, d));
   if (attention_mfma_supported(dtype, d) && attn_slice_fits32(N, H, Hkv, d) && aligned16(qkv) && aligned16(O))
     return launch_attention_fwd_mfma(s, quota, B, N, H, Hkv, d, causal, qkv, O, lse);
-  return launch_attention_fwd_simple(s, quota, dtype, B, N, H, Hkv, d, causal, qkv, O, lse);
+  return launch_attention_fwd_f32(s, quota, dtype, B, N, H, Hkv, d, causal, qkv, O, lse);
 }
 
 mosaic_status launch_attention_bwd(hipStream_t s, int quota, int dtype, int B, int N, int H, int Hkv, int d, int causal,
@@ -49,7 +47,7 @@ mosaic_status launch_attention_bwd(hipStream_t s, int quota, int dtype, int B, i
   if (attention_mfma_supported(dtype, d) && attn_slice_fits32(N, H, Hkv, d) && aligned16(qkv) && aligned16(O) && aligned16(dO) && aligned16(dqkv)) {
     return launch_attention_bwd_mfma(s, quota, B, N, H, Hkv, d, causal, qkv, O, lse, dO, dqkv, delta);
   }
-  return launch_attention_bwd_simple(s, quota, dtype, B, N, H, Hkv, d, causal, qkv, O, lse, dO, dqkv, delta);
+  return launch_attention_bwd_f32(s, quota, dtype, B, N, H, Hkv, d, causal, qkv, O, lse, dO, dqkv, delta);
 }
 
 static mosaic_status check_common(int32_t quota, int32_t dtype) {

@@ -1,0 +1,409 @@
+// Attention with fp32 arithmetic, any head size up to 128: the fp32 path, and bf16 head sizes and
+// tensors that the bf16 matrix-core kernels do not cover.
+//
+// v_mfma_f32_16x16x4_f32, one wave per workgroup and 16 owned rows per wave, no LDS and no
+// barriers: scores are formed so that a lane owns one column (lane%16) and four rows (4*(lane/16)+e),
+// which is exactly the layout in which the next product wants them as its second operand
+// (contraction index e-th instruction: row 4*(lane/16)+e), so probabilities go from one product to
+// the next in registers, and row maxima and sums are four values plus two exchanges.
+// Forward and dQ own 16 queries and stream keys; dK/dV owns 16 keys and streams queries, for every
+// query head of its group in turn.  Every sum has one owner and a fixed order, without atomics.
+// P is recomputed from the saved row log-sum-exp; D_i = sum_c dO_ic O_ic is formed by the dQ
+// kernel, which runs first, and read by the dK/dV kernel.
+//
+// What bounds it: the fp32 workloads have few rows (2 x 128 tokens x 4 heads = 64 waves), so a
+// kernel is one chain of load latency, products and softmax per streamed block.  The streamed
+// rows of the next block are requested before the current block's products, and the second
+// reading of the block's rows (in the other orientation) is in flight under them.  At B2 N128 H4
+// d32: forward 29 -> 9 us, dQ 25 -> 9, dK/dV 41 -> 10 against workgroups of 16 rows that formed
+// each score by scalar FMA over LDS (launches of 4.5 us included).
+#include <algorithm>
+#include "kernels.h"
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+__device__ __forceinline__ f32x4 mfma4(f32x4 a, f32x4 b, f32x4 c) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+  return c;
+}
+
+// columns c .. c+3 of a row of d; zero past the end and for rows that do not exist
+template <typename T, bool VEC>
+__device__ __forceinline__ f32x4 cols4(const T* row, int c, int d, bool live) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (!live) return v;
+  if constexpr (VEC) {
+    typedef T vec __attribute__((ext_vector_type(4)));
+    if (c < d) {
+      const vec x = *reinterpret_cast<const vec*>(row + c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = (float)x[e];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) if (c + e < d) v[e] = to_f32(row[c + e]);
+  }
+  return v;
+}
+template <typename T, bool VEC>
+__device__ __forceinline__ void put4(T* row, int c, int d, f32x4 v) {
+  if constexpr (VEC) {
+    typedef T vec __attribute__((ext_vector_type(4)));
+    if (c < d) {
+      vec o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (T)v[e];
+      *reinterpret_cast<vec*>(row + c) = o;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) if (c + e < d) row[c + e] = from_f32<T>(v[e]);
+  }
+}
+// DB blocks of 16 columns of one row: lane group g holds columns 16s + 4g .. +3
+template <typename T, int DB, bool VEC>
+__device__ __forceinline__ void row_frag(f32x4 (&f)[DB], const T* row, int g, int d, bool live) {
+#pragma unroll
+  for (int s = 0; s < DB; ++s) f[s] = cols4<T, VEC>(row, 16 * s + 4 * g, d, live);
+}
+// the other orientation: column 16s + lane%16 of rows r0 + 4g + e
+template <typename T, int DB>
+__device__ __forceinline__ void col_frag(f32x4 (&f)[DB], const T* base, int64_t rs, int r0, int N, int lr, int g, int d) {
+#pragma unroll
+  for (int s = 0; s < DB; ++s)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = r0 + 4 * g + e, c = 16 * s + lr;
+      f[s][e] = (r < N && c < d) ? to_f32(base[(int64_t)r * rs + c]) : 0.f;
+    }
+}
+__device__ __forceinline__ float groups_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, 64)); return fmaxf(v, __shfl_xor(v, 32, 64)); }
+__device__ __forceinline__ float groups_sum(float v) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); }
+
+// streamed blocks of 16 rows per step: two at small head sizes, where their fragments leave room
+template <int DB> constexpr int kBlocks = DB <= 2 ? 2 : 1;
+
+struct AttnArgs {
+  int B, N, H, Hkv, d, causal;
+  float scale;
+  int tiles;                 // tiles of 16 rows
+};
+
+template <typename T, int DB, bool VEC>
+__global__ __launch_bounds__(64) void attn_fwd_f32(const T* __restrict__ qkv, T* __restrict__ O, float* __restrict__ lse, AttnArgs p) {
+  constexpr int KB = kBlocks<DB>;
+  const int lr = threadIdx.x & 15, g = threadIdx.x >> 4;
+  // rows are [q (H heads) | k (Hkv heads) | v (Hkv heads)]; query head t uses key/value head t / (H/Hkv)
+  const int N = p.N, d = p.d, GQ = p.H / p.Hkv;
+  const int64_t rs = (int64_t)(p.H + 2 * p.Hkv) * d;
+  const int64_t items = (int64_t)p.B * p.H * p.tiles;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int64_t hb = item / p.tiles;
+    // the last tile of a causal row is the longest: it starts first
+    const int qt = p.causal ? p.tiles - 1 - (int)(item - hb * p.tiles) : (int)(item - hb * p.tiles);
+    const int hd = (int)(hb % p.H);
+    const int64_t b = hb / p.H;
+    const T* rowb = qkv + b * N * rs;
+    const T* kb_ = rowb + (int64_t)p.H * d + (hd / GQ) * d;
+    const T* vb_ = kb_ + (int64_t)p.Hkv * d;
+    const int i = qt * 16 + lr;
+    f32x4 qf[DB], kf[KB][DB], o[DB];
+    row_frag<T, DB, VEC>(qf, rowb + (int64_t)i * rs + hd * d, g, d, i < N);
+#pragma unroll
+    for (int s = 0; s < DB; ++s) o[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    const int kv_end = p.causal ? min(N, qt * 16 + 16) : N;
+    auto k_rows = [&](int j0) {
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        const int j = j0 + 16 * u + lr;
+        row_frag<T, DB, VEC>(kf[u], kb_ + (int64_t)j * rs, g, d, j < kv_end);
+      }
+    };
+    k_rows(0);
+    for (int j0 = 0; j0 < kv_end; j0 += 16 * KB) {
+      f32x4 vt[KB][DB], sc[KB];
+#pragma unroll
+      for (int u = 0; u < KB; ++u) col_frag<T, DB>(vt[u], vb_, rs, j0 + 16 * u, kv_end, lr, g, d);
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        sc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < DB; ++s) sc[u] = mfma4(kf[u][s], qf[s], sc[u]);
+      }
+      if (j0 + 16 * KB < kv_end) k_rows(j0 + 16 * KB);
+      float mx = -INFINITY;
+#pragma unroll
+      for (int u = 0; u < KB; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = j0 + 16 * u + 4 * g + e;
+          sc[u][e] = (j >= N || (p.causal && j > i)) ? -INFINITY : sc[u][e] * p.scale;
+          mx = fmaxf(mx, sc[u][e]);
+        }
+      const float mn = fmaxf(m, groups_max(mx));
+      // a row that has seen no unmasked key yet keeps m = -inf; exp(-inf - -inf) is avoided
+      const float corr = (m == -INFINITY) ? 0.f : expf(m - mn);
+      float ps = 0.f;
+#pragma unroll
+      for (int u = 0; u < KB; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sc[u][e] = (sc[u][e] == -INFINITY) ? 0.f : expf(sc[u][e] - mn);
+          ps += sc[u][e];
+        }
+      l = l * corr + ps;
+      m = mn;
+#pragma unroll
+      for (int s = 0; s < DB; ++s) {
+        o[s] *= corr;
+#pragma unroll
+        for (int u = 0; u < KB; ++u) o[s] = mfma4(vt[u][s], sc[u], o[s]);
+      }
+    }
+    l = groups_sum(l);                       // every lane group has summed its own keys
+    if (i < N) {
+      const float inv = 1.0f / l;
+      T* row = O + (b * N + i) * (int64_t)p.H * d + hd * d;
+#pragma unroll
+      for (int s = 0; s < DB; ++s) put4<T, VEC>(row, 16 * s + 4 * g, d, o[s] * inv);
+      if (g == 0) lse[hb * N + i] = m + logf(l);
+    }
+  }
+}
+
+template <typename T, int DB, bool VEC>
+__global__ __launch_bounds__(64) void attn_bwd_dq_f32(const T* __restrict__ qkv, const T* __restrict__ O, const T* __restrict__ dO,
+                                                      const float* __restrict__ lse, float* __restrict__ delta,
+                                                      T* __restrict__ dqkv, AttnArgs p) {
+  constexpr int KB = kBlocks<DB>;
+  const int lr = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int N = p.N, d = p.d, GQ = p.H / p.Hkv;
+  const int64_t rs = (int64_t)(p.H + 2 * p.Hkv) * d, h = (int64_t)p.H * d;
+  const int64_t items = (int64_t)p.B * p.H * p.tiles;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int64_t hb = item / p.tiles;
+    const int qt = p.causal ? p.tiles - 1 - (int)(item - hb * p.tiles) : (int)(item - hb * p.tiles);
+    const int hd = (int)(hb % p.H);
+    const int64_t b = hb / p.H;
+    const T* rowb = qkv + b * N * rs;
+    const T* kb_ = rowb + h + (hd / GQ) * d;
+    const T* vb_ = kb_ + (int64_t)p.Hkv * d;
+    const int i = qt * 16 + lr;
+    f32x4 qf[DB], dof[DB], kf[KB][DB], vf[KB][DB], dq[DB];
+    row_frag<T, DB, VEC>(qf, rowb + (int64_t)i * rs + hd * d, g, d, i < N);
+    row_frag<T, DB, VEC>(dof, dO + (b * N + i) * h + hd * d, g, d, i < N);
+    float dl = 0.f;
+    {
+      f32x4 of[DB];
+      row_frag<T, DB, VEC>(of, O + (b * N + i) * h + hd * d, g, d, i < N);
+#pragma unroll
+      for (int s = 0; s < DB; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dl = fmaf(dof[s][e], of[s][e], dl);
+    }
+    dl = groups_sum(dl);
+    if (i < N && g == 0) delta[hb * N + i] = dl;
+    const float li = i < N ? lse[hb * N + i] : 0.f;
+#pragma unroll
+    for (int s = 0; s < DB; ++s) dq[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int kv_end = p.causal ? min(N, qt * 16 + 16) : N;
+    auto kv_rows = [&](int j0) {
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        const int j = j0 + 16 * u + lr;
+        row_frag<T, DB, VEC>(kf[u], kb_ + (int64_t)j * rs, g, d, j < kv_end);
+        row_frag<T, DB, VEC>(vf[u], vb_ + (int64_t)j * rs, g, d, j < kv_end);
+      }
+    };
+    kv_rows(0);
+    for (int j0 = 0; j0 < kv_end; j0 += 16 * KB) {
+      f32x4 kt[KB][DB], sc[KB], dp[KB];
+#pragma unroll
+      for (int u = 0; u < KB; ++u) col_frag<T, DB>(kt[u], kb_, rs, j0 + 16 * u, kv_end, lr, g, d);
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        sc[u] = f32x4{0.f, 0.f, 0.f, 0.f}; dp[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < DB; ++s) { sc[u] = mfma4(kf[u][s], qf[s], sc[u]); dp[u] = mfma4(vf[u][s], dof[s], dp[u]); }
+      }
+      if (j0 + 16 * KB < kv_end) kv_rows(j0 + 16 * KB);
+#pragma unroll
+      for (int u = 0; u < KB; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = j0 + 16 * u + 4 * g + e;
+          const bool masked = i >= N || j >= N || (p.causal && j > i);
+          sc[u][e] = masked ? 0.f : expf(sc[u][e] * p.scale - li) * (dp[u][e] - dl);
+        }
+#pragma unroll
+      for (int s = 0; s < DB; ++s)
+#pragma unroll
+        for (int u = 0; u < KB; ++u) dq[s] = mfma4(kt[u][s], sc[u], dq[s]);
+    }
+    if (i < N) {
+      T* row = dqkv + (b * N + i) * rs + hd * d;
+#pragma unroll
+      for (int s = 0; s < DB; ++s) put4<T, VEC>(row, 16 * s + 4 * g, d, dq[s] * p.scale);
+    }
+  }
+}
+
+template <typename T, int DB, bool VEC>
+__global__ __launch_bounds__(64) void attn_bwd_dkv_f32(const T* __restrict__ qkv, const T* __restrict__ dO, const float* __restrict__ lse,
+                                                       const float* __restrict__ delta, T* __restrict__ dqkv, AttnArgs p) {
+  constexpr int QB = kBlocks<DB>;
+  const int lr = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int N = p.N, d = p.d, GQ = p.H / p.Hkv;
+  const int64_t rs = (int64_t)(p.H + 2 * p.Hkv) * d, h = (int64_t)p.H * d;
+  const int64_t items = (int64_t)p.B * p.Hkv * p.tiles;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int64_t hb = item / p.tiles;
+    const int kt = (int)(item - hb * p.tiles);             // the first tile of a causal row has the most queries
+    const int kvh = (int)(hb % p.Hkv);
+    const int64_t b = hb / p.Hkv;
+    const T* rowb = qkv + b * N * rs;
+    const int j = kt * 16 + lr;
+    f32x4 kf[DB], vf[DB], dk[DB], dv[DB];
+    row_frag<T, DB, VEC>(kf, rowb + (int64_t)j * rs + h + kvh * d, g, d, j < N);
+    row_frag<T, DB, VEC>(vf, rowb + (int64_t)j * rs + h + (int64_t)(p.Hkv + kvh) * d, g, d, j < N);
+#pragma unroll
+    for (int s = 0; s < DB; ++s) { dk[s] = f32x4{0.f, 0.f, 0.f, 0.f}; dv[s] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    const int i_begin = p.causal ? kt * 16 : 0;
+    // every query head of the group in turn, query blocks ascending inside a head
+    for (int hd = kvh * GQ; hd < (kvh + 1) * GQ; ++hd) {
+      const T* qb_ = rowb + hd * d;
+      const T* db_ = dO + b * N * h + hd * d;
+      const float* lse_ = lse + (b * p.H + hd) * N;
+      const float* del_ = delta + (b * p.H + hd) * N;
+      f32x4 qf[QB][DB], of[QB][DB];
+      auto q_rows = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < QB; ++u) {
+          const int i = i0 + 16 * u + lr;
+          row_frag<T, DB, VEC>(qf[u], qb_ + (int64_t)i * rs, g, d, i < N);
+          row_frag<T, DB, VEC>(of[u], db_ + (int64_t)i * h, g, d, i < N);
+        }
+      };
+      q_rows(i_begin);
+      for (int i0 = i_begin; i0 < N; i0 += 16 * QB) {
+        f32x4 qt[QB][DB], ot[QB][DB], sc[QB], dp[QB], li[QB], dl[QB];
+#pragma unroll
+        for (int u = 0; u < QB; ++u) {
+          col_frag<T, DB>(ot[u], db_, h, i0 + 16 * u, N, lr, g, d);
+          col_frag<T, DB>(qt[u], qb_, rs, i0 + 16 * u, N, lr, g, d);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int i = i0 + 16 * u + 4 * g + e;
+            li[u][e] = i < N ? lse_[i] : 0.f;
+            dl[u][e] = i < N ? del_[i] : 0.f;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < QB; ++u) {
+          sc[u] = f32x4{0.f, 0.f, 0.f, 0.f}; dp[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s = 0; s < DB; ++s) { sc[u] = mfma4(qf[u][s], kf[s], sc[u]); dp[u] = mfma4(of[u][s], vf[s], dp[u]); }
+        }
+        if (i0 + 16 * QB < N) q_rows(i0 + 16 * QB);
+#pragma unroll
+        for (int u = 0; u < QB; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int i = i0 + 16 * u + 4 * g + e;
+            const bool masked = i >= N || j >= N || (p.causal && j > i);
+            sc[u][e] = masked ? 0.f : expf(sc[u][e] * p.scale - li[u][e]);
+            dp[u][e] = sc[u][e] * (dp[u][e] - dl[u][e]);
+          }
+#pragma unroll
+        for (int s = 0; s < DB; ++s)
+#pragma unroll
+          for (int u = 0; u < QB; ++u) { dv[s] = mfma4(ot[u][s], sc[u], dv[s]); dk[s] = mfma4(qt[u][s], dp[u], dk[s]); }
+      }
+    }
+    if (j < N) {
+      T* row = dqkv + (b * N + j) * rs + h + kvh * d;
+#pragma unroll
+      for (int s = 0; s < DB; ++s) {
+        put4<T, VEC>(row, 16 * s + 4 * g, d, dk[s] * p.scale);
+        put4<T, VEC>(row + (int64_t)p.Hkv * d, 16 * s + 4 * g, d, dv[s]);
+      }
+    }
+  }
+}
+
+// four columns per access where every head of every row starts on such a boundary
+template <typename T>
+bool four_columns(int d, const void* a, const void* b, const void* c, const void* e) {
+  return d % 4 == 0 && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)e) & (4 * sizeof(T) - 1)) == 0;
+}
+
+template <typename T, int DB, bool VEC>
+mosaic_status fwd_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv, void* O, float* lse) {
+  const int grid = grid_for(quota, 8, (int64_t)p.B * p.H * p.tiles);
+  attn_fwd_f32<T, DB, VEC><<<grid, 64, 0, s>>>((const T*)qkv, (T*)O, lse, p);
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
+
+template <typename T, int DB, bool VEC>
+mosaic_status bwd_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv, const void* O, const float* lse, const void* dO,
+                    void* dqkv, float* delta) {
+  attn_bwd_dq_f32<T, DB, VEC><<<grid_for(quota, 8, (int64_t)p.B * p.H * p.tiles), 64, 0, s>>>((const T*)qkv, (const T*)O, (const T*)dO, lse,
+                                                                                            delta, (T*)dqkv, p);
+  MOSAIC_LAUNCH_CHECK();
+  attn_bwd_dkv_f32<T, DB, VEC><<<grid_for(quota, 8, (int64_t)p.B * p.Hkv * p.tiles), 64, 0, s>>>((const T*)qkv, (const T*)dO, lse, delta,
+                                                                                               (T*)dqkv, p);
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
+
+// column blocks of 16 that a head needs, rounded up to an instantiated count
+#define WITH_BLOCKS(CALL)                       \
+  if (p.d <= 16) return CALL(1);                \
+  if (p.d <= 32) return CALL(2);                \
+  if (p.d <= 64) return CALL(4);                \
+  return CALL(8)
+
+template <typename T, bool VEC>
+mosaic_status fwd_d(hipStream_t s, int quota, const AttnArgs& p, const void* qkv, void* O, float* lse) {
+#define CALL(DB) (fwd_t<T, DB, VEC>(s, quota, p, qkv, O, lse))
+  WITH_BLOCKS(CALL);
+#undef CALL
+}
+
+template <typename T, bool VEC>
+mosaic_status bwd_d(hipStream_t s, int quota, const AttnArgs& p, const void* qkv, const void* O, const float* lse, const void* dO,
+                    void* dqkv, float* delta) {
+#define CALL(DB) (bwd_t<T, DB, VEC>(s, quota, p, qkv, O, lse, dO, dqkv, delta))
+  WITH_BLOCKS(CALL);
+#undef CALL
+}
+
+AttnArgs attn_args(int B, int N, int H, int Hkv, int d, int causal) {
+  return {B, N, H, Hkv, d, causal, 1.0f / sqrtf((float)d), (int)ceil_div(N, 16)};
+}
+
+}  // namespace
+
+mosaic_status launch_attention_fwd_f32(hipStream_t s, int quota, int dtype, int B, int N, int H, int Hkv, int d,
+                                       int causal, const void* qkv, void* O, float* lse) {
+  const AttnArgs p = attn_args(B, N, H, Hkv, d, causal);
+  if (dtype == MOSAIC_BF16)
+    return four_columns<bf16>(d, qkv, O, O, O) ? fwd_d<bf16, true>(s, quota, p, qkv, O, lse) : fwd_d<bf16, false>(s, quota, p, qkv, O, lse);
+  return four_columns<float>(d, qkv, O, O, O) ? fwd_d<float, true>(s, quota, p, qkv, O, lse) : fwd_d<float, false>(s, quota, p, qkv, O, lse);
+}
+
+mosaic_status launch_attention_bwd_f32(hipStream_t s, int quota, int dtype, int B, int N, int H, int Hkv, int d,
+                                       int causal, const void* qkv, const void* O, const float* lse,
+                                       const void* dO, void* dqkv, float* delta) {
+  const AttnArgs p = attn_args(B, N, H, Hkv, d, causal);
+  if (dtype == MOSAIC_BF16)
+    return four_columns<bf16>(d, qkv, O, dO, dqkv) ? bwd_d<bf16, true>(s, quota, p, qkv, O, lse, dO, dqkv, delta)
+                                                   : bwd_d<bf16, false>(s, quota, p, qkv, O, lse, dO, dqkv, delta);
+  return four_columns<float>(d, qkv, O, dO, dqkv) ? bwd_d<float, true>(s, quota, p, qkv, O, lse, dO, dqkv, delta)
+                                                  : bwd_d<float, false>(s, quota, p, qkv, O, lse, dO, dqkv, delta);
+}

@@ -35,8 +35,7 @@
 //   * tiles are handed out so that the workgroups running on one XCD at the same time
 //     form a 4 x 8 patch of the tile grid and share operand panels in that XCD's L2.
 //
-// fp32 path (and shapes the MFMA path does not cover): a plain LDS-tiled FMA kernel with
-// arbitrary strides; ascending-k accumulation as well.
+// fp32 path, and shapes these kernels do not cover: gemm_f32.hip.
 #include <stdlib.h>
 #include <algorithm>
 #include <mutex>
@@ -1113,72 +1112,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   }
 }
 
-// ------------------------------------------------------------------ generic FMA kernel
-template <typename T>
-__global__ __launch_bounds__(256) void gemm_generic_kernel(
-    const T* __restrict__ A, const T* __restrict__ B, T* __restrict__ C, const T* __restrict__ bias,
-    const T* __restrict__ R, int M, int N, int K, int64_t sam, int64_t sak, int64_t sbk, int64_t sbn,
-    int64_t ldc, int tiles_m, int tiles_n) {
-  constexpr int TS = 64, KS = 16;
-  __shared__ float As[KS][TS + 1];
-  __shared__ float Bs[KS][TS + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int ntiles = tiles_m * tiles_n;
-  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int tn_i = tile / tiles_m, tm_i = tile - tn_i * tiles_m;
-    const int m0 = tm_i * TS, n0 = tn_i * TS;
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-    for (int k0 = 0; k0 < K; k0 += KS) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int idx = threadIdx.x + 256 * q;     // 0..1023
-        // A tile: prefer the contiguous index to vary fastest across threads
-        int am, ak;
-        if (sak == 1) { ak = idx % KS; am = idx / KS; } else { am = idx % TS; ak = idx / TS; }
-        const int gm = m0 + am, gk = k0 + ak;
-        As[ak][am] = (gm < M && gk < K) ? to_f32(A[(int64_t)gm * sam + (int64_t)gk * sak]) : 0.f;
-        int bn, bk;
-        if (sbk == 1) { bk = idx % KS; bn = idx / KS; } else { bn = idx % TS; bk = idx / TS; }
-        const int gn = n0 + bn, gk2 = k0 + bk;
-        Bs[bk][bn] = (gn < N && gk2 < K) ? to_f32(B[(int64_t)gk2 * sbk + (int64_t)gn * sbn]) : 0.f;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < KS; ++k) {
-        float a[4], b[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-      }
-      __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = m0 + ty * 4 + i;
-      if (row >= M) continue;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int col = n0 + tx * 4 + j;
-        if (col >= N) continue;
-        float v = acc[i][j];
-        if (bias) v += to_f32(bias[col]);
-        if (R) v += to_f32(R[(int64_t)row * ldc + col]);
-        C[(int64_t)row * ldc + col] = from_f32<T>(v);
-      }
-    }
-  }
-}
-
-
 // One launch of the MFMA kernel over coarse tiles [tile_begin, tile_begin + tile_count) of the
 // panel-major list of (sub*BM) x (sub*BN) tiles; tile_count < 0 means all of them.
 template <int BM, int BN, int NWM, int NWN, bool A_KC, bool B_KC, bool SPLITK = false, int ACT = ACT_NONE>
@@ -1409,6 +1342,10 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
 
 }  // namespace
 
+// gemm_f32.hip
+mosaic_status launch_gemm_f32(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int M, int N, int K, const void* A,
+                              int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, const void* bias, const void* R);
+
 size_t gemm_splitk_scratch_bytes(int64_t M, int64_t N, int64_t K) {
   int first = 0;
   const int sk = splitk_plan(M, N, K, &first);
@@ -1461,18 +1398,7 @@ static mosaic_status launch_gemm_impl(hipStream_t s, int quota, int dtype, bool 
     if (!a_kc && !b_kc) return launch_mfma_shape<false, false>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb, splitk_scratch);
     return launch_mfma_shape<false, true>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb, splitk_scratch);
   }
-  const int64_t sam = a_kc ? lda : 1, sak = a_kc ? 1 : lda;
-  const int64_t sbk = b_kc ? 1 : ldb, sbn = b_kc ? ldb : 1;
-  const int tiles_m = (int)ceil_div(M, 64), tiles_n = (int)ceil_div(N, 64);
-  const int grid = grid_for(quota, 8, (int64_t)tiles_m * tiles_n);
-  if (dtype == MOSAIC_BF16)
-    gemm_generic_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)A, (const bf16*)B, (bf16*)C, (const bf16*)bias,
-                                                   (const bf16*)R, (int)M, (int)N, (int)b_rows, sam, sak, sbk, sbn, ldc, tiles_m, tiles_n);
-  else
-    gemm_generic_kernel<float><<<grid, 256, 0, s>>>((const float*)A, (const float*)B, (float*)C, (const float*)bias,
-                                                    (const float*)R, (int)M, (int)N, (int)b_rows, sam, sak, sbk, sbn, ldc, tiles_m, tiles_n);
-  MOSAIC_LAUNCH_CHECK();
-  return MOSAIC_OK;
+  return launch_gemm_f32(s, quota, dtype, a_kc, b_kc, (int)M, (int)N, (int)b_rows, A, lda, B, ldb, C, ldc, bias, R);
 }
 
 mosaic_status launch_gemm(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int64_t M, int64_t N,

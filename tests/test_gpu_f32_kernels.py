@@ -1,0 +1,84 @@
+"""fp32 contractions and attention at the sizes where their tiles can go wrong: one row, one past a
+block of 16, a tile of 32 or 64 and a K-tile of 64, products on both sides of the tile rule (512 tiles of
+64 x 64), widths that allow no 4-element access, every head-size class, grouped heads, bf16
+shapes that the bf16 kernels do not take, tensors off a 16-byte boundary."""
+import numpy as np
+import pytest
+
+from oracle import layers as O
+from paper_2605_18710_amd import synth
+from helpers import quantize, to_dev, from_dev, assert_close
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def mb():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_18710_amd import binding
+    binding.lib()
+    return binding
+
+
+def off(a, dtype, offset):
+    t = to_dev(a, dtype)
+    out = torch.empty(t.numel() + offset, dtype=t.dtype, device="cuda")
+    out[offset:] = t.reshape(-1)
+    return out[offset:].view(t.shape)
+
+
+def bits(t):
+    return t.view(torch.uint8)
+
+
+@pytest.mark.parametrize("dtype,T,k,n,offset", [
+    ("f32", 1, 4, 4, 0), ("f32", 33, 64, 32, 0), ("f32", 32, 68, 36, 0), ("f32", 65, 128, 100, 0), ("f32", 7, 5, 3, 0),
+    ("f32", 31, 63, 65, 0), ("f32", 40, 32, 32, 1), ("f32", 1408, 60, 1472, 0), ("f32", 1408, 60, 1476, 0), ("f32", 2, 1500, 8, 0),
+    ("bf16", 33, 12, 20, 0), ("bf16", 65, 30, 7, 0), ("bf16", 64, 64, 64, 1), ("bf16", 100, 588, 36, 0)])
+def test_linear(mb, dtype, T, k, n, offset):
+    s = 6100 + T + k + n
+    X, W, b, R, dY = [quantize(synth.normal(s + i, sh, 0, sd), dtype) for i, (sh, sd) in
+                      enumerate([((T, k), 1), ((k, n), 0.05), ((n,), 0.1), ((T, n), 1), ((T, n), 1)])]
+    X_, W_, b_, R_, dY_ = [off(a, dtype, offset) for a in (X, W, b, R, dY)]
+    Rx = quantize(synth.normal(s + 9, (T, k)), dtype)
+    Rx_ = off(Rx, dtype, offset)
+    outs = []
+    for q in (256, 24):
+        Y, dX, dW, db = [off(np.full(sh, np.nan), dtype, offset) for sh in ((T, n), (T, k), (k, n), (n,))]
+        sc = torch.empty(max(16, mb.linear_wgrad_scratch_bytes(T, k, n)), dtype=torch.uint8, device="cuda")
+        mb.op_linear_fwd(None, q, dtype, T, k, n, X_, W_, b_, R_, Y)
+        mb.op_linear_dgrad(None, q, dtype, T, k, n, dY_, W_, Rx_, dX)
+        mb.op_linear_wgrad(None, q, dtype, T, k, n, X_, dY_, dW, None, sc)
+        torch.cuda.synchronize()
+        outs.append((Y, dX, dW))
+    dx_ref, dw_ref, _ = O.linear_bwd(X, W, dY)
+    assert_close(from_dev(Y), O.linear_fwd(X, W, b) + R, dtype, "Y")
+    assert_close(from_dev(dX), dx_ref + Rx, dtype, "dX")
+    assert_close(from_dev(dW), dw_ref, dtype, "dW")
+    assert all(torch.equal(bits(a), bits(c)) for a, c in zip(*outs))
+
+
+@pytest.mark.parametrize("dtype,B,N,H,Hkv,d,causal,offset", [
+    ("f32", 1, 1, 1, 1, 4, 1, 0), ("f32", 2, 16, 2, 1, 16, 1, 0), ("f32", 1, 17, 4, 2, 20, 0, 0), ("f32", 2, 33, 2, 2, 32, 1, 0),
+    ("f32", 1, 100, 6, 2, 64, 0, 0), ("f32", 1, 65, 2, 2, 128, 1, 0), ("f32", 2, 31, 3, 1, 5, 0, 0), ("f32", 1, 48, 2, 2, 80, 1, 0),
+    ("f32", 1, 40, 2, 1, 32, 1, 1), ("bf16", 2, 50, 4, 2, 32, 1, 0), ("bf16", 1, 37, 2, 2, 80, 0, 0), ("bf16", 1, 37, 2, 2, 13, 1, 0),
+    ("bf16", 1, 64, 2, 2, 64, 1, 1)])
+def test_attention(mb, dtype, B, N, H, Hkv, d, causal, offset):
+    w, s = (H + 2 * Hkv) * d, 6300 + N + d
+    qkv, dO = quantize(synth.normal(s, (B * N, w)), dtype), quantize(synth.normal(s + 1, (B * N, H * d)), dtype)
+    qkv_, dO_ = off(qkv, dtype, offset), off(dO, dtype, offset)
+    outs = []
+    for q in (256, 24):
+        Oo, dq = off(np.full((B * N, H * d), np.nan), dtype, offset), off(np.full((B * N, w), np.nan), dtype, offset)
+        lse, delta = [torch.full((B, H, N), float("nan"), device="cuda") for _ in range(2)]
+        mb.op_attention_gqa_fwd(None, q, dtype, B, N, H, Hkv, d, causal, qkv_, Oo, lse)
+        mb.op_attention_gqa_bwd(None, q, dtype, B, N, H, Hkv, d, causal, qkv_, Oo, lse, dO_, dq, delta)
+        torch.cuda.synchronize()
+        outs.append((Oo, lse, dq))
+    assert_close(from_dev(Oo), O.attention_fwd(qkv, B, N, H, causal, Hkv), dtype, "O", roundings=2)
+    assert_close(from_dev(lse), O.attention_lse(qkv, B, N, H, causal, Hkv), "f32", "lse", roundings=4)
+    if N > 1:          # over one key dS vanishes: only its rounding would be compared
+        assert_close(from_dev(dq), O.attention_bwd(qkv, dO, B, N, H, causal, Hkv), dtype, "dqkv", roundings=8)
+    assert all(torch.equal(bits(a), bits(c)) for a, c in zip(*outs))
