@@ -755,7 +755,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
         for (int g = 0; g < 4; ++g) {
           bf16x4 o;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (bf16)swiglu_f(zval(i, 0, g, e), zval(i, 1, g, e));
+          for (int e = 0; e < 4; ++e) o[e] = (bf16)swiglu_f<bf16>(zval(i, 0, g, e), zval(i, 1, g, e));
           *reinterpret_cast<bf16x4*>(patch + wr + ((g ^ wsx) << 4)) = o;
         }
       } else {
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
           for (int g = 0; g < 4; ++g) {
             bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)gelu_f(zval(i, j, g, e));
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)gelu_f<bf16>(zval(i, j, g, e));
             *reinterpret_cast<bf16x4*>(patch + wr + (((4 * j + g) ^ wsx) << 4)) = o;
           }
       }
