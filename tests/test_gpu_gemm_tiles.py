@@ -1,0 +1,57 @@
+"""Small products: 128 x 128 tiles take 64-deep K-tiles where every workgroup has a CU to itself and
+32-deep ones otherwise; the bits must not show which.  Contractions around one and two K-tiles and around the
+ring of stages, ragged in all dimensions, all three forms, bias, residual and activations."""
+import numpy as np
+import pytest
+
+from oracle import layers as O
+from paper_2605_18710_amd import synth
+from helpers import quantize, to_dev, from_dev, assert_close
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def mb():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_18710_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("T,k,n", [(130, 8, 128), (40, 56, 264), (257, 64, 136), (129, 72, 8), (300, 128, 520), (1, 320, 256),
+                                   (190, 384, 200), (136, 1000, 392), (1568, 776, 768)])
+def test_k_tile_depths_agree(mb, T, k, n):
+    s = 7000 + T + k + n
+    X, W, b, R, dY = [quantize(synth.normal(s + i, sh, 0, sd), "bf16") for i, (sh, sd) in
+                      enumerate([((T, k), 1), ((k, n), 0.05), ((n,), 0.1), ((T, n), 1), ((T, n), 1)])]
+    X_, W_, b_, R_, dY_ = [to_dev(a, "bf16") for a in (X, W, b, R, dY)]
+    outs = []
+    for q in (256, 1):                    # one workgroup per CU; more tiles than slots
+        e = lambda *sh: torch.full(sh, float("nan"), dtype=torch.bfloat16, device="cuda")
+        Y, Z, A, dX, dW = e(T, n), e(T, n), e(T, n), e(T, k), e(k, n)
+        sc = torch.empty(max(16, mb.linear_wgrad_scratch_bytes(T, k, n)), dtype=torch.uint8, device="cuda")
+        mb.op_linear_fwd(None, q, "bf16", T, k, n, X_, W_, b_, R_, Y)
+        mb.op_linear_act_fwd(None, q, "bf16", mb.GELU, T, k, n, X_, W_, b_, Z, A)
+        mb.op_linear_dgrad(None, q, "bf16", T, k, n, dY_, W_, None, dX)
+        mb.op_linear_wgrad(None, q, "bf16", T, k, n, X_, dY_, dW, None, sc)
+        got = [Y, Z, A, dX] + [dW]
+        if n % 256 == 0:
+            G, S = e(T, n), e(T, n // 2)
+            mb.op_linear_act_fwd(None, q, "bf16", mb.SWIGLU, T, k, n, X_, W_, None, G, S)
+            got += [G, S]
+        torch.cuda.synchronize()
+        outs.append(got)
+    z_ref = O.linear_fwd(X, W, b)
+    dx_ref, dw_ref, _ = O.linear_bwd(X, W, dY)
+    assert_close(from_dev(Y), z_ref + R, "bf16", "Y")
+    assert_close(from_dev(A), O.gelu(from_dev(Z)), "bf16", "A")
+    assert_close(from_dev(dX), dx_ref, "bf16", "dX")
+    assert_close(from_dev(dW), dw_ref, "bf16", "dW")
+    if n % 256 == 0:
+        g = from_dev(G)
+        assert_close(g, O.linear_fwd(X, W), "bf16", "gate | up")
+        assert_close(from_dev(S), O.swiglu_fwd(g[:, :n // 2], g[:, n // 2:]), "bf16", "swiglu")
+    assert all(torch.equal(a.view(torch.int16), c.view(torch.int16)) for a, c in zip(*outs))
