@@ -67,6 +67,10 @@ typedef __attribute__((ext_vector_type(4))) int i32x4;
 constexpr int NS = 5;             // LDS stages
 constexpr int AHEAD = 4;          // K-tiles between the load cursor and the compute cursor
 
+// position of 16-byte chunk c of row r of a K-contiguous tile: c ^ kc_swizzle(r); 16 lanes that
+// read one chunk of 16 consecutive rows touch every bank once
+template <int BKT> __device__ __forceinline__ int kc_swizzle(int r) { return BKT == 64 ? (r >> 1) & 7 : (r >> 2) & 3; }
+
 // Requests one operand tile (ROWS x BKT) from HBM straight into an LDS stage: every wave
 // instruction moves 64 x 16 bytes to 1 KB of consecutive LDS; which 16 bytes of the tile a
 // lane asks for is free, and that choice realises the swizzle.
@@ -79,10 +83,6 @@ constexpr int AHEAD = 4;          // K-tiles between the load cursor and the com
 // group c/2 of the gate half (c even) or of the up half (c odd), counted from column x0/2,
 // so that a wave's two 32-column accumulator blocks hold a gate column and its up column
 // in the same lane and register.
-// position of 16-byte chunk c of row r of a K-contiguous tile: c ^ kc_swizzle(r); 16 lanes that
-// read one chunk of 16 consecutive rows touch every bank once
-template <int BKT> __device__ __forceinline__ int kc_swizzle(int r) { return BKT == 64 ? (r >> 1) & 7 : (r >> 2) & 3; }
-
 template <int ROWS, bool KC, int NWAVES, bool GU = false, int BKT = BK>
 struct DmaLoader {
   static constexpr int NI = ROWS * BKT / 512 / NWAVES;     // wave instructions per wave and K-tile
@@ -1099,24 +1099,34 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kc4w_kernel(
 }
 
 // out = bf16( P[0] + P[1] + ... ) in ascending piece order, for the tiles [tile_begin,
-// tile_begin + tile_count) of the 256x256 tile list that the split launch covered.  One block
-// iteration takes four rows of one tile (256 float4), so the tile's place is found once per
-// iteration.
+// tile_begin + tile_count) of the TE x TE tile list that the split launch covered.  One block
+// iteration takes 256 float4 of one tile (1024 / TE rows), so the tile's place is found once per
+// iteration.  Four pieces are requested together.
+template <int TE>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ P, bf16* __restrict__ C,
                                                             int M, int N, int64_t ldc, int ksplit, int tiles_m,
                                                             int tiles_n, int tile_begin, int tile_count, int row_block) {
-  const int64_t piece = (int64_t)tile_count * 65536;
-  const int units = tile_count * 64;
+  constexpr int ROWS = 1024 / TE, PER = TE / ROWS;      // rows of an iteration, iterations of a tile
+  const int64_t piece = (int64_t)tile_count * (TE * TE);
+  const int units = tile_count * PER;
   for (int u = blockIdx.x; u < units; u += gridDim.x) {
-    const int tl = u >> 6;
+    const int tl = u / PER;
     int trow, tcol;
     tile_coords(tile_begin + tl, tiles_m, tiles_n, row_block, &trow, &tcol);
-    const int r = (u & 63) * 4 + (threadIdx.x >> 6), c = (threadIdx.x & 63) * 4;
-    const int row = trow * 256 + r, col = tcol * 256 + c;
+    const int r = (u % PER) * ROWS + threadIdx.x / (TE / 4), c = (threadIdx.x % (TE / 4)) * 4;
+    const int row = trow * TE + r, col = tcol * TE + c;
     if (row >= M || col >= N) continue;
-    const float* src = P + (int64_t)tl * 65536 + r * 256 + c;
+    const float* src = P + (int64_t)tl * (TE * TE) + r * TE + c;
     float4 a = *reinterpret_cast<const float4*>(src);
-    for (int s = 1; s < ksplit; ++s) {
+    int s = 1;
+    for (; s + 4 <= ksplit; s += 4) {
+      float4 b[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b[q] = *reinterpret_cast<const float4*>(src + (s + q) * piece);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { a.x += b[q].x; a.y += b[q].y; a.z += b[q].z; a.w += b[q].w; }
+    }
+    for (; s < ksplit; ++s) {
       const float4 b = *reinterpret_cast<const float4*>(src + s * piece);
       a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
     }
@@ -1172,9 +1182,9 @@ mosaic_status launch_mfma(hipStream_t s, int quota, int M, int N, int K, const b
                                           tiles_m, tiles_n, tile_begin, tile_count, sub, ksplit, ktiles_per, P, tq, ka);
   MOSAIC_LAUNCH_CHECK();
   if (SPLITK) {
-    static_assert(!SPLITK || (BM == 256 && BN == 256), "the reduce kernel walks 256x256 tiles");
-    const int g2 = grid_for(quota, 8, (int64_t)tile_count * 64);
-    splitk_reduce_kernel<<<g2, 256, 0, s>>>(P, C, M, N, ldc, ksplit, tiles_m, tiles_n, tile_begin, tile_count, ka.row_block);
+    static_assert(BM == BN, "the reduce kernel walks square tiles");
+    const int g2 = grid_for(quota, 8, (int64_t)tile_count * (BM * BM / 1024));
+    splitk_reduce_kernel<BM><<<g2, 256, 0, s>>>(P, C, M, N, ldc, ksplit, tiles_m, tiles_n, tile_begin, tile_count, ka.row_block);
     MOSAIC_LAUNCH_CHECK();
   }
   return MOSAIC_OK;
@@ -1281,6 +1291,34 @@ int splitk_plan(int64_t M, int64_t N, int64_t K, int* first) {
   return best;
 }
 
+// How a weight gradient of up to 128 tiles of 256x256 that has scratch for `reserved` pieces of
+// each is computed: *te = edge of the tiles, returns the piece count (1: not cut).  A function
+// of the shape alone.  Besides cutting the 256x256 tiles into `reserved` pieces there are 128x128 tiles,
+// one per CU with 64-deep K-tiles, in as many pieces as still fit one round of 256 (never more
+// scratch than reserved).  They need fewer or no pieces for the same number of busy CUs: a piece costs
+// its fp32 store and the reduce pass its reading.  Prices in microseconds on the whole device, fitted to
+// the products below: nanoseconds per unit of K of a tile, growing with the share of CUs at
+// work (the board's power is shared); 5 for launch, fill and drain; a reduce pass 4 and its bytes at
+// 4.5 TB/s.  The small tiles have to be priced 8 % lower, because on a share of the CUs, where
+// tiles queue up, they are less efficient.  Measured on 256 CUs (on 64): 256x256 cut -> plan
+//   9216 x 1024 x 4096  80 -> 72 us (185 -> 156), 256 tiles, not cut;   8192 x 2048 x 2048  74 -> 65 (169 -> 140)
+//   9216 x 1024 x 1024  36 -> 28 (59 -> 70), 64 tiles in 4 pieces;   24000 x 240 x 1280  61 -> 29 (61 -> 67)
+//   5000 x 1024 x 3072  46 -> 36 (101 -> 88);   12000 x 1280 x 1280  stays, 50 (130): small tiles 48 (152)
+//   12000 x 1280 x 3840  stays, 109: 300 small tiles, uncut, take 154
+int wgrad_tiles(int64_t M, int64_t N, int64_t K, int reserved, int* te) {
+  const double k = (double)K, t256 = (double)(ceil_div(M, 256) * ceil_div(N, 256)), t128 = (double)(ceil_div(M, 128) * ceil_div(N, 128));
+  const double reduce_us = 4.0, bytes_us = (double)M * (double)N * 4.0 / 4.5e6, n = t256 * reserved;
+  const double large = (n > 256 ? 2.0 : 1.0) * (k / reserved * (12.0 + 11.5 * std::min(1.0, n / 256)) * 1e-3 + 5.0) + 5.0 + reduce_us + reserved * bytes_us;
+  double best = 0.92 * large;
+  *te = 256;
+  int pieces = reserved;
+  for (int s = 1; s <= reserved && t128 * s <= 256 && t128 * s <= 4 * n; ++s) {
+    const double us = k / s * (5.7 + 1.7 * t128 * s / 256) * 1e-3 + 5.0 + (s > 1 ? reduce_us + s * bytes_us : 0.0);
+    if (us < best) { best = us; pieces = s; *te = 128; }
+  }
+  return pieces;
+}
+
 template <bool A_KC, bool B_KC>
 mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, const bf16* A, int64_t lda,
                                 const bf16* B, int64_t ldb, bf16* C, int64_t ldc, const bf16* bias, const bf16* R,
@@ -1293,6 +1331,13 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
   int sk = 1, split_first = 0;
   if constexpr (!A_KC && !B_KC) {
     if (splitk_scratch && !bias && !R) sk = splitk_plan(M, N, K, &split_first);
+    if (sk > 1 && split_first == 0) {
+      int te;
+      sk = wgrad_tiles(M, N, K, sk, &te);
+      if (te == 128 && sk > 1)
+        return launch_mfma<128, 128, 2, 2, A_KC, B_KC, true, ACT_NONE, 64>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes,
+                                                                          sk, (int)ceil_div(ceil_div(K, 64), sk), (float*)splitk_scratch);
+    }
   }
   auto launch_split = [&]() -> mosaic_status {
     const int per = (int)ceil_div(ceil_div(K, BK), sk);

@@ -55,3 +55,29 @@ def test_k_tile_depths_agree(mb, T, k, n):
         assert_close(g, O.linear_fwd(X, W), "bf16", "gate | up")
         assert_close(from_dev(S), O.swiglu_fwd(g[:, :n // 2], g[:, n // 2:]), "bf16", "swiglu")
     assert all(torch.equal(a.view(torch.int16), c.view(torch.int16)) for a, c in zip(*outs))
+
+
+@pytest.mark.parametrize("T,k,n,note", [
+    (2048, 264, 1032, "3 x 9 small tiles in pieces, ragged tile row and column"),
+    (2056, 128, 128, "one tile, pieces of 5 and fewer K-tiles of 64, the last one short"),
+    (4096, 1024, 2048, "128 small tiles in 2 pieces"),
+    (9216, 1024, 4096, "256 small tiles, scratch reserved and not used"),
+    (9216, 600, 1024, "patch embedding shape: 40 tiles in 6 pieces"),
+    (12000, 1280, 1280, "large tiles stay cut"),
+])
+def test_weight_gradient_of_few_tiles(mb, T, k, n, note):
+    """Tile size and pieces follow the shape: same bits at every quota, every column against the checker."""
+    X, dY = quantize(synth.normal(7300, (T, k)), "bf16"), quantize(synth.normal(7301, (T, n)), "bf16")
+    X_, dY_ = to_dev(X, "bf16"), to_dev(dY, "bf16")
+    nbytes = mb.linear_wgrad_scratch_bytes(T, k, n)
+    assert nbytes > mb.colsum_scratch_bytes(n), "this shape has scratch for pieces"
+    outs = []
+    for q in (256, 200, 64, 8):
+        ws = torch.full((nbytes + 4096,), 255, dtype=torch.uint8, device="cuda")        # NaN: nothing may be read before it is written
+        dW = torch.full((k, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+        mb.op_linear_wgrad(None, q, "bf16", T, k, n, X_, dY_, dW, None, ws)
+        torch.cuda.synchronize()
+        assert bool((ws[nbytes:] == 255).all()), "written past the scratch"
+        outs.append(dW)
+    assert_close(from_dev(outs[0]), X.T @ dY, "bf16", note)
+    assert all(torch.equal(o.view(torch.int16), outs[0].view(torch.int16)) for o in outs[1:]), note
