@@ -2,10 +2,11 @@
 //
 // bf16 path: persistent MFMA kernels.  gemm_bf16_kernel serves every form: a workgroup of 8
 // waves (256x256 tile, 128x64 per wave) or 4 waves (128x128 tile, 64x64 per wave) walks
-// output tiles; gemm_bf16_kc4w_kernel (described at its definition) takes the whole 256x256
-// tiles of the form with both operands K-contiguous.  In both,
+// output tiles; gemm_bf16_w4_kernel (described at its definition) takes the 256x256 tiles of
+// every product whose K-contiguous operands are whole 64-deep K-tiles long.  In both,
 // the grid is sized to the module's CU quota.  Each output element is produced by exactly
-// one wave that accumulates k in ascending order with v_mfma_f32_32x32x16_bf16, so the
+// one wave that accumulates k in ascending order (v_mfma_f32_32x32x16_bf16 twice or
+// v_mfma_f32_16x16x32_bf16 once per 32 k-values: the same bits), so the
 // bits of the result do not depend on the grid, the tile shape, the tile order or the CU.
 //
 // Data movement (gemm_bf16_kernel)
@@ -896,205 +897,353 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
   if (threadIdx.x == 0) tq_leave(tq);
 }
 
-// Both operands K-contiguous (the input-gradient form), K a multiple of 128: 256x256x64 tile,
-// four waves of 128x128 with the accumulators in the accumulator half of the register file.
-// A row of a K-contiguous operand gives a whole 128-byte line per K-tile of 64, so the path
-// to the L2 carries half the requests of the 32-wide K-tiles of the kernel above.  Operand
-// tiles go global -> registers -> LDS: two register sets are in flight (K-tiles kt+1 and kt+2
-// while kt is multiplied), LDS is double buffered, one barrier per K-tile.  Every output
-// element is still accumulated in ascending k with v_mfma_f32_32x32x16_bf16 in steps of 16
-// and rounded once after the same fp32 additions, so its bits equal the other kernel's.
-//   LDS tile: rows of 128 bytes, 16-byte pieces XOR-swizzled by (row/2)%8; a fragment is one
-//   ds_read_b128 per lane (row = lane%32, piece = 2*kstep + lane/32).
-//   Slots: one MFMA each; the fragment reads of the next k-step sit in slots 0..7 of a
-//   k-step, the LDS writes (each followed at once by the request that refills its
-//   registers) in read-free slots of k-steps 0..2; the barrier comes before k-step 3, whose
-//   slots read the first fragments of the next K-tile from the other LDS stage.
-template <bool HAS_R>
-__global__ __launch_bounds__(256, 1) void gemm_bf16_kc4w_kernel(
-    const bf16* __restrict__ A, const bf16* __restrict__ B, bf16* __restrict__ C, const bf16* __restrict__ R,
-    int M, int N, int K, int64_t lda, int64_t ldb, int64_t ldc, uint32_t a_bytes, uint32_t b_bytes, uint32_t c_bytes,
-    int tiles_m, int tiles_n, int tile_begin, int tile_count, int row_block, TileQueueArgs tq) {
-  constexpr int TBM = 256, TBK = 64, OPB = TBM * TBK * 2, STG = 2 * OPB;
+// ------------------------------------------------------------------ four-wave kernel
+// 256x256x64 tiles, four waves of 128x128, v_mfma_f32_16x16x32_bf16, for every form whose
+// K-contiguous operands have a contraction of whole K-tiles (K a multiple of 64).
+//
+// What bounds it: on the whole chip the board's power.  Registers only, random data, the
+// 16x16x32 instruction delivers 1830 TFLOP/s and the 32x32x16 one 1760 (it reads and writes twice
+// the accumulator bytes per flop); around it the kernel spends as little as it can: a wave tile of
+// 128x128 reads 1 LDS byte per 64 flops (half of what 128x64 wave tiles read), a K-tile of 64
+// brings whole 128-byte lines, operands go HBM -> LDS without passing registers, 128 matrix instructions
+// come with about 135 others per K-tile.
+//   LDS: two stages of 64 KB.  The fragments of a K-tile's second half are read under its first 16
+//     matrix instructions; after a barrier (slot 24 of 128) the stage is free and the K-tile after the
+//     next is requested into it, one request per six matrix instructions: requests made faster than
+//     the CU's vector cache takes them (16 cycles each, four waves) hold up the wave that makes
+//     them.  The next K-tile has to be there, behind a second barrier, at slot 88, when its first
+//     fragments are read.  Measured on 32768 x 4096 x 22016 input gradient / 12000 x 5120 x 1280
+//     forward: a request per two slots, one barrier in the middle 4697 / 118 us; per four 4734 / 112;
+//     two barriers and one per six 3960 / 112; without any requests the K loop takes 20 % less than
+//     the first of these.
+//   The stream of K-tiles runs on across output tiles; the epilogue passes through 4 KB per
+//     wave behind the stages, so the next tile's first K-tiles land under it.
+//   K-contiguous operand: rows of 128 bytes, 16-byte chunks XOR-swizzled by (row/2)%8, a fragment is
+//     one ds_read_b128.  K-strided operand: k-rows of 512 bytes as in HBM, 32-byte chunks XOR-swizzled
+//     by 2*(k%4) + (k/8)%2, a fragment is two ds_read_b64_tr_b16.  Both touch every bank once.
+//   Requests take a constant offset per lane; the K-tile moves the descriptor (base and remaining
+//     bytes: scalar instructions), which also bounds it: rows past the end read zeros, columns past
+//     the end read the next row's values and only reach outputs that are not stored.
+//   The matrix instruction is written in assembly to tie the result to its accumulator: left to
+//     itself the compiler copied 400 accumulator registers per K-tile.
+// Each output element is accumulated in ascending k: same bits as gemm_bf16_kernel's.
+// Measured, whole device, eight-wave kernel (input gradient: a four-wave kernel that staged through
+// registers) -> this: forward 32768 x 4096 x 12288 2525 -> 2300 us (1434 TFLOP/s), 8192 x 5632 x 2048
+// 149 -> 129; with GELU 12000 x 1280 x 5120 192 -> 169, with SwiGLU 8192 x 2048 x 11264 337 -> 317;
+// input gradient 32768 x 4096 x 22016 4433 -> 3960 (1492 TFLOP/s), 9216 x 4096 x 1024 77 -> 70;
+// weight gradient 4096 x 32768 x 22016 4368 -> 4130, 2048 x 8192 x 11264 318 -> 310.
+struct W4Args {
+  const bf16 *A, *B, *bias, *R;
+  bf16 *C, *C2;
+  float* P;
+  int M, N, K;
+  int64_t lda, ldb, ldc, ldc2;
+  uint32_t a_bytes, b_bytes, c_bytes, c2_bytes;
+  int tiles_m, tiles_n, tile_begin, tile_count, row_block, ktiles_per, gu_f;
+};
+enum { W4_PLAIN, W4_BIAS, W4_RES, W4_GELU, W4_SWIGLU, W4_SPLIT };
+constexpr int kW4Stage = 2 * 256 * 64 * 2;                         // both operands of a K-tile
+constexpr int kW4Pitch = 68;                                       // floats per row of the epilogue's patch: 16 rows of 64
+constexpr int kW4Lds = 2 * kW4Stage + 4 * 16 * kW4Pitch * 4;
+
+// One operand: what a lane requests of a K-tile, and where its fragments are.
+template <bool KC, bool GU>
+struct W4Operand {
+  unsigned voff[8];                        // byte offset of request j from the K-tile's first byte
+  int frag[KC ? 2 : 8];                    // LDS offsets: KC: of k-half 0 / 1, + 2048 per 16 rows; else of 16 columns each, + 16384 per k-half
+  __device__ __forceinline__ void init(int wave, int w0, int64_t ld, int gu_f) {
+    const int lane = threadIdx.x & 63, lr = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if constexpr (KC) {
+        const int r = 64 * wave + 8 * j + (lane >> 3), ch = (lane & 7) ^ ((r >> 1) & 7);
+        voff[j] = (unsigned)((int64_t)r * ld * 2 + ch * 16);
+      } else {
+        const int kr = 16 * wave + 2 * j + (lane >> 5), pos = lane & 31;
+        const int c32 = (pos >> 1) ^ (((kr & 3) << 1) | ((kr >> 3) & 1));
+        // GU: 16-column group c32 of the tile belongs to the gate half (even) or the up half (odd)
+        const int64_t byte = GU ? (c32 >> 1) * 32 + (int64_t)(c32 & 1) * gu_f * 2 : c32 * 32;
+        voff[j] = (unsigned)((int64_t)kr * ld * 2 + byte + (pos & 1) * 16);
+      }
+    }
+    if constexpr (KC) {
+      const int sw = (lr >> 1) & 7;
+      frag[0] = (w0 + lr) * 128 + ((g ^ sw) << 4);
+      frag[1] = (w0 + lr) * 128 + (((4 + g) ^ sw) << 4);
+    } else {
+      const int q = lr >> 2, f = (q << 1) | (g & 1);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) frag[i] = (8 * g + q) * 512 + (((w0 >> 4) + (i ^ f)) << 5) + 8 * (lr & 3);
+    }
+  }
+  __device__ __forceinline__ u32x4 read(const lds_byte* area, int i, int half) const {
+    if constexpr (KC) {
+      return *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(area + frag[half] + 2048 * i);
+    } else {
+      const lds_byte* p = area + frag[i] + 16384 * half;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 2048));
+      typedef __attribute__((ext_vector_type(8))) short s16x8;
+      return __builtin_bit_cast(u32x4, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+  }
+};
+
+// Where an operand's next K-tile starts and how many bytes of the tensor lie behind that point.
+struct W4Cursor {
+  uint64_t at;
+  uint32_t left;
+  __device__ __forceinline__ void set(const void* base, uint64_t off, uint32_t bytes) {
+    at = (uint64_t)(uintptr_t)base + off;
+    left = off < bytes ? (uint32_t)(bytes - off) : 0u;
+  }
+  __device__ __forceinline__ void advance(uint32_t step) { at += step; left = left > step ? left - step : 0u; }
+  __device__ __forceinline__ i32x4 desc(bool live) const {
+    i32x4 d;
+    d.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)at); d.y = __builtin_amdgcn_readfirstlane((int)((uint32_t)(at >> 32) & 0xffffu));
+    d.z = __builtin_amdgcn_readfirstlane((int)(live ? left : 0u)); d.w = 0x00020000;
+    return d;
+  }
+};
+
+template <bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueueArgs tq) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  constexpr int OPB = kW4Stage / 2;
   extern __shared__ __align__(16) unsigned char smem[];
   lds_byte* const lds = (lds_byte*)smem;
-  typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
-  typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const unsigned lds0 = (unsigned)(uintptr_t)lds;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
-  const int lr = lane & 31, hb = lane >> 5;
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, a_bytes), rb = make_rsrc(B, b_bytes);
-  const __amdgpu_buffer_rsrc_t rc = make_rsrc(C, c_bytes), rr = make_rsrc(R, HAS_R ? c_bytes : 0u);
-  const int nk = K / TBK;                       // even: K is a multiple of 128
-  // this thread's 8 pieces of an operand tile: piece c = tid + 256*i -> tile row tid/8 + 32*i,
-  // 16 bytes tid%8.  The swizzle term (row/2)%8 is the same for all eight (32*i/2 is a
-  // multiple of 8), so one LDS offset serves with immediates 4096*i; likewise for the
-  // fragment rows lr + 32*i.
-  const int grow0 = tid >> 3, gch = tid & 7;
-  const int lwr0 = grow0 * 128 + ((gch ^ ((grow0 >> 1) & 7)) << 4);
-  const int fro0 = lr * 128, frsw = (lr >> 1) & 7;
-  // Items come from the work queue (tile_queue.h), in the same panel-major tile list as
-  // gemm_bf16_kernel.  Thread 0 claims the next tile when the K loop is done and resolves the
-  // claim after the epilogue, so the round trip hides under the epilogue.
+  const int nk_all = (p.K + 63) / 64;
+  const uint32_t astep = A_KC ? 128u : (uint32_t)(64 * p.lda * 2), bstep = B_KC ? 128u : (uint32_t)(64 * p.ldb * 2);
+  W4Operand<A_KC, false> oa;
+  W4Operand<B_KC, EPI == W4_SWIGLU> ob;
+  oa.init(wave, wm, p.lda, 0);
+  ob.init(wave, wn, p.ldb, p.gu_f);
+
+  struct Item { int m0, n0, kt0, nk, split, tl; };
+  auto decode = [&](int item) -> Item {
+    Item it;
+    it.split = EPI == W4_SPLIT ? item / p.tile_count : 0;
+    it.tl = item - it.split * p.tile_count;
+    int trow, tcol;
+    tile_coords(p.tile_begin + it.tl, p.tiles_m, p.tiles_n, p.row_block, &trow, &tcol);
+    it.m0 = trow * 256; it.n0 = tcol * 256;
+    it.kt0 = it.split * p.ktiles_per;
+    // at least two K-tiles, the depth of the request stream: what lies past the end reads zeros
+    it.nk = EPI == W4_SPLIT ? max(2, min(nk_all - it.kt0, p.ktiles_per)) : nk_all;
+    return it;
+  };
+  W4Cursor ca, cb;
+  auto point = [&](const Item& it) {
+    ca.set(p.A, (A_KC ? (uint64_t)it.m0 * p.lda * 2 : (uint64_t)it.m0 * 2) + (uint64_t)it.kt0 * astep, p.a_bytes);
+    cb.set(p.B, (B_KC ? (uint64_t)it.n0 * p.ldb * 2 : (uint64_t)(EPI == W4_SWIGLU ? it.n0 : it.n0 * 2)) + (uint64_t)it.kt0 * bstep, p.b_bytes);
+  };
+  const unsigned wdst = lds0 + (unsigned)wave * 8192;
+  auto request = [&](const i32x4& d, unsigned off, unsigned dst) {
+    // m0 = LDS address of lane 0's 16 bytes; lane l lands at m0 + 16*l.  Completion is waited for by hand.
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(dst), "v"(off), "s"(d) : "m0");
+  };
+  auto request_tile = [&](int st) {
+    const i32x4 da = ca.desc(true), db = cb.desc(true);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) request(da, oa.voff[j], wdst + (unsigned)(st * kW4Stage + j * 1024));
+#pragma unroll
+    for (int j = 0; j < 8; ++j) request(db, ob.voff[j], wdst + (unsigned)(st * kW4Stage + OPB + j * 1024));
+    ca.advance(astep);
+    cb.advance(bstep);
+  };
+
   __shared__ int mail;
   TileQueueCursor qc;
   int item = tq_first(tq, qc, &mail);
-  while (item >= 0) {
-    const int tile = tile_begin + item;
-    int trow, tcol;
-    tile_coords(tile, tiles_m, tiles_n, row_block, &trow, &tcol);
-    const int m0 = trow * TBM, n0 = tcol * TBM;
-
-    f32x16 acc[4][4];
+  if (item < 0) { tq_done(tq); return; }
+  Item it = decode(item);
+  point(it);
+  request_tile(0);
+  request_tile(1);
+  f32x4 acc[8][8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 ax[8], bx[8], ay[8], by[8];          // fragments of the first and of the second half
+  __builtin_amdgcn_s_waitcnt((16 & 15) | (7 << 4) | (15 << 8) | ((16 >> 4) << 14));      // vmcnt(16): the first K-tile has landed
+  __builtin_amdgcn_s_barrier();
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    // byte offsets of this thread's pieces at K-tile 0; rows past the end fall outside the
-    // descriptor's range and read zeros
-    const unsigned oa0 = (unsigned)(((int64_t)(m0 + grow0) * lda) * 2 + gch * 16);
-    const unsigned ob0 = (unsigned)(((int64_t)(n0 + grow0) * ldb) * 2 + gch * 16);
-    const unsigned sa = (unsigned)(32 * lda * 2), sb = (unsigned)(32 * ldb * 2);     // 32 rows further
-    // K-tiles past the end are requested too (their registers are never used): the piece
-    // must not alias a valid row of the next K range, so it is sent out of range
-    auto ga_load = [&](int i, int kt) -> u32x4 {
-      return __builtin_amdgcn_raw_buffer_load_b128(ra, kt < nk ? (int)(oa0 + (unsigned)i * sa + (unsigned)kt * (TBK * 2)) : (int)kOob, 0, 0);
+  for (int i = 0; i < 8; ++i) { ax[i] = oa.read(lds, i, 0); bx[i] = ob.read(lds + OPB, i, 0); }
+  int st = 0;
+  bool live = true;
+  auto mfma = [](f32x4& c, const u32x4& b, const u32x4& a) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b), "v"(a));
+  };
+  // The compiler knows nothing of the latency of an assembly instruction: this stands between the
+  // matrix instructions and other reads or writes of their registers (more than the 19 wait
+  // states that the longest of those dependencies wants).
+  auto settle = [] { asm volatile("s_nop 15\n\ts_nop 15"); __builtin_amdgcn_sched_barrier(0); };
+  // One K-tile: 128 slots of one matrix instruction, the rest placed between them (see above).
+  constexpr int kFree = 24, kLanded = 88, kRequest = 25, kEvery = 6;
+  constexpr int kBefore = (kLanded - kRequest + kEvery - 1) / kEvery;        // requests made before kLanded
+  static_assert(kFree >= 16 && kRequest > kFree && kRequest + 15 * kEvery < 128 && kLanded + 30 < 128, "slots of a K-tile");
+  auto step = [&]() {
+    const lds_byte* const here = lds + st * kW4Stage;
+    const lds_byte* const there = lds + (st ^ 1) * kW4Stage;
+    const i32x4 da = ca.desc(live), db = cb.desc(live);
+    const unsigned dst = wdst + (unsigned)(st * kW4Stage);
+    __builtin_amdgcn_sched_barrier(0);
+    auto half = [&](auto first) {
+      constexpr int t0 = decltype(first)::value;
+#pragma unroll
+      for (int q = 0; q < 64; ++q) {
+        const int t = t0 + q;
+        if constexpr (t0 == 0) mfma(acc[q & 7][q >> 3], bx[q >> 3], ax[q & 7]);
+        else mfma(acc[q & 7][q >> 3], by[q >> 3], ay[q & 7]);
+        if (t < 8) ay[t] = oa.read(here, t, 1);
+        else if (t < 16) by[t - 8] = ob.read(here + OPB, t - 8, 1);
+        if (t == kFree) {
+          __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));                                       // lgkmcnt(0)
+          __builtin_amdgcn_s_barrier();
+        }
+        if (t == kLanded) {
+          __builtin_amdgcn_s_waitcnt((kBefore & 15) | (7 << 4) | (15 << 8) | ((kBefore >> 4) << 14));             // vmcnt(kBefore)
+          __builtin_amdgcn_s_barrier();
+        }
+        if (t >= kRequest && (t - kRequest) % kEvery == 0 && (t - kRequest) / kEvery < 16) {
+          const int r = (t - kRequest) / kEvery;
+          if (r < 8) request(da, oa.voff[r], dst + (unsigned)(r * 1024));
+          else request(db, ob.voff[r - 8], dst + (unsigned)(OPB + (r - 8) * 1024));
+        }
+        if (t >= kLanded && (t - kLanded) % 2 == 0 && t < kLanded + 32) {
+          const int r = (t - kLanded) / 2;
+          if (r < 8) ax[r] = oa.read(there, r, 0);
+          else bx[r - 8] = ob.read(there + OPB, r - 8, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     };
-    auto gb_load = [&](int i, int kt) -> u32x4 {
-      return __builtin_amdgcn_raw_buffer_load_b128(rb, kt < nk ? (int)(ob0 + (unsigned)i * sb + (unsigned)kt * (TBK * 2)) : (int)kOob, 0, 0);
-    };
-    u32x4 ga0[8], gb0[8], ga1[8], gb1[8];
-    bf16x8 fa[2][4], fb[2][4];
-    // prologue: K-tile 0 -> register set 1 -> LDS stage 0 and K-tile 1 -> register set 0 are
-    // requested together (one round trip, not two), then K-tile 2 -> register set 1
-    __syncthreads();                    // the previous tile's epilogue is done with the LDS
+    half(std::integral_constant<int, 0>{});
+    half(std::integral_constant<int, 64>{});
+    ca.advance(astep);
+    cb.advance(bstep);
+    st ^= 1;
+  };
+  const __amdgpu_buffer_rsrc_t rc = make_rsrc(p.C, p.c_bytes), rc2 = make_rsrc(p.C2, p.C2 ? p.c2_bytes : 0u);
+  const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.R, p.R ? p.c_bytes : 0u), rbias = make_rsrc(p.bias, p.bias ? (uint32_t)p.N * 2u : 0u);
+  while (true) {
+    settle();
+    for (int n = it.nk - 2; n > 0; --n) step();
+    // the last K-tile of this item has been requested: the requests move on to the next item
+    const unsigned entry = tq_claim_ahead(tq, qc);
+    const int next = tq_next(tq, qc, entry, &mail);
+    live = next >= 0;
+    const Item nit = decode(live ? next : item);
+    point(nit);
+    for (int n = 2; n > 0; --n) step();
+    settle();
+    // Epilogue, 16 rows x 64 columns at a time through the patch, leaving row-contiguous.
+    // acc[i][j][e] is output (row m0+wm+16i+lr, column n0+wn+16j+4g+e).
+    {
+      float* const patch = reinterpret_cast<float*>(smem + 2 * kW4Stage) + wave * (16 * kW4Pitch);
+      int ln = lane;
+      asm volatile("" : "+v"(ln));           // write-back offsets are formed here, not kept across the K loop
+      const int elr = ln & 15, eg = ln >> 4;
+      constexpr bool GU = EPI == W4_SWIGLU;
+      // a lane writes 8 columns: of rows prow and prow + 8, or (SwiGLU) of gate, up and activation of row prow
+      const int prow = GU ? ln >> 2 : ln >> 3, pcol = GU ? 32 * ((ln >> 1) & 1) + 8 * (ln & 1) : 8 * (ln & 7);
+      auto out_col = [&](int h) { return GU ? (it.n0 >> 1) + ((wn + 64 * h) >> 1) + (pcol >> 5) * 16 + (pcol & 15) : it.n0 + wn + 64 * h + pcol; };
+      const int ncols = GU ? p.gu_f : p.N;
+      auto off = [&](int row, int col, int64_t ld, bool ok) -> int { return ok ? (int)(unsigned)(((int64_t)row * ld + col) * 2) : (int)kOob; };
+      u32x4 bias_[2] = {}, bias_up[2] = {};
+      if constexpr (EPI != W4_PLAIN && EPI != W4_SPLIT) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { ga1[i] = ga_load(i, 0); gb1[i] = gb_load(i, 0); }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { ga0[i] = ga_load(i, 1); gb0[i] = gb_load(i, 1); }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      *reinterpret_cast<lds_u32x4*>(lds + lwr0 + 4096 * i) = ga1[i];
-      *reinterpret_cast<lds_u32x4*>(lds + OPB + lwr0 + 4096 * i) = gb1[i];
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { ga1[i] = ga_load(i, 2); gb1[i] = gb_load(i, 2); }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      fa[0][i] = *reinterpret_cast<const lds_bf16x8*>(lds + wm * 128 + fro0 + 4096 * i + ((hb ^ frsw) << 4));
-      fb[0][i] = *reinterpret_cast<const lds_bf16x8*>(lds + OPB + wn * 128 + fro0 + 4096 * i + ((hb ^ frsw) << 4));
-    }
-    auto body = [&](int kt, auto sel_) {
-      constexpr int SEL = decltype(sel_)::value;
-      const int st = kt & 1;
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const int cur = ks & 1, nxt = cur ^ 1;
-        // K-tile kt+1 is in LDS for everybody and nobody reads stage st after this k-step
-        if (ks == 3) __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const int i = q & 3, j = q >> 2;
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
-          if (q < 8) {
-            // fragments of the next k-step (of the next K-tile's first k-step when ks == 3)
-            const int rs_ = ks < 3 ? st : st ^ 1, rk = ks < 3 ? ks + 1 : 0;
-            if (q < 4) fa[nxt][q] = *reinterpret_cast<const lds_bf16x8*>(lds + rs_ * STG + wm * 128 + fro0 + 4096 * q + (((2 * rk + hb) ^ frsw) << 4));
-            else fb[nxt][q - 4] = *reinterpret_cast<const lds_bf16x8*>(lds + rs_ * STG + OPB + wn * 128 + fro0 + 4096 * (q - 4) + (((2 * rk + hb) ^ frsw) << 4));
-          }
-          if ((ks < 2 && q >= 8 && q < 14) || (ks == 2 && q >= 8 && q < 12)) {
-            // register set SEL (K-tile kt+1) -> the other LDS stage; the freed registers go
-            // straight back out for K-tile kt+3
-            const int w = ks * 6 + (q - 8), i8 = w >> 1;
-            if ((w & 1) == 0) {
-              u32x4& a_ = SEL ? ga1[i8] : ga0[i8];
-              *reinterpret_cast<lds_u32x4*>(lds + (st ^ 1) * STG + lwr0 + 4096 * i8) = a_;
-              a_ = ga_load(i8, kt + 3);
-            } else {
-              u32x4& b_ = SEL ? gb1[i8] : gb0[i8];
-              *reinterpret_cast<lds_u32x4*>(lds + (st ^ 1) * STG + OPB + lwr0 + 4096 * i8) = b_;
-              b_ = gb_load(i8, kt + 3);
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
+        for (int h = 0; h < 2; ++h) {
+          const int col = out_col(h);
+          bias_[h] = __builtin_amdgcn_raw_buffer_load_b128(rbias, col < ncols ? col * 2 : (int)kOob, 0, 0);
+          if constexpr (GU) bias_up[h] = __builtin_amdgcn_raw_buffer_load_b128(rbias, col < ncols ? (col + p.gu_f) * 2 : (int)kOob, 0, 0);
         }
       }
-    };
-    for (int kt = 0; kt < nk; kt += 2) {
-      body(kt, std::integral_constant<int, 0>{});
-      body(kt + 1, std::integral_constant<int, 1>{});
-    }
-    __syncthreads();                    // every wave is done reading fragments: LDS is free
-    const unsigned entry = tq_claim_ahead(tq, qc);
-
-    // Epilogue, one 32x32 block at a time through a 4 KB fp32 patch per wave (XOR swizzled),
-    // leaving row-contiguous; the residual is added in fp32 in that layout, one rounding.
-    // acc[i][j][4g+e] is output (row m0+wm+32i+lr, column n0+wn+32j+8g+4hb+e).
-    {
-      float* patch = reinterpret_cast<float*>(smem) + wave * 1024;
-      int ln = lane;
-      asm volatile("" : "+v"(ln));
-      const int elr = ln & 31, ehb = ln >> 5;
-      auto out_off = [&](int b, int q) -> unsigned {
-        const int row = m0 + wm + 32 * (b >> 2) + (ln >> 2) + 16 * q;
-        const int col = n0 + wn + 32 * (b & 3) + 8 * (ln & 3);
-        return (col < N) ? (unsigned)(((int64_t)row * ldc + col) * 2) : kOob;
+      auto patch_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       };
-      u32x4 rnext[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
-      if constexpr (HAS_R) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) rnext[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)out_off(0, q), 0, 0);
-      }
 #pragma unroll
       for (int b = 0; b < 16; ++b) {
-        const int i = b >> 2, j = b & 3;
+        const int i = b >> 1, h = b & 1, row0 = it.m0 + wm + 16 * i, col = out_col(h);
+        const bool ok = col < ncols;
+        u32x4 res[2] = {};
+        if constexpr (EPI == W4_RES) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int cg = (2 * g + ehb) ^ ((elr >> 1) & 7);
-          float4 v = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-          *reinterpret_cast<float4*>(patch + elr * 32 + cg * 4) = v;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        float4 v0[2], v1[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const int r = (ln >> 2) + 16 * q, c8 = ln & 3, sx = (r >> 1) & 7;
-          v0[q] = *reinterpret_cast<const float4*>(patch + r * 32 + (((2 * c8) ^ sx) * 4));
-          v1[q] = *reinterpret_cast<const float4*>(patch + r * 32 + (((2 * c8 + 1) ^ sx) * 4));
-        }
-        const u32x4 rcur[2] = {rnext[0], rnext[1]};
-        if constexpr (HAS_R) {
-          if (b + 1 < 16) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) rnext[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)out_off(b + 1, q), 0, 0);
-          }
+          for (int q = 0; q < 2; ++q) res[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, off(row0 + prow + 8 * q, col, p.ldc, ok), 0, 0);
         }
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const bf16x8 rv = __builtin_bit_cast(bf16x8, rcur[q]);
-          const float vals[8] = {v0[q].x, v0[q].y, v0[q].z, v0[q].w, v1[q].x, v1[q].y, v1[q].z, v1[q].w};
-          bf16x8 o;
+        for (int jj = 0; jj < 4; ++jj) {
+          f32x4& a = acc[i][4 * h + jj];
+          *reinterpret_cast<float4*>(patch + elr * kW4Pitch + 16 * jj + 4 * eg) = make_float4(a[0], a[1], a[2], a[3]);
+          a = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        patch_sync();
+        auto row8 = [&](int r, int c, float* v) {
+          const float4 x = *reinterpret_cast<const float4*>(patch + r * kW4Pitch + c), y = *reinterpret_cast<const float4*>(patch + r * kW4Pitch + c + 4);
+          v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
+        };
+        if constexpr (GU) {
+          float gv[8], uv[8];
+          row8(prow, pcol, gv);
+          row8(prow, pcol + 16, uv);
+          const bf16x8 bg = __builtin_bit_cast(bf16x8, bias_[h]), bu = __builtin_bit_cast(bf16x8, bias_up[h]);
+          bf16x8 og, ou, oc;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            float v = vals[e];
-            if constexpr (HAS_R) { v += 0.f; v += (float)rv[e]; }   // value + (absent bias) + residual
-            o[e] = (bf16)v;
+            og[e] = (bf16)(gv[e] + (float)bg[e]);
+            ou[e] = (bf16)(uv[e] + (float)bu[e]);
+            oc[e] = (bf16)swiglu_f<bf16>((float)og[e], (float)ou[e]);     // of the values as stored
           }
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rc, (int)out_off(b, q), 0, 0);
+          const int row = row0 + prow;
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, og), rc, off(row, col, p.ldc, ok), 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, ou), rc, off(row, col + p.gu_f, p.ldc, ok), 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, oc), rc2, off(row, col, p.ldc2, ok), 0, 0);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int row = row0 + prow + 8 * q;
+            float v[8];
+            row8(prow + 8 * q, pcol, v);
+            if constexpr (EPI == W4_SPLIT) {
+              if (row < p.M && ok) {
+                float* dst = p.P + ((int64_t)it.split * p.tile_count + it.tl) * 65536 + (row - it.m0) * 256 + (col - it.n0);
+                *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
+              }
+            } else {
+              const bf16x8 bv = __builtin_bit_cast(bf16x8, bias_[h]), rv = __builtin_bit_cast(bf16x8, res[q]);
+              bf16x8 o;
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                float x = v[e];
+                if constexpr (EPI != W4_PLAIN) x += (float)bv[e];
+                if constexpr (EPI == W4_RES) x += (float)rv[e];
+                o[e] = (bf16)x;
+              }
+              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rc, off(row, col, p.ldc, ok), 0, 0);
+              if constexpr (EPI == W4_GELU) {
+                bf16x8 a2;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) a2[e] = (bf16)gelu_f<bf16>((float)o[e]);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a2), rc2, off(row, col, p.ldc2, ok), 0, 0);
+              }
+            }
+          }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        patch_sync();
       }
     }
-    item = tq_next(tq, qc, entry, &mail);
+    if (!live) break;
+    item = next;
+    it = nit;
   }
+  __builtin_amdgcn_s_waitcnt(0);
   tq_done(tq);
 }
 
@@ -1190,54 +1339,70 @@ mosaic_status launch_mfma(hipStream_t s, int quota, int M, int N, int K, const b
   return MOSAIC_OK;
 }
 
-// The four-wave kernel for the K-contiguous x K-contiguous form: whole tiles only (sub = 1).
-mosaic_status launch_kc4w(hipStream_t s, int quota, int M, int N, int K, const bf16* A, int64_t lda, const bf16* B,
-                          int64_t ldb, bf16* C, int64_t ldc, const bf16* R, uint32_t a_bytes, uint32_t b_bytes,
-                          uint32_t c_bytes, int tile_begin, int tile_count) {
-  constexpr size_t smem = 2 * 2 * 256 * 64 * 2;        // two stages of two 256 x 64 operand tiles
+// The four-wave kernel takes a product when its K-contiguous operands are whole K-tiles long.
+template <bool A_KC, bool B_KC> constexpr bool w4_form() { return A_KC || !B_KC; }
+template <bool A_KC, bool B_KC> bool w4_takes(int64_t K) { return w4_form<A_KC, B_KC>() && K >= 128 && (!(A_KC || B_KC) || K % 64 == 0); }
+
+template <bool A_KC, bool B_KC, int EPI>
+mosaic_status launch_w4_epi(hipStream_t s, int quota, const W4Args& p, int pieces) {
+  auto kern = gemm_bf16_w4_kernel<A_KC, B_KC, EPI>;
   static std::once_flag attr_once;
   static hipError_t attr_rc = hipSuccess;
   std::call_once(attr_once, [&] {
-    attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_kc4w_kernel<true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (attr_rc == hipSuccess)
-      attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_kc4w_kernel<false>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kW4Lds);
   });
   MOSAIC_HIP(attr_rc);
-  const int tiles_m = (int)ceil_div(M, 256), tiles_n = (int)ceil_div(N, 256);
-  if (tile_count < 0) tile_count = tiles_m * tiles_n - tile_begin;
-  if (tile_count <= 0) return MOSAIC_OK;
   TileQueueArgs tq;
   int grid;
-  MOSAIC_TRY(tile_queue_plan(s, quota, 1, tile_count, 0, false, &tq, &grid));
-  const int rb = row_block_for(K, tiles_m);
-  if (R) gemm_bf16_kc4w_kernel<true><<<grid, 256, smem, s>>>(A, B, C, R, M, N, K, lda, ldb, ldc, a_bytes, b_bytes, c_bytes,
-                                                             tiles_m, tiles_n, tile_begin, tile_count, rb, tq);
-  else gemm_bf16_kc4w_kernel<false><<<grid, 256, smem, s>>>(A, B, C, R, M, N, K, lda, ldb, ldc, a_bytes, b_bytes, c_bytes,
-                                                            tiles_m, tiles_n, tile_begin, tile_count, rb, tq);
+  MOSAIC_TRY(tile_queue_plan(s, quota, 1, (int64_t)p.tile_count * pieces, 0, false, &tq, &grid));
+  kern<<<grid, 256, kW4Lds, s>>>(p, tq);
   MOSAIC_LAUNCH_CHECK();
+  if constexpr (EPI == W4_SPLIT) {
+    splitk_reduce_kernel<256><<<grid_for(quota, 8, (int64_t)p.tile_count * 64), 256, 0, s>>>(p.P, p.C, p.M, p.N, p.ldc, pieces, p.tiles_m, p.tiles_n,
+                                                                                           p.tile_begin, p.tile_count, p.row_block);
+    MOSAIC_LAUNCH_CHECK();
+  }
   return MOSAIC_OK;
 }
 
+// Tiles [tile_begin, tile_begin + tile_count) of the 256x256 tile list (tile_count < 0: all from
+// tile_begin on); pieces > 1: each cut into that many pieces of the contraction, added by a second pass.
+template <bool A_KC, bool B_KC>
+mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, bf16* C,
+                        int64_t ldc, const bf16* bias, const bf16* R, uint32_t a_bytes, uint32_t b_bytes, uint32_t c_bytes, int tile_begin,
+                        int tile_count, const ActArgs& aa, int pieces = 1, float* P = nullptr) {
+  W4Args p = {};
+  p.A = A; p.B = B; p.C = C; p.bias = bias; p.R = R; p.P = P; p.C2 = aa.C2;
+  p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldc2 = aa.ldc2;
+  p.a_bytes = a_bytes; p.b_bytes = b_bytes; p.c_bytes = c_bytes; p.c2_bytes = aa.c2_bytes; p.gu_f = aa.gu_f;
+  p.tiles_m = (int)ceil_div(M, 256); p.tiles_n = (int)ceil_div(N, 256);
+  p.tile_begin = tile_begin;
+  p.tile_count = tile_count < 0 ? p.tiles_m * p.tiles_n - tile_begin : tile_count;
+  if (p.tile_count <= 0) return MOSAIC_OK;
+  p.row_block = row_block_for(K, p.tiles_m);
+  p.ktiles_per = (int)ceil_div(ceil_div(K, 64), pieces);
+  if constexpr (!A_KC && !B_KC) {
+    if (pieces > 1) return launch_w4_epi<A_KC, B_KC, W4_SPLIT>(s, quota, p, pieces);
+  }
+  if constexpr (A_KC && !B_KC) {
+    if (aa.act == ACT_GELU) return launch_w4_epi<A_KC, B_KC, W4_GELU>(s, quota, p, 1);
+    if (aa.act == ACT_SWIGLU) return launch_w4_epi<A_KC, B_KC, W4_SWIGLU>(s, quota, p, 1);
+    if (bias && !R) return launch_w4_epi<A_KC, B_KC, W4_BIAS>(s, quota, p, 1);
+  }
+  if (R || bias) return launch_w4_epi<A_KC, B_KC, W4_RES>(s, quota, p, 1);
+  return launch_w4_epi<A_KC, B_KC, W4_PLAIN>(s, quota, p, 1);
+}
+
 // A/B switches for kernel timing, compiled in only with -DMOSAIC_TUNING (never in the library
-// that ships): MOSAIC_GEMM_KC4W=0 sends the input-gradient form back to the eight-wave kernel,
+// that ships): MOSAIC_GEMM_W4=0 sends the 256x256 tiles back to the eight-wave kernel,
 // MOSAIC_GEMM_TILE=256 / 128 / 1 forces the all-256, all-128 or mixed tile plan (the bits are
 // the same either way); MOSAIC_SPLITK=n forces the piece count of a weight gradient's cut tail
 // (0: no cut; the bits differ with n).
 #ifdef MOSAIC_TUNING
-bool kc4w_enabled() {
-  static int v = -1;
-  if (v < 0) { const char* e = getenv("MOSAIC_GEMM_KC4W"); v = e ? atoi(e) : 1; }
-  return v != 0;
-}
-int forced_tile() {
-  static int v = -1;
-  if (v < 0) { const char* e = getenv("MOSAIC_GEMM_TILE"); v = e ? atoi(e) : 0; }
-  return v;
-}
+bool w4_enabled() { const char* e = getenv("MOSAIC_GEMM_W4"); return !e || atoi(e) != 0; }
+int forced_tile() { const char* e = getenv("MOSAIC_GEMM_TILE"); return e ? atoi(e) : 0; }
 #else
-constexpr bool kc4w_enabled() { return true; }
+constexpr bool w4_enabled() { return true; }
 constexpr int forced_tile() { return 0; }
 #endif
 
@@ -1339,10 +1504,12 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
                                                                           sk, (int)ceil_div(ceil_div(K, 64), sk), (float*)splitk_scratch);
     }
   }
+  // cut products have a contraction of thousands (splitk_plan), which the four-wave kernel takes
   auto launch_split = [&]() -> mosaic_status {
-    const int per = (int)ceil_div(ceil_div(K, BK), sk);
-    return launch_mfma<256, 256, 2, 4, A_KC, B_KC, true>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes,
-                                                         sk, per, (float*)splitk_scratch, 1, split_first, (int)(t256_all - split_first));
+    if constexpr (!A_KC && !B_KC)
+      return launch_w4<A_KC, B_KC>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes, split_first,
+                                   (int)(t256_all - split_first), aa, sk, (float*)splitk_scratch);
+    else return MOSAIC_EUNSUPPORTED;
   };
   const bool part = sk > 1;          // the plans below cover tiles [0, t256) only
   if (part) {
@@ -1367,11 +1534,11 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
     constexpr double pen = (A_KC && B_KC) ? 1.3 : (!A_KC && !B_KC) ? 1.8 : 1.45;
     return (double)full * 2.0 * pen + (rem == 0 ? 0.0 : rem <= quota ? 1.2 * pen : 2.0 * pen);
   };
-  // whole 256x256 tiles of the K-contiguous x K-contiguous form go to the four-wave kernel
-  // (its K-tiles are 64 wide and come in pairs; no bias in its epilogue); a round of it takes
-  // about 3.7 units where the eight-wave kernel takes 4
-  const bool kc4w = A_KC && B_KC && !bias && (K % 128 == 0) && kc4w_enabled();
-  const double round256 = kc4w ? 3.7 : 4.0;
+  // 256x256 tiles go to the four-wave kernel where it takes the product; a round of it takes
+  // about 3.5 units where the eight-wave kernel takes 4 (9216 x 1024 x 3072 forward, 1.7 rounds: 52 us in
+  // two rounds of large tiles, 55 as one and quarter tiles)
+  const bool w4 = w4_takes<A_KC, B_KC>(K) && w4_enabled();
+  const double round256 = w4 ? 3.5 : 4.0;
   const int64_t whole = t256 / quota, rest = t256 % quota;
   const double cost256 = (double)ceil_div(t256, quota) * round256;
   const double cost128 = cost_small(t128);
@@ -1379,11 +1546,14 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
   int plan = cost256 <= cost128 ? (cost256 <= cost_mix ? 256 : 0) : (cost128 <= cost_mix ? 128 : 0);
   if (forced_tile() == 128 || forced_tile() == 256) plan = forced_tile();
   if (forced_tile() == 1 && whole > 0 && rest > 0) plan = 0;
-  // one launch of the eight-wave (big) or four-wave quarter-tile kernel over coarse tiles
+  // one launch of 256x256 tiles (big) or of 128x128 (quarter) tiles over coarse tiles
   // [tile_begin, tile_begin + tile_count) (tile_count < 0: all), with the epilogue `aa` asks for
   auto launch_tiles = [&](auto big_, int sub, int tile_begin, int tile_count) -> mosaic_status {
     constexpr bool BIG = decltype(big_)::value;
     constexpr int TB = BIG ? 256 : 128, WN_ = BIG ? 4 : 2;
+    if constexpr (BIG && w4_form<A_KC, B_KC>()) {
+      if (w4) return launch_w4<A_KC, B_KC>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes, tile_begin, tile_count, aa);
+    }
     if constexpr (A_KC && !B_KC) {
       if (aa.act == ACT_GELU)
         return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC, false, ACT_GELU>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
@@ -1396,7 +1566,6 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
                                                    nullptr, sub, tile_begin, tile_count);
   };
   if (plan == 256) {
-    if (kc4w) return launch_kc4w(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, R, a_bytes, b_bytes, c_bytes, 0, -1);
     MOSAIC_TRY(launch_tiles(std::true_type{}, 1, 0, part ? (int)t256 : -1));
     return part ? launch_split() : MOSAIC_OK;
   }
@@ -1405,9 +1574,7 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
     return part ? launch_split() : MOSAIC_OK;
   }
   const int head = (int)(whole * quota);
-  mosaic_status st = kc4w ? launch_kc4w(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, R, a_bytes, b_bytes, c_bytes, 0, head)
-                          : launch_tiles(std::true_type{}, 1, 0, head);
-  if (st != MOSAIC_OK) return st;
+  MOSAIC_TRY(launch_tiles(std::true_type{}, 1, 0, head));
   MOSAIC_TRY(launch_tiles(std::false_type{}, 2, head, (int)rest));
   return part ? launch_split() : MOSAIC_OK;
 }

@@ -81,3 +81,49 @@ def test_weight_gradient_of_few_tiles(mb, T, k, n, note):
         outs.append(dW)
     assert_close(from_dev(outs[0]), X.T @ dY, "bf16", note)
     assert all(torch.equal(o.view(torch.int16), outs[0].view(torch.int16)) for o in outs[1:]), note
+
+
+@pytest.mark.parametrize("T,k,n", [(510, 128, 504), (255, 192, 1016), (768, 320, 512), (1000, 1088, 768),      # forward: contraction k
+                                   (510, 248, 128), (1000, 760, 192), (249, 1024, 1088),                       # input gradient: n
+                                   (72, 504, 760), (136, 256, 1024), (1000, 512, 504)])                        # weight gradient: T, any length
+def test_large_tiles_agree_with_small_ones(mb, T, k, n):
+    """On the whole device these products take 128 x 128 tiles, on one CU 256 x 256 ones (where a form fits
+    them: otherwise both runs take small tiles), several to a workgroup: two and more K-tiles of 64, odd counts, a contraction that ends in
+    mid K-tile, ragged rows and columns, every epilogue."""
+    s = 7600 + T + k + n
+    X, W, b, R, dY = [quantize(synth.normal(s + i, sh, 0, sd), "bf16") for i, (sh, sd) in
+                      enumerate([((T, k), 1), ((k, n), 0.05), ((n,), 0.1), ((T, n), 1), ((T, n), 1)])]
+    X_, W_, b_, R_, dY_ = [to_dev(a, "bf16") for a in (X, W, b, R, dY)]
+    R2 = quantize(synth.normal(s + 9, (T, k)), "bf16")
+    R2_ = to_dev(R2, "bf16")
+    outs = []
+    for q in (256, 1, 3):
+        e = lambda *sh: torch.full(sh, float("nan"), dtype=torch.bfloat16, device="cuda")
+        P, Y, Yr, Z, A, dX, dXr, dW = e(T, n), e(T, n), e(T, n), e(T, n), e(T, n), e(T, k), e(T, k), e(k, n)
+        sc = torch.empty(max(16, mb.linear_wgrad_scratch_bytes(T, k, n)), dtype=torch.uint8, device="cuda")
+        mb.op_linear_fwd(None, q, "bf16", T, k, n, X_, W_, None, None, P)
+        mb.op_linear_fwd(None, q, "bf16", T, k, n, X_, W_, b_, None, Y)
+        mb.op_linear_fwd(None, q, "bf16", T, k, n, X_, W_, b_, R_, Yr)
+        mb.op_linear_act_fwd(None, q, "bf16", mb.GELU, T, k, n, X_, W_, b_, Z, A)
+        mb.op_linear_dgrad(None, q, "bf16", T, k, n, dY_, W_, None, dX)
+        mb.op_linear_dgrad(None, q, "bf16", T, k, n, dY_, W_, R2_, dXr)
+        mb.op_linear_wgrad(None, q, "bf16", T, k, n, X_, dY_, dW, None, sc)
+        got = [P, Y, Yr, Z, A, dX, dXr, dW]
+        if n % 256 == 0:
+            G, S = e(T, n), e(T, n // 2)
+            mb.op_linear_act_fwd(None, q, "bf16", mb.SWIGLU, T, k, n, X_, W_, b_, G, S)
+            got += [G, S]
+        torch.cuda.synchronize()
+        outs.append(got)
+    z_ref = O.linear_fwd(X, W, b)
+    dx_ref, dw_ref, _ = O.linear_bwd(X, W, dY)
+    P, Y, Yr, Z, A, dX, dXr, dW = outs[1][:8]
+    for got, want, what in ((P, O.linear_fwd(X, W), "P"), (Y, z_ref, "Y"), (Yr, z_ref + R, "Yr"), (Z, z_ref, "Z"), (A, O.gelu(from_dev(Z)), "A"),
+                            (dX, dx_ref, "dX"), (dXr, dx_ref + R2, "dXr"), (dW, dw_ref, "dW")):
+        assert_close(from_dev(got), want, "bf16", what)
+    if n % 256 == 0:
+        g = from_dev(outs[1][8])
+        assert_close(g, z_ref, "bf16", "gate | up")
+        assert_close(from_dev(outs[1][9]), O.swiglu_fwd(g[:, :n // 2], g[:, n // 2:]), "bf16", "swiglu")
+    for o in outs[1:]:
+        assert all(torch.equal(a.view(torch.int16), c.view(torch.int16)) for a, c in zip(o, outs[0]))
