@@ -947,16 +947,16 @@ constexpr int kW4Pitch = 68;                                       // floats per
 constexpr int kW4Lds = 2 * kW4Stage + 4 * 16 * kW4Pitch * 4;
 
 // One operand: what a lane requests of a K-tile, and where its fragments are.
-template <bool KC, bool GU>
+template <bool KC, bool GU, int NF = 8>
 struct W4Operand {
-  unsigned voff[8];                        // byte offset of request j from the K-tile's first byte
+  unsigned voff[NF];                       // byte offset of request j from the K-tile's first byte
   int frag[KC ? 2 : 8];                    // LDS offsets: KC: of k-half 0 / 1, + 2048 per 16 rows; else of 16 columns each, + 16384 per k-half
   __device__ __forceinline__ void init(int wave, int w0, int64_t ld, int gu_f) {
     const int lane = threadIdx.x & 63, lr = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < NF; ++j) {
       if constexpr (KC) {
-        const int r = 64 * wave + 8 * j + (lane >> 3), ch = (lane & 7) ^ ((r >> 1) & 7);
+        const int r = 8 * NF * wave + 8 * j + (lane >> 3), ch = (lane & 7) ^ ((r >> 1) & 7);
         voff[j] = (unsigned)((int64_t)r * ld * 2 + ch * 16);
       } else {
         const int kr = 16 * wave + 2 * j + (lane >> 5), pos = lane & 31;
@@ -1006,18 +1006,19 @@ struct W4Cursor {
   }
 };
 
-template <bool A_KC, bool B_KC, int EPI>
+template <bool A_KC, bool B_KC, int EPI, int MI>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueueArgs tq) {
   typedef __attribute__((ext_vector_type(4))) float f32x4;
   constexpr int OPB = kW4Stage / 2;
+  static_assert(MI == 8 || A_KC, "a K-strided row operand fills whole requests with 256 rows only");
   extern __shared__ __align__(16) unsigned char smem[];
   lds_byte* const lds = (lds_byte*)smem;
   const unsigned lds0 = (unsigned)(uintptr_t)lds;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
+  const int wm = (wave >> 1) * (16 * MI), wn = (wave & 1) * 128;
   const int nk_all = (p.K + 63) / 64;
   const uint32_t astep = A_KC ? 128u : (uint32_t)(64 * p.lda * 2), bstep = B_KC ? 128u : (uint32_t)(64 * p.ldb * 2);
-  W4Operand<A_KC, false> oa;
+  W4Operand<A_KC, false, MI> oa;
   W4Operand<B_KC, EPI == W4_SWIGLU> ob;
   oa.init(wave, wm, p.lda, 0);
   ob.init(wave, wn, p.ldb, p.gu_f);
@@ -1029,7 +1030,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
     it.tl = item - it.split * p.tile_count;
     int trow, tcol;
     tile_coords(p.tile_begin + it.tl, p.tiles_m, p.tiles_n, p.row_block, &trow, &tcol);
-    it.m0 = trow * 256; it.n0 = tcol * 256;
+    it.m0 = trow * (32 * MI); it.n0 = tcol * 256;
     it.kt0 = it.split * p.ktiles_per;
     // at least two K-tiles, the depth of the request stream: what lies past the end reads zeros
     it.nk = EPI == W4_SPLIT ? max(2, min(nk_all - it.kt0, p.ktiles_per)) : nk_all;
@@ -1040,7 +1041,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
     ca.set(p.A, (A_KC ? (uint64_t)it.m0 * p.lda * 2 : (uint64_t)it.m0 * 2) + (uint64_t)it.kt0 * astep, p.a_bytes);
     cb.set(p.B, (B_KC ? (uint64_t)it.n0 * p.ldb * 2 : (uint64_t)(EPI == W4_SWIGLU ? it.n0 : it.n0 * 2)) + (uint64_t)it.kt0 * bstep, p.b_bytes);
   };
-  const unsigned wdst = lds0 + (unsigned)wave * 8192;
+  const unsigned wdst = lds0 + (unsigned)wave * 8192, adst = lds0 + (unsigned)wave * (MI * 1024);
   auto request = [&](const i32x4& d, unsigned off, unsigned dst) {
     // m0 = LDS address of lane 0's 16 bytes; lane l lands at m0 + 16*l.  Completion is waited for by hand.
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(dst), "v"(off), "s"(d) : "m0");
@@ -1048,7 +1049,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
   auto request_tile = [&](int st) {
     const i32x4 da = ca.desc(true), db = cb.desc(true);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) request(da, oa.voff[j], wdst + (unsigned)(st * kW4Stage + j * 1024));
+    for (int j = 0; j < MI; ++j) request(da, oa.voff[j], adst + (unsigned)(st * kW4Stage + j * 1024));
 #pragma unroll
     for (int j = 0; j < 8; ++j) request(db, ob.voff[j], wdst + (unsigned)(st * kW4Stage + OPB + j * 1024));
     ca.advance(astep);
@@ -1063,16 +1064,19 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
   point(it);
   request_tile(0);
   request_tile(1);
-  f32x4 acc[8][8];
+  f32x4 acc[MI][8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  u32x4 ax[8], bx[8], ay[8], by[8];          // fragments of the first and of the second half
-  __builtin_amdgcn_s_waitcnt((16 & 15) | (7 << 4) | (15 << 8) | ((16 >> 4) << 14));      // vmcnt(16): the first K-tile has landed
+  u32x4 ax[MI], bx[8], ay[MI], by[8];          // fragments of the first and of the second half
+  __builtin_amdgcn_s_waitcnt(((MI + 8) & 15) | (7 << 4) | (15 << 8) | (((MI + 8) >> 4) << 14));      // vmcnt: the first K-tile has landed
   __builtin_amdgcn_s_barrier();
 #pragma unroll
-  for (int i = 0; i < 8; ++i) { ax[i] = oa.read(lds, i, 0); bx[i] = ob.read(lds + OPB, i, 0); }
+  for (int i = 0; i < 8; ++i) {
+    if (i < MI) ax[i] = oa.read(lds, i, 0);
+    bx[i] = ob.read(lds + OPB, i, 0);
+  }
   int st = 0;
   bool live = true;
   auto mfma = [](f32x4& c, const u32x4& b, const u32x4& a) {
@@ -1083,24 +1087,25 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
   // states that the longest of those dependencies wants).
   auto settle = [] { asm volatile("s_nop 15\n\ts_nop 15"); __builtin_amdgcn_sched_barrier(0); };
   // One K-tile: 128 slots of one matrix instruction, the rest placed between them (see above).
-  constexpr int kFree = 24, kLanded = 88, kRequest = 25, kEvery = 6;
+  constexpr int NR = MI + 8;                  // requests of a K-tile, fragments of half of it
+  constexpr int kFree = NR + 8, kLanded = 16 * MI - 2 * NR - 8, kRequest = kFree + 1, kEvery = MI == 8 ? 6 : MI - 1;
   constexpr int kBefore = (kLanded - kRequest + kEvery - 1) / kEvery;        // requests made before kLanded
-  static_assert(kFree >= 16 && kRequest > kFree && kRequest + 15 * kEvery < 128 && kLanded + 30 < 128, "slots of a K-tile");
+  static_assert(kFree <= 8 * MI && kLanded >= 8 * MI && kRequest + (NR - 1) * kEvery < 16 * MI, "slots of a K-tile");
   auto step = [&]() {
     const lds_byte* const here = lds + st * kW4Stage;
     const lds_byte* const there = lds + (st ^ 1) * kW4Stage;
     const i32x4 da = ca.desc(live), db = cb.desc(live);
-    const unsigned dst = wdst + (unsigned)(st * kW4Stage);
+    const unsigned dst = wdst + (unsigned)(st * kW4Stage), dsta = adst + (unsigned)(st * kW4Stage);
     __builtin_amdgcn_sched_barrier(0);
     auto half = [&](auto first) {
       constexpr int t0 = decltype(first)::value;
 #pragma unroll
-      for (int q = 0; q < 64; ++q) {
-        const int t = t0 + q;
-        if constexpr (t0 == 0) mfma(acc[q & 7][q >> 3], bx[q >> 3], ax[q & 7]);
-        else mfma(acc[q & 7][q >> 3], by[q >> 3], ay[q & 7]);
-        if (t < 8) ay[t] = oa.read(here, t, 1);
-        else if (t < 16) by[t - 8] = ob.read(here + OPB, t - 8, 1);
+      for (int q = 0; q < 8 * MI; ++q) {
+        const int t = t0 + q, i = q % MI, j = q / MI;
+        if constexpr (t0 == 0) mfma(acc[i][j], bx[j], ax[i]);
+        else mfma(acc[i][j], by[j], ay[i]);
+        if (t < MI) ay[t] = oa.read(here, t, 1);
+        else if (t < NR) by[t - MI] = ob.read(here + OPB, t - MI, 1);
         if (t == kFree) {
           __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));                                       // lgkmcnt(0)
           __builtin_amdgcn_s_barrier();
@@ -1109,21 +1114,21 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
           __builtin_amdgcn_s_waitcnt((kBefore & 15) | (7 << 4) | (15 << 8) | ((kBefore >> 4) << 14));             // vmcnt(kBefore)
           __builtin_amdgcn_s_barrier();
         }
-        if (t >= kRequest && (t - kRequest) % kEvery == 0 && (t - kRequest) / kEvery < 16) {
+        if (t >= kRequest && (t - kRequest) % kEvery == 0 && (t - kRequest) / kEvery < NR) {
           const int r = (t - kRequest) / kEvery;
-          if (r < 8) request(da, oa.voff[r], dst + (unsigned)(r * 1024));
-          else request(db, ob.voff[r - 8], dst + (unsigned)(OPB + (r - 8) * 1024));
+          if (r < MI) request(da, oa.voff[r], dsta + (unsigned)(r * 1024));
+          else request(db, ob.voff[r - MI], dst + (unsigned)(OPB + (r - MI) * 1024));
         }
-        if (t >= kLanded && (t - kLanded) % 2 == 0 && t < kLanded + 32) {
+        if (t >= kLanded && (t - kLanded) % 2 == 0 && t < kLanded + 2 * NR) {
           const int r = (t - kLanded) / 2;
-          if (r < 8) ax[r] = oa.read(there, r, 0);
-          else bx[r - 8] = ob.read(there + OPB, r - 8, 0);
+          if (r < MI) ax[r] = oa.read(there, r, 0);
+          else bx[r - MI] = ob.read(there + OPB, r - MI, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     };
     half(std::integral_constant<int, 0>{});
-    half(std::integral_constant<int, 64>{});
+    half(std::integral_constant<int, 8 * MI>{});
     ca.advance(astep);
     cb.advance(bstep);
     st ^= 1;
@@ -1169,7 +1174,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       };
 #pragma unroll
-      for (int b = 0; b < 16; ++b) {
+      for (int b = 0; b < 2 * MI; ++b) {
         const int i = b >> 1, h = b & 1, row0 = it.m0 + wm + 16 * i, col = out_col(h);
         const bool ok = col < ncols;
         u32x4 res[2] = {};
@@ -1343,9 +1348,9 @@ mosaic_status launch_mfma(hipStream_t s, int quota, int M, int N, int K, const b
 template <bool A_KC, bool B_KC> constexpr bool w4_form() { return A_KC || !B_KC; }
 template <bool A_KC, bool B_KC> bool w4_takes(int64_t K) { return w4_form<A_KC, B_KC>() && K >= 128 && (!(A_KC || B_KC) || K % 64 == 0); }
 
-template <bool A_KC, bool B_KC, int EPI>
+template <bool A_KC, bool B_KC, int EPI, int MI = 8>
 mosaic_status launch_w4_epi(hipStream_t s, int quota, const W4Args& p, int pieces) {
-  auto kern = gemm_bf16_w4_kernel<A_KC, B_KC, EPI>;
+  auto kern = gemm_bf16_w4_kernel<A_KC, B_KC, EPI, MI>;
   static std::once_flag attr_once;
   static hipError_t attr_rc = hipSuccess;
   std::call_once(attr_once, [&] {
@@ -1367,7 +1372,8 @@ mosaic_status launch_w4_epi(hipStream_t s, int quota, const W4Args& p, int piece
 
 // Tiles [tile_begin, tile_begin + tile_count) of the 256x256 tile list (tile_count < 0: all from
 // tile_begin on); pieces > 1: each cut into that many pieces of the contraction, added by a second pass.
-template <bool A_KC, bool B_KC>
+// MI < 8: tiles of 32 * MI rows, the whole list.
+template <bool A_KC, bool B_KC, int MI = 8>
 mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, bf16* C,
                         int64_t ldc, const bf16* bias, const bf16* R, uint32_t a_bytes, uint32_t b_bytes, uint32_t c_bytes, int tile_begin,
                         int tile_count, const ActArgs& aa, int pieces = 1, float* P = nullptr) {
@@ -1375,7 +1381,7 @@ mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf1
   p.A = A; p.B = B; p.C = C; p.bias = bias; p.R = R; p.P = P; p.C2 = aa.C2;
   p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldc2 = aa.ldc2;
   p.a_bytes = a_bytes; p.b_bytes = b_bytes; p.c_bytes = c_bytes; p.c2_bytes = aa.c2_bytes; p.gu_f = aa.gu_f;
-  p.tiles_m = (int)ceil_div(M, 256); p.tiles_n = (int)ceil_div(N, 256);
+  p.tiles_m = (int)ceil_div(M, 32 * MI); p.tiles_n = (int)ceil_div(N, 256);
   p.tile_begin = tile_begin;
   p.tile_count = tile_count < 0 ? p.tiles_m * p.tiles_n - tile_begin : tile_count;
   if (p.tile_count <= 0) return MOSAIC_OK;
@@ -1385,12 +1391,12 @@ mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf1
     if (pieces > 1) return launch_w4_epi<A_KC, B_KC, W4_SPLIT>(s, quota, p, pieces);
   }
   if constexpr (A_KC && !B_KC) {
-    if (aa.act == ACT_GELU) return launch_w4_epi<A_KC, B_KC, W4_GELU>(s, quota, p, 1);
-    if (aa.act == ACT_SWIGLU) return launch_w4_epi<A_KC, B_KC, W4_SWIGLU>(s, quota, p, 1);
-    if (bias && !R) return launch_w4_epi<A_KC, B_KC, W4_BIAS>(s, quota, p, 1);
+    if (aa.act == ACT_GELU) return launch_w4_epi<A_KC, B_KC, W4_GELU, MI>(s, quota, p, 1);
+    if (aa.act == ACT_SWIGLU) return launch_w4_epi<A_KC, B_KC, W4_SWIGLU, MI>(s, quota, p, 1);
+    if (bias && !R) return launch_w4_epi<A_KC, B_KC, W4_BIAS, MI>(s, quota, p, 1);
   }
-  if (R || bias) return launch_w4_epi<A_KC, B_KC, W4_RES>(s, quota, p, 1);
-  return launch_w4_epi<A_KC, B_KC, W4_PLAIN>(s, quota, p, 1);
+  if (R || bias) return launch_w4_epi<A_KC, B_KC, W4_RES, MI>(s, quota, p, 1);
+  return launch_w4_epi<A_KC, B_KC, W4_PLAIN, MI>(s, quota, p, 1);
 }
 
 // A/B switches for kernel timing, compiled in only with -DMOSAIC_TUNING (never in the library
@@ -1527,12 +1533,15 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
   const int launch_quota = quota;
   quota = tile_queue_sure_cus(quota);
   const int64_t t128 = part ? 4 * t256 : ceil_div(M, 128) * ceil_div(N, 128);
+  // share of the board's CUs that a round of `tiles` leaves idle: the others run faster for it
+  auto idle = [&](int64_t tiles) { return (double)(quota - tiles) / 256.0; };
   auto cost_small = [&](int64_t tiles) {       // 128x128 tiles on `quota` CUs
     const int64_t full = tiles / (2 * (int64_t)quota), rem = tiles % (2 * (int64_t)quota);
     // a CU shared by two workgroups finishes both in about 2 x 1.35 units (more when the
     // operands need the transposing LDS writes), a workgroup alone in 1.6
     constexpr double pen = (A_KC && B_KC) ? 1.3 : (!A_KC && !B_KC) ? 1.8 : 1.45;
-    return (double)full * 2.0 * pen + (rem == 0 ? 0.0 : rem <= quota ? 1.2 * pen : 2.0 * pen);
+    const double alone = A_KC ? 1.5 - 0.45 * idle(rem) : 1.2 * pen;
+    return (double)full * 2.0 * pen + (rem == 0 ? 0.0 : rem <= quota ? alone : 2.0 * pen);
   };
   // 256x256 tiles go to the four-wave kernel where it takes the product; a round of it takes
   // about 3.5 units where the eight-wave kernel takes 4 (9216 x 1024 x 3072 forward, 1.7 rounds: 52 us in
@@ -1540,9 +1549,42 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
   const bool w4 = w4_takes<A_KC, B_KC>(K) && w4_enabled();
   const double round256 = w4 ? 3.5 : 4.0;
   const int64_t whole = t256 / quota, rest = t256 % quota;
-  const double cost256 = (double)ceil_div(t256, quota) * round256;
+  auto cost_w4 = [&](int64_t tiles, double round) {
+    const int64_t rem = tiles % quota;
+    return round * ((double)(tiles / quota) + (rem ? 1.0 - 0.39 * idle(rem) : 0.0));
+  };
+  const double cost256 = A_KC && w4 && whole > 0 ? cost_w4(t256, round256) : (double)ceil_div(t256, quota) * round256;
   const double cost128 = cost_small(t128);
   const double cost_mix = (whole > 0 && rest > 0) ? (double)whole * round256 + cost_small(4 * rest) + 0.15 : 1e30;
+  // Tiles of 224, 192 or 160 rows: where tiles of 256 leave many CUs without one in the last (or only)
+  // round, lower ones fill it.  In the units above a round takes 3.15, 2.8 or 2.57 (3.5 for 256 rows: a
+  // lower tile reads its weight-side fragments for fewer instructions), less 0.39 of it times the
+  // share of the board that it leaves idle (which also has 8192 x 2048 x 11264, 5.5 rounds of 256 rows, end
+  // in half a round of large tiles, 274 us, not in quarter tiles, 284).  An activation's epilogue wants all CUs: with
+  // fewer tiles than CUs the quarter tiles keep it (1568 x 768 x 3072 with GELU 21.5 us, 23.9 in 160 rows).
+  // Measured, plan with 256 rows -> this: forward 9216 x 4096 x 1024 (144 tiles -> 232 of 160 rows)
+  // 74 -> 63 us, 9216 x 1024 x 1024 25.6 -> 21.9; input gradient 9216 x 1024 x 4096 73 -> 62; forward
+  // 8192 x 2048 x 3072 (1.5 rounds -> 444 tiles of 224) 93 -> 82; 9216 x 1024 x 4096 (2.25 rounds ->
+  // 768 tiles of 192) 73 -> 68; left alone: 12000 x 1280 x 1280, 235 tiles, 34 us, 42 and more in lower ones.
+  int mi = 8;
+  if constexpr (A_KC) {
+    if (w4 && forced_tile() == 0) {
+      double best = std::min(std::min(cost_w4(t256, round256), cost128), cost_mix);
+      for (int m = 7; m >= 5; --m) {
+        const int64_t tiles = ceil_div(M, 32 * m) * ceil_div(N, 256);
+        if (aa.act != ACT_NONE && tiles < quota) continue;
+        const double c = cost_w4(tiles, m == 7 ? 3.15 : m == 6 ? 2.8 : 2.57);
+        if (c < best) { best = c; mi = m; }
+      }
+    }
+    if (forced_tile() >= 5 && forced_tile() <= 7 && w4) mi = forced_tile();
+    auto low = [&](auto rows) {
+      return launch_w4<A_KC, B_KC, decltype(rows)::value>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes, 0, -1, aa);
+    };
+    if (mi == 7) return low(std::integral_constant<int, 7>{});
+    if (mi == 6) return low(std::integral_constant<int, 6>{});
+    if (mi == 5) return low(std::integral_constant<int, 5>{});
+  }
   int plan = cost256 <= cost128 ? (cost256 <= cost_mix ? 256 : 0) : (cost128 <= cost_mix ? 128 : 0);
   if (forced_tile() == 128 || forced_tile() == 256) plan = forced_tile();
   if (forced_tile() == 1 && whole > 0 && rest > 0) plan = 0;

@@ -85,10 +85,12 @@ def test_weight_gradient_of_few_tiles(mb, T, k, n, note):
 
 @pytest.mark.parametrize("T,k,n", [(510, 128, 504), (255, 192, 1016), (768, 320, 512), (1000, 1088, 768),      # forward: contraction k
                                    (510, 248, 128), (1000, 760, 192), (249, 1024, 1088),                       # input gradient: n
-                                   (72, 504, 760), (136, 256, 1024), (1000, 512, 504)])                        # weight gradient: T, any length
+                                   (72, 504, 760), (136, 256, 1024), (1000, 512, 504),                         # weight gradient: T, any length
+                                   (150, 192, 504), (330, 128, 1016), (181, 192, 512), (215, 320, 256), (430, 128, 768),
+                                   (160, 504, 128), (192, 256, 320), (224, 248, 192), (670, 256, 256)])        # tiles of 160, 192 and 224 rows
 def test_large_tiles_agree_with_small_ones(mb, T, k, n):
-    """On the whole device these products take 128 x 128 tiles, on one CU 256 x 256 ones (where a form fits
-    them: otherwise both runs take small tiles), several to a workgroup: two and more K-tiles of 64, odd counts, a contraction that ends in
+    """On the whole device these products take 128 x 128 tiles, on one CU 256 columns by 256, 224, 192 or 160
+    rows (where a form fits them: otherwise both runs take small tiles), several to a workgroup: two and more K-tiles of 64, odd counts, a contraction that ends in
     mid K-tile, ragged rows and columns, every epilogue."""
     s = 7600 + T + k + n
     X, W, b, R, dY = [quantize(synth.normal(s + i, sh, 0, sd), "bf16") for i, (sh, sd) in
