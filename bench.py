@@ -664,7 +664,7 @@ def main():
         for _ in range(3):
             dst.copy_(src)
         torch.cuda.synchronize()
-        print(json.dumps({"kernel": "gemm_bf16_kernel", "shape": [Tl, hl, 2 * fl], "ms": gms,
+        print(json.dumps({"kernel": "gemm_bf16_w4_kernel", "shape": [Tl, hl, 2 * fl], "ms": gms,
                           "tflops": {k: gflops / v / 1e9 for k, v in gms.items()}}))
         return
     bw = bandwidth_kernels(mb, Tl, hl, fl, reps=20)

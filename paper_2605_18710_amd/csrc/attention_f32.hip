@@ -15,7 +15,7 @@
 // kernel is one chain of load latency, products and softmax per streamed block.  The streamed
 // rows of the next block are requested before the current block's products, and the second
 // reading of the block's rows (in the other orientation) is in flight under them.  At B2 N128 H4
-// d32: forward 29 -> 9 us, dQ 25 -> 9, dK/dV 41 -> 10 against workgroups of 16 rows that formed
+// d32: forward 29 -> 10.1 us, dQ 25 -> 10.7, dK/dV 41 -> 13.7 against workgroups of 16 rows that formed
 // each score by scalar FMA over LDS (launches of 4.5 us included).
 #include <algorithm>
 #include "kernels.h"

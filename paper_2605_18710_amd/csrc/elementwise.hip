@@ -570,7 +570,7 @@ __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(const T* __res
 // patches) start on 16-byte boundaries and the matrix-core product takes them.  A thread writes one
 // 16-byte piece of a row; its pixels are neighbours, so the 2-byte reads hit the cache.  I: index
 // type (32 bits where they hold every piece: a 64-bit division per element took the 26 us that
-// this pass spent on 16 images of 336 x 336; with it in 32 bits, once per piece, it takes 10).
+// this pass spent on 16 images of 336 x 336; with it in 32 bits, once per piece, it takes 11).
 template <typename T, typename I>
 __global__ __launch_bounds__(kThreads) void unfold_kernel(const T* __restrict__ img, T* __restrict__ out,
                                                           int B, int side, int patch, int ld) {
@@ -595,6 +595,7 @@ __global__ __launch_bounds__(kThreads) void unfold_kernel(const T* __restrict__ 
 
 // y[b, t, :] += pos[t, :].  Work item = (sample, block of kThreads pieces of the N x h table): one
 // division per item.  V elements per access: 16 bytes, or one for tensors that are not 16-byte aligned.
+// Bound by memory: 16 x 576 x 1024 in bf16 12 us one element at a time -> 7.5, 8 x 1500 x 1280 20 -> 14.
 template <typename T, int V>
 __global__ __launch_bounds__(kThreads) void add_pos_kernel(const T* __restrict__ pos, T* __restrict__ y, int B, int64_t per, int blocks) {
   typedef typename Pack<T, V>::type vec;
@@ -609,7 +610,8 @@ __global__ __launch_bounds__(kThreads) void add_pos_kernel(const T* __restrict__
   }
 }
 
-// dpos[t, :] = sum over samples in ascending order; four samples' pieces are requested together
+// dpos[t, :] = sum over samples in ascending order; four samples' pieces are requested together.
+// Bound by memory: 16 x 576 x 1024 in bf16 9.6 us one element at a time -> 4.3, 8 x 1500 x 1280 19 -> 10.
 template <typename T, int V>
 __global__ __launch_bounds__(kThreads) void pos_grad_kernel(const T* __restrict__ dy, T* __restrict__ dpos, int B, int64_t per) {
   typedef typename Pack<T, V>::type vec;

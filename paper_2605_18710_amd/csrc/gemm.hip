@@ -899,12 +899,13 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
 
 // ------------------------------------------------------------------ four-wave kernel
 // 256x256x64 tiles, four waves of 128x128, v_mfma_f32_16x16x32_bf16, for every form whose
-// K-contiguous operands have a contraction of whole K-tiles (K a multiple of 64).
+// K-contiguous operands have a contraction of whole K-tiles (K a multiple of 64).  Where the row operand is
+// K-contiguous the tile may be 32 * MI rows high, MI = 8, 7, 6 or 5 (launch_mfma_shape says when).
 //
 // What bounds it: on the whole chip the board's power.  Registers only, random data, the
 // 16x16x32 instruction delivers 1830 TFLOP/s and the 32x32x16 one 1760 (it reads and writes twice
 // the accumulator bytes per flop); around it the kernel spends as little as it can: a wave tile of
-// 128x128 reads 1 LDS byte per 64 flops (half of what 128x64 wave tiles read), a K-tile of 64
+// 128x128 reads 1 LDS byte per 64 flops (two thirds of what 128x64 wave tiles read), a K-tile of 64
 // brings whole 128-byte lines, operands go HBM -> LDS without passing registers, 128 matrix instructions
 // come with about 135 others per K-tile.
 //   LDS: two stages of 64 KB.  The fragments of a K-tile's second half are read under its first 16
@@ -1401,8 +1402,8 @@ mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf1
 
 // A/B switches for kernel timing, compiled in only with -DMOSAIC_TUNING (never in the library
 // that ships): MOSAIC_GEMM_W4=0 sends the 256x256 tiles back to the eight-wave kernel,
-// MOSAIC_GEMM_TILE=256 / 128 / 1 forces the all-256, all-128 or mixed tile plan (the bits are
-// the same either way); MOSAIC_SPLITK=n forces the piece count of a weight gradient's cut tail
+// MOSAIC_GEMM_TILE=256 / 128 / 1 forces the all-256, all-128 or mixed tile plan, 7 / 6 / 5 tiles of
+// 224 / 192 / 160 rows (the bits are the same either way); MOSAIC_SPLITK=n forces the piece count of a weight gradient's cut tail
 // (0: no cut; the bits differ with n).
 #ifdef MOSAIC_TUNING
 bool w4_enabled() { const char* e = getenv("MOSAIC_GEMM_W4"); return !e || atoi(e) != 0; }
@@ -1476,6 +1477,7 @@ int splitk_plan(int64_t M, int64_t N, int64_t K, int* first) {
 //   9216 x 1024 x 1024  36 -> 28 (59 -> 70), 64 tiles in 4 pieces;   24000 x 240 x 1280  61 -> 29 (61 -> 67)
 //   5000 x 1024 x 3072  46 -> 36 (101 -> 88);   12000 x 1280 x 1280  stays, 50 (130): small tiles 48 (152)
 //   12000 x 1280 x 3840  stays, 109: 300 small tiles, uncut, take 154
+// (the cut 256x256 tiles on the eight-wave kernel; on the four-wave one 104 us in the last of these, 51 in the one before)
 int wgrad_tiles(int64_t M, int64_t N, int64_t K, int reserved, int* te) {
   const double k = (double)K, t256 = (double)(ceil_div(M, 256) * ceil_div(N, 256)), t128 = (double)(ceil_div(M, 128) * ceil_div(N, 128));
   const double reduce_us = 4.0, bytes_us = (double)M * (double)N * 4.0 / 4.5e6, n = t256 * reserved;
@@ -1524,7 +1526,7 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
   }
   // Tile shape only decides which workgroup computes an element, never its bits.  Large
   // tiles halve LDS traffic per MFMA; small tiles fill the CUs when there are few large
-  // ones.  Three plans, priced in units of a quarter of a 256x256 tile's time on one CU:
+  // ones.  Plans, priced in units of a quarter of a 256x256 tile's time on one CU (eight-wave kernel):
   //   all-256: whole rounds of 256x256 tiles, the last one possibly mostly idle;
   //   all-128: 128x128 tiles, two workgroups per CU;
   //   mixed:   the whole rounds with the large kernel, then the tiles of the partial round
@@ -1538,7 +1540,8 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
   auto cost_small = [&](int64_t tiles) {       // 128x128 tiles on `quota` CUs
     const int64_t full = tiles / (2 * (int64_t)quota), rem = tiles % (2 * (int64_t)quota);
     // a CU shared by two workgroups finishes both in about 2 x 1.35 units (more when the
-    // operands need the transposing LDS writes), a workgroup alone in 1.6
+    // operands need the transposing reads); a workgroup alone takes 1.5 with all CUs at work and 1.05
+    // with few (64-deep K-tiles: input gradient 4096 x 4096 x 1024, 256 tiles, 38 us; 1568 x 3072 x 768, 78 tiles, 23)
     constexpr double pen = (A_KC && B_KC) ? 1.3 : (!A_KC && !B_KC) ? 1.8 : 1.45;
     const double alone = A_KC ? 1.5 - 0.45 * idle(rem) : 1.2 * pen;
     return (double)full * 2.0 * pen + (rem == 0 ? 0.0 : rem <= quota ? alone : 2.0 * pen);

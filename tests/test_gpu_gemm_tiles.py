@@ -66,7 +66,7 @@ def test_k_tile_depths_agree(mb, T, k, n):
     (12000, 1280, 1280, "large tiles stay cut"),
 ])
 def test_weight_gradient_of_few_tiles(mb, T, k, n, note):
-    """Tile size and pieces follow the shape: same bits at every quota, every column against the checker."""
+    """Tile size and pieces follow the shape: same bits at every quota, every column against the oracle."""
     X, dY = quantize(synth.normal(7300, (T, k)), "bf16"), quantize(synth.normal(7301, (T, n)), "bf16")
     X_, dY_ = to_dev(X, "bf16"), to_dev(dY, "bf16")
     nbytes = mb.linear_wgrad_scratch_bytes(T, k, n)
