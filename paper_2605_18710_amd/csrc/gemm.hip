@@ -1048,7 +1048,12 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(dst), "v"(off), "s"(d) : "m0");
   };
   auto request_tile = [&](int st) {
-    const i32x4 da = ca.desc(true), db = cb.desc(true);
+    i32x4 da = ca.desc(true), db = cb.desc(true);
+    // A memory instruction may read a scalar register that the vector unit wrote (v_readfirstlane) five wait
+    // states later at the earliest, and the compiler does not see the requests: both descriptors
+    // pass through these five, so that no part of them is formed later.
+    asm volatile("s_nop 4" : "+s"(da), "+s"(db));
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < MI; ++j) request(da, oa.voff[j], adst + (unsigned)(st * kW4Stage + j * 1024));
 #pragma unroll
@@ -1095,6 +1100,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
   auto step = [&]() {
     const lds_byte* const here = lds + st * kW4Stage;
     const lds_byte* const there = lds + (st ^ 1) * kW4Stage;
+    // formed here, ahead of the scheduling barrier, and first read kRequest matrix instructions on: far beyond the
+    // five wait states that request_tile waits out
     const i32x4 da = ca.desc(live), db = cb.desc(live);
     const unsigned dst = wdst + (unsigned)(st * kW4Stage), dsta = adst + (unsigned)(st * kW4Stage);
     __builtin_amdgcn_sched_barrier(0);
