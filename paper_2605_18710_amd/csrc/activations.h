@@ -1,55 +1,12 @@
 // Activation formulas shared by the elementwise kernels and the GEMM epilogues that apply them
-// in place of a separate pass: one definition per storage type, so both roads give the same bits.
-//
-// fp32 tensors take the math library's erff and expf.  For bf16 tensors those made the passes
-// ALU-bound (about 70 instructions per element: the GELU backward of 12000 x 5120 ran at 3.3 TB/s,
-// 111 us; now 4.6 TB/s, 83 us), so the normal distribution is evaluated directly, in fp32, from one exponential and one
-// reciprocal:  Phi(-a) = exp(-a^2/2) q(t),  t = 1 / (1 + a/4),  a >= 0, with q a polynomial of degree 10
-// without constant term, fitted to exp(a^2/2) Phi(-a) by iteratively reweighted least squares
-// (relative error of the fit 2e-8).  Evaluated in fp32 against 64 bits: 1.7e-7 absolute, 2e-6 relative
-// down to z = -6, where 1 + erff(z/sqrt 2) has lost every digit; bf16 storage rounds at 2e-3.
+// in place of a separate pass: one definition, so both roads give the same bits.
 #pragma once
 #include <hip/hip_runtime.h>
 
-template <typename T> struct Activation {               // fp32
-  static __device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-  static __device__ __forceinline__ float gelu_grad(float z) {
-    return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
-  }
-  static __device__ __forceinline__ float sigmoid(float z) { return 1.0f / (1.0f + expf(-z)); }
-};
-
-template <> struct Activation<__bf16> {
-  // Phi(z), and exp(-z^2/2)
-  static __device__ __forceinline__ float normal_cdf(float z, float* e) {
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.25f, fabsf(z), 1.0f));
-    float q = 0.0206333108f;
-    q = fmaf(q, t, -0.0846438085f);
-    q = fmaf(q, t, 0.102581691f);
-    q = fmaf(q, t, -0.0387690502f);
-    q = fmaf(q, t, 0.0679129702f);
-    q = fmaf(q, t, 0.0574573237f);
-    q = fmaf(q, t, 0.0819243434f);
-    q = fmaf(q, t, 0.0934292733f);
-    q = fmaf(q, t, 0.0997384218f);
-    q = fmaf(q, t, 0.0997355333f);
-    *e = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
-    const float tail = q * t * *e;
-    return z > 0.f ? 1.0f - tail : tail;
-  }
-  static __device__ __forceinline__ float gelu(float z) { float e; return z * normal_cdf(z, &e); }
-  static __device__ __forceinline__ float gelu_grad(float z) {
-    float e;
-    const float c = normal_cdf(z, &e);
-    return fmaf(z * e, 0.39894228040143268f, c);
-  }
-  static __device__ __forceinline__ float sigmoid(float z) {
-    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z * -1.4426950408889634f));
-  }
-};
-
-template <typename T> __device__ __forceinline__ float gelu_f(float z) { return Activation<T>::gelu(z); }
-template <typename T> __device__ __forceinline__ float gelu_grad_f(float z) { return Activation<T>::gelu_grad(z); }
-template <typename T> __device__ __forceinline__ float sigmoid_f(float z) { return Activation<T>::sigmoid(z); }
+__device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
+__device__ __forceinline__ float gelu_grad_f(float z) {
+  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+}
+__device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + expf(-z)); }
 // SwiGLU: silu(gate) * up
-template <typename T> __device__ __forceinline__ float swiglu_f(float gate, float up) { return gate * sigmoid_f<T>(gate) * up; }
+__device__ __forceinline__ float swiglu_f(float gate, float up) { return gate * sigmoid_f(gate) * up; }

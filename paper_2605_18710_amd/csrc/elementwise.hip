@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kThreads) void gelu_fwd_kernel(const T* __restrict_
     Vec16<T> v, o;
     v.load(z + i * VN);
 #pragma unroll
-    for (int k = 0; k < VN; ++k) o.set(k, gelu_f<T>(v.get(k)));
+    for (int k = 0; k < VN; ++k) o.set(k, gelu_f(v.get(k)));
     o.store(a + i * VN);
   }
 }
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kThreads) void gelu_bwd_kernel(const T* __restrict_
     v.load(z + i * VN);
     d.load(da + i * VN);
 #pragma unroll
-    for (int k = 0; k < VN; ++k) o.set(k, d.get(k) * gelu_grad_f<T>(v.get(k)));
+    for (int k = 0; k < VN; ++k) o.set(k, d.get(k) * gelu_grad_f(v.get(k)));
     o.store(dz + i * VN);
   }
 }
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(kThreads) void gelu_bwd_colsum_kernel(const T* __re
     auto one = [&](const Vec16<T>& zv, const Vec16<T>& dv, int64_t r) {
       Vec16<T> o;
 #pragma unroll
-      for (int k = 0; k < VN; ++k) { o.set(k, dv.get(k) * gelu_grad_f<T>(zv.get(k))); acc[k] += o.get(k); }
+      for (int k = 0; k < VN; ++k) { o.set(k, dv.get(k) * gelu_grad_f(zv.get(k))); acc[k] += o.get(k); }
       o.store(dz + r * n + c);
     };
     int64_t r = r0;
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(kThreads) void swiglu_fwd_kernel(const T* __restric
     g.load(gu + r * 2 * f + c);
     u.load(gu + r * 2 * f + f + c);
 #pragma unroll
-    for (int k = 0; k < VN; ++k) o.set(k, swiglu_f<T>(g.get(k), u.get(k)));
+    for (int k = 0; k < VN; ++k) o.set(k, swiglu_f(g.get(k), u.get(k)));
     o.store(a + r * f + c);
   }
 }
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(kThreads) void swiglu_bwd_kernel(const T* __restric
     d.load(da + r * f + c);
 #pragma unroll
     for (int k = 0; k < VN; ++k) {
-      const float z = g.get(k), s = sigmoid_f<T>(z);
+      const float z = g.get(k), s = sigmoid_f(z);
       og.set(k, d.get(k) * u.get(k) * (s * (1.0f + z * (1.0f - s))));
       ou.set(k, d.get(k) * (z * s));
     }

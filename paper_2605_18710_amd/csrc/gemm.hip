@@ -770,7 +770,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
         for (int g = 0; g < 4; ++g) {
           bf16x4 o;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (bf16)swiglu_f<bf16>(zval(i, 0, g, e), zval(i, 1, g, e));
+          for (int e = 0; e < 4; ++e) o[e] = (bf16)swiglu_f(zval(i, 0, g, e), zval(i, 1, g, e));
           *reinterpret_cast<bf16x4*>(patch + wr + ((g ^ wsx) << 4)) = o;
         }
       } else {
@@ -780,7 +780,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
           for (int g = 0; g < 4; ++g) {
             bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)gelu_f<bf16>(zval(i, j, g, e));
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)gelu_f(zval(i, j, g, e));
             *reinterpret_cast<bf16x4*>(patch + wr + (((4 * j + g) ^ wsx) << 4)) = o;
           }
       }
@@ -1211,7 +1211,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
           for (int e = 0; e < 8; ++e) {
             og[e] = (bf16)(gv[e] + (float)bg[e]);
             ou[e] = (bf16)(uv[e] + (float)bu[e]);
-            oc[e] = (bf16)swiglu_f<bf16>((float)og[e], (float)ou[e]);     // of the values as stored
+            oc[e] = (bf16)swiglu_f((float)og[e], (float)ou[e]);     // of the values as stored
           }
           const int row = row0 + prow;
           __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, og), rc, off(row, col, p.ldc, ok), 0, 0);
@@ -1243,7 +1243,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
               if constexpr (EPI == W4_GELU) {
                 bf16x8 a2;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) a2[e] = (bf16)gelu_f<bf16>((float)o[e]);
+                for (int e = 0; e < 8; ++e) a2[e] = (bf16)gelu_f((float)o[e]);
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a2), rc2, off(row, col, p.ldc2, ok), 0, 0);
               }
             }
