@@ -10,3 +10,20 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + expf(-z)); }
 // SwiGLU: silu(gate) * up
 __device__ __forceinline__ float swiglu_f(float gate, float up) { return gate * sigmoid_f(gate) * up; }
+
+// GELU of bf16 numbers from a table in LDS that the workgroup fills with erff itself: the bits of gelu_f.
+// erff is odd and takes 1537 values over the bf16 numbers from 2^-9 to 8.  Below, the factor
+// 1 + erf is so near 1 that z / 2, a bf16 number, is what the product rounds to (entry 0; where z / 2
+// is none, because it is denormal, the factor is 1 in fp32); from 8 on erff is 1 in fp32.  The
+// limits at +-infinity and NaN are those of the formula.
+struct ErfTable {
+  static constexpr int kLow = (118 << 7) - 1, kHigh = 130 << 7;   // bf16 bits: the last number below 2^-9, and 8
+  static constexpr int kEntries = kHigh - kLow + 1;
+  static __device__ __forceinline__ void fill(float* t, int first, int step) {
+    for (int i = first; i < kEntries; i += step) t[i] = i == 0 ? 0.f : erff(__uint_as_float((unsigned)(kLow + i) << 16) * 0.70710678118654752f);
+  }
+  static __device__ __forceinline__ float gelu(const float* t, float z) {     // z: a bf16 number
+    const int u = (int)(__float_as_uint(z) >> 16) & 0x7fff;
+    return 0.5f * z * (1.0f + copysignf(t[min(max(u, kLow), kHigh) - kLow], z));
+  }
+};

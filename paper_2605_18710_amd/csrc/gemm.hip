@@ -945,7 +945,8 @@ struct W4Args {
 enum { W4_PLAIN, W4_BIAS, W4_RES, W4_GELU, W4_SWIGLU, W4_SPLIT };
 constexpr int kW4Stage = 2 * 256 * 64 * 2;                         // both operands of a K-tile
 constexpr int kW4Pitch = 68;                                       // floats per row of the epilogue's patch: 16 rows of 64
-constexpr int kW4Lds = 2 * kW4Stage + 4 * 16 * kW4Pitch * 4;
+constexpr int kW4Patch = 4 * 16 * kW4Pitch * 4;
+constexpr int w4_lds(int epi) { return 2 * kW4Stage + kW4Patch + (epi == W4_GELU ? ErfTable::kEntries * 4 : 0); }
 
 // One operand: what a lane requests of a K-tile, and where its fragments are.
 template <bool KC, bool GU, int NF = 8>
@@ -1070,6 +1071,13 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
   point(it);
   request_tile(0);
   request_tile(1);
+  // 256 values of a tile to a thread: six erff to fill the table instead of 256 (the epilogue of 12000 x 1280 x 5120
+  // takes 10 us of 150; with erff in it, four waves a CU, 83 of 239)
+  float* const erf_table = reinterpret_cast<float*>(smem + 2 * kW4Stage + kW4Patch);
+  if constexpr (EPI == W4_GELU) {
+    ErfTable::fill(erf_table, threadIdx.x, 256);
+    __syncthreads();
+  }
   f32x4 acc[MI][8];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -1243,7 +1251,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
               if constexpr (EPI == W4_GELU) {
                 bf16x8 a2;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) a2[e] = (bf16)gelu_f((float)o[e]);
+                for (int e = 0; e < 8; ++e) a2[e] = (bf16)ErfTable::gelu(erf_table, (float)o[e]);     // of the value as stored
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a2), rc2, off(row, col, p.ldc2, ok), 0, 0);
               }
             }
@@ -1362,13 +1370,13 @@ mosaic_status launch_w4_epi(hipStream_t s, int quota, const W4Args& p, int piece
   static std::once_flag attr_once;
   static hipError_t attr_rc = hipSuccess;
   std::call_once(attr_once, [&] {
-    attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kW4Lds);
+    attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, w4_lds(EPI));
   });
   MOSAIC_HIP(attr_rc);
   TileQueueArgs tq;
   int grid;
   MOSAIC_TRY(tile_queue_plan(s, quota, 1, (int64_t)p.tile_count * pieces, 0, false, &tq, &grid));
-  kern<<<grid, 256, kW4Lds, s>>>(p, tq);
+  kern<<<grid, 256, w4_lds(EPI), s>>>(p, tq);
   MOSAIC_LAUNCH_CHECK();
   if constexpr (EPI == W4_SPLIT) {
     splitk_reduce_kernel<256><<<grid_for(quota, 8, (int64_t)p.tile_count * 64), 256, 0, s>>>(p.P, p.C, p.M, p.N, p.ldc, pieces, p.tiles_m, p.tiles_n,

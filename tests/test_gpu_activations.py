@@ -51,3 +51,23 @@ def test_every_bf16_value():
     for k in ("gelu", "swiglu"):
         y = got["bf16"][k].cpu().double()
         assert y[at(float("inf"))] == float("inf") and y[at(0.0)] == 0.0 and bool(y[zd.isnan()].isnan().all()), k
+
+
+@pytest.mark.parametrize("quota", [256, 1])
+def test_every_finite_bf16_value_through_the_epilogue(quota):
+    """The product of unit rows and a weight that holds every finite bf16 value, on one CU in 256-wide tiles
+    (its epilogue reads erf from a table), on the whole device in small ones (erff)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_18710_amd import binding as mb
+    T, k, n = 130, 128, 512
+    w = torch.arange(N, dtype=torch.int32).sub(32768).to(torch.int16).view(torch.bfloat16).cuda().view(k, n)
+    w = torch.where(w.isfinite(), w, torch.zeros_like(w)).contiguous()
+    x = torch.zeros(T, k, dtype=torch.bfloat16, device="cuda")
+    x[:k] = torch.eye(k, dtype=torch.bfloat16, device="cuda")
+    z, a, want = [torch.full((T, n), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    mb.op_linear_act_fwd(None, quota, "bf16", mb.GELU, T, k, n, x, w, None, z, a)
+    mb.op_gelu_fwd(None, 256, "bf16", T * n, z, want)
+    torch.cuda.synchronize()
+    assert bool((z[:k] == w).all()) and bool((z[k:] == 0).all())
+    assert same(a, want)
