@@ -42,6 +42,7 @@
 #include <mutex>
 #include <type_traits>
 #include "activations.h"
+#include "gemm_plan.h"
 #include "kernels.h"
 #include "tile_queue.h"
 
@@ -248,13 +249,13 @@ static inline int row_block_for(int64_t K, int64_t tiles_m) {
   return (int)std::min<int64_t>(rb, (tiles_m + 3) / 4 * 4);
 }
 
-// One unit of work: an output tile, or (SPLITK) one K-piece of an output tile.
+// One unit of work: an output tile, or (PIECES_APART) one K-piece of an output tile.
 struct WorkItem {
   int m0, n0, kt0, kt_end, split, tl;      // tl: position of the item's coarse tile in this launch's range
   bool valid;
 };
 
-// SPLITK: the K range is cut into `ksplit` contiguous pieces of `ktiles_per` K-tiles; piece s
+// PIECES_APART: the K range is cut into `ksplit` contiguous pieces of `ktiles_per` K-tiles; piece s
 // of the launch's t-th tile is accumulated by its own workgroup and stored in fp32 to
 // P[s][t][BM][BN]; a second kernel adds the pieces in ascending s.  Which tiles are cut and
 // into how many pieces depends on the problem shape only.
@@ -280,14 +281,18 @@ struct ActArgs {
   int row_block = 1 << 20;   // tile rows per super-block of the tile order (set by the launcher)
 };
 
-template <int BM, int BN, int NWM, int NWN, bool A_KC, bool B_KC, bool SPLITK, int ACT = ACT_NONE, int BKT = BK>
+// PIECES_CHAINED: one workgroup takes the pieces of its tile one after the other and adds them in registers,
+// in the order and with the additions of the second kernel: the same bits as PIECES_APART, no scratch.
+constexpr int PIECES_NONE = 0, PIECES_APART = 1, PIECES_CHAINED = 2;
+template <int BM, int BN, int NWM, int NWN, bool A_KC, bool B_KC, int PIECES, int ACT = ACT_NONE, int BKT = BK>
 __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
     const bf16* __restrict__ A, const bf16* __restrict__ B, bf16* __restrict__ C,
     const bf16* __restrict__ bias, const bf16* __restrict__ R, int M, int N, int K,
     int64_t lda, int64_t ldb, int64_t ldc, uint32_t a_bytes, uint32_t b_bytes, uint32_t c_bytes,
     int tiles_m, int tiles_n, int tile_begin, int tile_count, int sub, int ksplit, int ktiles_per,
     float* __restrict__ P, TileQueueArgs tq, ActArgs aa) {
-  static_assert(ACT == ACT_NONE || (A_KC && !B_KC && !SPLITK), "activation epilogues exist for the forward form");
+  constexpr bool SPLITK = PIECES == PIECES_APART, CHAINED = PIECES == PIECES_CHAINED;
+  static_assert(ACT == ACT_NONE || (A_KC && !B_KC && PIECES == PIECES_NONE), "activation epilogues exist for the forward form");
   constexpr int NT = 64 * NWM * NWN;
   constexpr int WM = BM / NWM, WN = BN / NWN;   // wave tile
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -871,11 +876,27 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
     si = si + 1 >= NS ? 0 : si + 1;
     ++lkt; ++kt;
   };
+  f32x16 sum[CHAINED ? TM : 1][CHAINED ? TN : 1];     // of the finished pieces of the tile
+  int piece_end = CHAINED ? ktiles_per : 0;
   while (true) {
     int n = cur.kt_end - kt;
     if (lit.valid) n = min(n, lit.kt_end - lkt);
+    if constexpr (CHAINED) n = min(n, piece_end - kt);
     for (; n > 0; --n) step();
     if (lit.valid && lkt >= lit.kt_end) load_cursor_next_item();
+    if constexpr (CHAINED) {
+      const bool first = piece_end == ktiles_per, last = kt >= cur.kt_end;
+      if (kt == piece_end || last) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            if (!first) acc[i][j] = sum[i][j] + acc[i][j];
+            if (!last) { sum[i][j] = acc[i][j]; acc[i][j] = f32x16{}; }
+          }
+        piece_end = last ? ktiles_per : piece_end + ktiles_per;
+      }
+    }
     if (kt >= cur.kt_end) {
       // an item is claimed under the epilogue when none is drawn ahead
       const bool claim = tq.mode == TQ_QUEUE && !have_drawn && !drained && ahead_ok;
@@ -930,19 +951,18 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
 // Each output element is accumulated in ascending k: same bits as gemm_bf16_kernel's.
 // Measured, whole device, eight-wave kernel (input gradient: a four-wave kernel that staged through
 // registers) -> this: forward 32768 x 4096 x 12288 2525 -> 2300 us (1434 TFLOP/s), 8192 x 5632 x 2048
-// 149 -> 129; with GELU 12000 x 1280 x 5120 192 -> 169, with SwiGLU 8192 x 2048 x 11264 337 -> 317;
+// 149 -> 129; with GELU 12000 x 1280 x 5120 199 -> 151, with SwiGLU 8192 x 2048 x 11264 365 -> 338;
 // input gradient 32768 x 4096 x 22016 4433 -> 3960 (1492 TFLOP/s), 9216 x 4096 x 1024 77 -> 70;
-// weight gradient 4096 x 32768 x 22016 4368 -> 4130, 2048 x 8192 x 11264 318 -> 310.
+// weight gradient 4096 x 32768 x 22016 4268 -> 4000, 2048 x 8192 x 11264 339 -> 331.
 struct W4Args {
   const bf16 *A, *B, *bias, *R;
   bf16 *C, *C2;
-  float* P;
   int M, N, K;
   int64_t lda, ldb, ldc, ldc2;
   uint32_t a_bytes, b_bytes, c_bytes, c2_bytes;
-  int tiles_m, tiles_n, tile_begin, tile_count, row_block, ktiles_per, gu_f;
+  int tiles_m, tiles_n, tile_begin, tile_count, row_block, gu_f;
 };
-enum { W4_PLAIN, W4_BIAS, W4_RES, W4_GELU, W4_SWIGLU, W4_SPLIT };
+enum { W4_PLAIN, W4_BIAS, W4_RES, W4_GELU, W4_SWIGLU };
 constexpr int kW4Stage = 2 * 256 * 64 * 2;                         // both operands of a K-tile
 constexpr int kW4Pitch = 68;                                       // floats per row of the epilogue's patch: 16 rows of 64
 constexpr int kW4Patch = 4 * 16 * kW4Pitch * 4;
@@ -1018,30 +1038,23 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
   const unsigned lds0 = (unsigned)(uintptr_t)lds;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave >> 1) * (16 * MI), wn = (wave & 1) * 128;
-  const int nk_all = (p.K + 63) / 64;
+  const int nk = (p.K + 63) / 64;              // at least two, the depth of the request stream
   const uint32_t astep = A_KC ? 128u : (uint32_t)(64 * p.lda * 2), bstep = B_KC ? 128u : (uint32_t)(64 * p.ldb * 2);
   W4Operand<A_KC, false, MI> oa;
   W4Operand<B_KC, EPI == W4_SWIGLU> ob;
   oa.init(wave, wm, p.lda, 0);
   ob.init(wave, wn, p.ldb, p.gu_f);
 
-  struct Item { int m0, n0, kt0, nk, split, tl; };
+  struct Item { int m0, n0; };
   auto decode = [&](int item) -> Item {
-    Item it;
-    it.split = EPI == W4_SPLIT ? item / p.tile_count : 0;
-    it.tl = item - it.split * p.tile_count;
     int trow, tcol;
-    tile_coords(p.tile_begin + it.tl, p.tiles_m, p.tiles_n, p.row_block, &trow, &tcol);
-    it.m0 = trow * (32 * MI); it.n0 = tcol * 256;
-    it.kt0 = it.split * p.ktiles_per;
-    // at least two K-tiles, the depth of the request stream: what lies past the end reads zeros
-    it.nk = EPI == W4_SPLIT ? max(2, min(nk_all - it.kt0, p.ktiles_per)) : nk_all;
-    return it;
+    tile_coords(p.tile_begin + item, p.tiles_m, p.tiles_n, p.row_block, &trow, &tcol);
+    return {trow * (32 * MI), tcol * 256};
   };
   W4Cursor ca, cb;
   auto point = [&](const Item& it) {
-    ca.set(p.A, (A_KC ? (uint64_t)it.m0 * p.lda * 2 : (uint64_t)it.m0 * 2) + (uint64_t)it.kt0 * astep, p.a_bytes);
-    cb.set(p.B, (B_KC ? (uint64_t)it.n0 * p.ldb * 2 : (uint64_t)(EPI == W4_SWIGLU ? it.n0 : it.n0 * 2)) + (uint64_t)it.kt0 * bstep, p.b_bytes);
+    ca.set(p.A, A_KC ? (uint64_t)it.m0 * p.lda * 2 : (uint64_t)it.m0 * 2, p.a_bytes);
+    cb.set(p.B, B_KC ? (uint64_t)it.n0 * p.ldb * 2 : (uint64_t)(EPI == W4_SWIGLU ? it.n0 : it.n0 * 2), p.b_bytes);
   };
   const unsigned wdst = lds0 + (unsigned)wave * 8192, adst = lds0 + (unsigned)wave * (MI * 1024);
   auto request = [&](const i32x4& d, unsigned off, unsigned dst) {
@@ -1153,7 +1166,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
   const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.R, p.R ? p.c_bytes : 0u), rbias = make_rsrc(p.bias, p.bias ? (uint32_t)p.N * 2u : 0u);
   while (true) {
     settle();
-    for (int n = it.nk - 2; n > 0; --n) step();
+    for (int n = nk - 2; n > 0; --n) step();
     // the last K-tile of this item has been requested: the requests move on to the next item
     const unsigned entry = tq_claim_ahead(tq, qc);
     const int next = tq_next(tq, qc, entry, &mail);
@@ -1176,7 +1189,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
       const int ncols = GU ? p.gu_f : p.N;
       auto off = [&](int row, int col, int64_t ld, bool ok) -> int { return ok ? (int)(unsigned)(((int64_t)row * ld + col) * 2) : (int)kOob; };
       u32x4 bias_[2] = {}, bias_up[2] = {};
-      if constexpr (EPI != W4_PLAIN && EPI != W4_SPLIT) {
+      if constexpr (EPI != W4_PLAIN) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int col = out_col(h);
@@ -1231,13 +1244,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
             const int row = row0 + prow + 8 * q;
             float v[8];
             row8(prow + 8 * q, pcol, v);
-            if constexpr (EPI == W4_SPLIT) {
-              if (row < p.M && ok) {
-                float* dst = p.P + ((int64_t)it.split * p.tile_count + it.tl) * 65536 + (row - it.m0) * 256 + (col - it.n0);
-                *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-                *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
-              }
-            } else {
+            {
               const bf16x8 bv = __builtin_bit_cast(bf16x8, bias_[h]), rv = __builtin_bit_cast(bf16x8, res[q]);
               bf16x8 o;
 #pragma unroll
@@ -1308,11 +1315,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 
 // One launch of the MFMA kernel over coarse tiles [tile_begin, tile_begin + tile_count) of the
 // panel-major list of (sub*BM) x (sub*BN) tiles; tile_count < 0 means all of them.
-template <int BM, int BN, int NWM, int NWN, bool A_KC, bool B_KC, bool SPLITK = false, int ACT = ACT_NONE, int BKT = BK>
+// kper: k-values of a piece (PIECES), whole K-tiles of 32.
+template <int BM, int BN, int NWM, int NWN, bool A_KC, bool B_KC, int PIECES = PIECES_NONE, int ACT = ACT_NONE, int BKT = BK>
 mosaic_status launch_mfma(hipStream_t s, int quota, int M, int N, int K, const bf16* A, int64_t lda,
                           const bf16* B, int64_t ldb, bf16* C, int64_t ldc, const bf16* bias, const bf16* R,
                           uint32_t a_bytes, uint32_t b_bytes, uint32_t c_bytes, int ksplit = 1,
-                          int ktiles_per = 0, float* P = nullptr, int sub = 1, int tile_begin = 0,
+                          int kper = 0, float* P = nullptr, int sub = 1, int tile_begin = 0,
                           int tile_count = -1, const ActArgs& aa = ActArgs()) {
   // 128x128 tiles that all get a CU to themselves take 64-deep K-tiles: the five stages then fill
   // the LDS (two workgroups per CU would not fit), K-contiguous operands come in whole 128-byte
@@ -1322,13 +1330,13 @@ mosaic_status launch_mfma(hipStream_t s, int quota, int M, int N, int K, const b
   // weight gradient 768 x 1568 x 768 15.5 -> 14.1.  With more tiles than CUs two workgroups of
   // 32-deep tiles share a CU and cover each other's waits.  The order of the sum is the same.
   if constexpr (BM == 128 && BKT == BK) {
-    const int64_t it = (tile_count < 0 ? ceil_div(M, BM * sub) * ceil_div(N, BN * sub) - tile_begin : tile_count) * sub * sub * ksplit;
-    if (it <= tile_queue_sure_cus(quota))
-      return launch_mfma<BM, BN, NWM, NWN, A_KC, B_KC, SPLITK, ACT, 64>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes,
-                                                                      ksplit, ktiles_per, P, sub, tile_begin, tile_count, aa);
+    const int64_t it = (tile_count < 0 ? ceil_div(M, BM * sub) * ceil_div(N, BN * sub) - tile_begin : tile_count) * sub * sub * (PIECES == PIECES_APART ? ksplit : 1);
+    if (it <= tile_queue_sure_cus(quota) && (PIECES == PIECES_NONE || kper % 64 == 0))
+      return launch_mfma<BM, BN, NWM, NWN, A_KC, B_KC, PIECES, ACT, 64>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes,
+                                                                      ksplit, kper, P, sub, tile_begin, tile_count, aa);
   }
   constexpr size_t smem = (size_t)NS * (BM + BN) * BKT * 2;
-  auto kern = gemm_bf16_kernel<BM, BN, NWM, NWN, A_KC, B_KC, SPLITK, ACT, BKT>;
+  auto kern = gemm_bf16_kernel<BM, BN, NWM, NWN, A_KC, B_KC, PIECES, ACT, BKT>;
   static std::once_flag attr_once;   // per instantiation; launches come from several host threads
   static hipError_t attr_rc = hipSuccess;
   std::call_once(attr_once, [&] {
@@ -1339,6 +1347,7 @@ mosaic_status launch_mfma(hipStream_t s, int quota, int M, int N, int K, const b
   if (tile_count < 0) tile_count = tiles_m * tiles_n - tile_begin;
   if (tile_count <= 0) return MOSAIC_OK;
   const int wg_per_cu = (BM == 256 || BKT == 64) ? 1 : 2;
+  if constexpr (PIECES != PIECES_APART) ksplit = 1;
   const int64_t items = (int64_t)tile_count * sub * sub * ksplit;
   if (items > INT32_MAX) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "too many output tiles");
   TileQueueArgs tq;
@@ -1349,9 +1358,9 @@ mosaic_status launch_mfma(hipStream_t s, int quota, int M, int N, int K, const b
   // quarter tiles, split tiles) walks the same tile list
   ka.row_block = row_block_for(K, ceil_div((int64_t)M, 256)) * 256 / (BM * sub);
   kern<<<grid, 64 * NWM * NWN, smem, s>>>(A, B, C, bias, R, M, N, K, lda, ldb, ldc, a_bytes, b_bytes, c_bytes,
-                                          tiles_m, tiles_n, tile_begin, tile_count, sub, ksplit, ktiles_per, P, tq, ka);
+                                          tiles_m, tiles_n, tile_begin, tile_count, sub, ksplit, kper / BKT, P, tq, ka);
   MOSAIC_LAUNCH_CHECK();
-  if (SPLITK) {
+  if constexpr (PIECES == PIECES_APART) {
     static_assert(BM == BN, "the reduce kernel walks square tiles");
     const int g2 = grid_for(quota, 8, (int64_t)tile_count * (BM * BM / 1024));
     splitk_reduce_kernel<BM><<<g2, 256, 0, s>>>(P, C, M, N, ldc, ksplit, tiles_m, tiles_n, tile_begin, tile_count, ka.row_block);
@@ -1365,7 +1374,7 @@ template <bool A_KC, bool B_KC> constexpr bool w4_form() { return A_KC || !B_KC;
 template <bool A_KC, bool B_KC> bool w4_takes(int64_t K) { return w4_form<A_KC, B_KC>() && K >= 128 && (!(A_KC || B_KC) || K % 64 == 0); }
 
 template <bool A_KC, bool B_KC, int EPI, int MI = 8>
-mosaic_status launch_w4_epi(hipStream_t s, int quota, const W4Args& p, int pieces) {
+mosaic_status launch_w4_epi(hipStream_t s, int quota, const W4Args& p) {
   auto kern = gemm_bf16_w4_kernel<A_KC, B_KC, EPI, MI>;
   static std::once_flag attr_once;
   static hipError_t attr_rc = hipSuccess;
@@ -1375,26 +1384,20 @@ mosaic_status launch_w4_epi(hipStream_t s, int quota, const W4Args& p, int piece
   MOSAIC_HIP(attr_rc);
   TileQueueArgs tq;
   int grid;
-  MOSAIC_TRY(tile_queue_plan(s, quota, 1, (int64_t)p.tile_count * pieces, 0, false, &tq, &grid));
+  MOSAIC_TRY(tile_queue_plan(s, quota, 1, p.tile_count, 0, false, &tq, &grid));
   kern<<<grid, 256, w4_lds(EPI), s>>>(p, tq);
   MOSAIC_LAUNCH_CHECK();
-  if constexpr (EPI == W4_SPLIT) {
-    splitk_reduce_kernel<256><<<grid_for(quota, 8, (int64_t)p.tile_count * 64), 256, 0, s>>>(p.P, p.C, p.M, p.N, p.ldc, pieces, p.tiles_m, p.tiles_n,
-                                                                                           p.tile_begin, p.tile_count, p.row_block);
-    MOSAIC_LAUNCH_CHECK();
-  }
   return MOSAIC_OK;
 }
 
 // Tiles [tile_begin, tile_begin + tile_count) of the 256x256 tile list (tile_count < 0: all from
-// tile_begin on); pieces > 1: each cut into that many pieces of the contraction, added by a second pass.
-// MI < 8: tiles of 32 * MI rows, the whole list.
+// tile_begin on).  MI < 8: tiles of 32 * MI rows, the whole list.
 template <bool A_KC, bool B_KC, int MI = 8>
 mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, bf16* C,
                         int64_t ldc, const bf16* bias, const bf16* R, uint32_t a_bytes, uint32_t b_bytes, uint32_t c_bytes, int tile_begin,
-                        int tile_count, const ActArgs& aa, int pieces = 1, float* P = nullptr) {
+                        int tile_count, const ActArgs& aa) {
   W4Args p = {};
-  p.A = A; p.B = B; p.C = C; p.bias = bias; p.R = R; p.P = P; p.C2 = aa.C2;
+  p.A = A; p.B = B; p.C = C; p.bias = bias; p.R = R; p.C2 = aa.C2;
   p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldc2 = aa.ldc2;
   p.a_bytes = a_bytes; p.b_bytes = b_bytes; p.c_bytes = c_bytes; p.c2_bytes = aa.c2_bytes; p.gu_f = aa.gu_f;
   p.tiles_m = (int)ceil_div(M, 32 * MI); p.tiles_n = (int)ceil_div(N, 256);
@@ -1402,143 +1405,81 @@ mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf1
   p.tile_count = tile_count < 0 ? p.tiles_m * p.tiles_n - tile_begin : tile_count;
   if (p.tile_count <= 0) return MOSAIC_OK;
   p.row_block = row_block_for(K, p.tiles_m);
-  p.ktiles_per = (int)ceil_div(ceil_div(K, 64), pieces);
-  if constexpr (!A_KC && !B_KC) {
-    if (pieces > 1) return launch_w4_epi<A_KC, B_KC, W4_SPLIT>(s, quota, p, pieces);
-  }
   if constexpr (A_KC && !B_KC) {
-    if (aa.act == ACT_GELU) return launch_w4_epi<A_KC, B_KC, W4_GELU, MI>(s, quota, p, 1);
-    if (aa.act == ACT_SWIGLU) return launch_w4_epi<A_KC, B_KC, W4_SWIGLU, MI>(s, quota, p, 1);
-    if (bias && !R) return launch_w4_epi<A_KC, B_KC, W4_BIAS, MI>(s, quota, p, 1);
+    if (aa.act == ACT_GELU) return launch_w4_epi<A_KC, B_KC, W4_GELU, MI>(s, quota, p);
+    if (aa.act == ACT_SWIGLU) return launch_w4_epi<A_KC, B_KC, W4_SWIGLU, MI>(s, quota, p);
+    if (bias && !R) return launch_w4_epi<A_KC, B_KC, W4_BIAS, MI>(s, quota, p);
   }
-  if (R || bias) return launch_w4_epi<A_KC, B_KC, W4_RES, MI>(s, quota, p, 1);
-  return launch_w4_epi<A_KC, B_KC, W4_PLAIN, MI>(s, quota, p, 1);
+  if (R || bias) return launch_w4_epi<A_KC, B_KC, W4_RES, MI>(s, quota, p);
+  return launch_w4_epi<A_KC, B_KC, W4_PLAIN, MI>(s, quota, p);
 }
 
 // A/B switches for kernel timing, compiled in only with -DMOSAIC_TUNING (never in the library
 // that ships): MOSAIC_GEMM_W4=0 sends the 256x256 tiles back to the eight-wave kernel,
 // MOSAIC_GEMM_TILE=256 / 128 / 1 forces the all-256, all-128 or mixed tile plan, 7 / 6 / 5 tiles of
 // 224 / 192 / 160 rows (the bits are the same either way); MOSAIC_SPLITK=n forces the piece count of a weight gradient's cut tail
-// (0: no cut; the bits differ with n).
+// (0: no cut; the bits differ with n); MOSAIC_PIECES=1 / 2 / 3 forces 256x256 tiles, 128x128 tiles or 128x128 tiles one piece
+// after the other where all tiles are cut.
 #ifdef MOSAIC_TUNING
 bool w4_enabled() { const char* e = getenv("MOSAIC_GEMM_W4"); return !e || atoi(e) != 0; }
 int forced_tile() { const char* e = getenv("MOSAIC_GEMM_TILE"); return e ? atoi(e) : 0; }
+int forced_pieces() { const char* e = getenv("MOSAIC_PIECES"); return e ? atoi(e) : 0; }
 #else
 constexpr bool w4_enabled() { return true; }
 constexpr int forced_tile() { return 0; }
+constexpr int forced_pieces() { return 0; }
 #endif
 
-// Splitting the weight-gradient form along K.  Its contraction runs over the tokens and is
-// long; its output has few tiles.  Two cases, both decided by the shape alone (256 = CUs of the
-// device the kernels are written for; never the quota, so the bits stay quota-independent):
-//  - up to 128 tiles of 256x256: every tile is cut, into about as many work items as CUs;
-//  - more: the tiles that do not fill a round of 256 (the tail of the tile list) are cut when
-//    the contraction is at least 16384 long and the cut is priced well below the alternatives,
-//    one more round of large tiles or the tail as quarter tiles.  Prices in microseconds on the
-//    whole device: a 256x256 tile takes 25.5 ns per unit of K, a work item 12 us on top
-//    (pipeline fill, fp32 store of its piece), the pass that adds the pieces reads them at
-//    3.5 TB/s after 8 us; two small workgroups per CU take 1.8 quarter units each (as in
-//    launch_mfma_shape).  Measured, pieces forced to 2 .. 8: the gate/up gradient at T=32768
-//    (1376 tiles, 96 in the tail) 4845 us uncut, 4624 in 5 pieces (the plan's choice; 2 and 8
-//    pieces within 15 us of it); the same at T=16384 2405 -> 2315; the down-projection gradient
-//    (688 tiles, 176 in the tail, else a third round of large tiles) 2410 -> 2362 in 4 pieces
-//    and slower in any other count; at T=8192 no cut gains anything (331 us either way for 96
-//    tail tiles, 178 -> 211 and worse for a lone round of 192 tiles): pieces of a few thousand
-//    tokens are mostly fill and drain.
-// *first: first tile of the list that is cut; returns the piece count (1: nothing is cut).
-int splitk_plan(int64_t M, int64_t N, int64_t K, int* first) {
-  const int64_t t256 = ceil_div(M, 256) * ceil_div(N, 256);
-  *first = 0;
-  if (N % 4) return 1;
-  if (t256 <= 128) {
-    if (K < 2048) return 1;
-    int64_t s = 256 / t256;
-    if (s > 8) s = 8;
-    while (s > 1 && ceil_div(K, s) < 512) --s;
-    return (int)s;
+// dW[M,N] = A^T B, contraction K over the tokens (gemm_plan.h says in which tiles and pieces)
+mosaic_status launch_wgrad(hipStream_t s, int quota, int M, int N, int K, const bf16* A, int64_t lda, const bf16* B, int64_t ldb, bf16* C,
+                           int64_t ldc, const bf16* bias, const bf16* R, uint32_t a_bytes, uint32_t b_bytes, uint32_t c_bytes, float* scratch) {
+  const int cus = tile_queue_sure_cus(quota);
+  const bool w4 = w4_takes<false, false>(K) && w4_enabled();
+  WgradPlan p = wgrad_plan(M, N, K, cus, scratch && !bias && !R, w4);
+  const int t256 = (int)(ceil_div(M, 256) * ceil_div(N, 256));
+  typedef std::integral_constant<int, PIECES_NONE> None;
+  typedef std::integral_constant<int, PIECES_APART> Apart;
+  typedef std::integral_constant<int, PIECES_CHAINED> Chained;
+  auto large8 = [&](auto how, int tile_begin, int tile_count) {
+    return launch_mfma<256, 256, 2, 4, false, false, decltype(how)::value>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes,
+                                                                           p.pieces, p.kper, scratch, 1, tile_begin, tile_count);
+  };
+  auto small = [&](auto how, int sub, int tile_begin, int tile_count) {
+    return launch_mfma<128, 128, 2, 2, false, false, decltype(how)::value>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes,
+                                                                           p.pieces, p.kper, scratch, sub, tile_begin, tile_count);
+  };
+  const bool part = p.pieces > 1 && p.first > 0;
+  const int tiles = part ? p.first : t256, head = tiles / cus * cus;
+  if (p.way <= kPiecesChained) {
+    if (forced_pieces() > 0) p.way = (WgradWay)(forced_pieces() - 1);
+  } else {
+    if (forced_tile() == 256) p.way = w4 ? kWhole4 : kWhole8;
+    if (forced_tile() == 128) p.way = kWholeSmall;
+    if (forced_tile() == 1 && head > 0 && head < tiles) p.way = w4 ? kMixed4 : kMixed8;
   }
-  const int64_t tail = t256 % 256;
-  if (tail == 0 || K < 16384) return 1;
-  const double tile_us = 25.5e-3 * (double)K;
-  int best = 1;
-  double best_us = 1e30;
-  for (int s = 2; s <= 8 && K / s >= 1024; ++s) {
-    const double pieces = (double)(tail * s);
-    const double us = (double)ceil_div(tail * s, 256) * (tile_us / s + 12.0) + pieces * 262144.0 / 3.5e6 + 8.0;
-    if (us < best_us - 1e-9) { best_us = us; best = s; }
+  auto large4 = [&](int count) {
+    return launch_w4<false, false>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes, 0, count, ActArgs());
+  };
+  switch (p.way) {
+    case kPiecesLarge: return large8(Apart(), 0, -1);
+    case kPiecesSmall: return small(Apart(), 1, 0, -1);
+    case kPiecesChained: return small(Chained(), 1, 0, -1);
+    case kWhole8: MOSAIC_TRY(large8(None(), 0, tiles)); break;
+    case kWhole4: MOSAIC_TRY(large4(tiles)); break;
+    case kWholeSmall: MOSAIC_TRY(part ? small(None(), 2, 0, tiles) : small(None(), 1, 0, -1)); break;
+    default:
+      MOSAIC_TRY(p.way == kMixed8 ? large8(None(), 0, head) : large4(head));
+      MOSAIC_TRY(small(None(), 2, head, tiles - head));
   }
-  const int64_t q = 4 * tail, full = q / 512, rem = q % 512;
-  const double quarter_us = ((double)full * 2.0 * 1.8 + (rem == 0 ? 0.0 : rem <= 256 ? 1.2 * 1.8 : 2.0 * 1.8)) / 4.0 * tile_us;
-  const double other_us = std::min(tile_us, quarter_us);            // one more round of large tiles, or quarter tiles
-#ifdef MOSAIC_TUNING
-  if (const char* e = getenv("MOSAIC_SPLITK")) { const int f = atoi(e); if (f <= 1) return 1; *first = (int)(t256 - tail); return f; }
-#endif
-  if (best == 1 || best_us >= 0.92 * other_us) return 1;
-  *first = (int)(t256 - tail);
-  return best;
-}
-
-// How a weight gradient of up to 128 tiles of 256x256 that has scratch for `reserved` pieces of
-// each is computed: *te = edge of the tiles, returns the piece count (1: not cut).  A function
-// of the shape alone.  Besides cutting the 256x256 tiles into `reserved` pieces there are 128x128 tiles,
-// one per CU with 64-deep K-tiles, in as many pieces as still fit one round of 256 (never more
-// scratch than reserved).  They need fewer or no pieces for the same number of busy CUs: a piece costs
-// its fp32 store and the reduce pass its reading.  Prices in microseconds on the whole device, fitted to
-// the products below: nanoseconds per unit of K of a tile, growing with the share of CUs at
-// work (the board's power is shared); 5 for launch, fill and drain; a reduce pass 4 and its bytes at
-// 4.5 TB/s.  The small tiles have to be priced 8 % lower, because on a share of the CUs, where
-// tiles queue up, they are less efficient.  Measured on 256 CUs (on 64): 256x256 cut -> plan
-//   9216 x 1024 x 4096  80 -> 72 us (185 -> 156), 256 tiles, not cut;   8192 x 2048 x 2048  74 -> 65 (169 -> 140)
-//   9216 x 1024 x 1024  36 -> 28 (59 -> 70), 64 tiles in 4 pieces;   24000 x 240 x 1280  61 -> 29 (61 -> 67)
-//   5000 x 1024 x 3072  46 -> 36 (101 -> 88);   12000 x 1280 x 1280  stays, 50 (130): small tiles 48 (152)
-//   12000 x 1280 x 3840  stays, 109: 300 small tiles, uncut, take 154
-// (the cut 256x256 tiles on the eight-wave kernel; on the four-wave one 104 us in the last of these, 51 in the one before)
-int wgrad_tiles(int64_t M, int64_t N, int64_t K, int reserved, int* te) {
-  const double k = (double)K, t256 = (double)(ceil_div(M, 256) * ceil_div(N, 256)), t128 = (double)(ceil_div(M, 128) * ceil_div(N, 128));
-  const double reduce_us = 4.0, bytes_us = (double)M * (double)N * 4.0 / 4.5e6, n = t256 * reserved;
-  const double large = (n > 256 ? 2.0 : 1.0) * (k / reserved * (12.0 + 11.5 * std::min(1.0, n / 256)) * 1e-3 + 5.0) + 5.0 + reduce_us + reserved * bytes_us;
-  double best = 0.92 * large;
-  *te = 256;
-  int pieces = reserved;
-  for (int s = 1; s <= reserved && t128 * s <= 256 && t128 * s <= 4 * n; ++s) {
-    const double us = k / s * (5.7 + 1.7 * t128 * s / 256) * 1e-3 + 5.0 + (s > 1 ? reduce_us + s * bytes_us : 0.0);
-    if (us < best) { best = us; pieces = s; *te = 128; }
-  }
-  return pieces;
+  return part ? large8(Apart(), tiles, t256 - tiles) : MOSAIC_OK;
 }
 
 template <bool A_KC, bool B_KC>
 mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, const bf16* A, int64_t lda,
                                 const bf16* B, int64_t ldb, bf16* C, int64_t ldc, const bf16* bias, const bf16* R,
-                                uint32_t a_bytes, uint32_t b_bytes, uint32_t c_bytes, void* splitk_scratch,
-                                const ActArgs& aa = ActArgs()) {
-  // tiles [split_first, t256) of the tile list are cut along K (weight-gradient form only); the
-  // tiles before them are planned below as if they were the whole product
-  int64_t t256 = ceil_div(M, 256) * ceil_div(N, 256);
-  const int64_t t256_all = t256;
-  int sk = 1, split_first = 0;
-  if constexpr (!A_KC && !B_KC) {
-    if (splitk_scratch && !bias && !R) sk = splitk_plan(M, N, K, &split_first);
-    if (sk > 1 && split_first == 0) {
-      int te;
-      sk = wgrad_tiles(M, N, K, sk, &te);
-      if (te == 128 && sk > 1)
-        return launch_mfma<128, 128, 2, 2, A_KC, B_KC, true, ACT_NONE, 64>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes,
-                                                                          sk, (int)ceil_div(ceil_div(K, 64), sk), (float*)splitk_scratch);
-    }
-  }
-  // cut products have a contraction of thousands (splitk_plan), which the four-wave kernel takes
-  auto launch_split = [&]() -> mosaic_status {
-    if constexpr (!A_KC && !B_KC)
-      return launch_w4<A_KC, B_KC>(s, quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes, split_first,
-                                   (int)(t256_all - split_first), aa, sk, (float*)splitk_scratch);
-    else return MOSAIC_EUNSUPPORTED;
-  };
-  const bool part = sk > 1;          // the plans below cover tiles [0, t256) only
-  if (part) {
-    if (split_first == 0) return launch_split();
-    t256 = split_first;
-  }
+                                uint32_t a_bytes, uint32_t b_bytes, uint32_t c_bytes, const ActArgs& aa = ActArgs()) {
+  static_assert(A_KC || B_KC, "launch_wgrad takes the K-strided form");
+  const int64_t t256 = ceil_div(M, 256) * ceil_div(N, 256);
   // Tile shape only decides which workgroup computes an element, never its bits.  Large
   // tiles halve LDS traffic per MFMA; small tiles fill the CUs when there are few large
   // ones.  Plans, priced in units of a quarter of a 256x256 tile's time on one CU (eight-wave kernel):
@@ -1549,7 +1490,7 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
   // rounds are counted with the CUs that are certain to run a workgroup at the same time
   const int launch_quota = quota;
   quota = tile_queue_sure_cus(quota);
-  const int64_t t128 = part ? 4 * t256 : ceil_div(M, 128) * ceil_div(N, 128);
+  const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128);
   // share of the board's CUs that a round of `tiles` leaves idle: the others run faster for it
   auto idle = [&](int64_t tiles) { return (double)(quota - tiles) / 256.0; };
   auto cost_small = [&](int64_t tiles) {       // 128x128 tiles on `quota` CUs
@@ -1557,7 +1498,7 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
     // a CU shared by two workgroups finishes both in about 2 x 1.35 units (more when the
     // operands need the transposing reads); a workgroup alone takes 1.5 with all CUs at work and 1.05
     // with few (64-deep K-tiles: input gradient 4096 x 4096 x 1024, 256 tiles, 38 us; 1568 x 3072 x 768, 78 tiles, 23)
-    constexpr double pen = (A_KC && B_KC) ? 1.3 : (!A_KC && !B_KC) ? 1.8 : 1.45;
+    constexpr double pen = (A_KC && B_KC) ? 1.3 : 1.45;
     const double alone = A_KC ? 1.5 - 0.45 * idle(rem) : 1.2 * pen;
     return (double)full * 2.0 * pen + (rem == 0 ? 0.0 : rem <= quota ? alone : 2.0 * pen);
   };
@@ -1616,27 +1557,20 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
     }
     if constexpr (A_KC && !B_KC) {
       if (aa.act == ACT_GELU)
-        return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC, false, ACT_GELU>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
+        return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC, PIECES_NONE, ACT_GELU>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
                                                                         c_bytes, 1, 0, nullptr, sub, tile_begin, tile_count, aa);
       if (aa.act == ACT_SWIGLU)
-        return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC, false, ACT_SWIGLU>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
+        return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC, PIECES_NONE, ACT_SWIGLU>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
                                                                           c_bytes, 1, 0, nullptr, sub, tile_begin, tile_count, aa);
     }
     return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes, 1, 0,
                                                    nullptr, sub, tile_begin, tile_count);
   };
-  if (plan == 256) {
-    MOSAIC_TRY(launch_tiles(std::true_type{}, 1, 0, part ? (int)t256 : -1));
-    return part ? launch_split() : MOSAIC_OK;
-  }
-  if (plan == 128) {
-    MOSAIC_TRY(part ? launch_tiles(std::false_type{}, 2, 0, (int)t256) : launch_tiles(std::false_type{}, 1, 0, -1));
-    return part ? launch_split() : MOSAIC_OK;
-  }
+  if (plan == 256) return launch_tiles(std::true_type{}, 1, 0, -1);
+  if (plan == 128) return launch_tiles(std::false_type{}, 1, 0, -1);
   const int head = (int)(whole * quota);
   MOSAIC_TRY(launch_tiles(std::true_type{}, 1, 0, head));
-  MOSAIC_TRY(launch_tiles(std::false_type{}, 2, head, (int)rest));
-  return part ? launch_split() : MOSAIC_OK;
+  return launch_tiles(std::false_type{}, 2, head, (int)rest);
 }
 
 }  // namespace
@@ -1691,11 +1625,11 @@ static mosaic_status launch_gemm_impl(hipStream_t s, int quota, int dtype, bool 
           *fused = true;
         }
       }
-      return launch_mfma_shape<true, false>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb, splitk_scratch, aa);
+      return launch_mfma_shape<true, false>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb, aa);
     }
-    if (a_kc && b_kc) return launch_mfma_shape<true, true>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb, splitk_scratch);
-    if (!a_kc && !b_kc) return launch_mfma_shape<false, false>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb, splitk_scratch);
-    return launch_mfma_shape<false, true>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb, splitk_scratch);
+    if (a_kc && b_kc) return launch_mfma_shape<true, true>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb);
+    if (!a_kc && !b_kc) return launch_wgrad(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb, (float*)splitk_scratch);
+    return launch_mfma_shape<false, true>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb);
   }
   return launch_gemm_f32(s, quota, dtype, a_kc, b_kc, (int)M, (int)N, (int)b_rows, A, lda, B, ldb, C, ldc, bias, R);
 }

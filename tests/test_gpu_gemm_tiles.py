@@ -58,21 +58,23 @@ def test_k_tile_depths_agree(mb, T, k, n):
 
 
 @pytest.mark.parametrize("T,k,n,note", [
-    (2048, 264, 1032, "3 x 9 small tiles in pieces, ragged tile row and column"),
-    (2056, 128, 128, "one tile, pieces of 5 and fewer K-tiles of 64, the last one short"),
-    (4096, 1024, 2048, "128 small tiles in 2 pieces"),
-    (9216, 1024, 4096, "256 small tiles, scratch reserved and not used"),
-    (9216, 600, 1024, "patch embedding shape: 40 tiles in 6 pieces"),
-    (12000, 1280, 1280, "large tiles stay cut"),
+    (2048, 264, 1032, "27 small tiles in pieces beside each other, ragged tile row and column"),
+    (2056, 128, 128, "one tile in pieces that end in mid K-tile of 64"),
+    (4096, 1024, 2048, "eight pieces: chained in small tiles, or large tiles"),
+    (3000, 768, 3072, "pieces of an odd number of 32 k-values, chained one and two tiles to a CU"),
+    (9216, 1024, 4096, "four pieces: chained, small tiles and large tiles by the quota"),
+    (9216, 600, 1024, "patch embedding shape: 40 small tiles in 8 pieces"),
+    (12000, 1280, 1280, "large tiles in 8 pieces, small ones on 192 and 160 CUs"),
 ])
 def test_weight_gradient_of_few_tiles(mb, T, k, n, note):
-    """Tile size and pieces follow the shape: same bits at every quota, every column against the oracle."""
+    """Pieces follow the shape; tile size and whether the pieces stand beside each other or follow one
+    another go by the quota: same bits at every quota, every column against the oracle."""
     X, dY = quantize(synth.normal(7300, (T, k)), "bf16"), quantize(synth.normal(7301, (T, n)), "bf16")
     X_, dY_ = to_dev(X, "bf16"), to_dev(dY, "bf16")
     nbytes = mb.linear_wgrad_scratch_bytes(T, k, n)
     assert nbytes > mb.colsum_scratch_bytes(n), "this shape has scratch for pieces"
     outs = []
-    for q in (256, 200, 64, 8):
+    for q in (256, 224, 192, 64, 32, 8, 1):
         ws = torch.full((nbytes + 4096,), 255, dtype=torch.uint8, device="cuda")        # NaN: nothing may be read before it is written
         dW = torch.full((k, n), float("nan"), dtype=torch.bfloat16, device="cuda")
         mb.op_linear_wgrad(None, q, "bf16", T, k, n, X_, dY_, dW, None, ws)
