@@ -1504,25 +1504,32 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
   };
   // 256x256 tiles go to the four-wave kernel where it takes the product; a round of it takes
   // about 3.5 units where the eight-wave kernel takes 4 (9216 x 1024 x 3072 forward, 1.7 rounds: 52 us in
-  // two rounds of large tiles, 55 as one and quarter tiles)
-  const bool w4 = w4_takes<A_KC, B_KC>(K) && w4_enabled();
-  const double round256 = w4 ? 3.5 : 4.0;
+  // two rounds of large tiles, 55 as one and quarter tiles).  SwiGLU's epilogue, an exponential and a division per
+  // pair of values, is not covered by another wave there: up to 1024 k-values the eight-wave
+  // kernel is faster (1568 x 768 x 3072 on 96 CUs 28.6 us, 30.2 with four waves; 9216 x 1024 x 3072 on 64 194 and 203), except in whole
+  // rounds that load most of the board (the same on 256 CUs 78 and 71).
   const int64_t whole = t256 / quota, rest = t256 % quota;
+  const bool w4 = w4_takes<A_KC, B_KC>(K) && w4_enabled() && !(aa.act == ACT_SWIGLU && K <= 1024 && (whole == 0 || quota < 192));
+  const double round256 = w4 ? 3.5 : 4.0;
   auto cost_w4 = [&](int64_t tiles, double round) {
     const int64_t rem = tiles % quota;
     return round * ((double)(tiles / quota) + (rem ? 1.0 - 0.39 * idle(rem) : 0.0));
   };
-  const double cost256 = A_KC && w4 && whole > 0 ? cost_w4(t256, round256) : (double)ceil_div(t256, quota) * round256;
+  // A lone round of 256 rows, which leaves CUs without a tile, is priced in full against the quarter tiles (with the
+  // discount that it gets against lower tiles, GELU and SwiGLU products took 1 to 2 % longer over 36 shapes
+  // on 8 shares of the CUs).
+  const double cost256 = w4 && whole > 0 ? cost_w4(t256, round256) : (double)ceil_div(t256, quota) * round256;
   const double cost128 = cost_small(t128);
   const double cost_mix = (whole > 0 && rest > 0) ? (double)whole * round256 + cost_small(4 * rest) + 0.15 : 1e30;
   // Tiles of 224, 192 or 160 rows: where tiles of 256 leave many CUs without one in the last (or only)
   // round, lower ones fill it.  In the units above a round takes 3.15, 2.8 or 2.57 (3.5 for 256 rows: a
   // lower tile reads its weight-side fragments for fewer instructions), less 0.39 of it times the
   // share of the board that it leaves idle (which also has 8192 x 2048 x 11264, 5.5 rounds of 256 rows, end
-  // in half a round of large tiles, 274 us, not in quarter tiles, 284).  An activation's epilogue wants all CUs: with
-  // fewer tiles than CUs the quarter tiles keep it (1568 x 768 x 3072 with GELU 21.5 us, 23.9 in 160 rows).
+  // in half a round of large tiles, 274 us, not in quarter tiles, 284).  SwiGLU's epilogue wants all CUs: with
+  // fewer tiles than CUs the quarter tiles keep it.
   // Measured, plan with 256 rows -> this: forward 9216 x 4096 x 1024 (144 tiles -> 232 of 160 rows)
-  // 74 -> 63 us, 9216 x 1024 x 1024 25.6 -> 21.9; input gradient 9216 x 1024 x 4096 73 -> 62; forward
+  // 74 -> 63 us, 9216 x 1024 x 1024 25.6 -> 21.9; input gradient 9216 x 1024 x 4096 73 -> 62; with GELU
+  // 2048 x 4096 x 4096 (160 rows) 82 -> 63; forward
   // 8192 x 2048 x 3072 (1.5 rounds -> 444 tiles of 224) 93 -> 82; 9216 x 1024 x 4096 (2.25 rounds ->
   // 768 tiles of 192) 73 -> 68; left alone: 12000 x 1280 x 1280, 235 tiles, 34 us, 42 and more in lower ones.
   int mi = 8;
@@ -1531,7 +1538,7 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
       double best = std::min(std::min(cost_w4(t256, round256), cost128), cost_mix);
       for (int m = 7; m >= 5; --m) {
         const int64_t tiles = ceil_div(M, 32 * m) * ceil_div(N, 256);
-        if (aa.act != ACT_NONE && tiles < quota) continue;
+        if (aa.act == ACT_SWIGLU && tiles < quota) continue;
         const double c = cost_w4(tiles, m == 7 ? 3.15 : m == 6 ? 2.8 : 2.57);
         if (c < best) { best = c; mi = m; }
       }
