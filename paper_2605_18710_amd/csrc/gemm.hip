@@ -233,22 +233,6 @@ __device__ __forceinline__ void tile_coords(int tile, int tiles_m, int tiles_n, 
   *col = panel * 8 + in_panel % pw;
 }
 
-// Tile rows per super-block: the row operand of a super-block (rows x 256 x K bf16) is kept to
-// about half of the 256 MB last-level cache, in whole 4-row patches.  Depends on K alone.
-#ifndef MOSAIC_LLC_ROW_BYTES
-#define MOSAIC_LLC_ROW_BYTES (128 << 20)
-#endif
-// Only products with many tile rows are cut (tiles_m counts 256-row tiles): with 64 rows or
-// fewer, two rounds of 256 tiles already span every row and the plain order re-reads nothing
-// that a cut would save (the weight-gradient form of the 7B shape, 16 tile rows, lost 3 % to a
-// cut of 8 rows).
-static inline int row_block_for(int64_t K, int64_t tiles_m) {
-  if (tiles_m <= 64) return (int)((tiles_m + 3) / 4 * 4);
-  int64_t rb = (int64_t)MOSAIC_LLC_ROW_BYTES / (512 * (K > 0 ? K : 1)) / 4 * 4;
-  if (rb < 4) rb = 4;
-  return (int)std::min<int64_t>(rb, (tiles_m + 3) / 4 * 4);
-}
-
 // One unit of work: an output tile, or (PIECES_APART) one K-piece of an output tile.
 struct WorkItem {
   int m0, n0, kt0, kt_end, split, tl;      // tl: position of the item's coarse tile in this launch's range
@@ -1356,7 +1340,7 @@ mosaic_status launch_mfma(hipStream_t s, int quota, int M, int N, int K, const b
   ActArgs ka = aa;
   // coarse tile rows are BM * sub rows high; every launch over one product (whole rounds,
   // quarter tiles, split tiles) walks the same tile list
-  ka.row_block = row_block_for(K, ceil_div((int64_t)M, 256)) * 256 / (BM * sub);
+  ka.row_block = row_block_for(K, M, BM * sub);
   kern<<<grid, 64 * NWM * NWN, smem, s>>>(A, B, C, bias, R, M, N, K, lda, ldb, ldc, a_bytes, b_bytes, c_bytes,
                                           tiles_m, tiles_n, tile_begin, tile_count, sub, ksplit, kper / BKT, P, tq, ka);
   MOSAIC_LAUNCH_CHECK();
@@ -1404,7 +1388,7 @@ mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf1
   p.tile_begin = tile_begin;
   p.tile_count = tile_count < 0 ? p.tiles_m * p.tiles_n - tile_begin : tile_count;
   if (p.tile_count <= 0) return MOSAIC_OK;
-  p.row_block = row_block_for(K, p.tiles_m);
+  p.row_block = row_block_for(K, M, 32 * MI);
   if constexpr (A_KC && !B_KC) {
     if (aa.act == ACT_GELU) return launch_w4_epi<A_KC, B_KC, W4_GELU, MI>(s, quota, p);
     if (aa.act == ACT_SWIGLU) return launch_w4_epi<A_KC, B_KC, W4_SWIGLU, MI>(s, quota, p);

@@ -1,10 +1,26 @@
-// Which tiles a weight gradient is computed in, and which of its tiles are cut: host arithmetic only.
+// The order of a product's tiles, which tiles a weight gradient is computed in, and which of them are cut:
+// host arithmetic only.
 #pragma once
 #include <stdint.h>
 #include <stdlib.h>
 #include <algorithm>
 
 inline int64_t plan_ceil(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Tile rows (of `rows` rows each) per super-block of the tile order: the row operand of a super-block is kept to
+// about half of the 256 MB last-level cache, in whole 4-row patches.  Depends on the shape alone.
+#ifndef MOSAIC_LLC_ROW_BYTES
+#define MOSAIC_LLC_ROW_BYTES (128 << 20)
+#endif
+// Only products of more than 64 x 256 rows are cut: with fewer, two rounds of 256 tiles already span every
+// row and the plain order re-reads nothing that a cut would save (the weight-gradient form of the
+// 7B shape, 16 tile rows, lost 3 % to a cut of 8 rows).
+inline int row_block_for(int64_t K, int64_t M, int rows) {
+  const int64_t tiles_m = plan_ceil(M, rows), whole = plan_ceil(tiles_m, 4) * 4;
+  if (M <= 64 * 256) return (int)whole;
+  const int64_t rb = (int64_t)MOSAIC_LLC_ROW_BYTES / (2 * (K > 0 ? K : 1)) / rows / 4 * 4;
+  return (int)std::min<int64_t>(std::max<int64_t>(rb, 4), whole);
+}
 
 // Splitting the weight-gradient form along K.  Its contraction runs over the tokens and is
 // long; its output has few tiles.  Two cases, both decided by the shape alone (256 = CUs of the

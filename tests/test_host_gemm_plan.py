@@ -18,6 +18,7 @@ PROGRAM = r"""
 #include "gemm_plan.h"
 int main() {
   long M, N, K; int cus, cut, four;
+  if (scanf("rows %ld %ld %d", &K, &M, &cus) == 3) { printf("%d\n", row_block_for(K, M, cus)); return 0; }
   while (scanf("%ld %ld %ld %d %d %d", &M, &N, &K, &cus, &cut, &four) == 6) {
     const WgradPlan p = wgrad_plan(M, N, K, cus, cut, four);
     printf("%d %d %d %d\n", p.pieces, p.first, p.kper, (int)p.way);
@@ -34,9 +35,13 @@ def plan(tmp_path_factory):
     (d / "plan.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(d / "plan.cpp"), "-o", str(d / "plan")], check=True)
 
-    def ask(T, k, n, cus, cut=1, four=1):
-        out = subprocess.run([str(d / "plan")], input="%d %d %d %d %d %d\n" % (k, n, T, cus, cut, four), capture_output=True, text=True, check=True).stdout
+    def call(line):
+        out = subprocess.run([str(d / "plan")], input=line + "\n", capture_output=True, text=True, check=True).stdout
         return tuple(int(v) for v in out.split())
+
+    def ask(T, k, n, cus, cut=1, four=1):
+        return call("%d %d %d %d %d %d" % (k, n, T, cus, cut, four))
+    ask.rows = lambda K, M, rows: call("rows %d %d %d" % (K, M, rows))[0]
     return ask
 
 
@@ -83,3 +88,18 @@ def test_pieces_do_not_follow_the_share(plan, T, k, n):
 def test_without_scratch_or_four_waves(plan):
     assert all(plan(T, 2048, 2048, cus, cut=0)[0] == 1 for T in (8192, 100) for cus in (1, 64, 256))
     assert all(plan(T, 4096, 12288, cus, four=0)[3] not in (WHOLE4, MIXED4) for T in (100, 4608) for cus in (1, 64, 256))
+
+
+@pytest.mark.parametrize("rows", [128, 160, 192, 224, 256])
+def test_tile_rows_of_a_super_block(plan, rows):
+    """The tile order is cut by the rows of the matrix, not by how many tile rows they make: no cut up to 16384 rows,
+    above that whole 4-row patches whose operand is as near to 128 MB at every tile height."""
+    for K in (128, 4096, 11008):
+        for M in (1, 8192, 10496, 16384):
+            assert plan.rows(K, M, rows) >= -(-M // rows), (K, M)
+        for M in (16385, 32768, 100000):
+            rb = plan.rows(K, M, rows)
+            assert rb % 4 == 0 and rb >= 4
+            if rb < -(-M // rows):
+                per = rows * K * 2
+                assert rb * per <= 128 << 20 < (rb + 4) * per, (K, M)
