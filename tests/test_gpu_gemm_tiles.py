@@ -131,3 +131,43 @@ def test_large_tiles_agree_with_small_ones(mb, T, k, n):
         assert_close(from_dev(outs[1][9]), O.swiglu_fwd(g[:, :n // 2], g[:, n // 2:]), "bf16", "swiglu")
     for o in outs[1:]:
         assert all(torch.equal(a.view(torch.int16), c.view(torch.int16)) for a, c in zip(o, outs[0]))
+
+
+def _hard(torch, g, kind, shape):
+    x = torch.randn(shape, generator=g, device="cuda")
+    if kind == "spread":            # terms that differ by up to 2^60, and by all powers between
+        x *= torch.exp2(torch.randint(-30, 31, shape, generator=g, device="cuda").float())
+    elif kind == "denormal":        # bf16 numbers at and below the smallest normal one
+        x *= torch.exp2(torch.randint(-133, -120, shape, generator=g, device="cuda").float())
+    elif kind == "small":           # products at and below fp32's normal range
+        x *= 2.0 ** -62
+    return x.to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("a,b", [("spread", "spread"), ("spread", "normal"), ("cancel", "spread"), ("cancel", "normal"), ("denormal", "normal"),
+                                 ("normal", "denormal"), ("small", "small")])
+@pytest.mark.parametrize("T,k,n", [(510, 1024, 504), (256, 128, 256), (330, 320, 512), (200, 256, 264)])
+def test_matrix_instructions_agree_on_hard_data(mb, T, k, n, a, b):
+    """128 x 128 tiles multiply with the 32x32x16 instruction, the large ones of one CU with 16x16x32: the quota
+    decides which one an element meets.  Sums that show how an instruction aligns and rounds its terms."""
+    g = torch.Generator(device="cuda").manual_seed(T + k + n)
+    X, W, dY = _hard(torch, g, "spread" if a == "cancel" else a, (T, k)), _hard(torch, g, b, (k, n)), _hard(torch, g, "spread" if a == "cancel" else a, (T, n))
+    if a == "cancel":               # neighbouring terms of opposite sign, and a few that do not cancel
+        X[:, 1::2] = -X[:, 0::2]
+        W[1::2] = W[0::2]
+        W[5::16] = _hard(torch, g, b, tuple(W[5::16].shape))
+        dY[1::2] = -dY[0::2][:dY[1::2].shape[0]]
+    outs = []
+    for q in (256, 1, 3):
+        Y, dX, dW = [torch.full(s, float("nan"), dtype=torch.bfloat16, device="cuda") for s in ((T, n), (T, k), (k, n))]
+        sc = torch.empty(max(16, mb.linear_wgrad_scratch_bytes(T, k, n)), dtype=torch.uint8, device="cuda")
+        mb.op_linear_fwd(None, q, "bf16", T, k, n, X, W, None, None, Y)
+        mb.op_linear_dgrad(None, q, "bf16", T, k, n, dY, W, None, dX)
+        mb.op_linear_wgrad(None, q, "bf16", T, k, n, X, dY, dW, None, sc)
+        torch.cuda.synchronize()
+        outs.append((Y, dX, dW))
+    for o in outs[1:]:
+        assert all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(o, outs[0]))
+    # one rounding to bf16 (2^-9 of an element on average over the mantissas) of the 64-bit sum
+    ref = X.double() @ W.double()
+    assert float((outs[0][0].double() - ref).norm() / ref.norm()) < 2.5e-3
