@@ -12,11 +12,15 @@
 // Every sum has one owner and an order fixed by the ids alone: repeated ids need no atomics and
 // the bits do not depend on the grid.
 //
+// The order: segments of 16 positions ascending, then the pieces of a run that spans segments, as
+// four quarters added in turn.
+//
 // What bounds it: the table is written whole (V x h; 131 MB at V 32000, h 2048) and dy read once;
-// the sort moves a few bytes per position and is six short launches.  A whole step (forward and
-// backward) at B8 N1024 h2048 V32000, ids with the frequencies of running text: 99 us = 2.5 TB/s of
-// the bytes it cannot do without, against 2098 us when the owner of every table row walked all
-// positions (V x T id reads).
+// the sort moves a few bytes per position in two short launches per 8 bits of the largest key (four at
+// V 32000, six from 65536 on).  A whole step (forward and backward) at B8 N1024 h2048 V32000, ids with the
+// frequencies of running text: 99 us = 2.5 TB/s of the bytes it cannot do without, against 2098 us when the
+// owner of every table row walks all positions (V x T id reads).  That walk is one launch, and
+// still what small calls take (scan_is_faster).
 #include "kernels.h"
 
 namespace {
@@ -309,6 +313,70 @@ __global__ __launch_bounds__(kThreads) void embed_join_kernel(const int32_t* __r
   }
 }
 
+// Small calls: the workgroup that owns a table row walks all positions, 256 at a time, gathers
+// those that hold its id into a list in LDS in ascending order (waves in order, lanes in order, by ballot
+// and prefix count) and adds the listed rows of dy in that order, all columns of a row in registers.
+constexpr int kScanPositions = 640, kScanCols = 32;   // columns per thread: rows of up to 8192 elements
+template <typename T>
+__global__ __launch_bounds__(kThreads) void embed_scan_kernel(const T* __restrict__ dy, const int32_t* __restrict__ ids,
+                                                              const int32_t* __restrict__ counts, T* __restrict__ dtable,
+                                                              int B, int N, int n_img, int h, int vocab) {
+  __shared__ int list[kScanPositions];
+  __shared__ int wave_hits[kWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int total = B * N;
+  for (int v = blockIdx.x; v < vocab; v += gridDim.x) {
+    int n_list = 0;                                    // the same in every thread
+    for (int p0 = 0; p0 < total; p0 += kThreads) {
+      const int p = p0 + threadIdx.x;
+      bool hit = false;
+      if (p < total) {
+        const int b = p / N, t = p - b * N;
+        hit = t >= stem_n_img(counts, b, n_img) && stem_id(ids, counts, b, t, N, n_img, vocab) == v;
+      }
+      const unsigned long long m = __ballot(hit);
+      if (lane == 0) wave_hits[wave] = __popcll(m);
+      __syncthreads();
+      int before = n_list, all = 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) { if (w < wave) before += wave_hits[w]; all += wave_hits[w]; }
+      if (hit) list[before + __popcll(m & ((1ull << lane) - 1ull))] = p;
+      n_list += all;
+      __syncthreads();                                 // list entries visible; wave_hits free for the next chunk
+    }
+    float acc[kScanCols];
+#pragma unroll
+    for (int j = 0; j < kScanCols; ++j) acc[j] = 0.f;
+    for (int e = 0; e < n_list; ++e) {
+      const T* row = dy + (int64_t)list[e] * h;
+#pragma unroll
+      for (int j = 0; j < kScanCols; ++j) {
+        const int c = j * kThreads + threadIdx.x;
+        if (c < h) acc[j] += to_f32(row[c]);
+      }
+    }
+    __syncthreads();                                   // everybody is done with the list
+#pragma unroll
+    for (int j = 0; j < kScanCols; ++j) {
+      const int c = j * kThreads + threadIdx.x;
+      if (c < h) dtable[(int64_t)v * h + c] = from_f32<T>(acc[j]);
+    }
+  }
+}
+
+// One launch of the scan against four to six of the sort, whatever the CUs (the orders of the sums
+// differ, so the rule is one of the shape).  The scan takes a pass over the ids per table row and the rows of an id one
+// after the other: it loses with many rows, with many positions to an id, and with long sums of wide rows.  Measured
+// on 256 CUs, bf16, ids with the frequencies of running text, scan / sort in us:
+//   T 128 h 512 V 1000  9.0 / 22.6,  V 16000  20.7 / 21.1,  V 32000  38 / 22      T 16 h 64 V 32  4.9 / 14.4
+//   T 128 h 64 V 32  14.7 / 14.5     T 256 h 1024 V 4000  18.9 / 24.3,  h 2048  30 / 25     T 512 h 256 V 4000  24.0 / 27.1
+//   T 600 h 64 V 4000  22.3 / 28.0   T 1024 h 64 V 4000  44.7 / 28.4
+inline bool scan_is_faster(int64_t T, int64_t h, int64_t vocab) {
+  const bool one_digit = vocab < kBins;                // four launches of the sort instead of six
+  return vocab <= 16384 && T <= 4 * vocab && T <= (one_digit ? 256 : kScanPositions) && T * h <= (one_digit ? 1 << 17 : 1 << 18) &&
+         h <= kScanCols * kThreads;
+}
+
 struct EmbedScratch {
   size_t key[2], pos[2], hist, part, bytes;
   EmbedScratch(int64_t total, int64_t h) {
@@ -325,6 +393,11 @@ template <typename T, int V>
 mosaic_status embed_grad_t(hipStream_t s, int quota, int B, int N, int n_img, int h, int vocab, const T* dy,
                            const int32_t* ids, const int32_t* counts, T* dtable, char* scratch) {
   const int total = B * N;
+  if (scan_is_faster(total, h, vocab)) {
+    embed_scan_kernel<T><<<grid_for(quota, 8, vocab), kThreads, 0, s>>>(dy, ids, counts, dtable, B, N, n_img, h, vocab);
+    MOSAIC_LAUNCH_CHECK();
+    return MOSAIC_OK;
+  }
   const EmbedScratch sc(total, h);
   const int chunks = (int)ceil_div(total, kChunk);
   int32_t* key[2] = {(int32_t*)(scratch + sc.key[0]), (int32_t*)(scratch + sc.key[1])};
@@ -388,7 +461,7 @@ mosaic_status text_stem_bwd_t(hipStream_t s, int quota, int B, int N, int n_img,
   return embed_grad_t<T, 1>(s, quota, B, N, n_img, h, vocab, dy, ids, counts, dtable, scratch);
 }
 
-constexpr int kEmbedMaxWidth = 8192;
+constexpr int kEmbedMaxWidth = kScanCols * kThreads;   // the widest rows that the entry point takes
 
 }  // namespace
 

@@ -1,7 +1,8 @@
 """Text stem at the sizes where the sort by id, its segments and the access width can go wrong:
 position counts around a chunk (2048) and a segment (16), vocabularies on both sides of a digit
 (8 bits), one id for everything, no text at all, widths of one and several column tiles, and
-tensors that do not start on a 16-byte boundary."""
+tensors that do not start on a 16-byte boundary; and both sides of the rule by which small calls
+scan the ids instead of sorting them."""
 import numpy as np
 import pytest
 
@@ -23,6 +24,10 @@ CASES = [  # B, N, n_img, h, vocab, ids, offset of the caller's tensors in eleme
     (2, 1500, 700, 40, 65536, "mixed", 0),
     (2, 1500, 0, 24, 16777217, "mixed", 0),
     (5, 900, 11, 1032, 3, "mixed", 3),
+    # scanned (positions, positions x width, vocabulary at their limits), then one past each limit
+    (2, 128, 0, 512, 255, "mixed", 0), (1, 257, 0, 64, 255, "mixed", 0), (1, 256, 0, 520, 255, "mixed", 0),
+    (1, 512, 7, 512, 256, "mixed", 1), (1, 640, 0, 64, 300, "one", 0), (1, 641, 7, 64, 256, "one", 0), (1, 512, 0, 520, 257, "mixed", 0),
+    (4, 64, 20, 1024, 16384, "one", 0), (4, 64, 20, 64, 16385, "mixed", 0), (1, 32, 0, 8192, 16, "one", 0), (1, 64, 3, 1000, 16, "mixed", 0), (1, 65, 0, 1000, 16, "mixed", 0),
 ]
 
 
