@@ -16,7 +16,10 @@
 // rows of the next block are requested before the current block's products, and the second
 // reading of the block's rows (in the other orientation) is in flight under them.  At B2 N128 H4
 // d32: forward 29 -> 10.1 us, dQ 25 -> 10.7, dK/dV 41 -> 13.7 against workgroups of 16 rows that formed
-// each score by scalar FMA over LDS (launches of 4.5 us included).
+// each score by scalar FMA over LDS (launches of 4.5 us included).  Longer rows and the bf16 head sizes
+// that come here, forward and backward in us, against those workgroups: fp32 B4 N1500 H8 d80 3944 -> 529 and
+// 19622 -> 1868, fp32 B1 N2048 H8/2 d128 causal 2442 -> 308 and 13313 -> 2253; bf16 B8 N1500 H16 d80 15614 -> 3484 and
+// 74581 -> 14185, B2 N576 H16 d72 733 -> 206 and 2852 -> 870.
 #include <algorithm>
 #include "kernels.h"
 
