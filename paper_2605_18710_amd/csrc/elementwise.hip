@@ -6,6 +6,7 @@
 // All reductions run in an order fixed by the problem shape alone: persistent grids only
 // decide which workgroup handles a work item, so results are bit-identical for any quota.
 #include "activations.h"
+#include <type_traits>
 #include "kernels.h"
 
 namespace {
@@ -370,16 +371,23 @@ __global__ __launch_bounds__(kThreads) void gelu_fwd_kernel(const T* __restrict_
   }
 }
 
+// GELU backward: HBM-bound at 6 bytes per bf16 element once erf comes from a table that the workgroup fills
+// first (ErfTable; the same bits): with an erff per element the pass was bound by instructions.  12000 x 5120
+// 90 -> 73 us, 9216 x 4096 48 -> 39 (5.8 TB/s), on 64 CUs 12000 x 5120 285 -> 189; at eight elements a thread, the fewest
+// that there are, 7.6 -> 7.2.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void gelu_bwd_kernel(const T* __restrict__ z, const T* __restrict__ da,
                                                             T* __restrict__ dz, int64_t nvec) {
   constexpr int VN = Vec16<T>::N;
+  constexpr bool TAB = std::is_same<T, bf16>::value;
+  __shared__ float table[TAB ? ErfTable::kEntries : 1];
+  if constexpr (TAB) { ErfTable::fill(table, threadIdx.x, kThreads); __syncthreads(); }
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nvec; i += (int64_t)gridDim.x * kThreads) {
     Vec16<T> v, d, o;
     v.load(z + i * VN);
     d.load(da + i * VN);
 #pragma unroll
-    for (int k = 0; k < VN; ++k) o.set(k, d.get(k) * gelu_grad_f(v.get(k)));
+    for (int k = 0; k < VN; ++k) o.set(k, d.get(k) * (TAB ? ErfTable::gelu_grad(table, v.get(k)) : gelu_grad_f(v.get(k))));
     o.store(dz + i * VN);
   }
 }
@@ -393,6 +401,9 @@ __global__ __launch_bounds__(kThreads) void gelu_bwd_colsum_kernel(const T* __re
                                                                    T* __restrict__ dz, float* __restrict__ partial,
                                                                    int64_t rows, int64_t n, int rp, int np, int ctiles) {
   constexpr int VN = Vec16<T>::N;
+  constexpr bool TAB = std::is_same<T, bf16>::value;
+  __shared__ float table[TAB ? ErfTable::kEntries : 1];
+  if constexpr (TAB) { ErfTable::fill(table, threadIdx.x, kThreads); __syncthreads(); }
   const int64_t items = (int64_t)np * ctiles;
   for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
     const int p = (int)(it / ctiles), ct = (int)(it - (int64_t)p * ctiles);
@@ -406,7 +417,7 @@ __global__ __launch_bounds__(kThreads) void gelu_bwd_colsum_kernel(const T* __re
     auto one = [&](const Vec16<T>& zv, const Vec16<T>& dv, int64_t r) {
       Vec16<T> o;
 #pragma unroll
-      for (int k = 0; k < VN; ++k) { o.set(k, dv.get(k) * gelu_grad_f(zv.get(k))); acc[k] += o.get(k); }
+      for (int k = 0; k < VN; ++k) { o.set(k, dv.get(k) * (TAB ? ErfTable::gelu_grad(table, zv.get(k)) : gelu_grad_f(zv.get(k)))); acc[k] += o.get(k); }
       o.store(dz + r * n + c);
     };
     int64_t r = r0;

@@ -694,6 +694,14 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
     static_assert(ACT == ACT_NONE || TN == 2, "a wave holds two 32-column blocks");
     constexpr bool GU = ACT == ACT_SWIGLU;
     unsigned char* patch = smem + free_stage + wave * 4096;
+    // stages of 64-deep K-tiles have room for a table of erf behind the patches (ErfTable; the same bits): 7 erff to
+    // fill it where the tile has 64 values a thread
+    constexpr bool TABLE = ACT == ACT_GELU && NWM * NWN * 4096 + ErfTable::kEntries * 4 <= STAGE;
+    float* const erf_table = reinterpret_cast<float*>(smem + free_stage + NWM * NWN * 4096);
+    if constexpr (TABLE) {
+      ErfTable::fill(erf_table, threadIdx.x, NT);
+      __syncthreads();
+    }
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int elr = ln & 31, ehb = ln >> 5;
@@ -769,7 +777,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_bf16_kernel(
           for (int g = 0; g < 4; ++g) {
             bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)gelu_f(zval(i, j, g, e));
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)(TABLE ? ErfTable::gelu(erf_table, zval(i, j, g, e)) : gelu_f(zval(i, j, g, e)));
             *reinterpret_cast<bf16x4*>(patch + wr + (((4 * j + g) ^ wsx) << 4)) = o;
           }
       }

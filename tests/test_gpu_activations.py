@@ -1,5 +1,6 @@
-"""GELU and SwiGLU, forward and backward, over every bf16 value: the bf16 kernels give the fp32 formula's
-value rounded once, no other formula; and that value is the 64-bit one to its rounding."""
+"""GELU and SwiGLU, forward and backward, over every bf16 value: the bf16 kernels, whether they call erff or read
+it from a table, give the fp32 formula's value rounded once, no other formula; and that value is the
+64-bit one to its rounding."""
 import numpy as np
 import pytest
 
@@ -55,8 +56,8 @@ def test_every_bf16_value():
 
 @pytest.mark.parametrize("quota", [256, 1])
 def test_every_finite_bf16_value_through_the_epilogue(quota):
-    """The product of unit rows and a weight that holds every finite bf16 value, on one CU in 256-wide tiles
-    (its epilogue reads erf from a table), on the whole device in small ones (erff)."""
+    """The product of unit rows and a weight that holds every finite bf16 value, on one CU in 256-wide tiles, on
+    the whole device in small ones that have a CU each: both epilogues read erf from a table."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2605_18710_amd import binding as mb
