@@ -2,8 +2,8 @@
 //
 // bf16 path: persistent MFMA kernels.  gemm_bf16_kernel serves every form: a workgroup of 8
 // waves (256x256 tile, 128x64 per wave) or 4 waves (128x128 tile, 64x64 per wave) walks
-// output tiles; gemm_bf16_w4_kernel (described at its definition) takes the 256x256 tiles of
-// every product whose K-contiguous operands are whole 64-deep K-tiles long.  In both,
+// output tiles; gemm_bf16_w4_kernel (described at its definition) can take the 256x256 tiles of
+// every product whose K-contiguous operands are whole 64-deep K-tiles long (the plans say when it does).  In both,
 // the grid is sized to the module's CU quota.  Each output element is produced by exactly
 // one wave that accumulates k in ascending order (v_mfma_f32_32x32x16_bf16 twice or
 // v_mfma_f32_16x16x32_bf16 once per 32 k-values: the same bits), so the
