@@ -1076,7 +1076,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
   point(it);
   request_tile(0);
   request_tile(1);
-  // 256 values of a tile to a thread: six erff to fill the table instead of 256 (the epilogue of 12000 x 1280 x 5120
+  // 256 values of a tile to a thread: seven erff to fill the table instead of 256 (the epilogue of 12000 x 1280 x 5120
   // takes 10 us of 150; with erff in it, four waves a CU, 83 of 239)
   float* const erf_table = reinterpret_cast<float*>(smem + 2 * kW4Stage + kW4Patch);
   if constexpr (EPI == W4_GELU) {
@@ -1236,23 +1236,21 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
             const int row = row0 + prow + 8 * q;
             float v[8];
             row8(prow + 8 * q, pcol, v);
-            {
-              const bf16x8 bv = __builtin_bit_cast(bf16x8, bias_[h]), rv = __builtin_bit_cast(bf16x8, res[q]);
-              bf16x8 o;
+            const bf16x8 bv = __builtin_bit_cast(bf16x8, bias_[h]), rv = __builtin_bit_cast(bf16x8, res[q]);
+            bf16x8 o;
 #pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                float x = v[e];
-                if constexpr (EPI != W4_PLAIN) x += (float)bv[e];
-                if constexpr (EPI == W4_RES) x += (float)rv[e];
-                o[e] = (bf16)x;
-              }
-              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rc, off(row, col, p.ldc, ok), 0, 0);
-              if constexpr (EPI == W4_GELU) {
-                bf16x8 a2;
+            for (int e = 0; e < 8; ++e) {
+              float x = v[e];
+              if constexpr (EPI != W4_PLAIN) x += (float)bv[e];
+              if constexpr (EPI == W4_RES) x += (float)rv[e];
+              o[e] = (bf16)x;
+            }
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rc, off(row, col, p.ldc, ok), 0, 0);
+            if constexpr (EPI == W4_GELU) {
+              bf16x8 a2;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) a2[e] = (bf16)ErfTable::gelu(erf_table, (float)o[e]);     // of the value as stored
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a2), rc2, off(row, col, p.ldc2, ok), 0, 0);
-              }
+              for (int e = 0; e < 8; ++e) a2[e] = (bf16)ErfTable::gelu(erf_table, (float)o[e]);     // of the value as stored
+              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a2), rc2, off(row, col, p.ldc2, ok), 0, 0);
             }
           }
         }
