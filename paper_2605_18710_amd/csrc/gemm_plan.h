@@ -114,10 +114,11 @@ enum WgradWay { kPiecesLarge, kPiecesSmall, kPiecesChained, kWhole8, kWhole4, kW
 struct WgradPlan {
   int pieces, first, kper;     // tiles from `first` on are cut into `pieces` pieces of kper k-values (splitk_plan)
   WgradWay way;                // of the cut tiles if all are cut, else of the tiles before `first`
+  double us;                   // its price, without what every launch costs (only where first == 0)
 };
 inline WgradPlan wgrad_plan(int64_t M, int64_t N, int64_t K, int cus, bool may_cut, bool four_wave) {
   const int64_t t256 = plan_ceil(M, 256) * plan_ceil(N, 256), t128 = plan_ceil(M, 128) * plan_ceil(N, 128);
-  WgradPlan p = {1, 0, 0, kWhole8};
+  WgradPlan p = {1, 0, 0, kWhole8, 0.0};
   if (may_cut) p.pieces = splitk_plan(M, N, K, &p.first);
   if (p.pieces > 1) p.kper = (int)(plan_ceil(plan_ceil(K, 32), p.pieces) * 32);
   if (p.pieces > 1 && p.first == 0) {
@@ -126,6 +127,7 @@ inline WgradPlan wgrad_plan(int64_t M, int64_t N, int64_t K, int cus, bool may_c
     const double us[] = {large_us(kLarge8, p.kper, t256 * p.pieces, cus) + add_us, small_us(p.kper, t128 * p.pieces, cus, deep) + add_us,
                          small_us((double)K, t128, cus, deep, p.pieces - 1)};
     p.way = (WgradWay)(kPiecesLarge + (std::min_element(us, us + 3) - us));
+    p.us = *std::min_element(us, us + 3);
     return p;
   }
   const int64_t tiles = p.pieces > 1 ? p.first : t256, quarters = p.pieces > 1 ? 4 * tiles : t128, head = tiles / cus * cus, rest = tiles - head;
@@ -135,5 +137,42 @@ inline WgradPlan wgrad_plan(int64_t M, int64_t N, int64_t K, int cus, bool may_c
                        small_us((double)K, quarters, cus, true), mixed ? large_us(kLarge8, (double)K, head, cus) + quarter_us : never,
                        mixed && four_wave ? large_us(kLarge4, (double)K, head, cus) + quarter_us : never};
   p.way = (WgradWay)(kWhole8 + (std::min_element(us, us + 5) - us));
+  p.us = *std::min_element(us, us + 5);
+  return p;
+}
+
+// The two products of a linear layer's backward pass, dX[T,k] = dY W^T and dW[k,n] = X^T dY, as one launch of 128x128
+// tiles (64-deep K-tiles, one workgroup per CU): `wgs_d` workgroups walk the tiles of the first, `wgs_w` those of the
+// second, wgs_d + wgs_w <= cus.  Small products leave most of the chip idle one after the other (1568 x 768 x 768: 78 tiles,
+// then 36) and pay for two launches; side by side the longer one hides the shorter.  The tiles of a product are
+// the ones that its own launch would compute, in the same order of additions (a gradient that is cut has its
+// pieces chained), so the bits are those of two launches.
+// Priced against the two launches with the figures above (input gradients: those of the K-strided form, and lower
+// tiles of the four-wave kernel); a launch more costs kLaunchUs.
+constexpr double kLaunchUs = 3.0;
+struct PairPlan { bool pair; int wgs_d, wgs_w; double us, apart_us; };
+inline PairPlan pair_plan(int64_t T, int64_t k, int64_t n, int cus, const WgradPlan& w) {
+  PairPlan p = {false, 0, 0, 1e30, 0.0};
+  if (cus < 16 || w.first > 0 || (w.pieces > 1 && w.kper % 64)) return p;
+  const int64_t nd = plan_ceil(T, 128) * plan_ceil(k, 128), nw = plan_ceil(k, 128) * plan_ceil(n, 128);
+  if (nd + nw > 8 * (int64_t)cus) return p;           // the large tiles' ground
+  const double busy = (double)std::min<int64_t>(cus, nd + nw);
+  const double td = round_us(kLone, (double)n, busy), tw = round_us(kLone, (double)T, busy) + (w.pieces - 1) * kFold;
+  for (int g = 8; g + 8 <= cus / 8 * 8; g += 8) {
+    const double us = std::max((double)plan_ceil(nd, g) * td, (double)plan_ceil(nw, cus / 8 * 8 - g) * tw);
+    if (us < p.us - 1e-9) { p.us = us; p.wgs_d = g; p.wgs_w = cus / 8 * 8 - g; }
+  }
+  p.wgs_d = (int)std::min<int64_t>(p.wgs_d, plan_ceil(nd, 8) * 8);
+  p.wgs_w = (int)std::min<int64_t>(p.wgs_w, plan_ceil(nw, 8) * 8);
+  double apart = small_us((double)n, nd, cus, true);
+  if (n % 64 == 0 && n >= 128) {
+    const double round[] = {2.57, 2.8, 3.15, 3.5};    // of 160, 192, 224, 256 rows, as in launch_mfma_shape
+    for (int i = 0; i < 4; ++i) {
+      const int64_t tiles = plan_ceil(T, 160 + 32 * i) * plan_ceil(k, 256);
+      apart = std::min(apart, large_us(kLarge4, (double)n, tiles, cus) * round[i] / 3.5);
+    }
+  }
+  p.apart_us = apart + w.us + kLaunchUs;
+  p.pair = p.us < 0.95 * p.apart_us;
   return p;
 }

@@ -25,6 +25,10 @@ mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act
                                     const void* X, const void* W, const void* bias, void* Z, void* A);
 // Bytes of fp32 scratch the weight-gradient form wants for a deterministic split of a long
 // contraction over few output tiles (0 when no split is used for this shape).
+// dW[k,n] = X^T dY and dX[T,k] = dY W^T, dense rows; one launch where that is the faster way, else two, the input gradient's
+// first or last (1 - 2 % of a layer either way, by what the caches still hold)
+mosaic_status launch_linear_bwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t k, int64_t n, const void* X, const void* dY,
+                                const void* W, void* dX, void* dW, void* splitk_scratch, bool dx_first);
 size_t gemm_splitk_scratch_bytes(int64_t M, int64_t N, int64_t K);
 
 // ------------------------------------------------------------------------- attention

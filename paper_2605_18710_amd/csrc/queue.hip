@@ -83,12 +83,13 @@ mosaic_status tile_queue_plan(hipStream_t s, int quota, int wg_per_cu, int64_t n
   q->n_items = (int)n_items;
   q->ctr = nullptr;
   q->chunk = 1; q->n_full = 0; q->tail_per = 0;
+  q->wg0 = 0;
   if (even && (n_items <= resident || !prefer_queue)) {
     // every workgroup resident at once: static rounds, no queue
     q->mode = TQ_ROUNDS;
     int64_t g = resident;
     if (g > n_items) g = (resident & 7) == 0 ? (n_items + 7) / 8 * 8 : n_items;   // XCD x takes the x-th eighth
-    *grid = (int)g;
+    *grid = q->wgs = (int)g;
     return MOSAIC_OK;
   }
   q->mode = n_items <= resident ? TQ_ONCE : TQ_QUEUE;
@@ -104,6 +105,6 @@ mosaic_status tile_queue_plan(hipStream_t s, int quota, int wg_per_cu, int64_t n
   } else if (g > n_items) {
     g = n_items;
   }
-  *grid = (int)g;
+  *grid = q->wgs = (int)g;
   return tile_queue_for_stream(s, &q->ctr);
 }

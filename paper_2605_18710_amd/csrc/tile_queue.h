@@ -47,6 +47,7 @@ struct TileQueueArgs {
   int n_full;        // items covered by whole rounds of eight chunks (a multiple of 8 * chunk)
   int tail_per;      // the remaining n_items - n_full items go to the lists in pieces of this many
   int mode;
+  int wg0, wgs;      // the launch's workgroups that share this list: wg0 .. wg0 + wgs - 1 (all of them, but for TQ_ROUNDS in a launch of two products)
 };
 
 // Host side (queue.hip).  Fills `q` for a launch of n_items items on the stream's queue of the
@@ -92,7 +93,7 @@ struct TileQueueCursor {
 
 // TQ_ROUNDS: this workgroup's item of round r, or -1 when it has none (nor in any later round)
 __device__ __forceinline__ int tq_rounds_item(const TileQueueArgs& q, int r) {
-  const int G = gridDim.x, b = blockIdx.x;
+  const int G = q.wgs, b = (int)blockIdx.x - q.wg0;
   const int64_t base = (int64_t)r * G;
   if (base >= q.n_items) return -1;
   const int cnt = (int)min((int64_t)G, q.n_items - base);

@@ -171,3 +171,24 @@ def test_matrix_instructions_agree_on_hard_data(mb, T, k, n, a, b):
     # one rounding to bf16 (2^-9 of an element on average over the mantissas) of the 64-bit sum
     ref = X.double() @ W.double()
     assert float((outs[0][0].double() - ref).norm() / ref.norm()) < 2.5e-3
+
+
+@pytest.mark.parametrize("T,k,n", [(130, 136, 520), (257, 264, 8), (40, 1000, 72), (1568, 776, 768), (2048, 128, 2048)])
+def test_backward_products_in_one_launch(mb, T, k, n):
+    """Input and weight gradient side by side in one launch (from 16 CUs on, small products; 2048 rows: the weight
+    gradient's pieces chained) have the bits of two launches (8 CUs), and dx may lie on x."""
+    m = mb.Module(dict(kind="projector", batch=1, seq=T, in_dim=k, out_dim=n), "bf16")
+    m.params.copy_(torch.randn(m.params.numel(), generator=torch.Generator().manual_seed(T), dtype=torch.float32).mul_(0.05).to(torch.bfloat16))
+    x, dy = to_dev(synth.normal(8100 + T, (T, k)), "bf16"), to_dev(synth.normal(8101 + T, (T, n)), "bf16")
+    outs = []
+    for q, alias in ((8, False), (256, False), (64, False), (33, False), (256, True)):
+        xin = x.clone()
+        y, dx = torch.full_like(dy, float("nan")), xin if alias else torch.full_like(x, float("nan"))
+        m.grads.fill_(float("nan"))
+        m.step(q, None, xin, y, dy=dy, dx=dx)
+        torch.cuda.synchronize()
+        outs.append([t.clone().view(torch.int16) for t in (y, dx, m.grads[:m.param_elems])])
+    assert not any(torch.isnan(t.view(torch.bfloat16)).any() for t in outs[0])
+    for o in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(outs[0], o))
+    m.destroy()

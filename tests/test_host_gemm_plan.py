@@ -18,6 +18,12 @@ PROGRAM = r"""
 #include "gemm_plan.h"
 int main() {
   long M, N, K; int cus, cut, four;
+  long T, k, n;
+  if (scanf("pair %ld %ld %ld %d", &T, &k, &n, &cus) == 4) {
+    const PairPlan p = pair_plan(T, k, n, cus, wgrad_plan(k, n, T, cus, true, T >= 128));
+    printf("%d %d %d\n", (int)p.pair, p.wgs_d, p.wgs_w);
+    return 0;
+  }
   if (scanf("rows %ld %ld %d", &K, &M, &cus) == 3) { printf("%d\n", row_block_for(K, M, cus)); return 0; }
   while (scanf("%ld %ld %ld %d %d %d", &M, &N, &K, &cus, &cut, &four) == 6) {
     const WgradPlan p = wgrad_plan(M, N, K, cus, cut, four);
@@ -42,6 +48,7 @@ def plan(tmp_path_factory):
     def ask(T, k, n, cus, cut=1, four=1):
         return call("%d %d %d %d %d %d" % (k, n, T, cus, cut, four))
     ask.rows = lambda K, M, rows: call("rows %d %d %d" % (K, M, rows))[0]
+    ask.pair = lambda T, k, n, cus: call("pair %d %d %d %d" % (T, k, n, cus))
     return ask
 
 
@@ -103,3 +110,18 @@ def test_tile_rows_of_a_super_block(plan, rows):
             if rb < -(-M // rows):
                 per = rows * K * 2
                 assert rb * per <= 128 << 20 < (rb + 4) * per, (K, M)
+
+
+@pytest.mark.parametrize("T,k,n,pairs", [
+    (1568, 768, 768, {256, 192, 64}), (1568, 768, 3072, {256, 192, 64}), (600, 1024, 1024, {256, 192}), (2048, 128, 2048, {256, 192, 64}),
+    (2112, 768, 768, set()),            # pieces of 544 k-values are no whole 64-deep K-tiles
+    (9216, 1024, 4096, set()), (32768, 4096, 22016, set()), (8192, 2048, 2048, set())])
+def test_products_of_a_backward_pass_in_one_launch(plan, T, k, n, pairs):
+    for cus in (8, 31, 32, 64, 192, 256):
+        pair, d, w = plan.pair(T, k, n, cus)
+        if pair:
+            assert d >= 8 and w >= 8 and d % 8 == 0 and w % 8 == 0 and d + w <= cus, (cus, d, w)
+        if cus in (192, 256, 64):
+            assert bool(pair) == (cus in pairs), (cus, d, w)
+        if cus == 8:
+            assert not pair
