@@ -23,9 +23,10 @@
 // (bit-identical for any grid): the dK/dV kernel owns 128 or 256 keys and streams query
 // tiles; the dQ kernel owns 128 or 256 queries and streams key tiles.  Both recompute P from the saved
 // row log-sum-exp; D_i = sum_c dO_ic O_ic is formed by the dQ kernel, which runs first, from the
-// dO fragments it holds, and read by the dK/dV kernel.
+// dO fragments it holds; its negative is what the dK/dV kernels read.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include "kernels.h"
 #include "tile_queue.h"
 
@@ -104,14 +105,15 @@ struct LdsTile {
   // vector operand: the scalar offset field of the instruction is not range-checked.
   __device__ __forceinline__ void issue(i32x4 desc, unsigned base, unsigned dst) const {
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      const unsigned off = loff[j] + base;
-      // m0 = LDS address of lane 0's 16 bytes; lane l lands at m0 + 16*l.  Assembly, so that
-      // the compiler's wait-count pass does not put a vmcnt(0) in front of every LDS read;
-      // completion is waited for by hand before the barrier that publishes the tile.
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                   : : "s"(dst + (unsigned)(wave_base + j * 1024)), "v"(off), "s"(desc) : "m0");
-    }
+    for (int j = 0; j < NI; ++j) issue_j(desc, base, dst, j);
+  }
+  __device__ __forceinline__ void issue_j(i32x4 desc, unsigned base, unsigned dst, int j) const {
+    const unsigned off = loff[j] + base;
+    // m0 = LDS address of lane 0's 16 bytes; lane l lands at m0 + 16*l.  Assembly, so that
+    // the compiler's wait-count pass does not put a vmcnt(0) in front of every LDS read;
+    // completion is waited for by hand before the barrier that publishes the tile.
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 : : "s"(dst + (unsigned)(wave_base + j * 1024)), "v"(off), "s"(desc) : "m0");
   }
   // fragment whose contraction runs along the row: row `row`, columns 16*s + 8*hb .. +7
   __device__ static __forceinline__ bf16x8 nat(const lds_byte* t, int row, int s, int hb) {
@@ -153,6 +155,43 @@ __device__ __forceinline__ void wait_requests() {
 // ends step t.  Requests are issued for every step, past the last tile too (they point
 // outside the descriptor and fetch nothing), so that the wait count is a constant.
 template <int NW> struct Ring { static constexpr int NST = (NW == 8) ? 4 : 2, PD = NST - 1; };
+
+// Fragment addresses of one lane in a ring of stages, kept in registers and moved from stage to stage: formed for every read
+// they are a fifth of a block's vector instructions (forward at head size 64, B8 N1500 H20: 122.8 -> 117.4 us, on 64 CUs 237.8 -> 226.5; dQ 1 - 2 %).  The swizzle of a row repeats every 16 rows, so blocks of
+// 16 and 32 rows, and the second matrix of a stage, are offsets in the instruction.
+template <typename L, int D>
+struct TileReader {
+  const lds_byte *nat_[D / 16], *tr_[D / 32][2];
+  __device__ __forceinline__ void init(const lds_byte* at, int lr, int hb) {
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) nat_[s] = at + lr * L::ROWB + (((2 * s + hb) ^ L::swz(lr)) << 4);
+    const int lane = threadIdx.x & 63, G = lane >> 4, i = lane & 15, hh = G >> 1, q = i >> 2, g = i & 3;
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int r = 4 * hh + q + 8 * u, ch = 4 * c + 2 * (G & 1) + (g >> 1);
+        tr_[c][u] = at + r * L::ROWB + ((ch ^ L::swz(r)) << 4) + (g & 1) * 8;
+      }
+  }
+  __device__ __forceinline__ void move(int bytes) {
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) { nat_[s] += bytes; asm volatile("" : "+v"(nat_[s])); }
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) { tr_[c][u] += bytes; asm volatile("" : "+v"(tr_[c][u])); }
+  }
+  // LdsTile::nat of row `row` + lr and LdsTile::tr of rows from `row` on, `at` bytes into the stage
+  __device__ __forceinline__ bf16x8 nat(int s, int row, int at) const {
+    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(nat_[s] + row * L::ROWB + at);
+  }
+  __device__ __forceinline__ bf16x8 tr(int c, int row, int at) const {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(tr_[c][0] + row * L::ROWB + at));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(tr_[c][1] + row * L::ROWB + at));
+    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+};
 
 // registers 8*s2 .. 8*s2+7 of an accumulator block as a bf16 B-operand
 __device__ __forceinline__ bf16x8 pack8(const float* v) {
@@ -510,9 +549,9 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma(const bf16
     __syncthreads();
     unsigned entry = 0;
     const int claim_at = ntiles > kClaimTilesAhead ? ntiles - kClaimTilesAhead : 0;
+    TileReader<L, D> rd;
+    rd.init(smem, lr, hb);
     for (int t = 0; t < ntiles; ++t) {
-      const lds_byte* ks = smem + (t % NST) * STAGE;
-      const lds_byte* vs = ks + L::BYTES;
       request(t + PD);
       if (t == claim_at) entry = tq_claim_ahead(tq, qc);
       const int j0 = t * RS;
@@ -579,21 +618,21 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma(const bf16
         // runs under the second block's softmax.  Fragment reads are issued a phase ahead.
         bf16x8 kfa[NS], kfb[NS];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) kfa[s] = L::nat(ks, lr, s, hb);
+        for (int s = 0; s < NS; ++s) kfa[s] = rd.nat(s, 0, 0);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) kfb[s] = L::nat(ks, 32 + lr, s, hb);
+        for (int s = 0; s < NS; ++s) kfb[s] = rd.nat(s, 32, 0);
         __builtin_amdgcn_sched_barrier(0);
         const f32x16 sa = scores(kfa);
         const f32x16 sb = scores(kfb);
         bf16x8 vfa[NC][2];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) { vfa[c][0] = L::tr(vs, c, 0); vfa[c][1] = L::tr(vs, c, 16); }
+        for (int c = 0; c < NC; ++c) { vfa[c][0] = rd.tr(c, 0, L::BYTES); vfa[c][1] = rd.tr(c, 16, L::BYTES); }
         __builtin_amdgcn_sched_barrier(0);
         bf16x8 p0, p1;
         softmax_block(sa, j0, p0, p1);
         bf16x8 vfb[NC][2];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) { vfb[c][0] = L::tr(vs, c, 32); vfb[c][1] = L::tr(vs, c, 48); }
+        for (int c = 0; c < NC; ++c) { vfb[c][0] = rd.tr(c, 32, L::BYTES); vfb[c][1] = rd.tr(c, 48, L::BYTES); }
         add_pv(vfa, p0, p1);
         __builtin_amdgcn_sched_barrier(0);
         softmax_block(sb, j0 + 32, p0, p1);
@@ -601,17 +640,18 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma(const bf16
       } else if (visible(j0)) {
         bf16x8 kfr[NS];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) kfr[s] = L::nat(ks, lr, s, hb);
+        for (int s = 0; s < NS; ++s) kfr[s] = rd.nat(s, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         const f32x16 sa = scores(kfr);
         bf16x8 vfr[NC][2];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) { vfr[c][0] = L::tr(vs, c, 0); vfr[c][1] = L::tr(vs, c, 16); }
+        for (int c = 0; c < NC; ++c) { vfr[c][0] = rd.tr(c, 0, L::BYTES); vfr[c][1] = rd.tr(c, 16, L::BYTES); }
         __builtin_amdgcn_sched_barrier(0);
         bf16x8 p0, p1;
         softmax_block(sa, j0, p0, p1);
         add_pv(vfr, p0, p1);
       }
+      rd.move(t % NST == NST - 1 ? -(NST - 1) * STAGE : STAGE);
       wait_requests<(PD - 1) * NREQ>();    // this wave's share of the next tile has landed
       __syncthreads();
     }
@@ -688,7 +728,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dq_mfma(const bf16* 
       }
     }
     dlt += __shfl_xor(dlt, 32, 64);
-    if (i < N && hb == 0) delta[((int64_t)b * H + hd) * N + i] = dlt;
+    if (i < N && hb == 0) delta[((int64_t)b * H + hd) * N + i] = -dlt;
     const float lse2 = (i < N) ? lse[((int64_t)b * H + hd) * N + i] * kLog2e : 0.f;
     f32x16 dq[NC];
 #pragma unroll
@@ -713,9 +753,9 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dq_mfma(const bf16* 
     __syncthreads();
     unsigned entry = 0;
     const int claim_at = ntiles > kClaimTilesAhead ? ntiles - kClaimTilesAhead : 0;
+    TileReader<L, D> rd;
+    rd.init(smem, lr, hb);
     for (int t = 0; t < ntiles; ++t) {
-      const lds_byte* ks = smem + (t % NST) * STAGE;
-      const lds_byte* vs = ks + L::BYTES;
       request(t + PD);
       if (t == claim_at) entry = tq_claim_ahead(tq, qc);
       const int j0 = t * RS;
@@ -733,15 +773,15 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dq_mfma(const bf16* 
         bf16x8 kfr[NS], vfr[NS];
 #pragma unroll
         for (int s = 0; s < PF; ++s) {
-          kfr[s] = L::nat(ks, 32 * sub + lr, s, hb);
-          vfr[s] = L::nat(vs, 32 * sub + lr, s, hb);
+          kfr[s] = rd.nat(s, 32 * sub, 0);
+          vfr[s] = rd.nat(s, 32 * sub, L::BYTES);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
           if (s + PF < NS) {
-            kfr[s + PF] = L::nat(ks, 32 * sub + lr, s + PF, hb);
-            vfr[s + PF] = L::nat(vs, 32 * sub + lr, s + PF, hb);
+            kfr[s + PF] = rd.nat(s + PF, 32 * sub, 0);
+            vfr[s + PF] = rd.nat(s + PF, 32 * sub, L::BYTES);
           }
           sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[s], qf[s], sacc, 0, 0, 0);
           pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[s], dof[s], pacc, 0, 0, 0);
@@ -751,7 +791,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dq_mfma(const bf16* 
         // the probabilities are formed
         bf16x8 ta[NC], tb[NC];
 #pragma unroll
-        for (int c = 0; c < (NC < 2 ? NC : 2); ++c) { ta[c] = L::tr(ks, c, 32 * sub); tb[c] = L::tr(ks, c, 32 * sub + 16); }
+        for (int c = 0; c < (NC < 2 ? NC : 2); ++c) { ta[c] = rd.tr(c, 32 * sub, 0); tb[c] = rd.tr(c, 32 * sub + 16, 0); }
         __builtin_amdgcn_sched_barrier(0);
         // only blocks that touch the diagonal or the end of the sequence need the mask: a
         // masked score becomes -inf, so its recomputed probability is exactly 0
@@ -772,13 +812,14 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dq_mfma(const bf16* 
         // the one issued just before it
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          if (c + 2 < NC) { ta[c + 2] = L::tr(ks, c + 2, 32 * sub); tb[c + 2] = L::tr(ks, c + 2, 32 * sub + 16); }
+          if (c + 2 < NC) { ta[c + 2] = rd.tr(c + 2, 32 * sub, 0); tb[c + 2] = rd.tr(c + 2, 32 * sub + 16, 0); }
           dq[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ta[c], d0, dq[c], 0, 0, 0);
           if (c > 0) dq[c - 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tb[c - 1], d1, dq[c - 1], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
         }
         dq[NC - 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tb[NC - 1], d1, dq[NC - 1], 0, 0, 0);
       }
+      rd.move(t % NST == NST - 1 ? -(NST - 1) * STAGE : STAGE);
       wait_requests<(PD - 1) * NREQ>();
       __syncthreads();
     }
@@ -799,7 +840,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dq_mfma(const bf16* 
   tq_done(tq);
 }
 
-// --------------------------------------------------------------------------- dK, dV
+// ------------------------------------------------------------ dK, dV at head size 128
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dkv_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ dO,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
@@ -908,155 +949,70 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dkv_mfma(const bf16*
       request_next();                                  // block t + PD
       if (t == claim_at) entry = tq_claim_ahead(tq, qc);
       if (!(causal && ib + 31 < j0w) && j0w < N) {            // otherwise every (i, j) here is masked
-        if constexpr (D == 128) {
-          // at head size 128 the accumulators (128 registers), the K fragments (32) and the two
-          // score blocks leave no room for operand buffers: reads stay next to their use and the
-          // other wave of the SIMD covers their latency (with a lookahead the kernel spilled
-          // into scratch inside this loop and ran 9 % slower)
-          f32x16 sacc, pacc;
+        // at head size 128 the accumulators (128 registers), the K fragments (32) and the two
+        // score blocks leave no room for operand buffers: reads stay next to their use and the
+        // other wave of the SIMD covers their latency (with a lookahead the kernel spilled
+        // into scratch inside this loop and ran 9 % slower)
+        f32x16 sacc, pacc;
 #pragma unroll
-          for (int e = 0; e < 16; ++e) { sacc[e] = 0.f; pacc[e] = 0.f; }
+        for (int e = 0; e < 16; ++e) { sacc[e] = 0.f; pacc[e] = 0.f; }
 #pragma unroll
-          for (int s = 0; s < NS; ++s) {
-            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L::nat(qs, lr, s, hb), kf[s], sacc, 0, 0, 0);
-            pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L::nat(dos, lr, s, hb), LV::nat(vblk, 32 * wave + lr, s, hb), pacc, 0, 0, 0);
+        for (int s = 0; s < NS; ++s) {
+          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L::nat(qs, lr, s, hb), kf[s], sacc, 0, 0, 0);
+          pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L::nat(dos, lr, s, hb), LV::nat(vblk, 32 * wave + lr, s, hb), pacc, 0, 0, 0);
+        }
+        // only blocks that touch the diagonal or the end of the sequence need the mask: a
+        // masked score becomes -inf, so its recomputed probability is exactly 0
+        if ((ib + 32 > N) || (j0w + 32 > N) || (causal && j0w + 31 > ib)) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int gi = ib + acc_row(r, hb);
+            if ((gi >= N) || (j >= N) || (causal && j > gi)) sacc[r] = -INFINITY;
           }
-          // only blocks that touch the diagonal or the end of the sequence need the mask: a
-          // masked score becomes -inf, so its recomputed probability is exactly 0
-          if ((ib + 32 > N) || (j0w + 32 > N) || (causal && j0w + 31 > ib)) {
+        }
+        // registers 4g .. 4g+3 of a lane hold query rows 8g + 4*hb + {0..3}: their statistics
+        // are four consecutive floats, one 16-byte LDS read each
+        float pv[16], ds[16];
+        const float4* sl4 = reinterpret_cast<const float4*>(sl + 4 * hb);
+        const float4* sd4 = reinterpret_cast<const float4*>(sd + 4 * hb);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int gi = ib + acc_row(r, hb);
-              if ((gi >= N) || (j >= N) || (causal && j > gi)) sacc[r] = -INFINITY;
-            }
+        for (int g = 0; g < 4; ++g) {
+          const float4 l4 = sl4[2 * g], d4 = sd4[2 * g];
+          const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int r = 4 * g + e;
+            const float p = fast_exp2(fmaf(sacc[r], scale_log2, -lv[e] * kLog2e));
+            pv[r] = p;
+            ds[r] = p * (pacc[r] + dv4[e]);     // dv4: minus delta
           }
-          // registers 4g .. 4g+3 of a lane hold query rows 8g + 4*hb + {0..3}: their statistics
-          // are four consecutive floats, one 16-byte LDS read each
-          float pv[16], ds[16];
-          const float4* sl4 = reinterpret_cast<const float4*>(sl + 4 * hb);
-          const float4* sd4 = reinterpret_cast<const float4*>(sd + 4 * hb);
+        }
+        const bf16x8 p0 = pack8(pv), p1 = pack8(pv + 8), d0 = pack8(ds), d1 = pack8(ds + 8);
+        // From here on S, dP and the unpacked P and dS are dead: their registers hold a ring of
+        // transposed fragments read DKV_PF matrix instructions ahead (left to itself the compiler
+        // reads every fragment into the same four registers right in front of its instruction).
+        // Product w of 4 * NC: column block w / 4; w % 4 = 0: dV, keys half 0; 1: dK, half 0;
+        // 2: dV, half 1; 3: dK, half 1 (each accumulator takes half 0 first, as before).
+        constexpr int PF = DKV_PF;
+        auto tr_operand = [&](int w) -> bf16x8 {
+          const int c = w >> 2, part = w & 3;
+          return L::tr((part & 1) ? qs : dos, c, 16 * (part >> 1));
+        };
+        bf16x8 ta[PF + 1];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const float4 l4 = sl4[2 * g], d4 = sd4[2 * g];
-            const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+        for (int w = 0; w < PF; ++w) ta[w] = tr_operand(w);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int r = 4 * g + e;
-              const float p = fast_exp2(fmaf(sacc[r], scale_log2, -lv[e] * kLog2e));
-              pv[r] = p;
-              ds[r] = p * (pacc[r] - dv4[e]);
-            }
-          }
-          const bf16x8 p0 = pack8(pv), p1 = pack8(pv + 8), d0 = pack8(ds), d1 = pack8(ds + 8);
-          // From here on S, dP and the unpacked P and dS are dead: their registers hold a ring of
-          // transposed fragments read DKV_PF matrix instructions ahead (left to itself the compiler
-          // reads every fragment into the same four registers right in front of its instruction).
-          // Product w of 4 * NC: column block w / 4; w % 4 = 0: dV, keys half 0; 1: dK, half 0;
-          // 2: dV, half 1; 3: dK, half 1 (each accumulator takes half 0 first, as before).
-          constexpr int PF = DKV_PF;
-          auto tr_operand = [&](int w) -> bf16x8 {
-            const int c = w >> 2, part = w & 3;
-            return L::tr((part & 1) ? qs : dos, c, 16 * (part >> 1));
-          };
-          bf16x8 ta[PF + 1];
+        for (int w = 0; w < 4 * NC; ++w) {
+          if (w + PF < 4 * NC) ta[(w + PF) % (PF + 1)] = tr_operand(w + PF);
+          const int c = w >> 2, part = w & 3;
+          const bf16x8 a = ta[w % (PF + 1)];
+          if (part == 0) dv[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p0, dv[c], 0, 0, 0);
+          else if (part == 1) dk[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, d0, dk[c], 0, 0, 0);
+          else if (part == 2) dv[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p1, dv[c], 0, 0, 0);
+          else dk[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, d1, dk[c], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int w = 0; w < PF; ++w) ta[w] = tr_operand(w);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int w = 0; w < 4 * NC; ++w) {
-            if (w + PF < 4 * NC) ta[(w + PF) % (PF + 1)] = tr_operand(w + PF);
-            const int c = w >> 2, part = w & 3;
-            const bf16x8 a = ta[w % (PF + 1)];
-            if (part == 0) dv[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p0, dv[c], 0, 0, 0);
-            else if (part == 1) dk[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, d0, dk[c], 0, 0, 0);
-            else if (part == 2) dv[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p1, dv[c], 0, 0, 0);
-            else dk[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, d1, dk[c], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        } else {
-          // Operands come from LDS a fixed number of matrix instructions ahead of their use (a
-          // read issued right in front of the instruction that needs it costs the wave a whole
-          // LDS round trip per instruction); scheduling barriers keep that distance.
-          constexpr int PF = 2, PFS = 2;
-          f32x16 sacc, pacc;
-#pragma unroll
-          for (int e = 0; e < 16; ++e) { sacc[e] = 0.f; pacc[e] = 0.f; }
-          if constexpr (PFS > 0) {
-            bf16x8 qa[PFS + 1], da[PFS + 1], va[PFS + 1];       // Q, dO and V fragments of contraction step s in slot s % (PFS + 1)
-#pragma unroll
-            for (int s = 0; s < PFS; ++s) {
-              qa[s] = L::nat(qs, lr, s, hb); da[s] = L::nat(dos, lr, s, hb); va[s] = LV::nat(vblk, 32 * wave + lr, s, hb);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-              if (s + PFS < NS) {
-                const int n = (s + PFS) % (PFS + 1);
-                qa[n] = L::nat(qs, lr, s + PFS, hb); da[n] = L::nat(dos, lr, s + PFS, hb); va[n] = LV::nat(vblk, 32 * wave + lr, s + PFS, hb);
-              }
-              sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[s % (PFS + 1)], kf[s], sacc, 0, 0, 0);
-              pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da[s % (PFS + 1)], va[s % (PFS + 1)], pacc, 0, 0, 0);
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          } else {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-              sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L::nat(qs, lr, s, hb), kf[s], sacc, 0, 0, 0);
-              pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L::nat(dos, lr, s, hb), LV::nat(vblk, 32 * wave + lr, s, hb), pacc, 0, 0, 0);
-            }
-          }
-          // the first transposed fragments of the products below are on their way while the
-          // probabilities are formed.  Product w of 4 * NC: column block w / 4; w % 4 = 0: dV, keys
-          // half 0; 1: dK, half 0; 2: dV, half 1; 3: dK, half 1 (each accumulator takes half 0 first,
-          // and no instruction follows one that writes the same accumulator)
-          auto tr_operand = [&](int w) -> bf16x8 {
-            const int c = w >> 2, part = w & 3;
-            return L::tr((part & 1) ? qs : dos, c, 16 * (part >> 1));
-          };
-          bf16x8 ta[PF + 1];
-#pragma unroll
-          for (int w = 0; w < PF; ++w) ta[w] = tr_operand(w);
-          __builtin_amdgcn_sched_barrier(0);
-          // only blocks that touch the diagonal or the end of the sequence need the mask: a
-          // masked score becomes -inf, so its recomputed probability is exactly 0
-          if ((ib + 32 > N) || (j0w + 32 > N) || (causal && j0w + 31 > ib)) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int gi = ib + acc_row(r, hb);
-              if ((gi >= N) || (j >= N) || (causal && j > gi)) sacc[r] = -INFINITY;
-            }
-          }
-          // registers 4g .. 4g+3 of a lane hold query rows 8g + 4*hb + {0..3}: their statistics
-          // are four consecutive floats, one 16-byte LDS read each
-          float pv[16], ds[16];
-          const float4* sl4 = reinterpret_cast<const float4*>(sl + 4 * hb);
-          const float4* sd4 = reinterpret_cast<const float4*>(sd + 4 * hb);
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const float4 l4 = sl4[2 * g], d4 = sd4[2 * g];
-            const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int r = 4 * g + e;
-              const float p = fast_exp2(fmaf(sacc[r], scale_log2, -lv[e] * kLog2e));
-              pv[r] = p;
-              ds[r] = p * (pacc[r] - dv4[e]);
-            }
-          }
-          const bf16x8 p0 = pack8(pv), p1 = pack8(pv + 8), d0 = pack8(ds), d1 = pack8(ds + 8);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int w = 0; w < 4 * NC; ++w) {
-            if (w + PF < 4 * NC) ta[(w + PF) % (PF + 1)] = tr_operand(w + PF);
-            const int c = w >> 2, part = w & 3;
-            const bf16x8 a = ta[w % (PF + 1)];
-            if (part == 0) dv[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p0, dv[c], 0, 0, 0);
-            else if (part == 1) dk[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, d0, dk[c], 0, 0, 0);
-            else if (part == 2) dv[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p1, dv[c], 0, 0, 0);
-            else dk[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, d1, dk[c], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-          }
         }
       }
       ib += RS;
@@ -1088,6 +1044,364 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dkv_mfma(const bf16*
           for (int e = 0; e < 4; ++e) vv[e] = (bf16)dv[c][4 * g + e];
           *reinterpret_cast<bf16x4*>(out + vo + 32 * c + 8 * g + 4 * hb) = vv;
         }
+    }
+    item = tq_next(tq, qc, entry, &mail);
+  }
+  tq_done(tq);
+}
+
+// ------------------------------------------------------------- dK, dV at head size 64
+// Bound by instruction issue and by the round trips of a wave's chain (scores, probabilities, products) that the other
+// wave of the SIMD does not cover: attn_bwd_dkv_mfma issues 288 instructions and waits a third of its time
+// per 32x32 block of scores, 16 of them matrix instructions (1510 cycles of a SIMD per block for 512 of matrix work).  Here a block takes
+// about 160, and its phases are skewed by half a block so that a wave's vector work has matrix work of its own beside it:
+//   (1) products of rows 16..31 of block t-1 into dV and dK beside P and dS of rows 0..15 of block t,
+//   (2) products of rows 0..15 of block t beside P and dS of its rows 16..31,
+//   (3) S and dP of block t+1.
+//   * K enters as -K / 8 (exact: the softmax scale of 64 columns is 2^-3) and the S accumulator starts from lse, dP from
+//     minus delta: the accumulators are then lse - s and dP - delta, and a probability takes a multiplication
+//     and an exponential, a dS one multiplication.
+//   * V fragments stay in registers, LDS addresses advance once per tile of two blocks.
+//   * three stages of 64 rows (the tile of block t-1 is read transposed, that of t+1 by rows, one is landing), one
+//     barrier per tile.
+// B8 N1500 H20, this kernel alone: 284 -> 240 us, 1510 -> 1200 cycles per block, matrix cores busy 0.34 -> 0.43; backward pass
+// on 64 CUs 1049 -> 841; B16 N576 H16 backward 125 -> 116.  One wave per SIMD with 64 keys each (half the LDS reads, 512
+// registers) issued fewer instructions still and was slower, 344 us: one wave's chain of 350 instructions a step, 5.3 cycles each at
+// best, has nothing beside it.  Operands requested a phase earlier still: no change.
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+__device__ __forceinline__ unsigned pack2(float a, float b) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  bf16x2 v; v[0] = (bf16)a; v[1] = (bf16)b;
+  return __builtin_bit_cast(unsigned, v);
+}
+struct PackedHalf { u32x4 p, d; };            // P and dS of 16 rows as operands
+
+// dK and dV (a0 .. a63) and the K and V fragments (a64 .. a95) live in accumulator registers that the assembly below names
+// itself: as C++ values, carried through the branches of a step, the compiler keeps two copies of the accumulators and spills.
+// Every such statement declares all 96 overwritten, so the compiler keeps nothing there across one, and as long as
+// the kernel fits in its vector registers it has no reason to touch them in between (tests/test_host_wait_states.py looks).
+// It also knows nothing of a matrix instruction's latency in an assembly string: settle() and ready() keep the distances.
+struct Acc {
+#define MOSAIC_A10(t) "a" #t "0", "a" #t "1", "a" #t "2", "a" #t "3", "a" #t "4", "a" #t "5", "a" #t "6", "a" #t "7", "a" #t "8", "a" #t "9"
+#define MOSAIC_ACC MOSAIC_A10(), MOSAIC_A10(1), MOSAIC_A10(2), MOSAIC_A10(3), MOSAIC_A10(4), MOSAIC_A10(5), MOSAIC_A10(6), MOSAIC_A10(7), MOSAIC_A10(8), \
+                   "a90", "a91", "a92", "a93", "a94", "a95"
+  template <int R> __device__ static __forceinline__ void add(const bf16x8& a, const bf16x8& b) {         // a[R .. R + 15] += a b
+    static_assert(R % 16 == 0 && R < 64, "an accumulator");
+    asm volatile("v_mfma_f32_32x32x16_bf16 a[%c2:%c3], %0, %1, a[%c2:%c3]" : : "v"(a), "v"(b), "n"(R), "n"(R + 15) : MOSAIC_ACC);
+  }
+  template <int R> __device__ static __forceinline__ void add_to(f32x16& c, const bf16x8& a) {            // c += a fragment(a[R .. R + 3])
+    static_assert(R % 4 == 0 && R >= 64 && R < 96, "a fragment");
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, a[%c2:%c3], %0" : "+v"(c) : "v"(a), "n"(R), "n"(R + 3) : MOSAIC_ACC);
+  }
+  template <int R = 0> __device__ static __forceinline__ void clear() {
+    if constexpr (R < 64) {
+      asm volatile("v_accvgpr_write_b32 a%c0, 0" : : "n"(R) : MOSAIC_ACC);
+      clear<R + 1>();
+    }
+  }
+  template <int R> __device__ static __forceinline__ void put(const bf16x8& f) {
+    const u32x4 x = __builtin_bit_cast(u32x4, f);
+    asm volatile("v_accvgpr_write_b32 a%c4, %0\n\tv_accvgpr_write_b32 a%c5, %1\n\tv_accvgpr_write_b32 a%c6, %2\n\tv_accvgpr_write_b32 a%c7, %3"
+                 : : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "n"(R), "n"(R + 1), "n"(R + 2), "n"(R + 3) : MOSAIC_ACC);
+  }
+  template <int R> __device__ static __forceinline__ float get() {
+    float x;
+    asm volatile("v_accvgpr_read_b32 %0, a%c1" : "=v"(x) : "n"(R));
+    return x;
+  }
+  // 12 wait states from a matrix instruction to a vector instruction that reads its result, two from a vector instruction to a
+  // matrix instruction that reads its
+  __device__ static __forceinline__ void settle() { asm volatile("s_nop 7\n\ts_nop 4"); __builtin_amdgcn_sched_barrier(0); }
+  __device__ static __forceinline__ void ready() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 1");
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
+// f(integral_constant 0), f(1), .. : loops whose index names a register
+template <int N, int I = 0, typename F> __device__ __forceinline__ void unrolled(F&& f) {
+  if constexpr (I < N) { f(std::integral_constant<int, I>{}); unrolled<N, I + 1>(f); }
+}
+
+struct DkvSkew {
+  static constexpr int D = 64, RS = 64, NST = 3;
+  typedef LdsTile<RS, D, 4> L;
+  static constexpr int STATS = 2 * L::BYTES, STAGE = 2 * L::BYTES + 512;      // Q | dO | lse | -delta
+  static constexpr int SMEM = NST * STAGE;
+};
+
+__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_skew(const bf16* __restrict__ qkv, const bf16* __restrict__ dO,
+                                                            const float* __restrict__ lse, const float* __restrict__ mdelta,
+                                                            bf16* __restrict__ dqkv, int B, int N, int H, int Hkv, int causal,
+                                                            int ktiles, int hblk, TileQueueArgs tq) {
+  typedef DkvSkew C;
+  typedef C::L L;
+  constexpr int D = C::D, RS = C::RS, NS = D / 16, NC = D / 32, STAGE = C::STAGE, KT = 128;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const lds_byte* smem = (const lds_byte*)smem_raw;
+  const unsigned lds0 = (unsigned)(uintptr_t)smem;
+  L ld, ldo;
+  ld.init((unsigned)((H + 2 * Hkv) * D * 2));
+  ldo.init((unsigned)(H * D * 2));
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 31, hb = lane >> 5;
+  const int h = H * D, ko = H * D, vo = (H + Hkv) * D, GQ = H / Hkv;
+  const int64_t rs = (int64_t)(H + 2 * Hkv) * D;
+  __shared__ int mail;
+  TileQueueCursor qc;
+  int item = tq_first(tq, qc, &mail);
+  while (item >= 0) {
+    int head_, kt_i;
+    attn_item(item, B * Hkv, ktiles, hblk, false, attn_mirror(tq, qc, ktiles), &head_, &kt_i);
+    const int kvh = head_ % Hkv, b = head_ / Hkv;
+    const int hd0 = kvh * GQ;
+    const int k0 = kt_i * KT, j0w = k0 + 32 * wave, j = j0w + lr;
+    const bf16* rowb = qkv + (int64_t)b * N * rs;
+    const bf16* base = rowb + hd0 * D;
+    const bf16* dob = dO + (int64_t)b * N * h + hd0 * D;
+    const int q_begin = causal ? k0 : 0;
+    const int ntq = (N - q_begin + RS - 1) / RS;       // streamed tiles of one query head
+    const int ntiles = ntq * GQ;
+    auto desc_f32 = [&](const float* p) {
+      i32x4 d;
+      d.x = (int)(uint32_t)(uintptr_t)p; d.y = (int)((uint32_t)((uintptr_t)p >> 32) & 0xffffu);
+      d.z = GQ * N * 4; d.w = 0x00020000;
+      return d;
+    };
+    const i32x4 ds_ = desc_f32((wave ? mdelta : lse) + ((int64_t)b * H + hd0) * N);
+    const i32x4 dq_ = slice_desc(base, N, rs, GQ * D), do_ = slice_desc(dob, N, h, GQ * D);
+    const unsigned rsb = (unsigned)(rs * 2), hsb = (unsigned)(h * 2);
+    // the next tile to request: number, tiles left in its head, stage, and the offsets of its first row in q, dO and the statistics
+    int rq_t = 0, rq_left = ntq;
+    unsigned rq_dst = lds0, rq_q = (unsigned)q_begin * rsb, rq_o = (unsigned)q_begin * hsb, rq_i = (unsigned)q_begin, rq_end = (unsigned)N;
+    auto request = [&]() {
+      ld.issue(dq_, rq_q, rq_dst);
+      ldo.issue(do_, rq_o, rq_dst + L::BYTES);
+      if (wave < 2) {                                   // per-row statistics, 4 bytes a lane: lse by wave 0, -delta by wave 1
+        const unsigned off = rq_i + (unsigned)lane < rq_end ? (rq_i + (unsigned)lane) * 4u : 0xFFFFFFF0u;
+        i32x4 d = ds_;
+        // the descriptor may come back from lanes of a vector register: five wait states before a memory instruction reads it
+        asm volatile("s_nop 4" : "+s"(d));
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" : : "s"(rq_dst + (unsigned)(C::STATS + 256 * wave)), "v"(off), "s"(d) : "m0");
+      }
+      ++rq_t;
+      rq_dst = rq_dst == lds0 + (unsigned)((C::NST - 1) * STAGE) ? lds0 : rq_dst + (unsigned)STAGE;
+      rq_q += RS * rsb; rq_o += RS * hsb; rq_i += RS;
+      if (--rq_left == 0) {                             // the next head: its columns, its rows of statistics
+        rq_left = ntq;
+        rq_q += (unsigned)(2 * D) - (unsigned)ntq * RS * rsb;
+        rq_o += (unsigned)(2 * D) - (unsigned)ntq * RS * hsb;
+        rq_i += (unsigned)N - (unsigned)ntq * RS;
+        rq_end += (unsigned)N;
+      }
+    };
+    __syncthreads();                                    // the previous item's readers are done with the LDS
+    request();
+    if (ntiles > 1) request();
+    unrolled<NS>([&](auto s_) {
+      constexpr int s = decltype(s_)::value;
+      const bf16* at = rowb + (int64_t)j * rs + kvh * D + 16 * s + 8 * hb;
+      const bf16x8 z = {};
+      const bf16x8 k = j < N ? *reinterpret_cast<const bf16x8*>(at + ko) : z;
+      bf16x8 mk;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mk[e] = (bf16)((float)k[e] * -0.125f);
+      Acc::put<64 + 4 * s>(mk);
+      Acc::put<80 + 4 * s>(j < N ? *reinterpret_cast<const bf16x8*>(at + vo) : z);
+    });
+    Acc::clear();
+    wait_requests<0>();
+    __syncthreads();
+
+    // addresses: `nat` and `stat` of the tile of block t+1's scores, `trp` of the tile of the pending products
+    const lds_byte *nat[NS], *trp[NC][2], *stat;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) nat[s] = smem + lr * L::ROWB + (((2 * s + hb) ^ L::swz(lr)) << 4);
+    {
+      const int G = lane >> 4, i = lane & 15, hh = G >> 1, q = i >> 2, g = i & 3;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int r = 4 * hh + q + 8 * u, ch = 4 * c + 2 * (G & 1) + (g >> 1);
+          trp[c][u] = smem + r * L::ROWB + ((ch ^ L::swz(r)) << 4) + (g & 1) * 8;
+        }
+    }
+    stat = smem + C::STATS + hb * 16;
+    // swz of a row repeats every 16 rows: offsets of 16 and 32 rows are plain additions
+    auto read_nat = [&](int s, int at) -> bf16x8 { return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(nat[s] + at); };
+    // transposed fragment f of rows half `half` of block `sub` of the tile: column block f / 2 of dO (f even) or Q (odd)
+    auto read_tr = [&](int f, int half, int sub) -> bf16x8 {
+      const int c = f >> 1, at = ((f & 1) ? 0 : L::BYTES) + (32 * sub + 16 * half) * L::ROWB;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(trp[c][0] + at));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(trp[c][1] + at));
+      return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto add_product = [&](auto f_, const bf16x8& a, const PackedHalf& pk) {
+      constexpr int f = decltype(f_)::value, c = f >> 1;
+      if constexpr (f & 1) Acc::add<16 * c>(a, __builtin_bit_cast(bf16x8, pk.d));
+      else Acc::add<32 + 16 * c>(a, __builtin_bit_cast(bf16x8, pk.p));
+    };
+    constexpr int NF = 2 * NC, PF = 3;                  // transposed fragments of half a block, read this many ahead
+    f32x16 S, dP;                                       // lse - s, dP - delta
+    // a probability and a dS of row register r, in two steps (the exponential's result is not there at once)
+    struct Rows { float e[2], ds[2], p; };
+    auto unit_a = [&](Rows& w, int r) { w.e[r & 1] = fast_exp2(S[r] * -kLog2e); };
+    auto unit_b = [&](Rows& w, int r, PackedHalf& pk) {
+      w.ds[r & 1] = w.e[r & 1] * dP[r];
+      if (r & 1) {
+        pk.p[(r >> 1) & 3] = pack2(w.p, w.e[1]);
+        pk.d[(r >> 1) & 3] = pack2(w.ds[0], w.ds[1]);
+      } else {
+        w.p = w.e[0];                     // until its pair is packed
+      }
+    };
+    auto scores = [&](int sub) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 x = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(stat + 128 * sub + g * 32);
+        const f32x4 y = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(stat + 256 + 128 * sub + g * 32);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { S[4 * g + e] = x[e]; dP[4 * g + e] = y[e]; }
+      }
+      constexpr int LA = 2;                             // contraction steps read ahead
+      bf16x8 qa[LA + 1], oa[LA + 1];
+      auto read = [&](int s) {
+        qa[s % (LA + 1)] = read_nat(s, 32 * sub * L::ROWB);
+        oa[s % (LA + 1)] = read_nat(s, L::BYTES + 32 * sub * L::ROWB);
+      };
+#pragma unroll
+      for (int s = 0; s < LA; ++s) read(s);
+      __builtin_amdgcn_sched_barrier(0);
+      unrolled<NS>([&](auto s_) {
+        constexpr int s = decltype(s_)::value;
+        if constexpr (s + LA < NS) read(s + LA);
+        Acc::add_to<64 + 4 * s>(S, qa[s % (LA + 1)]);
+        Acc::add_to<80 + 4 * s>(dP, oa[s % (LA + 1)]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    // Blocks of 32 rows of a head, from q_begin on: those from `first` to `last` count for this wave's keys, those from
+    // `plain` to `full` need no mask (keys past the end need none: their columns are not stored).
+    const int shift = (j0w - q_begin) >> 5;
+    const int first = j0w >= N ? 1 << 30 : causal ? shift : 0, last = (N - q_begin + 31) >> 5;
+    const int plain = causal ? shift + 1 : 0, full = (N - q_begin) >> 5;
+    auto visible = [&](int blk) { return blk >= first && blk < last; };
+    int blk = 0, st = 0;                                // first block and stage of the current tile
+    bool pending = false;                               // rows 16..31 of the block before
+    PackedHalf pend = {};
+    unsigned entry = 0;
+    const int claim_at = ntiles > kClaimTilesAhead ? ntiles - kClaimTilesAhead : 0;
+    // products of half a block with nothing beside them
+    auto add_half = [&](int half, int sub, const PackedHalf& pk) {
+      Acc::ready();
+      unrolled<NF>([&](auto f) { add_product(f, read_tr(f, half, sub), pk); });
+    };
+    // phases (1) and (2) of block `sub` of the tile; step: bytes from the pending block's tile to this one's
+    auto block = [&](int sub, int step) {
+      const bool cur = visible(blk + sub), unmasked = blk + sub >= plain && blk + sub < full;
+      auto advance = [&]() {
+        if (sub) return;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) { trp[c][u] += step; asm volatile("" : "+v"(trp[c][u])); }
+      };
+      if (pending && cur && unmasked) {
+        PackedHalf now;
+        Rows w;
+        bf16x8 ta[PF + 1];
+#pragma unroll
+        for (int f = 0; f < PF; ++f) ta[f] = read_tr(f, 1, 1 - sub);
+        __builtin_amdgcn_sched_barrier(0);
+        unrolled<2>([&](auto half_) {
+          constexpr int half = decltype(half_)::value;
+          if constexpr (half) Acc::ready();
+          unrolled<NF>([&](auto f_) {
+            constexpr int f = decltype(f_)::value, g = f + PF;       // g: the fragment to read; past the last one of (1), those of (2)
+            if constexpr (half == 0 && g == NF) advance();
+            if constexpr (g < NF) ta[(half * NF + g) % (PF + 1)] = read_tr(g, 1 - half, half ? sub : 1 - sub);
+            else if constexpr (half == 0) ta[g % (PF + 1)] = read_tr(g - NF, 0, sub);
+            add_product(f_, ta[(half * NF + f) % (PF + 1)], half ? now : pend);
+            if constexpr (half == 0 && f == 0) Acc::settle();
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const int r = 8 * half + 2 * f + u;
+              unit_a(w, r);
+              if (2 * f + u > 0) unit_b(w, r - 1, half ? pend : now);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          });
+          unit_b(w, 8 * half + 7, half ? pend : now);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      } else {
+        if (pending) add_half(1, 1 - sub, pend);
+        advance();
+        if (cur) {
+          Acc::settle();
+          PackedHalf now;
+          Rows w;
+          if (!unmasked) {
+            const int i0 = q_begin + 32 * (blk + sub);
+            const int lo = causal ? j - i0 - 4 * hb : 0, hi = N - i0 - 4 * hb;       // rows of this lane that count, from i0 + 4 hb on
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int at = acc_row(r, 0);
+              S[r] = (at < lo || at >= hi) ? INFINITY : S[r];
+            }
+          }
+#pragma unroll
+          for (int r = 0; r < 8; ++r) { unit_a(w, r); unit_b(w, r, now); }
+          add_half(0, sub, now);
+#pragma unroll
+          for (int r = 8; r < 16; ++r) { unit_a(w, r); unit_b(w, r, pend); }
+        }
+      }
+      pending = cur;
+    };
+    // without scores the accumulators hold nothing: said to the compiler, which would carry (and copy) the old ones
+    auto no_scores = [&]() { asm volatile("" : "=v"(S), "=v"(dP)); };
+    if (visible(0)) scores(0); else no_scores();
+#pragma unroll 1
+    for (int t = 0; t < ntiles; ++t) {
+      if (t == claim_at) entry = tq_claim_ahead(tq, qc);
+      const int step = t == 0 ? 0 : st == 0 ? -(C::NST - 1) * STAGE : STAGE;
+      block(0, step);
+      if (visible(blk + 1)) scores(1); else no_scores();
+      block(1, 0);
+      // The next tile: all requests of this wave have landed; its reads of the tile before this one feed products above.
+      __builtin_amdgcn_sched_barrier(0);
+      wait_requests<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (rq_t < ntiles) request();                     // into the stage that was freed
+      const int wrap = st == C::NST - 1 ? -(C::NST - 1) * STAGE : STAGE;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) { nat[s] += wrap; asm volatile("" : "+v"(nat[s])); }
+      stat += wrap;
+      asm volatile("" : "+v"(stat));
+      st = st == C::NST - 1 ? 0 : st + 1;
+      blk += 2;
+      if (blk >= last) blk = 0;                         // the next head of the group
+      if (t + 1 < ntiles && visible(blk)) scores(0); else no_scores();
+    }
+    if (pending) add_half(1, 1, pend);
+    Acc::settle();
+    if (j < N) {
+      bf16* out = dqkv + ((int64_t)b * N + j) * rs + kvh * D;
+      // dK rows first, then dV rows: see attn_bwd_dkv_mfma
+      unrolled<16>([&](auto u) {
+        constexpr int q = decltype(u)::value, kind = q / 8, c = q / 4 % 2, g = q % 4;      // kind 0: dK
+        constexpr float f = kind ? 1.0f : 0.125f;
+        bf16x4 v;
+        v[0] = (bf16)(Acc::get<4 * q>() * f); v[1] = (bf16)(Acc::get<4 * q + 1>() * f);
+        v[2] = (bf16)(Acc::get<4 * q + 2>() * f); v[3] = (bf16)(Acc::get<4 * q + 3>() * f);
+        *reinterpret_cast<bf16x4*>(out + (kind ? vo : ko) + 32 * c + 8 * g + 4 * hb) = v;
+        if constexpr (q == 7) __builtin_amdgcn_sched_barrier(0);
+      });
     }
     item = tq_next(tq, qc, entry, &mail);
   }
@@ -1160,15 +1474,22 @@ mosaic_status bwd_t(hipStream_t s, int quota, int B, int N, int H, int Hkv, int 
     MOSAIC_LAUNCH_CHECK();
   }
   {
-    constexpr size_t smem = (size_t)Ring<NW>::NST * 2 * LdsTile<32, D, NW>::BYTES + LdsTile<32 * NW, D, NW>::BYTES +
-                            (size_t)Ring<NW>::NST * 2 * 64 * sizeof(float);
     static std::once_flag once;
     static hipError_t once_rc = hipSuccess;
     TileQueueArgs tq;
     int grid, hb;
-    MOSAIC_TRY(launch_queued(attn_bwd_dkv_mfma<D, NW>, once, once_rc, smem, s, quota, 8 / NW, (int64_t)B * Hkv, tiles, causal, &tq, &grid, &hb));
-    attn_bwd_dkv_mfma<D, NW><<<grid, 64 * NW, smem, s>>>(qkv, dO, lse, delta, dqkv, B, N, H, Hkv, causal, scale, tiles, hb, tq);
-    MOSAIC_LAUNCH_CHECK();
+    if constexpr (D == 64) {
+      constexpr size_t smem = DkvSkew::SMEM;
+      MOSAIC_TRY(launch_queued(attn_bwd_dkv_skew, once, once_rc, smem, s, quota, 2, (int64_t)B * Hkv, tiles, causal, &tq, &grid, &hb));
+      attn_bwd_dkv_skew<<<grid, 256, smem, s>>>(qkv, dO, lse, delta, dqkv, B, N, H, Hkv, causal, tiles, hb, tq);
+      MOSAIC_LAUNCH_CHECK();
+    } else {
+      constexpr size_t smem = (size_t)Ring<NW>::NST * 2 * LdsTile<32, D, NW>::BYTES + LdsTile<32 * NW, D, NW>::BYTES +
+                              (size_t)Ring<NW>::NST * 2 * 64 * sizeof(float);
+      MOSAIC_TRY(launch_queued(attn_bwd_dkv_mfma<D, NW>, once, once_rc, smem, s, quota, 8 / NW, (int64_t)B * Hkv, tiles, causal, &tq, &grid, &hb));
+      attn_bwd_dkv_mfma<D, NW><<<grid, 64 * NW, smem, s>>>(qkv, dO, lse, delta, dqkv, B, N, H, Hkv, causal, scale, tiles, hb, tq);
+      MOSAIC_LAUNCH_CHECK();
+    }
   }
   return MOSAIC_OK;
 }

@@ -180,6 +180,32 @@ def test_attention_fwd_bwd(mb, dtype, B, N, H, d, causal):
             assert np.array_equal(a, b0)
 
 
+@pytest.mark.parametrize("B,N,H,Hkv,causal", [(1, 31, 1, 1, 0), (1, 33, 2, 1, 1), (1, 64, 1, 1, 1), (1, 65, 3, 1, 0), (2, 127, 2, 2, 1),
+                                              (1, 128, 2, 1, 1), (1, 161, 4, 2, 1), (1, 192, 1, 1, 0), (1, 290, 4, 1, 1), (1, 321, 2, 2, 0)])
+def test_attention_bwd_of_64_columns_at_block_edges(mb, B, N, H, Hkv, causal):
+    """The dK/dV kernel at head size 64 takes 32-row blocks of 64-row tiles through three stages, with half a block
+    always pending: sequences that end in every place of a tile, one tile and more than the ring holds, groups of
+    query heads streamed one after the other (the pending half then belongs to the head before), diagonal blocks."""
+    d = 64
+    w = (H + 2 * Hkv) * d
+    qkv = quantize(synth.normal(500 + N, (B * N, w)), "bf16")
+    dO = quantize(synth.normal(501 + N, (B * N, H * d)), "bf16")
+    ref = O.attention_bwd(qkv, dO, B, N, H, causal, Hkv)
+    qkv_, dO_ = to_dev(qkv, "bf16"), to_dev(dO, "bf16")
+    outs = []
+    for q in (256, 8):                     # a workgroup per item; several items per workgroup
+        Oo = empty((B * N, H * d), "bf16"); dqkv = torch.full((B * N, w), float("nan"), dtype=torch.bfloat16, device="cuda")
+        lse, delta = [torch.full((B, H, N), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)]
+        mb.op_attention_gqa_fwd(None, q, "bf16", B, N, H, Hkv, d, causal, qkv_, Oo, lse)
+        mb.op_attention_gqa_bwd(None, q, "bf16", B, N, H, Hkv, d, causal, qkv_, Oo, lse, dO_, dqkv, delta)
+        torch.cuda.synchronize()
+        outs.append(bits(dqkv))
+    got = from_dev(dqkv)
+    for name, a, b in (("dq", 0, H * d), ("dk", H * d, (H + Hkv) * d), ("dv", (H + Hkv) * d, w)):
+        assert_close(got[:, a:b], ref[:, a:b], "bf16", name, roundings=8)
+    assert np.array_equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("kind", ["rising", "steep", "falling", "spike"])
 def test_attention_forward_when_the_row_maximum_moves_late(mb, kind, causal):

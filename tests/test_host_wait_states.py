@@ -5,7 +5,10 @@ for those inside an assembly string.  The direct-to-LDS requests are such string
 distances are checked in the machine code of the built library: between a vector-unit write of a scalar
 register (v_readfirstlane, compares, carries) and a memory instruction that reads it lie five
 wait states (a stale descriptor word would drop valid rows or lift the bounds check), between a scalar write
-of m0 and a direct-to-LDS request one."""
+of m0 and a direct-to-LDS request one.  The dK/dV kernel at head size 64 writes its matrix instructions as strings too and
+keeps its accumulators in registers that only those strings name: a vector instruction may read the
+result of a 32x32x16 matrix instruction after 12 wait states, a matrix instruction that of a vector instruction after
+two, and nothing but the strings may write these registers."""
 import os
 import re
 import shutil
@@ -54,15 +57,15 @@ def vector_unit_scalar_writes(op, operands):
     return set()
 
 
-def too_close(ins):
-    """Descriptions of the memory instructions that come too soon after the write of what they read."""
+def looking_back(ins):
+    """found(i, states, hit): whether hit(instruction) holds on some way to instruction i, within `states` wait states."""
     place = {x[0]: i for i, x in enumerate(ins)}
     jumps = {}
     for i, x in enumerate(ins):
         if x[3] in place:
             jumps.setdefault(place[x[3]], []).append(i)
 
-    def found(i, states, hit):                          # on some way to instruction i, within `states` wait states
+    def found(i, states, hit):
         work, seen = [(i, states)], set()
         while work:
             i, left = work.pop()
@@ -77,7 +80,33 @@ def too_close(ins):
                     return True
                 work.append((b, left - (int(ins[b][2].split()[0], 0) + 1 if ins[b][1] == "s_nop" else 1)))
         return False
+    return found
 
+
+def vector_registers(text):
+    return {(kind, r) for kind in "va" for r in registers(text, kind)}
+
+
+def matrix_too_close(ins):
+    """Descriptions of instructions that come too soon after a matrix instruction, or a matrix instruction too soon after
+    a vector instruction."""
+    found, bad = looking_back(ins), []
+    for i, (at, op, operands, _) in enumerate(ins):
+        first, _, rest = operands.partition(", ")
+        if op.startswith("v_mfma"):
+            reads = vector_registers(rest)
+            if found(i, 2, lambda x: x[1].startswith("v_") and not x[1].startswith("v_mfma") and vector_registers(x[2].split(", ")[0]) & reads):
+                bad.append("%x %s %s: written by the vector unit" % (at, op, operands))
+        elif op.startswith(("v_", "ds_write", "global_store", "buffer_store", "scratch_store")):
+            uses = vector_registers(operands)
+            if found(i, 12, lambda x: x[1].startswith("v_mfma") and vector_registers(x[2].split(", ")[0]) & uses):
+                bad.append("%x %s %s: result of a matrix instruction" % (at, op, operands))
+    return bad
+
+
+def too_close(ins):
+    """Descriptions of the memory instructions that come too soon after the write of what they read."""
+    found = looking_back(ins)
     bad = []
     for i, (at, op, operands, _) in enumerate(ins):
         if not op.startswith(("buffer_load", "buffer_store", "buffer_atomic", "global_", "scratch_")):
@@ -106,17 +135,43 @@ def test_the_check_itself(lines, bad):
     assert len(ins) == len(lines) and len(too_close(ins)) == bad
 
 
-def test_requests_keep_their_distance(tmp_path):
+@pytest.mark.parametrize("lines,bad", [
+    (("v_cvt_pk_bf16_f32 v8, v0, v1", "v_mfma_f32_32x32x16_bf16 a[0:15], v[4:7], v[8:11], a[0:15]"), 1),
+    (("v_cvt_pk_bf16_f32 v8, v0, v1", "s_nop 1", "v_mfma_f32_32x32x16_bf16 a[0:15], v[4:7], v[8:11], a[0:15]"), 0),
+    (("v_mfma_f32_32x32x16_bf16 v[16:31], v[4:7], a[64:67], v[16:31]", "s_nop 7", "v_exp_f32 v0, v20"), 1),
+    (("v_mfma_f32_32x32x16_bf16 v[16:31], v[4:7], a[64:67], v[16:31]", "s_nop 7", "s_nop 3", "v_exp_f32 v0, v20"), 0),
+    (("v_mfma_f32_32x32x16_bf16 a[16:31], v[4:7], v[8:11], a[16:31]", "v_exp_f32 v0, v20", "v_accvgpr_read_b32 v1, a16"), 1),
+])
+def test_the_check_of_matrix_instructions(lines, bad):
+    (_, ins), = kernels(listing_of(*lines))
+    assert len(matrix_too_close(ins)) == bad
+
+
+@pytest.fixture(scope="module")
+def listings(tmp_path_factory):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
     mb.lib()                                            # the library is built
-    so = shutil.copy(mb.LIB_PATH, tmp_path / "lib.so")
-    subprocess.run([OBJDUMP, "--offloading", str(so)], check=True, capture_output=True, cwd=tmp_path)
+    d = tmp_path_factory.mktemp("listing")
+    so = shutil.copy(mb.LIB_PATH, d / "lib.so")
+    subprocess.run([OBJDUMP, "--offloading", str(so)], check=True, capture_output=True, cwd=d)
+    return [k for f in sorted(d.glob("lib.so.*gfx950"))
+            for k in kernels(subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(f)], check=True, capture_output=True, text=True).stdout)]
+
+
+def test_requests_keep_their_distance(listings):
     requests, bad = 0, []
-    for f in sorted(tmp_path.glob("lib.so.*gfx950")):
-        listing = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(f)], check=True, capture_output=True, text=True).stdout
-        for name, ins in kernels(listing):
-            requests += sum(x[2].endswith(" lds") for x in ins)
-            bad += ["%s: %s" % (name[:60], b) for b in too_close(ins)]
+    for name, ins in listings:
+        requests += sum(x[2].endswith(" lds") for x in ins)
+        bad += ["%s: %s" % (name[:60], b) for b in too_close(ins)]
     assert requests > 1000, "the listings hold the direct-to-LDS requests"
     assert not bad, "%d in all, the first: %s" % (len(bad), bad[:3])
+
+
+def test_matrix_instructions_of_the_dkv_kernel_keep_their_distance(listings):
+    (ins,) = [ins for name, ins in listings if "attn_bwd_dkv_skew" in name]
+    assert sum(x[1].startswith("v_mfma") for x in ins) >= 40
+    assert not matrix_too_close(ins)
+    # dK, dV and the K and V fragments, a0 .. a95: written once per item (cleared, loaded), otherwise by matrix instructions
+    writes = [r for x in ins if x[1].startswith("v_accvgpr") and not x[1].startswith("v_accvgpr_read") for r in registers(x[2].split(", ")[0], "a")]
+    assert sorted(r for r in writes if r < 96) == list(range(96))
