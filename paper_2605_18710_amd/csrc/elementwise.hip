@@ -314,27 +314,30 @@ __global__ __launch_bounds__(kThreads) void norm_colgrad_partial_kernel(
   }
 }
 
-// out[col] = sum_p partial[p*ld + col], partitions taken in 8 contiguous slices that are
-// added in slice order: a fixed tree that depends on np only.  Columns [0, split) go to
-// out0, columns [split, split2) to out1, columns [split2, ncols) to out2; a null destination
-// skips its columns.
+// The final pass of column reductions (ColReduce): partitions taken in 8 contiguous slices that are added in slice
+// order, a fixed tree that depends on np only.  A workgroup takes 32 columns of one of the list's reductions.  Bound by
+// launch and latency: one alone takes 4.5 to 8 us for a few hundred KB to 10 MB of partial sums, so a layer's go in one launch
+// (two encoder layers of 1568 rows: 9 launches, 41 us -> 2, 12 us; one of 12000 rows: 5, 38 us -> 1).
 template <typename T>
-__global__ __launch_bounds__(kThreads) void reduce_partials_kernel(
-    const float* __restrict__ partial, int np, int64_t ld, int64_t ncols, int64_t split,
-    T* __restrict__ out0, T* __restrict__ out1, int64_t split2 = INT64_MAX, T* __restrict__ out2 = nullptr) {
+__global__ __launch_bounds__(kThreads) void col_reduce_kernel(ColReduceList list, int64_t total) {
   __shared__ float red[8][32];
   const int cl = threadIdx.x & 31, sl = threadIdx.x >> 5;
-  const int per = (np + 7) / 8;
-  const int64_t groups = (ncols + 31) / 32;
-  for (int64_t gidx = blockIdx.x; gidx < groups; gidx += gridDim.x) {
-    const int64_t col = gidx * 32 + cl;
+  for (int64_t at = blockIdx.x; at < total; at += gridDim.x) {
+    int64_t gidx = at;
+    int which = 0;
+    while (gidx >= (list.job[which].ncols + 31) / 32) { gidx -= (list.job[which].ncols + 31) / 32; ++which; }
+    const ColReduce& r = list.job[which];
+    const int np = r.np, per = (np + 7) / 8;
+    const int64_t col = gidx * 32 + cl, ld = r.ld;
+    const float* partial = r.partial;
     float acc = 0.f;
     T* dst = nullptr;
-    if (col < ncols) dst = col < split ? out0 + col : col < split2 ? (out1 ? out1 + (col - split) : nullptr) : (out2 ? out2 + (col - split2) : nullptr);
+    if (col < r.ncols)
+      dst = col < r.split ? (T*)r.out0 + col : col < r.split2 ? (r.out1 ? (T*)r.out1 + (col - r.split) : nullptr) : (r.out2 ? (T*)r.out2 + (col - r.split2) : nullptr);
     if (dst) {
       const int p1 = (sl + 1) * per < np ? (sl + 1) * per : np;
       int p = sl * per;
-      // eight independent requests in flight, added in ascending p as before
+      // eight independent requests in flight, added in ascending p
       for (; p + 8 <= p1; p += 8) {
         float v[8];
 #pragma unroll
@@ -701,6 +704,24 @@ mosaic_status launch_norm_fwd(hipStream_t s, int quota, int dtype, int norm, int
   return norm_fwd_t<float>(s, quota, norm, T, h, eps, (const float*)x, (const float*)gamma, (const float*)beta, (float*)y, stats);
 }
 
+mosaic_status launch_col_reduce(hipStream_t s, int quota, int dtype, const ColReduceList& list) {
+  int64_t total = 0;
+  for (int i = 0; i < list.n; ++i) total += ceil_div(list.job[i].ncols, 32);
+  if (total == 0) return MOSAIC_OK;
+  const int grid = grid_for(quota, 8, total);
+  if (dtype == MOSAIC_BF16) col_reduce_kernel<bf16><<<grid, kThreads, 0, s>>>(list, total);
+  else col_reduce_kernel<float><<<grid, kThreads, 0, s>>>(list, total);
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
+// now, or with the rest of `later`
+static mosaic_status col_reduce(hipStream_t s, int quota, int dtype, const ColReduce& r, ColReduceList* later) {
+  if (later && later->n < ColReduceList::kMax) { later->job[later->n++] = r; return MOSAIC_OK; }
+  ColReduceList one;
+  one.job[one.n++] = r;
+  return launch_col_reduce(s, quota, dtype, one);
+}
+
 static inline void col_partition(int64_t T, int* rp, int* np) {
   int64_t r = ceil_div(T, kColsumMaxParts);
   if (r < 8) r = 8;
@@ -715,7 +736,7 @@ constexpr int kNormDxSumMaxNV = 4;
 template <typename T>
 static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows, int64_t h, const T* x,
                                 const T* gamma, const float* stats, const T* dy, const T* R, T* dx,
-                                T* dgamma, T* dbeta, float* scratch, T* dxsum, int dtype) {
+                                T* dgamma, T* dbeta, float* scratch, T* dxsum, int dtype, ColReduceList* later) {
   constexpr int VN = Vec16<T>::N;
   if (h % VN) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "norm width %lld is not a multiple of %d", (long long)h, VN);
   const int nv = pick_nv((int)ceil_div(h, 64 * VN));
@@ -723,7 +744,6 @@ static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows
   if (rows == 0) return MOSAIC_OK;
   int rp, np;
   col_partition(rows, &rp, &np);
-  const int g2 = grid_for(quota, 8, ceil_div(2 * h, 32));
   if (dxsum && norm == MOSAIC_LAYERNORM && nv <= kNormDxSumMaxNV) {
     // one pass that also sums the columns of dx
     const int gf = grid_for(quota, 8, np);
@@ -736,11 +756,10 @@ static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows
     }
 #undef LC
     MOSAIC_LAUNCH_CHECK();
-    const int g3 = grid_for(quota, 8, ceil_div(3 * h, 32));
-    reduce_partials_kernel<T><<<g3, kThreads, 0, s>>>(scratch, np, 3 * h, 3 * h, h, dgamma, dbeta, 2 * h, dxsum);
-    MOSAIC_LAUNCH_CHECK();
-    return MOSAIC_OK;
+    return col_reduce(s, quota, dtype, {scratch, np, 3 * h, 3 * h, h, 2 * h, dgamma, dbeta, dxsum}, later);
   }
+  const ColReduce sums = {scratch, np, 2 * h, 2 * h, h, INT64_MAX, dgamma, norm == MOSAIC_LAYERNORM ? dbeta : nullptr, nullptr};
+  if (dxsum) later = nullptr;            // the pass over dx below writes its partial sums into the same scratch
   // no kernel that sums dx on the way for this norm or width: the sums take a pass of their own, afterwards
   auto sum_dx = [&]() -> mosaic_status { return dxsum ? launch_colsum(s, quota, dtype, rows, h, dx, dxsum, scratch) : MOSAIC_OK; };
   if (nv <= kNormFusedMaxNV || norm == MOSAIC_RMSNORM) {
@@ -765,9 +784,7 @@ static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows
     }
 #undef LF
     MOSAIC_LAUNCH_CHECK();
-    reduce_partials_kernel<T><<<g2, kThreads, 0, s>>>(scratch, np, 2 * h, 2 * h, h, dgamma,
-                                                      norm == MOSAIC_LAYERNORM ? dbeta : (T*)nullptr);
-    MOSAIC_LAUNCH_CHECK();
+    MOSAIC_TRY(col_reduce(s, quota, dtype, sums, later));
     return sum_dx();
   }
   const int grid = grid_for(quota, 8, ceil_div(rows, kWaves));
@@ -786,21 +803,19 @@ static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows
   else
     norm_colgrad_partial_kernel<T, MOSAIC_RMSNORM><<<g1, kThreads, 0, s>>>(x, stats, dy, scratch, rows, (int)h, rp, np, ctiles);
   MOSAIC_LAUNCH_CHECK();
-  reduce_partials_kernel<T><<<g2, kThreads, 0, s>>>(scratch, np, 2 * h, 2 * h, h, dgamma,
-                                                    norm == MOSAIC_LAYERNORM ? dbeta : (T*)nullptr);
-  MOSAIC_LAUNCH_CHECK();
+  MOSAIC_TRY(col_reduce(s, quota, dtype, sums, later));
   return sum_dx();
 }
 
 mosaic_status launch_norm_bwd(hipStream_t s, int quota, int dtype, int norm, int64_t T, int64_t h, const void* x,
                               const void* gamma, const float* stats, const void* dy, const void* R, void* dx,
-                              void* dgamma, void* dbeta, void* scratch, void* dxsum) {
+                              void* dgamma, void* dbeta, void* scratch, void* dxsum, ColReduceList* later) {
   if (norm != MOSAIC_LAYERNORM && norm != MOSAIC_RMSNORM) MOSAIC_FAIL(MOSAIC_EINVAL, "bad norm kind %d", norm);
   if (dtype == MOSAIC_BF16)
     return norm_bwd_t<bf16>(s, quota, norm, T, h, (const bf16*)x, (const bf16*)gamma, stats, (const bf16*)dy,
-                            (const bf16*)R, (bf16*)dx, (bf16*)dgamma, (bf16*)dbeta, (float*)scratch, (bf16*)dxsum, dtype);
+                            (const bf16*)R, (bf16*)dx, (bf16*)dgamma, (bf16*)dbeta, (float*)scratch, (bf16*)dxsum, dtype, later);
   return norm_bwd_t<float>(s, quota, norm, T, h, (const float*)x, (const float*)gamma, stats, (const float*)dy,
-                           (const float*)R, (float*)dx, (float*)dgamma, (float*)dbeta, (float*)scratch, (float*)dxsum, dtype);
+                           (const float*)R, (float*)dx, (float*)dgamma, (float*)dbeta, (float*)scratch, (float*)dxsum, dtype, later);
 }
 
 #define EW_CHECK_VEC(n, dtype)                                                               \
@@ -875,7 +890,7 @@ mosaic_status launch_mse(hipStream_t s, int quota, int dtype, int64_t n, const v
 size_t colsum_scratch_bytes(int64_t n) { return (size_t)kColsumMaxParts * (size_t)n * sizeof(float); }
 
 mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n, const void* X, void* out,
-                            void* scratch) {
+                            void* scratch, ColReduceList* later) {
   EW_CHECK_VEC(n, dtype);
   if (n == 0) return MOSAIC_OK;
   int rp, np;
@@ -889,17 +904,11 @@ mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int6
       colsum_partial_kernel<float><<<grid, kThreads, 0, s>>>((const float*)X, (float*)scratch, T, n, rp, np, ctiles);
     MOSAIC_LAUNCH_CHECK();
   }
-  const int g2 = grid_for(quota, 8, ceil_div(n, 32));
-  if (dtype == MOSAIC_BF16)
-    reduce_partials_kernel<bf16><<<g2, kThreads, 0, s>>>((const float*)scratch, np, n, n, n, (bf16*)out, (bf16*)nullptr);
-  else
-    reduce_partials_kernel<float><<<g2, kThreads, 0, s>>>((const float*)scratch, np, n, n, n, (float*)out, (float*)nullptr);
-  MOSAIC_LAUNCH_CHECK();
-  return MOSAIC_OK;
+  return col_reduce(s, quota, dtype, {(const float*)scratch, np, n, n, n, INT64_MAX, out, nullptr, nullptr}, later);
 }
 
 mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n, const void* z,
-                                     const void* da, void* dz, void* colsum, void* scratch) {
+                                     const void* da, void* dz, void* colsum, void* scratch, ColReduceList* later) {
   EW_CHECK_VEC(n, dtype);
   if (n == 0) return MOSAIC_OK;
   int rp, np;
@@ -913,13 +922,7 @@ mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_
       gelu_bwd_colsum_kernel<float><<<grid, kThreads, 0, s>>>((const float*)z, (const float*)da, (float*)dz, (float*)scratch, T, n, rp, np, ctiles);
     MOSAIC_LAUNCH_CHECK();
   }
-  const int g2 = grid_for(quota, 8, ceil_div(n, 32));
-  if (dtype == MOSAIC_BF16)
-    reduce_partials_kernel<bf16><<<g2, kThreads, 0, s>>>((const float*)scratch, np, n, n, n, (bf16*)colsum, (bf16*)nullptr);
-  else
-    reduce_partials_kernel<float><<<g2, kThreads, 0, s>>>((const float*)scratch, np, n, n, n, (float*)colsum, (float*)nullptr);
-  MOSAIC_LAUNCH_CHECK();
-  return MOSAIC_OK;
+  return col_reduce(s, quota, dtype, {(const float*)scratch, np, n, n, n, INT64_MAX, colsum, nullptr, nullptr}, later);
 }
 
 // 16-byte accesses where every row of both tensors starts on a 16-byte boundary

@@ -44,22 +44,39 @@ mosaic_status launch_attention_bwd(hipStream_t s, int quota, int dtype, int B, i
 mosaic_status launch_norm_fwd(hipStream_t s, int quota, int dtype, int norm, int64_t T,
                               int64_t h, float eps, const void* x, const void* gamma,
                               const void* beta, void* y, float* stats);
+// A column reduction whose partial sums are written and whose final pass is not: out[col] = sum_p partial[p * ld + col] for
+// col < ncols, columns from `split` on to out1, from `split2` on to out2 (a null destination skips its columns).  The backward
+// pass of a layer collects those of its norms and biases and launches them together; each keeps its partial sums
+// in scratch of its own until then.
+struct ColReduce {
+  const float* partial;
+  int np;
+  int64_t ld, ncols, split, split2;
+  void *out0, *out1, *out2;
+};
+struct ColReduceList {
+  static constexpr int kMax = 6;
+  ColReduce job[kMax];
+  int n = 0;
+};
+mosaic_status launch_col_reduce(hipStream_t s, int quota, int dtype, const ColReduceList& list);
 // scratch of launch_norm_bwd: two slabs of partial sums per row partition, a third when dxsum is asked for
 size_t norm_bwd_scratch_bytes(int64_t h, bool with_dxsum = true);
 mosaic_status launch_norm_bwd(hipStream_t s, int quota, int dtype, int norm, int64_t T,
                               int64_t h, const void* x, const void* gamma, const float* stats,
                               const void* dy, const void* R, void* dx, void* dgamma,
-                              void* dbeta, void* scratch, void* dxsum = nullptr);
+                              void* dbeta, void* scratch, void* dxsum = nullptr, ColReduceList* later = nullptr);
 // dxsum (may be null): receives the column sums of dx[T,h] as stored, in the fixed two-level
 // order of launch_colsum's partitions; formed inside the norm kernel where it has a variant
 // for that (LayerNorm rows of up to 2048 bf16 / 1024 fp32 elements), by a pass over dx otherwise.
+// later (here and below; may be null): the final pass of the column sums is appended there and not launched
 mosaic_status launch_gelu_fwd(hipStream_t s, int quota, int dtype, int64_t n, const void* z, void* a);
 mosaic_status launch_gelu_bwd(hipStream_t s, int quota, int dtype, int64_t n, const void* z,
                               const void* da, void* dz);
 // dz = da * gelu'(z) and colsum[n] = column sums of dz[T,n] as stored (same bits as launch_colsum
 // over dz); scratch: colsum_scratch_bytes(n)
 mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n, const void* z,
-                                     const void* da, void* dz, void* colsum, void* scratch);
+                                     const void* da, void* dz, void* colsum, void* scratch, ColReduceList* later = nullptr);
 mosaic_status launch_swiglu_fwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t f,
                                 const void* gu, void* a);
 mosaic_status launch_swiglu_bwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t f,
@@ -90,7 +107,7 @@ mosaic_status launch_mse(hipStream_t s, int quota, int dtype, int64_t n, const v
 size_t colsum_scratch_bytes(int64_t n);
 // out[n] = sum over T rows of X[T,n] in a fixed two-level order.
 mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n,
-                            const void* X, void* out, void* scratch);
+                            const void* X, void* out, void* scratch, ColReduceList* later = nullptr);
 
 // ----------------------------------------------------------------------------- stems
 // rows of `out` are ld elements apart (whole 16-byte pieces), zeros past 3*patch*patch

@@ -41,7 +41,7 @@ struct mosaic_module {
   int64_t param_elems = 0;
   size_t ws_bytes = 0;
   // scratch byte offsets
-  size_t s_dA, s_dZ, s_dU, s_dX1, s_dO, s_dQKV, s_delta, s_g0, s_g1, s_norm, s_colsum, s_mse, s_dyloss, s_splitk;
+  size_t s_dA, s_dZ, s_dU, s_dX1, s_dO, s_dQKV, s_delta, s_g0, s_g1, s_norm, s_norm2, s_colsum, s_colsum2, s_colsum3, s_mse, s_dyloss, s_splitk;
   size_t s_patches;
   size_t s_embed = 0;    // sorted positions and run pieces of the embedding gradient
   size_t s_rope = 0;     // (cos, sin) table of the rotary embedding, when on
@@ -191,9 +191,14 @@ void build_layout(mosaic_module* m) {
     m->s_delta = take(&cur, (size_t)d.batch * d.heads * d.seq * sizeof(float));
     m->s_g0 = take(&cur, T * h * es);
     m->s_g1 = take(&cur, T * h * es);
+    // partial column sums of a layer's norms and biases, kept side by side until the layer's one reduction
     m->s_norm = take(&cur, norm_bwd_scratch_bytes(h));
-    const int64_t widest = (qw > zf) ? qw : zf;
-    m->s_colsum = take(&cur, colsum_scratch_bytes(widest));
+    m->s_norm2 = take(&cur, norm_bwd_scratch_bytes(h));
+    if (d.bias) {
+      m->s_colsum = take(&cur, colsum_scratch_bytes(zf));
+      m->s_colsum2 = take(&cur, colsum_scratch_bytes(qw));
+      m->s_colsum3 = take(&cur, colsum_scratch_bytes(h));
+    }
     size_t sk = gemm_splitk_scratch_bytes(h, qw, T);
     sk = std::max(sk, gemm_splitk_scratch_bytes(h, h, T));
     sk = std::max(sk, gemm_splitk_scratch_bytes(h, zf, T));
@@ -214,6 +219,7 @@ void build_layout(mosaic_module* m) {
     m->s_dA = take(&cur, T * d.out_dim * es);
     m->s_dZ = take(&cur, T * d.out_dim * es);
     m->s_colsum = take(&cur, colsum_scratch_bytes(d.out_dim));
+    m->s_colsum2 = take(&cur, colsum_scratch_bytes(d.out_dim));
     m->s_splitk = take(&cur, std::max(gemm_splitk_scratch_bytes(d.out_dim, d.out_dim, T),
                                       gemm_splitk_scratch_bytes(d.in_dim, d.out_dim, T)));
   } else if (d.kind == MOSAIC_PATCH_STEM) {
@@ -245,6 +251,7 @@ void build_layout(mosaic_module* m) {
     m->c_dz1 = take(&cur, Tin * h * es);
     m->c_dp1 = take(&cur, Tin * 3 * C * es);
     m->s_colsum = take(&cur, colsum_scratch_bytes(h));
+    m->s_colsum2 = take(&cur, colsum_scratch_bytes(h));
     m->s_splitk = take(&cur, std::max(gemm_splitk_scratch_bytes(3 * C, h, Tin), gemm_splitk_scratch_bytes(3 * h, h, T)));
   } else {  // TEXT_STEM
     LayerParams q;
@@ -307,12 +314,12 @@ mosaic_status layers_backward(mosaic_module* m, hipStream_t s, int q, const void
   const int64_t qw = qkv_width(d);
   void* dA = W(m, m->s_dA); void* dZ = W(m, m->s_dZ); void* dU = W(m, m->s_dU);
   void* dX1 = W(m, m->s_dX1); void* dO = W(m, m->s_dO); void* dQKV = W(m, m->s_dQKV);
-  void* nsc = W(m, m->s_norm); void* csc = W(m, m->s_colsum);
   const void* gin = dy;
   for (int l = d.layers - 1; l >= 0; --l) {
     const LayerParams& p = m->lp[l];
     const LayerSaved& sv = m->ls[l];
     const void* xin = (l == 0) ? m->last_x : W(m, m->ls[l - 1].y);
+    ColReduceList sums;
     void* gout = (l == 0) ? (dx ? dx : W(m, m->s_g0)) : W(m, (l & 1) ? m->s_g1 : m->s_g0);
     // MLP down projection
     MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, f, h, W(m, sv.a), gin, P(m, p.w_2), dA, G(m, p.w_2), W(m, m->s_splitk), true));
@@ -320,19 +327,19 @@ mosaic_status layers_backward(mosaic_module* m, hipStream_t s, int q, const void
     // that writes that gradient where there is one of ours: the first norm's backward of the
     // layer above (this layer's incoming gradient), the GELU backward, the second norm's
     // backward.  Only the top layer's incoming gradient and dQKV take a pass of their own.
-    if (p.b_2 >= 0 && l == d.layers - 1) MOSAIC_TRY(launch_colsum(s, q, dt, T, h, gin, G(m, p.b_2), csc));
+    if (p.b_2 >= 0 && l == d.layers - 1) MOSAIC_TRY(launch_colsum(s, q, dt, T, h, gin, G(m, p.b_2), W(m, m->s_colsum3), &sums));
     // activation
     bool b1_done = false;
     if (glu) MOSAIC_TRY(launch_swiglu_bwd(s, q, dt, T, f, W(m, sv.z), dA, dZ));
     else if (d.act == MOSAIC_GELU_TANH) MOSAIC_TRY(launch_gelu_tanh_bwd(s, q, dt, T * f, W(m, sv.z), dA, dZ));
-    else if (p.b_1 >= 0) { MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, f, W(m, sv.z), dA, dZ, G(m, p.b_1), csc)); b1_done = true; }
+    else if (p.b_1 >= 0) { MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, f, W(m, sv.z), dA, dZ, G(m, p.b_1), W(m, m->s_colsum), &sums)); b1_done = true; }
     else MOSAIC_TRY(launch_gelu_bwd(s, q, dt, T * f, W(m, sv.z), dA, dZ));
     // MLP up projection
-    if (p.b_1 >= 0 && !b1_done) MOSAIC_TRY(launch_colsum(s, q, dt, T, zf, dZ, G(m, p.b_1), csc));
+    if (p.b_1 >= 0 && !b1_done) MOSAIC_TRY(launch_colsum(s, q, dt, T, zf, dZ, G(m, p.b_1), W(m, m->s_colsum), &sums));
     MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, h, zf, W(m, sv.u2), dZ, P(m, p.w_1), dU, G(m, p.w_1), W(m, m->s_splitk), false));
     // second norm; residual branch adds the incoming gradient
-    MOSAIC_TRY(launch_norm_bwd(s, q, dt, d.norm, T, h, W(m, sv.x1), P(m, p.n2_g), (const float*)W(m, sv.st2), dU, gin, dX1, G(m, p.n2_g), G(m, p.n2_b), nsc,
-                               G(m, p.b_o)));   // dX1 is the output gradient of the attention output projection
+    MOSAIC_TRY(launch_norm_bwd(s, q, dt, d.norm, T, h, W(m, sv.x1), P(m, p.n2_g), (const float*)W(m, sv.st2), dU, gin, dX1, G(m, p.n2_g), G(m, p.n2_b), W(m, m->s_norm2),
+                               G(m, p.b_o), &sums));   // dX1 is the output gradient of the attention output projection
     // attention output projection
     MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, h, h, W(m, sv.o), dX1, P(m, p.w_o), dO, G(m, p.w_o), W(m, m->s_splitk), true));
     // attention
@@ -342,11 +349,12 @@ mosaic_status layers_backward(mosaic_module* m, hipStream_t s, int q, const void
     // the forward pass is still in the workspace)
     if (d.rope_base > 0.f) MOSAIC_TRY(launch_rope(s, q, dt, d.batch, d.seq, d.heads, kvh, (int)(h / d.heads), -1, dQKV, W(m, m->s_rope)));
     // QKV projection
-    if (p.b_qkv >= 0) MOSAIC_TRY(launch_colsum(s, q, dt, T, qw, dQKV, G(m, p.b_qkv), csc));
+    if (p.b_qkv >= 0) MOSAIC_TRY(launch_colsum(s, q, dt, T, qw, dQKV, G(m, p.b_qkv), W(m, m->s_colsum2), &sums));
     MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, h, qw, W(m, sv.u1), dQKV, P(m, p.w_qkv), dU, G(m, p.w_qkv), W(m, m->s_splitk), false));
     // first norm
-    MOSAIC_TRY(launch_norm_bwd(s, q, dt, d.norm, T, h, xin, P(m, p.n1_g), (const float*)W(m, sv.st1), dU, dX1, gout, G(m, p.n1_g), G(m, p.n1_b), nsc,
-                               l > 0 ? G(m, m->lp[l - 1].b_2) : nullptr));   // gout is the incoming gradient of the layer below
+    MOSAIC_TRY(launch_norm_bwd(s, q, dt, d.norm, T, h, xin, P(m, p.n1_g), (const float*)W(m, sv.st1), dU, dX1, gout, G(m, p.n1_g), G(m, p.n1_b), W(m, m->s_norm),
+                               l > 0 ? G(m, m->lp[l - 1].b_2) : nullptr, &sums));   // gout is the incoming gradient of the layer below
+    MOSAIC_TRY(launch_col_reduce(s, q, dt, sums));
     gin = gout;
   }
   return MOSAIC_OK;
@@ -369,10 +377,12 @@ mosaic_status projector_backward(mosaic_module* m, hipStream_t s, int q, const v
   const LayerSaved& sv = m->ls[0];
   const int64_t T = m->T, no = d.out_dim, ni = d.in_dim;
   const int dt = d.dtype;
-  void* dA = W(m, m->s_dA); void* dZ = W(m, m->s_dZ); void* csc = W(m, m->s_colsum);
+  void* dA = W(m, m->s_dA); void* dZ = W(m, m->s_dZ);
+  ColReduceList sums;
   MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, no, no, W(m, sv.a), dy, P(m, p.w_2), dA, G(m, p.w_2), W(m, m->s_splitk), true));
-  MOSAIC_TRY(launch_colsum(s, q, dt, T, no, dy, G(m, p.b_2), csc));
-  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, no, W(m, sv.z), dA, dZ, G(m, p.b_1), csc));
+  MOSAIC_TRY(launch_colsum(s, q, dt, T, no, dy, G(m, p.b_2), W(m, m->s_colsum2), &sums));
+  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, no, W(m, sv.z), dA, dZ, G(m, p.b_1), W(m, m->s_colsum), &sums));
+  MOSAIC_TRY(launch_col_reduce(s, q, dt, sums));
   if (dx) return launch_linear_bwd(s, q, dt, T, ni, no, m->last_x, dZ, P(m, p.w_1), dx, G(m, p.w_1), W(m, m->s_splitk), false);
   return launch_gemm(s, q, dt, false, false, ni, no, T, m->last_x, ni, dZ, no, G(m, p.w_1), no, nullptr, nullptr, W(m, m->s_splitk));
 }
@@ -423,12 +433,14 @@ mosaic_status conv_stem_backward(mosaic_module* m, hipStream_t s, int q, const v
   const LayerParams& p = m->lp[0];
   const int dt = d.dtype, C = d.in_dim, h = d.hidden, Lo = d.seq, L = 2 * d.seq;
   const int64_t T = m->T, Tin = 2 * T;
-  void* csc = W(m, m->s_colsum); void* sk = W(m, m->s_splitk);
+  void* sk = W(m, m->s_splitk);
+  ColReduceList sums;
   MOSAIC_TRY(launch_pos_grad(s, q, dt, d.batch, Lo, h, dy, G(m, p.w_o)));
-  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, h, W(m, m->c_z2), dy, W(m, m->c_dz2), G(m, p.b_2), csc));
+  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, h, W(m, m->c_z2), dy, W(m, m->c_dz2), G(m, p.b_2), W(m, m->s_colsum2), &sums));
   MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, 3 * h, h, W(m, m->c_p2), W(m, m->c_dz2), P(m, p.w_2), W(m, m->c_dp2), G(m, p.w_2), sk, false));
   MOSAIC_TRY(launch_col2im1d(s, q, dt, d.batch, L, Lo, h, 2, W(m, m->c_dp2), W(m, m->c_da1)));
-  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, Tin, h, W(m, m->c_z1), W(m, m->c_da1), W(m, m->c_dz1), G(m, p.b_1), csc));
+  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, Tin, h, W(m, m->c_z1), W(m, m->c_da1), W(m, m->c_dz1), G(m, p.b_1), W(m, m->s_colsum), &sums));
+  MOSAIC_TRY(launch_col_reduce(s, q, dt, sums));
   if (!dx) {
     MOSAIC_TRY(launch_gemm(s, q, dt, false, false, 3 * C, h, Tin, W(m, m->c_p1), 3 * C, W(m, m->c_dz1), h, G(m, p.w_1), h, nullptr, nullptr, sk));
   } else {
