@@ -1615,6 +1615,8 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
 // gemm_f32.hip
 mosaic_status launch_gemm_f32(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int M, int N, int K, const void* A,
                               int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, const void* bias, const void* R);
+mosaic_status launch_linear_bwd_f32(hipStream_t s, int quota, int64_t T, int64_t k, int64_t n, const void* X, const void* dY, const void* W,
+                                    void* dX, void* dW, bool* taken);
 
 size_t gemm_splitk_scratch_bytes(int64_t M, int64_t N, int64_t K) {
   int first = 0;
@@ -1714,13 +1716,19 @@ mosaic_status launch_pair(hipStream_t s, const PairHalf& dg, const PairHalf& wg)
 
 mosaic_status launch_linear_bwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t k, int64_t n, const void* X, const void* dY,
                                 const void* W, void* dX, void* dW, void* splitk_scratch, bool dx_first) {
-  const int64_t xb = T * k * 2, yb = T * n * 2, wb = k * n * 2, lim = (int64_t)1 << 31;
+  const int64_t es = (int64_t)dtype_size(dtype), xb = T * k * es, yb = T * n * es, wb = k * n * es, lim = (int64_t)1 << 31;
   const uintptr_t all = (uintptr_t)X | (uintptr_t)dY | (uintptr_t)W | (uintptr_t)dX | (uintptr_t)dW;
   const bool fits = dtype == MOSAIC_BF16 && T > 0 && k > 0 && n > 0 && T <= INT32_MAX && k <= INT32_MAX && n <= INT32_MAX && k % 8 == 0 && n % 8 == 0 &&
                     all % 16 == 0 && xb < lim && yb < lim && wb < lim;
   // an output that lies on an input, which the order of two launches may allow, keeps them
-  if (fits && !overlap(dX, xb, X, xb) && !overlap(dX, xb, dY, yb) && !overlap(dX, xb, W, wb) && !overlap(dX, xb, dW, wb) &&
-      !overlap(dW, wb, X, xb) && !overlap(dW, wb, dY, yb) && !overlap(dW, wb, W, wb)) {
+  const bool apart = !overlap(dX, xb, X, xb) && !overlap(dX, xb, dY, yb) && !overlap(dX, xb, W, wb) && !overlap(dX, xb, dW, wb) &&
+                     !overlap(dW, wb, X, xb) && !overlap(dW, wb, dY, yb) && !overlap(dW, wb, W, wb);
+  if (dtype == MOSAIC_F32 && T > 0 && k > 0 && n > 0 && apart && pair_enabled()) {
+    bool taken;
+    MOSAIC_TRY(launch_linear_bwd_f32(s, quota, T, k, n, X, dY, W, dX, dW, &taken));
+    if (taken) return MOSAIC_OK;
+  }
+  if (fits && apart) {
     const int cus = tile_queue_sure_cus(quota);
     const WgradPlan wp = wgrad_plan(k, n, T, cus, splitk_scratch != nullptr, w4_takes<false, false>(T));
     const PairPlan pp = pair_plan(T, k, n, cus, wp);

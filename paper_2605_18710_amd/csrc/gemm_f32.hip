@@ -167,13 +167,33 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Gemm p) {
   for (int tile = blockIdx.x; tile < p.tiles_m * p.tiles_n; tile += gridDim.x) gemm_f32_tile<T, BT, KS, A_KC, B_KC, VEC>(p, tile, lds);
 }
 
+// The input gradient (both operands K-contiguous) and the weight gradient (both K-strided) of a linear layer in one
+// launch of 32 x 32 tiles, those with the longer contraction first: each is a chain of a few tiles' latency that leaves
+// most CUs idle.  Products of a decoder layer of 256 rows, width 128: 6.1 + 5.6 us in two launches, 7.0 in one (a launch less
+// to wait for besides: with the attention's, the layer's step 120 -> 92 us).
+__global__ __launch_bounds__(256) void gemm_f32_pair_kernel(F32Gemm d, F32Gemm w, int w_first) {
+  typedef F32Tile<float, 32, 64, true, true> Contiguous;
+  typedef F32Tile<float, 32, 64, false, true> Strided;
+  constexpr int STAGE = 2 * (Contiguous::FLOATS > Strided::FLOATS ? Contiguous::FLOATS : Strided::FLOATS);
+  __shared__ __align__(16) float lds[2 * STAGE];
+  const int nd = d.tiles_m * d.tiles_n, nw = w.tiles_m * w.tiles_n;
+  for (int u = blockIdx.x; u < nd + nw; u += gridDim.x) {
+    const int td = w_first ? u - nw : u, tw = w_first ? u : u - nd;
+    if (td >= 0 && td < nd) gemm_f32_tile<float, 32, 64, true, true, true>(d, td, lds);
+    else gemm_f32_tile<float, 32, 64, false, false, true>(w, tw, lds);
+  }
+}
+
+// a function of the shape alone; the order of every sum is the same in both.  Figures in launch_t.
+bool large_tiles(int64_t M, int64_t N) { return ceil_div(M, 64) * ceil_div(N, 64) >= 512; }
+
 template <typename T, bool A_KC, bool B_KC, bool VEC>
 mosaic_status launch_t(hipStream_t s, int quota, F32Gemm p) {
   // A function of the shape alone; the order of every sum is the same in both.  Measured, forward, tiles of 32 / of 64
   // on 256 CUs (on 64): 256 tiles of 64 (1024 x 512 x 1024) 15.7 / 16.8 us (22.6 / 16.6), 512 (1024 x 512 x 2048)
   // 28.7 / 26.0 (43.9 / 31.1), 576 31.1 / 34.1 (48.9 / 45.2), 1024 53.1 / 44.3 (84.9 / 59.7), 4096 386 / 312; input gradient,
   // 192 tiles 31.0 / 41.8.  bf16 tensors, 256 tiles 33.0 / 39.3, 576 76.5 / 66.0, 1024 122.6 / 82.2.
-  const bool large = ceil_div(p.M, 64) * ceil_div(p.N, 64) >= 512;
+  const bool large = large_tiles(p.M, p.N);
   const int bt = large ? 64 : 32;
   const int64_t tm = ceil_div(p.M, bt), tn = ceil_div(p.N, bt);
   if (tm * tn > INT32_MAX / 2) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "too many output tiles");
@@ -198,6 +218,22 @@ mosaic_status launch_form(hipStream_t s, int quota, bool a_kc, bool b_kc, const 
 }
 
 }  // namespace
+
+// dX[T,k] = dY W^T and dW[k,n] = X^T dY of fp32 tensors, dense rows, no output on an input; *taken: in one launch
+mosaic_status launch_linear_bwd_f32(hipStream_t s, int quota, int64_t T, int64_t k, int64_t n, const void* X, const void* dY, const void* W,
+                                    void* dX, void* dW, bool* taken) {
+  *taken = false;
+  const uintptr_t all = (uintptr_t)X | (uintptr_t)dY | (uintptr_t)W | (uintptr_t)dX | (uintptr_t)dW;
+  if (T > INT32_MAX || k > INT32_MAX || n > INT32_MAX || k % 4 || n % 4 || all % 16 || large_tiles(T, k) || large_tiles(k, n)) return MOSAIC_OK;
+  auto product = [](const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t M, int64_t N, int64_t K) {
+    return F32Gemm{A, B, nullptr, nullptr, C, (int)M, (int)N, (int)K, lda, ldb, N, (int)ceil_div(M, 32), (int)ceil_div(N, 32)};
+  };
+  const F32Gemm d = product(dY, n, W, n, dX, T, k, n), w = product(X, k, dY, n, dW, k, n, T);
+  gemm_f32_pair_kernel<<<grid_for(quota, 4, (int64_t)d.tiles_m * d.tiles_n + (int64_t)w.tiles_m * w.tiles_n), 256, 0, s>>>(d, w, T > n);
+  MOSAIC_LAUNCH_CHECK();
+  *taken = true;
+  return MOSAIC_OK;
+}
 
 mosaic_status launch_gemm_f32(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int M, int N, int K, const void* A,
                               int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, const void* bias, const void* R) {
