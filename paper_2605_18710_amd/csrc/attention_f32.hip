@@ -21,6 +21,7 @@
 // 19622 -> 1868, fp32 B1 N2048 H8/2 d128 causal 2442 -> 308 and 13313 -> 2253; bf16 B8 N1500 H16 d80 15614 -> 3484 and
 // 74581 -> 14185, B2 N576 H16 d72 733 -> 206 and 2852 -> 870.
 #include <algorithm>
+#include <type_traits>
 #include "kernels.h"
 
 namespace {
@@ -178,16 +179,18 @@ __global__ __launch_bounds__(64) void attn_fwd_f32(const T* __restrict__ qkv, T*
   }
 }
 
+// workgroups first .. first + count - 1 of the launch
+struct Share { int first, count; };
+
 template <typename T, int DB, bool VEC>
-__global__ __launch_bounds__(64) void attn_bwd_dq_f32(const T* __restrict__ qkv, const T* __restrict__ O, const T* __restrict__ dO,
-                                                      const float* __restrict__ lse, float* __restrict__ delta,
-                                                      T* __restrict__ dqkv, AttnArgs p) {
+__device__ __forceinline__ void dq_items(const T* __restrict__ qkv, const T* __restrict__ O, const T* __restrict__ dO,
+                                         const float* __restrict__ lse, float* __restrict__ delta, T* __restrict__ dqkv, const AttnArgs& p, Share sh) {
   constexpr int KB = kBlocks<DB>;
   const int lr = threadIdx.x & 15, g = threadIdx.x >> 4;
   const int N = p.N, d = p.d, GQ = p.H / p.Hkv;
   const int64_t rs = (int64_t)(p.H + 2 * p.Hkv) * d, h = (int64_t)p.H * d;
   const int64_t items = (int64_t)p.B * p.H * p.tiles;
-  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+  for (int64_t item = (int)blockIdx.x - sh.first; item < items; item += sh.count) {
     const int64_t hb = item / p.tiles;
     const int qt = p.causal ? p.tiles - 1 - (int)(item - hb * p.tiles) : (int)(item - hb * p.tiles);
     const int hd = (int)(hb % p.H);
@@ -209,7 +212,7 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_f32(const T* __restrict__ qkv,
         for (int e = 0; e < 4; ++e) dl = fmaf(dof[s][e], of[s][e], dl);
     }
     dl = groups_sum(dl);
-    if (i < N && g == 0) delta[hb * N + i] = dl;
+    if (delta && i < N && g == 0) delta[hb * N + i] = dl;
     const float li = i < N ? lse[hb * N + i] : 0.f;
 #pragma unroll
     for (int s = 0; s < DB; ++s) dq[s] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -255,15 +258,16 @@ __global__ __launch_bounds__(64) void attn_bwd_dq_f32(const T* __restrict__ qkv,
   }
 }
 
-template <typename T, int DB, bool VEC>
-__global__ __launch_bounds__(64) void attn_bwd_dkv_f32(const T* __restrict__ qkv, const T* __restrict__ dO, const float* __restrict__ lse,
-                                                       const float* __restrict__ delta, T* __restrict__ dqkv, AttnArgs p) {
+// OWN_DELTA: the row sums D_i are formed here from dO and O, with the additions of dq_items, and not read
+template <typename T, int DB, bool VEC, bool OWN_DELTA>
+__device__ __forceinline__ void dkv_items(const T* __restrict__ qkv, const T* __restrict__ O, const T* __restrict__ dO, const float* __restrict__ lse,
+                                          const float* __restrict__ delta, T* __restrict__ dqkv, const AttnArgs& p, Share sh) {
   constexpr int QB = kBlocks<DB>;
   const int lr = threadIdx.x & 15, g = threadIdx.x >> 4;
   const int N = p.N, d = p.d, GQ = p.H / p.Hkv;
   const int64_t rs = (int64_t)(p.H + 2 * p.Hkv) * d, h = (int64_t)p.H * d;
   const int64_t items = (int64_t)p.B * p.Hkv * p.tiles;
-  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+  for (int64_t item = (int)blockIdx.x - sh.first; item < items; item += sh.count) {
     const int64_t hb = item / p.tiles;
     const int kt = (int)(item - hb * p.tiles);             // the first tile of a causal row has the most queries
     const int kvh = (int)(hb % p.Hkv);
@@ -281,14 +285,16 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_f32(const T* __restrict__ qkv
       const T* qb_ = rowb + hd * d;
       const T* db_ = dO + b * N * h + hd * d;
       const float* lse_ = lse + (b * p.H + hd) * N;
-      const float* del_ = delta + (b * p.H + hd) * N;
-      f32x4 qf[QB][DB], of[QB][DB];
+      const float* del_ = OWN_DELTA ? nullptr : delta + (b * p.H + hd) * N;
+      const T* ob_ = O + b * N * h + hd * d;
+      f32x4 qf[QB][DB], of[QB][DB], out[OWN_DELTA ? QB : 1][DB];
       auto q_rows = [&](int i0) {
 #pragma unroll
         for (int u = 0; u < QB; ++u) {
           const int i = i0 + 16 * u + lr;
           row_frag<T, DB, VEC>(qf[u], qb_ + (int64_t)i * rs, g, d, i < N);
           row_frag<T, DB, VEC>(of[u], db_ + (int64_t)i * h, g, d, i < N);
+          if constexpr (OWN_DELTA) row_frag<T, DB, VEC>(out[u], ob_ + (int64_t)i * h, g, d, i < N);
         }
       };
       q_rows(i_begin);
@@ -302,7 +308,17 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_f32(const T* __restrict__ qkv
           for (int e = 0; e < 4; ++e) {
             const int i = i0 + 16 * u + 4 * g + e;
             li[u][e] = i < N ? lse_[i] : 0.f;
-            dl[u][e] = i < N ? del_[i] : 0.f;
+            if constexpr (!OWN_DELTA) dl[u][e] = i < N ? del_[i] : 0.f;
+          }
+          if constexpr (OWN_DELTA) {                     // of row lr of the block in every lane group, then of this lane's rows
+            float t = 0.f;
+#pragma unroll
+            for (int s = 0; s < DB; ++s)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) t = fmaf(of[u][s][e], out[u][s][e], t);
+            t = groups_sum(t);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dl[u][e] = __shfl(t, 4 * g + e, 64);
           }
         }
 #pragma unroll
@@ -338,6 +354,25 @@ __global__ __launch_bounds__(64) void attn_bwd_dkv_f32(const T* __restrict__ qkv
   }
 }
 
+template <typename T, int DB, bool VEC>
+__global__ __launch_bounds__(64) void attn_bwd_dq_f32(const T* __restrict__ qkv, const T* __restrict__ O, const T* __restrict__ dO,
+                                                      const float* __restrict__ lse, float* __restrict__ delta, T* __restrict__ dqkv, AttnArgs p) {
+  dq_items<T, DB, VEC>(qkv, O, dO, lse, delta, dqkv, p, {0, (int)gridDim.x});
+}
+template <typename T, int DB, bool VEC>
+__global__ __launch_bounds__(64) void attn_bwd_dkv_f32(const T* __restrict__ qkv, const T* __restrict__ dO, const float* __restrict__ lse,
+                                                       const float* __restrict__ delta, T* __restrict__ dqkv, AttnArgs p) {
+  dkv_items<T, DB, VEC, false>(qkv, nullptr, dO, lse, delta, dqkv, p, {0, (int)gridDim.x});
+}
+// Both in one launch where every item has a wave slot of its own: the two chains, each a launch's latency and a few blocks
+// long, then run side by side, at the price of reading O for dK/dV as well.  B2 N128 H4 d32: 10.3 + 13.7 us -> 15.0.
+template <int DB>
+__global__ __launch_bounds__(64) void attn_bwd_f32(const float* __restrict__ qkv, const float* __restrict__ O, const float* __restrict__ dO,
+                                                   const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, AttnArgs p, int ndkv) {
+  if ((int)blockIdx.x < ndkv) dkv_items<float, DB, true, true>(qkv, O, dO, lse, nullptr, dqkv, p, {0, ndkv});
+  else dq_items<float, DB, true>(qkv, O, dO, lse, delta, dqkv, p, {ndkv, (int)gridDim.x - ndkv});
+}
+
 // four columns per access where every head of every row starts on such a boundary
 template <typename T>
 bool four_columns(int d, const void* a, const void* b, const void* c, const void* e) {
@@ -355,10 +390,18 @@ mosaic_status fwd_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv
 template <typename T, int DB, bool VEC>
 mosaic_status bwd_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv, const void* O, const float* lse, const void* dO,
                     void* dqkv, float* delta) {
-  attn_bwd_dq_f32<T, DB, VEC><<<grid_for(quota, 8, (int64_t)p.B * p.H * p.tiles), 64, 0, s>>>((const T*)qkv, (const T*)O, (const T*)dO, lse,
+  const int64_t ndq = (int64_t)p.B * p.H * p.tiles, ndkv = (int64_t)p.B * p.Hkv * p.tiles;
+  if constexpr (std::is_same<T, float>::value && VEC && DB <= 4) {
+    if (ndq + ndkv <= (int64_t)quota * 4) {            // one wave per SIMD at most
+      attn_bwd_f32<DB><<<(int)(ndq + ndkv), 64, 0, s>>>((const float*)qkv, (const float*)O, (const float*)dO, lse, delta, (float*)dqkv, p, (int)ndkv);
+      MOSAIC_LAUNCH_CHECK();
+      return MOSAIC_OK;
+    }
+  }
+  attn_bwd_dq_f32<T, DB, VEC><<<grid_for(quota, 8, ndq), 64, 0, s>>>((const T*)qkv, (const T*)O, (const T*)dO, lse,
                                                                                             delta, (T*)dqkv, p);
   MOSAIC_LAUNCH_CHECK();
-  attn_bwd_dkv_f32<T, DB, VEC><<<grid_for(quota, 8, (int64_t)p.B * p.Hkv * p.tiles), 64, 0, s>>>((const T*)qkv, (const T*)dO, lse, delta,
+  attn_bwd_dkv_f32<T, DB, VEC><<<grid_for(quota, 8, ndkv), 64, 0, s>>>((const T*)qkv, (const T*)dO, lse, delta,
                                                                                                (T*)dqkv, p);
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;

@@ -82,3 +82,46 @@ def test_attention(mb, dtype, B, N, H, Hkv, d, causal, offset):
     if N > 1:          # over one key dS vanishes: only its rounding would be compared
         assert_close(from_dev(dq), O.attention_bwd(qkv, dO, B, N, H, causal, Hkv), dtype, "dqkv", roundings=8)
     assert all(torch.equal(bits(a), bits(c)) for a, c in zip(*outs))
+
+
+@pytest.mark.parametrize("B,N,H,Hkv,d,causal", [(2, 128, 4, 4, 32, 1), (1, 33, 4, 2, 16, 0), (2, 17, 2, 1, 64, 1), (1, 1, 2, 2, 4, 0), (1, 100, 3, 3, 28, 1)])
+def test_attention_backward_in_one_launch_has_the_bits_of_two(mb, B, N, H, Hkv, d, causal):
+    """dQ and dK/dV share a launch where every tile of 16 rows has a wave slot (256 CUs) and dK/dV then forms the row
+    sums of dO O itself; with one CU they are two launches.  The gradients and the row sums must not show which."""
+    w = (H + 2 * Hkv) * d
+    qkv, dO = [to_dev(synth.normal(900 + N + i, (B * N, n)), "f32") for i, n in enumerate((w, H * d))]
+    outs = []
+    for q in (256, 1):
+        Oo, dqkv = [torch.full((B * N, n), float("nan"), device="cuda") for n in (H * d, w)]
+        lse, delta = [torch.full((B, H, N), float("nan"), device="cuda") for _ in range(2)]
+        mb.op_attention_gqa_fwd(None, q, "f32", B, N, H, Hkv, d, causal, qkv, Oo, lse)
+        mb.op_attention_gqa_bwd(None, q, "f32", B, N, H, Hkv, d, causal, qkv, Oo, lse, dO, dqkv, delta)
+        torch.cuda.synchronize()
+        outs.append([bits(dqkv), bits(delta)])
+    assert not torch.isnan(outs[0][0].view(torch.float32)).any()
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+@pytest.mark.parametrize("T,k,n", [(1, 4, 4), (33, 64, 36), (256, 128, 384), (31, 132, 68), (300, 36, 8)])
+def test_backward_products_in_one_launch_have_the_bits_of_two(mb, T, k, n):
+    """A module takes the input and the weight gradient of a linear layer in one launch, the entry points one each."""
+    m = mb.Module(dict(kind="projector", batch=1, seq=T, in_dim=k, out_dim=n), "f32")
+    m.params.copy_(torch.randn(m.params.numel(), generator=torch.Generator().manual_seed(T)).mul_(0.1))
+    x, dy = to_dev(synth.normal(950 + T, (T, k)), "f32"), to_dev(synth.normal(951 + T, (T, n)), "f32")
+    y, dx = torch.full_like(dy, float("nan")), torch.full_like(x, float("nan"))
+    m.grads.fill_(float("nan"))
+    m.step(256, None, x, y, dy=dy, dx=dx)
+    part = lambda buf, name: buf[m.tensors[name][0]:m.tensors[name][0] + m.tensors[name][1] * m.tensors[name][2]].view(m.tensors[name][1], -1)
+    e = lambda *sh: torch.full(sh, float("nan"), device="cuda")
+    sc = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    z, a, da, dz, dx2, dw1, dw2 = e(T, n), e(T, n), e(T, n), e(T, n), e(T, k), e(k, n), e(n, n)
+    mb.op_linear_act_fwd(None, 256, "f32", mb.GELU, T, k, n, x, part(m.params, "w_1").contiguous(), part(m.params, "b_1").contiguous(), z, a)
+    mb.op_linear_dgrad(None, 256, "f32", T, n, n, dy, part(m.params, "w_2").contiguous(), None, da)
+    mb.op_linear_wgrad(None, 256, "f32", T, n, n, a, dy, dw2, None, sc)
+    mb.op_gelu_bwd(None, 256, "f32", T * n, z, da, dz)
+    mb.op_linear_dgrad(None, 256, "f32", T, k, n, dz, part(m.params, "w_1").contiguous(), None, dx2)
+    mb.op_linear_wgrad(None, 256, "f32", T, k, n, x, dz, dw1, None, sc)
+    torch.cuda.synchronize()
+    for name, got, want in (("dx", dx, dx2), ("w_1", part(m.grads, "w_1"), dw1), ("w_2", part(m.grads, "w_2"), dw2)):
+        assert torch.equal(bits(got.contiguous()), bits(want)), name
+    m.destroy()
