@@ -2,25 +2,26 @@
 //
 // Forward and the image-token gradient are row copies (HBM-bound).  The embedding gradient
 // needs, for every table row, the sum of the output gradients at the positions that hold it:
-//   1. the T positions are sorted by id with a stable radix sort (8 bits a pass, two launches a
-//      pass), so the occurrences of an id are one run in ascending position;
+//   1. the T positions are sorted by id with a stable radix sort (8 bits a pass), so the occurrences of an id are
+//      one run in ascending position: by one workgroup in its LDS while the others fill the table rows that nobody
+//      used and copy the image-token gradient (up to 8192 positions), else in two launches a pass;
 //   2. the sorted list is cut into segments of kSeg entries; a workgroup requests all rows of
 //      its segment at once and adds them run by run, so the work is balanced however often an
 //      id occurs; runs inside a segment go straight to the table, pieces of longer runs to scratch;
-//   3. the pieces of a run are added by the segment it starts in.  Rows that nobody used are
-//      found by bisection in the sorted list and filled with zeros beside step 2.
+//   3. the pieces of a run are added by the segment it starts in.  After the sort in several launches, rows that nobody
+//      used are found by bisection in the sorted list and filled with zeros beside step 2.
 // Every sum has one owner and an order fixed by the ids alone: repeated ids need no atomics and
 // the bits do not depend on the grid.
 //
 // The order: segments of 16 positions ascending, then the pieces of a run that spans segments, as
 // four quarters added in turn.
 //
-// What bounds it: the table is written whole (V x h; 131 MB at V 32000, h 2048) and dy read once;
-// the sort moves a few bytes per position in two short launches per 8 bits of the largest key (four at
-// V 32000, six from 65536 on).  A whole step (forward and backward) at B8 N1024 h2048 V32000, ids with the
-// frequencies of running text: 99 us = 2.5 TB/s of the bytes it cannot do without, against 2098 us when the
-// owner of every table row walks all positions (V x T id reads).  That walk is one launch, and
-// still what small calls take (scan_is_faster).
+// What bounds it: the table is written whole (V x h; 131 MB at V 32000, h 2048) and dy read once.
+// At B 8, N 1024, h 2048, V 32000, bf16, 196 or fewer image tokens: sort and fill 27 us, sums 11, joins 8 (forward 12); in six
+// launches of the sort, sums with the fill beside them, a join with a bisection per run and a launch for the image
+// tokens the whole pass took 100 us instead of 71, forward included.
+// A walk over all positions by the owner of every table row (V x T id reads) takes 2000 us there, but is one launch,
+// and still what small calls take (scan_is_faster).
 #include "kernels.h"
 
 namespace {
@@ -187,6 +188,128 @@ __global__ __launch_bounds__(kThreads) void sort_scatter_kernel(SortInput in, in
   }
 }
 
+// Sort, fill and image-token gradient in one launch.  Workgroup 0 sorts: a key and its position share 32 bits, a thread
+// holds up to 8 of them, and a pass scatters them through LDS in the order of sort_scatter_kernel, so the lists are the
+// same.  The others (all, if there is one) take table rows and image-token rows; which table rows are used they find
+// out by a walk over the ids, 2048 rows at a time.  What bounds it is the fill (27 us for 131 MB, the rate of a copy),
+// which covers the sort's 10 to 20 us of short dependent steps.
+constexpr int kOneThreads = 1024, kOneWaves = kOneThreads / 64, kFlagRows = 2048;
+constexpr int kOneMax = 8 * kOneThreads;              // positions that one workgroup sorts
+static_assert(kFlagRows <= kOneWaves * kBins + kOneMax, "flags");
+template <typename T, int V>
+__global__ __launch_bounds__(kOneThreads) void embed_prepare_kernel(SortInput in, const T* __restrict__ dy, T* __restrict__ d_img, T* __restrict__ dtable,
+                                                                    int B, int h, int total, int pos_bits, int32_t* __restrict__ key_out,
+                                                                    int32_t* __restrict__ pos_out) {
+  typedef typename Pack<T, V>::type vec;
+  __shared__ int lds[kOneWaves * kBins + kOneMax];    // workgroup 0: digit places [16 waves][256 bins], entries; others: flags of kFlagRows rows
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (blockIdx.x == 0) {
+    int* const place = lds;
+    int* const entry = lds + kOneWaves * kBins;
+    constexpr int R = kOneMax / kOneThreads;
+    __shared__ int wave_total[kWaves];
+    const int rounds = (total + kOneThreads - 1) / kOneThreads, first = wave * 64 * rounds + lane;
+    unsigned x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int e = first + 64 * r;
+      x[r] = r < rounds && e < total ? ((unsigned)in.key_of(e) << pos_bits) | (unsigned)e : 0u;
+    }
+    for (int shift = 0; shift == 0 || (in.vocab >> shift) > 0; shift += kDigit) {      // the largest key is `vocab`
+      const int at_bit = pos_bits + shift;
+#pragma unroll
+      for (int u = 0; u < kOneWaves * kBins / kOneThreads; ++u) place[u * kOneThreads + threadIdx.x] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (r < rounds && first + 64 * r < total) atomicAdd(&place[wave * kBins + ((x[r] >> at_bit) & (kBins - 1))], 1);
+      __syncthreads();
+      int all = 0, scan = 0;
+      if (threadIdx.x < kBins) {
+#pragma unroll
+        for (int w = 0; w < kOneWaves; ++w) all += place[w * kBins + threadIdx.x];
+        scan = all;                                    // inclusive over the bins
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int v = __shfl_up(scan, o, 64);
+          if (lane >= o) scan += v;
+        }
+        if (lane == 63) wave_total[wave] = scan;
+      }
+      __syncthreads();
+      if (threadIdx.x < kBins) {
+        int at = scan - all;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) if (w < wave) at += wave_total[w];
+#pragma unroll
+        for (int w = 0; w < kOneWaves; ++w) { const int v = place[w * kBins + threadIdx.x]; place[w * kBins + threadIdx.x] = at; at += v; }
+      }
+      __syncthreads();
+      volatile int* mine = place + wave * kBins;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (r < rounds) {
+          const bool live = first + 64 * r < total;
+          const int dgt = (x[r] >> at_bit) & (kBins - 1);
+          unsigned long long same = __ballot(live);      // lanes of this round with the same digit
+#pragma unroll
+          for (int b = 0; b < kDigit; ++b) {
+            const unsigned long long m = __ballot((dgt >> b) & 1);
+            same &= ((dgt >> b) & 1) ? m : ~m;
+          }
+          const int rank = __popcll(same & ((1ull << lane) - 1ull));
+          const int base = live ? mine[dgt] : 0;
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();               // every lane has read its base before a leader moves it
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+          if (live) {
+            if (rank == 0) mine[dgt] = base + __popcll(same);
+            entry[base + rank] = (int)x[r];
+          }
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < R; ++r) if (r < rounds && first + 64 * r < total) x[r] = (unsigned)entry[first + 64 * r];
+    }
+    for (int e = threadIdx.x; e < total; e += kOneThreads) {
+      const unsigned v = (unsigned)entry[e];
+      key_out[e] = (int32_t)(v >> pos_bits);
+      pos_out[e] = (int32_t)(v & ((1u << pos_bits) - 1u));
+    }
+    if (gridDim.x > 1) return;
+    __syncthreads();
+  }
+  const int workers = gridDim.x > 1 ? gridDim.x - 1 : 1, me = gridDim.x > 1 ? (int)blockIdx.x - 1 : 0;
+  const int per = (in.vocab + workers - 1) / workers, v0 = me * per, v1 = min(v0 + per, in.vocab);
+  for (int r0 = v0; r0 < v1; r0 += kFlagRows) {
+    const int n = min(kFlagRows, v1 - r0);
+    for (int i = threadIdx.x; i < n; i += kOneThreads) lds[i] = 0;
+    __syncthreads();
+    for (int e = threadIdx.x; e < total; e += kOneThreads) {
+      const int k = in.key_of(e) - r0;
+      if (k >= 0 && k < n) lds[k] = 1;
+    }
+    __syncthreads();
+    for (int r = wave; r < n; r += kOneWaves) {
+      if (lds[r]) continue;
+      for (int c = lane * V; c < h; c += 64 * V) *reinterpret_cast<vec*>(dtable + (int64_t)(r0 + r) * h + c) = vec{};
+    }
+    __syncthreads();
+  }
+  if (!d_img) return;
+  // image-token rows: those that the sample did not use get zero
+  for (int row = me * kOneWaves + wave; row < B * in.n_img; row += workers * kOneWaves) {
+    const int b = row / in.n_img, t = row - b * in.n_img;
+    const bool used = t < stem_n_img(in.counts, b, in.n_img);
+    const T* src = dy + ((int64_t)b * in.N + t) * h;
+    for (int c = lane * V; c < h; c += 64 * V) *reinterpret_cast<vec*>(d_img + (int64_t)row * h + c) = used ? *reinterpret_cast<const vec*>(src + c) : vec{};
+  }
+}
+
 // ---------------------------------------------------------------- sums over the runs
 constexpr int kSeg = 16;         // entries of a segment: as many rows as a thread holds in registers at once
 constexpr int kFillRows = 16;    // table rows a wave looks up and, where nobody used them, fills
@@ -277,46 +400,62 @@ __global__ __launch_bounds__(kThreads) void embed_join_kernel(const int32_t* __r
                                                               int ctiles) {
   __shared__ float red[kWaves][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int item = blockIdx.x; item < segs * ctiles; item += gridDim.x) {
-    const int seg = item / ctiles, c = (item - seg * ctiles) * 64 + lane;
-    const int last = seg * kSeg + kSeg - 1;
-    if (last + 1 >= total) continue;
-    const int id = key[last];
-    if (id >= vocab || key[last + 1] != id) continue;                                   // ends here
-    if (key[seg * kSeg] == id && seg > 0 && key[seg * kSeg - 1] == id) continue;        // started earlier
-    int lo = last + 1, hi = total;                                                      // end of the run
-    while (lo < hi) { const int mid = (lo + hi) >> 1; if (key[mid] == id) lo = mid + 1; else hi = mid; }
-    const int n = (lo - 1) / kSeg - seg;                                                // segments that follow
-    const int per = (n + kWaves - 1) / kWaves;
-    const int s0 = seg + 1 + wave * per, s1 = min(s0 + per, seg + 1 + n);
-    float acc = 0.f;
-    if (c < h) {
-      if (wave == 0) acc = part[((int64_t)seg * 2 + 1) * h + c];
-      int s = s0;
-      for (; s + 8 <= s1; s += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(s + u) * 2 * h + c];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += v[u];
+  const int items = segs * ctiles;
+  // 64 of this workgroup's items are looked at together, a lane each (every wave comes to the same): few have work to do,
+  // and the key loads of one after the other were most of this kernel
+  for (int64_t first = blockIdx.x; first < items; first += 64ll * gridDim.x) {
+    const int64_t mine = first + (int64_t)lane * gridDim.x;
+    bool starts = false;                               // a run that starts in the segment goes on behind it
+    if (mine < items) {
+      const int seg = (int)mine / ctiles, e0 = seg * kSeg, next = e0 + kSeg;
+      if (next < total) {
+        const int id = key[next - 1], after = key[next], head = key[e0], before = e0 > 0 ? key[e0 - 1] : -1;
+        starts = id < vocab && after == id && !(head == id && before == id);
       }
-      for (; s < s1; ++s) acc += part[(int64_t)s * 2 * h + c];
     }
-    red[wave][lane] = acc;
-    __syncthreads();
-    if (wave == 0 && c < h) {
+    unsigned long long todo = __ballot(starts);
+    while (todo) {
+      const int item = (int)(first + (int64_t)(__ffsll(todo) - 1) * gridDim.x);
+      todo &= todo - 1;
+      const int seg = item / ctiles, c = (item - seg * ctiles) * 64 + lane;
+      const int id = key[seg * kSeg + kSeg - 1];
+      // segments that follow: those whose first entry is the run's, 64 looked at together
+      int n = 0;
+      for (bool all = true; all; ) {
+        const int64_t e = (int64_t)(seg + 1 + n + lane) * kSeg;
+        const unsigned long long m = ~__ballot(e < total && key[e] == id);
+        all = m == 0;
+        n += all ? 64 : __ffsll(m) - 1;
+      }
+      const int per = (n + kWaves - 1) / kWaves;
+      const int s0 = seg + 1 + wave * per, s1 = min(s0 + per, seg + 1 + n);
+      float acc = 0.f;
+      if (c < h) {
+        if (wave == 0) acc = part[((int64_t)seg * 2 + 1) * h + c];
+        for (int s = s0; s < s1; s += 8) {
+          float v[8];
 #pragma unroll
-      for (int w = 1; w < kWaves; ++w) acc += red[w][lane];
-      dtable[(int64_t)id * h + c] = from_f32<T>(acc);
+          for (int u = 0; u < 8; ++u) v[u] = s + u < s1 ? part[(int64_t)(s + u) * 2 * h + c] : 0.f;
+#pragma unroll
+          for (int u = 0; u < 8; ++u) if (s + u < s1) acc += v[u];
+        }
+      }
+      red[wave][lane] = acc;
+      __syncthreads();
+      if (wave == 0 && c < h) {
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) acc += red[w][lane];
+        dtable[(int64_t)id * h + c] = from_f32<T>(acc);
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
 // Small calls: the workgroup that owns a table row walks all positions, 256 at a time, gathers
 // those that hold its id into a list in LDS in ascending order (waves in order, lanes in order, by ballot
 // and prefix count) and adds the listed rows of dy in that order, all columns of a row in registers.
-constexpr int kScanPositions = 640, kScanCols = 32;   // columns per thread: rows of up to 8192 elements
+constexpr int kScanPositions = 96, kScanCols = 32;   // columns per thread: rows of up to 8192 elements
 template <typename T>
 __global__ __launch_bounds__(kThreads) void embed_scan_kernel(const T* __restrict__ dy, const int32_t* __restrict__ ids,
                                                               const int32_t* __restrict__ counts, T* __restrict__ dtable,
@@ -364,17 +503,15 @@ __global__ __launch_bounds__(kThreads) void embed_scan_kernel(const T* __restric
   }
 }
 
-// One launch of the scan against four to six of the sort, whatever the CUs (the orders of the sums
+// One launch of the scan against three of the sort, whatever the CUs (the orders of the sums
 // differ, so the rule is one of the shape).  The scan takes a pass over the ids per table row and the rows of an id one
-// after the other: it loses with many rows, with many positions to an id, and with long sums of wide rows.  Measured
+// after the other: it loses with many rows and with many positions to an id.  Measured
 // on 256 CUs, bf16, ids with the frequencies of running text, scan / sort in us:
-//   T 128 h 512 V 1000  9.0 / 22.6,  V 16000  20.7 / 21.1,  V 32000  38 / 22      T 16 h 64 V 32  4.9 / 14.4
-//   T 128 h 64 V 32  14.7 / 14.5     T 256 h 1024 V 4000  18.9 / 24.3,  h 2048  30 / 25     T 512 h 256 V 4000  24.0 / 27.1
-//   T 600 h 64 V 4000  22.3 / 28.0   T 1024 h 64 V 4000  44.7 / 28.4
+//   T 16 h 64 V 32  5.0 / 12.2      T 64 h 64 V 16  10.7 / 12.7      h 512 V 255  5.4 / 12.9     h 2048 V 8000  14.0 / 16.0
+//   T 64 h 64 V 16000  17.9 / 13.5  T 96 h 128 V 64  11.1 / 12.5     V 1000  6.2 / 14.5         h 2048 V 4000  16.2 / 15.6
+//   T 128 h 64 V 32  15.3 / 12.6    h 512 V 1000  13.7 / 14.2        T 256 h 1024 V 4000  22.6 / 15.4
 inline bool scan_is_faster(int64_t T, int64_t h, int64_t vocab) {
-  const bool one_digit = vocab < kBins;                // four launches of the sort instead of six
-  return vocab <= 16384 && T <= 4 * vocab && T <= (one_digit ? 256 : kScanPositions) && T * h <= (one_digit ? 1 << 17 : 1 << 18) &&
-         h <= kScanCols * kThreads;
+  return vocab <= 8192 && T <= kScanPositions && T <= 4 * vocab && T * h <= 1 << 18 && h <= kScanCols * kThreads;
 }
 
 struct EmbedScratch {
@@ -390,15 +527,46 @@ struct EmbedScratch {
 };
 
 template <typename T, int V>
+mosaic_status split_img(hipStream_t s, int quota, int B, int N, int n_img, int h, const T* dy, const int32_t* counts, T* d_img) {
+  if (!d_img || n_img <= 0) return MOSAIC_OK;
+  split_img_kernel<T, V><<<grid_for(quota, 8, ceil_div((int64_t)B * n_img, kWaves)), kThreads, 0, s>>>(dy, counts, d_img, B, N, n_img, h);
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
+
+inline int bits_of(int v) { int n = 0; while (v >> n) ++n; return n; }
+// One workgroup's LDS holds the positions, 32 bits a key (up to `vocab`) and its position.  One launch against five and
+// more; one CU sorts, which tells at more positions.  Measured on 256 CUs, bf16, one / several launches in us:
+//   T 2048 h 64 V 1048576  54 / 99     T 4096 h 2048 V 32000  33 / 54     T 8192 h 2048 V 32000  43 / 61     h 256 V 400  34 / 37
+//   T 16384 h 2048 V 32000  76 / 72    h 512 V 500  63 / 43 (32 keys a thread)
+inline bool sorts_in_one(int64_t total, int64_t vocab) { return total <= kOneMax && bits_of((int)vocab) + bits_of((int)total - 1) <= 32; }
+
+template <typename T, int V>
 mosaic_status embed_grad_t(hipStream_t s, int quota, int B, int N, int n_img, int h, int vocab, const T* dy,
-                           const int32_t* ids, const int32_t* counts, T* dtable, char* scratch) {
+                           const int32_t* ids, const int32_t* counts, T* d_img, T* dtable, char* scratch) {
   const int total = B * N;
   if (scan_is_faster(total, h, vocab)) {
+    MOSAIC_TRY((split_img<T, V>(s, quota, B, N, n_img, h, dy, counts, d_img)));
     embed_scan_kernel<T><<<grid_for(quota, 8, vocab), kThreads, 0, s>>>(dy, ids, counts, dtable, B, N, n_img, h, vocab);
     MOSAIC_LAUNCH_CHECK();
     return MOSAIC_OK;
   }
+  const int segs = (int)ceil_div(total, kSeg), ctiles = (int)ceil_div(h, kThreads * V), jtiles = (int)ceil_div(h, 64);
   const EmbedScratch sc(total, h);
+  if (sorts_in_one(total, vocab)) {
+    int32_t *key = (int32_t*)(scratch + sc.key[0]), *pos = (int32_t*)(scratch + sc.pos[0]);
+    float* part = (float*)(scratch + sc.part);
+    const SortInput in = {nullptr, nullptr, ids, counts, N, n_img, vocab};
+    embed_prepare_kernel<T, V><<<grid_for(quota, 1, 1 + ceil_div(vocab, kOneWaves)), kOneThreads, 0, s>>>(in, dy, n_img > 0 ? d_img : nullptr, dtable, B, h,
+                                                                                                         total, bits_of(total - 1), key, pos);
+    MOSAIC_LAUNCH_CHECK();
+    embed_sum_kernel<T, V><<<grid_for(quota, 8, (int64_t)segs * ctiles), kThreads, 0, s>>>(dy, key, pos, dtable, part, total, h, vocab, segs, ctiles, 0);
+    MOSAIC_LAUNCH_CHECK();
+    embed_join_kernel<T><<<grid_for(quota, 8, (int64_t)segs * jtiles), kThreads, 0, s>>>(key, part, dtable, total, h, vocab, segs, jtiles);
+    MOSAIC_LAUNCH_CHECK();
+    return MOSAIC_OK;
+  }
+  MOSAIC_TRY((split_img<T, V>(s, quota, B, N, n_img, h, dy, counts, d_img)));
   const int chunks = (int)ceil_div(total, kChunk);
   int32_t* key[2] = {(int32_t*)(scratch + sc.key[0]), (int32_t*)(scratch + sc.key[1])};
   int32_t* pos[2] = {(int32_t*)(scratch + sc.pos[0]), (int32_t*)(scratch + sc.pos[1])};
@@ -414,9 +582,7 @@ mosaic_status embed_grad_t(hipStream_t s, int quota, int B, int N, int n_img, in
     sort_scatter_kernel<<<grid, kThreads, 0, s>>>(in, shift, total, chunks, hist, key[cur], pos[cur]);
     MOSAIC_LAUNCH_CHECK();
   }
-  const int segs = (int)ceil_div(total, kSeg), ctiles = (int)ceil_div(h, kThreads * V);
   const int fills = (int)ceil_div(vocab, kWaves * kFillRows);
-  const int jtiles = (int)ceil_div(h, 64);
   if ((int64_t)segs * jtiles + fills > INT32_MAX) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "embedding gradient over %d positions", total);
   embed_sum_kernel<T, V><<<grid_for(quota, 8, (int64_t)segs * ctiles + fills), kThreads, 0, s>>>(dy, key[cur], pos[cur], dtable, part, total, h,
                                                                                                 vocab, segs, ctiles, fills);
@@ -451,14 +617,8 @@ template <typename T>
 mosaic_status text_stem_bwd_t(hipStream_t s, int quota, int B, int N, int n_img, int h, int vocab, const T* dy,
                               const int32_t* ids, const int32_t* counts, T* d_img, T* dtable, char* scratch) {
   const bool wide = wide_rows<T>(h, dy, d_img, dtable);
-  if (d_img != nullptr && n_img > 0) {
-    const int grid = grid_for(quota, 8, ceil_div((int64_t)B * n_img, kWaves));
-    if (wide) split_img_kernel<T, Vec16<T>::N><<<grid, kThreads, 0, s>>>(dy, counts, d_img, B, N, n_img, h);
-    else split_img_kernel<T, 1><<<grid, kThreads, 0, s>>>(dy, counts, d_img, B, N, n_img, h);
-    MOSAIC_LAUNCH_CHECK();
-  }
-  if (wide) return embed_grad_t<T, Vec16<T>::N>(s, quota, B, N, n_img, h, vocab, dy, ids, counts, dtable, scratch);
-  return embed_grad_t<T, 1>(s, quota, B, N, n_img, h, vocab, dy, ids, counts, dtable, scratch);
+  if (wide) return embed_grad_t<T, Vec16<T>::N>(s, quota, B, N, n_img, h, vocab, dy, ids, counts, d_img, dtable, scratch);
+  return embed_grad_t<T, 1>(s, quota, B, N, n_img, h, vocab, dy, ids, counts, d_img, dtable, scratch);
 }
 
 constexpr int kEmbedMaxWidth = kScanCols * kThreads;   // the widest rows that the entry point takes

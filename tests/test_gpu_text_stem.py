@@ -24,7 +24,7 @@ CASES = [  # B, N, n_img, h, vocab, ids, offset of the caller's tensors in eleme
     (2, 1500, 700, 40, 65536, "mixed", 0),
     (2, 1500, 0, 24, 16777217, "mixed", 0),
     (5, 900, 11, 1032, 3, "mixed", 3),
-    # scanned (positions, positions x width, vocabulary at their limits), then one past each limit
+    # few positions to many, narrow and wide, small and large vocabularies
     (2, 128, 0, 512, 255, "mixed", 0), (1, 257, 0, 64, 255, "mixed", 0), (1, 256, 0, 520, 255, "mixed", 0),
     (1, 512, 7, 512, 256, "mixed", 1), (1, 640, 0, 64, 300, "one", 0), (1, 641, 7, 64, 256, "one", 0), (1, 512, 0, 520, 257, "mixed", 0),
     (4, 64, 20, 1024, 16384, "one", 0), (4, 64, 20, 64, 16385, "mixed", 0), (1, 32, 0, 8192, 16, "one", 0), (1, 64, 3, 1000, 16, "mixed", 0), (1, 65, 0, 1000, 16, "mixed", 0),
@@ -83,3 +83,17 @@ def test_text_stem_step(dtype, B, N, n_img, h, vocab, how, offset):
         assert not bool(got.any()), "rows that nobody used"          # NaN counts as non-zero
     finally:
         stem.destroy()
+
+
+# one workgroup sorts up to 8192 positions where a key and its position fit 32 bits: both sides of both limits, of a
+# round (1024 positions), of a wave's share, and of the scan's limits; more rows to a workgroup than it flags at once
+ONE_SORT = [(1, 97, 0, 64, 30, "mixed", 0), (1, 97, 0, 64, 8192, "mixed", 0), (1, 96, 5, 64, 8193, "mixed", 0), (1, 96, 0, 64, 24, "one", 0),
+            (1, 1024, 0, 8, 300, "mixed", 0), (1, 1025, 1, 8, 300, "mixed", 0), (1, 8192, 0, 8, 524287, "mixed", 0),
+            (1, 8192, 0, 8, 524288, "mixed", 0), (3, 2731, 40, 24, 999, "mixed", 1), (1, 8192, 5, 72, 65537, "one", 0),
+            (1, 300, 0, 8, 1200007, "mixed", 0), (8, 1024, 196, 128, 70, "mixed", 0)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,N,n_img,h,vocab,how,offset", ONE_SORT)
+def test_sort_in_one_launch(dtype, B, N, n_img, h, vocab, how, offset):
+    test_text_stem_step(dtype, B, N, n_img, h, vocab, how, offset)
