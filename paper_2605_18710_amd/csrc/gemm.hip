@@ -263,7 +263,10 @@ struct ActArgs {
   uint32_t c2_bytes = 0;
   int gu_f = 0;
   int row_block = 1 << 20;   // tile rows per super-block of the tile order (set by the launcher)
+  uint32_t r_rows = 0, r_magic = 0;   // r_rows > 0: R has that many rows, and row r of C gets row r mod r_rows (a position table)
 };
+// r mod r_rows with r_magic = 2^32 / r_rows + 1: exact as long as r * r_rows < 2^32 (checked by the launcher)
+__device__ __forceinline__ int table_row(int r, uint32_t r_rows, uint32_t r_magic) { return r - (int)(__umulhi((uint32_t)r, r_magic) * r_rows); }
 
 // PIECES_CHAINED: one workgroup takes the pieces of its tile one after the other and adds them in registers,
 // in the order and with the additions of the second kernel: the same bits as PIECES_APART, no scratch.
@@ -286,7 +289,7 @@ __device__ __forceinline__ void gemm_bf16_body(
 
   const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, a_bytes), rb = make_rsrc(B, b_bytes);
   const __amdgpu_buffer_rsrc_t rc = make_rsrc(C, c_bytes);
-  const __amdgpu_buffer_rsrc_t rr = make_rsrc(R, R ? c_bytes : 0u);
+  const __amdgpu_buffer_rsrc_t rr = make_rsrc(R, !R ? 0u : aa.r_rows ? (uint32_t)(aa.r_rows * ldc * 2) : c_bytes);
   const __amdgpu_buffer_rsrc_t rbias = make_rsrc(bias, bias ? (uint32_t)N * 2u : 0u);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -517,6 +520,12 @@ __device__ __forceinline__ void gemm_bf16_body(
       const int col = it.n0 + wn + 32 * (b % TN) + 8 * (ln & 3);
       return (col < N) ? (unsigned)(((int64_t)row * ldc + col) * 2) : kOob;
     };
+    auto res_off = [&](int b, int q) -> int {            // the same in R
+      if (!aa.r_rows) return (int)out_off(b, q);
+      const int row = table_row(it.m0 + wm + 32 * (b / TN) + (ln >> 2) + 16 * q, aa.r_rows, aa.r_magic);
+      const int col = it.n0 + wn + 32 * (b % TN) + 8 * (ln & 3);
+      return (col < N) ? (int)(unsigned)(((int64_t)row * ldc + col) * 2) : (int)kOob;
+    };
     // bias for the 8 columns this lane writes back in column block j (same for every row block)
     auto bias_req = [&](int j) -> u32x4 {
       const int col = it.n0 + wn + 32 * j + 8 * (ln & 3);
@@ -532,7 +541,7 @@ __device__ __forceinline__ void gemm_bf16_body(
     if constexpr (MODE == EPI_RES) {
       bnext = bias_req(0);
 #pragma unroll
-      for (int q = 0; q < 2; ++q) rnext[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)out_off(0, q), 0, 0);
+      for (int q = 0; q < 2; ++q) rnext[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, res_off(0, q), 0, 0);
     }
 #pragma unroll
     for (int b = 0; b < TM * TN; ++b) {
@@ -580,7 +589,7 @@ __device__ __forceinline__ void gemm_bf16_body(
           if constexpr (MODE == EPI_RES) {
             if (b + 1 < TM * TN) {
 #pragma unroll
-              for (int q = 0; q < 2; ++q) rnext[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, (int)out_off(b + 1, q), 0, 0);
+              for (int q = 0; q < 2; ++q) rnext[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, res_off(b + 1, q), 0, 0);
               bnext = bias_req((b + 1) % TN);
             }
           }
@@ -991,8 +1000,9 @@ struct W4Args {
   int64_t lda, ldb, ldc, ldc2;
   uint32_t a_bytes, b_bytes, c_bytes, c2_bytes;
   int tiles_m, tiles_n, tile_begin, tile_count, row_block, gu_f;
+  uint32_t r_rows, r_magic;        // W4_TABLE: see ActArgs
 };
-enum { W4_PLAIN, W4_BIAS, W4_RES, W4_GELU, W4_SWIGLU };
+enum { W4_PLAIN, W4_BIAS, W4_RES, W4_GELU, W4_SWIGLU, W4_TABLE };
 constexpr int kW4Stage = 2 * 256 * 64 * 2;                         // both operands of a K-tile
 constexpr int kW4Pitch = 68;                                       // floats per row of the epilogue's patch: 16 rows of 64
 constexpr int kW4Patch = 4 * 16 * kW4Pitch * 4;
@@ -1193,7 +1203,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
     st ^= 1;
   };
   const __amdgpu_buffer_rsrc_t rc = make_rsrc(p.C, p.c_bytes), rc2 = make_rsrc(p.C2, p.C2 ? p.c2_bytes : 0u);
-  const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.R, p.R ? p.c_bytes : 0u), rbias = make_rsrc(p.bias, p.bias ? (uint32_t)p.N * 2u : 0u);
+  const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.R, !p.R ? 0u : EPI == W4_TABLE ? (uint32_t)(p.r_rows * p.ldc * 2) : p.c_bytes), rbias = make_rsrc(p.bias, p.bias ? (uint32_t)p.N * 2u : 0u);
   while (true) {
     settle();
     for (int n = nk - 2; n > 0; --n) step();
@@ -1237,9 +1247,12 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
         const int i = b >> 1, h = b & 1, row0 = it.m0 + wm + 16 * i, col = out_col(h);
         const bool ok = col < ncols;
         u32x4 res[2] = {};
-        if constexpr (EPI == W4_RES) {
+        if constexpr (EPI == W4_RES || EPI == W4_TABLE) {
 #pragma unroll
-          for (int q = 0; q < 2; ++q) res[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, off(row0 + prow + 8 * q, col, p.ldc, ok), 0, 0);
+          for (int q = 0; q < 2; ++q) {
+            const int row = row0 + prow + 8 * q;
+            res[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, off(EPI == W4_TABLE ? table_row(row, p.r_rows, p.r_magic) : row, col, p.ldc, ok), 0, 0);
+          }
         }
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
@@ -1280,7 +1293,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
             for (int e = 0; e < 8; ++e) {
               float x = v[e];
               if constexpr (EPI != W4_PLAIN) x += (float)bv[e];
-              if constexpr (EPI == W4_RES) x += (float)rv[e];
+              if constexpr (EPI == W4_RES || EPI == W4_TABLE) x += (float)rv[e];
               o[e] = (bf16)x;
             }
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rc, off(row, col, p.ldc, ok), 0, 0);
@@ -1427,7 +1440,7 @@ mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf1
   W4Args p = {};
   p.A = A; p.B = B; p.C = C; p.bias = bias; p.R = R; p.C2 = aa.C2;
   p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.ldc2 = aa.ldc2;
-  p.a_bytes = a_bytes; p.b_bytes = b_bytes; p.c_bytes = c_bytes; p.c2_bytes = aa.c2_bytes; p.gu_f = aa.gu_f;
+  p.a_bytes = a_bytes; p.b_bytes = b_bytes; p.c_bytes = c_bytes; p.c2_bytes = aa.c2_bytes; p.gu_f = aa.gu_f; p.r_rows = aa.r_rows; p.r_magic = aa.r_magic;
   p.tiles_m = (int)ceil_div(M, 32 * MI); p.tiles_n = (int)ceil_div(N, 256);
   p.tile_begin = tile_begin;
   p.tile_count = tile_count < 0 ? p.tiles_m * p.tiles_n - tile_begin : tile_count;
@@ -1437,6 +1450,7 @@ mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf1
     if (aa.act == ACT_GELU) return launch_w4_epi<A_KC, B_KC, W4_GELU, MI>(s, quota, p);
     if (aa.act == ACT_SWIGLU) return launch_w4_epi<A_KC, B_KC, W4_SWIGLU, MI>(s, quota, p);
     if (bias && !R) return launch_w4_epi<A_KC, B_KC, W4_BIAS, MI>(s, quota, p);
+    if (R && aa.r_rows) return launch_w4_epi<A_KC, B_KC, W4_TABLE, MI>(s, quota, p);
   }
   if (R || bias) return launch_w4_epi<A_KC, B_KC, W4_RES, MI>(s, quota, p);
   return launch_w4_epi<A_KC, B_KC, W4_PLAIN, MI>(s, quota, p);
@@ -1601,7 +1615,7 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
                                                                           c_bytes, 1, 0, nullptr, sub, tile_begin, tile_count, aa);
     }
     return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes, c_bytes, 1, 0,
-                                                   nullptr, sub, tile_begin, tile_count);
+                                                   nullptr, sub, tile_begin, tile_count, aa);
   };
   if (plan == 256) return launch_tiles(std::true_type{}, 1, 0, -1);
   if (plan == 128) return launch_tiles(std::false_type{}, 1, 0, -1);
@@ -1630,7 +1644,7 @@ size_t gemm_splitk_scratch_bytes(int64_t M, int64_t N, int64_t K) {
 static mosaic_status launch_gemm_impl(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int64_t M, int64_t N,
                           int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
                           int64_t ldc, const void* bias, const void* R, void* splitk_scratch,
-                          int64_t b_rows, int act, void* C2, int64_t ldc2, bool* fused) {
+                          int64_t b_rows, int act, void* C2, int64_t ldc2, bool* fused, int64_t r_rows = 0) {
   if (fused) *fused = false;
   if (b_rows < 0 || b_kc) b_rows = K;
   if (M < 0 || N < 0 || K < 0) MOSAIC_FAIL(MOSAIC_EINVAL, "negative GEMM size");
@@ -1652,6 +1666,7 @@ static mosaic_status launch_gemm_impl(hipStream_t s, int quota, int dtype, bool 
     bf16* c = (bf16*)C;
     if (a_kc && !b_kc) {
       ActArgs aa;
+      if (r_rows > 0) { aa.r_rows = (uint32_t)r_rows; aa.r_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)r_rows + 1); }
       if (fused && C2 && !R && (uintptr_t)C2 % 16 == 0 && ldc2 % 8 == 0) {
         const int64_t n2 = act == MOSAIC_SWIGLU ? N / 2 : N;
         const int64_t c2_ext = ((M - 1) * ldc2 + n2) * 2;
@@ -1670,6 +1685,10 @@ static mosaic_status launch_gemm_impl(hipStream_t s, int quota, int dtype, bool 
     if (!a_kc && !b_kc) return launch_wgrad(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb, (float*)splitk_scratch);
     return launch_mfma_shape<false, true>(s, quota, (int)M, (int)N, (int)K, a, lda, b, ldb, c, ldc, bi, r, ab, bb, cb);
   }
+  if (r_rows > 0) {
+    MOSAIC_TRY(launch_gemm_f32(s, quota, dtype, a_kc, b_kc, (int)M, (int)N, (int)b_rows, A, lda, B, ldb, C, ldc, bias, nullptr));
+    return launch_add_pos(s, quota, dtype, (int)(M / r_rows), (int)r_rows, (int)N, R, C);
+  }
   return launch_gemm_f32(s, quota, dtype, a_kc, b_kc, (int)M, (int)N, (int)b_rows, A, lda, B, ldb, C, ldc, bias, R);
 }
 
@@ -1677,6 +1696,16 @@ mosaic_status launch_gemm(hipStream_t s, int quota, int dtype, bool a_kc, bool b
                           int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
                           int64_t ldc, const void* bias, const void* R, void* splitk_scratch, int64_t b_rows) {
   return launch_gemm_impl(s, quota, dtype, a_kc, b_kc, M, N, K, A, lda, B, ldb, C, ldc, bias, R, splitk_scratch, b_rows, 0, nullptr, 0, nullptr);
+}
+
+mosaic_status launch_embed_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t rows, int64_t n, int64_t k, int64_t ldx, const void* X,
+                               const void* W, const void* bias, const void* table, void* Y) {
+  const int64_t M = B * rows;
+  if (rows < 2 || (M + 255) * rows >= (int64_t)1 << 32) {      // not table_row's range (rows of a tile past M too)
+    MOSAIC_TRY(launch_gemm_impl(s, quota, dtype, true, false, M, n, ldx, X, ldx, W, n, Y, n, bias, nullptr, nullptr, k, 0, nullptr, 0, nullptr));
+    return launch_add_pos(s, quota, dtype, (int)B, (int)rows, (int)n, table, Y);
+  }
+  return launch_gemm_impl(s, quota, dtype, true, false, M, n, ldx, X, ldx, W, n, Y, n, bias, table, nullptr, k, 0, nullptr, 0, nullptr, rows);
 }
 
 mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act, int64_t T, int64_t k, int64_t n,

@@ -17,6 +17,10 @@ mosaic_status launch_gemm(hipStream_t s, int quota, int dtype, bool a_kc, bool b
 // Padded rows: with lda >= M rounded up to 8, a K-strided A may have any M (its rows must be
 // readable up to that width).  b_rows >= 0: a K-strided B has only that many of its K rows; the
 // columns of A past them must hold zeros.
+// Y[b, t, :] = X[b, t, :] W + bias + table[t, :]: B x rows patches of k values, ldx apart (zeros past k), W [k, n].  One rounding
+// where the bf16 matrix-core kernel takes the product and the table in its epilogue, else the product and add_pos.
+mosaic_status launch_embed_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t rows, int64_t n, int64_t k, int64_t ldx, const void* X,
+                               const void* W, const void* bias, const void* table, void* Y);
 // Z[T,n] = X[T,k] W[k,n] (+ bias[n]) and A = act(Z): GELU / tanh GELU give A[T,n]; SwiGLU reads Z
 // as [gate | up] halves and gives A[T,n/2] = silu(gate) * up.  Where the bf16 matrix-core kernel
 // takes the product, the activation is applied in its epilogue (same bits as the separate pass);

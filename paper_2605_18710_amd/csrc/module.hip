@@ -130,9 +130,15 @@ inline int64_t qkv_width(const mosaic_module_desc& d) {
 }
 inline int kv_heads_of(const mosaic_module_desc& d) { return d.kv_heads > 0 ? d.kv_heads : d.heads; }
 
-// distance between unfolded patches: whole 16-byte pieces, so that the matrix-core product takes
-// patches of 588 elements too (14 x 14); tokens that the caller brings (patch = 0) are dense
-inline int64_t patch_ld(const mosaic_module_desc& d) { return d.patch > 0 ? ceil_div(d.in_dim, 8) * 8 : d.in_dim; }
+// Distance between unfolded patches: whole 16-byte pieces, so that the matrix-core product takes patches of 588 elements too
+// (14 x 14); whole K-tiles of the four-wave kernel (64) where that adds at most an eighth (588 -> 640; forward product of 9216
+// patches, h 1024: 22.2 us with eight waves and 7.5 for the position table in a pass of its own -> 21.0 for both).  Tokens that the
+// caller brings (patch = 0) are dense.
+inline int64_t patch_ld(const mosaic_module_desc& d) {
+  if (d.patch <= 0) return d.in_dim;
+  const int64_t tile = ceil_div(d.in_dim, 64) * 64;
+  return d.dtype == MOSAIC_BF16 && 8 * (tile - d.in_dim) <= d.in_dim ? tile : ceil_div(d.in_dim, 8) * 8;
+}
 
 void build_layout(mosaic_module* m) {
   const mosaic_module_desc& d = m->d;
@@ -397,10 +403,7 @@ mosaic_status patch_stem_forward(mosaic_module* m, hipStream_t s, int q, const v
     MOSAIC_TRY(launch_unfold(s, q, d.dtype, d.batch, side, d.patch, x, W(m, m->s_patches), (int)patch_ld(d)));
     tokens = W(m, m->s_patches);
   }
-  MOSAIC_TRY(launch_gemm(s, q, d.dtype, true, false, m->T, d.hidden, patch_ld(d), tokens, patch_ld(d), P(m, p.w_1), d.hidden, y, d.hidden, P(m, p.b_1), nullptr,
-                         nullptr, d.in_dim));
-  MOSAIC_TRY(launch_add_pos(s, q, d.dtype, d.batch, d.seq, d.hidden, P(m, p.w_2), y));
-  return MOSAIC_OK;
+  return launch_embed_fwd(s, q, d.dtype, d.batch, d.seq, d.hidden, d.in_dim, patch_ld(d), tokens, P(m, p.w_1), P(m, p.b_1), P(m, p.w_2), y);
 }
 
 mosaic_status patch_stem_backward(mosaic_module* m, hipStream_t s, int q, const void* dy, void* dx) {

@@ -1,5 +1,5 @@
 """Patch stem at the sizes where padded patch rows and the access widths can go wrong: 14 x 14
-patches (588 elements, padded to 592 in bf16), one patch per sample, patches whose rows need no padding,
+patches (588 elements, padded in bf16), one patch per sample, patches whose rows need no padding,
 widths around a tile, and a caller's tensors that do not start on a 16-byte boundary."""
 import numpy as np
 import pytest
@@ -52,3 +52,10 @@ def test_patch_stem_step(dtype, B, g, patch, h, offset):
             assert_close(got[k], g_ref[k], dtype, k, roundings=2)
     finally:
         m.destroy()
+
+
+# the position table in the product's epilogue: fewer positions than a tile has rows, one position (a pass of its own), tiles of four
+# waves and of eight (the share of the CUs decides; the bits must not follow it), a last tile that is partly past the tokens
+@pytest.mark.parametrize("B,g,patch,h", [(300, 1, 14, 256), (130, 2, 16, 640), (40, 7, 14, 520), (9, 24, 14, 1024), (7, 13, 16, 768)])
+def test_position_table_in_the_product(B, g, patch, h):
+    test_patch_stem_step("bf16", B, g, patch, h, 0)
