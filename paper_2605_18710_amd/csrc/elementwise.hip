@@ -395,10 +395,45 @@ __global__ __launch_bounds__(kThreads) void gelu_bwd_kernel(const T* __restrict_
   }
 }
 
+// Column sums over a row partition by one workgroup: its waves take a quarter of the rows each, in ascending order, and the
+// four sums are added in the order of the rows.  Lane l of every wave owns the VN columns from c on; `row(r)` adds
+// row r into its argument.  rows4(r) adds four rows, requested together.  What bounds these passes is memory, given enough
+// waves: with the rows of a partition walked by one thread per column vector, widths below 2048 left lanes idle and
+// there were 5 waves on a CU at width 1280 (24000 and 12000 rows of 1280 with GELU 95 us in all -> 68, of 276 MB; 1568 x 3072
+// and less: 3 us a layer).
+template <int VN, typename Rows4, typename Row>
+__device__ __forceinline__ void column_sums(float4 (*red)[VN / 4][64], float* __restrict__ partial, int64_t r0, int64_t r1, bool in, const Rows4& rows4,
+                                            const Row& row) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t per = (r1 - r0 + 3) >> 2, w0 = r0 + wave * per, w1 = w0 + per < r1 ? w0 + per : r1;
+  float acc[VN];
+#pragma unroll
+  for (int k = 0; k < VN; ++k) acc[k] = 0.f;
+  if (in) {
+    int64_t r = w0;
+    for (; r + 4 <= w1; r += 4) rows4(r, acc);
+    for (; r < w1; ++r) row(r, acc);
+  }
+  if (wave > 0) {
+#pragma unroll
+    for (int j = 0; j < VN / 4; ++j) red[wave - 1][j][lane] = make_float4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
+  }
+  __syncthreads();
+  if (wave == 0 && in) {
+#pragma unroll
+    for (int j = 0; j < VN / 4; ++j) {
+      float4 t = make_float4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
+#pragma unroll
+      for (int w = 0; w < 3; ++w) { const float4 o = red[w][j][lane]; t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w; }
+      *reinterpret_cast<float4*>(partial + 4 * j) = t;
+    }
+  }
+  __syncthreads();
+}
+
 // dz = da * gelu'(z) and, in the same pass, the partial column sums of dz as stored (the bias
-// gradient of the linear layer that produced z): work item = (row partition p, tile of 256
-// column vectors); a thread owns VN columns and walks the partition's rows in ascending order,
-// exactly as colsum_partial_kernel does over the stored dz, so the sums have the same bits.
+// gradient of the linear layer that produced z): work item = (row partition p, tile of 64
+// column vectors), rows in the order of colsum_partial_kernel over the stored dz, so the sums have the same bits.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void gelu_bwd_colsum_kernel(const T* __restrict__ z, const T* __restrict__ da,
                                                                    T* __restrict__ dz, float* __restrict__ partial,
@@ -406,38 +441,32 @@ __global__ __launch_bounds__(kThreads) void gelu_bwd_colsum_kernel(const T* __re
   constexpr int VN = Vec16<T>::N;
   constexpr bool TAB = std::is_same<T, bf16>::value;
   __shared__ float table[TAB ? ErfTable::kEntries : 1];
+  __shared__ float4 red[3][VN / 4][64];
   if constexpr (TAB) { ErfTable::fill(table, threadIdx.x, kThreads); __syncthreads(); }
   const int64_t items = (int64_t)np * ctiles;
   for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
     const int p = (int)(it / ctiles), ct = (int)(it - (int64_t)p * ctiles);
-    const int64_t c = ((int64_t)ct * kThreads + threadIdx.x) * VN;
-    if (c >= n) continue;
-    float acc[VN];
-#pragma unroll
-    for (int k = 0; k < VN; ++k) acc[k] = 0.f;
+    const int64_t c = ((int64_t)ct * 64 + (threadIdx.x & 63)) * VN;
     const int64_t r0 = (int64_t)p * rp;
-    const int64_t r1 = (r0 + rp < rows) ? r0 + rp : rows;
-    auto one = [&](const Vec16<T>& zv, const Vec16<T>& dv, int64_t r) {
+    auto one = [&](const Vec16<T>& zv, const Vec16<T>& dv, int64_t r, float* acc) {
       Vec16<T> o;
 #pragma unroll
       for (int k = 0; k < VN; ++k) { o.set(k, dv.get(k) * (TAB ? ErfTable::gelu_grad(table, zv.get(k)) : gelu_grad_f(zv.get(k)))); acc[k] += o.get(k); }
       o.store(dz + r * n + c);
     };
-    int64_t r = r0;
-    for (; r + 4 <= r1; r += 4) {          // four rows requested together, taken in ascending order
-      Vec16<T> zv[4], dv[4];
+    column_sums<VN>(red, partial + (int64_t)p * n + c, r0, r0 + rp < rows ? r0 + rp : rows, c < n,
+                    [&](int64_t r, float* acc) {
+                      Vec16<T> zv[4], dv[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) { zv[u].load(z + (r + u) * n + c); dv[u].load(da + (r + u) * n + c); }
+                      for (int u = 0; u < 4; ++u) { zv[u].load(z + (r + u) * n + c); dv[u].load(da + (r + u) * n + c); }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) one(zv[u], dv[u], r + u);
-    }
-    for (; r < r1; ++r) {
-      Vec16<T> zv, dv;
-      zv.load(z + r * n + c); dv.load(da + r * n + c);
-      one(zv, dv, r);
-    }
-#pragma unroll
-    for (int k = 0; k < VN; ++k) partial[(int64_t)p * n + c + k] = acc[k];
+                      for (int u = 0; u < 4; ++u) one(zv[u], dv[u], r + u, acc);
+                    },
+                    [&](int64_t r, float* acc) {
+                      Vec16<T> zv, dv;
+                      zv.load(z + r * n + c); dv.load(da + r * n + c);
+                      one(zv, dv, r, acc);
+                    });
   }
 }
 
@@ -546,35 +575,28 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(const T* __restrict__ X, float* __restrict__ partial,
                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles) {
   constexpr int VN = Vec16<T>::N;
+  __shared__ float4 red[3][VN / 4][64];
   const int64_t items = (int64_t)np * ctiles;
   for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
     const int p = (int)(it / ctiles), ct = (int)(it - (int64_t)p * ctiles);
-    const int64_t c = ((int64_t)ct * kThreads + threadIdx.x) * VN;
-    if (c >= n) continue;
-    float acc[VN];
-#pragma unroll
-    for (int k = 0; k < VN; ++k) acc[k] = 0.f;
+    const int64_t c = ((int64_t)ct * 64 + (threadIdx.x & 63)) * VN;
     const int64_t r0 = (int64_t)p * rp;
-    const int64_t r1 = (r0 + rp < rows) ? r0 + rp : rows;
-    int64_t r = r0;
-    // four rows requested together, added in ascending row order
-    for (; r + 4 <= r1; r += 4) {
-      Vec16<T> v[4];
+    column_sums<VN>(red, partial + (int64_t)p * n + c, r0, r0 + rp < rows ? r0 + rp : rows, c < n,
+                    [&](int64_t r, float* acc) {
+                      Vec16<T> v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u].load(X + (r + u) * n + c);
+                      for (int u = 0; u < 4; ++u) v[u].load(X + (r + u) * n + c);
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+                      for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int k = 0; k < VN; ++k) acc[k] += v[u].get(k);
-    }
-    for (; r < r1; ++r) {
-      Vec16<T> v;
-      v.load(X + r * n + c);
+                        for (int k = 0; k < VN; ++k) acc[k] += v[u].get(k);
+                    },
+                    [&](int64_t r, float* acc) {
+                      Vec16<T> v;
+                      v.load(X + r * n + c);
 #pragma unroll
-      for (int k = 0; k < VN; ++k) acc[k] += v.get(k);
-    }
-#pragma unroll
-    for (int k = 0; k < VN; ++k) partial[(int64_t)p * n + c + k] = acc[k];
+                      for (int k = 0; k < VN; ++k) acc[k] += v.get(k);
+                    });
   }
 }
 
@@ -895,7 +917,7 @@ mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int6
   if (n == 0) return MOSAIC_OK;
   int rp, np;
   col_partition(T, &rp, &np);
-  const int ctiles = (int)ceil_div(n, (int64_t)kThreads * vn__);
+  const int ctiles = (int)ceil_div(n, (int64_t)64 * vn__);
   if (np > 0) {
     const int grid = grid_for(quota, 8, (int64_t)np * ctiles);
     if (dtype == MOSAIC_BF16)
@@ -913,7 +935,7 @@ mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_
   if (n == 0) return MOSAIC_OK;
   int rp, np;
   col_partition(T, &rp, &np);
-  const int ctiles = (int)ceil_div(n, (int64_t)kThreads * vn__);
+  const int ctiles = (int)ceil_div(n, (int64_t)64 * vn__);
   if (np > 0) {
     const int grid = grid_for(quota, 8, (int64_t)np * ctiles);
     if (dtype == MOSAIC_BF16)
