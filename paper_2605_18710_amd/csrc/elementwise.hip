@@ -434,10 +434,13 @@ __device__ __forceinline__ void column_sums(float4 (*red)[VN / 4][64], float* __
 // dz = da * gelu'(z) and, in the same pass, the partial column sums of dz as stored (the bias
 // gradient of the linear layer that produced z): work item = (row partition p, tile of 64
 // column vectors), rows in the order of colsum_partial_kernel over the stored dz, so the sums have the same bits.
-template <typename T>
+// TAPS: da is the gradient [B * lo, 3n] of the gathered input of a three-tap convolution of stride 2 over B x 2 lo rows, and a row's
+// gradient the sum of its taps (ascending) in fp32: row 2t is tap 1 of output t, row 2t + 1 tap 0 of output t + 1 and tap 2 of output t.
+// A pass of its own for that wrote and read 61 MB each for 24000 rows of 1280: 32 + 42 us -> 58.
+template <typename T, bool TAPS>
 __global__ __launch_bounds__(kThreads) void gelu_bwd_colsum_kernel(const T* __restrict__ z, const T* __restrict__ da,
                                                                    T* __restrict__ dz, float* __restrict__ partial,
-                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles) {
+                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles, int lo) {
   constexpr int VN = Vec16<T>::N;
   constexpr bool TAB = std::is_same<T, bf16>::value;
   __shared__ float table[TAB ? ErfTable::kEntries : 1];
@@ -448,25 +451,41 @@ __global__ __launch_bounds__(kThreads) void gelu_bwd_colsum_kernel(const T* __re
     const int p = (int)(it / ctiles), ct = (int)(it - (int64_t)p * ctiles);
     const int64_t c = ((int64_t)ct * 64 + (threadIdx.x & 63)) * VN;
     const int64_t r0 = (int64_t)p * rp;
-    auto one = [&](const Vec16<T>& zv, const Vec16<T>& dv, int64_t r, float* acc) {
+    struct Req { Vec16<T> z, d, d2; bool two; };
+    auto request = [&](int64_t r) {
+      Req q;
+      q.z.load(z + r * n + c);
+      if constexpr (TAPS) {
+        const int64_t t = r >> 1;                                     // output row, over all samples
+        const bool odd = r & 1;
+        q.two = odd && (uint32_t)(t + 1) % (uint32_t)lo != 0;         // the sample's last row has no output after it
+        q.d2.load(da + t * 3 * n + (odd ? 2 * n : n) + c);
+        q.d.load(q.two ? da + (t + 1) * 3 * n + c : da + t * 3 * n + (odd ? 2 * n : n) + c);
+      } else {
+        q.d.load(da + r * n + c);
+      }
+      return q;
+    };
+    auto one = [&](const Req& q, int64_t r, float* acc) {
       Vec16<T> o;
 #pragma unroll
-      for (int k = 0; k < VN; ++k) { o.set(k, dv.get(k) * (TAB ? ErfTable::gelu_grad(table, zv.get(k)) : gelu_grad_f(zv.get(k)))); acc[k] += o.get(k); }
+      for (int k = 0; k < VN; ++k) {
+        float d = q.d.get(k);
+        if constexpr (TAPS) d = q.two ? d + q.d2.get(k) : q.d2.get(k);
+        o.set(k, d * (TAB ? ErfTable::gelu_grad(table, q.z.get(k)) : gelu_grad_f(q.z.get(k))));
+        acc[k] += o.get(k);
+      }
       o.store(dz + r * n + c);
     };
     column_sums<VN>(red, partial + (int64_t)p * n + c, r0, r0 + rp < rows ? r0 + rp : rows, c < n,
                     [&](int64_t r, float* acc) {
-                      Vec16<T> zv[4], dv[4];
+                      Req q[4];
 #pragma unroll
-                      for (int u = 0; u < 4; ++u) { zv[u].load(z + (r + u) * n + c); dv[u].load(da + (r + u) * n + c); }
+                      for (int u = 0; u < 4; ++u) q[u] = request(r + u);
 #pragma unroll
-                      for (int u = 0; u < 4; ++u) one(zv[u], dv[u], r + u, acc);
+                      for (int u = 0; u < 4; ++u) one(q[u], r + u, acc);
                     },
-                    [&](int64_t r, float* acc) {
-                      Vec16<T> zv, dv;
-                      zv.load(z + r * n + c); dv.load(da + r * n + c);
-                      one(zv, dv, r, acc);
-                    });
+                    [&](int64_t r, float* acc) { one(request(r), r, acc); });
   }
 }
 
@@ -930,18 +949,21 @@ mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int6
 }
 
 mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n, const void* z,
-                                     const void* da, void* dz, void* colsum, void* scratch, ColReduceList* later) {
+                                     const void* da, void* dz, void* colsum, void* scratch, ColReduceList* later, int taps_lo) {
   EW_CHECK_VEC(n, dtype);
   if (n == 0) return MOSAIC_OK;
+  if (taps_lo < 0 || (taps_lo > 0 && (T % (2 * (int64_t)taps_lo) || T / 2 >= UINT32_MAX))) MOSAIC_FAIL(MOSAIC_EINVAL, "%lld rows are no whole samples", (long long)T);
   int rp, np;
   col_partition(T, &rp, &np);
   const int ctiles = (int)ceil_div(n, (int64_t)64 * vn__);
   if (np > 0) {
     const int grid = grid_for(quota, 8, (int64_t)np * ctiles);
-    if (dtype == MOSAIC_BF16)
-      gelu_bwd_colsum_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)z, (const bf16*)da, (bf16*)dz, (float*)scratch, T, n, rp, np, ctiles);
-    else
-      gelu_bwd_colsum_kernel<float><<<grid, kThreads, 0, s>>>((const float*)z, (const float*)da, (float*)dz, (float*)scratch, T, n, rp, np, ctiles);
+    auto launch = [&](auto type, auto taps) {
+      typedef decltype(type) E;
+      gelu_bwd_colsum_kernel<E, decltype(taps)::value><<<grid, kThreads, 0, s>>>((const E*)z, (const E*)da, (E*)dz, (float*)scratch, T, n, rp, np, ctiles, taps_lo);
+    };
+    if (dtype == MOSAIC_BF16) { if (taps_lo) launch(bf16{}, std::true_type{}); else launch(bf16{}, std::false_type{}); }
+    else { if (taps_lo) launch(float{}, std::true_type{}); else launch(float{}, std::false_type{}); }
     MOSAIC_LAUNCH_CHECK();
   }
   return col_reduce(s, quota, dtype, {(const float*)scratch, np, n, n, n, INT64_MAX, colsum, nullptr, nullptr}, later);

@@ -78,9 +78,10 @@ mosaic_status launch_gelu_fwd(hipStream_t s, int quota, int dtype, int64_t n, co
 mosaic_status launch_gelu_bwd(hipStream_t s, int quota, int dtype, int64_t n, const void* z,
                               const void* da, void* dz);
 // dz = da * gelu'(z) and colsum[n] = column sums of dz[T,n] as stored (same bits as launch_colsum
-// over dz); scratch: colsum_scratch_bytes(n)
+// over dz); scratch: colsum_scratch_bytes(n).  taps_lo > 0: T rows are samples of 2 * taps_lo positions, the input of a three-tap
+// convolution of stride 2, and da is the gradient [T / 2, 3n] of its gathered input (launch_im2col1d)
 mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n, const void* z,
-                                     const void* da, void* dz, void* colsum, void* scratch, ColReduceList* later = nullptr);
+                                     const void* da, void* dz, void* colsum, void* scratch, ColReduceList* later = nullptr, int taps_lo = 0);
 mosaic_status launch_swiglu_fwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t f,
                                 const void* gu, void* a);
 mosaic_status launch_swiglu_bwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t f,

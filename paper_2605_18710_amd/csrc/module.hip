@@ -45,7 +45,7 @@ struct mosaic_module {
   size_t s_patches;
   size_t s_embed = 0;    // sorted positions and run pieces of the embedding gradient
   size_t s_rope = 0;     // (cos, sin) table of the rotary embedding, when on
-  size_t c_p1 = 0, c_z1 = 0, c_a1 = 0, c_p2 = 0, c_z2 = 0, c_dz2 = 0, c_dp2 = 0, c_da1 = 0, c_dz1 = 0, c_dp1 = 0;   // conv stem
+  size_t c_p1 = 0, c_z1 = 0, c_a1 = 0, c_p2 = 0, c_z2 = 0, c_dz2 = 0, c_dp2 = 0, c_dz1 = 0, c_dp1 = 0;   // conv stem
   // bound buffers
   char* params = nullptr;
   char* grads = nullptr;
@@ -253,7 +253,6 @@ void build_layout(mosaic_module* m) {
     m->c_z2 = take(&cur, T * h * es);
     m->c_dz2 = take(&cur, T * h * es);
     m->c_dp2 = take(&cur, T * 3 * h * es);
-    m->c_da1 = take(&cur, Tin * h * es);
     m->c_dz1 = take(&cur, Tin * h * es);
     m->c_dp1 = take(&cur, Tin * 3 * C * es);
     m->s_colsum = take(&cur, colsum_scratch_bytes(h));
@@ -441,8 +440,7 @@ mosaic_status conv_stem_backward(mosaic_module* m, hipStream_t s, int q, const v
   MOSAIC_TRY(launch_pos_grad(s, q, dt, d.batch, Lo, h, dy, G(m, p.w_o)));
   MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, h, W(m, m->c_z2), dy, W(m, m->c_dz2), G(m, p.b_2), W(m, m->s_colsum2), &sums));
   MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, 3 * h, h, W(m, m->c_p2), W(m, m->c_dz2), P(m, p.w_2), W(m, m->c_dp2), G(m, p.w_2), sk, false));
-  MOSAIC_TRY(launch_col2im1d(s, q, dt, d.batch, L, Lo, h, 2, W(m, m->c_dp2), W(m, m->c_da1)));
-  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, Tin, h, W(m, m->c_z1), W(m, m->c_da1), W(m, m->c_dz1), G(m, p.b_1), W(m, m->s_colsum), &sums));
+  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, Tin, h, W(m, m->c_z1), W(m, m->c_dp2), W(m, m->c_dz1), G(m, p.b_1), W(m, m->s_colsum), &sums, Lo));
   MOSAIC_TRY(launch_col_reduce(s, q, dt, sums));
   if (!dx) {
     MOSAIC_TRY(launch_gemm(s, q, dt, false, false, 3 * C, h, Tin, W(m, m->c_p1), 3 * C, W(m, m->c_dz1), h, G(m, p.w_1), h, nullptr, nullptr, sk));

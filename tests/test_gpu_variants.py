@@ -188,6 +188,12 @@ def test_conv_stem_matches_oracle_and_is_quota_invariant(mb, dtype, B, N, C, h):
     m.destroy()
 
 
+# taps at the ends of a sample: samples of one and two outputs, row partitions that end inside a sample, a column tile partly past the width
+@pytest.mark.parametrize("dtype,B,N,C,h", [("f32", 5, 1, 8, 64), ("bf16", 5, 1, 8, 64), ("bf16", 7, 2, 16, 520), ("bf16", 3, 37, 80, 1032), ("f32", 2, 300, 8, 264)])
+def test_conv_stem_at_sample_ends(mb, dtype, B, N, C, h):
+    test_conv_stem_matches_oracle_and_is_quota_invariant(mb, dtype, B, N, C, h)
+
+
 @pytest.mark.parametrize("dtype,n,master", [("f32", 4 * 1031, False), ("bf16", 8 * 4099, False), ("bf16", 8 * 4099, True), ("bf16", 4 * 4099, True)])
 def test_adamw_steps(mb, dtype, n, master):
     hp = dict(lr=3e-3, beta1=0.9, beta2=0.95, eps=1e-8, weight_decay=0.05)
