@@ -88,9 +88,9 @@ struct LdsTile {
   // rows are rs_bytes apart (row of the tile times the stride, plus the swizzled column)
   unsigned loff[NI];
   int wave_base;
-  __device__ __forceinline__ void init(unsigned rs_bytes) {
+  __device__ __forceinline__ void init(unsigned rs_bytes) { init(rs_bytes, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)); }
+  __device__ __forceinline__ void init(unsigned rs_bytes, int w) {          // w: this wave among the NW that fetch the tile
     const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     wave_base = w * NI * 1024;
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
@@ -841,8 +841,11 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dq_mfma(const bf16* 
 }
 
 // ------------------------------------------------------------ dK, dV at head size 128
-template <int D, int NW>
-__global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dkv_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ dO,
+// PARTS 2: two groups of NW waves share a key tile, each with a ring of its own, take every second query tile, and the first adds
+// the second's sums to its own at the end (dkv_in_parts says when).  Every wave waits for all of its requests in every step, those
+// past the last tile too, so the rings are quiet when the sums pass through them.
+template <int D, int NW, int PARTS>
+__global__ __launch_bounds__(64 * NW * PARTS, 8 / NW / PARTS) void attn_bwd_dkv_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ dO,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
                                                          bf16* __restrict__ dqkv, int B, int N, int H, int Hkv, int causal,
                                                          float scale, int ktiles, int hblk, TileQueueArgs tq) {
@@ -850,18 +853,20 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dkv_mfma(const bf16*
   typedef LdsTile<RS, D, NW> L;
   constexpr int STAGE = 2 * L::BYTES;                      // Q | dO
   constexpr int NST = Ring<NW>::NST, PD = Ring<NW>::PD, KT = 32 * NW, NREQ = 2 * L::NI + 2;
+  constexpr int PART = NST * STAGE + NST * 2 * 64 * 4;      // a group's ring, then its statistics [NST][2][64]: lse, delta
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const lds_byte* smem = (const lds_byte*)smem_raw;        // [NST][STAGE]
+  const int part = PARTS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * NW)) : 0;
+  const lds_byte* smem = (const lds_byte*)smem_raw + part * PART;        // [NST][STAGE]
   const unsigned lds0 = (unsigned)(uintptr_t)smem;
   // the V rows of the owned keys stay in LDS for the whole item (as registers they would
   // push the kernel past its register budget and into scratch)
-  typedef LdsTile<KT, D, NW> LV;
-  const lds_byte* vblk = smem + NST * STAGE;
-  const float* stat = reinterpret_cast<const float*>(smem_raw + NST * STAGE + LV::BYTES);  // [NST][2][64]: lse, delta
+  typedef LdsTile<KT, D, NW * PARTS> LV;
+  const lds_byte* vblk = (const lds_byte*)smem_raw + PARTS * PART;
+  const float* stat = reinterpret_cast<const float*>(smem_raw + part * PART + NST * STAGE);
   L ld, ldo;           // lane offsets for the two row strides: q rows and dO rows
-  ld.init((unsigned)((H + 2 * Hkv) * D * 2));
-  ldo.init((unsigned)(H * D * 2));
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % NW;
+  ld.init((unsigned)((H + 2 * Hkv) * D * 2), __builtin_amdgcn_readfirstlane(wave));
+  ldo.init((unsigned)(H * D * 2), __builtin_amdgcn_readfirstlane(wave));
   const int lr = lane & 31, hb = lane >> 5;
   // rows are [q (H heads) | k (Hkv heads) | v (Hkv heads)]; query head t uses key/value head t / (H/Hkv)
   const int h = H * D, ko = H * D, vo = (H + Hkv) * D, GQ = H / Hkv;
@@ -895,6 +900,13 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dkv_mfma(const bf16*
     const int q_begin = causal ? (k0 / RS) * RS : 0;
     const int ntq = (N - q_begin + RS - 1) / RS;       // query tiles of one head
     const int ntiles = ntq * GQ;                         // streamed for every query head of the group in turn
+    const int steps = PARTS > 1 ? (ntiles + PARTS - 1) / PARTS : ntiles;
+    // first row and blocks left in the head of a tile, moved to the group's next one (and by a tile to the group's first)
+    auto advance = [&](int by, int* row, int* left, int* g) {
+      *row += by * RS;
+      *left -= by;
+      while (*left <= 0) { *row = q_begin - *left * RS; *left += ntq; ++*g; }
+    };
     // per-row statistics of streamed tile `tile` (lse, delta) take the same road as the tiles:
     // one 4-byte request per lane straight into the tile's stage slot.  Every wave issues
     // them (same values, same place) so that all waves count the same number of requests.
@@ -911,36 +923,43 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dkv_mfma(const bf16*
     // Tiles are requested in order and the position of the next one advances by increments
     // instead of a division per request (tile -> head, block): 35 of the loop's 420
     // instructions (0.5 - 1 % of the kernel's time: the loop waits on LDS more than it issues).
-    int rq_t = 0, rq_g = 0, rq_row = q_begin, rq_left = ntq;       // next tile: number, head, first row, blocks left in the head
+    int rq_t = 0, rq_g = 0, rq_row = q_begin, rq_left = ntq;       // next tile: the group's count, head, first row, blocks left in the head
+    if (PARTS > 1 && part > 0) advance(part, &rq_row, &rq_left, &rq_g);
     auto request_next = [&]() {
-      const bool real = rq_t < ntiles;
+      const bool real = PARTS * rq_t + part < ntiles;
       const unsigned nb = lds0 + (unsigned)((rq_t % NST) * STAGE);
       const int row0 = real ? rq_row : N;
       const unsigned col = real ? (unsigned)(rq_g * D * 2) : 0u;
       ld.issue(dq_, (unsigned)row0 * rsb + col, nb);
       ldo.issue(do_, (unsigned)row0 * hsb + col, nb + L::BYTES);
       const unsigned off = (real && lane < RS && rq_row + lane < N) ? (unsigned)(rq_g * N + rq_row + lane) * 4u : 0xFFFFFFF0u;
-      const unsigned dst = lds0 + (unsigned)(NST * STAGE + LV::BYTES + (rq_t % NST) * 2 * 64 * 4);
+      const unsigned dst = lds0 + (unsigned)(NST * STAGE + (rq_t % NST) * 2 * 64 * 4);
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" : : "s"(dst), "v"(off), "s"(dl_) : "m0");
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" : : "s"(dst + 256u), "v"(off), "s"(dd_) : "m0");
       ++rq_t;
-      rq_row += RS;
-      if (--rq_left == 0) { rq_left = ntq; rq_row = q_begin; ++rq_g; }
+      if constexpr (PARTS > 1) {
+        advance(PARTS, &rq_row, &rq_left, &rq_g);
+      } else {
+        rq_row += RS;
+        if (--rq_left == 0) { rq_left = ntq; rq_row = q_begin; ++rq_g; }
+      }
     };
     __syncthreads();
     {
       LV ldv;            // built here so that its per-lane offsets do not live across the tile loop
       ldv.init(rsb);
-      ldv.issue(slice_desc(rowb + vo + kvh * D, N, rs, D), (unsigned)k0 * rsb, lds0 + NST * STAGE);
+      ldv.issue(slice_desc(rowb + vo + kvh * D, N, rs, D), (unsigned)k0 * rsb, (unsigned)(uintptr_t)vblk);
     }
 #pragma unroll
     for (int u = 0; u < PD; ++u) request_next();
     wait_requests<(PD - 1) * NREQ>();
     __syncthreads();
     unsigned entry = 0;
-    const int claim_at = ntiles > 2 * kClaimTilesAhead ? ntiles - 2 * kClaimTilesAhead : 0;   // tiles of 32 rows here
+    const int claim_at = steps > 2 * kClaimTilesAhead ? steps - 2 * kClaimTilesAhead : 0;   // tiles of 32 rows here
     int ib = q_begin, ib_left = ntq;                   // first query row of block t, blocks left in its head
-    for (int t = 0; t < ntiles; ++t) {
+    int ib_g = 0;
+    if (PARTS > 1 && part > 0) advance(part, &ib, &ib_left, &ib_g);
+    for (int t = 0; t < steps; ++t) {
       const int slot = t % NST;
       const lds_byte* qs = smem + slot * STAGE;
       const lds_byte* dos = qs + L::BYTES;
@@ -948,7 +967,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dkv_mfma(const bf16*
       const float* sd = stat + (slot * 2 + 1) * 64;
       request_next();                                  // block t + PD
       if (t == claim_at) entry = tq_claim_ahead(tq, qc);
-      if (!(causal && ib + 31 < j0w) && j0w < N) {            // otherwise every (i, j) here is masked
+      if (!(causal && ib + 31 < j0w) && j0w < N && (PARTS == 1 || PARTS * t + part < ntiles)) {      // otherwise every (i, j) here is masked
         // at head size 128 the accumulators (128 registers), the K fragments (32) and the two
         // score blocks leave no room for operand buffers: reads stay next to their use and the
         // other wave of the SIMD covers their latency (with a lookahead the kernel spilled
@@ -1015,12 +1034,42 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bwd_dkv_mfma(const bf16*
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      ib += RS;
-      if (--ib_left == 0) { ib_left = ntq; ib = q_begin; }
+      if constexpr (PARTS > 1) {
+        advance(PARTS, &ib, &ib_left, &ib_g);
+      } else {
+        ib += RS;
+        if (--ib_left == 0) { ib_left = ntq; ib = q_begin; }
+      }
       wait_requests<(PD - 1) * NREQ>();
       __syncthreads();
     }
-    if (j < N) {
+    if constexpr (PARTS > 1) {
+      // dK, then dV, of the second group through the LDS that the rings no longer need: 16 KB a wave
+      static_assert(PARTS == 2 && NW * NC * 4 * 1024 <= PARTS * PART + LV::BYTES, "no room for a group's sums");
+      float4* const sums = reinterpret_cast<float4*>(smem_raw) + wave * NC * 4 * 64 + lane;
+      auto add = [&](f32x16 (&acc)[NC]) {
+        if (part == 1) {
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) sums[(4 * c + g) * 64] = make_float4(acc[c][4 * g], acc[c][4 * g + 1], acc[c][4 * g + 2], acc[c][4 * g + 3]);
+        }
+        __syncthreads();
+        if (part == 0) {
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              const float4 o = sums[(4 * c + g) * 64];
+              acc[c][4 * g] += o.x; acc[c][4 * g + 1] += o.y; acc[c][4 * g + 2] += o.z; acc[c][4 * g + 3] += o.w;
+            }
+        }
+        __syncthreads();
+      };
+      add(dk);
+      add(dv);
+    }
+    if (j < N && part == 0) {
       bf16* out = dqkv + ((int64_t)b * N + j) * rs + kvh * D;
       // dK rows first, then dV rows: the eight 16-byte pieces that make up a 128-byte line
       // leave in consecutive instructions and meet in the L2 before the line is written out
@@ -1456,6 +1505,18 @@ mosaic_status fwd_t(hipStream_t s, int quota, int B, int N, int H, int Hkv, int 
   return MOSAIC_OK;
 }
 
+// Head size 128: two groups of waves to a key tile where there is at most one tile to a CU, so that the longest tile is what the
+// kernel takes and a wave has its SIMD to itself (2040 cycles a block for 1024 of matrix work).  A function of the shape: the
+// two groups' sums are added, so the bits follow it.  With more tiles than half the CUs a share of the board is slower that
+// way (eight waves in step against two workgroups of four on a CU), so those wait for long items of unequal length: a causal
+// mask and four or more query heads to a key head.  Measured, whole backward pass in us, one group -> two, on 256, 192, 128, 64 CUs:
+//   B4 N1024 H16 Hkv4 causal (128 tiles)  235 226 220 263 -> 181 173 167 235     B1 N1024 H16 causal (128)  83 82 82 82 -> 72 72 72 88
+//   B8 N1024 H16 Hkv4 causal (256)        256 260 269 376 -> 206 234 242 465     B2 N300 H8 (48)  38.4 -> 37.4     B8 N128 H16 causal (128) 28.5 -> 30.0
+//   left alone: B8 N1024 H16 Hkv4 (256)   294 286 307 582 -> 262 347 365 708     B3 N1024 H10 causal (240)  85 85 85 153 -> 75 110 109 181
+inline bool dkv_in_parts(int64_t items, int64_t query_tiles, int group, bool causal) {
+  return query_tiles >= 8 && (items <= 128 || (items <= 256 && causal && group >= 4));
+}
+
 template <int D, int NW>
 mosaic_status bwd_t(hipStream_t s, int quota, int B, int N, int H, int Hkv, int causal, const bf16* qkv, const bf16* O,
                     const float* lse, const bf16* dO, bf16* dqkv, float* delta) {
@@ -1474,21 +1535,27 @@ mosaic_status bwd_t(hipStream_t s, int quota, int B, int N, int H, int Hkv, int 
     MOSAIC_LAUNCH_CHECK();
   }
   {
-    static std::once_flag once;
-    static hipError_t once_rc = hipSuccess;
     TileQueueArgs tq;
     int grid, hb;
     if constexpr (D == 64) {
+      static std::once_flag once;
+      static hipError_t once_rc = hipSuccess;
       constexpr size_t smem = DkvSkew::SMEM;
       MOSAIC_TRY(launch_queued(attn_bwd_dkv_skew, once, once_rc, smem, s, quota, 2, (int64_t)B * Hkv, tiles, causal, &tq, &grid, &hb));
       attn_bwd_dkv_skew<<<grid, 256, smem, s>>>(qkv, dO, lse, delta, dqkv, B, N, H, Hkv, causal, tiles, hb, tq);
       MOSAIC_LAUNCH_CHECK();
     } else {
-      constexpr size_t smem = (size_t)Ring<NW>::NST * 2 * LdsTile<32, D, NW>::BYTES + LdsTile<32 * NW, D, NW>::BYTES +
-                              (size_t)Ring<NW>::NST * 2 * 64 * sizeof(float);
-      MOSAIC_TRY(launch_queued(attn_bwd_dkv_mfma<D, NW>, once, once_rc, smem, s, quota, 8 / NW, (int64_t)B * Hkv, tiles, causal, &tq, &grid, &hb));
-      attn_bwd_dkv_mfma<D, NW><<<grid, 64 * NW, smem, s>>>(qkv, dO, lse, delta, dqkv, B, N, H, Hkv, causal, scale, tiles, hb, tq);
-      MOSAIC_LAUNCH_CHECK();
+      auto launch = [&](auto parts) -> mosaic_status {
+        constexpr int PARTS = decltype(parts)::value;
+        constexpr size_t smem = PARTS * (size_t)Ring<NW>::NST * (2 * LdsTile<32, D, NW>::BYTES + 2 * 64 * sizeof(float)) + LdsTile<32 * NW, D, NW>::BYTES;
+        static std::once_flag once;
+        static hipError_t once_rc = hipSuccess;
+        MOSAIC_TRY(launch_queued(attn_bwd_dkv_mfma<D, NW, PARTS>, once, once_rc, smem, s, quota, 8 / NW / PARTS, (int64_t)B * Hkv, tiles, causal, &tq, &grid, &hb));
+        attn_bwd_dkv_mfma<D, NW, PARTS><<<grid, 64 * NW * PARTS, smem, s>>>(qkv, dO, lse, delta, dqkv, B, N, H, Hkv, causal, scale, tiles, hb, tq);
+        MOSAIC_LAUNCH_CHECK();
+        return MOSAIC_OK;
+      };
+      MOSAIC_TRY(dkv_in_parts((int64_t)B * Hkv * tiles, (int64_t)(H / Hkv) * ceil_div(N, 32), H / Hkv, causal) ? launch(std::integral_constant<int, 2>{}) : launch(std::integral_constant<int, 1>{}));
     }
   }
   return MOSAIC_OK;

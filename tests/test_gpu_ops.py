@@ -186,7 +186,18 @@ def test_attention_bwd_of_64_columns_at_block_edges(mb, B, N, H, Hkv, causal):
     """The dK/dV kernel at head size 64 takes 32-row blocks of 64-row tiles through three stages, with half a block
     always pending: sequences that end in every place of a tile, one tile and more than the ring holds, groups of
     query heads streamed one after the other (the pending half then belongs to the head before), diagonal blocks."""
-    d = 64
+    check_attention_bwd(mb, B, N, H, Hkv, causal, 64)
+
+
+@pytest.mark.parametrize("B,N,H,Hkv,causal", [(1, 224, 1, 1, 0), (1, 225, 1, 1, 0), (1, 257, 2, 2, 1), (2, 289, 1, 1, 1), (2, 33, 8, 1, 1), (1, 130, 6, 2, 1),
+                                              (64, 250, 1, 1, 1), (65, 250, 1, 1, 1), (20, 290, 16, 4, 1), (20, 290, 16, 4, 0), (22, 290, 16, 4, 1)])
+def test_attention_bwd_of_128_columns_by_two_groups(mb, B, N, H, Hkv, causal):
+    """Two groups of waves that take every second query tile of a key tile (both sides of the rule's limits): odd and even
+    numbers of tiles, groups that pass from head to head at different tiles, heads of one tile, a last tile that only one has."""
+    check_attention_bwd(mb, B, N, H, Hkv, causal, 128)
+
+
+def check_attention_bwd(mb, B, N, H, Hkv, causal, d):
     w = (H + 2 * Hkv) * d
     qkv = quantize(synth.normal(500 + N, (B * N, w)), "bf16")
     dO = quantize(synth.normal(501 + N, (B * N, H * d)), "bf16")
