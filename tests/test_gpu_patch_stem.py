@@ -59,3 +59,10 @@ def test_patch_stem_step(dtype, B, g, patch, h, offset):
 @pytest.mark.parametrize("B,g,patch,h", [(300, 1, 14, 256), (130, 2, 16, 640), (40, 7, 14, 520), (9, 24, 14, 1024), (7, 13, 16, 768)])
 def test_position_table_in_the_product(B, g, patch, h):
     test_patch_stem_step("bf16", B, g, patch, h, 0)
+
+
+# rows of patches that pass through LDS and those that do not: the smallest even patch that does and the one below, an odd one, the
+# widest image that fits and the next, an image that starts 2 bytes off
+@pytest.mark.parametrize("B,g,patch,h,offset", [(2, 9, 2, 16, 0), (2, 9, 4, 24, 0), (1, 7, 6, 24, 0), (1, 5, 5, 8, 0), (1, 64, 16, 8, 0), (1, 65, 16, 8, 0), (2, 6, 8, 16, 1)])
+def test_unfolding_by_rows_of_patches(B, g, patch, h, offset):
+    test_patch_stem_step("bf16", B, g, patch, h, offset)
