@@ -255,7 +255,7 @@ struct WorkItem {
 // weight tile's columns are gathered so that a wave holds matching gate and up columns
 // (DmaLoader GU).  The activation is taken of the bf16 value that is stored to C, as the
 // separate pass would.
-constexpr int ACT_NONE = 0, ACT_GELU = 1, ACT_SWIGLU = 2;
+constexpr int ACT_NONE = 0, ACT_GELU = 1, ACT_SWIGLU = 2, ACT_TAPS = 3;
 struct ActArgs {
   int act = ACT_NONE;
   bf16* C2 = nullptr;
@@ -264,9 +264,25 @@ struct ActArgs {
   int gu_f = 0;
   int row_block = 1 << 20;   // tile rows per super-block of the tile order (set by the launcher)
   uint32_t r_rows = 0, r_magic = 0;   // r_rows > 0: R has that many rows, and row r of C gets row r mod r_rows (a position table)
+  // ACT_TAPS: GELU, and C2 is the gathered input [M / 2, 3N] of a three-tap convolution of stride 2 over samples of 2 * r_rows rows
 };
+// Where row r of the activation goes in that input (24000 x 1280 from 240 k-values: product 59 us and gather 35 -> 82): tap 1 of output r / 2 (even rows), or tap 2 of it and tap 0 of the next one; the last row
+// of a sample, which has no next one, clears tap 0 of the sample's first output.  Element offsets of its first column, -1: none.
+struct TapRows { int64_t first, second; bool zero; };
 // r mod r_rows with r_magic = 2^32 / r_rows + 1: exact as long as r * r_rows < 2^32 (checked by the launcher)
 __device__ __forceinline__ int table_row(int r, uint32_t r_rows, uint32_t r_magic) { return r - (int)(__umulhi((uint32_t)r, r_magic) * r_rows); }
+__device__ __forceinline__ TapRows tap_rows(int r, int M, int64_t n, uint32_t lo, uint32_t magic) {
+  const int t = r >> 1;
+  TapRows o = {-1, -1, false};
+  if (r < M) {
+    o.first = (3 * (int64_t)t + 1 + (r & 1)) * n;
+    if (r & 1) {
+      o.zero = table_row(t + 1, lo, magic) == 0;
+      o.second = 3 * (int64_t)(o.zero ? t + 1 - (int)lo : t + 1) * n;
+    }
+  }
+  return o;
+}
 
 // PIECES_CHAINED: one workgroup takes the pieces of its tile one after the other and adds them in registers,
 // in the order and with the additions of the second kernel: the same bits as PIECES_APART, no scratch.
@@ -705,7 +721,7 @@ __device__ __forceinline__ void gemm_bf16_body(
     unsigned char* patch = smem + free_stage + wave * 4096;
     // stages of 64-deep K-tiles have room for a table of erf behind the patches (ErfTable; the same bits): 7 erff to
     // fill it where the tile has 64 values a thread
-    constexpr bool TABLE = ACT == ACT_GELU && NWM * NWN * 4096 + ErfTable::kEntries * 4 <= STAGE;
+    constexpr bool TABLE = (ACT == ACT_GELU || ACT == ACT_TAPS) && NWM * NWN * 4096 + ErfTable::kEntries * 4 <= STAGE;
     float* const erf_table = reinterpret_cast<float*>(smem + free_stage + NWM * NWN * 4096);
     if constexpr (TABLE) {
       ErfTable::fill(erf_table, threadIdx.x, NT);
@@ -743,7 +759,8 @@ __device__ __forceinline__ void gemm_bf16_body(
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     // patch (32 rows of 128 bytes, chunks XOR-swizzled) -> rows of `rsrc`, 8 rows per instruction
-    auto drain = [&](int i, __amdgpu_buffer_rsrc_t rsrc, int64_t ld, int col, int ncols) {
+    auto drain = [&](int i, __amdgpu_buffer_rsrc_t rsrc, int64_t ld, int col, int ncols, auto second_) {
+      constexpr bool TAPS = decltype(second_)::value && ACT == ACT_TAPS;
       u32x4 v[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -753,7 +770,14 @@ __device__ __forceinline__ void gemm_bf16_body(
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int row = it.m0 + wm + 32 * i + (ln >> 3) + 8 * q;
-        const unsigned off = (col >= 0 && col < ncols) ? (unsigned)(((int64_t)row * ld + col) * 2) : kOob;
+        const bool in = col >= 0 && col < ncols;
+        if constexpr (TAPS) {
+          const TapRows t = tap_rows(row, M, N, aa.r_rows, aa.r_magic);
+          __builtin_amdgcn_raw_buffer_store_b128(v[q], rsrc, (int)(in && t.first >= 0 ? (unsigned)((t.first + col) * 2) : kOob), 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(t.zero ? u32x4{0u, 0u, 0u, 0u} : v[q], rsrc, (int)(in && t.second >= 0 ? (unsigned)((t.second + col) * 2) : kOob), 0, 0);
+          continue;
+        }
+        const unsigned off = in ? (unsigned)(((int64_t)row * ld + col) * 2) : kOob;
         __builtin_amdgcn_raw_buffer_store_b128(v[q], rsrc, (int)off, 0, 0);
       }
     };
@@ -769,7 +793,7 @@ __device__ __forceinline__ void gemm_bf16_body(
           *reinterpret_cast<bf16x4*>(patch + wr + (((4 * j + g) ^ wsx) << 4)) = o;
         }
       patch_sync();
-      drain(i, rc, ldc, zcol, N);
+      drain(i, rc, ldc, zcol, N, std::false_type{});
       patch_sync();
       if constexpr (GU) {
 #pragma unroll
@@ -791,7 +815,7 @@ __device__ __forceinline__ void gemm_bf16_body(
           }
       }
       patch_sync();
-      drain(i, rc2, aa.ldc2, acol, a_n);
+      drain(i, rc2, aa.ldc2, acol, a_n, std::true_type{});
       patch_sync();
     }
 #pragma unroll
@@ -1000,13 +1024,13 @@ struct W4Args {
   int64_t lda, ldb, ldc, ldc2;
   uint32_t a_bytes, b_bytes, c_bytes, c2_bytes;
   int tiles_m, tiles_n, tile_begin, tile_count, row_block, gu_f;
-  uint32_t r_rows, r_magic;        // W4_TABLE: see ActArgs
+  uint32_t r_rows, r_magic;        // W4_TABLE, W4_TAPS: see ActArgs
 };
-enum { W4_PLAIN, W4_BIAS, W4_RES, W4_GELU, W4_SWIGLU, W4_TABLE };
+enum { W4_PLAIN, W4_BIAS, W4_RES, W4_GELU, W4_SWIGLU, W4_TABLE, W4_TAPS };
 constexpr int kW4Stage = 2 * 256 * 64 * 2;                         // both operands of a K-tile
 constexpr int kW4Pitch = 68;                                       // floats per row of the epilogue's patch: 16 rows of 64
 constexpr int kW4Patch = 4 * 16 * kW4Pitch * 4;
-constexpr int w4_lds(int epi) { return 2 * kW4Stage + kW4Patch + (epi == W4_GELU ? ErfTable::kEntries * 4 : 0); }
+constexpr int w4_lds(int epi) { return 2 * kW4Stage + kW4Patch + (epi == W4_GELU || epi == W4_TAPS ? ErfTable::kEntries * 4 : 0); }
 
 // One operand: what a lane requests of a K-tile, and where its fragments are.
 template <bool KC, bool GU, int NF = 8>
@@ -1127,7 +1151,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
   // 256 values of a tile to a thread: seven erff to fill the table instead of 256 (the epilogue of 12000 x 1280 x 5120
   // takes 10 us of 150; with erff in it, four waves a CU, 83 of 239)
   float* const erf_table = reinterpret_cast<float*>(smem + 2 * kW4Stage + kW4Patch);
-  if constexpr (EPI == W4_GELU) {
+  if constexpr (EPI == W4_GELU || EPI == W4_TAPS) {
     ErfTable::fill(erf_table, threadIdx.x, 256);
     __syncthreads();
   }
@@ -1297,11 +1321,18 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(W4Args p, TileQueu
               o[e] = (bf16)x;
             }
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rc, off(row, col, p.ldc, ok), 0, 0);
-            if constexpr (EPI == W4_GELU) {
+            if constexpr (EPI == W4_GELU || EPI == W4_TAPS) {
               bf16x8 a2;
 #pragma unroll
               for (int e = 0; e < 8; ++e) a2[e] = (bf16)ErfTable::gelu(erf_table, (float)o[e]);     // of the value as stored
-              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a2), rc2, off(row, col, p.ldc2, ok), 0, 0);
+              const u32x4 av = __builtin_bit_cast(u32x4, a2);
+              if constexpr (EPI == W4_TAPS) {
+                const TapRows t = tap_rows(row, p.M, p.N, p.r_rows, p.r_magic);
+                __builtin_amdgcn_raw_buffer_store_b128(av, rc2, ok && t.first >= 0 ? (int)(unsigned)((t.first + col) * 2) : (int)kOob, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(t.zero ? u32x4{0u, 0u, 0u, 0u} : av, rc2, ok && t.second >= 0 ? (int)(unsigned)((t.second + col) * 2) : (int)kOob, 0, 0);
+              } else {
+                __builtin_amdgcn_raw_buffer_store_b128(av, rc2, off(row, col, p.ldc2, ok), 0, 0);
+              }
             }
           }
         }
@@ -1448,6 +1479,7 @@ mosaic_status launch_w4(hipStream_t s, int quota, int M, int N, int K, const bf1
   p.row_block = row_block_for(K, M, 32 * MI);
   if constexpr (A_KC && !B_KC) {
     if (aa.act == ACT_GELU) return launch_w4_epi<A_KC, B_KC, W4_GELU, MI>(s, quota, p);
+    if (aa.act == ACT_TAPS) return launch_w4_epi<A_KC, B_KC, W4_TAPS, MI>(s, quota, p);
     if (aa.act == ACT_SWIGLU) return launch_w4_epi<A_KC, B_KC, W4_SWIGLU, MI>(s, quota, p);
     if (bias && !R) return launch_w4_epi<A_KC, B_KC, W4_BIAS, MI>(s, quota, p);
     if (R && aa.r_rows) return launch_w4_epi<A_KC, B_KC, W4_TABLE, MI>(s, quota, p);
@@ -1610,6 +1642,9 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
       if (aa.act == ACT_GELU)
         return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC, PIECES_NONE, ACT_GELU>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
                                                                         c_bytes, 1, 0, nullptr, sub, tile_begin, tile_count, aa);
+      if (aa.act == ACT_TAPS)
+        return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC, PIECES_NONE, ACT_TAPS>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
+                                                                        c_bytes, 1, 0, nullptr, sub, tile_begin, tile_count, aa);
       if (aa.act == ACT_SWIGLU)
         return launch_mfma<TB, TB, 2, WN_, A_KC, B_KC, PIECES_NONE, ACT_SWIGLU>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
                                                                           c_bytes, 1, 0, nullptr, sub, tile_begin, tile_count, aa);
@@ -1644,7 +1679,7 @@ size_t gemm_splitk_scratch_bytes(int64_t M, int64_t N, int64_t K) {
 static mosaic_status launch_gemm_impl(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int64_t M, int64_t N,
                           int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
                           int64_t ldc, const void* bias, const void* R, void* splitk_scratch,
-                          int64_t b_rows, int act, void* C2, int64_t ldc2, bool* fused, int64_t r_rows = 0) {
+                          int64_t b_rows, int act, void* C2, int64_t ldc2, bool* fused, int64_t r_rows = 0, int64_t taps_lo = 0) {
   if (fused) *fused = false;
   if (b_rows < 0 || b_kc) b_rows = K;
   if (M < 0 || N < 0 || K < 0) MOSAIC_FAIL(MOSAIC_EINVAL, "negative GEMM size");
@@ -1666,14 +1701,14 @@ static mosaic_status launch_gemm_impl(hipStream_t s, int quota, int dtype, bool 
     bf16* c = (bf16*)C;
     if (a_kc && !b_kc) {
       ActArgs aa;
-      if (r_rows > 0) { aa.r_rows = (uint32_t)r_rows; aa.r_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)r_rows + 1); }
+      if (const int64_t d = std::max(r_rows, taps_lo)) { aa.r_rows = (uint32_t)d; aa.r_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)d + 1); }
       if (fused && C2 && !R && (uintptr_t)C2 % 16 == 0 && ldc2 % 8 == 0) {
         const int64_t n2 = act == MOSAIC_SWIGLU ? N / 2 : N;
-        const int64_t c2_ext = ((M - 1) * ldc2 + n2) * 2;
+        const int64_t c2_ext = taps_lo > 0 ? M / 2 * 3 * N * 2 : ((M - 1) * ldc2 + n2) * 2;
         // gate and up halves must be whole quarter tiles wide: a tile then never straddles the halves
         const bool ok = c2_ext < lim && (act == MOSAIC_GELU || (act == MOSAIC_SWIGLU && N % 256 == 0));
         if (ok) {
-          aa.act = act == MOSAIC_GELU ? ACT_GELU : ACT_SWIGLU;
+          aa.act = taps_lo > 0 ? ACT_TAPS : act == MOSAIC_GELU ? ACT_GELU : ACT_SWIGLU;
           aa.C2 = (bf16*)C2; aa.ldc2 = ldc2; aa.c2_bytes = (uint32_t)c2_ext;
           aa.gu_f = act == MOSAIC_SWIGLU ? (int)(N / 2) : 0;
           *fused = true;
@@ -1720,6 +1755,18 @@ mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act
   if (act == MOSAIC_SWIGLU) return launch_swiglu_fwd(s, quota, dtype, T, na, Z, Aout);
   if (act == MOSAIC_GELU_TANH) return launch_gelu_tanh_fwd(s, quota, dtype, T * n, Z, Aout);
   return launch_gelu_fwd(s, quota, dtype, T * n, Z, Aout);
+}
+
+mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t lo, int64_t n, int64_t k, const void* X, const void* W,
+                                   const void* bias, void* Z, void* A, void* P) {
+  const int64_t T = 2 * B * lo;
+  const bool in_range = lo >= 2 && (T / 2 + 256) * lo < (int64_t)1 << 32;
+  bool fused = false;
+  MOSAIC_TRY(launch_gemm_impl(s, quota, dtype, true, false, T, n, k, X, k, W, n, Z, n, bias, nullptr, nullptr, -1, MOSAIC_GELU, P, 3 * n,
+                              in_range ? &fused : nullptr, 0, in_range ? lo : 0));
+  if (fused || T == 0 || n == 0) return MOSAIC_OK;
+  MOSAIC_TRY(launch_gelu_fwd(s, quota, dtype, T * n, Z, A));
+  return launch_im2col1d(s, quota, dtype, B, (int)(2 * lo), (int)lo, (int)n, 2, A, P);
 }
 
 namespace {

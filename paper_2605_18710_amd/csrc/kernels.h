@@ -27,6 +27,11 @@ mosaic_status launch_embed_fwd(hipStream_t s, int quota, int dtype, int64_t B, i
 // otherwise the elementwise kernel follows the product.
 mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act, int64_t T, int64_t k, int64_t n,
                                     const void* X, const void* W, const void* bias, void* Z, void* A);
+// Z = X W + bias over samples of 2 lo rows and P [B lo, 3n] = the gathered input of a three-tap convolution of stride 2 over gelu(Z)
+// (launch_im2col1d), written by the epilogue
+// where the bf16 matrix-core kernel takes the product, else through A [2 B lo, n]; the same bits.
+mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t lo, int64_t n, int64_t k, const void* X, const void* W,
+                                   const void* bias, void* Z, void* A, void* P);
 // Bytes of fp32 scratch the weight-gradient form wants for a deterministic split of a long
 // contraction over few output tiles (0 when no split is used for this shape).
 // dW[k,n] = X^T dY and dX[T,k] = dY W^T, dense rows; one launch where that is the faster way, else two, the input gradient's

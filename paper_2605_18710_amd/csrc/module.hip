@@ -421,13 +421,10 @@ mosaic_status conv_stem_forward(mosaic_module* m, hipStream_t s, int q, const vo
   const mosaic_module_desc& d = m->d;
   const LayerParams& p = m->lp[0];
   const int dt = d.dtype, C = d.in_dim, h = d.hidden, Lo = d.seq, L = 2 * d.seq;
-  const int64_t T = m->T, Tin = 2 * T;
   MOSAIC_TRY(launch_im2col1d(s, q, dt, d.batch, L, L, C, 1, x, W(m, m->c_p1)));
-  MOSAIC_TRY(launch_linear_act_fwd(s, q, dt, MOSAIC_GELU, Tin, 3 * C, h, W(m, m->c_p1), P(m, p.w_1), P(m, p.b_1), W(m, m->c_z1), W(m, m->c_a1)));
-  MOSAIC_TRY(launch_im2col1d(s, q, dt, d.batch, L, Lo, h, 2, W(m, m->c_a1), W(m, m->c_p2)));
-  MOSAIC_TRY(launch_linear_act_fwd(s, q, dt, MOSAIC_GELU, T, 3 * h, h, W(m, m->c_p2), P(m, p.w_2), P(m, p.b_2), W(m, m->c_z2), y));
-  MOSAIC_TRY(launch_add_pos(s, q, dt, d.batch, Lo, h, P(m, p.w_o), y));
-  return MOSAIC_OK;
+  MOSAIC_TRY(launch_gelu_taps_fwd(s, q, dt, d.batch, Lo, h, 3 * C, W(m, m->c_p1), P(m, p.w_1), P(m, p.b_1), W(m, m->c_z1), W(m, m->c_a1), W(m, m->c_p2)));
+  MOSAIC_TRY(launch_linear_act_fwd(s, q, dt, MOSAIC_GELU, m->T, 3 * h, h, W(m, m->c_p2), P(m, p.w_2), P(m, p.b_2), W(m, m->c_z2), y));
+  return launch_add_pos(s, q, dt, d.batch, Lo, h, P(m, p.w_o), y);
 }
 
 mosaic_status conv_stem_backward(mosaic_module* m, hipStream_t s, int q, const void* dy, void* dx) {

@@ -188,8 +188,10 @@ def test_conv_stem_matches_oracle_and_is_quota_invariant(mb, dtype, B, N, C, h):
     m.destroy()
 
 
-# taps at the ends of a sample: samples of one and two outputs, row partitions that end inside a sample, a column tile partly past the width
-@pytest.mark.parametrize("dtype,B,N,C,h", [("f32", 5, 1, 8, 64), ("bf16", 5, 1, 8, 64), ("bf16", 7, 2, 16, 520), ("bf16", 3, 37, 80, 1032), ("f32", 2, 300, 8, 264)])
+# taps at the ends of a sample: samples of one and two outputs, row partitions that end inside a sample, a column tile partly past the width,
+# products that four waves, eight waves and small tiles take (the share of the CUs decides) and that write the gathered rows themselves
+@pytest.mark.parametrize("dtype,B,N,C,h", [("f32", 5, 1, 8, 64), ("bf16", 5, 1, 8, 64), ("bf16", 7, 2, 16, 520), ("bf16", 3, 37, 80, 1032), ("f32", 2, 300, 8, 264),
+                                                ("bf16", 3, 400, 128, 512), ("bf16", 5, 203, 80, 512)])
 def test_conv_stem_at_sample_ends(mb, dtype, B, N, C, h):
     test_conv_stem_matches_oracle_and_is_quota_invariant(mb, dtype, B, N, C, h)
 
