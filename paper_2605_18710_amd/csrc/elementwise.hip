@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kThreads) void norm_bwd_dx_kernel(
 // rows r0+w, r0+w+4, ... in ascending order, holds the row of x and dy in registers, writes
 // dx and adds dy*xhat (and dy) into per-lane column accumulators.  The four waves'
 // accumulators are added in wave order through LDS, one 64-lane column slab at a time, and
-// land in scratch[p][2][h]; reduce_partials_kernel adds the partitions in a fixed order.
+// land in scratch[p][2][h]; col_reduce_kernel adds the partitions in a fixed order.
 // CS: the column sums of the values written to dx (as stored, after rounding) are formed the
 // same way in a third slab, scratch[p][3][h]: dx is the output gradient of the linear layer in
 // front of the residual branch, so this is that layer's bias gradient, without another pass.
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kThreads) void norm_bwd_fused_kernel(
 
 // dgamma / dbeta partial column sums: work item = (row partition p, tile of 256 column
 // vectors); a thread owns VN columns and walks the partition's rows in ascending order.
-// scratch[p][2][h]; the partitions are added in a fixed order by reduce_partials_kernel.
+// scratch[p][2][h]; the partitions are added in a fixed order by col_reduce_kernel.
 template <typename T, int NORM>
 __global__ __launch_bounds__(kThreads) void norm_colgrad_partial_kernel(
     const T* __restrict__ x, const float* __restrict__ stats, const T* __restrict__ dy,
