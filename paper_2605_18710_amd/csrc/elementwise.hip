@@ -395,98 +395,110 @@ __global__ __launch_bounds__(kThreads) void gelu_bwd_kernel(const T* __restrict_
   }
 }
 
-// Column sums over a row partition by one workgroup: its waves take a quarter of the rows each, in ascending order, and the
-// four sums are added in the order of the rows.  Lane l of every wave owns the VN columns from c on; `row(r)` adds
-// row r into its argument.  rows4(r) adds four rows, requested together.  What bounds these passes is memory, given enough
-// waves: with the rows of a partition walked by one thread per column vector, widths below 2048 left lanes idle and
-// there were 5 waves on a CU at width 1280 (24000 and 12000 rows of 1280 with GELU 95 us in all -> 68, of 276 MB; 1568 x 3072
-// and less: 3 us a layer).
-template <int VN, typename Rows4, typename Row>
-__device__ __forceinline__ void column_sums(float4 (*red)[VN / 4][64], float* __restrict__ partial, int64_t r0, int64_t r1, bool in, const Rows4& rows4,
-                                            const Row& row) {
+// Partial column sums of a row partition: a lane owns V columns and adds the rows in ascending order, ONCE of them requested
+// together (request(row, column)) and then used (use(what was requested, row, column, sums)).  A wave takes 64 * V columns
+// of a partition; with QUARTERS (colsum_quarters says where) the four waves of a workgroup take a quarter of its rows each, and
+// the four sums are added in the order of the rows.
+template <int V, int ONCE, bool QUARTERS, typename Request, typename Use>
+__device__ __forceinline__ void column_sums(int64_t rows, int64_t n, int rp, int np, int ctiles, float* __restrict__ partial, const Request& request,
+                                            const Use& use) {
+  static_assert(!QUARTERS || V % 4 == 0, "the quarters' sums pass through LDS in pieces of four");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t per = (r1 - r0 + 3) >> 2, w0 = r0 + wave * per, w1 = w0 + per < r1 ? w0 + per : r1;
-  float acc[VN];
+  const int64_t items = (int64_t)np * ctiles, step = QUARTERS ? gridDim.x : (int64_t)gridDim.x * kWaves;
+  for (int64_t it = QUARTERS ? blockIdx.x : (int64_t)blockIdx.x * kWaves + wave; it < items; it += step) {
+    const int p = (int)(it / ctiles), ct = (int)(it - (int64_t)p * ctiles);
+    const int64_t c = ((int64_t)ct * 64 + lane) * V;
+    int64_t r = (int64_t)p * rp, r1 = r + rp < rows ? r + rp : rows;
+    if constexpr (QUARTERS) {
+      const int64_t per = (r1 - r + 3) >> 2;
+      r += wave * per;
+      r1 = r + per < r1 ? r + per : r1;
+    }
+    float acc[V] = {};
+    if (c < n) {
+      decltype(request(r, c)) q[ONCE];
+      for (; r + ONCE <= r1; r += ONCE) {
 #pragma unroll
-  for (int k = 0; k < VN; ++k) acc[k] = 0.f;
-  if (in) {
-    int64_t r = w0;
-    for (; r + 4 <= w1; r += 4) rows4(r, acc);
-    for (; r < w1; ++r) row(r, acc);
-  }
-  if (wave > 0) {
+        for (int u = 0; u < ONCE; ++u) q[u] = request(r + u, c);
 #pragma unroll
-    for (int j = 0; j < VN / 4; ++j) red[wave - 1][j][lane] = make_float4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
-  }
-  __syncthreads();
-  if (wave == 0 && in) {
+        for (int u = 0; u < ONCE; ++u) use(q[u], r + u, c, acc);
+      }
+      if (r < r1) {
 #pragma unroll
-    for (int j = 0; j < VN / 4; ++j) {
-      float4 t = make_float4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
+        for (int u = 0; u < ONCE - 1; ++u) if (r + u < r1) q[u] = request(r + u, c);
 #pragma unroll
-      for (int w = 0; w < 3; ++w) { const float4 o = red[w][j][lane]; t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w; }
-      *reinterpret_cast<float4*>(partial + 4 * j) = t;
+        for (int u = 0; u < ONCE - 1; ++u) if (r + u < r1) use(q[u], r + u, c, acc);
+      }
+    }
+    if constexpr (QUARTERS) {
+      __shared__ float4 red[3][V / 4][64];
+      if (wave > 0) {
+#pragma unroll
+        for (int j = 0; j < V / 4; ++j) red[wave - 1][j][lane] = make_float4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
+      }
+      __syncthreads();
+      if (wave == 0) {
+#pragma unroll
+        for (int j = 0; j < V / 4; ++j)
+#pragma unroll
+          for (int w = 0; w < 3; ++w) { const float4 o = red[w][j][lane]; acc[4 * j] += o.x; acc[4 * j + 1] += o.y; acc[4 * j + 2] += o.z; acc[4 * j + 3] += o.w; }
+      }
+      __syncthreads();
+    }
+    if (c < n && (!QUARTERS || wave == 0)) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) partial[(int64_t)p * n + c + k] = acc[k];
     }
   }
-  __syncthreads();
 }
 
 // dz = da * gelu'(z) and, in the same pass, the partial column sums of dz as stored (the bias
-// gradient of the linear layer that produced z): work item = (row partition p, tile of 64
-// column vectors), rows in the order of colsum_partial_kernel over the stored dz, so the sums have the same bits.
+// gradient of the linear layer that produced z), in the order of launch_colsum over the stored dz, so the sums have the same bits.
+// Bound by memory where waves are many, by the chain of one wave where they are few: 8 bytes a lane and four rows at once in the first
+// case, 4 bytes and eight rows, so twice the waves, in the second (the rule is at the launch; both add in the same order).
+// Microseconds, final reduction included, on 256 CUs (on 64), bf16: partitions walked by one thread per 16 bytes of a row / by
+// four waves, a quarter each / this: 1568 x 3072 16.5 (30.7) / 13.6 (24.6) / 13.2 (23.4), 4608 x 4096 27.6 (67.1) / 30.0 (77.5) / 27.5 (66.6),
+// 9216 x 4096 44.7 (121.8) / 46.8 (127.1) / 45.0 (119.6), 12000 x 5120 90.9 (212) / 83.6 (201) / 83.6 (196), 24000 x 1280 55.8 (139) / 41.6 (117) / 39.3 (98).
 // TAPS: da is the gradient [B * lo, 3n] of the gathered input of a three-tap convolution of stride 2 over B x 2 lo rows, and a row's
 // gradient the sum of its taps (ascending) in fp32: row 2t is tap 1 of output t, row 2t + 1 tap 0 of output t + 1 and tap 2 of output t.
-// A pass of its own for that wrote and read 61 MB each for 24000 rows of 1280: 32 + 42 us -> 58.
-template <typename T, bool TAPS>
+// A pass of its own for that wrote and read 61 MB each for 24000 rows of 1280: 32 + 42 us -> 58, and with one multiplication for the
+// address of a row's taps 46 (on 64 CUs 143 -> 114).
+template <typename T, int V, int ONCE, bool QUARTERS, bool TAPS>
 __global__ __launch_bounds__(kThreads) void gelu_bwd_colsum_kernel(const T* __restrict__ z, const T* __restrict__ da,
                                                                    T* __restrict__ dz, float* __restrict__ partial,
-                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles, int lo) {
-  constexpr int VN = Vec16<T>::N;
+                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles, int lo, uint64_t m_lo) {
+  typedef typename Pack<T, V>::type vec;
   constexpr bool TAB = std::is_same<T, bf16>::value;
   __shared__ float table[TAB ? ErfTable::kEntries : 1];
-  __shared__ float4 red[3][VN / 4][64];
   if constexpr (TAB) { ErfTable::fill(table, threadIdx.x, kThreads); __syncthreads(); }
-  const int64_t items = (int64_t)np * ctiles;
-  for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-    const int p = (int)(it / ctiles), ct = (int)(it - (int64_t)p * ctiles);
-    const int64_t c = ((int64_t)ct * 64 + (threadIdx.x & 63)) * VN;
-    const int64_t r0 = (int64_t)p * rp;
-    struct Req { Vec16<T> z, d, d2; bool two; };
-    auto request = [&](int64_t r) {
-      Req q;
-      q.z.load(z + r * n + c);
-      if constexpr (TAPS) {
-        const int64_t t = r >> 1;                                     // output row, over all samples
-        const bool odd = r & 1;
-        q.two = odd && (uint32_t)(t + 1) % (uint32_t)lo != 0;         // the sample's last row has no output after it
-        q.d2.load(da + t * 3 * n + (odd ? 2 * n : n) + c);
-        q.d.load(q.two ? da + (t + 1) * 3 * n + c : da + t * 3 * n + (odd ? 2 * n : n) + c);
-      } else {
-        q.d.load(da + r * n + c);
-      }
-      return q;
-    };
-    auto one = [&](const Req& q, int64_t r, float* acc) {
-      Vec16<T> o;
+  struct Req { vec z, d, d2; bool two; };
+  column_sums<V, ONCE, QUARTERS>(rows, n, rp, np, ctiles, partial, [&](int64_t r, int64_t c) {
+    Req q;
+    q.z = *reinterpret_cast<const vec*>(z + r * n + c);
+    if constexpr (TAPS) {
+      const int64_t t = r >> 1, odd = r & 1;                        // t: output row, over all samples
+      // the sample's last row has no output after it; m_lo = 2^64 / lo, rounded up: exact for 32-bit numbers (lo 1: every row)
+      q.two = odd && lo > 1 && (uint32_t)(t + 1) != (uint32_t)__umul64hi((uint64_t)(t + 1), m_lo) * (uint32_t)lo;
+      const T* at = da + (3 * t + 1 + odd) * n;
+      q.d2 = *reinterpret_cast<const vec*>(at + c);
+      q.d = *reinterpret_cast<const vec*>((q.two ? at + n : at) + c);
+    } else {
+      q.d = *reinterpret_cast<const vec*>(da + r * n + c);
+    }
+    return q;
+  }, [&](const Req& q, int64_t r, int64_t c, float (&acc)[V]) {
+#pragma clang fp contract(off)          // what is stored is added: a product rounded to T, not one fused with the addition
+    vec o;
 #pragma unroll
-      for (int k = 0; k < VN; ++k) {
-        float d = q.d.get(k);
-        if constexpr (TAPS) d = q.two ? d + q.d2.get(k) : q.d2.get(k);
-        o.set(k, d * (TAB ? ErfTable::gelu_grad(table, q.z.get(k)) : gelu_grad_f(q.z.get(k))));
-        acc[k] += o.get(k);
-      }
-      o.store(dz + r * n + c);
-    };
-    column_sums<VN>(red, partial + (int64_t)p * n + c, r0, r0 + rp < rows ? r0 + rp : rows, c < n,
-                    [&](int64_t r, float* acc) {
-                      Req q[4];
-#pragma unroll
-                      for (int u = 0; u < 4; ++u) q[u] = request(r + u);
-#pragma unroll
-                      for (int u = 0; u < 4; ++u) one(q[u], r + u, acc);
-                    },
-                    [&](int64_t r, float* acc) { one(request(r), r, acc); });
-  }
+    for (int k = 0; k < V; ++k) {
+      const float zk = pack_get<T, V>(q.z, k);
+      float d = pack_get<T, V>(q.d, k);
+      if constexpr (TAPS) d = q.two ? d + pack_get<T, V>(q.d2, k) : pack_get<T, V>(q.d2, k);
+      pack_set<T, V>(o, k, d * (TAB ? ErfTable::gelu_grad(table, zk) : gelu_grad_f(zk)));
+      acc[k] += pack_get<T, V>(o, k);
+    }
+    *reinterpret_cast<vec*>(dz + r * n + c) = o;
+  });
 }
 
 template <typename T>
@@ -593,29 +605,55 @@ constexpr int kNormFusedMaxNV = 8;   // LayerNorm; RMSNorm (one sum per column) 
 template <typename T>
 __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(const T* __restrict__ X, float* __restrict__ partial,
                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles) {
-  constexpr int VN = Vec16<T>::N;
-  __shared__ float4 red[3][VN / 4][64];
+  constexpr int V = Vec16<T>::N;
+  typedef typename Pack<T, V>::type vec;
+  column_sums<V, 8, false>(rows, n, rp, np, ctiles, partial, [&](int64_t r, int64_t c) { return *reinterpret_cast<const vec*>(X + r * n + c); },
+                           [&](const vec& x, int64_t, int64_t, float (&acc)[V]) {
+#pragma unroll
+                             for (int k = 0; k < V; ++k) acc[k] += pack_get<T, V>(x, k);
+                           });
+}
+
+// The sums of column_sums with QUARTERS, by one wave: two rows of each quarter are requested together.  32768 x 2048 on 256, 128,
+// 64 CUs: four waves 28.8 36.4 34.1 us, this 27.5 26.7 31.4; 24000 x 4096 37.9 38.3 50.3 -> 38.2 37.9 46.4; 32768 x 4096 46.8 48 79 -> 51.5 59 76.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void colsum_quarters_kernel(const T* __restrict__ X, float* __restrict__ partial,
+                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles) {
+  constexpr int V = Vec16<T>::N;
   const int64_t items = (int64_t)np * ctiles;
-  for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+  for (int64_t it = (int64_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); it < items; it += (int64_t)gridDim.x * kWaves) {
     const int p = (int)(it / ctiles), ct = (int)(it - (int64_t)p * ctiles);
-    const int64_t c = ((int64_t)ct * 64 + (threadIdx.x & 63)) * VN;
+    const unsigned c = (unsigned)(ct * 64 + (threadIdx.x & 63)) * V;
     const int64_t r0 = (int64_t)p * rp;
-    column_sums<VN>(red, partial + (int64_t)p * n + c, r0, r0 + rp < rows ? r0 + rp : rows, c < n,
-                    [&](int64_t r, float* acc) {
-                      Vec16<T> v[4];
+    if (c >= n) continue;
+    const int count = (int)(r0 + rp < rows ? rp : rows - r0), per = (count + 3) >> 2, whole = max(count - 3 * per, 0) & ~1;
+    const T* x = X + r0 * n;
+    float acc[4][V] = {};
+    Vec16<T> v[4][2];
+    for (int i = 0; i < whole; i += 2, x += 2 * n) {
 #pragma unroll
-                      for (int u = 0; u < 4; ++u) v[u].load(X + (r + u) * n + c);
+      for (int k = 0; k < 4; ++k)
 #pragma unroll
-                      for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 2; ++u) v[k][u].load(x + (k * per + u) * n + c);
 #pragma unroll
-                        for (int k = 0; k < VN; ++k) acc[k] += v[u].get(k);
-                    },
-                    [&](int64_t r, float* acc) {
-                      Vec16<T> v;
-                      v.load(X + r * n + c);
+      for (int k = 0; k < 4; ++k)
 #pragma unroll
-                      for (int k = 0; k < VN; ++k) acc[k] += v.get(k);
-                    });
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int e = 0; e < V; ++e) acc[k][e] += v[k][u].get(e);
+    }
+    for (int i = whole; i < per; ++i, x += n) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) if (k * per + i < count) v[k][0].load(x + k * per * n + c);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k * per + i < count) {
+#pragma unroll
+          for (int e = 0; e < V; ++e) acc[k][e] += v[k][0].get(e);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) partial[(int64_t)p * n + c + e] = acc[0][e] + acc[1][e] + acc[2][e] + acc[3][e];
   }
 }
 
@@ -972,19 +1010,28 @@ mosaic_status launch_mse(hipStream_t s, int quota, int dtype, int64_t n, const v
 
 size_t colsum_scratch_bytes(int64_t n) { return (size_t)kColsumMaxParts * (size_t)n * sizeof(float); }
 
+// Long partitions of wide rows are summed in quarters.  A function of the shape: the bits follow it.  Partitions then start so far
+// apart, often by a power of two, that waves which walk them in step meet in the same parts of memory; four waves in four places of a
+// partition do not.  GELU's pass in us on 256 CUs (on 64), ascending / in quarters: 16384 x 4096 94.2 (208) / 84.1 (209), 32768 x 4096
+// 179 (405) / 168 (400), 24000 x 4096 131 (303) / 126 (305), 16384 x 3072 61.0 (158) / 60.2 (160); not so where rows are short or
+// partitions are: 32768 x 1024 44.8 (106) / 45.2 (105), 24000 x 1280 39.3 (98) / 41.6 (117), 12000 x 3840 (24 rows) 55 (148) / 59.5 (162).
+static bool colsum_quarters(int rp, int64_t n) { return rp >= 28 && n >= 2048; }
+
 mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n, const void* X, void* out,
                             void* scratch, ColReduceList* later) {
   EW_CHECK_VEC(n, dtype);
   if (n == 0) return MOSAIC_OK;
   int rp, np;
   col_partition(T, &rp, &np);
-  const int ctiles = (int)ceil_div(n, (int64_t)64 * vn__);
   if (np > 0) {
-    const int grid = grid_for(quota, 8, (int64_t)np * ctiles);
-    if (dtype == MOSAIC_BF16)
-      colsum_partial_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)X, (float*)scratch, T, n, rp, np, ctiles);
-    else
-      colsum_partial_kernel<float><<<grid, kThreads, 0, s>>>((const float*)X, (float*)scratch, T, n, rp, np, ctiles);
+    const int ctiles = (int)ceil_div(n, (int64_t)64 * vn__);
+    const int grid = grid_for(quota, 8, ceil_div((int64_t)np * ctiles, kWaves));
+    auto launch = [&](auto type) {
+      typedef decltype(type) E;
+      if (colsum_quarters(rp, n)) colsum_quarters_kernel<E><<<grid, kThreads, 0, s>>>((const E*)X, (float*)scratch, T, n, rp, np, ctiles);
+      else colsum_partial_kernel<E><<<grid, kThreads, 0, s>>>((const E*)X, (float*)scratch, T, n, rp, np, ctiles);
+    };
+    if (dtype == MOSAIC_BF16) launch(bf16{}); else launch(float{});
     MOSAIC_LAUNCH_CHECK();
   }
   return col_reduce(s, quota, dtype, {(const float*)scratch, np, n, n, n, INT64_MAX, out, nullptr, nullptr}, later);
@@ -997,15 +1044,31 @@ mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_
   if (taps_lo < 0 || (taps_lo > 0 && (T % (2 * (int64_t)taps_lo) || T / 2 >= UINT32_MAX))) MOSAIC_FAIL(MOSAIC_EINVAL, "%lld rows are no whole samples", (long long)T);
   int rp, np;
   col_partition(T, &rp, &np);
-  const int ctiles = (int)ceil_div(n, (int64_t)64 * vn__);
   if (np > 0) {
-    const int grid = grid_for(quota, 8, (int64_t)np * ctiles);
-    auto launch = [&](auto type, auto taps) {
+    const uint64_t m_lo = taps_lo > 1 ? ~(uint64_t)0 / (uint64_t)taps_lo + 1 : 0;
+    auto launch = [&](auto type, auto bytes, auto once, auto quarters, auto taps) {
       typedef decltype(type) E;
-      gelu_bwd_colsum_kernel<E, decltype(taps)::value><<<grid, kThreads, 0, s>>>((const E*)z, (const E*)da, (E*)dz, (float*)scratch, T, n, rp, np, ctiles, taps_lo);
+      constexpr int V = decltype(bytes)::value / sizeof(E);
+      constexpr bool Q = decltype(quarters)::value;
+      const int ctiles = (int)ceil_div(n, (int64_t)64 * V), grid = grid_for(quota, 8, ceil_div((int64_t)np * ctiles, Q ? 1 : kWaves));
+      gelu_bwd_colsum_kernel<E, V, decltype(once)::value, Q, decltype(taps)::value><<<grid, kThreads, 0, s>>>((const E*)z, (const E*)da, (E*)dz, (float*)scratch, T, n, rp, np, ctiles, taps_lo, m_lo);
     };
-    if (dtype == MOSAIC_BF16) { if (taps_lo) launch(bf16{}, std::true_type{}); else launch(bf16{}, std::false_type{}); }
-    else { if (taps_lo) launch(float{}, std::true_type{}); else launch(float{}, std::false_type{}); }
+    // Waves on a CU with 8 bytes a lane.  Measured with 8 bytes / 4 bytes a lane, us, waves in brackets: partitions of a whole number of
+    // eights 1568 x 3072 14.3 / 13.2 (9), 17.1 / 16.5 (18), 24.1 / 23.4 (37); 12000 x 3840 58.1 / 54 (30), 80.6 / 84 (60); others
+    // 4608 x 3072 22.3 / 22.8 (24), 31.0 / 33.1 (48), 4608 x 4096 27.5 / 28.1 (32), 24000 x 1280 44 / 39 (10), 58.2 / 55.9 (20), 98.1 / 99.6 (40);
+    // taps 24000 x 1280 57 / 46 (10), 73 / 80 (20), 6748 x 768 24.9 / 24.8 (11), 33.2 / 37.6 (23).
+    const double waves = (double)np * (double)ceil_div(n, (int64_t)512 / (int64_t)dtype_size(dtype)) / quota;
+    const bool many = waves >= (taps_lo ? 16 : rp % 8 ? 24 : 48), quarters = colsum_quarters(rp, n);
+    typedef std::integral_constant<int, 4> Four;
+    typedef std::integral_constant<int, 8> Eight;
+    typedef std::integral_constant<int, 16> Sixteen;
+    auto of_type = [&](auto type, auto taps) {
+      if (quarters) launch(type, Sixteen{}, Four{}, std::true_type{}, taps);
+      else if (many) launch(type, Eight{}, Four{}, std::false_type{}, taps);
+      else launch(type, Four{}, std::conditional_t<decltype(taps)::value, Four, Eight>{}, std::false_type{}, taps);
+    };
+    auto of_taps = [&](auto type) { if (taps_lo) of_type(type, std::true_type{}); else of_type(type, std::false_type{}); };
+    if (dtype == MOSAIC_BF16) of_taps(bf16{}); else of_taps(float{});
     MOSAIC_LAUNCH_CHECK();
   }
   return col_reduce(s, quota, dtype, {(const float*)scratch, np, n, n, n, INT64_MAX, colsum, nullptr, nullptr}, later);
