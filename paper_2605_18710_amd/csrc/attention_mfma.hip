@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
+#include "attention_plan.h"
 #include "kernels.h"
 #include "tile_queue.h"
 
@@ -216,7 +217,7 @@ __device__ __forceinline__ int acc_row(int r, int hb) { return 8 * (r >> 2) + 4 
 // (longest-first list scheduling).  The host sizes a block to about two rounds of an XCD's
 // workgroups, so several tiles of every head of the block are in flight together.  Without a
 // mask all tiles cost the same and hb = 1 keeps a head's tiles together.
-// Under static rounds (equal-cost tiles, or too few items for the queue to pay) hb = 1 and
+// Under static rounds (equal-cost tiles, or too few items for the queue to pay: attention_plan.h) hb = 1 and
 // `mirror` flips the position inside the head on odd rounds when a round covers whole heads,
 // so that a workgroup that drew a heavy tile next draws a light one.
 __device__ __forceinline__ void attn_item(int item, int heads, int tiles, int hb, bool heavy_last, bool mirror, int* head, int* tile) {
@@ -853,6 +854,7 @@ __global__ __launch_bounds__(64 * NW * PARTS, 8 / NW / PARTS) void attn_bwd_dkv_
   typedef LdsTile<RS, D, NW> L;
   constexpr int STAGE = 2 * L::BYTES;                      // Q | dO
   constexpr int NST = Ring<NW>::NST, PD = Ring<NW>::PD, KT = 32 * NW, NREQ = 2 * L::NI + 2;
+  static_assert(PARTS == 1 || PD == 1, "a request may be on its way when the sums pass through the rings");
   constexpr int PART = NST * STAGE + NST * 2 * 64 * 4;      // a group's ring, then its statistics [NST][2][64]: lse, delta
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int part = PARTS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * NW)) : 0;
@@ -1470,16 +1472,9 @@ mosaic_status launch_queued(K kern, std::once_flag& once, hipError_t& once_rc, s
     once_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   });
   MOSAIC_HIP(once_rc);
-  // heads per block: about two rounds of an XCD's workgroups under a causal mask, else one head
-  // The queue pays once every workgroup draws several items (tiles of unequal cost under a
-  // causal mask, ragged last tiles, and heads that stay together on an XCD: measured 5-10 %
-  // on the audio encoder's full attention at 32 and 64 CUs, 25-40 % on causal rows of 4096);
-  // with up to three rounds static rounds do as well without the claims.
-  const int64_t resident = (int64_t)tile_queue_sure_cus(quota) * wg_per_cu;
-  const bool prefer_queue = heads * tiles > 3 * resident;
-  const int per_xcd = (int)((resident + 7) / 8);
-  *hb = causal ? (int)std::min<int64_t>(std::max<int64_t>(1, (2 * per_xcd + tiles - 1) / tiles), std::max<int64_t>(1, heads / 8)) : 1;
-  MOSAIC_TRY(tile_queue_plan(s, quota, wg_per_cu, heads * tiles, *hb * tiles, prefer_queue, tq, grid));
+  const AttnDeal deal = attn_deal(heads, tiles, (int64_t)tile_queue_sure_cus(quota) * wg_per_cu, causal, wg_per_cu == 1);
+  *hb = deal.hb;
+  MOSAIC_TRY(tile_queue_plan(s, quota, wg_per_cu, heads * tiles, deal.unit, deal.queue, tq, grid));
   if (tq->mode == TQ_ROUNDS) *hb = 1;
   return MOSAIC_OK;
 }
@@ -1503,18 +1498,6 @@ mosaic_status fwd_t(hipStream_t s, int quota, int B, int N, int H, int Hkv, int 
   kern<<<grid, 64 * NW, smem, s>>>(qkv, O, lse, B, N, H, Hkv, causal, kLog2e / sqrtf((float)D), qtiles, hb, tq);
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;
-}
-
-// Head size 128: two groups of waves to a key tile where there is at most one tile to a CU, so that the longest tile is what the
-// kernel takes and a wave has its SIMD to itself (2040 cycles a block for 1024 of matrix work).  A function of the shape: the
-// two groups' sums are added, so the bits follow it.  With more tiles than half the CUs a share of the board is slower that
-// way (eight waves in step against two workgroups of four on a CU), so those wait for long items of unequal length: a causal
-// mask and four or more query heads to a key head.  Measured, whole backward pass in us, one group -> two, on 256, 192, 128, 64 CUs:
-//   B4 N1024 H16 Hkv4 causal (128 tiles)  235 226 220 263 -> 181 173 167 235     B1 N1024 H16 causal (128)  83 82 82 82 -> 72 72 72 88
-//   B8 N1024 H16 Hkv4 causal (256)        256 260 269 376 -> 206 234 242 465     B2 N300 H8 (48)  38.4 -> 37.4     B8 N128 H16 causal (128) 28.5 -> 30.0
-//   left alone: B8 N1024 H16 Hkv4 (256)   294 286 307 582 -> 262 347 365 708     B3 N1024 H10 causal (240)  85 85 85 153 -> 75 110 109 181
-inline bool dkv_in_parts(int64_t items, int64_t query_tiles, int group, bool causal) {
-  return query_tiles >= 8 && (items <= 128 || (items <= 256 && causal && group >= 4));
 }
 
 template <int D, int NW>

@@ -190,10 +190,12 @@ def test_attention_bwd_of_64_columns_at_block_edges(mb, B, N, H, Hkv, causal):
 
 
 @pytest.mark.parametrize("B,N,H,Hkv,causal", [(1, 224, 1, 1, 0), (1, 225, 1, 1, 0), (1, 257, 2, 2, 1), (2, 289, 1, 1, 1), (2, 33, 8, 1, 1), (1, 130, 6, 2, 1),
-                                              (64, 250, 1, 1, 1), (65, 250, 1, 1, 1), (20, 290, 16, 4, 1), (20, 290, 16, 4, 0), (22, 290, 16, 4, 1)])
+                                              (64, 250, 1, 1, 1), (65, 250, 1, 1, 1), (20, 290, 16, 4, 1), (20, 290, 16, 4, 0), (22, 290, 16, 4, 1),
+                                              (5, 250, 8, 2, 1), (3, 300, 4, 2, 1), (2, 600, 1, 1, 1), (4, 260, 8, 4, 1)])
 def test_attention_bwd_of_128_columns_by_two_groups(mb, B, N, H, Hkv, causal):
     """Two groups of waves that take every second query tile of a key tile (both sides of the rule's limits): odd and even
-    numbers of tiles, groups that pass from head to head at different tiles, heads of one tile, a last tile that only one has."""
+    numbers of tiles, groups that pass from head to head at different tiles, heads of one tile, a last tile that only one has; two
+    rounds of tiles and part of a third on few CUs, dealt longest first (heads that fill the eight lists and heads that do not)."""
     check_attention_bwd(mb, B, N, H, Hkv, causal, 128)
 
 
