@@ -454,9 +454,11 @@ __global__ __launch_bounds__(kThreads) void embed_join_kernel(const int32_t* __r
 
 // Small calls: the workgroup that owns a table row walks all positions, 256 at a time, gathers
 // those that hold its id into a list in LDS in ascending order (waves in order, lanes in order, by ballot
-// and prefix count) and adds the listed rows of dy in that order, all columns of a row in registers.
-constexpr int kScanPositions = 96, kScanCols = 32;   // columns per thread: rows of up to 8192 elements
-template <typename T>
+// and prefix count) and adds the listed rows of dy in that order, all columns of a row in registers: COLS of them a thread, ROWS
+// rows requested together.  Bound by an id's rows, one batch after the other: T 128 h 64, one id for all, 58 us row by row with 32
+// columns a thread, now 24; with the frequencies of running text T 128 h 512 V 1000 13.6 -> 7.5, T 96 h 64 V 32 11.9 -> 5.6.
+constexpr int kScanPositions = 128, kScanCols = 32;  // columns per thread: rows of up to 8192 elements
+template <typename T, int COLS, int ROWS>
 __global__ __launch_bounds__(kThreads) void embed_scan_kernel(const T* __restrict__ dy, const int32_t* __restrict__ ids,
                                                               const int32_t* __restrict__ counts, T* __restrict__ dtable,
                                                               int B, int N, int n_img, int h, int vocab) {
@@ -483,20 +485,29 @@ __global__ __launch_bounds__(kThreads) void embed_scan_kernel(const T* __restric
       n_list += all;
       __syncthreads();                                 // list entries visible; wave_hits free for the next chunk
     }
-    float acc[kScanCols];
+    float acc[COLS] = {};
+    for (int e = 0; e < n_list; e += ROWS) {
+      float v[ROWS][COLS] = {};
 #pragma unroll
-    for (int j = 0; j < kScanCols; ++j) acc[j] = 0.f;
-    for (int e = 0; e < n_list; ++e) {
-      const T* row = dy + (int64_t)list[e] * h;
+      for (int u = 0; u < ROWS; ++u)
+        if (e + u < n_list) {
+          const T* row = dy + (int64_t)list[e + u] * h;
 #pragma unroll
-      for (int j = 0; j < kScanCols; ++j) {
-        const int c = j * kThreads + threadIdx.x;
-        if (c < h) acc[j] += to_f32(row[c]);
-      }
+          for (int j = 0; j < COLS; ++j) {
+            const int c = j * kThreads + threadIdx.x;
+            if (c < h) v[u][j] = to_f32(row[c]);
+          }
+        }
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u)
+        if (e + u < n_list) {
+#pragma unroll
+          for (int j = 0; j < COLS; ++j) acc[j] += v[u][j];
+        }
     }
     __syncthreads();                                   // everybody is done with the list
 #pragma unroll
-    for (int j = 0; j < kScanCols; ++j) {
+    for (int j = 0; j < COLS; ++j) {
       const int c = j * kThreads + threadIdx.x;
       if (c < h) dtable[(int64_t)v * h + c] = from_f32<T>(acc[j]);
     }
@@ -504,14 +515,17 @@ __global__ __launch_bounds__(kThreads) void embed_scan_kernel(const T* __restric
 }
 
 // One launch of the scan against three of the sort, whatever the CUs (the orders of the sums
-// differ, so the rule is one of the shape).  The scan takes a pass over the ids per table row and the rows of an id one
-// after the other: it loses with many rows and with many positions to an id.  Measured
-// on 256 CUs, bf16, ids with the frequencies of running text, scan / sort in us:
-//   T 16 h 64 V 32  5.0 / 12.2      T 64 h 64 V 16  10.7 / 12.7      h 512 V 255  5.4 / 12.9     h 2048 V 8000  14.0 / 16.0
-//   T 64 h 64 V 16000  17.9 / 13.5  T 96 h 128 V 64  11.1 / 12.5     V 1000  6.2 / 14.5         h 2048 V 4000  16.2 / 15.6
-//   T 128 h 64 V 32  15.3 / 12.6    h 512 V 1000  13.7 / 14.2        T 256 h 1024 V 4000  22.6 / 15.4
+// differ, so the rule is one of the shape).  The scan takes a pass over the ids per table row and the rows of an id in batches one
+// after the other: it loses with many rows, on few CUs first, and with many positions to an id.  Measured on 256 CUs (on 64, on 32),
+// bf16, ids with the frequencies of running text, scan / sort in us:
+//   T 16 h 64 V 32  4.0 / 12.2     T 96 h 512 V 1000  5.4 (5.9, 6.8) / 14.5      h 2048 V 4000  13.4 (17.4, 24.0) / 15.6
+//   T 112 h 64 V 128  6.3 / 11.7   h 64 V 2000  4.0 (5.1, 7.9) / 13.4            V 4000  6.8 (17.8, 32.4) row by row / 12.9 (12.5, 12.9)
+//   T 128 h 512 V 1000  7.5 (7.9, 8.9) / 12.9 (12.7, 15.3)   V 2000  6.7 (6.4, 8.4) / 12.9   h 2048 V 1000  21.7 row by row / 13.7
+// and with one id for all positions: T 96 h 64  18.5 / 12;  T 128 h 64  24 / 12, h 400  36 / 12;  T 200 h 64  37 / 14, h 400  55 / 13, which is
+// why more positions are sorted although T 160 h 64 V 1000 takes the scan 5.6 and the sort 13.2.
 inline bool scan_is_faster(int64_t T, int64_t h, int64_t vocab) {
-  return vocab <= 8192 && T <= kScanPositions && T <= 4 * vocab && T * h <= 1 << 18 && h <= kScanCols * kThreads;
+  if (T <= 96) return vocab <= 8192 && T <= 4 * vocab && T * h <= 1 << 18 && h <= kScanCols * kThreads;
+  return T <= kScanPositions && T < vocab && vocab <= 2048 && T * h <= 1 << 16;
 }
 
 struct EmbedScratch {
@@ -547,7 +561,10 @@ mosaic_status embed_grad_t(hipStream_t s, int quota, int B, int N, int n_img, in
   const int total = B * N;
   if (scan_is_faster(total, h, vocab)) {
     MOSAIC_TRY((split_img<T, V>(s, quota, B, N, n_img, h, dy, counts, d_img)));
-    embed_scan_kernel<T><<<grid_for(quota, 8, vocab), kThreads, 0, s>>>(dy, ids, counts, dtable, B, N, n_img, h, vocab);
+    const int grid = grid_for(quota, 8, vocab);
+    if (h <= 2 * kThreads) embed_scan_kernel<T, 2, 8><<<grid, kThreads, 0, s>>>(dy, ids, counts, dtable, B, N, n_img, h, vocab);
+    else if (h <= 8 * kThreads) embed_scan_kernel<T, 8, 4><<<grid, kThreads, 0, s>>>(dy, ids, counts, dtable, B, N, n_img, h, vocab);
+    else embed_scan_kernel<T, kScanCols, 1><<<grid, kThreads, 0, s>>>(dy, ids, counts, dtable, B, N, n_img, h, vocab);
     MOSAIC_LAUNCH_CHECK();
     return MOSAIC_OK;
   }

@@ -1,8 +1,8 @@
-"""Text stem at the sizes where the sort by id, its segments and the access width can go wrong:
-position counts around a chunk (2048) and a segment (16), vocabularies on both sides of a digit
-(8 bits), one id for everything, no text at all, widths of one and several column tiles, and
-tensors that do not start on a 16-byte boundary; and both sides of the rule by which small calls
-scan the ids instead of sorting them."""
+"""Text stem at the sizes where the embedding gradient's three ways can go wrong, on both sides of the rules between
+them.  The scan of small calls (up to 128 positions): widths and positions at its limits.  The sort by one
+workgroup (up to 8192 positions, keys and positions in 32 bits): rounds of 1024 positions, digits of 8 bits.  The sort in several
+launches (more positions, or more bits): chunks of 2048 positions.  The sums after either sort: segments of 16 positions, one id
+for everything, no text at all, widths of one and several column tiles, tensors that do not start on a 16-byte boundary."""
 import numpy as np
 import pytest
 
@@ -97,3 +97,38 @@ ONE_SORT = [(1, 97, 0, 64, 30, "mixed", 0), (1, 97, 0, 64, 8192, "mixed", 0), (1
 @pytest.mark.parametrize("B,N,n_img,h,vocab,how,offset", ONE_SORT)
 def test_sort_in_one_launch(dtype, B, N, n_img, h, vocab, how, offset):
     test_text_stem_step(dtype, B, N, n_img, h, vocab, how, offset)
+
+
+# the scan, for more than 96 positions: its limits of positions, vocabulary and width, and the widths at which a thread takes more columns
+SCAN = [(1, 128, 0, 512, 2048, "mixed", 0), (1, 128, 0, 512, 2049, "mixed", 0), (1, 128, 3, 520, 500, "mixed", 0), (1, 129, 0, 64, 300, "mixed", 0), (1, 97, 0, 64, 97, "mixed", 0),
+        (2, 49, 5, 64, 99, "mixed", 1), (1, 120, 0, 520, 1000, "one", 0), (1, 97, 0, 8, 2047, "one", 0), (1, 64, 0, 2048, 40, "mixed", 0), (1, 63, 0, 2056, 40, "mixed", 0),
+        (1, 33, 0, 8184, 16, "mixed", 0)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,N,n_img,h,vocab,how,offset", SCAN)
+def test_scan(dtype, B, N, n_img, h, vocab, how, offset):
+    test_text_stem_step(dtype, B, N, n_img, h, vocab, how, offset)
+
+
+@pytest.mark.parametrize("T,h,vocab", [(128, 512, 1000), (97, 64, 128), (100, 600, 2048), (96, 2048, 100), (30, 8192, 50)])
+def test_small_calls_add_the_rows_of_an_id_in_ascending_order(T, h, vocab):
+    """fp32, every position the same id: the scan has one chain of sums, the sort pieces of 16 positions."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_18710_amd import binding as mb
+    stem = mb.Module(dict(kind="text_stem", batch=1, seq=T, hidden=h, vocab=vocab, n_img=0), "f32")
+    stem.bind_ids(torch.full((T,), 7, dtype=torch.int32, device="cuda"))
+    g = to_dev(synth.normal(4900 + T, (T, h)), "f32")
+    y = torch.empty_like(g)
+    stem.grads.fill_(float("nan"))
+    stem.forward(256, None, g, y)
+    stem.backward(256, None, g, None)
+    torch.cuda.synchronize()
+    acc = torch.zeros(h, device="cuda")
+    for t in range(T):
+        acc = acc + g[t]
+    got = stem.grads[:vocab * h].view(vocab, h)
+    assert torch.equal(got[7].view(torch.int32), acc.view(torch.int32))
+    assert not bool(got[:7].any()) and not bool(got[8:].any())
+    stem.destroy()
