@@ -132,3 +132,54 @@ def test_small_calls_add_the_rows_of_an_id_in_ascending_order(T, h, vocab):
     assert torch.equal(got[7].view(torch.int32), acc.view(torch.int32))
     assert not bool(got[:7].any()) and not bool(got[8:].any())
     stem.destroy()
+
+
+# sample lengths and the most image tokens; the counts go from none to that many.  Positions that the scan, the sort by one workgroup and
+# the sort in several launches take; of the last: whole chunks, a last chunk of 1 and of 2047 positions, keys of one, two and three digits
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,N,n_img,h,vocab", [(3, 31, 12, 64, 40), (2, 64, 64, 8, 1000), (4, 200, 70, 264, 300), (8, 1024, 196, 64, 70), (1, 8193, 100, 8, 254), (5, 2048, 300, 72, 255),
+                                               (3, 3413, 500, 24, 256), (3, 3413, 0, 8, 65536), (2, 5121, 77, 16, 70000), (4, 4096, 196, 40, 3)])
+def test_text_stem_with_image_counts(dtype, B, N, n_img, h, vocab):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_18710_amd import binding as mb
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator().manual_seed(N + vocab)
+    ids = torch.randint(0, vocab, (B, N), generator=gen, dtype=torch.int32)
+    ids[:, ::3] = vocab - 1
+    counts = torch.tensor([n_img * b // max(1, B - 1) for b in range(B)], dtype=torch.int32)
+    img, dy = torch.randn(B * n_img, h, generator=gen).to(td).cuda(), torch.randn(B * N, h, generator=gen).to(td).cuda()
+    stem = mb.Module(dict(kind="text_stem", batch=B, seq=N, hidden=h, vocab=vocab, n_img=n_img), dtype)
+    try:
+        stem.params[:vocab * h].copy_(torch.randn(vocab * h, generator=gen).to(td))
+        stem.bind_ids(ids.cuda())
+        stem.bind_image_counts(counts.cuda())
+        text = torch.arange(N)[None, :] >= counts[:, None]                       # [B, N]
+        sel, at = text.reshape(-1).cuda(), ids[text].long().cuda()
+        ref_y = torch.empty_like(dy)
+        ref_y[sel] = stem.params[:vocab * h].view(vocab, h)[at]
+        ref_y.view(B, N, h)[:, :n_img][~text[:, :n_img].cuda()] = img.view(B, n_img, h)[~text[:, :n_img].cuda()]
+        ref_img = torch.where(text[:, :n_img, None].cuda(), torch.zeros((), dtype=td, device="cuda"), dy.view(B, N, h)[:, :n_img])
+        ref = torch.zeros(vocab, h, dtype=torch.float64, device="cuda").index_add_(0, at, dy[sel].double())
+        snaps = []
+        for quota in (256, 24):
+            stem.grads.fill_(float("nan"))
+            y, dx = torch.full_like(dy, float("nan")), torch.full_like(img, float("nan"))
+            stem.forward(quota, None, img if n_img else dy, y)
+            stem.backward(quota, None, dy, dx if n_img else None)
+            torch.cuda.synchronize()
+            assert torch.equal(y, ref_y) and torch.equal(dx.view(B, n_img, h), ref_img)
+            snaps.append(stem.grads[:vocab * h].clone())
+        assert torch.equal(snaps[0].view(torch.uint8), snaps[1].view(torch.uint8))
+        got = snaps[0].view(vocab, h).double()
+        assert bool((got[torch.bincount(at, minlength=vocab) == 0] == 0).all()), "rows that nobody used"
+        # one rounding of a sum of up to 16000 terms in fp32
+        assert_close(got.cpu().numpy(), ref.cpu().numpy(), dtype, "table gradient", roundings=4)
+    finally:
+        stem.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,N,n_img,h,vocab,how,offset", [(1, 33, 0, 8192, 50, "mixed", 0), (1, 32, 0, 8192, 50, "mixed", 0), (1, 8193, 0, 64, 254, "one", 0), (3, 3413, 2, 264, 257, "mixed", 1)])
+def test_limits_of_the_scan_and_of_the_one_workgroup(dtype, B, N, n_img, h, vocab, how, offset):
+    test_text_stem_step(dtype, B, N, n_img, h, vocab, how, offset)
