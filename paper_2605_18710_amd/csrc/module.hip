@@ -45,7 +45,7 @@ struct mosaic_module {
   size_t s_patches;
   size_t s_embed = 0;    // sorted positions and run pieces of the embedding gradient
   size_t s_rope = 0;     // (cos, sin) table of the rotary embedding, when on
-  size_t c_p1 = 0, c_z1 = 0, c_a1 = 0, c_p2 = 0, c_z2 = 0, c_dz2 = 0, c_dp2 = 0, c_dz1 = 0, c_dp1 = 0;   // conv stem
+  size_t c_p1 = 0, c_z1 = 0, c_p2 = 0, c_z2 = 0, c_dz2 = 0, c_dp2 = 0, c_dz1 = 0, c_dp1 = 0;   // conv stem
   // bound buffers
   char* params = nullptr;
   char* grads = nullptr;
@@ -248,7 +248,6 @@ void build_layout(mosaic_module* m) {
     m->lp.push_back(q);
     m->c_p1 = take(&cur, Tin * 3 * C * es);
     m->c_z1 = take(&cur, Tin * h * es);
-    m->c_a1 = take(&cur, Tin * h * es);
     m->c_p2 = take(&cur, T * 3 * h * es);
     m->c_z2 = take(&cur, T * h * es);
     m->c_dz2 = take(&cur, T * h * es);
@@ -422,7 +421,8 @@ mosaic_status conv_stem_forward(mosaic_module* m, hipStream_t s, int q, const vo
   const LayerParams& p = m->lp[0];
   const int dt = d.dtype, C = d.in_dim, h = d.hidden, Lo = d.seq, L = 2 * d.seq;
   MOSAIC_TRY(launch_im2col1d(s, q, dt, d.batch, L, L, C, 1, x, W(m, m->c_p1)));
-  MOSAIC_TRY(launch_gelu_taps_fwd(s, q, dt, d.batch, Lo, h, 3 * C, W(m, m->c_p1), P(m, p.w_1), P(m, p.b_1), W(m, m->c_z1), W(m, m->c_a1), W(m, m->c_p2)));
+  // where the activation has to be stored, it goes to what the backward pass writes last
+  MOSAIC_TRY(launch_gelu_taps_fwd(s, q, dt, d.batch, Lo, h, 3 * C, W(m, m->c_p1), P(m, p.w_1), P(m, p.b_1), W(m, m->c_z1), W(m, m->c_dz1), W(m, m->c_p2)));
   MOSAIC_TRY(launch_linear_act_fwd(s, q, dt, MOSAIC_GELU, m->T, 3 * h, h, W(m, m->c_p2), P(m, p.w_2), P(m, p.b_2), W(m, m->c_z2), y));
   return launch_add_pos(s, q, dt, d.batch, Lo, h, P(m, p.w_o), y);
 }

@@ -187,6 +187,21 @@ def test_encoder_layout_has_biases_and_betas():
     l.mosaic_module_destroy(h)
 
 
+def test_workspace_of_the_audio_stem_holds_what_it_keeps_and_no_more():
+    """Saved gathers and pre-activations and the gradients of the same; the activation of the first convolution, which the
+    product's epilogue gathers and only a fallback stores, has no room of its own (24000 x 1280: 61 MB)."""
+    B, lo, c, h = 8, 1500, 80, 1280
+    st, m = _create(dict(kind="conv_stem", batch=B, seq=lo, in_dim=c, hidden=h))
+    assert st == mb.OK
+    T, Tin = B * lo, 2 * B * lo
+    kept = 2 * 2 * (Tin * 3 * c + Tin * h + T * 3 * h + T * h)
+    sums = 2 * mb.colsum_scratch_bytes(h)
+    pieces = max(mb.linear_wgrad_scratch_bytes(Tin, 3 * c, h), mb.linear_wgrad_scratch_bytes(T, 3 * h, h)) - mb.colsum_scratch_bytes(h)
+    have = mb.lib().mosaic_module_workspace_bytes(m)
+    assert kept + sums + pieces <= have <= kept + sums + pieces + 16 * 256
+    mb.lib().mosaic_module_destroy(m)
+
+
 def test_unbound_module_and_null_arguments_are_errors_not_crashes():
     import ctypes as C
     l = mb.lib()
