@@ -194,7 +194,7 @@ def test_workspace_of_the_audio_stem_holds_what_it_keeps_and_no_more():
     st, m = _create(dict(kind="conv_stem", batch=B, seq=lo, in_dim=c, hidden=h))
     assert st == mb.OK
     T, Tin = B * lo, 2 * B * lo
-    kept = 2 * 2 * (Tin * 3 * c + Tin * h + T * 3 * h + T * h)
+    kept = 2 * 2 * (Tin * 3 * c + Tin * h + T * 3 * h + T * h) + 2 * T * h + mb.mse_scratch_bytes()      # and the gradient of a loss
     sums = 2 * mb.colsum_scratch_bytes(h)
     pieces = max(mb.linear_wgrad_scratch_bytes(Tin, 3 * c, h), mb.linear_wgrad_scratch_bytes(T, 3 * h, h)) - mb.colsum_scratch_bytes(h)
     have = mb.lib().mosaic_module_workspace_bytes(m)
