@@ -443,7 +443,7 @@ mosaic_status conv_stem_backward(mosaic_module* m, hipStream_t s, int q, const v
     MOSAIC_TRY(launch_gemm(s, q, dt, false, false, 3 * C, h, Tin, W(m, m->c_p1), 3 * C, W(m, m->c_dz1), h, G(m, p.w_1), h, nullptr, nullptr, sk));
   } else {
     MOSAIC_TRY(launch_linear_bwd(s, q, dt, Tin, 3 * C, h, W(m, m->c_p1), W(m, m->c_dz1), P(m, p.w_1), W(m, m->c_dp1), G(m, p.w_1), sk, false));
-    MOSAIC_TRY(launch_col2im1d(s, q, dt, d.batch, L, L, C, 1, W(m, m->c_dp1), dx));
+    MOSAIC_TRY(launch_col2im1d(s, q, dt, d.batch, L, C, W(m, m->c_dp1), dx));
   }
   return MOSAIC_OK;
 }

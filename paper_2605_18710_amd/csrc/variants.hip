@@ -148,11 +148,10 @@ __global__ __launch_bounds__(kThreads) void im2col1d_kernel(const T* __restrict_
   }
 }
 
-// The transpose of the gather: dx[b, s, c] = sum over taps k (ascending) of
-// dP[(b*Lo + t), k*C + c] with t*stride - 1 + k == s; one owner per element, fixed order.
+// The transpose of the gather of stride 1: dx[b, s, c] = sum over taps k (ascending) of
+// dP[(b*L + t), k*C + c] with t - 1 + k == s; one owner per element, fixed order.
 template <typename T>
-__global__ __launch_bounds__(kThreads) void col2im1d_kernel(const T* __restrict__ dP, T* __restrict__ dx, int64_t B, int L,
-                                                            int Lo, int C, int stride) {
+__global__ __launch_bounds__(kThreads) void col2im1d_kernel(const T* __restrict__ dP, T* __restrict__ dx, int64_t B, int L, int C) {
   constexpr int VN = Vec16<T>::N;
   const int cv = C / VN;
   const int64_t nvec = B * L * cv;
@@ -165,12 +164,10 @@ __global__ __launch_bounds__(kThreads) void col2im1d_kernel(const T* __restrict_
 #pragma unroll
     for (int e = 0; e < VN; ++e) acc[e] = 0.f;
     for (int k = 0; k < 3; ++k) {
-      const int num = s_ + 1 - k;
-      if (num < 0 || num % stride) continue;
-      const int t = num / stride;
-      if (t >= Lo) continue;
+      const int t = s_ + 1 - k;
+      if (t < 0 || t >= L) continue;
       Vec16<T> val;
-      val.load(dP + (b * Lo + t) * 3 * (int64_t)C + (int64_t)k * C + c);
+      val.load(dP + (b * L + t) * 3 * (int64_t)C + (int64_t)k * C + c);
 #pragma unroll
       for (int e = 0; e < VN; ++e) acc[e] += val.get(e);
     }
@@ -195,14 +192,13 @@ mosaic_status launch_im2col1d(hipStream_t s, int quota, int dtype, int64_t B, in
   return MOSAIC_OK;
 }
 
-mosaic_status launch_col2im1d(hipStream_t s, int quota, int dtype, int64_t B, int L, int Lo, int C, int stride,
-                              const void* dP, void* dx) {
+mosaic_status launch_col2im1d(hipStream_t s, int quota, int dtype, int64_t B, int L, int C, const void* dP, void* dx) {
   const int vn = dtype == MOSAIC_BF16 ? 8 : 4;
   if (C % vn) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "channel count %d is not a multiple of %d", C, vn);
-  if (B <= 0 || L <= 0 || Lo <= 0) return MOSAIC_OK;
+  if (B <= 0 || L <= 0) return MOSAIC_OK;
   const int grid = grid_for(quota, 8, ceil_div(B * L * (C / vn), kThreads));
-  if (dtype == MOSAIC_BF16) col2im1d_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)dP, (bf16*)dx, B, L, Lo, C, stride);
-  else col2im1d_kernel<float><<<grid, kThreads, 0, s>>>((const float*)dP, (float*)dx, B, L, Lo, C, stride);
+  if (dtype == MOSAIC_BF16) col2im1d_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)dP, (bf16*)dx, B, L, C);
+  else col2im1d_kernel<float><<<grid, kThreads, 0, s>>>((const float*)dP, (float*)dx, B, L, C);
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;
 }
