@@ -10,13 +10,16 @@
 // fprop  Y = X W      : A = X  [T,k] a_kc=1, B = W  [k,n] b_kc=0
 // dgrad  dX = dY W^T  : A = dY [T,n] a_kc=1, B = W  [k,n] b_kc=1 (contraction over n)
 // wgrad  dW = X^T dY  : A = X  [T,k] a_kc=0, B = dY [T,n] b_kc=0 (contraction over T)
+// Padded rows: with lda >= M rounded up to 8, a K-strided A may have any M (its rows must be
+// readable up to that width).  b_rows >= 0: a K-strided B has only that many of its K rows; the
+// columns of A past them must hold zeros.
 mosaic_status launch_gemm(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc,
                           int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
                           const void* B, int64_t ldb, void* C, int64_t ldc,
                           const void* bias, const void* R, void* splitk_scratch = nullptr, int64_t b_rows = -1);
-// Padded rows: with lda >= M rounded up to 8, a K-strided A may have any M (its rows must be
-// readable up to that width).  b_rows >= 0: a K-strided B has only that many of its K rows; the
-// columns of A past them must hold zeros.
+// Bytes of fp32 scratch the weight-gradient form wants for a deterministic split of a long
+// contraction over few output tiles (0 when no split is used for this shape).
+size_t gemm_splitk_scratch_bytes(int64_t M, int64_t N, int64_t K);
 // Y[b, t, :] = X[b, t, :] W + bias + table[t, :]: B x rows patches of k values, ldx apart (zeros past k), W [k, n].  One rounding
 // where the bf16 matrix-core kernel takes the product and the table in its epilogue, else the product and add_pos.
 mosaic_status launch_embed_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t rows, int64_t n, int64_t k, int64_t ldx, const void* X,
@@ -27,18 +30,15 @@ mosaic_status launch_embed_fwd(hipStream_t s, int quota, int dtype, int64_t B, i
 // otherwise the elementwise kernel follows the product.
 mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act, int64_t T, int64_t k, int64_t n,
                                     const void* X, const void* W, const void* bias, void* Z, void* A);
-// Z = X W + bias over samples of 2 lo rows and P [B lo, 3n] = the gathered input of a three-tap convolution of stride 2 over gelu(Z)
-// (launch_im2col1d), written by the epilogue
-// where the bf16 matrix-core kernel takes the product, else through A [2 B lo, n]; the same bits.
+// Z = X W + bias over samples of 2 lo rows, and P [B lo, 3n] = the gathered input of a three-tap convolution of stride 2 over
+// gelu(Z) (launch_im2col1d): written by the epilogue where the bf16 matrix-core kernel takes the product, else through A [2 B lo, n];
+// the same bits.
 mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t lo, int64_t n, int64_t k, const void* X, const void* W,
                                    const void* bias, void* Z, void* A, void* P);
-// Bytes of fp32 scratch the weight-gradient form wants for a deterministic split of a long
-// contraction over few output tiles (0 when no split is used for this shape).
 // dW[k,n] = X^T dY and dX[T,k] = dY W^T, dense rows; one launch where that is the faster way, else two, the input gradient's
 // first or last (1 - 2 % of a layer either way, by what the caches still hold)
 mosaic_status launch_linear_bwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t k, int64_t n, const void* X, const void* dY,
                                 const void* W, void* dX, void* dW, void* splitk_scratch, bool dx_first);
-size_t gemm_splitk_scratch_bytes(int64_t M, int64_t N, int64_t K);
 
 // ------------------------------------------------------------------------- attention
 // packed rows [q (H heads) | k (Hkv heads) | v (Hkv heads)]; Hkv divides H; query head t
