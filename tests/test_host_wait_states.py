@@ -104,6 +104,21 @@ def matrix_too_close(ins):
     return bad
 
 
+def accumulator_writes(ins):
+    """(registers a0 .. a95 that anything but a matrix instruction writes, matrix instructions that write other ones of them than a whole
+    accumulator).  Loads and reads of LDS may write accumulator registers directly; a swap writes both its operands."""
+    plain, odd = [], []
+    for at, op, operands, _ in ins:
+        if op.startswith("v_mfma"):
+            to = {r for r in registers(operands.partition(", ")[0], "a") if r < 96}
+            if to and to not in [set(range(i, i + 16)) for i in (0, 16, 32, 48)]:
+                odd.append("%x %s %s" % (at, op, operands))
+        elif op.startswith("v_") or re.match(r"(ds|buffer|global|flat|scratch)_", op) and "store" not in op and "write" not in op:
+            written = operands.split(", ")[:2 if "swap" in op else 1]
+            plain += [r for x in written for r in registers(x, "a") if r < 96]
+    return plain, odd
+
+
 def too_close(ins):
     """Descriptions of the memory instructions that come too soon after the write of what they read."""
     found = looking_back(ins)
@@ -147,6 +162,21 @@ def test_the_check_of_matrix_instructions(lines, bad):
     assert len(matrix_too_close(ins)) == bad
 
 
+@pytest.mark.parametrize("lines,plain,odd", [
+    (("v_accvgpr_write_b32 a3, 0", "v_accvgpr_read_b32 v1, a16", "ds_write_b128 v0, a[4:7]", "global_store_dwordx4 v[0:1], a[8:11], off"), [3], 0),
+    (("ds_read_b128 a[0:3], v0",), [0, 1, 2, 3], 0),
+    (("buffer_load_dwordx4 a[92:95], v0, s[0:3], 0 offen",), [92, 93, 94, 95], 0),
+    (("global_load_dword a7, v[0:1], off", "scratch_load_dword a9, off, off offset:16"), [7, 9], 0),
+    (("v_accvgpr_mov_b32 a5, a96", "v_swap_b32 v0, a6"), [5, 6], 0),
+    (("ds_read_b128 a[96:99], v0", "v_mfma_f32_32x32x16_bf16 a[16:31], v[4:7], v[8:11], a[16:31]"), [], 0),
+    (("v_mfma_f32_32x32x16_bf16 a[64:79], v[4:7], v[8:11], a[64:79]", "v_mfma_f32_16x16x32_bf16 a[4:7], v[4:7], v[8:11], a[4:7]"), [], 2),
+])
+def test_the_check_of_accumulator_writes(lines, plain, odd):
+    (_, ins), = kernels(listing_of(*lines))
+    got = accumulator_writes(ins)
+    assert sorted(got[0]) == plain and len(got[1]) == odd
+
+
 @pytest.fixture(scope="module")
 def listings(tmp_path_factory):
     if not os.path.exists(OBJDUMP):
@@ -173,5 +203,5 @@ def test_matrix_instructions_of_the_dkv_kernel_keep_their_distance(listings):
     assert sum(x[1].startswith("v_mfma") for x in ins) >= 40
     assert not matrix_too_close(ins)
     # dK, dV and the K and V fragments, a0 .. a95: written once per item (cleared, loaded), otherwise by matrix instructions
-    writes = [r for x in ins if x[1].startswith("v_accvgpr") and not x[1].startswith("v_accvgpr_read") for r in registers(x[2].split(", ")[0], "a")]
-    assert sorted(r for r in writes if r < 96) == list(range(96))
+    plain, odd = accumulator_writes(ins)
+    assert sorted(plain) == list(range(96)) and not odd
