@@ -1105,7 +1105,7 @@ __global__ __launch_bounds__(64 * NW * PARTS, 8 / NW / PARTS) void attn_bwd_dkv_
 // Bound by instruction issue and by the round trips of a wave's chain (scores, probabilities, products) that the other
 // wave of the SIMD does not cover: attn_bwd_dkv_mfma issues 288 instructions and waits a third of its time
 // per 32x32 block of scores, 16 of them matrix instructions (1510 cycles of a SIMD per block for 512 of matrix work).  Here a block takes
-// about 160, and its phases are skewed by half a block so that a wave's vector work has matrix work of its own beside it:
+// 188, and its phases are skewed by half a block so that a wave's vector work has matrix work of its own beside it:
 //   (1) products of rows 16..31 of block t-1 into dV and dK beside P and dS of rows 0..15 of block t,
 //   (2) products of rows 0..15 of block t beside P and dS of its rows 16..31,
 //   (3) S and dP of block t+1.
@@ -1115,7 +1115,7 @@ __global__ __launch_bounds__(64 * NW * PARTS, 8 / NW / PARTS) void attn_bwd_dkv_
 //   * V fragments stay in registers, LDS addresses advance once per tile of two blocks.
 //   * three stages of 64 rows (the tile of block t-1 is read transposed, that of t+1 by rows, one is landing), one
 //     barrier per tile.
-// B8 N1500 H20, this kernel alone: 284 -> 240 us, 1510 -> 1200 cycles per block, matrix cores busy 0.34 -> 0.43; backward pass
+// B8 N1500 H20, this kernel alone: 284 -> 238 us, 1510 -> 1215 cycles per block, matrix cores busy 0.34 -> 0.42; backward pass
 // on 64 CUs 1049 -> 841; B16 N576 H16 backward 125 -> 116.  One wave per SIMD with 64 keys each (half the LDS reads, 512
 // registers) issued fewer instructions still and was slower, 344 us: one wave's chain of 350 instructions a step, 5.3 cycles each at
 // best, has nothing beside it.  Operands requested a phase earlier still: no change.
