@@ -553,6 +553,8 @@ inline int bits_of(int v) { int n = 0; while (v >> n) ++n; return n; }
 // more; one CU sorts, which tells at more positions.  Measured on 256 CUs, bf16, one / several launches in us:
 //   T 2048 h 64 V 1048576  54 / 99     T 4096 h 2048 V 32000  33 / 54     T 8192 h 2048 V 32000  43 / 61     h 256 V 400  34 / 37
 //   T 16384 h 2048 V 32000  76 / 72    h 512 V 500  63 / 43 (32 keys a thread)
+// and on 64 and 8 CUs (masked streams; several launches with the join that they had): T 8192 h 2048 V 32000  59 / 111, 356 / 612;  h 256 V 400
+// 40 / 47, 103 / 141;  T 1024 h 512 V 1000  16 / 28, 24 / 44;  T 2048 h 64 V 1048576  165 / 266, 1369 / 1775.
 inline bool sorts_in_one(int64_t total, int64_t vocab) { return total <= kOneMax && bits_of((int)vocab) + bits_of((int)total - 1) <= 32; }
 
 template <typename T, int V>
