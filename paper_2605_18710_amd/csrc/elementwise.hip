@@ -602,12 +602,12 @@ constexpr int kColsumMaxParts = 512;
 // widest row (in 16-byte vectors per lane) whose column accumulators the fused norm backward keeps in registers
 constexpr int kNormFusedMaxNV = 8;   // LayerNorm; RMSNorm (one sum per column) also fits at 10
 
-template <typename T>
+template <typename T, bool QUARTERS>
 __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(const T* __restrict__ X, float* __restrict__ partial,
                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles) {
   constexpr int V = Vec16<T>::N;
   typedef typename Pack<T, V>::type vec;
-  column_sums<V, 8, false>(rows, n, rp, np, ctiles, partial, [&](int64_t r, int64_t c) { return *reinterpret_cast<const vec*>(X + r * n + c); },
+  column_sums<V, QUARTERS ? 4 : 8, QUARTERS>(rows, n, rp, np, ctiles, partial, [&](int64_t r, int64_t c) { return *reinterpret_cast<const vec*>(X + r * n + c); },
                            [&](const vec& x, int64_t, int64_t, float (&acc)[V]) {
 #pragma unroll
                              for (int k = 0; k < V; ++k) acc[k] += pack_get<T, V>(x, k);
@@ -615,7 +615,7 @@ __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(const T* __res
 }
 
 // The sums of column_sums with QUARTERS, by one wave: two rows of each quarter are requested together.  32768 x 2048 on 256, 128,
-// 64 CUs: four waves 28.8 36.4 34.1 us, this 27.5 26.7 31.4; 24000 x 4096 37.9 38.3 50.3 -> 38.2 37.9 46.4; 32768 x 4096 46.8 48 79 -> 51.5 59 76.
+// 64 CUs: four waves 28.1 36.4 34.1 us, this 27.5 26.6 31.2; 24000 x 4096 38.1 38.1 50.3 -> 37.5 37.4 46.6; 65536 x 4096 100 122 187 -> 101 117 179.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void colsum_quarters_kernel(const T* __restrict__ X, float* __restrict__ partial,
                                                                    int64_t rows, int64_t n, int rp, int np, int ctiles) {
@@ -1025,11 +1025,16 @@ mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int6
   col_partition(T, &rp, &np);
   if (np > 0) {
     const int ctiles = (int)ceil_div(n, (int64_t)64 * vn__);
-    const int grid = grid_for(quota, 8, ceil_div((int64_t)np * ctiles, kWaves));
+    // One wave's requests go to four rows a quarter of a partition apart.  Where that is a multiple of 128 KB and the CUs are many, the four
+    // waves of a workgroup, which drift apart, are faster: one wave / four, us on 256 (192) CUs, 32768 x 4096 54 (49) / 46 (44),
+    // 65536 x 2048 49.3 (47.6) / 46.0 (45.5), 131072 x 2048 103 (105) / 98.5 (99); on 64 CUs 78 / 79, 69.5 / 71.5, 174 / 181.
+    const bool quarters = colsum_quarters(rp, n), apart = quota > 128 && (int64_t)rp / 4 * n * (int64_t)dtype_size(dtype) % (128 << 10) == 0;
+    const int grid = grid_for(quota, 8, ceil_div((int64_t)np * ctiles, quarters && apart ? 1 : kWaves));
     auto launch = [&](auto type) {
       typedef decltype(type) E;
-      if (colsum_quarters(rp, n)) colsum_quarters_kernel<E><<<grid, kThreads, 0, s>>>((const E*)X, (float*)scratch, T, n, rp, np, ctiles);
-      else colsum_partial_kernel<E><<<grid, kThreads, 0, s>>>((const E*)X, (float*)scratch, T, n, rp, np, ctiles);
+      if (quarters && apart) colsum_partial_kernel<E, true><<<grid, kThreads, 0, s>>>((const E*)X, (float*)scratch, T, n, rp, np, ctiles);
+      else if (quarters) colsum_quarters_kernel<E><<<grid, kThreads, 0, s>>>((const E*)X, (float*)scratch, T, n, rp, np, ctiles);
+      else colsum_partial_kernel<E, false><<<grid, kThreads, 0, s>>>((const E*)X, (float*)scratch, T, n, rp, np, ctiles);
     };
     if (dtype == MOSAIC_BF16) launch(bf16{}); else launch(float{});
     MOSAIC_LAUNCH_CHECK();
