@@ -223,6 +223,28 @@ def test_adamw_steps(mb, dtype, n, master):
         assert np.array_equal(from_dev(p_), quantize(from_dev(mast), "bf16"))        # params = rounding of the master copy
 
 
+# one workgroup per block from 64 MB on, past the caches from 256 MB on: the same bits as the update in pieces that take neither
+@pytest.mark.parametrize("dtype,master,mb_total", [("bf16", True, 64), ("bf16", False, 257), ("bf16", True, 257), ("f32", False, 257)])
+def test_adamw_of_large_states(mb, dtype, master, mb_total):
+    per = (28 if master else 22) if dtype == "bf16" else 28
+    n = 4 * ((mb_total << 20) // per // 4 + 257)                      # the last block is partly past the end
+    g = torch.Generator(device="cuda").manual_seed(7)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    p = torch.randn(n, generator=g, device="cuda").to(td)
+    grad = torch.randn(n, generator=g, device="cuda").mul_(1e-3).to(td)
+    m = torch.randn(n, generator=g, device="cuda").mul_(1e-4)
+    v = torch.rand(n, generator=g, device="cuda").mul_(1e-6)
+    mast = p.float() if master else None
+    hp = dict(lr=1e-3, beta1=0.9, beta2=0.95, eps=1e-8, weight_decay=0.1, step=3)
+    q, mq, vq, sq = p.clone(), m.clone(), v.clone(), mast.clone() if master else None
+    mb.op_adamw(None, 256, dtype, n, p, grad, m, v, mast, **hp)
+    for at in range(0, n, 1 << 20):
+        part = slice(at, min(n, at + (1 << 20)))
+        mb.op_adamw(None, 256, dtype, part.stop - at, q[part], grad[part], mq[part], vq[part], sq[part] if master else None, **hp)
+    torch.cuda.synchronize()
+    assert torch.equal(p, q) and torch.equal(m, mq) and torch.equal(v, vq) and (not master or torch.equal(mast, sq))
+
+
 def test_module_adamw_step_moves_every_tensor(mb):
     cfg = dec(2, 64, 128, 4, 256, 2)
     m = mb.Module(cfg, "bf16")
