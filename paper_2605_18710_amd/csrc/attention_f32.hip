@@ -1,8 +1,8 @@
 // Attention with fp32 arithmetic, any head size up to 128: the fp32 path, and bf16 head sizes and
 // tensors that the bf16 matrix-core kernels do not cover.
 //
-// v_mfma_f32_16x16x4_f32, one wave per workgroup and 16 owned rows per wave, no LDS and no
-// barriers: scores are formed so that a lane owns one column (lane%16) and four rows (4*(lane/16)+e),
+// v_mfma_f32_16x16x4_f32, 16 owned rows (an item) per wave, or per four waves, no LDS and no
+// barriers in the loops: scores are formed so that a lane owns one column (lane%16) and four rows (4*(lane/16)+e),
 // which is exactly the layout in which the next product wants them as its second operand
 // (contraction index e-th instruction: row 4*(lane/16)+e), so probabilities go from one product to
 // the next in registers, and row maxima and sums are four values plus two exchanges.
@@ -11,12 +11,13 @@
 // P is recomputed from the saved row log-sum-exp; D_i = sum_c dO_ic O_ic is formed by the dQ
 // kernel, which runs first, and read by the dK/dV kernel.
 //
-// What bounds it: the fp32 workloads have few rows (2 x 128 tokens x 4 heads = 64 waves), so a
+// What bounds it: the fp32 workloads have few rows (2 x 128 tokens x 4 heads = 64 items), so a
 // kernel is one chain of load latency, products and softmax per streamed block.  The streamed
 // rows of the next block are requested before the current block's products, and the second
-// reading of the block's rows (in the other orientation) is in flight under them.  At B2 N128 H4
-// d32: forward 29 -> 10.1 us, dQ 25 -> 10.7, dK/dV 41 -> 13.7 against workgroups of 16 rows that formed
-// each score by scalar FMA over LDS (launches of 4.5 us included).  Longer rows and the bf16 head sizes
+// reading of the block's rows (in the other orientation) is in flight under them.  Where items are few, four waves share
+// one, each with every fourth step over the streamed rows, and add their sums in wave order: B2 N128 H4 d32 forward
+// 9.1 -> 5.3 us, backward 14.6 -> 7.0.  At that size, one wave to an item: forward 29 -> 10.1 us, dQ 25 -> 10.7,
+// dK/dV 41 -> 13.7 against workgroups of 16 rows that formed each score by scalar FMA over LDS (launches of 4.5 us included).  Longer rows and the bf16 head sizes
 // that come here, forward and backward in us, against those workgroups: fp32 B4 N1500 H8 d80 3944 -> 529 and
 // 19622 -> 1868, fp32 B1 N2048 H8/2 d128 causal 2442 -> 308 and 13313 -> 2253; bf16 B8 N1500 H16 d80 15614 -> 3484 and
 // 74581 -> 14185, B2 N576 H16 d72 733 -> 206 and 2852 -> 870.
@@ -96,10 +97,31 @@ struct AttnArgs {
   int tiles;                 // tiles of 16 rows
 };
 
-template <typename T, int DB, bool VEC>
-__global__ __launch_bounds__(64) void attn_fwd_f32(const T* __restrict__ qkv, T* __restrict__ O, float* __restrict__ lse, AttnArgs p) {
+// With SPLIT waves to an item each takes every SPLIT-th step over the streamed rows, and their sums are added in wave order
+// through LDS.  sums[w][b][lane]: block b of 16 x 16 values of wave w.
+template <int SPLIT, int NB>
+__device__ __forceinline__ void add_waves(f32x4 (&v)[NB], f32x4* sums, int wave, int lane) {
+#pragma unroll
+  for (int b = 0; b < NB; ++b) sums[(wave * NB + b) * 64 + lane] = v[b];
+  __syncthreads();
+  // wave w finishes blocks w, w + SPLIT, ...; the others' values are not used
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    if (b % SPLIT != wave) continue;
+    v[b] = sums[b * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < SPLIT; ++w) v[b] += sums[(w * NB + b) * 64 + lane];
+  }
+  __syncthreads();
+}
+template <int SPLIT> __device__ __forceinline__ bool mine(int block, int wave) { return SPLIT == 1 || block % SPLIT == wave; }
+
+template <typename T, int DB, bool VEC, int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) void attn_fwd_f32(const T* __restrict__ qkv, T* __restrict__ O, float* __restrict__ lse, AttnArgs p) {
   constexpr int KB = kBlocks<DB>;
-  const int lr = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int lane = threadIdx.x & 63, lr = lane & 15, g = lane >> 4, wave = SPLIT == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ f32x4 sums[SPLIT == 1 ? 1 : SPLIT * DB * 64];
+  __shared__ float rows_m[SPLIT][16], rows_l[SPLIT][16];
   // rows are [q (H heads) | k (Hkv heads) | v (Hkv heads)]; query head t uses key/value head t / (H/Hkv)
   const int N = p.N, d = p.d, GQ = p.H / p.Hkv;
   const int64_t rs = (int64_t)(p.H + 2 * p.Hkv) * d;
@@ -127,8 +149,8 @@ __global__ __launch_bounds__(64) void attn_fwd_f32(const T* __restrict__ qkv, T*
         row_frag<T, DB, VEC>(kf[u], kb_ + (int64_t)j * rs, g, d, j < kv_end);
       }
     };
-    k_rows(0);
-    for (int j0 = 0; j0 < kv_end; j0 += 16 * KB) {
+    if (SPLIT == 1 || wave * 16 * KB < kv_end) k_rows(wave * 16 * KB);
+    for (int j0 = wave * 16 * KB; j0 < kv_end; j0 += 16 * KB * SPLIT) {
       f32x4 vt[KB][DB], sc[KB];
 #pragma unroll
       for (int u = 0; u < KB; ++u) col_frag<T, DB>(vt[u], vb_, rs, j0 + 16 * u, kv_end, lr, g, d);
@@ -138,7 +160,7 @@ __global__ __launch_bounds__(64) void attn_fwd_f32(const T* __restrict__ qkv, T*
 #pragma unroll
         for (int s = 0; s < DB; ++s) sc[u] = mfma4(kf[u][s], qf[s], sc[u]);
       }
-      if (j0 + 16 * KB < kv_end) k_rows(j0 + 16 * KB);
+      if (j0 + 16 * KB * SPLIT < kv_end) k_rows(j0 + 16 * KB * SPLIT);
       float mx = -INFINITY;
 #pragma unroll
       for (int u = 0; u < KB; ++u)
@@ -169,12 +191,26 @@ __global__ __launch_bounds__(64) void attn_fwd_f32(const T* __restrict__ qkv, T*
       }
     }
     l = groups_sum(l);                       // every lane group has summed its own keys
+    if constexpr (SPLIT > 1) {               // the waves' sums brought to one reference; a wave without keys has m = -inf and l = 0
+      if (g == 0) { rows_m[wave][lr] = m; rows_l[wave][lr] = l; }
+      __syncthreads();
+      float top = rows_m[0][lr], total = 0.f;
+#pragma unroll
+      for (int w = 1; w < SPLIT; ++w) top = fmaxf(top, rows_m[w][lr]);
+#pragma unroll
+      for (int w = 0; w < SPLIT; ++w) total += rows_m[w][lr] == -INFINITY ? 0.f : rows_l[w][lr] * expf(rows_m[w][lr] - top);
+      const float own = m == -INFINITY ? 0.f : expf(m - top);
+#pragma unroll
+      for (int s = 0; s < DB; ++s) o[s] *= own;
+      m = top; l = total;
+      add_waves<SPLIT, DB>(o, sums, wave, lane);       // its barriers also keep the rows' values until all have read them
+    }
     if (i < N) {
       const float inv = 1.0f / l;
       T* row = O + (b * N + i) * (int64_t)p.H * d + hd * d;
 #pragma unroll
-      for (int s = 0; s < DB; ++s) put4<T, VEC>(row, 16 * s + 4 * g, d, o[s] * inv);
-      if (g == 0) lse[hb * N + i] = m + logf(l);
+      for (int s = 0; s < DB; ++s) if (mine<SPLIT>(s, wave)) put4<T, VEC>(row, 16 * s + 4 * g, d, o[s] * inv);
+      if (g == 0 && wave == 0) lse[hb * N + i] = m + logf(l);
     }
   }
 }
@@ -182,11 +218,11 @@ __global__ __launch_bounds__(64) void attn_fwd_f32(const T* __restrict__ qkv, T*
 // workgroups first .. first + count - 1 of the launch
 struct Share { int first, count; };
 
-template <typename T, int DB, bool VEC>
+template <typename T, int DB, bool VEC, int SPLIT>
 __device__ __forceinline__ void dq_items(const T* __restrict__ qkv, const T* __restrict__ O, const T* __restrict__ dO,
-                                         const float* __restrict__ lse, float* __restrict__ delta, T* __restrict__ dqkv, const AttnArgs& p, Share sh) {
+                                         const float* __restrict__ lse, float* __restrict__ delta, T* __restrict__ dqkv, const AttnArgs& p, Share sh, f32x4* sums) {
   constexpr int KB = kBlocks<DB>;
-  const int lr = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int lane = threadIdx.x & 63, lr = lane & 15, g = lane >> 4, wave = SPLIT == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int N = p.N, d = p.d, GQ = p.H / p.Hkv;
   const int64_t rs = (int64_t)(p.H + 2 * p.Hkv) * d, h = (int64_t)p.H * d;
   const int64_t items = (int64_t)p.B * p.H * p.tiles;
@@ -212,7 +248,7 @@ __device__ __forceinline__ void dq_items(const T* __restrict__ qkv, const T* __r
         for (int e = 0; e < 4; ++e) dl = fmaf(dof[s][e], of[s][e], dl);
     }
     dl = groups_sum(dl);
-    if (delta && i < N && g == 0) delta[hb * N + i] = dl;
+    if (delta && i < N && g == 0 && wave == 0) delta[hb * N + i] = dl;
     const float li = i < N ? lse[hb * N + i] : 0.f;
 #pragma unroll
     for (int s = 0; s < DB; ++s) dq[s] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -225,8 +261,8 @@ __device__ __forceinline__ void dq_items(const T* __restrict__ qkv, const T* __r
         row_frag<T, DB, VEC>(vf[u], vb_ + (int64_t)j * rs, g, d, j < kv_end);
       }
     };
-    kv_rows(0);
-    for (int j0 = 0; j0 < kv_end; j0 += 16 * KB) {
+    if (SPLIT == 1 || wave * 16 * KB < kv_end) kv_rows(wave * 16 * KB);
+    for (int j0 = wave * 16 * KB; j0 < kv_end; j0 += 16 * KB * SPLIT) {
       f32x4 kt[KB][DB], sc[KB], dp[KB];
 #pragma unroll
       for (int u = 0; u < KB; ++u) col_frag<T, DB>(kt[u], kb_, rs, j0 + 16 * u, kv_end, lr, g, d);
@@ -236,7 +272,7 @@ __device__ __forceinline__ void dq_items(const T* __restrict__ qkv, const T* __r
 #pragma unroll
         for (int s = 0; s < DB; ++s) { sc[u] = mfma4(kf[u][s], qf[s], sc[u]); dp[u] = mfma4(vf[u][s], dof[s], dp[u]); }
       }
-      if (j0 + 16 * KB < kv_end) kv_rows(j0 + 16 * KB);
+      if (j0 + 16 * KB * SPLIT < kv_end) kv_rows(j0 + 16 * KB * SPLIT);
 #pragma unroll
       for (int u = 0; u < KB; ++u)
 #pragma unroll
@@ -250,20 +286,21 @@ __device__ __forceinline__ void dq_items(const T* __restrict__ qkv, const T* __r
 #pragma unroll
         for (int u = 0; u < KB; ++u) dq[s] = mfma4(kt[u][s], sc[u], dq[s]);
     }
+    if constexpr (SPLIT > 1) add_waves<SPLIT, DB>(dq, sums, wave, lane);
     if (i < N) {
       T* row = dqkv + (b * N + i) * rs + hd * d;
 #pragma unroll
-      for (int s = 0; s < DB; ++s) put4<T, VEC>(row, 16 * s + 4 * g, d, dq[s] * p.scale);
+      for (int s = 0; s < DB; ++s) if (mine<SPLIT>(s, wave)) put4<T, VEC>(row, 16 * s + 4 * g, d, dq[s] * p.scale);
     }
   }
 }
 
 // OWN_DELTA: the row sums D_i are formed here from dO and O, with the additions of dq_items, and not read
-template <typename T, int DB, bool VEC, bool OWN_DELTA>
+template <typename T, int DB, bool VEC, bool OWN_DELTA, int SPLIT>
 __device__ __forceinline__ void dkv_items(const T* __restrict__ qkv, const T* __restrict__ O, const T* __restrict__ dO, const float* __restrict__ lse,
-                                          const float* __restrict__ delta, T* __restrict__ dqkv, const AttnArgs& p, Share sh) {
+                                          const float* __restrict__ delta, T* __restrict__ dqkv, const AttnArgs& p, Share sh, f32x4* sums) {
   constexpr int QB = kBlocks<DB>;
-  const int lr = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int lane = threadIdx.x & 63, lr = lane & 15, g = lane >> 4, wave = SPLIT == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int N = p.N, d = p.d, GQ = p.H / p.Hkv;
   const int64_t rs = (int64_t)(p.H + 2 * p.Hkv) * d, h = (int64_t)p.H * d;
   const int64_t items = (int64_t)p.B * p.Hkv * p.tiles;
@@ -279,7 +316,7 @@ __device__ __forceinline__ void dkv_items(const T* __restrict__ qkv, const T* __
     row_frag<T, DB, VEC>(vf, rowb + (int64_t)j * rs + h + (int64_t)(p.Hkv + kvh) * d, g, d, j < N);
 #pragma unroll
     for (int s = 0; s < DB; ++s) { dk[s] = f32x4{0.f, 0.f, 0.f, 0.f}; dv[s] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    const int i_begin = p.causal ? kt * 16 : 0;
+    const int i_begin = (p.causal ? kt * 16 : 0) + wave * 16 * QB;
     // every query head of the group in turn, query blocks ascending inside a head
     for (int hd = kvh * GQ; hd < (kvh + 1) * GQ; ++hd) {
       const T* qb_ = rowb + hd * d;
@@ -297,8 +334,8 @@ __device__ __forceinline__ void dkv_items(const T* __restrict__ qkv, const T* __
           if constexpr (OWN_DELTA) row_frag<T, DB, VEC>(out[u], ob_ + (int64_t)i * h, g, d, i < N);
         }
       };
-      q_rows(i_begin);
-      for (int i0 = i_begin; i0 < N; i0 += 16 * QB) {
+      if (SPLIT == 1 || i_begin < N) q_rows(i_begin);
+      for (int i0 = i_begin; i0 < N; i0 += 16 * QB * SPLIT) {
         f32x4 qt[QB][DB], ot[QB][DB], sc[QB], dp[QB], li[QB], dl[QB];
 #pragma unroll
         for (int u = 0; u < QB; ++u) {
@@ -327,7 +364,7 @@ __device__ __forceinline__ void dkv_items(const T* __restrict__ qkv, const T* __
 #pragma unroll
           for (int s = 0; s < DB; ++s) { sc[u] = mfma4(qf[u][s], kf[s], sc[u]); dp[u] = mfma4(of[u][s], vf[s], dp[u]); }
         }
-        if (i0 + 16 * QB < N) q_rows(i0 + 16 * QB);
+        if (i0 + 16 * QB * SPLIT < N) q_rows(i0 + 16 * QB * SPLIT);
 #pragma unroll
         for (int u = 0; u < QB; ++u)
 #pragma unroll
@@ -343,10 +380,12 @@ __device__ __forceinline__ void dkv_items(const T* __restrict__ qkv, const T* __
           for (int u = 0; u < QB; ++u) { dv[s] = mfma4(ot[u][s], sc[u], dv[s]); dk[s] = mfma4(qt[u][s], dp[u], dk[s]); }
       }
     }
+    if constexpr (SPLIT > 1) { add_waves<SPLIT, DB>(dk, sums, wave, lane); add_waves<SPLIT, DB>(dv, sums, wave, lane); }
     if (j < N) {
       T* row = dqkv + (b * N + j) * rs + h + kvh * d;
 #pragma unroll
       for (int s = 0; s < DB; ++s) {
+        if (!mine<SPLIT>(s, wave)) continue;
         put4<T, VEC>(row, 16 * s + 4 * g, d, dk[s] * p.scale);
         put4<T, VEC>(row + (int64_t)p.Hkv * d, 16 * s + 4 * g, d, dv[s]);
       }
@@ -354,23 +393,28 @@ __device__ __forceinline__ void dkv_items(const T* __restrict__ qkv, const T* __
   }
 }
 
-template <typename T, int DB, bool VEC>
-__global__ __launch_bounds__(64) void attn_bwd_dq_f32(const T* __restrict__ qkv, const T* __restrict__ O, const T* __restrict__ dO,
-                                                      const float* __restrict__ lse, float* __restrict__ delta, T* __restrict__ dqkv, AttnArgs p) {
-  dq_items<T, DB, VEC>(qkv, O, dO, lse, delta, dqkv, p, {0, (int)gridDim.x});
+template <int SPLIT, int DB> constexpr int kSums = SPLIT == 1 ? 1 : SPLIT * DB * 64;
+
+template <typename T, int DB, bool VEC, int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) void attn_bwd_dq_f32(const T* __restrict__ qkv, const T* __restrict__ O, const T* __restrict__ dO,
+                                                              const float* __restrict__ lse, float* __restrict__ delta, T* __restrict__ dqkv, AttnArgs p) {
+  __shared__ f32x4 sums[kSums<SPLIT, DB>];
+  dq_items<T, DB, VEC, SPLIT>(qkv, O, dO, lse, delta, dqkv, p, {0, (int)gridDim.x}, sums);
 }
-template <typename T, int DB, bool VEC>
-__global__ __launch_bounds__(64) void attn_bwd_dkv_f32(const T* __restrict__ qkv, const T* __restrict__ dO, const float* __restrict__ lse,
-                                                       const float* __restrict__ delta, T* __restrict__ dqkv, AttnArgs p) {
-  dkv_items<T, DB, VEC, false>(qkv, nullptr, dO, lse, delta, dqkv, p, {0, (int)gridDim.x});
+template <typename T, int DB, bool VEC, int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) void attn_bwd_dkv_f32(const T* __restrict__ qkv, const T* __restrict__ dO, const float* __restrict__ lse,
+                                                               const float* __restrict__ delta, T* __restrict__ dqkv, AttnArgs p) {
+  __shared__ f32x4 sums[kSums<SPLIT, DB>];
+  dkv_items<T, DB, VEC, false, SPLIT>(qkv, nullptr, dO, lse, delta, dqkv, p, {0, (int)gridDim.x}, sums);
 }
-// Both in one launch where every item has a wave slot of its own: the two chains, each a launch's latency and a few blocks
-// long, then run side by side, at the price of reading O for dK/dV as well.  B2 N128 H4 d32: 10.3 + 13.7 us -> 15.0.
-template <int DB>
-__global__ __launch_bounds__(64) void attn_bwd_f32(const float* __restrict__ qkv, const float* __restrict__ O, const float* __restrict__ dO,
-                                                   const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, AttnArgs p, int ndkv) {
-  if ((int)blockIdx.x < ndkv) dkv_items<float, DB, true, true>(qkv, O, dO, lse, nullptr, dqkv, p, {0, ndkv});
-  else dq_items<float, DB, true>(qkv, O, dO, lse, delta, dqkv, p, {ndkv, (int)gridDim.x - ndkv});
+// Both in one launch where every item has wave slots of its own: the two chains, each a launch's latency and a few blocks
+// long, then run side by side, at the price of reading O for dK/dV as well.  B2 N128 H4 d32, one wave to an item: 10.3 + 13.7 us -> 15.0; four 7.0.
+template <int DB, int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) void attn_bwd_f32(const float* __restrict__ qkv, const float* __restrict__ O, const float* __restrict__ dO,
+                                                           const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, AttnArgs p, int ndkv) {
+  __shared__ f32x4 sums[kSums<SPLIT, DB>];
+  if ((int)blockIdx.x < ndkv) dkv_items<float, DB, true, true, SPLIT>(qkv, O, dO, lse, nullptr, dqkv, p, {0, ndkv}, sums);
+  else dq_items<float, DB, true, SPLIT>(qkv, O, dO, lse, delta, dqkv, p, {ndkv, (int)gridDim.x - ndkv}, sums);
 }
 
 // four columns per access where every head of every row starts on such a boundary
@@ -379,10 +423,38 @@ bool four_columns(int d, const void* a, const void* b, const void* c, const void
   return d % 4 == 0 && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)e) & (4 * sizeof(T) - 1)) == 0;
 }
 
+// Four waves to an item where the items are few (with 1024 waves every SIMD of the device has one): a function of the shape, because the
+// order of the sums follows it.
+bool split_items(const AttnArgs& p) { return p.N > 32 && p.d <= 64 && (int64_t)p.B * p.H * p.tiles <= 256; }
+
 template <typename T, int DB, bool VEC>
 mosaic_status fwd_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv, void* O, float* lse) {
-  const int grid = grid_for(quota, 8, (int64_t)p.B * p.H * p.tiles);
-  attn_fwd_f32<T, DB, VEC><<<grid, 64, 0, s>>>((const T*)qkv, (T*)O, lse, p);
+  const int64_t items = (int64_t)p.B * p.H * p.tiles;
+  bool split = false;
+  if constexpr (std::is_same<T, float>::value && DB <= 4) split = split_items(p);
+  if constexpr (std::is_same<T, float>::value && DB <= 4)
+    if (split) attn_fwd_f32<T, DB, VEC, 4><<<grid_for(quota, 4, items), 256, 0, s>>>((const T*)qkv, (T*)O, lse, p);
+  if (!split) attn_fwd_f32<T, DB, VEC, 1><<<grid_for(quota, 8, items), 64, 0, s>>>((const T*)qkv, (T*)O, lse, p);
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
+
+template <typename T, int DB, bool VEC, int SPLIT>
+mosaic_status bwd_split_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv, const void* O, const float* lse, const void* dO,
+                          void* dqkv, float* delta) {
+  const int64_t ndq = (int64_t)p.B * p.H * p.tiles, ndkv = (int64_t)p.B * p.Hkv * p.tiles;
+  if constexpr (std::is_same<T, float>::value && VEC && DB <= 4) {
+    // one wave per SIMD at most; two where four waves share an item
+    if ((ndq + ndkv) * SPLIT <= (int64_t)quota * (SPLIT > 1 ? 8 : 4)) {
+      attn_bwd_f32<DB, SPLIT><<<(int)(ndq + ndkv), 64 * SPLIT, 0, s>>>((const float*)qkv, (const float*)O, (const float*)dO, lse, delta, (float*)dqkv, p, (int)ndkv);
+      MOSAIC_LAUNCH_CHECK();
+      return MOSAIC_OK;
+    }
+  }
+  constexpr int PER_CU = SPLIT > 1 ? 2 : 8;
+  attn_bwd_dq_f32<T, DB, VEC, SPLIT><<<grid_for(quota, PER_CU, ndq), 64 * SPLIT, 0, s>>>((const T*)qkv, (const T*)O, (const T*)dO, lse, delta, (T*)dqkv, p);
+  MOSAIC_LAUNCH_CHECK();
+  attn_bwd_dkv_f32<T, DB, VEC, SPLIT><<<grid_for(quota, PER_CU, ndkv), 64 * SPLIT, 0, s>>>((const T*)qkv, (const T*)dO, lse, delta, (T*)dqkv, p);
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;
 }
@@ -390,21 +462,9 @@ mosaic_status fwd_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv
 template <typename T, int DB, bool VEC>
 mosaic_status bwd_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv, const void* O, const float* lse, const void* dO,
                     void* dqkv, float* delta) {
-  const int64_t ndq = (int64_t)p.B * p.H * p.tiles, ndkv = (int64_t)p.B * p.Hkv * p.tiles;
-  if constexpr (std::is_same<T, float>::value && VEC && DB <= 4) {
-    if (ndq + ndkv <= (int64_t)quota * 4) {            // one wave per SIMD at most
-      attn_bwd_f32<DB><<<(int)(ndq + ndkv), 64, 0, s>>>((const float*)qkv, (const float*)O, (const float*)dO, lse, delta, (float*)dqkv, p, (int)ndkv);
-      MOSAIC_LAUNCH_CHECK();
-      return MOSAIC_OK;
-    }
-  }
-  attn_bwd_dq_f32<T, DB, VEC><<<grid_for(quota, 8, ndq), 64, 0, s>>>((const T*)qkv, (const T*)O, (const T*)dO, lse,
-                                                                                            delta, (T*)dqkv, p);
-  MOSAIC_LAUNCH_CHECK();
-  attn_bwd_dkv_f32<T, DB, VEC><<<grid_for(quota, 8, ndkv), 64, 0, s>>>((const T*)qkv, (const T*)dO, lse, delta,
-                                                                                               (T*)dqkv, p);
-  MOSAIC_LAUNCH_CHECK();
-  return MOSAIC_OK;
+  if constexpr (std::is_same<T, float>::value && DB <= 4)
+    if (split_items(p)) return bwd_split_t<T, DB, VEC, 4>(s, quota, p, qkv, O, lse, dO, dqkv, delta);
+  return bwd_split_t<T, DB, VEC, 1>(s, quota, p, qkv, O, lse, dO, dqkv, delta);
 }
 
 // column blocks of 16 that a head needs, rounded up to an instantiated count

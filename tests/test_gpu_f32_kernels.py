@@ -102,6 +102,15 @@ def test_attention_backward_in_one_launch_has_the_bits_of_two(mb, B, N, H, Hkv, 
     assert all(torch.equal(a, b) for a, b in zip(*outs))
 
 
+# one step of keys more than one wave takes, waves without a key, the most items that four waves share and one tile more, grouped heads
+@pytest.mark.parametrize("B,N,H,Hkv,d,causal", [(1, 33, 2, 1, 32, 1), (1, 33, 2, 2, 64, 0), (1, 49, 2, 1, 16, 1), (2, 128, 16, 4, 16, 1), (2, 129, 16, 4, 16, 1),
+                                                (1, 250, 3, 1, 60, 0)])
+def test_attention_items_of_four_waves(mb, B, N, H, Hkv, d, causal):
+    test_attention(mb, "f32", B, N, H, Hkv, d, causal, 0)
+    if d % 16 == 0:
+        test_attention_backward_in_one_launch_has_the_bits_of_two(mb, B, N, H, Hkv, d, causal)
+
+
 @pytest.mark.parametrize("T,k,n", [(1, 4, 4), (33, 64, 36), (256, 128, 384), (31, 132, 68), (300, 36, 8)])
 def test_backward_products_in_one_launch_have_the_bits_of_two(mb, T, k, n):
     """A module takes the input and the weight gradient of a linear layer in one launch, the entry points one each."""
