@@ -10,6 +10,11 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + expf(-z)); }
 // SwiGLU: silu(gate) * up
 __device__ __forceinline__ float swiglu_f(float gate, float up) { return gate * sigmoid_f(gate) * up; }
+__device__ __forceinline__ void swiglu_grad_f(float gate, float up, float d, float* dgate, float* dup) {
+  const float s = sigmoid_f(gate);
+  *dgate = d * up * (s * (1.0f + gate * (1.0f - s)));
+  *dup = d * (gate * s);
+}
 
 // GELU of bf16 numbers from a table in LDS that the workgroup fills with erff itself: the bits of gelu_f.
 // erff is odd and takes 1665 values over the bf16 numbers from 2^-10 to 8.  Below, the factor

@@ -6,6 +6,7 @@
 // All reductions run in an order fixed by the problem shape alone: persistent grids only
 // decide which workgroup handles a work item, so results are bit-identical for any quota.
 #include "activations.h"
+#include <algorithm>
 #include <type_traits>
 #include "kernels.h"
 
@@ -314,6 +315,26 @@ __global__ __launch_bounds__(kThreads) void norm_colgrad_partial_kernel(
   }
 }
 
+__device__ __forceinline__ float block_sum_fixed(float v, float* red) {
+  // fixed-shape reduction: butterfly inside each wave, then waves added in index order
+  v = wave_sum(v);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane == 0) red[wave] = v;
+  __syncthreads();
+  float t = 0.f;
+  for (int w = 0; w < kWaves; ++w) t += red[w];
+  __syncthreads();
+  return t;
+}
+
+// loss = scale * (the partial sums in a fixed order)
+__device__ __forceinline__ void loss_sum(const float* __restrict__ partial, int np, float* __restrict__ loss, float scale, float* red) {
+  float acc = 0.f;
+  for (int p = threadIdx.x; p < np; p += kThreads) acc += partial[p];
+  const float t = block_sum_fixed(acc, red);
+  if (threadIdx.x == 0) *loss = t * scale;
+}
+
 // The final pass of column reductions (ColReduce): partitions taken in 8 contiguous slices that are added in slice
 // order, a fixed tree that depends on np only.  A workgroup takes 32 columns of one of the list's reductions.  Bound by
 // launch and latency: one alone takes 4.5 to 8 us for a few hundred KB to 10 MB of partial sums, so a layer's go in one launch
@@ -322,6 +343,7 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void col_reduce_kernel(ColReduceList list, int64_t total) {
   __shared__ float red[8][32];
   const int cl = threadIdx.x & 31, sl = threadIdx.x >> 5;
+  if (list.loss && blockIdx.x == gridDim.x - 1) loss_sum(list.loss_partial, list.loss_np, list.loss, list.loss_scale, &red[0][0]);
   for (int64_t at = blockIdx.x; at < total; at += gridDim.x) {
     int64_t gidx = at;
     int which = 0;
@@ -534,9 +556,10 @@ __global__ __launch_bounds__(kThreads) void swiglu_bwd_kernel(const T* __restric
     d.load(da + r * f + c);
 #pragma unroll
     for (int k = 0; k < VN; ++k) {
-      const float z = g.get(k), s = sigmoid_f(z);
-      og.set(k, d.get(k) * u.get(k) * (s * (1.0f + z * (1.0f - s))));
-      ou.set(k, d.get(k) * (z * s));
+      float dg, du;
+      swiglu_grad_f(g.get(k), u.get(k), d.get(k), &dg, &du);
+      og.set(k, dg);
+      ou.set(k, du);
     }
     og.store(dgu + r * 2 * f + c);
     ou.store(dgu + r * 2 * f + f + c);
@@ -546,29 +569,15 @@ __global__ __launch_bounds__(kThreads) void swiglu_bwd_kernel(const T* __restric
 // ---------------------------------------------------------------------------------- MSE
 constexpr int kMsePartials = 1024;
 
-__device__ __forceinline__ float block_sum_fixed(float v, float* red) {
-  // fixed-shape reduction: butterfly inside each wave, then waves added in index order
-  v = wave_sum(v);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  float t = 0.f;
-  for (int w = 0; w < kWaves; ++w) t += red[w];
-  __syncthreads();
-  return t;
-}
-
 template <typename T>
 __global__ __launch_bounds__(kThreads) void mse_kernel(const T* __restrict__ y, const T* __restrict__ tg,
                                                        T* __restrict__ dy, float* __restrict__ partial,
-                                                       int64_t nvec, int64_t chunk, float scale) {
+                                                       int64_t nvec, int np, float scale) {
   constexpr int VN = Vec16<T>::N;
   __shared__ float red[kWaves];
-  for (int p = blockIdx.x; p < kMsePartials; p += gridDim.x) {
-    const int64_t v0 = (int64_t)p * chunk;
-    const int64_t v1 = (v0 + chunk < nvec) ? v0 + chunk : nvec;
+  for (int p = blockIdx.x; p < np; p += gridDim.x) {
     float acc = 0.f;
-    for (int64_t i = v0 + threadIdx.x; i < v1; i += kThreads) {
+    for (int64_t i = (int64_t)p * kThreads + threadIdx.x; i < nvec; i += (int64_t)np * kThreads) {
       Vec16<T> a, b, o;
       a.load(y + i * VN);
       b.load(tg + i * VN);
@@ -585,13 +594,9 @@ __global__ __launch_bounds__(kThreads) void mse_kernel(const T* __restrict__ y, 
   }
 }
 
-__global__ __launch_bounds__(kThreads) void mse_final_kernel(const float* __restrict__ partial,
-                                                             float* __restrict__ loss, float inv_n) {
+__global__ __launch_bounds__(kThreads) void mse_final_kernel(const float* __restrict__ partial, int np, float* __restrict__ loss, float inv_n) {
   __shared__ float red[kWaves];
-  float acc = 0.f;
-  for (int p = threadIdx.x; p < kMsePartials; p += kThreads) acc += partial[p];
-  const float t = block_sum_fixed(acc, red);
-  if (threadIdx.x == 0) *loss = t * inv_n;
+  loss_sum(partial, np, loss, inv_n, red);
 }
 
 // ------------------------------------------------------------------------------ colsum
@@ -828,7 +833,7 @@ mosaic_status launch_norm_fwd(hipStream_t s, int quota, int dtype, int norm, int
 mosaic_status launch_col_reduce(hipStream_t s, int quota, int dtype, const ColReduceList& list) {
   int64_t total = 0;
   for (int i = 0; i < list.n; ++i) total += ceil_div(list.job[i].ncols, 32);
-  if (total == 0) return MOSAIC_OK;
+  if (total == 0 && !list.loss) return MOSAIC_OK;
   const int grid = grid_for(quota, 8, total);
   if (dtype == MOSAIC_BF16) col_reduce_kernel<bf16><<<grid, kThreads, 0, s>>>(list, total);
   else col_reduce_kernel<float><<<grid, kThreads, 0, s>>>(list, total);
@@ -991,19 +996,23 @@ mosaic_status launch_swiglu_bwd(hipStream_t s, int quota, int dtype, int64_t T, 
 size_t mse_scratch_bytes() { return kMsePartials * sizeof(float); }
 
 mosaic_status launch_mse(hipStream_t s, int quota, int dtype, int64_t n, const void* y, const void* target,
-                         void* dy, float* loss, void* scratch) {
+                         void* dy, float* loss, void* scratch, ColReduceList* later) {
   EW_CHECK_VEC(n, dtype);
   if (n == 0) MOSAIC_FAIL(MOSAIC_EINVAL, "mse over zero elements");
   const int64_t nvec = n / vn__;
-  const int64_t chunk = ceil_div(nvec, kMsePartials);
-  const int grid = grid_for(quota, 8, kMsePartials);
+  const int np = (int)std::min<int64_t>(kMsePartials, ceil_div(nvec, kThreads));      // a function of the size alone
+  const int grid = grid_for(quota, 8, np);
   const float scale = (float)(2.0 / (double)n);
   if (dtype == MOSAIC_BF16)
-    mse_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)y, (const bf16*)target, (bf16*)dy, (float*)scratch, nvec, chunk, scale);
+    mse_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)y, (const bf16*)target, (bf16*)dy, (float*)scratch, nvec, np, scale);
   else
-    mse_kernel<float><<<grid, kThreads, 0, s>>>((const float*)y, (const float*)target, (float*)dy, (float*)scratch, nvec, chunk, scale);
+    mse_kernel<float><<<grid, kThreads, 0, s>>>((const float*)y, (const float*)target, (float*)dy, (float*)scratch, nvec, np, scale);
   MOSAIC_LAUNCH_CHECK();
-  mse_final_kernel<<<1, kThreads, 0, s>>>((const float*)scratch, loss, (float)(1.0 / (double)n));
+  if (later) {
+    later->loss_partial = (const float*)scratch; later->loss = loss; later->loss_np = np; later->loss_scale = (float)(1.0 / (double)n);
+    return MOSAIC_OK;
+  }
+  mse_final_kernel<<<1, kThreads, 0, s>>>((const float*)scratch, np, loss, (float)(1.0 / (double)n));
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;
 }

@@ -1665,7 +1665,9 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
 mosaic_status launch_gemm_f32(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int M, int N, int K, const void* A,
                               int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, const void* bias, const void* R);
 mosaic_status launch_linear_bwd_f32(hipStream_t s, int quota, int64_t T, int64_t k, int64_t n, const void* X, const void* dY, const void* W,
-                                    void* dX, void* dW, bool* taken);
+                                    void* dX, void* dW, bool* taken, int act = -1, const void* Z = nullptr, void* dZ = nullptr, float* sums = nullptr);
+mosaic_status launch_layer_fwd_f32(hipStream_t s, int quota, int norm, int act, int64_t T, int64_t k, int64_t n, float eps, const void* X, const void* gamma,
+                                   const void* beta, void* U, float* stats, const void* W, const void* bias, void* Z, void* A, bool* taken);
 
 size_t gemm_splitk_scratch_bytes(int64_t M, int64_t N, int64_t K) {
   int first = 0;
@@ -1749,6 +1751,10 @@ mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act
   if (act == MOSAIC_SWIGLU && (n % 2)) MOSAIC_FAIL(MOSAIC_EINVAL, "SwiGLU needs an even output width, got %lld", (long long)n);
   const int64_t na = act == MOSAIC_SWIGLU ? n / 2 : n;
   bool fused = false;
+  if (dtype == MOSAIC_F32) {
+    MOSAIC_TRY(launch_layer_fwd_f32(s, quota, 0, act, T, k, n, 0.f, X, nullptr, nullptr, nullptr, nullptr, W, bias, Z, Aout, &fused));
+    if (fused) return MOSAIC_OK;
+  }
   MOSAIC_TRY(launch_gemm_impl(s, quota, dtype, true, false, T, n, k, X, k, W, n, Z, n, bias, nullptr, nullptr, -1, act, Aout, na,
                               act == MOSAIC_GELU_TANH ? nullptr : &fused));
   if (fused || T == 0 || n == 0) return MOSAIC_OK;
@@ -1829,4 +1835,37 @@ mosaic_status launch_linear_bwd(hipStream_t s, int quota, int dtype, int64_t T, 
   if (dx_first) MOSAIC_TRY(input_grad());
   MOSAIC_TRY(launch_gemm(s, quota, dtype, false, false, k, n, T, X, k, dY, n, dW, n, nullptr, nullptr, splitk_scratch));
   return dx_first ? MOSAIC_OK : input_grad();
+}
+
+mosaic_status launch_norm_linear_fwd(hipStream_t s, int quota, int dtype, int norm, int act, int64_t T, int64_t h, int64_t n, float eps, const void* X,
+                                     const void* gamma, const void* beta, void* U, float* stats, const void* W, const void* bias, void* Z, void* A) {
+  if (dtype == MOSAIC_F32) {
+    bool taken;
+    MOSAIC_TRY(launch_layer_fwd_f32(s, quota, norm, act, T, h, n, eps, X, gamma, beta, U, stats, W, bias, Z, A, &taken));
+    if (taken) return MOSAIC_OK;
+  }
+  MOSAIC_TRY(launch_norm_fwd(s, quota, dtype, norm, T, h, eps, X, gamma, beta, U, stats));
+  if (act < 0) return launch_gemm(s, quota, dtype, true, false, T, n, h, U, h, W, n, Z, n, bias, nullptr);
+  return launch_linear_act_fwd(s, quota, dtype, act, T, h, n, U, W, bias, Z, A);
+}
+
+mosaic_status launch_act_linear_bwd(hipStream_t s, int quota, int dtype, int act, int64_t T, int64_t k, int64_t n, const void* Z, const void* A, const void* dY,
+                                    const void* W, void* dA, void* dZ, void* dW, void* splitk_scratch, void* colsum, void* scratch, ColReduceList* later) {
+  const int64_t np = ceil_div(T, 16), es = (int64_t)dtype_size(dtype), zb = T * k * es * (act == MOSAIC_SWIGLU ? 2 : 1), wb = k * n * es;
+  const bool apart = !overlap(dW, wb, A, T * k * es) && !overlap(dW, wb, dY, T * n * es) && !overlap(dW, wb, W, wb) && !overlap(dW, wb, Z, zb) &&
+                     !overlap(dW, wb, dZ, zb) && !overlap(dZ, zb, A, T * k * es) && !overlap(dZ, zb, dY, T * n * es) && !overlap(dZ, zb, W, wb) && !overlap(dZ, zb, Z, zb);
+  if (dtype == MOSAIC_F32 && apart && T > 0 && k > 0 && n > 0 && (act == MOSAIC_GELU || act == MOSAIC_SWIGLU) && later && later->n < ColReduceList::kMax &&
+      (!colsum || (size_t)np * (size_t)k * sizeof(float) <= colsum_scratch_bytes(k)) && pair_enabled()) {
+    bool taken;
+    MOSAIC_TRY(launch_linear_bwd_f32(s, quota, T, k, n, A, dY, W, dA, dW, &taken, act, Z, dZ, colsum ? (float*)scratch : nullptr));
+    if (taken) {
+      if (colsum) later->job[later->n++] = {(const float*)scratch, (int)np, k, k, k, INT64_MAX, colsum, nullptr, nullptr};
+      return MOSAIC_OK;
+    }
+  }
+  MOSAIC_TRY(launch_linear_bwd(s, quota, dtype, T, k, n, A, dY, W, dA, dW, splitk_scratch, true));
+  if (act == MOSAIC_SWIGLU) return launch_swiglu_bwd(s, quota, dtype, T, k, Z, dA, dZ);
+  if (act == MOSAIC_GELU_TANH) return launch_gelu_tanh_bwd(s, quota, dtype, T * k, Z, dA, dZ);
+  if (colsum) return launch_gelu_bwd_colsum(s, quota, dtype, T, k, Z, dA, dZ, colsum, scratch, later);
+  return launch_gelu_bwd(s, quota, dtype, T * k, Z, dA, dZ);
 }

@@ -4,14 +4,19 @@
 // v_mfma_f32_16x16x4_f32: fp32 products and sums, no narrower type anywhere.  Four waves share a
 // square output tile.  A lane's four consecutive k-values feed four consecutive instructions:
 // instruction s of a 16-wide k-step contracts k = s, 4+s, 8+s, 12+s; both operands agree on that
-// order, so each output is a fixed sum that depends on K alone.
+// order, so each output is a fixed sum that depends on the sizes alone.
 //
 // What bounds it: the fp32 workloads are a few hundred rows wide, every product is a chain of
-// latencies (load, barrier, matrix instructions, store), so tiles are small enough to give most
-// CUs one (32 x 32), a K-tile is 64 deep and the next one is requested before the current one
-// is multiplied.  Products with at least two 64 x 64 tiles per CU take those: twice the flops per
-// LDS byte (rule and figures in launch_t).  256 x 128 x 384 (M x K x N) and the like: 47 us with 64 x 64 tiles of scalar FMA, 16 deep,
-// before; 4.8 to 5.9 now (launch included).
+// latencies (load, barrier, matrix instructions, store) behind a launch that costs 4 us or more whatever it does.  So what stands
+// around a product in a layer (norm in front, activation or its derivative behind) shares its launch; tiles are small
+// enough to give most CUs one; and products of up to 512 blocks of 16 x 16 are summed in shares of the contraction, which
+// eight waves take side by side where the CUs hold all blocks (gemm_f32_share_tile).  32 x 32 tiles: four waves, a K-tile is 64 deep and
+// the next one is requested before the current one is multiplied.  Products with at least two 64 x 64 tiles per CU take those:
+// twice the flops per LDS byte (rule and figures in launch_t).
+// A decoder layer of 256 rows, width 128, MLP 384 (forward, loss, backward): 19 launches, 92.8 us -> 14, 62.3.
+#include <algorithm>
+#include <type_traits>
+#include "activations.h"
 #include "kernels.h"
 
 namespace {
@@ -24,7 +29,23 @@ struct F32Gemm {
   int M, N, K;
   int64_t lda, ldb, ldc;
   int tiles_m, tiles_n;
+  bool in_shares;            // the order of the sums (share_order)
+  // what the epilogues and the norm in front take (fp32 tensors, rows of whole 16-byte pieces)
+  const float* Z;            // the stored input of the activation whose derivative is applied
+  float* C2;                 // the activation, or the gradient behind the derivative
+  float* sums;               // column sums of C2 over 16 rows each, [M / 16 rounded up][N]
+  int f;                     // SwiGLU: width of the gate half
+  const float *gamma, *beta; // A is the normalised input: U = norm(A) is formed here
+  float *U, *stats;
+  float eps;
 };
+
+// EPI: what follows the product.  F32_GELU: C2 = gelu(C).  F32_SWIGLU: C is [gate | up], C2 = silu(gate) * up; a tile holds 16 columns of either
+// half.  F32_DGELU / F32_DSWIGLU: the product is the gradient of the activation; it is not stored, C2 is the gradient in front.
+enum { F32_PLAIN, F32_GELU, F32_SWIGLU, F32_DGELU, F32_DSWIGLU };
+// widest row that the norm in front of a product keeps in LDS (32 rows)
+constexpr int kF32NormMax = 256;
+constexpr int kF32NormPitch = kF32NormMax + 4;
 
 // four consecutive elements as fp32; elements from `n` on are zero
 template <typename T, bool VEC>
@@ -54,7 +75,8 @@ struct F32Tile {
   static constexpr int PITCH = (KC ? KS : BT) + 4;
   static constexpr int FLOATS = (KC ? BT : KS) * PITCH;
   f32x4 reg[NCH];
-  __device__ __forceinline__ void request(const T* base, int64_t ld, int x0, int X, int k0, int K) {
+  // half > 0: the tile's upper 16 columns lie that far behind column x0, the lower 16 at x0 (K strided)
+  __device__ __forceinline__ void request(const T* base, int64_t ld, int x0, int X, int k0, int K, int half = 0) {
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int q = threadIdx.x + 256 * i;
@@ -62,8 +84,8 @@ struct F32Tile {
         const int r = x0 + q / (KS / 4), k = k0 + q % (KS / 4) * 4;
         reg[i] = load4<T, VEC>(base + (int64_t)r * ld + k, r < X ? K - k : 0);
       } else {
-        const int k = k0 + q / (BT / 4), x = x0 + q % (BT / 4) * 4;
-        reg[i] = load4<T, VEC>(base + (int64_t)k * ld + x, k < K ? X - x : 0);
+        const int k = k0 + q / (BT / 4), c = q % (BT / 4) * 4, x = half ? x0 + c % 16 : x0 + c;
+        reg[i] = load4<T, VEC>(base + (int64_t)k * ld + x + (half && c >= 16 ? half : 0), k < K ? (half ? half : X) - x : 0);
       }
     }
   }
@@ -85,42 +107,163 @@ struct F32Tile {
   }
 };
 
-template <typename T, int BT, int KS, bool A_KC, bool B_KC, bool VEC>
+// y = norm(x) of the tile's 32 rows into `panel` (zeros behind the row's end); the workgroup of the first tile column stores it too.
+// Eight lanes a row; mean first, then the squares around it, as in the norm's own kernel.
+template <int NORM>
+__device__ __forceinline__ void f32_norm_panel(const F32Gemm& p, int m0, bool first, float* panel) {
+  constexpr int NV = kF32NormMax / 32;
+  const int r = threadIdx.x >> 3, l = threadIdx.x & 7, row = m0 + r, h = p.K;
+  const float* x = (const float*)p.A + (int64_t)row * p.lda;
+  f32x4 v[NV], gm[NV], bt[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = (l + 8 * i) * 4;
+    v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    gm[i] = v[i]; bt[i] = v[i];
+    if (c < h) {
+      if (row < p.M) v[i] = *reinterpret_cast<const f32x4*>(x + c);
+      gm[i] = *reinterpret_cast<const f32x4*>(p.gamma + c);
+      if (NORM == MOSAIC_LAYERNORM) bt[i] = *reinterpret_cast<const f32x4*>(p.beta + c);
+    }
+  }
+  auto row_sum = [](float s) { s += __shfl_xor(s, 1, 64); s += __shfl_xor(s, 2, 64); return s + __shfl_xor(s, 4, 64); };
+  const float inv_h = 1.0f / (float)h;
+  float s = 0.f, mean = 0.f;
+  if constexpr (NORM == MOSAIC_LAYERNORM) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) s += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+    mean = row_sum(s) * inv_h;
+    s = 0.f;
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { const float d = v[i][e] - mean; if ((l + 8 * i) * 4 < h) s += d * d; }
+  const float rstd = 1.0f / sqrtf(row_sum(s) * inv_h + p.eps);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = (l + 8 * i) * 4;
+    f32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (v[i][e] - mean) * rstd * gm[i][e] + bt[i][e];
+    *reinterpret_cast<f32x4*>(panel + r * kF32NormPitch + c) = o;
+    if (first && row < p.M && c < h) *reinterpret_cast<f32x4*>(p.U + (int64_t)row * h + c) = o;
+  }
+  if (first && row < p.M && l == 0) { p.stats[2 * row] = mean; p.stats[2 * row + 1] = rstd; }
+}
+
+// What follows a product of fp32 tensors, for columns c .. c+3 of a row.  up: (SwiGLU) they belong to the up half, whose lanes hand them to
+// the gate half's through `mail`; every lane of the workgroup comes here.  sum_rows adds a value over the 16 rows of a block.
+template <int EPI, typename SumRows>
+__device__ __forceinline__ void f32_epilogue(const F32Gemm& p, f32x4 v, int row, int c, bool up, float* mail, bool first_row, const SumRows& sum_rows) {
+  constexpr bool GU = EPI == F32_SWIGLU;
+  const int width = GU ? p.f : p.N, col = up ? p.f + c : c;
+  const bool in = row < p.M && c < width;
+  f32x4 a2 = {0.f, 0.f, 0.f, 0.f};
+  auto at = [&](const void* t, int64_t ld, int cc) { return reinterpret_cast<f32x4*>(const_cast<float*>((const float*)t) + (int64_t)row * ld + cc); };
+  if constexpr (EPI == F32_PLAIN) {
+    if (!in) return;
+    if (p.bias) v += *reinterpret_cast<const f32x4*>((const float*)p.bias + c);
+    if (p.R) v += *at(p.R, p.ldc, c);
+    *at(p.C, p.ldc, c) = v;
+  }
+  if constexpr (EPI == F32_GELU || GU) {
+    if (in && p.bias) v += *reinterpret_cast<const f32x4*>((const float*)p.bias + col);
+    if (in) *at(p.C, p.ldc, col) = v;
+  }
+  if constexpr (EPI == F32_GELU) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a2[e] = gelu_f(v[e]);
+    if (in) *at(p.C2, p.N, c) = a2;
+  }
+  if constexpr (GU) {
+    if (up) *reinterpret_cast<f32x4*>(mail) = v;
+    __syncthreads();
+    if (!up) {
+      const f32x4 u = *reinterpret_cast<const f32x4*>(mail);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a2[e] = swiglu_f(v[e], u[e]);
+      if (in) *at(p.C2, p.f, c) = a2;
+    }
+    __syncthreads();
+  }
+  if constexpr (EPI == F32_DGELU) {
+    if (in) {
+      const f32x4 z = *at(p.Z, p.N, c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a2[e] = v[e] * gelu_grad_f(z[e]);
+      *at(p.C2, p.N, c) = a2;
+    }
+    if (p.sums) {                                      // of what is stored
+      a2 = sum_rows(a2);
+      if (first_row && in) *reinterpret_cast<f32x4*>(p.sums + (int64_t)(row >> 4) * p.N + c) = a2;
+    }
+  }
+  if constexpr (EPI == F32_DSWIGLU) {
+    if (!in) return;
+    const f32x4 z = *at(p.Z, 2 * p.N, c), u = *at(p.Z, 2 * p.N, p.N + c);
+    f32x4 du;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float dg, dp;
+      swiglu_grad_f(z[e], u[e], v[e], &dg, &dp);
+      a2[e] = dg; du[e] = dp;
+    }
+    *at(p.C2, 2 * p.N, c) = a2;
+    *at(p.C2, 2 * p.N, p.N + c) = du;
+  }
+}
+
+// k-values of a wave's share of a contraction (gemm_f32_share_tile): whole K-tiles of 64
+constexpr int kShares = 8;
+__device__ __host__ __forceinline__ int share_length(int K) { return (K + 64 * kShares - 1) / (64 * kShares) * 64; }
+
+template <typename T, int BT, int KS, bool A_KC, bool B_KC, bool VEC, bool SHARES, int EPI = F32_PLAIN, int NORM = 0>
 __device__ __forceinline__ void gemm_f32_tile(const F32Gemm& p, int tile, float* lds) {
+  static_assert((EPI == F32_PLAIN && !SHARES) || BT == 32, "shares and the other epilogues exist for 32 x 32 tiles");
+  constexpr bool GU = EPI == F32_SWIGLU;
   constexpr int TW = BT / 32;                                      // 16-wide blocks per wave and direction
   typedef F32Tile<T, BT, KS, A_KC, VEC> TA;
   typedef F32Tile<T, BT, KS, B_KC, VEC> TB;
-  constexpr int STAGE = TA::FLOATS + TB::FLOATS;
+  constexpr int AFLOATS = NORM ? 0 : TA::FLOATS, STAGE = AFLOATS + TB::FLOATS;
+  float* const panel = lds + 2 * STAGE;  // NORM: the rows of A, normalised
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, g = lane >> 4;
   const int wm = (wave >> 1) * (BT / 2), wn = (wave & 1) * (BT / 2);
   const T *A = (const T*)p.A, *B = (const T*)p.B;
   const int tn = tile / p.tiles_m, tm = tile - tn * p.tiles_m;
-  const int m0 = tm * BT, n0 = tn * BT;
+  const int m0 = tm * BT, n0 = tn * (GU ? 16 : BT);
   TA ta; TB tb;
-  f32x4 acc[TW][TW];
+  // SHARES: the sum of gemm_f32_share_tile, a share of the contraction at a time
+  const int share = p.in_shares ? share_length(p.K) : 0;
+  f32x4 acc[TW][TW], sum = {-0.f, -0.f, -0.f, -0.f};        // -0 + x is x for every x
 #pragma unroll
   for (int i = 0; i < TW; ++i)
 #pragma unroll
     for (int j = 0; j < TW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  ta.request(A, p.lda, m0, p.M, 0, p.K);
-  tb.request(B, p.ldb, n0, p.N, 0, p.K);
-  int st = 0;
+  if constexpr (!NORM) ta.request(A, p.lda, m0, p.M, 0, p.K);
+  tb.request(B, p.ldb, n0, p.N, 0, p.K, GU ? p.f : 0);
+  if constexpr (NORM != 0) f32_norm_panel<NORM>(p, m0, tn == 0, panel);
+  int st = 0, fold = 0;
   for (int k0 = 0; k0 < p.K; k0 += KS, st ^= 1) {
     float* a = lds + st * STAGE;
-    float* b = a + TA::FLOATS;
-    ta.put(a);
+    float* b = a + AFLOATS;
+    if constexpr (!NORM) ta.put(a);
     tb.put(b);
     __syncthreads();                     // the other stage was read before this barrier, and is written after the next
     if (k0 + KS < p.K) {
-      ta.request(A, p.lda, m0, p.M, k0 + KS, p.K);
-      tb.request(B, p.ldb, n0, p.N, k0 + KS, p.K);
+      if constexpr (!NORM) ta.request(A, p.lda, m0, p.M, k0 + KS, p.K);
+      tb.request(B, p.ldb, n0, p.N, k0 + KS, p.K, GU ? p.f : 0);
     }
 #pragma unroll
     for (int ks = 0; ks < KS / 16; ++ks) {
       f32x4 fa[TW], fb[TW];
 #pragma unroll
-      for (int i = 0; i < TW; ++i) { fa[i] = TA::frag(a, wm + 16 * i + lr, ks, g); fb[i] = TB::frag(b, wn + 16 * i + lr, ks, g); }
+      for (int i = 0; i < TW; ++i) {
+        if constexpr (NORM != 0) fa[i] = *reinterpret_cast<const f32x4*>(panel + (wm + 16 * i + lr) * kF32NormPitch + k0 + 16 * ks + 4 * g);
+        else fa[i] = TA::frag(a, wm + 16 * i + lr, ks, g);
+        fb[i] = TB::frag(b, wn + 16 * i + lr, ks, g);
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -128,9 +271,24 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Gemm& p, int tile, float*
 #pragma unroll
           for (int j = 0; j < TW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[i][e], acc[i][j], 0, 0, 0);
     }
+    if constexpr (SHARES) {
+      fold += KS;
+      if (fold == share) { sum += acc[0][0]; acc[0][0] = f32x4{0.f, 0.f, 0.f, 0.f}; fold = 0; }
+    }
   }
+  if constexpr (SHARES) acc[0][0] = sum + acc[0][0];
   __syncthreads();                       // the next tile writes stage 0
   // acc[i][j][e] is output (row m0+wm+16i+lr, column n0+wn+16j+4g+e)
+  if constexpr (EPI != F32_PLAIN) {
+    f32_epilogue<EPI>(p, acc[0][0], m0 + wm + lr, n0 + (GU ? 0 : wn) + 4 * g, GU && wn, lds + (wm + lr) * 20 + 4 * g, lr == 0, [](f32x4 v) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) v[e] += __shfl_xor(v[e], o, 64);
+      return v;
+    });
+    return;
+  }
   const T *bias = (const T*)p.bias, *R = (const T*)p.R;
   T* C = (T*)p.C;
 #pragma unroll
@@ -160,17 +318,136 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Gemm& p, int tile, float*
   }
 }
 
-template <typename T, int BT, int KS, bool A_KC, bool B_KC, bool VEC>
+template <typename T, int BT, int KS, bool A_KC, bool B_KC, bool VEC, bool SHARES>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Gemm p) {
   constexpr int STAGE = F32Tile<T, BT, KS, A_KC, VEC>::FLOATS + F32Tile<T, BT, KS, B_KC, VEC>::FLOATS;
   __shared__ __align__(16) float lds[2 * STAGE];
-  for (int tile = blockIdx.x; tile < p.tiles_m * p.tiles_n; tile += gridDim.x) gemm_f32_tile<T, BT, KS, A_KC, B_KC, VEC>(p, tile, lds);
+  for (int tile = blockIdx.x; tile < p.tiles_m * p.tiles_n; tile += gridDim.x) gemm_f32_tile<T, BT, KS, A_KC, B_KC, VEC, SHARES>(p, tile, lds);
 }
+
+// ------------------------------------------------- 16 x 16 tiles of fp32 tensors, a share of the contraction per wave
+constexpr int kSharePitch = 20;
+constexpr int kShareFloats = kShares * 16 * kSharePitch;
+constexpr int kOutside = (int)0xFFFFFFF0u;     // a byte offset beyond every descriptor's range: reads zero
+
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+
+// Fragments of 16 rows of an operand, 16 k-values per step: lane (lr, g) holds k = 4g .. 4g+3 of row lr.  Requests are
+// unconditional, so that the compiler counts them and waits for each only where it is used; what lies outside reads zero.
+template <bool KC>
+struct ShareOperand {
+  __amdgpu_buffer_rsrc_t rsrc;
+  int off[KC ? 1 : 4];           // byte offset of this lane's accesses at k = 0
+  int step;                      // bytes per k-value
+  int k4;
+  __device__ __forceinline__ void init(const float* base, int64_t ld, int x0, int X, int K, int lr, int g) {
+    const int64_t skip = KC ? (int64_t)x0 * ld : x0, all = KC ? (int64_t)(X - 1) * ld + K : (int64_t)(K - 1) * ld + X;
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base) + skip, 0, (int)(uint32_t)((all - skip) * 4), 0x00020000);
+    step = KC ? 4 : (int)(ld * 4);
+    k4 = 4 * g;
+#pragma unroll
+    for (int e = 0; e < (KC ? 1 : 4); ++e) off[e] = (int)(uint32_t)((KC ? (int64_t)lr * ld + 4 * g : (int64_t)(4 * g + e) * ld + lr) * 4);
+  }
+  __device__ __forceinline__ f32x4 request(int k, int ke) const {
+    if constexpr (KC) return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, k + k4 < ke ? off[0] + k * 4 : kOutside, 0, 0));
+    f32x4 f;
+#pragma unroll
+    for (int e = 0; e < (KC ? 1 : 4); ++e) f[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, k + k4 + e < ke ? off[e] + k * step : kOutside, 0, 0));
+    return f;
+  }
+};
+
+// A tile is one block of 16 x 16 outputs; each of eight waves takes an eighth of the contraction (share_length), its fragments straight from
+// memory, and the eight sums meet in LDS, added in wave order.  For long contractions over few tiles, which are one chain of
+// latencies: 128 x 256 outputs, K 768 (384): tiles of 32 x 32 8.8 us (5.6), this 5.3 (4.1); 100 x 64, K 1500 16.3 -> 5.7.
+template <bool A_KC, bool B_KC, int EPI>
+__device__ __forceinline__ void gemm_f32_share_tile(const F32Gemm& p, int tile, float* lds) {
+  constexpr int STEPS = 2;                     // k-steps of 16 requested together
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, g = lane >> 4;
+  const int tn = tile / p.tiles_m, tm = tile - tn * p.tiles_m;
+  const int m0 = tm * 16, n0 = tn * 16;
+  const int per = share_length(p.K), kb = wave * per, ke = min(p.K, kb + per);
+  ShareOperand<A_KC> A;
+  ShareOperand<B_KC> B;
+  A.init((const float*)p.A, p.lda, m0, p.M, p.K, lr, g);
+  B.init((const float*)p.B, p.ldb, n0, p.N, p.K, lr, g);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  f32x4 fa[2][STEPS], fb[2][STEPS];            // [buffer][step]
+  auto request = [&](auto buf_, int k0) {
+    constexpr int buf = decltype(buf_)::value;
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) { fa[buf][t] = A.request(k0 + 16 * t, ke); fb[buf][t] = B.request(k0 + 16 * t, ke); }
+  };
+  auto multiply = [&](auto buf_, int k0) {
+    constexpr int buf = decltype(buf_)::value;
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+      if (k0 + 16 * t >= ke) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[buf][t][e], fa[buf][t][e], acc, 0, 0, 0);
+    }
+  };
+  typedef std::integral_constant<int, 0> B0;
+  typedef std::integral_constant<int, 1> B1;
+  request(B0{}, kb);
+  for (int k0 = kb; k0 < ke; k0 += 32 * STEPS) {
+    request(B1{}, k0 + 16 * STEPS);
+    multiply(B0{}, k0);
+    request(B0{}, k0 + 32 * STEPS);
+    multiply(B1{}, k0 + 16 * STEPS);
+  }
+  // acc[e] is output (row lr, column 4g + e)
+  *reinterpret_cast<f32x4*>(lds + (wave * 16 + lr) * kSharePitch + 4 * g) = acc;
+  __syncthreads();
+  if (wave == 0) {
+    f32x4 v = acc;
+#pragma unroll
+    for (int w = 1; w < kShares; ++w) v += *reinterpret_cast<const f32x4*>(lds + (w * 16 + lr) * kSharePitch + 4 * g);
+    f32_epilogue<EPI>(p, v, m0 + lr, n0 + 4 * g, false, nullptr, lr == 0, [](f32x4 x) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) x[e] += __shfl_xor(x[e], o, 64);
+      return x;
+    });
+  }
+  __syncthreads();                             // the next tile's sums take the same place
+}
+
+template <bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(64 * kShares) void gemm_f32_share_kernel(F32Gemm p) {
+  static_assert(EPI != F32_SWIGLU, "a tile of 16 columns holds one half");
+  __shared__ __align__(16) float lds[kShareFloats];
+  for (int tile = blockIdx.x; tile < p.tiles_m * p.tiles_n; tile += gridDim.x) gemm_f32_share_tile<A_KC, B_KC, EPI>(p, tile, lds);
+}
+
+template <int EPI>
+__global__ __launch_bounds__(64 * kShares) void gemm_f32_share_pair_kernel(F32Gemm d, F32Gemm w, int w_first) {
+  __shared__ __align__(16) float lds[kShareFloats];
+  const int nd = d.tiles_m * d.tiles_n, nw = w.tiles_m * w.tiles_n;
+  for (int u = blockIdx.x; u < nd + nw; u += gridDim.x) {
+    const int td = w_first ? u - nw : u, tw = w_first ? u : u - nd;
+    if (td >= 0 && td < nd) gemm_f32_share_tile<true, true, EPI>(d, td, lds);
+    else gemm_f32_share_tile<false, false, F32_PLAIN>(w, tw, lds);
+  }
+}
+
+// Which products are summed in shares, by whatever kernel: a function of the shape (512: two workgroups to a CU of the whole device; operands
+// that 32-bit offsets reach).  They are computed in 16 x 16 tiles where two workgroups to a CU take all of them and a wave
+// has work for its latency; below 128 k-values 32 x 32 tiles are as fast.
+int64_t share_tiles(const F32Gemm& p) { return ceil_div(p.M, 16) * ceil_div(p.N, 16); }
+bool share_order(const F32Gemm& p) {
+  const int64_t rows_a = (int64_t)std::max(p.M, p.K) + 32, rows_b = (int64_t)std::max(p.N, p.K) + 32, lim = (int64_t)1 << 29;
+  return share_tiles(p) <= 512 && rows_a * p.lda + p.K < lim && rows_b * p.ldb + p.K < lim;
+}
+void share_layout(F32Gemm* p) { p->tiles_m = (int)ceil_div(p->M, 16); p->tiles_n = (int)ceil_div(p->N, 16); }
 
 // The input gradient (both operands K-contiguous) and the weight gradient (both K-strided) of a linear layer in one
 // launch of 32 x 32 tiles, those with the longer contraction first: each is a chain of a few tiles' latency that leaves
 // most CUs idle.  Products of a decoder layer of 256 rows, width 128: 6.1 + 5.6 us in two launches, 7.0 in one (a launch less
 // to wait for besides: with the attention's, the layer's step 120 -> 92 us).
+template <int EPI, bool SHARES>
 __global__ __launch_bounds__(256) void gemm_f32_pair_kernel(F32Gemm d, F32Gemm w, int w_first) {
   typedef F32Tile<float, 32, 64, true, true> Contiguous;
   typedef F32Tile<float, 32, 64, false, true> Strided;
@@ -179,9 +456,18 @@ __global__ __launch_bounds__(256) void gemm_f32_pair_kernel(F32Gemm d, F32Gemm w
   const int nd = d.tiles_m * d.tiles_n, nw = w.tiles_m * w.tiles_n;
   for (int u = blockIdx.x; u < nd + nw; u += gridDim.x) {
     const int td = w_first ? u - nw : u, tw = w_first ? u : u - nd;
-    if (td >= 0 && td < nd) gemm_f32_tile<float, 32, 64, true, true, true>(d, td, lds);
-    else gemm_f32_tile<float, 32, 64, false, false, true>(w, tw, lds);
+    if (td >= 0 && td < nd) gemm_f32_tile<float, 32, 64, true, true, true, SHARES, EPI>(d, td, lds);
+    else gemm_f32_tile<float, 32, 64, false, false, true, SHARES>(w, tw, lds);
   }
+}
+
+// The forward product with what stands before and behind it in a layer of the fp32 path: a launch costs 4 us or more however little
+// it does.  The norm is formed again by every tile column (rows of at most kF32NormMax values, read once more from the caches).
+template <int EPI, int NORM, bool SHARES>
+__global__ __launch_bounds__(256) void gemm_f32_layer_kernel(F32Gemm p) {
+  constexpr int STAGE = (NORM ? 0 : F32Tile<float, 32, 64, true, true>::FLOATS) + F32Tile<float, 32, 64, false, true>::FLOATS;
+  __shared__ __align__(16) float lds[2 * STAGE + (NORM ? 32 * kF32NormPitch : 0)];
+  for (int tile = blockIdx.x; tile < p.tiles_m * p.tiles_n; tile += gridDim.x) gemm_f32_tile<float, 32, 64, true, false, true, SHARES, EPI, NORM>(p, tile, lds);
 }
 
 // a function of the shape alone; the order of every sum is the same in both.  Figures in launch_t.
@@ -194,13 +480,27 @@ mosaic_status launch_t(hipStream_t s, int quota, F32Gemm p) {
   // 28.7 / 26.0 (43.9 / 31.1), 576 31.1 / 34.1 (48.9 / 45.2), 1024 53.1 / 44.3 (84.9 / 59.7), 4096 386 / 312; input gradient,
   // 192 tiles 31.0 / 41.8.  bf16 tensors, 256 tiles 33.0 / 39.3, 576 76.5 / 66.0, 1024 122.6 / 82.2.
   const bool large = large_tiles(p.M, p.N);
+  p.in_shares = std::is_same<T, float>::value && !large && share_order(p);
+  if constexpr (std::is_same<T, float>::value && VEC) {
+    if (p.in_shares && p.K >= 128 && share_tiles(p) <= 2 * (int64_t)quota) {
+      share_layout(&p);
+      gemm_f32_share_kernel<A_KC, B_KC, F32_PLAIN><<<p.tiles_m * p.tiles_n, 64 * kShares, 0, s>>>(p);
+      MOSAIC_LAUNCH_CHECK();
+      return MOSAIC_OK;
+    }
+  }
   const int bt = large ? 64 : 32;
   const int64_t tm = ceil_div(p.M, bt), tn = ceil_div(p.N, bt);
   if (tm * tn > INT32_MAX / 2) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "too many output tiles");
   p.tiles_m = (int)tm; p.tiles_n = (int)tn;
   const int grid = grid_for(quota, 4, tm * tn);
-  if (large) gemm_f32_kernel<T, 64, 32, A_KC, B_KC, VEC><<<grid, 256, 0, s>>>(p);
-  else gemm_f32_kernel<T, 32, 64, A_KC, B_KC, VEC><<<grid, 256, 0, s>>>(p);
+  if (large) {
+    gemm_f32_kernel<T, 64, 32, A_KC, B_KC, VEC, false><<<grid, 256, 0, s>>>(p);
+  } else {
+    if constexpr (std::is_same<T, float>::value)
+      if (p.in_shares) gemm_f32_kernel<T, 32, 64, A_KC, B_KC, VEC, true><<<grid, 256, 0, s>>>(p);
+    if (!p.in_shares) gemm_f32_kernel<T, 32, 64, A_KC, B_KC, VEC, false><<<grid, 256, 0, s>>>(p);
+  }
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;
 }
@@ -219,17 +519,73 @@ mosaic_status launch_form(hipStream_t s, int quota, bool a_kc, bool b_kc, const 
 
 }  // namespace
 
-// dX[T,k] = dY W^T and dW[k,n] = X^T dY of fp32 tensors, dense rows, no output on an input; *taken: in one launch
-mosaic_status launch_linear_bwd_f32(hipStream_t s, int quota, int64_t T, int64_t k, int64_t n, const void* X, const void* dY, const void* W,
-                                    void* dX, void* dW, bool* taken) {
+// (norm and) product (and activation) of fp32 tensors, dense rows; *taken: in one launch
+mosaic_status launch_layer_fwd_f32(hipStream_t s, int quota, int norm, int act, int64_t T, int64_t k, int64_t n, float eps, const void* X, const void* gamma,
+                                   const void* beta, void* U, float* stats, const void* W, const void* bias, void* Z, void* A, bool* taken) {
   *taken = false;
-  const uintptr_t all = (uintptr_t)X | (uintptr_t)dY | (uintptr_t)W | (uintptr_t)dX | (uintptr_t)dW;
-  if (T > INT32_MAX || k > INT32_MAX || n > INT32_MAX || k % 4 || n % 4 || all % 16 || large_tiles(T, k) || large_tiles(k, n)) return MOSAIC_OK;
-  auto product = [](const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t M, int64_t N, int64_t K) {
-    return F32Gemm{A, B, nullptr, nullptr, C, (int)M, (int)N, (int)K, lda, ldb, N, (int)ceil_div(M, 32), (int)ceil_div(N, 32)};
+  const bool glu = act == MOSAIC_SWIGLU;
+  const int64_t f = glu ? n / 2 : n;
+  const uintptr_t all = (uintptr_t)X | (uintptr_t)gamma | (uintptr_t)beta | (uintptr_t)U | (uintptr_t)W | (uintptr_t)bias | (uintptr_t)Z | (uintptr_t)A;
+  if (T <= 0 || k <= 0 || n <= 0 || T > INT32_MAX || k > INT32_MAX || n > INT32_MAX || k % 4 || f % 4 || all % 16 || large_tiles(T, n)) return MOSAIC_OK;
+  if (act != -1 && act != MOSAIC_GELU && !glu) return MOSAIC_OK;
+  if (norm && (k > kF32NormMax || (norm != MOSAIC_LAYERNORM && norm != MOSAIC_RMSNORM))) return MOSAIC_OK;
+  F32Gemm p = {};
+  p.A = X; p.B = W; p.bias = bias; p.C = Z; p.C2 = (float*)A; p.M = (int)T; p.N = (int)n; p.K = (int)k; p.lda = k; p.ldb = n; p.ldc = n; p.f = (int)f;
+  p.tiles_m = (int)ceil_div(T, 32); p.tiles_n = (int)(glu ? ceil_div(f, 16) : ceil_div(n, 32));
+  p.in_shares = share_order(p);
+  p.gamma = (const float*)gamma; p.beta = (const float*)beta; p.U = (float*)U; p.stats = stats; p.eps = eps;
+  const int grid = grid_for(quota, 4, (int64_t)p.tiles_m * p.tiles_n);
+  auto go = [&](auto epi, auto shares) {
+    constexpr int EPI = decltype(epi)::value;
+    constexpr bool SHARES = decltype(shares)::value;
+    if (norm == MOSAIC_LAYERNORM) gemm_f32_layer_kernel<EPI, MOSAIC_LAYERNORM, SHARES><<<grid, 256, 0, s>>>(p);
+    else if (norm) gemm_f32_layer_kernel<EPI, MOSAIC_RMSNORM, SHARES><<<grid, 256, 0, s>>>(p);
+    else gemm_f32_layer_kernel<EPI, 0, SHARES><<<grid, 256, 0, s>>>(p);
   };
-  const F32Gemm d = product(dY, n, W, n, dX, T, k, n), w = product(X, k, dY, n, dW, k, n, T);
-  gemm_f32_pair_kernel<<<grid_for(quota, 4, (int64_t)d.tiles_m * d.tiles_n + (int64_t)w.tiles_m * w.tiles_n), 256, 0, s>>>(d, w, T > n);
+  auto launch = [&](auto epi) { if (p.in_shares) go(epi, std::true_type{}); else go(epi, std::false_type{}); };
+  if (glu) launch(std::integral_constant<int, F32_SWIGLU>{});
+  else if (act == MOSAIC_GELU) launch(std::integral_constant<int, F32_GELU>{});
+  else launch(std::integral_constant<int, F32_PLAIN>{});
+  MOSAIC_LAUNCH_CHECK();
+  *taken = true;
+  return MOSAIC_OK;
+}
+
+// dX[T,k] = dY W^T and dW[k,n] = X^T dY of fp32 tensors, dense rows, no output on an input; *taken: in one launch.  act >= 0: X is an
+// activation, the gradient goes on to its input, dZ[T, k] (SwiGLU: [T, 2k]) = act'(Z) dX, and dX is not written; sums (may be null): column sums
+// of dZ over 16 rows each.
+mosaic_status launch_linear_bwd_f32(hipStream_t s, int quota, int64_t T, int64_t k, int64_t n, const void* X, const void* dY, const void* W,
+                                    void* dX, void* dW, bool* taken, int act, const void* Z, void* dZ, float* sums) {
+  *taken = false;
+  const uintptr_t all = (uintptr_t)X | (uintptr_t)dY | (uintptr_t)W | (uintptr_t)dX | (uintptr_t)dW | (uintptr_t)Z | (uintptr_t)dZ | (uintptr_t)sums;
+  if (T > INT32_MAX || k > INT32_MAX || n > INT32_MAX || k % 4 || n % 4 || all % 16 || large_tiles(T, k) || large_tiles(k, n)) return MOSAIC_OK;
+  if (act != -1 && act != MOSAIC_GELU && act != MOSAIC_SWIGLU) return MOSAIC_OK;
+  auto product = [](const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t M, int64_t N, int64_t K) {
+    F32Gemm p = {};
+    p.A = A; p.B = B; p.C = C; p.M = (int)M; p.N = (int)N; p.K = (int)K; p.lda = lda; p.ldb = ldb; p.ldc = N;
+    p.tiles_m = (int)ceil_div(M, 32); p.tiles_n = (int)ceil_div(N, 32);
+    return p;
+  };
+  F32Gemm d = product(dY, n, W, n, dX, T, k, n), w = product(X, k, dY, n, dW, k, n, T);
+  d.Z = (const float*)Z; d.C2 = (float*)dZ; d.sums = sums;
+  d.in_shares = share_order(d);
+  w.in_shares = share_order(w);
+  const bool share = d.in_shares && w.in_shares && std::max(T, n) >= 128 && share_tiles(d) + share_tiles(w) <= 2 * (int64_t)quota;
+  auto launch = [&](auto epi) {
+    constexpr int EPI = decltype(epi)::value;
+    if (share) {
+      share_layout(&d);
+      share_layout(&w);
+      gemm_f32_share_pair_kernel<EPI><<<d.tiles_m * d.tiles_n + w.tiles_m * w.tiles_n, 64 * kShares, 0, s>>>(d, w, T > n);
+    } else {
+      const int grid = grid_for(quota, 4, (int64_t)d.tiles_m * d.tiles_n + (int64_t)w.tiles_m * w.tiles_n);
+      if (d.in_shares || w.in_shares) gemm_f32_pair_kernel<EPI, true><<<grid, 256, 0, s>>>(d, w, T > n);
+      else gemm_f32_pair_kernel<EPI, false><<<grid, 256, 0, s>>>(d, w, T > n);
+    }
+  };
+  if (act == MOSAIC_SWIGLU) launch(std::integral_constant<int, F32_DSWIGLU>{});
+  else if (act == MOSAIC_GELU) launch(std::integral_constant<int, F32_DGELU>{});
+  else launch(std::integral_constant<int, F32_PLAIN>{});
   MOSAIC_LAUNCH_CHECK();
   *taken = true;
   return MOSAIC_OK;
@@ -237,6 +593,7 @@ mosaic_status launch_linear_bwd_f32(hipStream_t s, int quota, int64_t T, int64_t
 
 mosaic_status launch_gemm_f32(hipStream_t s, int quota, int dtype, bool a_kc, bool b_kc, int M, int N, int K, const void* A,
                               int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, const void* bias, const void* R) {
-  const F32Gemm p = {A, B, bias, R, C, M, N, K, lda, ldb, ldc, 0, 0};
+  F32Gemm p = {};
+  p.A = A; p.B = B; p.bias = bias; p.R = R; p.C = C; p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc;
   return dtype == MOSAIC_BF16 ? launch_form<bf16>(s, quota, a_kc, b_kc, p) : launch_form<float>(s, quota, a_kc, b_kc, p);
 }

@@ -40,6 +40,16 @@ mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t 
 mosaic_status launch_linear_bwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t k, int64_t n, const void* X, const void* dY,
                                 const void* W, void* dX, void* dW, void* splitk_scratch, bool dx_first);
 
+// U = norm(X), stats, then Z[T,n] = U W (+ bias) and, act >= 0, A = act(Z): one launch for small fp32 layers, else launch_norm_fwd and
+// launch_gemm or launch_linear_act_fwd
+mosaic_status launch_norm_linear_fwd(hipStream_t s, int quota, int dtype, int norm, int act, int64_t T, int64_t h, int64_t n, float eps, const void* X,
+                                     const void* gamma, const void* beta, void* U, float* stats, const void* W, const void* bias, void* Z, void* A);
+// The backward pass of Y = act(Z) W: dW = act(Z)^T dY with A = act(Z)[T,k], and dZ = act'(Z) (dY W^T) in one launch with it for small fp32 layers, else
+// through dA[T,k].  colsum (may be null; GELU): the column sums of dZ, partial sums in `scratch`, the last pass in `later`.
+struct ColReduceList;
+mosaic_status launch_act_linear_bwd(hipStream_t s, int quota, int dtype, int act, int64_t T, int64_t k, int64_t n, const void* Z, const void* A, const void* dY,
+                                    const void* W, void* dA, void* dZ, void* dW, void* splitk_scratch, void* colsum, void* scratch, ColReduceList* later);
+
 // ------------------------------------------------------------------------- attention
 // packed rows [q (H heads) | k (Hkv heads) | v (Hkv heads)]; Hkv divides H; query head t
 // attends to key/value head t / (H/Hkv)
@@ -67,6 +77,11 @@ struct ColReduceList {
   static constexpr int kMax = 6;
   ColReduce job[kMax];
   int n = 0;
+  // a loss whose partial sums launch_mse left here: loss = loss_scale * their sum, formed beside the column sums
+  const float* loss_partial = nullptr;
+  float* loss = nullptr;
+  int loss_np = 0;
+  float loss_scale = 0.f;
 };
 mosaic_status launch_col_reduce(hipStream_t s, int quota, int dtype, const ColReduceList& list);
 // scratch of launch_norm_bwd: two slabs of partial sums per row partition, a third when dxsum is asked for
@@ -112,7 +127,7 @@ mosaic_status launch_im2col1d(hipStream_t s, int quota, int dtype, int64_t B, in
 mosaic_status launch_col2im1d(hipStream_t s, int quota, int dtype, int64_t B, int L, int C, const void* dP, void* dx);
 size_t mse_scratch_bytes();
 mosaic_status launch_mse(hipStream_t s, int quota, int dtype, int64_t n, const void* y,
-                         const void* target, void* dy, float* loss, void* scratch);
+                         const void* target, void* dy, float* loss, void* scratch, ColReduceList* later = nullptr);
 size_t colsum_scratch_bytes(int64_t n);
 // out[n] = sum over T rows of X[T,n] in a fixed two-level order.
 mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n,

@@ -293,22 +293,22 @@ mosaic_status layers_forward(mosaic_module* m, hipStream_t s, int q, const void*
     const LayerParams& p = m->lp[l];
     const LayerSaved& sv = m->ls[l];
     void* yout = (l + 1 < d.layers) ? W(m, sv.y) : y;
-    MOSAIC_TRY(launch_norm_fwd(s, q, dt, d.norm, T, h, d.eps, xin, P(m, p.n1_g), P(m, p.n1_b), W(m, sv.u1), (float*)W(m, sv.st1)));
-    MOSAIC_TRY(launch_gemm(s, q, dt, true, false, T, qw, h, W(m, sv.u1), h, P(m, p.w_qkv), qw, W(m, sv.qkv), qw, P(m, p.b_qkv), nullptr));
+    MOSAIC_TRY(launch_norm_linear_fwd(s, q, dt, d.norm, -1, T, h, qw, d.eps, xin, P(m, p.n1_g), P(m, p.n1_b), W(m, sv.u1), (float*)W(m, sv.st1),
+                                      P(m, p.w_qkv), P(m, p.b_qkv), W(m, sv.qkv), nullptr));
     if (rope) MOSAIC_TRY(launch_rope(s, q, dt, d.batch, d.seq, d.heads, kvh, dh, +1, W(m, sv.qkv), W(m, m->s_rope)));   // saved rotated
     MOSAIC_TRY(launch_attention_fwd(s, q, dt, d.batch, d.seq, d.heads, kvh, dh, d.causal, W(m, sv.qkv), W(m, sv.o), (float*)W(m, sv.lse)));
     MOSAIC_TRY(launch_gemm(s, q, dt, true, false, T, h, h, W(m, sv.o), h, P(m, p.w_o), h, W(m, sv.x1), h, P(m, p.b_o), xin));
-    MOSAIC_TRY(launch_norm_fwd(s, q, dt, d.norm, T, h, d.eps, W(m, sv.x1), P(m, p.n2_g), P(m, p.n2_b), W(m, sv.u2), (float*)W(m, sv.st2)));
-    const int64_t zf = glu ? 2 * f : f;
     // up projection and activation in one launch where the matrix-core kernel takes it
-    MOSAIC_TRY(launch_linear_act_fwd(s, q, dt, d.act, T, h, zf, W(m, sv.u2), P(m, p.w_1), P(m, p.b_1), W(m, sv.z), W(m, sv.a)));
+    MOSAIC_TRY(launch_norm_linear_fwd(s, q, dt, d.norm, d.act, T, h, glu ? 2 * f : f, d.eps, W(m, sv.x1), P(m, p.n2_g), P(m, p.n2_b), W(m, sv.u2),
+                                      (float*)W(m, sv.st2), P(m, p.w_1), P(m, p.b_1), W(m, sv.z), W(m, sv.a)));
     MOSAIC_TRY(launch_gemm(s, q, dt, true, false, T, h, f, W(m, sv.a), f, P(m, p.w_2), h, yout, h, P(m, p.b_2), W(m, sv.x1)));
     xin = yout;
   }
   return MOSAIC_OK;
 }
 
-mosaic_status layers_backward(mosaic_module* m, hipStream_t s, int q, const void* dy, void* dx) {
+// loss: partial sums of a loss that the last reduction of the top layer finishes; may be null
+mosaic_status layers_backward(mosaic_module* m, hipStream_t s, int q, const void* dy, void* dx, const ColReduceList* loss = nullptr) {
   const mosaic_module_desc& d = m->d;
   const int64_t T = m->T, h = d.hidden, f = d.mlp;
   const int dt = d.dtype;
@@ -324,20 +324,17 @@ mosaic_status layers_backward(mosaic_module* m, hipStream_t s, int q, const void
     const LayerSaved& sv = m->ls[l];
     const void* xin = (l == 0) ? m->last_x : W(m, m->ls[l - 1].y);
     ColReduceList sums;
+    if (loss && l == d.layers - 1) sums = *loss;
     void* gout = (l == 0) ? (dx ? dx : W(m, m->s_g0)) : W(m, (l & 1) ? m->s_g1 : m->s_g0);
-    // MLP down projection
-    MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, f, h, W(m, sv.a), gin, P(m, p.w_2), dA, G(m, p.w_2), W(m, m->s_splitk), true));
+    // MLP down projection and activation
     // Bias gradients are column sums of a layer's output gradient.  Each is formed by the kernel
     // that writes that gradient where there is one of ours: the first norm's backward of the
     // layer above (this layer's incoming gradient), the GELU backward, the second norm's
     // backward.  Only the top layer's incoming gradient and dQKV take a pass of their own.
     if (p.b_2 >= 0 && l == d.layers - 1) MOSAIC_TRY(launch_colsum(s, q, dt, T, h, gin, G(m, p.b_2), W(m, m->s_colsum3), &sums));
-    // activation
-    bool b1_done = false;
-    if (glu) MOSAIC_TRY(launch_swiglu_bwd(s, q, dt, T, f, W(m, sv.z), dA, dZ));
-    else if (d.act == MOSAIC_GELU_TANH) MOSAIC_TRY(launch_gelu_tanh_bwd(s, q, dt, T * f, W(m, sv.z), dA, dZ));
-    else if (p.b_1 >= 0) { MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, f, W(m, sv.z), dA, dZ, G(m, p.b_1), W(m, m->s_colsum), &sums)); b1_done = true; }
-    else MOSAIC_TRY(launch_gelu_bwd(s, q, dt, T * f, W(m, sv.z), dA, dZ));
+    const bool b1_done = d.act == MOSAIC_GELU && p.b_1 >= 0;
+    MOSAIC_TRY(launch_act_linear_bwd(s, q, dt, d.act, T, f, h, W(m, sv.z), W(m, sv.a), gin, P(m, p.w_2), dA, dZ, G(m, p.w_2), W(m, m->s_splitk),
+                                     b1_done ? G(m, p.b_1) : nullptr, b1_done ? W(m, m->s_colsum) : nullptr, &sums));
     // MLP up projection
     if (p.b_1 >= 0 && !b1_done) MOSAIC_TRY(launch_colsum(s, q, dt, T, zf, dZ, G(m, p.b_1), W(m, m->s_colsum), &sums));
     MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, h, zf, W(m, sv.u2), dZ, P(m, p.w_1), dU, G(m, p.w_1), W(m, m->s_splitk), false));
@@ -383,9 +380,9 @@ mosaic_status projector_backward(mosaic_module* m, hipStream_t s, int q, const v
   const int dt = d.dtype;
   void* dA = W(m, m->s_dA); void* dZ = W(m, m->s_dZ);
   ColReduceList sums;
-  MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, no, no, W(m, sv.a), dy, P(m, p.w_2), dA, G(m, p.w_2), W(m, m->s_splitk), true));
   MOSAIC_TRY(launch_colsum(s, q, dt, T, no, dy, G(m, p.b_2), W(m, m->s_colsum2), &sums));
-  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, no, W(m, sv.z), dA, dZ, G(m, p.b_1), W(m, m->s_colsum), &sums));
+  MOSAIC_TRY(launch_act_linear_bwd(s, q, dt, MOSAIC_GELU, T, no, no, W(m, sv.z), W(m, sv.a), dy, P(m, p.w_2), dA, dZ, G(m, p.w_2), W(m, m->s_splitk),
+                                   G(m, p.b_1), W(m, m->s_colsum), &sums));
   MOSAIC_TRY(launch_col_reduce(s, q, dt, sums));
   if (dx) return launch_linear_bwd(s, q, dt, T, ni, no, m->last_x, dZ, P(m, p.w_1), dx, G(m, p.w_1), W(m, m->s_splitk), false);
   return launch_gemm(s, q, dt, false, false, ni, no, T, m->last_x, ni, dZ, no, G(m, p.w_1), no, nullptr, nullptr, W(m, m->s_splitk));
@@ -564,7 +561,7 @@ mosaic_status mosaic_module_forward(mosaic_module* m, int32_t quota, const mosai
   return st;
 }
 
-mosaic_status mosaic_module_backward(mosaic_module* m, int32_t quota, const mosaic_stream* stream, const void* dy, void* dx) {
+static mosaic_status module_backward(mosaic_module* m, int32_t quota, const mosaic_stream* stream, const void* dy, void* dx, const ColReduceList* loss) {
   MOSAIC_TRY(check_bound(m));
   if (!dy) MOSAIC_FAIL(MOSAIC_EINVAL, "null upstream gradient");
   if (!m->forward_done) MOSAIC_FAIL(MOSAIC_EINVAL, "backward called before forward");
@@ -573,7 +570,7 @@ mosaic_status mosaic_module_backward(mosaic_module* m, int32_t quota, const mosa
   hipStream_t s = mosaic_stream_hip(stream);
   switch (m->d.kind) {
     case MOSAIC_ENCODER:
-    case MOSAIC_DECODER: return layers_backward(m, s, q, dy, dx);
+    case MOSAIC_DECODER: return layers_backward(m, s, q, dy, dx, loss);
     case MOSAIC_PROJECTOR: return projector_backward(m, s, q, dy, dx);
     case MOSAIC_PATCH_STEM: return patch_stem_backward(m, s, q, dy, dx);
     case MOSAIC_CONV_STEM: return conv_stem_backward(m, s, q, dy, dx);
@@ -583,6 +580,10 @@ mosaic_status mosaic_module_backward(mosaic_module* m, int32_t quota, const mosa
   }
 }
 
+mosaic_status mosaic_module_backward(mosaic_module* m, int32_t quota, const mosaic_stream* stream, const void* dy, void* dx) {
+  return module_backward(m, quota, stream, dy, dx, nullptr);
+}
+
 mosaic_status mosaic_module_step(mosaic_module* m, int32_t quota, const mosaic_stream* stream, const void* x,
                                  const void* dy, const void* target, void* y, void* dx, float* loss) {
   MOSAIC_TRY(check_bound(m));
@@ -590,12 +591,15 @@ mosaic_status mosaic_module_step(mosaic_module* m, int32_t quota, const mosaic_s
   if (target && !loss) MOSAIC_FAIL(MOSAIC_EINVAL, "a target needs a loss output");
   MOSAIC_TRY(mosaic_module_forward(m, quota, stream, x, y));
   const void* g = dy;
+  ColReduceList loss_sums;
+  const bool layers = m->d.kind == MOSAIC_ENCODER || m->d.kind == MOSAIC_DECODER;      // their backward pass ends in column sums
   if (target) {
     hipStream_t s = mosaic_stream_hip(stream);
-    MOSAIC_TRY(launch_mse(s, quota, m->d.dtype, (int64_t)mosaic_module_output_elems(m), y, target, W(m, m->s_dyloss), loss, W(m, m->s_mse)));
+    MOSAIC_TRY(launch_mse(s, quota, m->d.dtype, (int64_t)mosaic_module_output_elems(m), y, target, W(m, m->s_dyloss), loss, W(m, m->s_mse),
+                          layers ? &loss_sums : nullptr));
     g = W(m, m->s_dyloss);
   }
-  return mosaic_module_backward(m, quota, stream, g, dx);
+  return module_backward(m, quota, stream, g, dx, target && layers ? &loss_sums : nullptr);
 }
 
 size_t mosaic_module_optimizer_state_bytes(const mosaic_module* m, int32_t use_master) {

@@ -82,6 +82,15 @@ def test_stack_step_matches_oracle_and_is_quota_invariant(mb, dtype, cfg):
     m.destroy()
 
 
+# fp32 layers whose norms, activations and products share launches: one row, rows past a tile and a block of 16, MLP widths that end inside a
+# tile of 16 columns of either half, the widest row that the norm keeps in LDS and a wider one, K-tiles that end inside a row,
+# products on both sides of the share rule (512 tiles of 16 x 16)
+@pytest.mark.parametrize("cfg", [dec(1, 1, 64, 4, 36, 1), dec(1, 33, 64, 4, 36, 2), dec(2, 17, 256, 4, 100, 1), dec(1, 40, 272, 4, 272, 1), dec(3, 96, 128, 4, 900, 1),
+                                 enc(1, 1, 64, 4, 100, 1), enc(1, 33, 64, 4, 100, 2), enc(2, 17, 256, 4, 36, 1), enc(1, 40, 272, 4, 300, 1), enc(3, 96, 128, 4, 900, 1)])
+def test_small_f32_layers(mb, cfg):
+    test_stack_step_matches_oracle_and_is_quota_invariant(mb, "f32", cfg)
+
+
 def test_given_upstream_gradient_instead_of_target(mb):
     cfg = dec(1, 32, 64, 2, 96, 1)
     layers = quantize_tree([layer_params(cfg, 3000)], "f32")
