@@ -66,3 +66,10 @@ def test_position_table_in_the_product(B, g, patch, h):
 @pytest.mark.parametrize("B,g,patch,h,offset", [(2, 9, 2, 16, 0), (2, 9, 4, 24, 0), (1, 7, 6, 24, 0), (1, 5, 5, 8, 0), (1, 64, 16, 8, 0), (1, 65, 16, 8, 0), (2, 6, 8, 16, 1)])
 def test_unfolding_by_rows_of_patches(B, g, patch, h, offset):
     test_patch_stem_step("bf16", B, g, patch, h, offset)
+
+
+# position and bias gradient in one pass: positions that make more than one to a partition and a last partition that is short, samples
+# past a batch of eight, a width that ends inside a wave's columns, more samples than the pass takes
+@pytest.mark.parametrize("dtype,B,g,patch,h", [("bf16", 9, 23, 4, 264), ("f32", 3, 24, 2, 132), ("bf16", 17, 3, 4, 72), ("bf16", 33, 3, 4, 72)])
+def test_position_and_bias_gradient(dtype, B, g, patch, h):
+    test_patch_stem_step(dtype, B, g, patch, h, 0)
