@@ -781,20 +781,16 @@ __global__ __launch_bounds__(kThreads) void pos_grad_kernel(const T* __restrict_
   }
 }
 
-// What the gradient of a stem's output gives besides the products: dpos[t, :] = sum over samples (ascending) of dy, and the partial column
-// sums of the bias gradient, of dy itself or (GELU) of dz = dy * gelu'(z) as stored, which is written too.  A wave takes 64 * V columns of
-// `rp` positions and goes through the samples of a position, eight of them requested together; the bias sums run over its positions and
-// samples in that order.  Bound by memory and, as the waves are few, by the latency of their requests: four bytes a lane.  One pass over dy
-// where there were two, and a launch less: patch stem of 16 x 576 x 1024 65.3 -> 61.1 us (eight bytes a lane 61.8), of
-// 4 x 196 x 768 32.8 -> 31.6, audio stem of 8 x 1500 x 1280 531.8 -> 527.6 (532.2).
-template <typename T, int V, bool GELU>
-__global__ __launch_bounds__(kThreads) void stem_grad_kernel(const T* __restrict__ dy, const T* __restrict__ z, T* __restrict__ dz, T* __restrict__ dpos,
-                                                             float* __restrict__ partial, int B, int N, int h, int rp, int np, int ctiles) {
+// What the gradient of a patch stem's output gives besides the product: dpos[t, :] = sum over samples (ascending) of dy, and the partial
+// column sums of the bias gradient.  A wave takes 64 * V columns of `rp` positions and goes through the samples of a position, eight of them
+// requested together; the bias sums run over its positions and samples in that order.  Bound by memory and, as the waves are few, by the
+// latency of their requests: four bytes a lane.  One pass over dy where there were two, and a launch less: the stem's step of
+// 16 x 576 x 1024 65.3 -> 61.1 us (eight bytes a lane 61.8), of 4 x 196 x 768 32.8 -> 31.6.
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void stem_grad_kernel(const T* __restrict__ dy, T* __restrict__ dpos, float* __restrict__ partial, int B, int N, int h,
+                                                             int rp, int np, int ctiles) {
   typedef typename Pack<T, V>::type vec;
   constexpr int ONCE = 8;
-  constexpr bool TAB = GELU && std::is_same<T, bf16>::value;
-  __shared__ float table[TAB ? ErfTable::kEntries : 1];
-  if constexpr (TAB) { ErfTable::fill(table, threadIdx.x, kThreads); __syncthreads(); }
   const int lane = threadIdx.x & 63;
   const int64_t items = (int64_t)np * ctiles, per = (int64_t)N * h;
   for (int64_t it = (int64_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); it < items; it += (int64_t)gridDim.x * kWaves) {
@@ -805,32 +801,14 @@ __global__ __launch_bounds__(kThreads) void stem_grad_kernel(const T* __restrict
       const int64_t at = (int64_t)t * h + c;
       float pos[V] = {};
       for (int b0 = 0; b0 < B; b0 += ONCE) {
-        vec d[ONCE], zv[GELU ? ONCE : 1];
+        vec d[ONCE];
 #pragma unroll
-        for (int u = 0; u < ONCE; ++u)
-          if (b0 + u < B) {
-            d[u] = *reinterpret_cast<const vec*>(dy + (b0 + u) * per + at);
-            if constexpr (GELU) zv[u] = *reinterpret_cast<const vec*>(z + (b0 + u) * per + at);
-          }
+        for (int u = 0; u < ONCE; ++u) if (b0 + u < B) d[u] = *reinterpret_cast<const vec*>(dy + (b0 + u) * per + at);
 #pragma unroll
         for (int u = 0; u < ONCE; ++u)
           if (b0 + u < B) {
 #pragma unroll
-            for (int k = 0; k < V; ++k) pos[k] += pack_get<T, V>(d[u], k);
-            if constexpr (GELU) {
-#pragma clang fp contract(off)          // what is stored is added
-              vec o;
-#pragma unroll
-              for (int k = 0; k < V; ++k) {
-                const float zk = pack_get<T, V>(zv[u], k);
-                pack_set<T, V>(o, k, pack_get<T, V>(d[u], k) * (TAB ? ErfTable::gelu_grad(table, zk) : gelu_grad_f(zk)));
-                col[k] += pack_get<T, V>(o, k);
-              }
-              *reinterpret_cast<vec*>(dz + (b0 + u) * per + at) = o;
-            } else {
-#pragma unroll
-              for (int k = 0; k < V; ++k) col[k] += pack_get<T, V>(d[u], k);
-            }
+            for (int k = 0; k < V; ++k) { pos[k] += pack_get<T, V>(d[u], k); col[k] += pack_get<T, V>(d[u], k); }
           }
       }
       vec o;
@@ -910,9 +888,9 @@ static mosaic_status col_reduce(hipStream_t s, int quota, int dtype, const ColRe
   return launch_col_reduce(s, quota, dtype, one);
 }
 
+int64_t colsum_partition_rows(int64_t T) { return std::max<int64_t>(8, ceil_div(T, kColsumMaxParts)); }
 static inline void col_partition(int64_t T, int* rp, int* np) {
-  int64_t r = ceil_div(T, kColsumMaxParts);
-  if (r < 8) r = 8;
+  const int64_t r = colsum_partition_rows(T);
   *rp = (int)r;
   *np = (int)ceil_div(T, r);
 }
@@ -1210,24 +1188,20 @@ mosaic_status launch_pos_grad(hipStream_t s, int quota, int dtype, int B, int N,
   return MOSAIC_OK;
 }
 
-mosaic_status launch_stem_grad(hipStream_t s, int quota, int dtype, int B, int N, int h, const void* dy, const void* z, void* dz, void* dpos, void* colsum,
-                               void* scratch, ColReduceList* later) {
-  const bool wide = wide_access(h, dtype, dy, dpos) && wide_access(h, dtype, z, dz);
+mosaic_status launch_stem_grad(hipStream_t s, int quota, int dtype, int B, int N, int h, const void* dy, void* dpos, void* colsum, void* scratch) {
   // rows that start off a 16-byte boundary, or more samples than a wave should walk one position after the other
-  if (B <= 0 || N <= 0 || h <= 0 || !wide || B > 32) {
+  if (B <= 0 || N <= 0 || h <= 0 || B > 32 || !wide_access(h, dtype, dy, dpos)) {
     MOSAIC_TRY(launch_pos_grad(s, quota, dtype, B, N, h, dy, dpos));
-    if (z) return launch_gelu_bwd_colsum(s, quota, dtype, (int64_t)B * N, h, z, dy, dz, colsum, scratch, later);
-    return launch_colsum(s, quota, dtype, (int64_t)B * N, h, dy, colsum, scratch, later);
+    return launch_colsum(s, quota, dtype, (int64_t)B * N, h, dy, colsum, scratch);
   }
   const int rp = (int)ceil_div(N, kColsumMaxParts), np = (int)ceil_div(N, rp);
-  auto launch = [&](auto type, auto gelu) {
+  auto launch = [&](auto type) {
     typedef decltype(type) E;
     constexpr int V = 4 / sizeof(E);
     const int ctiles = (int)ceil_div(h, 64 * V), grid = grid_for(quota, 8, ceil_div((int64_t)np * ctiles, kWaves));
-    stem_grad_kernel<E, V, decltype(gelu)::value><<<grid, kThreads, 0, s>>>((const E*)dy, (const E*)z, (E*)dz, (E*)dpos, (float*)scratch, B, N, h, rp, np, ctiles);
+    stem_grad_kernel<E, V><<<grid, kThreads, 0, s>>>((const E*)dy, (E*)dpos, (float*)scratch, B, N, h, rp, np, ctiles);
   };
-  auto of_type = [&](auto type) { if (z) launch(type, std::true_type{}); else launch(type, std::false_type{}); };
-  if (dtype == MOSAIC_BF16) of_type(bf16{}); else of_type(float{});
+  if (dtype == MOSAIC_BF16) launch(bf16{}); else launch(float{});
   MOSAIC_LAUNCH_CHECK();
-  return col_reduce(s, quota, dtype, {(const float*)scratch, np, h, h, h, INT64_MAX, colsum, nullptr, nullptr}, later);
+  return col_reduce(s, quota, dtype, {(const float*)scratch, np, h, h, h, INT64_MAX, colsum, nullptr, nullptr}, nullptr);
 }

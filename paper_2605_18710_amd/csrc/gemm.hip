@@ -1851,11 +1851,11 @@ mosaic_status launch_norm_linear_fwd(hipStream_t s, int quota, int dtype, int no
 
 mosaic_status launch_act_linear_bwd(hipStream_t s, int quota, int dtype, int act, int64_t T, int64_t k, int64_t n, const void* Z, const void* A, const void* dY,
                                     const void* W, void* dA, void* dZ, void* dW, void* splitk_scratch, void* colsum, void* scratch, ColReduceList* later) {
-  const int64_t np = ceil_div(T, 16), es = (int64_t)dtype_size(dtype), zb = T * k * es * (act == MOSAIC_SWIGLU ? 2 : 1), wb = k * n * es;
+  const int64_t np = ceil_div(T, 8), es = (int64_t)dtype_size(dtype), zb = T * k * es * (act == MOSAIC_SWIGLU ? 2 : 1), wb = k * n * es;
   const bool apart = !overlap(dW, wb, A, T * k * es) && !overlap(dW, wb, dY, T * n * es) && !overlap(dW, wb, W, wb) && !overlap(dW, wb, Z, zb) &&
                      !overlap(dW, wb, dZ, zb) && !overlap(dZ, zb, A, T * k * es) && !overlap(dZ, zb, dY, T * n * es) && !overlap(dZ, zb, W, wb) && !overlap(dZ, zb, Z, zb);
   if (dtype == MOSAIC_F32 && apart && T > 0 && k > 0 && n > 0 && (act == MOSAIC_GELU || act == MOSAIC_SWIGLU) && later && later->n < ColReduceList::kMax &&
-      (!colsum || (size_t)np * (size_t)k * sizeof(float) <= colsum_scratch_bytes(k)) && pair_enabled()) {
+      (!colsum || colsum_partition_rows(T) == 8) && pair_enabled()) {
     bool taken;
     MOSAIC_TRY(launch_linear_bwd_f32(s, quota, T, k, n, A, dY, W, dA, dW, &taken, act, Z, dZ, colsum ? (float*)scratch : nullptr));
     if (taken) {

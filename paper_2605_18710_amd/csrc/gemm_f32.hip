@@ -33,7 +33,7 @@ struct F32Gemm {
   // what the epilogues and the norm in front take (fp32 tensors, rows of whole 16-byte pieces)
   const float* Z;            // the stored input of the activation whose derivative is applied
   float* C2;                 // the activation, or the gradient behind the derivative
-  float* sums;               // column sums of C2 over 16 rows each, [M / 16 rounded up][N]
+  float* sums;               // column sums of C2 over 8 rows each, [M / 8 rounded up][N]
   int f;                     // SwiGLU: width of the gate half
   const float *gamma, *beta; // A is the normalised input: U = norm(A) is formed here
   float *U, *stats;
@@ -153,9 +153,10 @@ __device__ __forceinline__ void f32_norm_panel(const F32Gemm& p, int m0, bool fi
 }
 
 // What follows a product of fp32 tensors, for columns c .. c+3 of a row.  up: (SwiGLU) they belong to the up half, whose lanes hand them to
-// the gate half's through `mail`; every lane of the workgroup comes here.  sum_rows adds a value over the 16 rows of a block.
-template <int EPI, typename SumRows>
-__device__ __forceinline__ void f32_epilogue(const F32Gemm& p, f32x4 v, int row, int c, bool up, float* mail, bool first_row, const SumRows& sum_rows) {
+// the gate half's through `mail`; every lane of the workgroup comes here.  Lane (lr, g) of a wave: row lr of a block of 16 rows that starts
+// at a multiple of 16, columns 4g .. 4g+3 of a block of 16.
+template <int EPI>
+__device__ __forceinline__ void f32_epilogue(const F32Gemm& p, f32x4 v, int row, int c, bool up, float* mail) {
   constexpr bool GU = EPI == F32_SWIGLU;
   const int width = GU ? p.f : p.N, col = up ? p.f + c : c;
   const bool in = row < p.M && c < width;
@@ -194,9 +195,14 @@ __device__ __forceinline__ void f32_epilogue(const F32Gemm& p, f32x4 v, int row,
       for (int e = 0; e < 4; ++e) a2[e] = v[e] * gelu_grad_f(z[e]);
       *at(p.C2, p.N, c) = a2;
     }
-    if (p.sums) {                                      // of what is stored
-      a2 = sum_rows(a2);
-      if (first_row && in) *reinterpret_cast<f32x4*>(p.sums + (int64_t)(row >> 4) * p.N + c) = a2;
+    if (p.sums) {                                      // of what is stored, eight rows in ascending order: the partitions of launch_colsum
+      const int first = threadIdx.x & 56;              // the lane of these columns in the first of the eight rows
+      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] += __shfl(a2[e], first + r, 64);
+      if (in && (row & 7) == 0) *reinterpret_cast<f32x4*>(p.sums + (int64_t)(row >> 3) * p.N + c) = sum;
     }
   }
   if constexpr (EPI == F32_DSWIGLU) {
@@ -280,13 +286,7 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Gemm& p, int tile, float*
   __syncthreads();                       // the next tile writes stage 0
   // acc[i][j][e] is output (row m0+wm+16i+lr, column n0+wn+16j+4g+e)
   if constexpr (EPI != F32_PLAIN) {
-    f32_epilogue<EPI>(p, acc[0][0], m0 + wm + lr, n0 + (GU ? 0 : wn) + 4 * g, GU && wn, lds + (wm + lr) * 20 + 4 * g, lr == 0, [](f32x4 v) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) v[e] += __shfl_xor(v[e], o, 64);
-      return v;
-    });
+    f32_epilogue<EPI>(p, acc[0][0], m0 + wm + lr, n0 + (GU ? 0 : wn) + 4 * g, GU && wn, lds + (wm + lr) * 20 + 4 * g);
     return;
   }
   const T *bias = (const T*)p.bias, *R = (const T*)p.R;
@@ -404,13 +404,7 @@ __device__ __forceinline__ void gemm_f32_share_tile(const F32Gemm& p, int tile, 
     f32x4 v = acc;
 #pragma unroll
     for (int w = 1; w < kShares; ++w) v += *reinterpret_cast<const f32x4*>(lds + (w * 16 + lr) * kSharePitch + 4 * g);
-    f32_epilogue<EPI>(p, v, m0 + lr, n0 + 4 * g, false, nullptr, lr == 0, [](f32x4 x) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) x[e] += __shfl_xor(x[e], o, 64);
-      return x;
-    });
+    f32_epilogue<EPI>(p, v, m0 + lr, n0 + 4 * g, false, nullptr);
   }
   __syncthreads();                             // the next tile's sums take the same place
 }
@@ -553,7 +547,7 @@ mosaic_status launch_layer_fwd_f32(hipStream_t s, int quota, int norm, int act, 
 
 // dX[T,k] = dY W^T and dW[k,n] = X^T dY of fp32 tensors, dense rows, no output on an input; *taken: in one launch.  act >= 0: X is an
 // activation, the gradient goes on to its input, dZ[T, k] (SwiGLU: [T, 2k]) = act'(Z) dX, and dX is not written; sums (may be null): column sums
-// of dZ over 16 rows each.
+// of dZ over 8 rows each.
 mosaic_status launch_linear_bwd_f32(hipStream_t s, int quota, int64_t T, int64_t k, int64_t n, const void* X, const void* dY, const void* W,
                                     void* dX, void* dW, bool* taken, int act, const void* Z, void* dZ, float* sums) {
   *taken = false;

@@ -129,6 +129,7 @@ size_t mse_scratch_bytes();
 mosaic_status launch_mse(hipStream_t s, int quota, int dtype, int64_t n, const void* y,
                          const void* target, void* dy, float* loss, void* scratch, ColReduceList* later = nullptr);
 size_t colsum_scratch_bytes(int64_t n);
+int64_t colsum_partition_rows(int64_t T);      // rows of a partition; each is summed in ascending order (colsum_quarters aside)
 // out[n] = sum over T rows of X[T,n] in a fixed two-level order.
 mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n,
                             const void* X, void* out, void* scratch, ColReduceList* later = nullptr);
@@ -143,10 +144,8 @@ mosaic_status launch_add_pos(hipStream_t s, int quota, int dtype, int B, int N, 
 // dpos[t,:] = sum_b dy[b*N+t,:] in ascending b
 mosaic_status launch_pos_grad(hipStream_t s, int quota, int dtype, int B, int N, int h,
                               const void* dy, void* dpos);
-// The backward pass of Y[b*N+t, :] = V[b*N+t, :] + pos[t, :], where V = X W + bias or (z not null) V = gelu(Z), Z = X W + bias: dpos as launch_pos_grad,
-// dz = dy * gelu'(z) in the second case, and colsum[h], the column sums of dy or of dz.  scratch: colsum_scratch_bytes(h)
-mosaic_status launch_stem_grad(hipStream_t s, int quota, int dtype, int B, int N, int h, const void* dy, const void* z, void* dz, void* dpos, void* colsum,
-                               void* scratch, ColReduceList* later = nullptr);
+// launch_pos_grad, and colsum[h] = the column sums of dy over all positions and samples; scratch: colsum_scratch_bytes(h)
+mosaic_status launch_stem_grad(hipStream_t s, int quota, int dtype, int B, int N, int h, const void* dy, void* dpos, void* colsum, void* scratch);
 // out rows: per sample b, [0,n_b) from img_tok, [n_b,N) from table[ids]; n_b = n_img, or
 // counts[b] (clamped to [0,n_img]) when counts is given; ids is [B, N-n_img] without counts and
 // one id per sequence position, [B, N], with them

@@ -407,7 +407,7 @@ mosaic_status patch_stem_backward(mosaic_module* m, hipStream_t s, int q, const 
   if (dx) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "the patch stem has no input gradient");
   const void* tokens = d.patch > 0 ? W(m, m->s_patches) : m->last_x;
   MOSAIC_TRY(launch_gemm(s, q, d.dtype, false, false, d.in_dim, d.hidden, m->T, tokens, patch_ld(d), dy, d.hidden, G(m, p.w_1), d.hidden, nullptr, nullptr, W(m, m->s_splitk)));
-  return launch_stem_grad(s, q, d.dtype, d.batch, d.seq, d.hidden, dy, nullptr, nullptr, G(m, p.w_2), G(m, p.b_1), W(m, m->s_colsum));
+  return launch_stem_grad(s, q, d.dtype, d.batch, d.seq, d.hidden, dy, G(m, p.w_2), G(m, p.b_1), W(m, m->s_colsum));
 }
 
 // conv stem: each convolution is a three-tap gather followed by a linear layer
@@ -429,7 +429,8 @@ mosaic_status conv_stem_backward(mosaic_module* m, hipStream_t s, int q, const v
   const int64_t T = m->T, Tin = 2 * T;
   void* sk = W(m, m->s_splitk);
   ColReduceList sums;
-  MOSAIC_TRY(launch_stem_grad(s, q, dt, d.batch, Lo, h, dy, W(m, m->c_z2), W(m, m->c_dz2), G(m, p.w_o), G(m, p.b_2), W(m, m->s_colsum2), &sums));
+  MOSAIC_TRY(launch_pos_grad(s, q, dt, d.batch, Lo, h, dy, G(m, p.w_o)));
+  MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, T, h, W(m, m->c_z2), dy, W(m, m->c_dz2), G(m, p.b_2), W(m, m->s_colsum2), &sums));
   MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, 3 * h, h, W(m, m->c_p2), W(m, m->c_dz2), P(m, p.w_2), W(m, m->c_dp2), G(m, p.w_2), sk, false));
   MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, Tin, h, W(m, m->c_z1), W(m, m->c_dp2), W(m, m->c_dz1), G(m, p.b_1), W(m, m->s_colsum), &sums, Lo));
   MOSAIC_TRY(launch_col_reduce(s, q, dt, sums));

@@ -196,12 +196,6 @@ def test_conv_stem_at_sample_ends(mb, dtype, B, N, C, h):
     test_conv_stem_matches_oracle_and_is_quota_invariant(mb, dtype, B, N, C, h)
 
 
-# GELU's derivative, position and bias gradient in one pass: more positions than partitions, samples past a batch of eight, more than it takes
-@pytest.mark.parametrize("dtype,B,N,C,h", [("bf16", 9, 520, 16, 136), ("f32", 2, 515, 8, 72), ("bf16", 33, 5, 16, 64)])
-def test_conv_stem_gradient_of_positions(mb, dtype, B, N, C, h):
-    test_conv_stem_matches_oracle_and_is_quota_invariant(mb, dtype, B, N, C, h)
-
-
 @pytest.mark.parametrize("dtype,n,master", [("f32", 4 * 1031, False), ("bf16", 8 * 4099, False), ("bf16", 8 * 4099, True), ("bf16", 4 * 4099, True)])
 def test_adamw_steps(mb, dtype, n, master):
     hp = dict(lr=3e-3, beta1=0.9, beta2=0.95, eps=1e-8, weight_decay=0.05)
