@@ -76,6 +76,86 @@ __global__ __launch_bounds__(kThreads) void norm_fwd_kernel(
   }
 }
 
+// ------------------------------------------------------------------------ column sums
+// Partial column sums of a row partition: a lane owns V columns and adds the rows in ascending order, ONCE of them requested
+// together (request(row, column)) and then used (use(what was requested, row, column, sums)).  A wave takes 64 * V columns
+// of a partition; with QUARTERS (colsum_quarters says where) the four waves of a workgroup take a quarter of its rows each, and
+// the four sums are added in the order of the rows.
+// block, blocks: this workgroup's number among those that share the pass.
+template <int V, int ONCE, bool QUARTERS, typename Request, typename Use>
+__device__ __forceinline__ void column_sums(int block, int blocks, int64_t rows, int64_t n, int rp, int np, int ctiles, float* __restrict__ partial,
+                                            const Request& request, const Use& use) {
+  static_assert(!QUARTERS || V % 4 == 0, "the quarters' sums pass through LDS in pieces of four");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t items = (int64_t)np * ctiles, step = QUARTERS ? blocks : (int64_t)blocks * kWaves;
+  for (int64_t it = QUARTERS ? block : (int64_t)block * kWaves + wave; it < items; it += step) {
+    const int p = (int)(it / ctiles), ct = (int)(it - (int64_t)p * ctiles);
+    const int64_t c = ((int64_t)ct * 64 + lane) * V;
+    int64_t r = (int64_t)p * rp, r1 = r + rp < rows ? r + rp : rows;
+    if constexpr (QUARTERS) {
+      const int64_t per = (r1 - r + 3) >> 2;
+      r += wave * per;
+      r1 = r + per < r1 ? r + per : r1;
+    }
+    float acc[V] = {};
+    if (c < n) {
+      decltype(request(r, c)) q[ONCE];
+      for (; r + ONCE <= r1; r += ONCE) {
+#pragma unroll
+        for (int u = 0; u < ONCE; ++u) q[u] = request(r + u, c);
+#pragma unroll
+        for (int u = 0; u < ONCE; ++u) use(q[u], r + u, c, acc);
+      }
+      if (r < r1) {
+#pragma unroll
+        for (int u = 0; u < ONCE - 1; ++u) if (r + u < r1) q[u] = request(r + u, c);
+#pragma unroll
+        for (int u = 0; u < ONCE - 1; ++u) if (r + u < r1) use(q[u], r + u, c, acc);
+      }
+    }
+    if constexpr (QUARTERS) {
+      __shared__ float4 red[3][V / 4][64];
+      if (wave > 0) {
+#pragma unroll
+        for (int j = 0; j < V / 4; ++j) red[wave - 1][j][lane] = make_float4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
+      }
+      __syncthreads();
+      if (wave == 0) {
+#pragma unroll
+        for (int j = 0; j < V / 4; ++j)
+#pragma unroll
+          for (int w = 0; w < 3; ++w) { const float4 o = red[w][j][lane]; acc[4 * j] += o.x; acc[4 * j + 1] += o.y; acc[4 * j + 2] += o.z; acc[4 * j + 3] += o.w; }
+      }
+      __syncthreads();
+    }
+    if (c < n && (!QUARTERS || wave == 0)) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) partial[(int64_t)p * n + c + k] = acc[k];
+    }
+  }
+}
+
+template <typename T, bool QUARTERS>
+__device__ __forceinline__ void plain_column_sums(int block, int blocks, const T* __restrict__ X, float* __restrict__ partial, int64_t rows, int64_t n, int rp,
+                                                  int np, int ctiles) {
+  constexpr int V = Vec16<T>::N;
+  typedef typename Pack<T, V>::type vec;
+  column_sums<V, QUARTERS ? 4 : 8, QUARTERS>(block, blocks, rows, n, rp, np, ctiles, partial, [&](int64_t r, int64_t c) { return *reinterpret_cast<const vec*>(X + r * n + c); },
+                           [&](const vec& x, int64_t, int64_t, float (&acc)[V]) {
+#pragma unroll
+                             for (int k = 0; k < V; ++k) acc[k] += pack_get<T, V>(x, k);
+                           });
+}
+// The first `blocks` workgroups of a launch that takes a ColSumJob along form its sums; true in those.  A pass of its own costs a launch: layers of
+// 1568 rows, width 768 (two; three such passes) 480.0 -> 473.4 us, projector 768 -> 2048 117.1 -> 114.5, 9216 rows, width 1024, 1071 -> 1063.
+struct Along { ColSumJob job; int blocks; };
+template <typename T>
+__device__ __forceinline__ bool sums_along(const Along& a) {
+  if ((int)blockIdx.x >= a.blocks) return false;
+  plain_column_sums<T, false>(blockIdx.x, a.blocks, (const T*)a.job.X, a.job.partial, a.job.rows, a.job.n, a.job.rp, a.job.np, a.job.ctiles);
+  return true;
+}
+
 // ----------------------------------------------------------------------- norm backward
 // dx: one wave per row, the row of x and dy held in registers (read once), optional
 // residual added on the way out.
@@ -151,7 +231,8 @@ template <typename T, int NORM, int NV, bool CS = false>
 __global__ __launch_bounds__(kThreads) void norm_bwd_fused_kernel(
     const T* __restrict__ x, const T* __restrict__ gamma, const float* __restrict__ stats,
     const T* __restrict__ dy, const T* __restrict__ R, T* __restrict__ dx, float* __restrict__ scratch,
-    int64_t rows, int h, int rp, int np) {
+    int64_t rows, int h, int rp, int np, Along along) {
+  if (sums_along<T>(along)) return;
   constexpr int VN = Vec16<T>::N;
   constexpr int NSUM = (NORM == MOSAIC_LAYERNORM) ? 2 : 1;
   constexpr int NSLAB = CS ? 3 : 2;                    // slabs per partition in scratch
@@ -164,7 +245,7 @@ __global__ __launch_bounds__(kThreads) void norm_bwd_fused_kernel(
     const int c = (j * 64 + lane) * VN;
     if (c < h) g[j].load(gamma + c);
   }
-  for (int p = blockIdx.x; p < np; p += gridDim.x) {
+  for (int p = (int)blockIdx.x - along.blocks; p < np; p += (int)gridDim.x - along.blocks) {
     float ag[NV][VN], ab[NSUM == 2 ? NV : 1][VN], ax[CS ? NV : 1][VN];
 #pragma unroll
     for (int j = 0; j < NV; ++j)
@@ -417,63 +498,6 @@ __global__ __launch_bounds__(kThreads) void gelu_bwd_kernel(const T* __restrict_
   }
 }
 
-// Partial column sums of a row partition: a lane owns V columns and adds the rows in ascending order, ONCE of them requested
-// together (request(row, column)) and then used (use(what was requested, row, column, sums)).  A wave takes 64 * V columns
-// of a partition; with QUARTERS (colsum_quarters says where) the four waves of a workgroup take a quarter of its rows each, and
-// the four sums are added in the order of the rows.
-template <int V, int ONCE, bool QUARTERS, typename Request, typename Use>
-__device__ __forceinline__ void column_sums(int64_t rows, int64_t n, int rp, int np, int ctiles, float* __restrict__ partial, const Request& request,
-                                            const Use& use) {
-  static_assert(!QUARTERS || V % 4 == 0, "the quarters' sums pass through LDS in pieces of four");
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t items = (int64_t)np * ctiles, step = QUARTERS ? gridDim.x : (int64_t)gridDim.x * kWaves;
-  for (int64_t it = QUARTERS ? blockIdx.x : (int64_t)blockIdx.x * kWaves + wave; it < items; it += step) {
-    const int p = (int)(it / ctiles), ct = (int)(it - (int64_t)p * ctiles);
-    const int64_t c = ((int64_t)ct * 64 + lane) * V;
-    int64_t r = (int64_t)p * rp, r1 = r + rp < rows ? r + rp : rows;
-    if constexpr (QUARTERS) {
-      const int64_t per = (r1 - r + 3) >> 2;
-      r += wave * per;
-      r1 = r + per < r1 ? r + per : r1;
-    }
-    float acc[V] = {};
-    if (c < n) {
-      decltype(request(r, c)) q[ONCE];
-      for (; r + ONCE <= r1; r += ONCE) {
-#pragma unroll
-        for (int u = 0; u < ONCE; ++u) q[u] = request(r + u, c);
-#pragma unroll
-        for (int u = 0; u < ONCE; ++u) use(q[u], r + u, c, acc);
-      }
-      if (r < r1) {
-#pragma unroll
-        for (int u = 0; u < ONCE - 1; ++u) if (r + u < r1) q[u] = request(r + u, c);
-#pragma unroll
-        for (int u = 0; u < ONCE - 1; ++u) if (r + u < r1) use(q[u], r + u, c, acc);
-      }
-    }
-    if constexpr (QUARTERS) {
-      __shared__ float4 red[3][V / 4][64];
-      if (wave > 0) {
-#pragma unroll
-        for (int j = 0; j < V / 4; ++j) red[wave - 1][j][lane] = make_float4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
-      }
-      __syncthreads();
-      if (wave == 0) {
-#pragma unroll
-        for (int j = 0; j < V / 4; ++j)
-#pragma unroll
-          for (int w = 0; w < 3; ++w) { const float4 o = red[w][j][lane]; acc[4 * j] += o.x; acc[4 * j + 1] += o.y; acc[4 * j + 2] += o.z; acc[4 * j + 3] += o.w; }
-      }
-      __syncthreads();
-    }
-    if (c < n && (!QUARTERS || wave == 0)) {
-#pragma unroll
-      for (int k = 0; k < V; ++k) partial[(int64_t)p * n + c + k] = acc[k];
-    }
-  }
-}
-
 // dz = da * gelu'(z) and, in the same pass, the partial column sums of dz as stored (the bias
 // gradient of the linear layer that produced z), in the order of launch_colsum over the stored dz, so the sums have the same bits.
 // Bound by memory where waves are many, by the chain of one wave where they are few: 8 bytes a lane and four rows at once in the first
@@ -488,13 +512,14 @@ __device__ __forceinline__ void column_sums(int64_t rows, int64_t n, int rp, int
 template <typename T, int V, int ONCE, bool QUARTERS, bool TAPS>
 __global__ __launch_bounds__(kThreads) void gelu_bwd_colsum_kernel(const T* __restrict__ z, const T* __restrict__ da,
                                                                    T* __restrict__ dz, float* __restrict__ partial,
-                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles, int lo, uint64_t m_lo) {
+                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles, int lo, uint64_t m_lo, Along along) {
+  if (sums_along<T>(along)) return;
   typedef typename Pack<T, V>::type vec;
   constexpr bool TAB = std::is_same<T, bf16>::value;
   __shared__ float table[TAB ? ErfTable::kEntries : 1];
   if constexpr (TAB) { ErfTable::fill(table, threadIdx.x, kThreads); __syncthreads(); }
   struct Req { vec z, d, d2; bool two; };
-  column_sums<V, ONCE, QUARTERS>(rows, n, rp, np, ctiles, partial, [&](int64_t r, int64_t c) {
+  column_sums<V, ONCE, QUARTERS>((int)blockIdx.x - along.blocks, (int)gridDim.x - along.blocks, rows, n, rp, np, ctiles, partial, [&](int64_t r, int64_t c) {
     Req q;
     q.z = *reinterpret_cast<const vec*>(z + r * n + c);
     if constexpr (TAPS) {
@@ -610,13 +635,7 @@ constexpr int kNormFusedMaxNV = 8;   // LayerNorm; RMSNorm (one sum per column) 
 template <typename T, bool QUARTERS>
 __global__ __launch_bounds__(kThreads) void colsum_partial_kernel(const T* __restrict__ X, float* __restrict__ partial,
                                                                   int64_t rows, int64_t n, int rp, int np, int ctiles) {
-  constexpr int V = Vec16<T>::N;
-  typedef typename Pack<T, V>::type vec;
-  column_sums<V, QUARTERS ? 4 : 8, QUARTERS>(rows, n, rp, np, ctiles, partial, [&](int64_t r, int64_t c) { return *reinterpret_cast<const vec*>(X + r * n + c); },
-                           [&](const vec& x, int64_t, int64_t, float (&acc)[V]) {
-#pragma unroll
-                             for (int k = 0; k < V; ++k) acc[k] += pack_get<T, V>(x, k);
-                           });
+  plain_column_sums<T, QUARTERS>(blockIdx.x, gridDim.x, X, partial, rows, n, rp, np, ctiles);
 }
 
 // The sums of column_sums with QUARTERS, by one wave: two rows of each quarter are requested together.  32768 x 2048 on 256, 128,
@@ -870,7 +889,16 @@ mosaic_status launch_norm_fwd(hipStream_t s, int quota, int dtype, int norm, int
   return norm_fwd_t<float>(s, quota, norm, T, h, eps, (const float*)x, (const float*)gamma, (const float*)beta, (float*)y, stats);
 }
 
+static mosaic_status launch_pending(hipStream_t s, int quota, int dtype, const ColSumJob& j) {
+  if (j.np == 0) return MOSAIC_OK;
+  const int grid = grid_for(quota, 8, ceil_div((int64_t)j.np * j.ctiles, kWaves));
+  if (dtype == MOSAIC_BF16) colsum_partial_kernel<bf16, false><<<grid, kThreads, 0, s>>>((const bf16*)j.X, j.partial, j.rows, j.n, j.rp, j.np, j.ctiles);
+  else colsum_partial_kernel<float, false><<<grid, kThreads, 0, s>>>((const float*)j.X, j.partial, j.rows, j.n, j.rp, j.np, j.ctiles);
+  MOSAIC_LAUNCH_CHECK();
+  return MOSAIC_OK;
+}
 mosaic_status launch_col_reduce(hipStream_t s, int quota, int dtype, const ColReduceList& list) {
+  MOSAIC_TRY(launch_pending(s, quota, dtype, list.pending));
   int64_t total = 0;
   for (int i = 0; i < list.n; ++i) total += ceil_div(list.job[i].ncols, 32);
   if (total == 0 && !list.loss) return MOSAIC_OK;
@@ -879,6 +907,15 @@ mosaic_status launch_col_reduce(hipStream_t s, int quota, int dtype, const ColRe
   else col_reduce_kernel<float><<<grid, kThreads, 0, s>>>(list, total);
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;
+}
+// the pending sums of a layer, to go with the launch at hand
+static Along take_along(int quota, ColReduceList* later) {
+  Along a = {};
+  if (!later || later->pending.np == 0) return a;
+  a.job = later->pending;
+  a.blocks = grid_for(quota, 8, ceil_div((int64_t)a.job.np * a.job.ctiles, kWaves));
+  later->pending = ColSumJob();
+  return a;
 }
 // now, or with the rest of `later`
 static mosaic_status col_reduce(hipStream_t s, int quota, int dtype, const ColReduce& r, ColReduceList* later) {
@@ -913,7 +950,8 @@ static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows
   if (dxsum && norm == MOSAIC_LAYERNORM && nv <= kNormDxSumMaxNV) {
     // one pass that also sums the columns of dx
     const int gf = grid_for(quota, 8, np);
-#define LC(NVC) norm_bwd_fused_kernel<T, MOSAIC_LAYERNORM, NVC, true><<<gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np)
+    const Along along = take_along(quota, later);
+#define LC(NVC) norm_bwd_fused_kernel<T, MOSAIC_LAYERNORM, NVC, true><<<along.blocks + gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np, along)
     switch (nv) {
       case 1: LC(1); break;
       case 2: LC(2); break;
@@ -925,17 +963,23 @@ static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows
     return col_reduce(s, quota, dtype, {scratch, np, 3 * h, 3 * h, h, 2 * h, dgamma, dbeta, dxsum}, later);
   }
   const ColReduce sums = {scratch, np, 2 * h, 2 * h, h, INT64_MAX, dgamma, norm == MOSAIC_LAYERNORM ? dbeta : nullptr, nullptr};
+  const bool fused = nv <= kNormFusedMaxNV || norm == MOSAIC_RMSNORM;
+  if (later && (dxsum || !fused)) {      // no kernel below takes them along, and dx may lie on what they are formed of
+    MOSAIC_TRY(launch_pending(s, quota, dtype, later->pending));
+    later->pending = ColSumJob();
+  }
   if (dxsum) later = nullptr;            // the pass over dx below writes its partial sums into the same scratch
   // no kernel that sums dx on the way for this norm or width: the sums take a pass of their own, afterwards
   auto sum_dx = [&]() -> mosaic_status { return dxsum ? launch_colsum(s, quota, dtype, rows, h, dx, dxsum, scratch) : MOSAIC_OK; };
-  if (nv <= kNormFusedMaxNV || norm == MOSAIC_RMSNORM) {
+  if (fused) {
     // one pass: x and dy are read once for dx and for the column sums
     const int gf = grid_for(quota, 8, np);
+    const Along along = take_along(quota, later);
 #define LF(NVC)                                                                                       \
     if (norm == MOSAIC_LAYERNORM)                                                                     \
-      norm_bwd_fused_kernel<T, MOSAIC_LAYERNORM, NVC><<<gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np); \
+      norm_bwd_fused_kernel<T, MOSAIC_LAYERNORM, NVC><<<along.blocks + gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np, along); \
     else                                                                                              \
-      norm_bwd_fused_kernel<T, MOSAIC_RMSNORM, NVC><<<gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np)
+      norm_bwd_fused_kernel<T, MOSAIC_RMSNORM, NVC><<<along.blocks + gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np, along)
     switch (nv) {
       case 1: LF(1); break;
       case 2: LF(2); break;
@@ -945,7 +989,7 @@ static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows
       case 6: LF(6); break;
       case 8: LF(8); break;
       default:
-        norm_bwd_fused_kernel<T, MOSAIC_RMSNORM, 10><<<gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np);
+        norm_bwd_fused_kernel<T, MOSAIC_RMSNORM, 10><<<along.blocks + gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np, along);
         break;
     }
 #undef LF
@@ -1067,11 +1111,16 @@ size_t colsum_scratch_bytes(int64_t n) { return (size_t)kColsumMaxParts * (size_
 static bool colsum_quarters(int rp, int64_t n) { return rp >= 28 && n >= 2048; }
 
 mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n, const void* X, void* out,
-                            void* scratch, ColReduceList* later) {
+                            void* scratch, ColReduceList* later, bool in_passing) {
   EW_CHECK_VEC(n, dtype);
   if (n == 0) return MOSAIC_OK;
   int rp, np;
   col_partition(T, &rp, &np);
+  if (in_passing && later && later->n < ColReduceList::kMax && later->pending.np == 0 && np > 0 && !colsum_quarters(rp, n)) {
+    later->pending.X = X; later->pending.partial = (float*)scratch; later->pending.rows = T; later->pending.n = n;
+    later->pending.rp = rp; later->pending.np = np; later->pending.ctiles = (int)ceil_div(n, (int64_t)64 * vn__);
+    np = -np;
+  }
   if (np > 0) {
     const int ctiles = (int)ceil_div(n, (int64_t)64 * vn__);
     // One wave's requests go to four rows a quarter of a partition apart.  Where that is a multiple of 128 KB and the CUs are many, the four
@@ -1088,7 +1137,7 @@ mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int6
     if (dtype == MOSAIC_BF16) launch(bf16{}); else launch(float{});
     MOSAIC_LAUNCH_CHECK();
   }
-  return col_reduce(s, quota, dtype, {(const float*)scratch, np, n, n, n, INT64_MAX, out, nullptr, nullptr}, later);
+  return col_reduce(s, quota, dtype, {(const float*)scratch, np < 0 ? -np : np, n, n, n, INT64_MAX, out, nullptr, nullptr}, later);
 }
 
 mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n, const void* z,
@@ -1105,7 +1154,8 @@ mosaic_status launch_gelu_bwd_colsum(hipStream_t s, int quota, int dtype, int64_
       constexpr int V = decltype(bytes)::value / sizeof(E);
       constexpr bool Q = decltype(quarters)::value;
       const int ctiles = (int)ceil_div(n, (int64_t)64 * V), grid = grid_for(quota, 8, ceil_div((int64_t)np * ctiles, Q ? 1 : kWaves));
-      gelu_bwd_colsum_kernel<E, V, decltype(once)::value, Q, decltype(taps)::value><<<grid, kThreads, 0, s>>>((const E*)z, (const E*)da, (E*)dz, (float*)scratch, T, n, rp, np, ctiles, taps_lo, m_lo);
+      const Along along = take_along(quota, later);
+      gelu_bwd_colsum_kernel<E, V, decltype(once)::value, Q, decltype(taps)::value><<<along.blocks + grid, kThreads, 0, s>>>((const E*)z, (const E*)da, (E*)dz, (float*)scratch, T, n, rp, np, ctiles, taps_lo, m_lo, along);
     };
     // Waves on a CU with 8 bytes a lane.  Measured with 8 bytes / 4 bytes a lane, us, waves in brackets: partitions of a whole number of
     // eights 1568 x 3072 14.3 / 13.2 (9), 17.1 / 16.5 (18), 24.1 / 23.4 (37); 12000 x 3840 58.1 / 54 (30), 80.6 / 84 (60); others

@@ -73,10 +73,19 @@ struct ColReduce {
   int64_t ld, ncols, split, split2;
   void *out0, *out1, *out2;
 };
+// Partial column sums of X[rows, n] that have not been formed yet: the next byte-bound kernel of the list's layer takes them along in its
+// launch (a pass of its own costs 4 to 5 us however small), or the final reduction launches them first.  np == 0: none.
+struct ColSumJob {
+  const void* X = nullptr;
+  float* partial = nullptr;
+  int64_t rows = 0, n = 0;
+  int rp = 0, np = 0, ctiles = 0;
+};
 struct ColReduceList {
   static constexpr int kMax = 6;
   ColReduce job[kMax];
   int n = 0;
+  ColSumJob pending;
   // a loss whose partial sums launch_mse left here: loss = loss_scale * their sum, formed beside the column sums
   const float* loss_partial = nullptr;
   float* loss = nullptr;
@@ -131,8 +140,9 @@ mosaic_status launch_mse(hipStream_t s, int quota, int dtype, int64_t n, const v
 size_t colsum_scratch_bytes(int64_t n);
 int64_t colsum_partition_rows(int64_t T);      // rows of a partition; each is summed in ascending order (colsum_quarters aside)
 // out[n] = sum over T rows of X[T,n] in a fixed two-level order.
+// in_passing: the partial sums may be left to a later kernel (ColSumJob); X has to stay as it is until then
 mosaic_status launch_colsum(hipStream_t s, int quota, int dtype, int64_t T, int64_t n,
-                            const void* X, void* out, void* scratch, ColReduceList* later = nullptr);
+                            const void* X, void* out, void* scratch, ColReduceList* later = nullptr, bool in_passing = false);
 
 // ----------------------------------------------------------------------------- stems
 // rows of `out` are ld elements apart (whole 16-byte pieces), zeros past 3*patch*patch

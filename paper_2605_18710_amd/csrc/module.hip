@@ -331,7 +331,7 @@ mosaic_status layers_backward(mosaic_module* m, hipStream_t s, int q, const void
     // that writes that gradient where there is one of ours: the first norm's backward of the
     // layer above (this layer's incoming gradient), the GELU backward, the second norm's
     // backward.  Only the top layer's incoming gradient and dQKV take a pass of their own.
-    if (p.b_2 >= 0 && l == d.layers - 1) MOSAIC_TRY(launch_colsum(s, q, dt, T, h, gin, G(m, p.b_2), W(m, m->s_colsum3), &sums));
+    if (p.b_2 >= 0 && l == d.layers - 1) MOSAIC_TRY(launch_colsum(s, q, dt, T, h, gin, G(m, p.b_2), W(m, m->s_colsum3), &sums, true));
     const bool b1_done = d.act == MOSAIC_GELU && p.b_1 >= 0;
     MOSAIC_TRY(launch_act_linear_bwd(s, q, dt, d.act, T, f, h, W(m, sv.z), W(m, sv.a), gin, P(m, p.w_2), dA, dZ, G(m, p.w_2), W(m, m->s_splitk),
                                      b1_done ? G(m, p.b_1) : nullptr, b1_done ? W(m, m->s_colsum) : nullptr, &sums));
@@ -350,7 +350,7 @@ mosaic_status layers_backward(mosaic_module* m, hipStream_t s, int q, const void
     // the forward pass is still in the workspace)
     if (d.rope_base > 0.f) MOSAIC_TRY(launch_rope(s, q, dt, d.batch, d.seq, d.heads, kvh, (int)(h / d.heads), -1, dQKV, W(m, m->s_rope)));
     // QKV projection
-    if (p.b_qkv >= 0) MOSAIC_TRY(launch_colsum(s, q, dt, T, qw, dQKV, G(m, p.b_qkv), W(m, m->s_colsum2), &sums));
+    if (p.b_qkv >= 0) MOSAIC_TRY(launch_colsum(s, q, dt, T, qw, dQKV, G(m, p.b_qkv), W(m, m->s_colsum2), &sums, true));
     MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, h, qw, W(m, sv.u1), dQKV, P(m, p.w_qkv), dU, G(m, p.w_qkv), W(m, m->s_splitk), false));
     // first norm
     MOSAIC_TRY(launch_norm_bwd(s, q, dt, d.norm, T, h, xin, P(m, p.n1_g), (const float*)W(m, sv.st1), dU, dX1, gout, G(m, p.n1_g), G(m, p.n1_b), W(m, m->s_norm),
@@ -380,7 +380,7 @@ mosaic_status projector_backward(mosaic_module* m, hipStream_t s, int q, const v
   const int dt = d.dtype;
   void* dA = W(m, m->s_dA); void* dZ = W(m, m->s_dZ);
   ColReduceList sums;
-  MOSAIC_TRY(launch_colsum(s, q, dt, T, no, dy, G(m, p.b_2), W(m, m->s_colsum2), &sums));
+  MOSAIC_TRY(launch_colsum(s, q, dt, T, no, dy, G(m, p.b_2), W(m, m->s_colsum2), &sums, true));
   MOSAIC_TRY(launch_act_linear_bwd(s, q, dt, MOSAIC_GELU, T, no, no, W(m, sv.z), W(m, sv.a), dy, P(m, p.w_2), dA, dZ, G(m, p.w_2), W(m, m->s_splitk),
                                    G(m, p.b_1), W(m, m->s_colsum), &sums));
   MOSAIC_TRY(launch_col_reduce(s, q, dt, sums));

@@ -121,3 +121,27 @@ def test_with_gelu_and_taps(mb, B, lo, C, h):
         assert same(part(m.grads, "b_c2").reshape(-1), ref2), q
         assert same(part(m.grads, "b_c1").reshape(-1), ref1), q
     m.destroy()
+
+
+# sums that a later kernel takes along: encoders whose norms take them (one layer, and several: the top layer's and each layer's q|k|v bias), and
+# rows too wide for the norms that do, where they get a launch of their own before dx is written, which may lie on the incoming gradient
+@pytest.mark.parametrize("dtype,B,N,h,heads,f,L", [("f32", 1, 9, 64, 4, 96, 2), ("bf16", 2, 70, 256, 4, 512, 2), ("f32", 1, 6, 2052, 18, 64, 1)])
+def test_sums_taken_along(mb, dtype, B, N, h, heads, f, L):
+    m = mb.Module(dict(kind="encoder", batch=B, seq=N, hidden=h, heads=heads, mlp=f, layers=L, norm="layernorm", act="gelu", causal=0, bias=1, eps=1e-5), dtype)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    m.params.copy_(torch.randn(m.params.numel(), generator=torch.Generator().manual_seed(h)).mul_(0.05).to(td))
+    x, dy = [to_dev(synth.normal(1500 + i + h, (B * N, h)), dtype) for i in range(2)]
+    ref = column_sums(dy.float()).to(td)
+    outs = []
+    for q in (256, 24):
+        y, grad = torch.empty_like(x), dy.clone()
+        m.grads.fill_(float("nan"))
+        m.step(q, None, x, y, dy=grad, dx=grad)            # dx over dy
+        torch.cuda.synchronize()
+        off, rows, cols = m.tensors["L%d.b_2" % (L - 1)]
+        assert same(m.grads[off:off + rows * cols].float(), ref.float()), q
+        grads = torch.cat([m.grads[o:o + r * c] for o, r, c in m.tensors.values()])
+        assert not torch.isnan(grads.float()).any()
+        outs.append((y, grad, grads))
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    m.destroy()
