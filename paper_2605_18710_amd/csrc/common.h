@@ -98,8 +98,9 @@ template <typename T> struct Vec16;
 template <> struct Vec16<float> {
   static constexpr int N = 4;
   float4 v;
-  __device__ __forceinline__ void load(const float* p) { v = *reinterpret_cast<const float4*>(p); }
-  __device__ __forceinline__ void store(float* p) const { *reinterpret_cast<float4*>(p) = v; }
+  typedef __attribute__((ext_vector_type(4))) float v4;
+  template <bool PAST = false> __device__ __forceinline__ void load(const float* p) { v = __builtin_bit_cast(float4, load_from<PAST>(reinterpret_cast<const v4*>(p))); }
+  template <bool PAST = false> __device__ __forceinline__ void store(float* p) const { store_to<PAST>(reinterpret_cast<v4*>(p), __builtin_bit_cast(v4, v)); }
   __device__ __forceinline__ float get(int i) const { return (&v.x)[i]; }
   __device__ __forceinline__ void set(int i, float f) { (&v.x)[i] = f; }
 };
@@ -107,8 +108,8 @@ template <> struct Vec16<bf16> {
   static constexpr int N = 8;
   typedef __attribute__((ext_vector_type(8))) __bf16 v8;
   v8 v;
-  __device__ __forceinline__ void load(const bf16* p) { v = *reinterpret_cast<const v8*>(p); }
-  __device__ __forceinline__ void store(bf16* p) const { *reinterpret_cast<v8*>(p) = v; }
+  template <bool PAST = false> __device__ __forceinline__ void load(const bf16* p) { v = load_from<PAST>(reinterpret_cast<const v8*>(p)); }
+  template <bool PAST = false> __device__ __forceinline__ void store(bf16* p) const { store_to<PAST>(reinterpret_cast<v8*>(p), v); }
   __device__ __forceinline__ float get(int i) const { return (float)v[i]; }
   __device__ __forceinline__ void set(int i, float f) { v[i] = (bf16)f; }
 };

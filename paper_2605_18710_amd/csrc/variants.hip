@@ -252,7 +252,7 @@ mosaic_status launch_rope(hipStream_t s, int quota, int dtype, int B, int N, int
   const int64_t rows = (int64_t)B * N;
   if (rows == 0) return MOSAIC_OK;
   const int rot = (H + Hkv) * d, width = (H + 2 * Hkv) * d;
-  const int grid = grid_for(quota, 8, ceil_div(rows * (rot / vn), kThreads));
+  const int grid = sweep_grid(quota, ceil_div(rows * (rot / vn), kThreads), 2 * rows * rot * (int64_t)dtype_size(dtype));
   if (dtype == MOSAIC_BF16) rope_kernel<bf16><<<grid, kThreads, 0, s>>>((bf16*)qkv, (const float2*)table, rows, N, rot, width, d, (float)direction);
   else rope_kernel<float><<<grid, kThreads, 0, s>>>((float*)qkv, (const float2*)table, rows, N, rot, width, d, (float)direction);
   MOSAIC_LAUNCH_CHECK();
