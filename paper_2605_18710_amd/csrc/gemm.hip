@@ -1775,12 +1775,12 @@ mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act
   return launch_gelu_fwd(s, quota, dtype, T * n, Z, Aout);
 }
 
-mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t lo, int64_t n, int64_t k, const void* X, const void* W,
+mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t lo, int64_t n, int64_t k, int64_t ldx, const void* X, const void* W,
                                    const void* bias, void* Z, void* A, void* P) {
   const int64_t T = 2 * B * lo;
   const bool in_range = lo >= 2 && (T / 2 + 256) * lo < (int64_t)1 << 32;
   bool fused = false;
-  MOSAIC_TRY(launch_gemm_impl(s, quota, dtype, true, false, T, n, k, X, k, W, n, Z, n, bias, nullptr, nullptr, -1, MOSAIC_GELU, P, 3 * n,
+  MOSAIC_TRY(launch_gemm_impl(s, quota, dtype, true, false, T, n, ldx, X, ldx, W, n, Z, n, bias, nullptr, nullptr, k, MOSAIC_GELU, P, 3 * n,
                               in_range ? &fused : nullptr, 0, in_range ? lo : 0));
   if (fused || T == 0 || n == 0) return MOSAIC_OK;
   MOSAIC_TRY(launch_gelu_fwd(s, quota, dtype, T * n, Z, A));

@@ -30,10 +30,10 @@ mosaic_status launch_embed_fwd(hipStream_t s, int quota, int dtype, int64_t B, i
 // otherwise the elementwise kernel follows the product.
 mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act, int64_t T, int64_t k, int64_t n,
                                     const void* X, const void* W, const void* bias, void* Z, void* A);
-// Z = X W + bias over samples of 2 lo rows, and P [B lo, 3n] = the gathered input of a three-tap convolution of stride 2 over
+// Z = X W + bias over samples of 2 lo rows (of X, ldx apart, zeros past k), and P [B lo, 3n] = the gathered input of a three-tap convolution of stride 2 over
 // gelu(Z) (launch_im2col1d): written by the epilogue where the bf16 matrix-core kernel takes the product, else through A [2 B lo, n];
 // the same bits.
-mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t lo, int64_t n, int64_t k, const void* X, const void* W,
+mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t lo, int64_t n, int64_t k, int64_t ldx, const void* X, const void* W,
                                    const void* bias, void* Z, void* A, void* P);
 // dW[k,n] = X^T dY and dX[T,k] = dY W^T, dense rows; one launch where that is the faster way, else two, the input gradient's
 // first or last (1 - 2 % of a layer either way, by what the caches still hold)
@@ -132,7 +132,7 @@ mosaic_status launch_adamw(hipStream_t s, int quota, int dtype, int64_t n, void*
 // k=3, pad=1 convolution over frames-major [B, L, C] as gather + GEMM: out [B*Lo, 3*C] with
 // column index tap*C + channel; col2im1d is the transposed gather at stride 1 (one owner per element)
 mosaic_status launch_im2col1d(hipStream_t s, int quota, int dtype, int64_t B, int L, int Lo, int C,
-                              int stride, const void* x, void* out);
+                              int stride, const void* x, void* out, int64_t ld = 0);      // rows ld >= 3C apart (0: 3C), zeros between
 mosaic_status launch_col2im1d(hipStream_t s, int quota, int dtype, int64_t B, int L, int C, const void* dP, void* dx);
 size_t mse_scratch_bytes();
 mosaic_status launch_mse(hipStream_t s, int quota, int dtype, int64_t n, const void* y,

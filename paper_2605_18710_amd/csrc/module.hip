@@ -140,6 +140,14 @@ inline int64_t patch_ld(const mosaic_module_desc& d) {
   return d.dtype == MOSAIC_BF16 && 8 * (tile - d.in_dim) <= d.in_dim ? tile : ceil_div(d.in_dim, 8) * 8;
 }
 
+// Distance between rows of the first convolution's gathered input: whole K-tiles of the four-wave kernel where that adds at most an eighth
+// (three taps of 80 mel bins, 240 -> 256; the kernel of eight waves takes an erff per value.  The stem's step of 8 x 1500 positions, width 1280,
+// 523.5 -> 514.7 us; of 5 x 900, width 1024, 208.6 -> 200.9; of 2 x 400, width 512, 83.5 -> 82.6).
+inline int64_t taps_ld(const mosaic_module_desc& d) {
+  const int64_t k = 3 * (int64_t)d.in_dim, tile = ceil_div(k, 64) * 64;
+  return d.dtype == MOSAIC_BF16 && 8 * (tile - k) <= k ? tile : k;
+}
+
 void build_layout(mosaic_module* m) {
   const mosaic_module_desc& d = m->d;
   const int64_t T = m->T, h = d.hidden, f = d.mlp;
@@ -246,7 +254,7 @@ void build_layout(mosaic_module* m) {
     q.b_2 = add_tensor(m, "b_c2", 1, h);
     q.w_o = add_tensor(m, "pos", d.seq, h);
     m->lp.push_back(q);
-    m->c_p1 = take(&cur, Tin * 3 * C * es);
+    m->c_p1 = take(&cur, Tin * taps_ld(d) * es);
     m->c_z1 = take(&cur, Tin * h * es);
     m->c_p2 = take(&cur, T * 3 * h * es);
     m->c_z2 = take(&cur, T * h * es);
@@ -415,9 +423,9 @@ mosaic_status conv_stem_forward(mosaic_module* m, hipStream_t s, int q, const vo
   const mosaic_module_desc& d = m->d;
   const LayerParams& p = m->lp[0];
   const int dt = d.dtype, C = d.in_dim, h = d.hidden, Lo = d.seq, L = 2 * d.seq;
-  MOSAIC_TRY(launch_im2col1d(s, q, dt, d.batch, L, L, C, 1, x, W(m, m->c_p1)));
+  MOSAIC_TRY(launch_im2col1d(s, q, dt, d.batch, L, L, C, 1, x, W(m, m->c_p1), taps_ld(d)));
   // where the activation has to be stored, it goes to what the backward pass writes last
-  MOSAIC_TRY(launch_gelu_taps_fwd(s, q, dt, d.batch, Lo, h, 3 * C, W(m, m->c_p1), P(m, p.w_1), P(m, p.b_1), W(m, m->c_z1), W(m, m->c_dz1), W(m, m->c_p2)));
+  MOSAIC_TRY(launch_gelu_taps_fwd(s, q, dt, d.batch, Lo, h, 3 * C, taps_ld(d), W(m, m->c_p1), P(m, p.w_1), P(m, p.b_1), W(m, m->c_z1), W(m, m->c_dz1), W(m, m->c_p2)));
   MOSAIC_TRY(launch_linear_act_fwd(s, q, dt, MOSAIC_GELU, m->T, 3 * h, h, W(m, m->c_p2), P(m, p.w_2), P(m, p.b_2), W(m, m->c_z2), y));
   return launch_add_pos(s, q, dt, d.batch, Lo, h, P(m, p.w_o), y);
 }
@@ -434,12 +442,14 @@ mosaic_status conv_stem_backward(mosaic_module* m, hipStream_t s, int q, const v
   MOSAIC_TRY(launch_linear_bwd(s, q, dt, T, 3 * h, h, W(m, m->c_p2), W(m, m->c_dz2), P(m, p.w_2), W(m, m->c_dp2), G(m, p.w_2), sk, false));
   MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, Tin, h, W(m, m->c_z1), W(m, m->c_dp2), W(m, m->c_dz1), G(m, p.b_1), W(m, m->s_colsum), &sums, Lo));
   MOSAIC_TRY(launch_col_reduce(s, q, dt, sums));
-  if (!dx) {
-    MOSAIC_TRY(launch_gemm(s, q, dt, false, false, 3 * C, h, Tin, W(m, m->c_p1), 3 * C, W(m, m->c_dz1), h, G(m, p.w_1), h, nullptr, nullptr, sk));
-  } else {
+  const int64_t ld = taps_ld(d);
+  if (dx && ld == 3 * C) {
     MOSAIC_TRY(launch_linear_bwd(s, q, dt, Tin, 3 * C, h, W(m, m->c_p1), W(m, m->c_dz1), P(m, p.w_1), W(m, m->c_dp1), G(m, p.w_1), sk, false));
-    MOSAIC_TRY(launch_col2im1d(s, q, dt, d.batch, L, C, W(m, m->c_dp1), dx));
+  } else {
+    MOSAIC_TRY(launch_gemm(s, q, dt, false, false, 3 * C, h, Tin, W(m, m->c_p1), ld, W(m, m->c_dz1), h, G(m, p.w_1), h, nullptr, nullptr, sk));
+    if (dx) MOSAIC_TRY(launch_gemm(s, q, dt, true, true, Tin, 3 * C, h, W(m, m->c_dz1), h, P(m, p.w_1), h, W(m, m->c_dp1), 3 * C, nullptr, nullptr));
   }
+  if (dx) MOSAIC_TRY(launch_col2im1d(s, q, dt, d.batch, L, C, W(m, m->c_dp1), dx));
   return MOSAIC_OK;
 }
 

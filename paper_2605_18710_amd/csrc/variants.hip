@@ -130,27 +130,26 @@ __global__ __launch_bounds__(kThreads) void adamw_kernel(T* __restrict__ p, cons
 }
 
 // Gathers the three taps of a k=3, pad=1 convolution over frames-major x [B, L, C]:
-// out[(b*Lo + t), k*C + c] = x[b, t*stride - 1 + k, c], zero outside [0, L).
+// out[(b*Lo + t), k*C + c] = x[b, t*stride - 1 + k, c], zero outside [0, L); rows of out are ld elements apart, zeros past 3C.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void im2col1d_kernel(const T* __restrict__ x, T* __restrict__ out, int64_t B, int L,
-                                                            int Lo, int C, int stride) {
+                                                            int Lo, int C, int stride, int64_t ld) {
   constexpr int VN = Vec16<T>::N;
-  const int cv = C / VN;
-  const int64_t nvec = B * Lo * 3 * cv;
+  const int cv = C / VN, rv = (int)(ld / VN);
+  const int64_t nvec = B * Lo * rv;
   for (int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x; v < nvec; v += (int64_t)gridDim.x * kThreads) {
-    const int c = (int)(v % cv) * VN;
-    const int k = (int)((v / cv) % 3);
-    const int64_t row = v / (3 * cv);
+    const int64_t row = v / rv;
+    const int piece = (int)(v - row * rv), k = piece / cv, c = (piece - k * cv) * VN;
     const int t = (int)(row % Lo);
     const int64_t b = row / Lo;
     const int src = t * stride - 1 + k;
     Vec16<T> val;
-    if (src >= 0 && src < L) val.load(x + (b * L + src) * C + c);
+    if (k < 3 && src >= 0 && src < L) val.load(x + (b * L + src) * C + c);
     else {
 #pragma unroll
       for (int e = 0; e < VN; ++e) val.set(e, 0.f);
     }
-    val.store(out + row * 3 * (int64_t)C + (int64_t)k * C + c);
+    val.store(out + row * ld + piece * VN);
   }
 }
 
@@ -187,13 +186,15 @@ __global__ __launch_bounds__(kThreads) void col2im1d_kernel(const T* __restrict_
 }  // namespace
 
 mosaic_status launch_im2col1d(hipStream_t s, int quota, int dtype, int64_t B, int L, int Lo, int C, int stride,
-                              const void* x, void* out) {
+                              const void* x, void* out, int64_t ld) {
   const int vn = dtype == MOSAIC_BF16 ? 8 : 4;
   if (C % vn) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "channel count %d is not a multiple of %d", C, vn);
+  if (ld == 0) ld = 3 * (int64_t)C;
+  if (ld < 3 * (int64_t)C || ld % vn || ld > INT32_MAX) MOSAIC_FAIL(MOSAIC_EINVAL, "gathered rows of %lld elements", (long long)ld);
   if (B <= 0 || L <= 0 || Lo <= 0) return MOSAIC_OK;
-  const int grid = grid_for(quota, 8, ceil_div(B * Lo * 3 * (C / vn), kThreads));
-  if (dtype == MOSAIC_BF16) im2col1d_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)x, (bf16*)out, B, L, Lo, C, stride);
-  else im2col1d_kernel<float><<<grid, kThreads, 0, s>>>((const float*)x, (float*)out, B, L, Lo, C, stride);
+  const int grid = grid_for(quota, 8, ceil_div(B * Lo * (ld / vn), kThreads));
+  if (dtype == MOSAIC_BF16) im2col1d_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)x, (bf16*)out, B, L, Lo, C, stride, ld);
+  else im2col1d_kernel<float><<<grid, kThreads, 0, s>>>((const float*)x, (float*)out, B, L, Lo, C, stride, ld);
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;
 }
