@@ -142,10 +142,11 @@ inline int64_t patch_ld(const mosaic_module_desc& d) {
 
 // Distance between rows of the first convolution's gathered input: whole K-tiles of the four-wave kernel where that adds at most an eighth
 // (three taps of 80 mel bins, 240 -> 256; the kernel of eight waves takes an erff per value.  The stem's step of 8 x 1500 positions, width 1280,
-// 523.5 -> 514.7 us; of 5 x 900, width 1024, 208.6 -> 200.9; of 2 x 400, width 512, 83.5 -> 82.6).
+// 523.5 -> 514.7 us; of 5 x 900, width 1024, 208.6 -> 200.9; of 2 x 400, width 512, 83.5 -> 82.6).  The workspace stays as large as with dense
+rows: the gathered gradient then lies where the second convolution's was, which holds it from a width of two input rows on.
 inline int64_t taps_ld(const mosaic_module_desc& d) {
   const int64_t k = 3 * (int64_t)d.in_dim, tile = ceil_div(k, 64) * 64;
-  return d.dtype == MOSAIC_BF16 && 8 * (tile - k) <= k ? tile : k;
+  return d.dtype == MOSAIC_BF16 && 8 * (tile - k) <= k && d.hidden >= 2 * d.in_dim ? tile : k;
 }
 
 void build_layout(mosaic_module* m) {
@@ -254,14 +255,17 @@ void build_layout(mosaic_module* m) {
     q.b_2 = add_tensor(m, "b_c2", 1, h);
     q.w_o = add_tensor(m, "pos", d.seq, h);
     m->lp.push_back(q);
-    m->c_p1 = take(&cur, Tin * taps_ld(d) * es);
+    // Padded rows take the room of the gathered gradient as well.  That lies on the second convolution's (T * 3h >= Tin * 3C values), which the
+    // derivative of the first GELU has read, on the same stream, before the product that writes it.
+    const bool padded = taps_ld(d) > 3 * C;
+    m->c_p1 = take(&cur, (padded ? 2 : 1) * Tin * 3 * C * es);
     m->c_z1 = take(&cur, Tin * h * es);
     m->c_p2 = take(&cur, T * 3 * h * es);
     m->c_z2 = take(&cur, T * h * es);
     m->c_dz2 = take(&cur, T * h * es);
     m->c_dp2 = take(&cur, T * 3 * h * es);
     m->c_dz1 = take(&cur, Tin * h * es);
-    m->c_dp1 = take(&cur, Tin * 3 * C * es);
+    m->c_dp1 = padded ? m->c_dp2 : take(&cur, Tin * 3 * C * es);
     m->s_colsum = take(&cur, colsum_scratch_bytes(h));
     m->s_colsum2 = take(&cur, colsum_scratch_bytes(h));
     m->s_splitk = take(&cur, std::max(gemm_splitk_scratch_bytes(3 * C, h, Tin), gemm_splitk_scratch_bytes(3 * h, h, T)));
