@@ -143,7 +143,7 @@ inline int64_t patch_ld(const mosaic_module_desc& d) {
 // Distance between rows of the first convolution's gathered input: whole K-tiles of the four-wave kernel where that adds at most an eighth
 // (three taps of 80 mel bins, 240 -> 256; the kernel of eight waves takes an erff per value.  The stem's step of 8 x 1500 positions, width 1280,
 // 523.5 -> 514.7 us; of 5 x 900, width 1024, 208.6 -> 200.9; of 2 x 400, width 512, 83.5 -> 82.6).  The workspace stays as large as with dense
-rows: the gathered gradient then lies where the second convolution's was, which holds it from a width of two input rows on.
+// rows: the gathered gradient then lies where the second convolution's was, which holds it from a width of two input rows on.
 inline int64_t taps_ld(const mosaic_module_desc& d) {
   const int64_t k = 3 * (int64_t)d.in_dim, tile = ceil_div(k, 64) * 64;
   return d.dtype == MOSAIC_BF16 && 8 * (tile - k) <= k && d.hidden >= 2 * d.in_dim ? tile : k;
