@@ -1,7 +1,7 @@
 // Linear-layer contractions (forward, input gradient, weight gradient) for gfx950.
 //
 // bf16 path: persistent MFMA kernels.  gemm_bf16_kernel serves every form: a workgroup of 8
-// waves (256x256 tile, 128x64 per wave) or 4 waves (128x128 tile, 64x64 per wave) walks
+// waves (256x256 tile, 128x64 per wave) or 4 waves (128x128 tile, 64x64 per wave; 64x128, 32x64 per wave) walks
 // output tiles; gemm_bf16_w4_kernel (described at its definition) can take the 256x256 tiles of
 // every product whose K-contiguous operands are whole 64-deep K-tiles long (the plans say when it does).  In both,
 // the grid is sized to the module's CU quota.  Each output element is produced by exactly
@@ -1665,6 +1665,22 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
                                                    nullptr, sub, tile_begin, tile_count, aa);
   };
   if (plan == 256) return launch_tiles(std::true_type{}, 1, 0, -1);
+  // Tiles of 64 rows where even those all get a CU of their own: a lone tile is bound by what its CU's vector cache and LDS pass per
+  // K-tile (a 128 x 128 tile 0.35 us per 64 k-values, 0.21 of it matrix work), so half a tile to each of twice the CUs is faster however
+  // short the contraction.  128 -> 64 rows: forward 1568 x 768 x 768 9.6 -> 8.3 us, 1568 x 3072 x 768 22.8 -> 19.2, with GELU
+  // 12.8 -> 10.5 and 25.9 -> 21.4; input gradient 200 x 1024 x 3072 21.4 -> 17.7, on 64 CUs 21.4 -> 17.6.
+  if constexpr (A_KC) {
+    if (plan == 128 && ceil_div(M, 64) * ceil_div(N, 128) <= quota) {
+      auto go = [&](auto act) {
+        return launch_mfma<64, 128, 2, 2, A_KC, B_KC, PIECES_NONE, decltype(act)::value, 64>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
+                                                                                          c_bytes, 1, 0, nullptr, 1, 0, -1, aa);
+      };
+      if constexpr (!B_KC) {
+        if (aa.act == ACT_GELU) return go(std::integral_constant<int, ACT_GELU>{});
+      }
+      if (aa.act == ACT_NONE) return go(std::integral_constant<int, ACT_NONE>{});
+    }
+  }
   if (plan == 128) return launch_tiles(std::false_type{}, 1, 0, -1);
   const int head = (int)(whole * quota);
   MOSAIC_TRY(launch_tiles(std::true_type{}, 1, 0, head));

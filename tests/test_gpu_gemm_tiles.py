@@ -57,6 +57,33 @@ def test_k_tile_depths_agree(mb, T, k, n):
     assert all(torch.equal(a.view(torch.int16), c.view(torch.int16)) for a, c in zip(*outs))
 
 
+@pytest.mark.parametrize("T,k,n", [(1, 8, 8), (63, 72, 136), (64, 128, 128), (65, 64, 264), (128, 1000, 120), (129, 136, 392), (200, 520, 1024)])
+def test_tiles_of_64_rows(mb, T, k, n):
+    """The share of the CUs decides between 64 and 128 rows to a tile: on both sides of that line, for the forward
+    product (plain, with a residual, with GELU) and the input gradient."""
+    s = 7600 + T + k + n
+    X, W, b, R, dY = [quantize(synth.normal(s + i, sh, 0, sd), "bf16") for i, (sh, sd) in
+                      enumerate([((T, k), 1), ((k, n), 0.05), ((n,), 0.1), ((T, n), 1), ((T, n), 1)])]
+    X_, W_, b_, R_, dY_ = [to_dev(a, "bf16") for a in (X, W, b, R, dY)]
+    tiles = lambda cols: -(-T // 64) * -(-cols // 128)
+    quotas = sorted({q for t in (tiles(n), tiles(k)) for q in (t - 1, t, t + 1) if q > 0} | {1, 256})
+    first = None
+    for q in quotas:
+        Y, Z, A, dX = [torch.full(sh, float("nan"), dtype=torch.bfloat16, device="cuda") for sh in ((T, n), (T, n), (T, n), (T, k))]
+        mb.op_linear_fwd(None, q, "bf16", T, k, n, X_, W_, b_, R_, Y)
+        mb.op_linear_act_fwd(None, q, "bf16", mb.GELU, T, k, n, X_, W_, b_, Z, A)
+        mb.op_linear_dgrad(None, q, "bf16", T, k, n, dY_, W_, None, dX)
+        torch.cuda.synchronize()
+        got = [t.view(torch.int16) for t in (Y, Z, A, dX)]
+        first = first or got
+        assert all(torch.equal(a, c) for a, c in zip(got, first)), f"bits at {q} CUs differ from those at {quotas[0]}"
+    z_ref = O.linear_fwd(X, W, b)
+    assert_close(from_dev(Y), z_ref + R, "bf16", "Y")
+    assert_close(from_dev(Z), z_ref, "bf16", "Z")
+    assert_close(from_dev(A), O.gelu(from_dev(Z)), "bf16", "A")
+    assert_close(from_dev(dX), O.linear_bwd(X, W, dY)[0], "bf16", "dX")
+
+
 @pytest.mark.parametrize("T,k,n,note", [
     (2048, 264, 1032, "27 small tiles in pieces beside each other, ragged tile row and column"),
     (2056, 128, 128, "one tile in pieces that end in mid K-tile of 64"),
