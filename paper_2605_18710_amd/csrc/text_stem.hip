@@ -17,9 +17,9 @@
 // four quarters added in turn.
 //
 // What bounds it: the table is written whole (V x h; 131 MB at V 32000, h 2048) and dy read once.
-// At B 8, N 1024, h 2048, V 32000, bf16, 196 or fewer image tokens: sort and fill 27 us, sums 11, joins 8 (forward 12); in six
+// At B 8, N 1024, h 2048, V 32000, bf16, 196 or fewer image tokens: sort and fill 24 us, sums 10, joins 8 (forward 11); in six
 // launches of the sort, sums with the fill beside them, a join with a bisection per run and a launch for the image
-// tokens the whole pass took 100 us instead of 71, forward included.
+// tokens the whole pass took 100 us instead of 67, forward included.
 // A walk over all positions by the owner of every table row (V x T id reads) takes 2000 us there, but is one launch,
 // and still what small calls take (scan_is_faster).
 #include "kernels.h"
@@ -188,11 +188,41 @@ __global__ __launch_bounds__(kThreads) void sort_scatter_kernel(SortInput in, in
   }
 }
 
+// Keys of the positions first + r * step, r < rounds, all of them requested together (conditional loads would wait for each
+// other); -1 past the end.  Positions without an id to read are requested outside the buffer, which reads nothing.  The sample of a
+// position is floor((e + 1/2) / N), in fp32: exact below 2^21, and e < 2^14 here; an integer division a key costs more than the loads.
+template <int R, int N>
+__device__ __forceinline__ void keys_at(const SortInput& in, int first, int step, int rounds, int total, int (&key)[N]) {
+  if constexpr (R > 1) {
+    if (rounds <= R / 2) return keys_at<R / 2>(in, first, step, rounds, total, key);        // alike for all threads
+  }
+  constexpr int kOutside = INT32_MIN;
+  const __amdgpu_buffer_rsrc_t ids = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(in.ids), 0, in.ids ? total * 4 : 0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t counts = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(in.counts), 0, in.counts ? total * 4 : 0, 0x00020000);
+  const float inv = 1.f / (float)in.N;
+  int t[R], img[R], id[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int e = first + r * step, b = (int)(((float)e + 0.5f) * inv);
+    const bool live = r < rounds && e < total;
+    t[r] = live ? e - b * in.N : -1;
+    img[r] = in.counts ? (int)__builtin_amdgcn_raw_buffer_load_b32(counts, live ? b * 4 : kOutside, 0, 0) : in.n_img;
+    const bool read = in.counts ? live : t[r] >= in.n_img && live;
+    id[r] = (int)__builtin_amdgcn_raw_buffer_load_b32(ids, read ? (in.counts ? e : b * (in.N - in.n_img) + t[r] - in.n_img) * 4 : kOutside, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < N; ++r) {
+    key[r] = -1;
+    if (r < R && t[r % R] >= 0) key[r] = t[r % R] >= min(max(img[r % R], 0), in.n_img) ? min(max(id[r % R], 0), in.vocab - 1) : in.vocab;
+  }
+}
+
 // Sort, fill and image-token gradient in one launch.  Workgroup 0 sorts: a key and its position share 32 bits, a thread
 // holds up to 8 of them, and a pass scatters them through LDS in the order of sort_scatter_kernel, so the lists are the
 // same.  The others (all, if there is one) take table rows and image-token rows; which table rows are used they find
-// out by a walk over the ids, 2048 rows at a time.  What bounds it is the fill (27 us for 131 MB, the rate of a copy),
-// which covers the sort's 10 to 20 us of short dependent steps.
+// out by a walk over the ids, 2048 rows at a time.  What bounds it is the fill of what nobody used (106 of 131 MB), which covers
+// the sort's 10 to 20 us of short dependent steps, and the ids before it: eight conditional reads a thread, one after the other,
+// took 5 us of which keys_at leaves half (the whole pass with buffers in cache 54.7 -> 52.3 us; 1400 positions, 1000 x 512, 18.7 -> 18.5).
 constexpr int kOneThreads = 1024, kOneWaves = kOneThreads / 64, kFlagRows = 2048;
 constexpr int kOneMax = 8 * kOneThreads;              // positions that one workgroup sorts
 static_assert(kFlagRows <= kOneWaves * kBins + kOneMax, "flags");
@@ -210,11 +240,10 @@ __global__ __launch_bounds__(kOneThreads) void embed_prepare_kernel(SortInput in
     __shared__ int wave_total[kWaves];
     const int rounds = (total + kOneThreads - 1) / kOneThreads, first = wave * 64 * rounds + lane;
     unsigned x[R];
+    int key[R];
+    keys_at<R>(in, first, 64, rounds, total, key);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int e = first + 64 * r;
-      x[r] = r < rounds && e < total ? ((unsigned)in.key_of(e) << pos_bits) | (unsigned)e : 0u;
-    }
+    for (int r = 0; r < R; ++r) x[r] = r < rounds && first + 64 * r < total ? ((unsigned)key[r] << pos_bits) | (unsigned)(first + 64 * r) : 0u;
     for (int shift = 0; shift == 0 || (in.vocab >> shift) > 0; shift += kDigit) {      // the largest key is `vocab`
       const int at_bit = pos_bits + shift;
 #pragma unroll
@@ -285,12 +314,15 @@ __global__ __launch_bounds__(kOneThreads) void embed_prepare_kernel(SortInput in
   }
   const int workers = gridDim.x > 1 ? gridDim.x - 1 : 1, me = gridDim.x > 1 ? (int)blockIdx.x - 1 : 0;
   const int per = (in.vocab + workers - 1) / workers, v0 = me * per, v1 = min(v0 + per, in.vocab);
+  int key[kOneMax / kOneThreads];
+  keys_at<kOneMax / kOneThreads>(in, threadIdx.x, kOneThreads, (total + kOneThreads - 1) / kOneThreads, total, key);
   for (int r0 = v0; r0 < v1; r0 += kFlagRows) {
     const int n = min(kFlagRows, v1 - r0);
     for (int i = threadIdx.x; i < n; i += kOneThreads) lds[i] = 0;
     __syncthreads();
-    for (int e = threadIdx.x; e < total; e += kOneThreads) {
-      const int k = in.key_of(e) - r0;
+#pragma unroll
+    for (int r = 0; r < kOneMax / kOneThreads; ++r) {
+      const int k = key[r] - r0;
       if (k >= 0 && k < n) lds[k] = 1;
     }
     __syncthreads();

@@ -183,3 +183,10 @@ def test_text_stem_with_image_counts(dtype, B, N, n_img, h, vocab):
 @pytest.mark.parametrize("B,N,n_img,h,vocab,how,offset", [(1, 33, 0, 8192, 50, "mixed", 0), (1, 32, 0, 8192, 50, "mixed", 0), (1, 8193, 0, 64, 254, "one", 0), (3, 3413, 2, 264, 257, "mixed", 1)])
 def test_limits_of_the_scan_and_of_the_one_workgroup(dtype, B, N, n_img, h, vocab, how, offset):
     test_text_stem_step(dtype, B, N, n_img, h, vocab, how, offset)
+
+
+# a thread of the one workgroup's launch requests one, two, four or eight keys at once; samples of one position, of image tokens alone
+@pytest.mark.parametrize("B,N,n_img", [(1000, 1, 0), (1023, 1, 1), (3, 683, 5), (2, 1025, 1025), (8191, 1, 1), (4, 1025, 100), (2731, 3, 2), (2, 4096, 4000)])
+def test_keys_requested_together(B, N, n_img):
+    test_text_stem_step("bf16", B, N, n_img, 72, 300, "mixed", 0)
+    test_text_stem_with_image_counts("f32", B, N, n_img, 8, 300)

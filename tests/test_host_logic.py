@@ -276,3 +276,11 @@ def test_weight_gradient_split_is_a_function_of_the_shape(T, k, n, pieces, cut_t
     pieces_bytes = pieces * cut_tiles * 256 * 256 * 4 if pieces > 1 else 0
     aligned = (pieces_bytes + 255) // 256 * 256
     assert got == aligned + mb.colsum_scratch_bytes(n), why
+
+
+def test_sample_of_a_position_by_a_reciprocal():
+    """The text stem's floor((e + 1/2) * (1 / N)) in fp32 against the integer division, over the positions that one workgroup sorts."""
+    e = np.arange(9216, dtype=np.int32)
+    half = e.astype(np.float32) + np.float32(0.5)
+    for N in range(1, 8193):
+        assert np.array_equal((half * (np.float32(1) / np.float32(N))).astype(np.int32), e // N), N
