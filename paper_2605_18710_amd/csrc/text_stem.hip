@@ -17,7 +17,7 @@
 // four quarters added in turn.
 //
 // What bounds it: the table is written whole (V x h; 131 MB at V 32000, h 2048) and dy read once.
-// At B 8, N 1024, h 2048, V 32000, bf16, 196 or fewer image tokens: sort and fill 24 us, sums 10, joins 8 (forward 11); in six
+// At B 8, N 1024, h 2048, V 32000, bf16, 196 or fewer image tokens: sort and fill 23 us, sums 11, joins 7 (forward 12); in six
 // launches of the sort, sums with the fill beside them, a join with a bisection per run and a launch for the image
 // tokens the whole pass took 100 us instead of 67, forward included.
 // A walk over all positions by the owner of every table row (V x T id reads) takes 2000 us there, but is one launch,
