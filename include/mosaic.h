@@ -421,9 +421,10 @@ mosaic_status mosaic_op_swiglu_bwd(void* stream, int32_t quota, int32_t dtype, i
  * [T,n].  act = MOSAIC_SWIGLU: Z = [gate | up] halves of n/2 columns, A[T,n/2] = silu(gate)*up.
  * Z is kept because the backward pass needs it.  All pointers are device memory owned by the
  * caller.  For bf16 operands whose sizes and alignment suit the matrix-core kernel (SwiGLU: n
- * a multiple of 256) the activation is applied in that kernel's epilogue and no second pass is
- * launched; otherwise the product is followed by the elementwise kernel.  Both roads give the
- * same bits.  MOSAIC_EINVAL for an unknown activation, negative sizes or an odd n with SwiGLU. */
+ * a multiple of 256), and for fp32 products of few tiles, the activation is applied in the
+ * product's epilogue and no second pass is launched; otherwise the product is followed by the
+ * elementwise kernel.  Both roads give the same bits.  fp32: A may lie on X, W or bias, or be Z
+ * (GELU), and the elementwise kernel then follows the product.  MOSAIC_EINVAL for an unknown activation, negative sizes or an odd n with SwiGLU. */
 mosaic_status mosaic_op_linear_act_fwd(void* stream, int32_t quota, int32_t dtype, int32_t act,
                                        int64_t T, int64_t k, int64_t n, const void* X,
                                        const void* W, const void* bias, void* Z, void* A);

@@ -1804,10 +1804,6 @@ mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t 
 }
 
 namespace {
-bool overlap(const void* p, int64_t pn, const void* q, int64_t qn) {
-  return (uintptr_t)p < (uintptr_t)q + (uintptr_t)qn && (uintptr_t)q < (uintptr_t)p + (uintptr_t)pn;
-}
-
 template <int PIECES>
 mosaic_status launch_pair(hipStream_t s, const PairHalf& dg, const PairHalf& wg) {
   constexpr size_t smem = (size_t)NS * (128 + 128) * 64 * 2;

@@ -513,7 +513,7 @@ mosaic_status launch_form(hipStream_t s, int quota, bool a_kc, bool b_kc, const 
 
 }  // namespace
 
-// (norm and) product (and activation) of fp32 tensors, dense rows; *taken: in one launch
+// (norm and) product (and activation) of fp32 tensors, dense rows, no output on an input or on another; *taken: in one launch
 mosaic_status launch_layer_fwd_f32(hipStream_t s, int quota, int norm, int act, int64_t T, int64_t k, int64_t n, float eps, const void* X, const void* gamma,
                                    const void* beta, void* U, float* stats, const void* W, const void* bias, void* Z, void* A, bool* taken) {
   *taken = false;
@@ -523,6 +523,13 @@ mosaic_status launch_layer_fwd_f32(hipStream_t s, int quota, int norm, int act, 
   if (T <= 0 || k <= 0 || n <= 0 || T > INT32_MAX || k > INT32_MAX || n > INT32_MAX || k % 4 || f % 4 || all % 16 || large_tiles(T, n)) return MOSAIC_OK;
   if (act != -1 && act != MOSAIC_GELU && !glu) return MOSAIC_OK;
   if (norm && (k > kF32NormMax || (norm != MOSAIC_LAYERNORM && norm != MOSAIC_RMSNORM))) return MOSAIC_OK;
+  // A tile's outputs are stored while other tiles still read the inputs: an output that lies on an input, which the order of separate
+  // launches allows (the activation on X or W), keeps them, and so does an activation on Z
+  struct Span { const void* p; int64_t n; };
+  const Span in[] = {{X, T * k * 4}, {W, k * n * 4}, {bias, n * 4}, {gamma, k * 4}, {beta, k * 4}}, out[] = {{Z, T * n * 4}, {A, T * f * 4}, {U, T * k * 4}, {stats, T * 8}};
+  for (const Span& o : out)
+    for (const Span& i : in) if (overlap(o.p, o.n, i.p, i.n)) return MOSAIC_OK;
+  if (overlap(Z, T * n * 4, A, T * f * 4)) return MOSAIC_OK;
   F32Gemm p = {};
   p.A = X; p.B = W; p.bias = bias; p.C = Z; p.C2 = (float*)A; p.M = (int)T; p.N = (int)n; p.K = (int)k; p.lda = k; p.ldb = n; p.ldc = n; p.f = (int)f;
   p.tiles_m = (int)ceil_div(T, 32); p.tiles_n = (int)(glu ? ceil_div(f, 16) : ceil_div(n, 32));

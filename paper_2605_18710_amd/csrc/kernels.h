@@ -4,6 +4,11 @@
 #pragma once
 #include "common.h"
 
+// whether pn bytes at p and qn bytes at q share any; nothing overlaps a null pointer
+inline bool overlap(const void* p, int64_t pn, const void* q, int64_t qn) {
+  return p && q && (uintptr_t)p < (uintptr_t)q + (uintptr_t)qn && (uintptr_t)q < (uintptr_t)p + (uintptr_t)pn;
+}
+
 // ------------------------------------------------------------------------------ GEMM
 // C[M,N] = op(A) op(B) (+ bias[N]) (+ R[M,N]), fp32 accumulation in ascending k.
 //   a_kc: A is stored [M,K] (K contiguous) else [K,M];  b_kc: B is stored [N,K] else [K,N].
@@ -26,8 +31,8 @@ mosaic_status launch_embed_fwd(hipStream_t s, int quota, int dtype, int64_t B, i
                                const void* W, const void* bias, const void* table, void* Y);
 // Z[T,n] = X[T,k] W[k,n] (+ bias[n]) and A = act(Z): GELU / tanh GELU give A[T,n]; SwiGLU reads Z
 // as [gate | up] halves and gives A[T,n/2] = silu(gate) * up.  Where the bf16 matrix-core kernel
-// takes the product, the activation is applied in its epilogue (same bits as the separate pass);
-// otherwise the elementwise kernel follows the product.
+// takes the product, and for small fp32 products, the activation is applied in its epilogue (same bits as the separate pass);
+// otherwise the elementwise kernel follows the product.  fp32: A may lie on X, W or the bias, or be Z (GELU); the elementwise kernel then follows.
 mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act, int64_t T, int64_t k, int64_t n,
                                     const void* X, const void* W, const void* bias, void* Z, void* A);
 // Z = X W + bias over samples of 2 lo rows (of X, ldx apart, zeros past k), and P [B lo, 3n] = the gathered input of a three-tap convolution of stride 2 over

@@ -60,6 +60,22 @@ def test_linear(mb, dtype, T, k, n, offset):
     assert all(torch.equal(bits(a), bits(c)) for a, c in zip(*outs))
 
 
+# the activation on an input of the product, or Z itself: several tile columns, k == n (GELU) and n == 2k (SwiGLU)
+@pytest.mark.parametrize("act,T,h,on", [(a, *c) for a in ("gelu", "swiglu") for c in ((96, 160, "X"), (300, 128, "X"), (40, 64, "W"), (64, 64, "bias"))] +
+                         [("gelu", 33, 96, "Z")])
+def test_activation_on_an_input(mb, act, T, h, on):
+    n, code = (h, mb.GELU) if act == "gelu" else (2 * h, mb.SWIGLU)
+    rnd = lambda i, *sh: to_dev(synth.normal(6200 + T + i, sh, 0, 0.3), "f32")
+    X, W, b, Z = rnd(0, T, h), rnd(1, h, n), rnd(2, max(n, T * h)), torch.full((T, n), float("nan"), device="cuda")
+    want_z, want_a = torch.full_like(Z, float("nan")), torch.full((T, h), float("nan"), device="cuda")
+    mb.op_linear_act_fwd(None, 256, "f32", code, T, h, n, X.clone(), W.clone(), b.clone(), want_z, want_a)
+    A = {"X": X, "W": W, "Z": Z, "bias": b}[on]
+    mb.op_linear_act_fwd(None, 256, "f32", code, T, h, n, X, W, b, Z, A)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(A.reshape(-1)[:T * h]), bits(want_a.reshape(-1)))
+    assert on == "Z" or torch.equal(bits(Z), bits(want_z))
+
+
 @pytest.mark.parametrize("dtype,B,N,H,Hkv,d,causal,offset", [
     ("f32", 1, 1, 1, 1, 4, 1, 0), ("f32", 2, 16, 2, 1, 16, 1, 0), ("f32", 1, 17, 4, 2, 20, 0, 0), ("f32", 2, 33, 2, 2, 32, 1, 0),
     ("f32", 1, 100, 6, 2, 64, 0, 0), ("f32", 1, 65, 2, 2, 128, 1, 0), ("f32", 2, 31, 3, 1, 5, 0, 0), ("f32", 1, 48, 2, 2, 80, 1, 0),
