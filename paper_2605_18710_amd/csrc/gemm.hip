@@ -1669,8 +1669,10 @@ mosaic_status launch_mfma_shape(hipStream_t s, int quota, int M, int N, int K, c
   // K-tile (a 128 x 128 tile 0.35 us per 64 k-values, 0.21 of it matrix work), so half a tile to each of twice the CUs is faster however
   // short the contraction.  128 -> 64 rows: forward 1568 x 768 x 768 9.6 -> 8.3 us, 1568 x 3072 x 768 22.8 -> 19.2, with GELU
   // 12.8 -> 10.5 and 25.9 -> 21.4; input gradient 200 x 1024 x 3072 21.4 -> 17.7, on 64 CUs 21.4 -> 17.6.
+  // An output on an operand stays with 128 rows, of which there may be only one tile: it then reads everything before it stores.
   if constexpr (A_KC) {
-    if (plan == 128 && ceil_div(M, 64) * ceil_div(N, 128) <= quota) {
+    auto on_operand = [&](const void* out, uint32_t bytes) { return overlap(out, bytes, A, a_bytes) || overlap(out, bytes, B, b_bytes); };
+    if (plan == 128 && ceil_div(M, 64) * ceil_div(N, 128) <= quota && !on_operand(C, c_bytes) && !on_operand(aa.C2, aa.c2_bytes)) {
       auto go = [&](auto act) {
         return launch_mfma<64, 128, 2, 2, A_KC, B_KC, PIECES_NONE, decltype(act)::value, 64>(s, launch_quota, M, N, K, A, lda, B, ldb, C, ldc, bias, R, a_bytes, b_bytes,
                                                                                           c_bytes, 1, 0, nullptr, 1, 0, -1, aa);

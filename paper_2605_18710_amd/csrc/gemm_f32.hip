@@ -475,8 +475,11 @@ mosaic_status launch_t(hipStream_t s, int quota, F32Gemm p) {
   // 192 tiles 31.0 / 41.8.  bf16 tensors, 256 tiles 33.0 / 39.3, 576 76.5 / 66.0, 1024 122.6 / 82.2.
   const bool large = large_tiles(p.M, p.N);
   p.in_shares = std::is_same<T, float>::value && !large && share_order(p);
+  // (an output on an operand stays with the larger tiles, of which there may be only one: it then reads everything before it stores)
+  const int64_t ab = (A_KC ? (int64_t)(p.M - 1) * p.lda + p.K : (int64_t)(p.K - 1) * p.lda + p.M) * 4;
+  const int64_t bb = (B_KC ? (int64_t)(p.N - 1) * p.ldb + p.K : (int64_t)(p.K - 1) * p.ldb + p.N) * 4, cb = ((int64_t)(p.M - 1) * p.ldc + p.N) * 4;
   if constexpr (std::is_same<T, float>::value && VEC) {
-    if (p.in_shares && p.K >= 128 && share_tiles(p) <= 2 * (int64_t)quota) {
+    if (p.in_shares && p.K >= 128 && share_tiles(p) <= 2 * (int64_t)quota && !overlap(p.C, cb, p.A, ab) && !overlap(p.C, cb, p.B, bb)) {
       share_layout(&p);
       gemm_f32_share_kernel<A_KC, B_KC, F32_PLAIN><<<p.tiles_m * p.tiles_n, 64 * kShares, 0, s>>>(p);
       MOSAIC_LAUNCH_CHECK();

@@ -219,3 +219,27 @@ def test_backward_products_in_one_launch(mb, T, k, n):
     for o in outs[1:]:
         assert all(torch.equal(a, b) for a, b in zip(outs[0], o))
     m.destroy()
+
+
+@pytest.mark.parametrize("dtype,T,k,n", [("bf16", 128, 128, 128), ("bf16", 100, 72, 64), ("f32", 32, 256, 32), ("f32", 20, 28, 132)])
+def test_output_of_one_tile_on_an_operand(mb, dtype, T, k, n):
+    """A product of one tile of 128 x 128 (fp32: 32 x 32) reads both operands before it stores: its output may lie on
+    either, and it must not be dealt out in smaller tiles then."""
+    rnd = lambda i, *sh: to_dev(synth.normal(7800 + T + i, sh, 0, 0.3), dtype)
+    X, W, dY = rnd(0, T, k), rnd(1, k, n), rnd(2, T, n)
+    Y, dX = torch.empty_like(dY), torch.empty_like(X)
+    mb.op_linear_fwd(None, 256, dtype, T, k, n, X, W, None, None, Y)
+    mb.op_linear_dgrad(None, 256, dtype, T, k, n, dY, W, None, dX)
+    side = 128 if dtype == "bf16" else 32
+    for which in range(2):
+        at = [torch.zeros(max(T * n, T * k, k * n), dtype=X.dtype, device="cuda") for _ in range(3)]
+        for buf, t in zip(at, (X, W, dY)):
+            buf[:t.numel()] = t.reshape(-1)
+        if n <= side:
+            bufs = [b.clone() for b in at]
+            mb.op_linear_fwd(None, 256, dtype, T, k, n, bufs[0], bufs[1], None, None, bufs[which])
+            assert torch.equal(bufs[which][:T * n], Y.reshape(-1))
+        if k <= side:
+            bufs = [b.clone() for b in at]
+            mb.op_linear_dgrad(None, 256, dtype, T, k, n, bufs[2], bufs[1], None, bufs[2 - which])
+            assert torch.equal(bufs[2 - which][:T * k], dX.reshape(-1))
