@@ -191,14 +191,14 @@ __global__ __launch_bounds__(64 * SPLIT) void attn_fwd_f32(const T* __restrict__
       }
     }
     l = groups_sum(l);                       // every lane group has summed its own keys
-    if constexpr (SPLIT > 1) {               // the waves' sums brought to one reference; a wave without keys has m = -inf and l = 0
+    if constexpr (SPLIT > 1) {               // the waves' sums brought to one reference; a wave without keys has l = 0 (a NaN among its scores: l = NaN, m = -inf)
       if (g == 0) { rows_m[wave][lr] = m; rows_l[wave][lr] = l; }
       __syncthreads();
       float top = rows_m[0][lr], total = 0.f;
 #pragma unroll
       for (int w = 1; w < SPLIT; ++w) top = fmaxf(top, rows_m[w][lr]);
 #pragma unroll
-      for (int w = 0; w < SPLIT; ++w) total += rows_m[w][lr] == -INFINITY ? 0.f : rows_l[w][lr] * expf(rows_m[w][lr] - top);
+      for (int w = 0; w < SPLIT; ++w) total += rows_l[w][lr] == 0.f ? 0.f : rows_l[w][lr] * expf(rows_m[w][lr] - top);
       const float own = m == -INFINITY ? 0.f : expf(m - top);
 #pragma unroll
       for (int s = 0; s < DB; ++s) o[s] *= own;

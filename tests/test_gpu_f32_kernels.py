@@ -127,6 +127,40 @@ def test_attention_items_of_four_waves(mb, B, N, H, Hkv, d, causal):
         test_attention_backward_in_one_launch_has_the_bits_of_two(mb, B, N, H, Hkv, d, causal)
 
 
+@pytest.mark.parametrize("d", [32, 64])
+def test_attention_non_finite_scores(mb, d):
+    """NaN in a query row, and in all keys of one of the four waves: O and the log-sum-exp of the rows that see them are NaN, the
+    others untouched.  Scores of -inf in all keys of one wave: those keys have no weight."""
+    B, N, H, step = 1, 128, 2, 32 if d == 32 else 16
+    def run(q, k, v, causal):
+        qkv = to_dev(np.concatenate([q, k, v], 1), "f32")
+        Oo, lse = torch.empty(N, H * d, device="cuda"), torch.empty(B, H, N, device="cuda")
+        mb.op_attention_fwd(None, 256, "f32", B, N, H, d, causal, qkv, Oo, lse)
+        torch.cuda.synchronize()
+        return from_dev(Oo).reshape(N, H, d), from_dev(lse)[0]
+    q, k, v = [synth.normal(6400 + d + i, (N, H * d)) for i in range(3)]
+    base_o, base_l = run(q, k, v, 1)
+    bad = q.copy()
+    bad[37, :d] = np.nan                                   # head 0
+    o, l = run(bad, k, v, 1)
+    assert np.isnan(l[0, 37]) and np.isnan(o[37, 0]).all()
+    o[37, 0], l[0, 37] = base_o[37, 0], base_l[0, 37]
+    assert np.array_equal(o, base_o) and np.array_equal(l, base_l)
+    bad = k.copy()
+    for j in range(step, N, 4 * step):                     # the second wave's steps
+        bad[j:j + step] = np.nan
+    o, l = run(q, bad, v, 1)
+    assert np.isnan(l[:, step:]).all() and np.isnan(o[step:]).all()
+    assert np.array_equal(o[:step], base_o[:step]) and np.array_equal(l[:, :step], base_l[:, :step])
+    q, k = 1e20 * (0.5 + np.abs(q)), 1e-20 * k
+    for j in range(step, N, 4 * step):
+        k[j:j + step] = -1e20
+    o, l = run(q, k, v, 0)
+    qkv = quantize(np.concatenate([q, k, v], 1), "f32")
+    assert_close(o.reshape(N, -1), O.attention_fwd(qkv, B, N, H, 0, H), "f32", "O", roundings=2)
+    assert_close(l, O.attention_lse(qkv, B, N, H, 0, H)[0], "f32", "lse", roundings=4)
+
+
 @pytest.mark.parametrize("T,k,n", [(1, 4, 4), (33, 64, 36), (256, 128, 384), (31, 132, 68), (300, 36, 8)])
 def test_backward_products_in_one_launch_have_the_bits_of_two(mb, T, k, n):
     """A module takes the input and the weight gradient of a linear layer in one launch, the entry points one each."""
