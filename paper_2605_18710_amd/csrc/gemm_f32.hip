@@ -145,7 +145,7 @@ __device__ __forceinline__ void f32_norm_panel(const F32Gemm& p, int m0, bool fi
     const int c = (l + 8 * i) * 4;
     f32x4 o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = (v[i][e] - mean) * rstd * gm[i][e] + bt[i][e];
+    for (int e = 0; e < 4; ++e) o[e] = c < h ? (v[i][e] - mean) * rstd * gm[i][e] + bt[i][e] : 0.f;      // mean * rstd may overflow
     *reinterpret_cast<f32x4*>(panel + r * kF32NormPitch + c) = o;
     if (first && row < p.M && c < h) *reinterpret_cast<f32x4*>(p.U + (int64_t)row * h + c) = o;
   }

@@ -184,3 +184,17 @@ def test_backward_products_in_one_launch_have_the_bits_of_two(mb, T, k, n):
     for name, got, want in (("dx", dx, dx2), ("w_1", part(m.grads, "w_1"), dw1), ("w_2", part(m.grads, "w_2"), dw2)):
         assert torch.equal(bits(got.contiguous()), bits(want)), name
     m.destroy()
+
+
+@pytest.mark.parametrize("h", [32, 64])
+def test_norm_of_large_constant_rows(mb, h):
+    """Rows of one value have no variance and the normalised row is zero, though mean * rstd is beyond fp32.  Widths below and of
+    a whole K-tile of the product that the norm shares a launch with."""
+    m = mb.Module(dict(kind="encoder", batch=1, seq=40, hidden=h, heads=2, mlp=2 * h, layers=1, norm="layernorm", act="gelu", causal=0, bias=1, eps=1e-5), "f32")
+    m.params.copy_(torch.randn(m.params.numel(), generator=torch.Generator().manual_seed(h)).mul_(0.1))
+    x = torch.full((40, h), 2.0 ** 121, device="cuda")
+    y = torch.full_like(x, float("nan"))
+    m.forward(256, None, x, y)
+    torch.cuda.synchronize()
+    assert torch.equal(y, x)                # the layer adds values far below x's last bit
+    m.destroy()
