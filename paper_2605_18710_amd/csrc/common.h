@@ -65,14 +65,17 @@ static inline int grid_for(int quota, int wg_per_cu, int64_t items) {
 }
 
 // Grid of a pass over `items` blocks that moves `bytes` in all.  What fits the caches goes to a persistent grid; above, a
-// workgroup per block, started in order (a masked stream keeps them on its CUs): the accesses in flight then lie side by side, where
-// workgroups that stride drift apart over the whole tensors.  A plain copy of 1 GiB: 4.5 TB/s by 2048 striding workgroups, 6.1 by one per block.
+// workgroup per block, started in order: the accesses in flight then lie side by side, where workgroups that stride drift apart over the
+// whole tensors.  A plain copy of 1 GiB: 4.5 TB/s by 2048 striding workgroups, 6.1 by one per block.  Such a launch is held to its
+// quota by the stream's CU mask alone, so it is made only where there is one (stream_within) or the quota is the device.
 constexpr int64_t kSweepBytes = (int64_t)64 << 20;
-static inline int sweep_grid(int quota, int64_t items, int64_t bytes) {
-  if (bytes <= kSweepBytes) return grid_for(quota, 8, items);
-  return (int)(items < (1 << 22) ? items : (1 << 22));        // a launch holds fewer than 2^32 threads; kernels stride past that
+bool stream_within(hipStream_t s, int quota);      // launcher.hip: whether work on `s` runs on at most `quota` CUs
+struct Sweep { int grid; bool in_order; };
+static inline Sweep sweep_grid(hipStream_t s, int quota, int64_t items, int64_t bytes) {
+  if (bytes <= kSweepBytes || !stream_within(s, quota)) return {grid_for(quota, 8, items), false};
+  return {(int)(items < (1 << 22) ? items : (1 << 22)), true};        // a launch holds fewer than 2^32 threads; kernels stride past that
 }
-// Tensors larger than the last-level cache (256 MB) together are read and written past it.
+// Tensors larger than the last-level cache (256 MB) together are read and written past it, by workgroups in order.
 constexpr int64_t kPastCacheBytes = (int64_t)256 << 20;
 
 // --------------------------------------------------------------- device-side helpers

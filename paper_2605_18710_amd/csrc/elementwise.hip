@@ -878,7 +878,7 @@ static mosaic_status norm_fwd_t(hipStream_t s, int quota, int norm, int64_t rows
   if (rows == 0) return MOSAIC_OK;
   // in order, a row to a wave, only where the tensors are well past 64 MB: the gain is paid for by reading the gains again for every row.
   // 32768 x 4096 RMSNorm 130 -> 105 us (64 CUs 337 -> 236), LayerNorm 153 -> 141 (462 -> 446); 8192 x 2048, 67 MB, 11.4 / 11.4, 9216 x 1024 6.1 / 6.8
-  const int grid = sweep_grid(quota, ceil_div(rows, kWaves), rows * h * (int64_t)sizeof(T));
+  const int grid = sweep_grid(s, quota, ceil_div(rows, kWaves), rows * h * (int64_t)sizeof(T)).grid;
 #define L(NVC)                                                                                         \
   if (norm == MOSAIC_LAYERNORM)                                                                        \
     norm_fwd_kernel<T, MOSAIC_LAYERNORM, NVC><<<grid, kThreads, 0, s>>>(x, gamma, beta, y, stats, rows, (int)h, eps); \
@@ -1045,7 +1045,7 @@ mosaic_status launch_gelu_fwd(hipStream_t s, int quota, int dtype, int64_t n, co
   EW_CHECK_VEC(n, dtype);
   if (n == 0) return MOSAIC_OK;
   const int64_t nvec = n / vn__;
-  const int grid = sweep_grid(quota, ceil_div(nvec, kThreads), 2 * n * (int64_t)dtype_size(dtype));
+  const int grid = sweep_grid(s, quota, ceil_div(nvec, kThreads), 2 * n * (int64_t)dtype_size(dtype)).grid;
   if (dtype == MOSAIC_BF16) gelu_fwd_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)z, (bf16*)a, nvec);
   else gelu_fwd_kernel<float><<<grid, kThreads, 0, s>>>((const float*)z, (float*)a, nvec);
   MOSAIC_LAUNCH_CHECK();
@@ -1067,7 +1067,7 @@ mosaic_status launch_swiglu_fwd(hipStream_t s, int quota, int dtype, int64_t T, 
   EW_CHECK_VEC(f, dtype);
   if (T * f == 0) return MOSAIC_OK;
   const int fv = (int)(f / vn__);
-  const int grid = sweep_grid(quota, ceil_div(T * fv, kThreads), 3 * T * f * (int64_t)dtype_size(dtype));
+  const int grid = sweep_grid(s, quota, ceil_div(T * fv, kThreads), 3 * T * f * (int64_t)dtype_size(dtype)).grid;
   if (dtype == MOSAIC_BF16) swiglu_fwd_kernel<bf16><<<grid, kThreads, 0, s>>>((const bf16*)gu, (bf16*)a, T, fv);
   else swiglu_fwd_kernel<float><<<grid, kThreads, 0, s>>>((const float*)gu, (float*)a, T, fv);
   MOSAIC_LAUNCH_CHECK();
@@ -1080,12 +1080,12 @@ mosaic_status launch_swiglu_bwd(hipStream_t s, int quota, int dtype, int64_t T, 
   if (T * f == 0) return MOSAIC_OK;
   const int fv = (int)(f / vn__);
   const int64_t bytes = 5 * T * f * (int64_t)dtype_size(dtype);
-  const int grid = sweep_grid(quota, ceil_div(T * fv, kThreads), bytes);
+  const Sweep sw = sweep_grid(s, quota, ceil_div(T * fv, kThreads), bytes);
   auto launch = [&](auto type, auto past) {
     typedef decltype(type) E;
-    swiglu_bwd_kernel<E, decltype(past)::value><<<grid, kThreads, 0, s>>>((const E*)gu, (const E*)da, (E*)dgu, T, fv);
+    swiglu_bwd_kernel<E, decltype(past)::value><<<sw.grid, kThreads, 0, s>>>((const E*)gu, (const E*)da, (E*)dgu, T, fv);
   };
-  auto of_type = [&](auto type) { if (bytes > kPastCacheBytes) launch(type, std::true_type{}); else launch(type, std::false_type{}); };
+  auto of_type = [&](auto type) { if (sw.in_order && bytes > kPastCacheBytes) launch(type, std::true_type{}); else launch(type, std::false_type{}); };
   if (dtype == MOSAIC_BF16) of_type(bf16{}); else of_type(float{});
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;

@@ -129,6 +129,24 @@ extern "C" mosaic_status mosaic_stream_create(int32_t cu_quota, int32_t cu_offse
   return MOSAIC_OK;
 }
 
+// Asks the runtime, which knows the mask of any stream, the caller's own too.  The default streams have none.
+bool stream_within(hipStream_t s, int quota) {
+  constexpr int kWords = 32;
+  DeviceInfo di;
+  if (mosaic_device_info(&di) != MOSAIC_OK) return false;
+  if (quota >= di.cu_count) return true;
+  if (s == nullptr || s == hipStreamPerThread || s == hipStreamLegacy) return false;
+  uint32_t mask[kWords] = {};
+  if (di.cu_count > 32 * kWords) return false;
+  if (hipExtStreamGetCUMask(s, (uint32_t)((di.cu_count + 31) / 32), mask) != hipSuccess) {
+    (void)hipGetLastError();                     // or the next launch's check would report it
+    return false;
+  }
+  int cus = 0;
+  for (uint32_t w : mask) cus += __builtin_popcount(w);
+  return cus > 0 && cus <= quota;
+}
+
 extern "C" void* mosaic_stream_native(const mosaic_stream* s) { return s ? (void*)s->s : nullptr; }
 extern "C" int32_t mosaic_stream_quota(const mosaic_stream* s) { return s ? s->quota : 0; }
 extern "C" int32_t mosaic_stream_offset(const mosaic_stream* s) { return s ? s->offset : 0; }

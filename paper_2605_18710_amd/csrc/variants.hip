@@ -253,7 +253,7 @@ mosaic_status launch_rope(hipStream_t s, int quota, int dtype, int B, int N, int
   const int64_t rows = (int64_t)B * N;
   if (rows == 0) return MOSAIC_OK;
   const int rot = (H + Hkv) * d, width = (H + 2 * Hkv) * d;
-  const int grid = sweep_grid(quota, ceil_div(rows * (rot / vn), kThreads), 2 * rows * rot * (int64_t)dtype_size(dtype));
+  const int grid = sweep_grid(s, quota, ceil_div(rows * (rot / vn), kThreads), 2 * rows * rot * (int64_t)dtype_size(dtype)).grid;
   if (dtype == MOSAIC_BF16) rope_kernel<bf16><<<grid, kThreads, 0, s>>>((bf16*)qkv, (const float2*)table, rows, N, rot, width, d, (float)direction);
   else rope_kernel<float><<<grid, kThreads, 0, s>>>((float*)qkv, (const float2*)table, rows, N, rot, width, d, (float)direction);
   MOSAIC_LAUNCH_CHECK();
@@ -272,12 +272,12 @@ mosaic_status launch_adamw(hipStream_t s, int quota, int dtype, int64_t n, void*
   const float inv_bc1 = (float)(1.0 / (1.0 - pow((double)beta1, (double)step)));
   const float inv_bc2 = (float)(1.0 / (1.0 - pow((double)beta2, (double)step)));
   const int64_t nvec = n / vn, es = (int64_t)dtype_size(dtype), bytes = n * (master ? 2 * es + 24 : 3 * es + 16);
-  const int grid = sweep_grid(quota, ceil_div(nvec, kThreads), bytes);
+  const Sweep sw = sweep_grid(s, quota, ceil_div(nvec, kThreads), bytes);
   auto launch = [&](auto type, auto past) {
     typedef decltype(type) E;
-    adamw_kernel<E, decltype(past)::value><<<grid, kThreads, 0, s>>>((E*)p, (const E*)g, m, v, master, nvec, lr, beta1, beta2, eps, weight_decay, inv_bc1, inv_bc2);
+    adamw_kernel<E, decltype(past)::value><<<sw.grid, kThreads, 0, s>>>((E*)p, (const E*)g, m, v, master, nvec, lr, beta1, beta2, eps, weight_decay, inv_bc1, inv_bc2);
   };
-  auto of_type = [&](auto type) { if (bytes > kPastCacheBytes) launch(type, std::true_type{}); else launch(type, std::false_type{}); };
+  auto of_type = [&](auto type) { if (sw.in_order && bytes > kPastCacheBytes) launch(type, std::true_type{}); else launch(type, std::false_type{}); };
   if (dtype == MOSAIC_BF16) of_type(bf16{}); else of_type(float{});
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;
