@@ -71,8 +71,8 @@ static inline int grid_for(int quota, int wg_per_cu, int64_t items) {
 constexpr int64_t kSweepBytes = (int64_t)64 << 20;
 bool stream_within(hipStream_t s, int quota);      // launcher.hip: whether work on `s` runs on at most `quota` CUs
 struct Sweep { int grid; bool in_order; };
-static inline Sweep sweep_grid(hipStream_t s, int quota, int64_t items, int64_t bytes) {
-  if (bytes <= kSweepBytes || !stream_within(s, quota)) return {grid_for(quota, 8, items), false};
+static inline Sweep sweep_grid(hipStream_t s, int quota, int64_t items, int64_t bytes, int64_t from = kSweepBytes) {
+  if (bytes <= from || !stream_within(s, quota)) return {grid_for(quota, 8, items), false};
   return {(int)(items < (1 << 22) ? items : (1 << 22)), true};        // a launch holds fewer than 2^32 threads; kernels stride past that
 }
 // Tensors larger than the last-level cache (256 MB) together are read and written past it, by workgroups in order.

@@ -88,10 +88,10 @@ __global__ __launch_bounds__(kThreads) void rope_kernel(T* __restrict__ qkv, con
 // AdamW with decoupled weight decay and bias-corrected moments; moments (and the optional
 // master copy of the parameters) are fp32 whatever the parameter dtype.
 // Bound by memory: 28 bytes per bf16 parameter with a master copy (the stored parameters are written only), 22 without.  Workgroups
-// in order and, where the state is larger than the last-level cache, accesses past it: 202 M parameters with a master copy
+// in order and, where what is read does not stay in the last-level cache, accesses past it: 202 M parameters with a master copy
 // 1267 us -> 933 (6.1 TB/s), without 953 -> 719, 52 M 324 -> 252 and 240 -> 180; on 64 CUs 2290 -> 1920.  A state that the cache
-// holds is faster through it: 8.4 M with a master copy 34.9, past it 39.6; on 64 CUs 45.6, and 83.
-template <typename T, bool PAST>
+// holds is faster through it: 14.7 M fp32 parameters with a master copy 58.6 us, past it 69; on 64 CUs 84.5, and 154.
+template <typename T, bool PAST, bool MASTER>
 __global__ __launch_bounds__(kThreads) void adamw_kernel(T* __restrict__ p, const T* __restrict__ g, float* __restrict__ m,
                                                          float* __restrict__ v, float* __restrict__ master, int64_t nvec,
                                                          float lr, float b1, float b2, float eps, float wd,
@@ -103,17 +103,17 @@ __global__ __launch_bounds__(kThreads) void adamw_kernel(T* __restrict__ p, cons
   typedef __attribute__((ext_vector_type(4))) T vec4;
   typedef __attribute__((ext_vector_type(4))) float f32x4;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nvec; i += (int64_t)gridDim.x * kThreads) {
-    vec4 pv = {};
-    f32x4 ms = {0.f, 0.f, 0.f, 0.f};
-    if (master) ms = load_from<PAST>(reinterpret_cast<const f32x4*>(master + i * 4));
-    else pv = load_from<PAST>(reinterpret_cast<const vec4*>(p + i * 4));
     const vec4 gv = load_from<PAST>(reinterpret_cast<const vec4*>(g + i * 4));
     f32x4 mv = load_from<PAST>(reinterpret_cast<const f32x4*>(m + i * 4));
     f32x4 vv = load_from<PAST>(reinterpret_cast<const f32x4*>(v + i * 4));
+    vec4 pv = {};
+    f32x4 ms = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (MASTER) ms = load_from<PAST>(reinterpret_cast<const f32x4*>(master + i * 4));
+    else pv = load_from<PAST>(reinterpret_cast<const vec4*>(p + i * 4));
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float gk = (float)gv[k];
-      const float pk = master ? ms[k] : (float)pv[k];
+      const float pk = MASTER ? ms[k] : (float)pv[k];
       const float mk = b1 * mv[k] + (1.0f - b1) * gk;
       const float vk = b2 * vv[k] + (1.0f - b2) * gk * gk;
       mv[k] = mk; vv[k] = vk;
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kThreads) void adamw_kernel(T* __restrict__ p, cons
     }
     store_to<PAST>(reinterpret_cast<f32x4*>(m + i * 4), mv);
     store_to<PAST>(reinterpret_cast<f32x4*>(v + i * 4), vv);
-    if (master) store_to<PAST>(reinterpret_cast<f32x4*>(master + i * 4), ms);
+    if constexpr (MASTER) store_to<PAST>(reinterpret_cast<f32x4*>(master + i * 4), ms);
     store_to<PAST>(reinterpret_cast<vec4*>(p + i * 4), pv);
   }
 }
@@ -271,13 +271,23 @@ mosaic_status launch_adamw(hipStream_t s, int quota, int dtype, int64_t n, void*
   // bias corrections in double on the host: 1 - beta^t loses digits in float for small t
   const float inv_bc1 = (float)(1.0 / (1.0 - pow((double)beta1, (double)step)));
   const float inv_bc2 = (float)(1.0 / (1.0 - pow((double)beta2, (double)step)));
-  const int64_t nvec = n / vn, es = (int64_t)dtype_size(dtype), bytes = n * (master ? 2 * es + 24 : 3 * es + 16);
-  const Sweep sw = sweep_grid(s, quota, ceil_div(nvec, kThreads), bytes);
-  auto launch = [&](auto type, auto past) {
+  const int64_t nvec = n / vn, es = (int64_t)dtype_size(dtype), bytes = n * (master ? 2 * es + 24 : 3 * es + 16), reads = n * (es + (master ? 12 : es + 8));
+  // In order from 64 MB; on more than half of the device from 100 MB unless bf16 has a master copy (without one, striding / in order on 256
+  // CUs: 77 MB 12.4 / 13.1 us, 110 MB 17.5 / 18; with one 70 MB 12.0 / 10.7; on 64 CUs 77 MB 19.6 / 17.9).
+  const Sweep sw = sweep_grid(s, quota, ceil_div(nvec, kThreads), bytes, quota > 128 && !(master && dtype == MOSAIC_BF16) ? (int64_t)100 << 20 : kSweepBytes);
+  // Past the cache from 288 MB that are read: below, what the last step left there is found again (in order through it / past it, bf16 with a
+  // master copy on 256 and 64 CUs: 264 MB held, 231 read, 77 / 79 and 151 / 169 us; 320 held, 280 read, 92 / 96 and 227 / 205; 400, 350 read, 138 / 119
+  // and 284 / 259; fp32 350 held, 280 read, 77 / 85 and 191 / 194; 400, 320 read, 90 / 97 and 233 / 221).
+  const bool past_cache = sw.in_order && reads > (int64_t)288 << 20;
+  auto launch = [&](auto type, auto past, auto with_master) {
     typedef decltype(type) E;
-    adamw_kernel<E, decltype(past)::value><<<sw.grid, kThreads, 0, s>>>((E*)p, (const E*)g, m, v, master, nvec, lr, beta1, beta2, eps, weight_decay, inv_bc1, inv_bc2);
+    adamw_kernel<E, decltype(past)::value, decltype(with_master)::value>
+        <<<sw.grid, kThreads, 0, s>>>((E*)p, (const E*)g, m, v, master, nvec, lr, beta1, beta2, eps, weight_decay, inv_bc1, inv_bc2);
   };
-  auto of_type = [&](auto type) { if (sw.in_order && bytes > kPastCacheBytes) launch(type, std::true_type{}); else launch(type, std::false_type{}); };
+  auto of_type = [&](auto type) {
+    auto where = [&](auto past) { if (master) launch(type, past, std::true_type{}); else launch(type, past, std::false_type{}); };
+    if (past_cache) where(std::true_type{}); else where(std::false_type{});
+  };
   if (dtype == MOSAIC_BF16) of_type(bf16{}); else of_type(float{});
   MOSAIC_LAUNCH_CHECK();
   return MOSAIC_OK;

@@ -223,10 +223,12 @@ def test_adamw_steps(mb, dtype, n, master):
         assert np.array_equal(from_dev(p_), quantize(from_dev(mast), "bf16"))        # params = rounding of the master copy
 
 
-# one workgroup per block from 64 MB on, past the caches from 256 MB on: the same bits as the update in pieces that take neither
-@pytest.mark.parametrize("dtype,master,mb_total", [("bf16", True, 64), ("bf16", False, 257), ("bf16", True, 257), ("f32", False, 257)])
+# one workgroup per block from 64 MB on (without a master copy 100), past the caches from 288 MB that are read on (of 28 bytes a parameter
+# with a master copy 14, of 22 without 12, of 28 in fp32 16): the same bits as the update in pieces that take neither
+@pytest.mark.parametrize("dtype,master,mb_total", [("bf16", True, 64), ("bf16", False, 257), ("bf16", True, 257), ("f32", False, 257),
+                                                   ("bf16", False, 529), ("bf16", True, 577), ("f32", False, 505), ("f32", True, 577)])
 def test_adamw_of_large_states(mb, dtype, master, mb_total):
-    per = (28 if master else 22) if dtype == "bf16" else 28
+    per = (28 if master else 22) if dtype == "bf16" else 32 if master else 28
     n = 4 * ((mb_total << 20) // per // 4 + 257)                      # the last block is partly past the end
     g = torch.Generator(device="cuda").manual_seed(7)
     td = torch.bfloat16 if dtype == "bf16" else torch.float32
