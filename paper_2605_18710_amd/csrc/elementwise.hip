@@ -868,6 +868,17 @@ int pick_nv(int need) {
     default: MACRO(10); break;  \
   }
 
+// workgroups of kThreads that a CU holds at once, by the kernel's registers
+template <auto kernel>
+static int resident_workgroups() {
+  static const int n = [] {
+    int r = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, reinterpret_cast<const void*>(kernel), kThreads, 0) != hipSuccess) { (void)hipGetLastError(); r = 0; }
+    return r > 0 ? r : 8;
+  }();
+  return n;
+}
+
 template <typename T>
 static mosaic_status norm_fwd_t(hipStream_t s, int quota, int norm, int64_t rows, int64_t h, float eps,
                                 const T* x, const T* gamma, const T* beta, T* y, float* stats) {
@@ -876,14 +887,17 @@ static mosaic_status norm_fwd_t(hipStream_t s, int quota, int norm, int64_t rows
   const int nv = pick_nv((int)ceil_div(h, 64 * VN));
   if (nv < 0) MOSAIC_FAIL(MOSAIC_EUNSUPPORTED, "norm width %lld too large", (long long)h);
   if (rows == 0) return MOSAIC_OK;
-  // in order, a row to a wave, only where the tensors are well past 64 MB: the gain is paid for by reading the gains again for every row.
-  // 32768 x 4096 RMSNorm 130 -> 105 us (64 CUs 337 -> 236), LayerNorm 153 -> 141 (462 -> 446); 8192 x 2048, 67 MB, 11.4 / 11.4, 9216 x 1024 6.1 / 6.8
-  const int grid = sweep_grid(s, quota, ceil_div(rows, kWaves), rows * h * (int64_t)sizeof(T)).grid;
-#define L(NVC)                                                                                         \
-  if (norm == MOSAIC_LAYERNORM)                                                                        \
-    norm_fwd_kernel<T, MOSAIC_LAYERNORM, NVC><<<grid, kThreads, 0, s>>>(x, gamma, beta, y, stats, rows, (int)h, eps); \
-  else                                                                                                 \
-    norm_fwd_kernel<T, MOSAIC_RMSNORM, NVC><<<grid, kThreads, 0, s>>>(x, gamma, beta, y, stats, rows, (int)h, eps)
+  // Workgroups that a CU holds at once, not eight where registers allow three to seven: those behind the first would start when the first have
+  // walked their whole share.  Eight to a CU / resident, us on 256 and 64 CUs: LayerNorm 24576 x 1536 (seven) 27.5 / 24.0 and 65.6 / 47.7, 35840 x 2048
+  // (five) 66.5 / 59.4 and 189 / 165; RMSNorm 35840 x 4096 (seven) 134 / 119 and 370 / 272.  One workgroup per four rows, started in order, reads the
+  // gains again for every row: rows of 64 to 1024 values up to a quarter slower (1048576 x 64 225 / 262, on 64 CUs 858 / 1044).
+  auto launch = [&](auto nvc, auto kind) {
+    constexpr auto kern = norm_fwd_kernel<T, decltype(kind)::value, decltype(nvc)::value>;
+    kern<<<grid_for(quota, std::min(8, resident_workgroups<kern>()), ceil_div(rows, kWaves)), kThreads, 0, s>>>(x, gamma, beta, y, stats, rows, (int)h, eps);
+  };
+#define L(NVC)                                                                                                                          \
+  if (norm == MOSAIC_LAYERNORM) launch(std::integral_constant<int, NVC>{}, std::integral_constant<int, MOSAIC_LAYERNORM>{});           \
+  else launch(std::integral_constant<int, NVC>{}, std::integral_constant<int, MOSAIC_RMSNORM>{})
   DISPATCH_NV(nv, L);
 #undef L
   MOSAIC_LAUNCH_CHECK();

@@ -1,5 +1,5 @@
 """Byte-bound passes over tensors that are walked in order, one workgroup per block (from 64 MB on), or past the caches (from
-256 MB on): the same bits as in pieces that take neither road."""
+256 MB on), and norms, whose grid is what the CUs hold at once: the same bits as in pieces that take neither road."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -49,7 +49,8 @@ def test_swiglu(mb, dtype, T, f, q):
     assert torch.equal(a, a2) and torch.equal(dgu, dgu2)
 
 
-@pytest.mark.parametrize("dtype,norm,T,h,q", [("bf16", "layernorm", 8201, 4104, 256), ("bf16", "rmsnorm", 8201, 4104, 64), ("f32", "rmsnorm", 17003, 1028, 256)])
+@pytest.mark.parametrize("dtype,norm,T,h,q", [("bf16", "layernorm", 40001, 1536, 64), ("f32", "layernorm", 3001, 2048, 64), ("bf16", "rmsnorm", 9001, 5120, 64),
+                                              ("bf16", "layernorm", 8201, 4104, 256), ("bf16", "rmsnorm", 8201, 4104, 64), ("f32", "rmsnorm", 17003, 1028, 256)])
 def test_norm_forward(mb, dtype, norm, T, h, q):
     x, gain, bias = normal(dtype, T, h), normal(dtype, h), normal(dtype, h, 1).reshape(-1)
     y, y2 = nan_like(x), nan_like(x)
