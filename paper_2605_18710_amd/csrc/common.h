@@ -64,7 +64,7 @@ static inline int grid_for(int quota, int wg_per_cu, int64_t items) {
   return (int)g;
 }
 
-// Grid of a pass over `items` blocks that moves `bytes` in all.  What fits the caches goes to a persistent grid; above, a
+// Grid of a pass over `items` blocks that moves `bytes` in all.  Up to `from` bytes, a persistent grid; above, a
 // workgroup per block, started in order: the accesses in flight then lie side by side, where workgroups that stride drift apart over the
 // whole tensors.  A plain copy of 1 GiB: 4.5 TB/s by 2048 striding workgroups, 6.1 by one per block.  Such a launch is held to its
 // quota by the stream's CU mask alone, so it is made only where there is one (stream_within) or the quota is the device.

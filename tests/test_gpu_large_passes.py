@@ -63,6 +63,21 @@ def test_norm_forward(mb, dtype, norm, T, h, q):
     assert torch.equal(y, y2) and torch.equal(st, st2)
 
 
+# the sizes between which GELU's grid is chosen: in order from 64 MB, fp32 striding up to 100 MB and from 256 to 320
+@pytest.mark.parametrize("dtype,megabytes,q", [("bf16", 65, 256), ("bf16", 65, 64), ("f32", 70, 256), ("f32", 120, 256), ("f32", 280, 256), ("f32", 330, 256),
+                                               ("f32", 120, 64), ("f32", 280, 64)])
+def test_gelu_forward(mb, dtype, megabytes, q):
+    n = (megabytes << 20) // (4 if dtype == "bf16" else 8) + 1032            # the last block is partly past the end
+    z = normal(dtype, n)
+    a, a2 = nan_like(z), nan_like(z)
+    torch.cuda.synchronize()
+    mb.op_gelu_fwd(native(mb, q), q, dtype, n, z, a)
+    for at in range(0, n, 1 << 22):
+        mb.op_gelu_fwd(None, 256, dtype, min(1 << 22, n - at), z[at:], a2[at:])
+    torch.cuda.synchronize()
+    assert torch.equal(a, a2)
+
+
 def test_rotary(mb):
     B, N, H, d = 3, 1030, 48, 128
     x = normal("bf16", B * N, 3 * H * d)
