@@ -230,7 +230,13 @@ __global__ __launch_bounds__(kThreads) void norm_bwd_dx_kernel(
 // CS: the column sums of the values written to dx (as stored, after rounding) are formed the
 // same way in a third slab, scratch[p][3][h]: dx is the output gradient of the linear layer in
 // front of the residual branch, so this is that layer's bias gradient, without another pass.
-template <typename T, int NORM, int NV, bool CS = false>
+// EARLY: the residual with the row.  norm_bwd_tight names the kernels whose waves per SIMD its registers halve (or take from four to three).
+template <typename T, int NORM, int NV>
+constexpr bool norm_bwd_tight() {
+  constexpr bool ln = NORM == MOSAIC_LAYERNORM;
+  return std::is_same<T, float>::value ? (ln ? NV == 3 || NV == 8 : NV == 10) : !ln && (NV == 3 || NV == 5);
+}
+template <typename T, int NORM, int NV, bool CS = false, bool EARLY = true>
 __global__ __launch_bounds__(kThreads) void norm_bwd_fused_kernel(
     const T* __restrict__ x, const T* __restrict__ gamma, const float* __restrict__ stats,
     const T* __restrict__ dy, const T* __restrict__ R, T* __restrict__ dx, float* __restrict__ scratch,
@@ -258,7 +264,7 @@ __global__ __launch_bounds__(kThreads) void norm_bwd_fused_kernel(
     const int64_t r1 = (r0 + rp < rows) ? r0 + rp : rows;
     for (int64_t row = r0 + wave; row < r1; row += kWaves) {
       const float mean = stats[row * 2], rstd = stats[row * 2 + 1];
-      Vec16<T> xv[NV], dv[NV], rv[NV];
+      Vec16<T> xv[NV], dv[NV], rv[EARLY ? NV : 1];
       float s1 = 0.f, s2 = 0.f;
 #pragma unroll
       for (int j = 0; j < NV; ++j) {
@@ -266,7 +272,7 @@ __global__ __launch_bounds__(kThreads) void norm_bwd_fused_kernel(
         if (c < h) {
           xv[j].load(x + row * h + c);
           dv[j].load(dy + row * h + c);
-          if (R) rv[j].load(R + row * h + c);
+          if (EARLY && R) rv[EARLY ? j : 0].load(R + row * h + c);
         }
       }
 #pragma unroll
@@ -295,6 +301,7 @@ __global__ __launch_bounds__(kThreads) void norm_bwd_fused_kernel(
         const int c = (j * 64 + lane) * VN;
         if (c < h) {
           Vec16<T> o;
+          if (!EARLY && R) rv[0].load(R + row * h + c);
 #pragma unroll
           for (int i = 0; i < VN; ++i) {
             const float xr = xv[j].get(i);
@@ -302,7 +309,7 @@ __global__ __launch_bounds__(kThreads) void norm_bwd_fused_kernel(
             float r;
             if (NORM == MOSAIC_LAYERNORM) r = (t - s1 - (xr - mean) * rstd * s2) * rstd;
             else r = rstd * t - rstd * rstd * rstd * xr * s2;
-            if (R) r += rv[j].get(i);
+            if (R) r += rv[EARLY ? j : 0].get(i);
             o.set(i, r);
             if (CS) ax[CS ? j : 0][i] += o.get(i);
           }
@@ -998,11 +1005,22 @@ static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows
     // one pass: x and dy are read once for dx and for the column sums
     const int gf = grid_for(quota, 8, np);
     const Along along = take_along(quota, later);
-#define LF(NVC)                                                                                       \
-    if (norm == MOSAIC_LAYERNORM)                                                                     \
-      norm_bwd_fused_kernel<T, MOSAIC_LAYERNORM, NVC><<<along.blocks + gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np, along); \
-    else                                                                                              \
-      norm_bwd_fused_kernel<T, MOSAIC_RMSNORM, NVC><<<along.blocks + gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np, along)
+    // A kernel that the residual's registers cost a wave per SIMD requests it with the row where a CU has one workgroup at most, and (three vectors a
+    // lane) where there is one: late / early, fp32 RMSNorm 500 x 2560 15.2 / 12.3 us, 4096 x 2560 33.9 / 37.7, on 64 CUs without a residual 49.0 / 62.4;
+    // bf16 RMSNorm 4096 x 2560 on 64 CUs 45.7 / 56.9, 4096 x 1536 on 256 16.7 / 15.5, on 64 without 23.3 / 24.6.
+    auto launch = [&](auto kind, auto nvc) {
+      constexpr int KIND = decltype(kind)::value, NVC = decltype(nvc)::value;
+      auto go = [&](auto early) {
+        norm_bwd_fused_kernel<T, KIND, NVC, false, decltype(early)::value><<<along.blocks + gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np, along);
+      };
+      if constexpr (norm_bwd_tight<T, KIND, NVC>()) {
+        if (!(NVC == 3 ? R != nullptr : np <= quota)) return go(std::false_type{});
+      }
+      go(std::true_type{});
+    };
+#define LF(NVC)                                                                                                                \
+    if (norm == MOSAIC_LAYERNORM) launch(std::integral_constant<int, MOSAIC_LAYERNORM>{}, std::integral_constant<int, NVC>{}); \
+    else launch(std::integral_constant<int, MOSAIC_RMSNORM>{}, std::integral_constant<int, NVC>{})
     switch (nv) {
       case 1: LF(1); break;
       case 2: LF(2); break;
@@ -1012,7 +1030,7 @@ static mosaic_status norm_bwd_t(hipStream_t s, int quota, int norm, int64_t rows
       case 6: LF(6); break;
       case 8: LF(8); break;
       default:
-        norm_bwd_fused_kernel<T, MOSAIC_RMSNORM, 10><<<along.blocks + gf, kThreads, 0, s>>>(x, gamma, stats, dy, R, dx, scratch, rows, (int)h, rp, np, along);
+        launch(std::integral_constant<int, MOSAIC_RMSNORM>{}, std::integral_constant<int, 10>{});
         break;
     }
 #undef LF

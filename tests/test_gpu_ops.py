@@ -299,6 +299,26 @@ def test_norm_fwd_bwd(mb, dtype, norm, T, h):
             assert np.array_equal(a, b0)
 
 
+# widths whose kernel requests the residual with the row or behind its sums by how many workgroups there are for a CU (125 partitions)
+@pytest.mark.parametrize("dtype,norm,T,h", [("f32", "layernorm", 1000, 1900), ("f32", "rmsnorm", 1000, 2560), ("bf16", "rmsnorm", 1000, 2304)])
+def test_norm_bwd_residual_early_and_late(mb, dtype, norm, T, h):
+    test_norm_fwd_bwd(mb, dtype, norm, T, h)
+
+
+# and those of three vectors a lane, by whether there is a residual: a residual of zeros changes no bit
+@pytest.mark.parametrize("dtype,norm,T,h", [("f32", "layernorm", 300, 760), ("bf16", "rmsnorm", 300, 1528)])
+def test_norm_bwd_without_a_residual(mb, dtype, norm, T, h):
+    x, dy = [to_dev(synth.normal(25 + i, (T, h)), dtype) for i in range(2)]
+    g, stats = to_dev(1 + synth.normal(27, (h,), 0, 0.1), dtype), to_dev(np.abs(synth.normal(28, (T, 2))), "f32")
+    scratch, outs = torch.empty(mb.norm_bwd_scratch_bytes(h), dtype=torch.uint8, device="cuda"), []
+    for R in (None, torch.zeros_like(x)):
+        dx, dg, db = empty((T, h), dtype), empty((h,), dtype), torch.zeros(h, dtype=x.dtype, device="cuda")
+        mb.op_norm_bwd(None, 256, dtype, norm, T, h, x, g, stats, dy, R, dx, dg, db, scratch)
+        torch.cuda.synchronize()
+        outs.append((dx, dg, db))
+    assert all(torch.equal(a, b) for a, b in zip(*outs))          # values: r + 0 is r, but for the sign of a zero
+
+
 @pytest.mark.parametrize("dtype,T,f", [("f32", 32, 512), ("bf16", 1568, 3072), ("bf16", 77, 88), ("f32", 256, 384)])
 def test_activations(mb, dtype, T, f):
     z = quantize(synth.normal(30, (T, f), 0, 2.0), dtype); da = quantize(synth.normal(31, (T, f)), dtype)
