@@ -452,7 +452,8 @@ __global__ __launch_bounds__(kThreads) void col_reduce_kernel(ColReduceList list
       int p = sl * per;
       // sixteen independent requests in flight, added in ascending p; past the slice's end the last partition is asked for again and not
       // added (one by one, the up to seven partitions behind whole batches of eight took most of the time: 12000 x 1280, 500 partitions, partial
-      // sums included 11.9 -> 9.4 us, 12000 x 5120 26.8 -> 24.2; 256 x 128 7.4 -> 8.2; batches of 32 8.7, 23.5, 8.3)
+      // sums included 11.9 -> 9.4 us, 12000 x 5120 26.8 -> 24.2; this kernel alone 256 x 128, 32 partitions, 3.0 -> 2.4, 64 x 64, 8 partitions,
+      // 1.8 -> 2.2; batches of 32 8.7 and 23.5; of four where a slice has no more 2.4 and 2.2)
       constexpr int ONCE = 16;
       for (; p < p1; p += ONCE) {
         float v[ONCE];
