@@ -818,8 +818,9 @@ __global__ __launch_bounds__(kThreads) void pos_grad_kernel(const T* __restrict_
 // What the gradient of a patch stem's output gives besides the product: dpos[t, :] = sum over samples (ascending) of dy, and the partial
 // column sums of the bias gradient.  A wave takes 64 * V columns of `rp` positions and goes through the samples of a position, eight of them
 // requested together; the bias sums run over its positions and samples in that order.  Bound by memory and, as the waves are few, by the
-// latency of their requests: four bytes a lane.  One pass over dy where there were two, and a launch less: the stem's step of
-// 16 x 576 x 1024 65.3 -> 61.1 us (eight bytes a lane 61.8), of 4 x 196 x 768 32.8 -> 31.6.
+// latency of their requests: four bytes a lane, up to four samples 16 (bits do not follow it: a lane owns its columns).  One pass over dy where there
+// were two, and a launch less: the backward pass of 16 x 576 x 1024 31.0 -> 25.1 us (eight bytes a lane 25.9), of 4 x 196 x 768 19.9 -> 16.2.  Four / 16
+// bytes a lane at 2 x 4096 x 1024, us: 27.2 / 26.6, on 32 CUs 55 / 38 (two passes 43); at 8 x 1024 x 1024 24.6 / 26.1.
 template <typename T, int V>
 __global__ __launch_bounds__(kThreads) void stem_grad_kernel(const T* __restrict__ dy, T* __restrict__ dpos, float* __restrict__ partial, int B, int N, int h,
                                                              int rp, int np, int ctiles) {
@@ -1293,7 +1294,8 @@ mosaic_status launch_pos_grad(hipStream_t s, int quota, int dtype, int B, int N,
 }
 
 mosaic_status launch_stem_grad(hipStream_t s, int quota, int dtype, int B, int N, int h, const void* dy, void* dpos, void* colsum, void* scratch) {
-  // rows that start off a 16-byte boundary, or more samples than a wave should walk one position after the other
+  // Rows that start off a 16-byte boundary.  More than 32 samples would be faster here too (48 x 576 x 1024 50.9 -> 42.1 us), but a position's
+  // samples are one chain of additions in the bias sums, where the column sums' partitions start at eight rows: it is kept short.
   if (B <= 0 || N <= 0 || h <= 0 || B > 32 || !wide_access(h, dtype, dy, dpos)) {
     MOSAIC_TRY(launch_pos_grad(s, quota, dtype, B, N, h, dy, dpos));
     return launch_colsum(s, quota, dtype, (int64_t)B * N, h, dy, colsum, scratch);
@@ -1301,9 +1303,13 @@ mosaic_status launch_stem_grad(hipStream_t s, int quota, int dtype, int B, int N
   const int rp = (int)ceil_div(N, kColsumMaxParts), np = (int)ceil_div(N, rp);
   auto launch = [&](auto type) {
     typedef decltype(type) E;
-    constexpr int V = 4 / sizeof(E);
-    const int ctiles = (int)ceil_div(h, 64 * V), grid = grid_for(quota, 8, ceil_div((int64_t)np * ctiles, kWaves));
-    stem_grad_kernel<E, V><<<grid, kThreads, 0, s>>>((const E*)dy, (E*)dpos, (float*)scratch, B, N, h, rp, np, ctiles);
+    auto wide = [&](auto bytes) {
+      constexpr int V = decltype(bytes)::value / sizeof(E);
+      const int ctiles = (int)ceil_div(h, 64 * V), grid = grid_for(quota, 8, ceil_div((int64_t)np * ctiles, kWaves));
+      stem_grad_kernel<E, V><<<grid, kThreads, 0, s>>>((const E*)dy, (E*)dpos, (float*)scratch, B, N, h, rp, np, ctiles);
+    };
+    if (B <= 4) wide(std::integral_constant<int, 16>{});
+    else wide(std::integral_constant<int, 4>{});
   };
   if (dtype == MOSAIC_BF16) launch(bf16{}); else launch(float{});
   MOSAIC_LAUNCH_CHECK();

@@ -69,7 +69,8 @@ def test_unfolding_by_rows_of_patches(B, g, patch, h, offset):
 
 
 # position and bias gradient in one pass: positions that make more than one to a partition and a last partition that is short, samples
-# past a batch of eight, a width that ends inside a wave's columns, more samples than the pass takes
-@pytest.mark.parametrize("dtype,B,g,patch,h", [("bf16", 9, 23, 4, 264), ("f32", 3, 24, 2, 132), ("bf16", 17, 3, 4, 72), ("bf16", 33, 3, 4, 72)])
+# past a batch of eight, a width that ends inside a wave's columns, the most samples of which a lane takes 16 bytes and one more, more samples
+# than the pass takes
+@pytest.mark.parametrize("dtype,B,g,patch,h", [("bf16", 9, 23, 4, 264), ("bf16", 4, 23, 4, 520), ("bf16", 1, 23, 4, 264), ("bf16", 5, 3, 4, 72), ("f32", 4, 3, 4, 260), ("f32", 3, 24, 2, 132), ("bf16", 17, 3, 4, 72), ("bf16", 33, 3, 4, 72)])
 def test_position_and_bias_gradient(dtype, B, g, patch, h):
     test_patch_stem_step(dtype, B, g, patch, h, 0)
