@@ -1823,15 +1823,16 @@ mosaic_status launch_pair(hipStream_t s, const PairHalf& dg, const PairHalf& wg)
 }  // namespace
 
 mosaic_status launch_linear_bwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t k, int64_t n, const void* X, const void* dY,
-                                const void* W, void* dX, void* dW, void* splitk_scratch, bool dx_first) {
-  const int64_t es = (int64_t)dtype_size(dtype), xb = T * k * es, yb = T * n * es, wb = k * n * es, lim = (int64_t)1 << 31;
+                                const void* W, void* dX, void* dW, void* splitk_scratch, bool dx_first, int64_t ldx) {
+  if (ldx == 0) ldx = k;
+  const int64_t es = (int64_t)dtype_size(dtype), xin = ((T - 1) * ldx + k) * es, xb = T * k * es, yb = T * n * es, wb = k * n * es, lim = (int64_t)1 << 31;
   const uintptr_t all = (uintptr_t)X | (uintptr_t)dY | (uintptr_t)W | (uintptr_t)dX | (uintptr_t)dW;
-  const bool fits = dtype == MOSAIC_BF16 && T > 0 && k > 0 && n > 0 && T <= INT32_MAX && k <= INT32_MAX && n <= INT32_MAX && k % 8 == 0 && n % 8 == 0 &&
-                    all % 16 == 0 && xb < lim && yb < lim && wb < lim;
+  const bool fits = dtype == MOSAIC_BF16 && T > 0 && k > 0 && n > 0 && T <= INT32_MAX && k <= INT32_MAX && n <= INT32_MAX && k % 8 == 0 && n % 8 == 0 && ldx % 8 == 0 &&
+                    all % 16 == 0 && xin < lim && xb < lim && yb < lim && wb < lim;
   // an output that lies on an input, which the order of two launches may allow, keeps them
-  const bool apart = !overlap(dX, xb, X, xb) && !overlap(dX, xb, dY, yb) && !overlap(dX, xb, W, wb) && !overlap(dX, xb, dW, wb) &&
-                     !overlap(dW, wb, X, xb) && !overlap(dW, wb, dY, yb) && !overlap(dW, wb, W, wb);
-  if (dtype == MOSAIC_F32 && T > 0 && k > 0 && n > 0 && apart && pair_enabled()) {
+  const bool apart = !overlap(dX, xb, X, xin) && !overlap(dX, xb, dY, yb) && !overlap(dX, xb, W, wb) && !overlap(dX, xb, dW, wb) &&
+                     !overlap(dW, wb, X, xin) && !overlap(dW, wb, dY, yb) && !overlap(dW, wb, W, wb);
+  if (dtype == MOSAIC_F32 && T > 0 && k > 0 && n > 0 && ldx == k && apart && pair_enabled()) {
     bool taken;
     MOSAIC_TRY(launch_linear_bwd_f32(s, quota, T, k, n, X, dY, W, dX, dW, &taken));
     if (taken) return MOSAIC_OK;
@@ -1850,16 +1851,16 @@ mosaic_status launch_linear_bwd(hipStream_t s, int quota, int dtype, int64_t T, 
         h.aa.row_block = row_block_for(K, M, 128);
         return h;
       };
-      PairHalf dg = half(dY, n, W, n, dX, T, k, n, 0, pp.wgs_d), wg = half(X, k, dY, n, dW, k, n, T, pp.wgs_d, pp.wgs_w);
+      PairHalf dg = half(dY, n, W, n, dX, T, k, n, 0, pp.wgs_d), wg = half(X, ldx, dY, n, dW, k, n, T, pp.wgs_d, pp.wgs_w);
       dg.a_bytes = (uint32_t)yb; dg.b_bytes = (uint32_t)wb; dg.c_bytes = (uint32_t)xb;
-      wg.a_bytes = (uint32_t)xb; wg.b_bytes = (uint32_t)yb; wg.c_bytes = (uint32_t)wb;
+      wg.a_bytes = (uint32_t)xin; wg.b_bytes = (uint32_t)yb; wg.c_bytes = (uint32_t)wb;
       if (wp.pieces > 1) { wg.ktiles_per = wp.kper / 64; return launch_pair<PIECES_CHAINED>(s, dg, wg); }
       return launch_pair<PIECES_NONE>(s, dg, wg);
     }
   }
   auto input_grad = [&] { return launch_gemm(s, quota, dtype, true, true, T, k, n, dY, n, W, n, dX, k, nullptr, nullptr); };
   if (dx_first) MOSAIC_TRY(input_grad());
-  MOSAIC_TRY(launch_gemm(s, quota, dtype, false, false, k, n, T, X, k, dY, n, dW, n, nullptr, nullptr, splitk_scratch));
+  MOSAIC_TRY(launch_gemm(s, quota, dtype, false, false, k, n, T, X, ldx, dY, n, dW, n, nullptr, nullptr, splitk_scratch));
   return dx_first ? MOSAIC_OK : input_grad();
 }
 

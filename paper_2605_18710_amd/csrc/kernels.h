@@ -40,10 +40,10 @@ mosaic_status launch_linear_act_fwd(hipStream_t s, int quota, int dtype, int act
 // the same bits.
 mosaic_status launch_gelu_taps_fwd(hipStream_t s, int quota, int dtype, int64_t B, int64_t lo, int64_t n, int64_t k, int64_t ldx, const void* X, const void* W,
                                    const void* bias, void* Z, void* A, void* P);
-// dW[k,n] = X^T dY and dX[T,k] = dY W^T, dense rows; one launch where that is the faster way, else two, the input gradient's
+// dW[k,n] = X^T dY and dX[T,k] = dY W^T, dense rows (X's ldx apart; 0: k); one launch where that is the faster way, else two, the input gradient's
 // first or last (1 - 2 % of a layer either way, by what the caches still hold)
 mosaic_status launch_linear_bwd(hipStream_t s, int quota, int dtype, int64_t T, int64_t k, int64_t n, const void* X, const void* dY,
-                                const void* W, void* dX, void* dW, void* splitk_scratch, bool dx_first);
+                                const void* W, void* dX, void* dW, void* splitk_scratch, bool dx_first, int64_t ldx = 0);
 
 // U = norm(X), stats, then Z[T,n] = U W (+ bias) and, act >= 0, A = act(Z): one launch for small fp32 layers, else launch_norm_fwd and
 // launch_gemm or launch_linear_act_fwd

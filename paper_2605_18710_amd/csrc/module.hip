@@ -447,14 +447,9 @@ mosaic_status conv_stem_backward(mosaic_module* m, hipStream_t s, int q, const v
   MOSAIC_TRY(launch_gelu_bwd_colsum(s, q, dt, Tin, h, W(m, m->c_z1), W(m, m->c_dp2), W(m, m->c_dz1), G(m, p.b_1), W(m, m->s_colsum), &sums, Lo));
   MOSAIC_TRY(launch_col_reduce(s, q, dt, sums));
   const int64_t ld = taps_ld(d);
-  if (dx && ld == 3 * C) {
-    MOSAIC_TRY(launch_linear_bwd(s, q, dt, Tin, 3 * C, h, W(m, m->c_p1), W(m, m->c_dz1), P(m, p.w_1), W(m, m->c_dp1), G(m, p.w_1), sk, false));
-  } else {
-    MOSAIC_TRY(launch_gemm(s, q, dt, false, false, 3 * C, h, Tin, W(m, m->c_p1), ld, W(m, m->c_dz1), h, G(m, p.w_1), h, nullptr, nullptr, sk));
-    if (dx) MOSAIC_TRY(launch_gemm(s, q, dt, true, true, Tin, 3 * C, h, W(m, m->c_dz1), h, P(m, p.w_1), h, W(m, m->c_dp1), 3 * C, nullptr, nullptr));
-  }
-  if (dx) MOSAIC_TRY(launch_col2im1d(s, q, dt, d.batch, L, C, W(m, m->c_dp1), dx));
-  return MOSAIC_OK;
+  if (!dx) return launch_gemm(s, q, dt, false, false, 3 * C, h, Tin, W(m, m->c_p1), ld, W(m, m->c_dz1), h, G(m, p.w_1), h, nullptr, nullptr, sk);
+  MOSAIC_TRY(launch_linear_bwd(s, q, dt, Tin, 3 * C, h, W(m, m->c_p1), W(m, m->c_dz1), P(m, p.w_1), W(m, m->c_dp1), G(m, p.w_1), sk, false, ld));
+  return launch_col2im1d(s, q, dt, d.batch, L, C, W(m, m->c_dp1), dx);
 }
 
 }  // namespace
