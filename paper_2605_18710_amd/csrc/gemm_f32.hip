@@ -250,39 +250,53 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Gemm& p, int tile, float*
   if constexpr (!NORM) ta.request(A, p.lda, m0, p.M, 0, p.K);
   tb.request(B, p.ldb, n0, p.N, 0, p.K, GU ? p.f : 0);
   if constexpr (NORM != 0) f32_norm_panel<NORM>(p, m0, tn == 0, panel);
-  int st = 0, fold = 0;
-  for (int k0 = 0; k0 < p.K; k0 += KS, st ^= 1) {
-    float* a = lds + st * STAGE;
-    float* b = a + AFLOATS;
-    if constexpr (!NORM) ta.put(a);
-    tb.put(b);
-    __syncthreads();                     // the other stage was read before this barrier, and is written after the next
-    if (k0 + KS < p.K) {
-      if constexpr (!NORM) ta.request(A, p.lda, m0, p.M, k0 + KS, p.K);
-      tb.request(B, p.ldb, n0, p.N, k0 + KS, p.K, GU ? p.f : 0);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS / 16; ++ks) {
-      f32x4 fa[TW], fb[TW];
-#pragma unroll
-      for (int i = 0; i < TW; ++i) {
-        if constexpr (NORM != 0) fa[i] = *reinterpret_cast<const f32x4*>(panel + (wm + 16 * i + lr) * kF32NormPitch + k0 + 16 * ks + 4 * g);
-        else fa[i] = TA::frag(a, wm + 16 * i + lr, ks, g);
-        fb[i] = TB::frag(b, wn + 16 * i + lr, ks, g);
+  int st = 0, k0 = 0;
+  // A share's K-tiles in a loop of their own, and the reads from LDS dealt out by hand: with a share's sum taken inside the loop the compiler kept
+  // one pair of registers for B's fragments and waited for LDS eight times a K-tile.  Forward, us: 32 x 3072 x 768 on 32 CUs 34.9 -> 29.8 (29.8
+  // without shares, 32.4 by the loop alone), 64 x 768 x 768 on 64 10.5 -> 9.5 (9.2), 512 x 512 x 512, not in shares, 7.7 -> 7.0; input gradient
+  // 1024 x 1024 x 1024 27.0 -> 24.9.  All fragments before the first instruction: 32 x 3072 x 768 31.3, but 1024 x 1024 x 1024 29.1.
+  do {
+    const int k_end = SHARES && share ? min(p.K, k0 + share) : p.K;
+    for (; k0 < k_end; k0 += KS, st ^= 1) {
+      float* a = lds + st * STAGE;
+      float* b = a + AFLOATS;
+      if constexpr (!NORM) ta.put(a);
+      tb.put(b);
+      __syncthreads();                     // the other stage was read before this barrier, and is written after the next
+      if (k0 + KS < p.K) {
+        if constexpr (!NORM) ta.request(A, p.lda, m0, p.M, k0 + KS, p.K);
+        tb.request(B, p.ldb, n0, p.N, k0 + KS, p.K, GU ? p.f : 0);
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int ks = 0; ks < KS / 16; ++ks) {
+        f32x4 fa[TW], fb[TW];
 #pragma unroll
-        for (int i = 0; i < TW; ++i)
+        for (int i = 0; i < TW; ++i) {
+          if constexpr (NORM != 0) fa[i] = *reinterpret_cast<const f32x4*>(panel + (wm + 16 * i + lr) * kF32NormPitch + k0 + 16 * ks + 4 * g);
+          else fa[i] = TA::frag(a, wm + 16 * i + lr, ks, g);
+          fb[i] = TB::frag(b, wn + 16 * i + lr, ks, g);
+        }
 #pragma unroll
-          for (int j = 0; j < TW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[i][e], acc[i][j], 0, 0, 0);
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < TW; ++i)
+#pragma unroll
+            for (int j = 0; j < TW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[i][e], acc[i][j], 0, 0, 0);
+      }
+      if constexpr (TW == 1) {
+        // a step's fragments are read from LDS two steps before they are multiplied
+        constexpr int READS = (NORM || A_KC ? 1 : 2) + (B_KC ? 1 : 2);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * READS, 0);
+#pragma unroll
+        for (int ks = 0; ks < KS / 16; ++ks) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+          if (ks + 2 < KS / 16) __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+        }
+      }
     }
-    if constexpr (SHARES) {
-      fold += KS;
-      if (fold == share) { sum += acc[0][0]; acc[0][0] = f32x4{0.f, 0.f, 0.f, 0.f}; fold = 0; }
-    }
-  }
-  if constexpr (SHARES) acc[0][0] = sum + acc[0][0];
+    if constexpr (SHARES) { sum += acc[0][0]; acc[0][0] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  } while (SHARES && k0 < p.K);
+  if constexpr (SHARES) acc[0][0] = sum;
   __syncthreads();                       // the next tile writes stage 0
   // acc[i][j][e] is output (row m0+wm+16i+lr, column n0+wn+16j+4g+e)
   if constexpr (EPI != F32_PLAIN) {
