@@ -127,15 +127,34 @@ def test_attention_items_of_four_waves(mb, B, N, H, Hkv, d, causal):
         test_attention_backward_in_one_launch_has_the_bits_of_two(mb, B, N, H, Hkv, d, causal)
 
 
+@pytest.mark.parametrize("B,N,H,Hkv,d,causal", [(1, 33, 2, 1, 32, 1), (1, 48, 4, 4, 64, 0), (2, 100, 4, 2, 60, 1), (1, 257, 3, 3, 16, 1), (1, 250, 3, 1, 28, 0),
+                                                (2, 256, 8, 8, 32, 1), (1, 64, 64, 64, 16, 0)])
+def test_attention_four_sums_by_four_waves_or_one(mb, B, N, H, Hkv, d, causal):
+    """The share of the CUs decides whether four waves form an item's four sums or one: the bits must not show which."""
+    w = (H + 2 * Hkv) * d
+    qkv, dO = [to_dev(synth.normal(1000 + N + i, (B * N, n)), "f32") for i, n in enumerate((w, H * d))]
+    first = None
+    for q in (256, 128, 64, 32, 16, 8, 1):
+        Oo, dqkv = [torch.full((B * N, n), float("nan"), device="cuda") for n in (H * d, w)]
+        lse, delta = [torch.full((B, H, N), float("nan"), device="cuda") for _ in range(2)]
+        mb.op_attention_gqa_fwd(None, q, "f32", B, N, H, Hkv, d, causal, qkv, Oo, lse)
+        mb.op_attention_gqa_bwd(None, q, "f32", B, N, H, Hkv, d, causal, qkv, Oo, lse, dO, dqkv, delta)
+        torch.cuda.synchronize()
+        got = [bits(t) for t in (Oo, lse, dqkv, delta)]
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(got, first)), q
+
+
+@pytest.mark.parametrize("q", [256, 2])
 @pytest.mark.parametrize("d", [32, 64])
-def test_attention_non_finite_scores(mb, d):
+def test_attention_non_finite_scores(mb, d, q):
     """NaN in a query row, and in all keys of one of the four waves: O and the log-sum-exp of the rows that see them are NaN, the
     others untouched.  Scores of -inf in all keys of one wave: those keys have no weight."""
-    B, N, H, step = 1, 128, 2, 32 if d == 32 else 16
+    B, N, H, step, cus = 1, 128, 2, 32 if d == 32 else 16, q          # 2 CUs: one wave forms the four sums
     def run(q, k, v, causal):
         qkv = to_dev(np.concatenate([q, k, v], 1), "f32")
         Oo, lse = torch.empty(N, H * d, device="cuda"), torch.empty(B, H, N, device="cuda")
-        mb.op_attention_fwd(None, 256, "f32", B, N, H, d, causal, qkv, Oo, lse)
+        mb.op_attention_fwd(None, cus, "f32", B, N, H, d, causal, qkv, Oo, lse)
         torch.cuda.synchronize()
         return from_dev(Oo).reshape(N, H, d), from_dev(lse)[0]
     q, k, v = [synth.normal(6400 + d + i, (N, H * d)) for i in range(3)]
