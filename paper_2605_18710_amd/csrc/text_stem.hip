@@ -23,6 +23,7 @@
 // A walk over all positions by the owner of every table row (V x T id reads) takes 2000 us there, but is one launch,
 // and still what small calls take (scan_is_faster).
 #include "kernels.h"
+#include "sample_index.h"
 
 namespace {
 
@@ -189,8 +190,8 @@ __global__ __launch_bounds__(kThreads) void sort_scatter_kernel(SortInput in, in
 }
 
 // Keys of the positions first + r * step, r < rounds, all of them requested together (conditional loads would wait for each
-// other); -1 past the end.  Positions without an id to read are requested outside the buffer, which reads nothing.  The sample of a
-// position is floor((e + 1/2) / N), in fp32: exact below 2^21, and e < 2^14 here; an integer division a key costs more than the loads.
+// other); -1 past the end.  Positions without an id to read are requested outside the buffer, which reads nothing.  An integer division a
+// key would cost more than the loads (sample_of).
 template <int R, int N>
 __device__ __forceinline__ void keys_at(const SortInput& in, int first, int step, int rounds, int total, int (&key)[N]) {
   if constexpr (R > 1) {
@@ -203,7 +204,7 @@ __device__ __forceinline__ void keys_at(const SortInput& in, int first, int step
   int t[R], img[R], id[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int e = first + r * step, b = (int)(((float)e + 0.5f) * inv);
+    const int e = first + r * step, b = sample_of(e, inv);
     const bool live = r < rounds && e < total;
     t[r] = live ? e - b * in.N : -1;
     img[r] = in.counts ? (int)__builtin_amdgcn_raw_buffer_load_b32(counts, live ? b * 4 : kOutside, 0, 0) : in.n_img;
@@ -226,6 +227,7 @@ __device__ __forceinline__ void keys_at(const SortInput& in, int first, int step
 constexpr int kOneThreads = 1024, kOneWaves = kOneThreads / 64, kFlagRows = 2048;
 constexpr int kOneMax = 8 * kOneThreads;              // positions that one workgroup sorts
 static_assert(kFlagRows <= kOneWaves * kBins + kOneMax, "flags");
+static_assert(2 * kOneMax <= kSampleMax, "sample_of, positions past the end (fewer than as many again) included");
 template <typename T, int V>
 __global__ __launch_bounds__(kOneThreads) void embed_prepare_kernel(SortInput in, const T* __restrict__ dy, T* __restrict__ d_img, T* __restrict__ dtable,
                                                                     int B, int h, int total, int pos_bits, int32_t* __restrict__ key_out,

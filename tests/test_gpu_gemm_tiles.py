@@ -1,5 +1,6 @@
 """Small products: 128 x 128 tiles take 64-deep K-tiles where every workgroup has a CU to itself and
-32-deep ones otherwise; the bits must not show which.  Contractions around one and two K-tiles and around the
+32-deep ones otherwise, and where the CUs hold them all, tiles of 64 x 128 take their place (not in the weight gradient, nor
+with SwiGLU); the bits must not show which.  Contractions around one and two K-tiles and around the
 ring of stages, ragged in all dimensions, all three forms, bias, residual and activations."""
 import numpy as np
 import pytest
@@ -28,8 +29,14 @@ def test_k_tile_depths_agree(mb, T, k, n):
     X, W, b, R, dY = [quantize(synth.normal(s + i, sh, 0, sd), "bf16") for i, (sh, sd) in
                       enumerate([((T, k), 1), ((k, n), 0.05), ((n,), 0.1), ((T, n), 1), ((T, n), 1)])]
     X_, W_, b_, R_, dY_ = [to_dev(a, "bf16") for a in (X, W, b, R, dY)]
+    # CUs for tiles of 128 rows, one to a CU, but not for those of 64 (above 32, shares count in steps of 32)
+    deep = set()
+    for cols in (n, k):
+        t128, t64 = -(-T // 128) * -(-cols // 128), -(-T // 64) * -(-cols // 128)
+        q = t128 if t128 <= 32 else -(-t128 // 32) * 32
+        deep |= {q} if q < t64 else set()
     outs = []
-    for q in (256, 1):                    # one workgroup per CU; more tiles than slots
+    for q in [256, 1] + sorted(deep):     # one workgroup per CU; more tiles than slots
         e = lambda *sh: torch.full(sh, float("nan"), dtype=torch.bfloat16, device="cuda")
         Y, Z, A, dX, dW = e(T, n), e(T, n), e(T, n), e(T, k), e(k, n)
         sc = torch.empty(max(16, mb.linear_wgrad_scratch_bytes(T, k, n)), dtype=torch.uint8, device="cuda")
@@ -54,7 +61,7 @@ def test_k_tile_depths_agree(mb, T, k, n):
         g = from_dev(G)
         assert_close(g, O.linear_fwd(X, W), "bf16", "gate | up")
         assert_close(from_dev(S), O.swiglu_fwd(g[:, :n // 2], g[:, n // 2:]), "bf16", "swiglu")
-    assert all(torch.equal(a.view(torch.int16), c.view(torch.int16)) for a, c in zip(*outs))
+    assert all(torch.equal(a.view(torch.int16), c.view(torch.int16)) for o in outs[1:] for a, c in zip(o, outs[0]))
 
 
 @pytest.mark.parametrize("T,k,n", [(1, 8, 8), (63, 72, 136), (64, 128, 128), (65, 64, 264), (128, 1000, 120), (129, 136, 392), (200, 520, 1024)])

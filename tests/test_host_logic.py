@@ -3,6 +3,8 @@ declares, and its host-side logic (mask arithmetic, plan validation, quota choic
 descriptor validation, parameter layout) behaves as the header states."""
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -278,9 +280,27 @@ def test_weight_gradient_split_is_a_function_of_the_shape(T, k, n, pieces, cut_t
     assert got == aligned + mb.colsum_scratch_bytes(n), why
 
 
-def test_sample_of_a_position_by_a_reciprocal():
-    """The text stem's floor((e + 1/2) * (1 / N)) in fp32 against the integer division, over the positions that one workgroup sorts."""
-    e = np.arange(9216, dtype=np.int32)
-    half = e.astype(np.float32) + np.float32(0.5)
-    for N in range(1, 8193):
-        assert np.array_equal((half * (np.float32(1) / np.float32(N))).astype(np.int32), e // N), N
+SAMPLES = r"""
+#include <stdio.h>
+#include "sample_index.h"
+int main() {
+  long wrong = 0;
+  auto check = [&](int e, int N) { if (sample_of(e, 1.f / (float)N) != e / N) ++wrong; };
+  for (int N = 1; N <= 8192; ++N)
+    for (int e = 0; e < 16384; ++e) check(e, N);
+  for (int N = 1; N < kSampleMax; N += 1 + N / 64)
+    for (int e = N - 1; e < kSampleMax; e += N) { check(e, N); if (e + 1 < kSampleMax) check(e + 1, N); }
+  printf("%ld\n", wrong);
+}
+"""
+
+
+def test_sample_of_a_position_by_a_reciprocal(tmp_path):
+    """The text stem's sample index, compiled from the header that its kernel includes, against the integer division: all positions that one
+    workgroup sorts and as many again, and both sides of every sample's end up to the bound that the header states."""
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_18710_amd", "csrc")
+    (tmp_path / "s.cpp").write_text(SAMPLES)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", csrc, str(tmp_path / "s.cpp"), "-o", str(tmp_path / "s")], check=True)
+    assert subprocess.run([str(tmp_path / "s")], capture_output=True, text=True, check=True).stdout.split() == ["0"]
