@@ -91,7 +91,9 @@ __global__ __launch_bounds__(kThreads) void rope_kernel(T* __restrict__ qkv, con
 // in order and, where what is read does not stay in the last-level cache, accesses past it: 202 M parameters with a master copy
 // 1267 us -> 933 (6.1 TB/s), without 953 -> 719, 52 M 324 -> 252 and 240 -> 180; on 64 CUs 2290 -> 1920.  A state that the cache
 // holds is faster through it: 14.7 M fp32 parameters with a master copy 58.6 us, past it 69; on 64 CUs 84.5, and 154.
-template <typename T, bool PAST, bool MASTER>
+// MASTER: with a master copy, without (1, 0), or as the pointer says (2).  The branch costs states that the caches hold up to 7 %, but past them the kernel
+// with it is the faster one (202 M with a master copy 955 us, without the branch 974).
+template <typename T, bool PAST, int MASTER>
 __global__ __launch_bounds__(kThreads) void adamw_kernel(T* __restrict__ p, const T* __restrict__ g, float* __restrict__ m,
                                                          float* __restrict__ v, float* __restrict__ master, int64_t nvec,
                                                          float lr, float b1, float b2, float eps, float wd,
@@ -102,18 +104,19 @@ __global__ __launch_bounds__(kThreads) void adamw_kernel(T* __restrict__ p, cons
   // instruction.
   typedef __attribute__((ext_vector_type(4))) T vec4;
   typedef __attribute__((ext_vector_type(4))) float f32x4;
+  const bool has_master = MASTER == 2 ? master != nullptr : MASTER == 1;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nvec; i += (int64_t)gridDim.x * kThreads) {
+    vec4 pv = {};
+    f32x4 ms = {0.f, 0.f, 0.f, 0.f};
+    if (has_master) ms = load_from<PAST>(reinterpret_cast<const f32x4*>(master + i * 4));
+    else pv = load_from<PAST>(reinterpret_cast<const vec4*>(p + i * 4));
     const vec4 gv = load_from<PAST>(reinterpret_cast<const vec4*>(g + i * 4));
     f32x4 mv = load_from<PAST>(reinterpret_cast<const f32x4*>(m + i * 4));
     f32x4 vv = load_from<PAST>(reinterpret_cast<const f32x4*>(v + i * 4));
-    vec4 pv = {};
-    f32x4 ms = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (MASTER) ms = load_from<PAST>(reinterpret_cast<const f32x4*>(master + i * 4));
-    else pv = load_from<PAST>(reinterpret_cast<const vec4*>(p + i * 4));
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float gk = (float)gv[k];
-      const float pk = MASTER ? ms[k] : (float)pv[k];
+      const float pk = has_master ? ms[k] : (float)pv[k];
       const float mk = b1 * mv[k] + (1.0f - b1) * gk;
       const float vk = b2 * vv[k] + (1.0f - b2) * gk * gk;
       mv[k] = mk; vv[k] = vk;
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void adamw_kernel(T* __restrict__ p, cons
     }
     store_to<PAST>(reinterpret_cast<f32x4*>(m + i * 4), mv);
     store_to<PAST>(reinterpret_cast<f32x4*>(v + i * 4), vv);
-    if constexpr (MASTER) store_to<PAST>(reinterpret_cast<f32x4*>(master + i * 4), ms);
+    if (has_master) store_to<PAST>(reinterpret_cast<f32x4*>(master + i * 4), ms);
     store_to<PAST>(reinterpret_cast<vec4*>(p + i * 4), pv);
   }
 }
@@ -288,8 +291,9 @@ mosaic_status launch_adamw(hipStream_t s, int quota, int dtype, int64_t n, void*
         <<<sw.grid, kThreads, 0, s>>>((E*)p, (const E*)g, m, v, master, nvec, lr, beta1, beta2, eps, weight_decay, inv_bc1, inv_bc2);
   };
   auto of_type = [&](auto type) {
-    auto where = [&](auto past) { if (master) launch(type, past, std::true_type{}); else launch(type, past, std::false_type{}); };
-    if (past_cache) where(std::true_type{}); else where(std::false_type{});
+    if (past_cache) launch(type, std::true_type{}, std::integral_constant<int, 2>{});
+    else if (master) launch(type, std::false_type{}, std::integral_constant<int, 1>{});
+    else launch(type, std::false_type{}, std::integral_constant<int, 0>{});
   };
   if (dtype == MOSAIC_BF16) of_type(bf16{}); else of_type(float{});
   MOSAIC_LAUNCH_CHECK();
