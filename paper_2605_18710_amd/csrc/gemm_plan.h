@@ -148,7 +148,8 @@ inline WgradPlan wgrad_plan(int64_t M, int64_t N, int64_t K, int cus, bool may_c
 // the ones that its own launch would compute, in the same order of additions (a gradient that is cut has its
 // pieces chained), so the bits are those of two launches.
 // Priced against the two launches with the figures above (input gradients: those of the K-strided form, and lower
-// tiles of the four-wave kernel); a launch more costs kLaunchUs.
+// tiles of the four-wave kernel); a launch more costs kLaunchUs.  The tiles of 64 rows that an input gradient of its own may take
+// (launch_mfma_shape) are not priced: pairs are chosen as if it took 128 rows, up to a fifth slower than it is there.
 constexpr double kLaunchUs = 3.0;
 struct PairPlan { bool pair; int wgs_d, wgs_w; double us, apart_us; };
 inline PairPlan pair_plan(int64_t T, int64_t k, int64_t n, int cus, const WgradPlan& w) {

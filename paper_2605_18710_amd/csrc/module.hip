@@ -342,7 +342,7 @@ mosaic_status layers_backward(mosaic_module* m, hipStream_t s, int q, const void
     // Bias gradients are column sums of a layer's output gradient.  Each is formed by the kernel
     // that writes that gradient where there is one of ours: the first norm's backward of the
     // layer above (this layer's incoming gradient), the GELU backward, the second norm's
-    // backward.  Only the top layer's incoming gradient and dQKV take a pass of their own.
+    // backward.  The top layer's incoming gradient and dQKV have no such kernel: the next byte-bound launch takes their sums along.
     if (p.b_2 >= 0 && l == d.layers - 1) MOSAIC_TRY(launch_colsum(s, q, dt, T, h, gin, G(m, p.b_2), W(m, m->s_colsum3), &sums, true));
     const bool b1_done = d.act == MOSAIC_GELU && p.b_1 >= 0;
     MOSAIC_TRY(launch_act_linear_bwd(s, q, dt, d.act, T, f, h, W(m, sv.z), W(m, sv.a), gin, P(m, p.w_2), dA, dZ, G(m, p.w_2), W(m, m->s_splitk),
