@@ -540,6 +540,10 @@ mosaic_status launch_layer_fwd_f32(hipStream_t s, int quota, int norm, int act, 
   if (T <= 0 || k <= 0 || n <= 0 || T > INT32_MAX || k > INT32_MAX || n > INT32_MAX || k % 4 || f % 4 || all % 16 || large_tiles(T, n)) return MOSAIC_OK;
   if (act != -1 && act != MOSAIC_GELU && !glu) return MOSAIC_OK;
   if (norm && (k > kF32NormMax || (norm != MOSAIC_LAYERNORM && norm != MOSAIC_RMSNORM))) return MOSAIC_OK;
+  // The norm, formed again by every tile column, shares the launch up to two tiles to a CU of the device: a function of the shape, because its bits
+  // are not those of the norm's own kernel.  In the product's launch / apart, us: encoder layer of 2048 rows, width 256, 1536 tiles, 338 / 335, on 32 CUs
+  // 1524 / 1482; decoder layer of 1024 rows, width 256, 768 and 1536 tiles, on 64 391 / 372; 256 rows, width 128, 96 tiles, 62 / 70.
+  if (norm && ceil_div(T, 32) * (glu ? ceil_div(f, 16) : ceil_div(n, 32)) > 512) return MOSAIC_OK;
   // A tile's outputs are stored while other tiles still read the inputs: an output that lies on an input, which the order of separate
   // launches allows (the activation on X or W), keeps them, and so does an activation on Z
   struct Span { const void* p; int64_t n; };

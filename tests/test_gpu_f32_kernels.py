@@ -7,7 +7,7 @@ import pytest
 
 from oracle import layers as O
 from paper_2605_18710_amd import synth
-from helpers import quantize, to_dev, from_dev, assert_close
+from helpers import quantize, quantize_tree, to_dev, from_dev, assert_close, layer_params, load_layer_params
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -217,3 +217,25 @@ def test_norm_of_large_constant_rows(mb, h):
     torch.cuda.synchronize()
     assert torch.equal(y, x)                # the layer adds values far below x's last bit
     m.destroy()
+
+
+# 504 and 528 tiles of the q|k|v product: the norm in its launch and apart
+@pytest.mark.parametrize("kind,batch", [("encoder", 42), ("encoder", 44), ("decoder", 42), ("decoder", 44)])
+def test_norm_in_the_launch_of_the_product(mb, kind, batch):
+    ln = kind == "encoder"
+    cfg = dict(kind=kind, batch=batch, seq=32, hidden=128, heads=4, mlp=128, layers=1, norm="layernorm" if ln else "rmsnorm",
+               act="gelu" if ln else "swiglu", causal=int(not ln), bias=int(ln), eps=1e-5)
+    layers = quantize_tree([layer_params(cfg, 6600 + batch)], "f32")
+    x = quantize(synth.normal(6700 + batch, (batch * 32, 128)), "f32")
+    y_ref, _ = O.stack_fwd(x, layers, cfg)
+    m = mb.Module(cfg, "f32")
+    load_layer_params(m, layers)
+    x_, outs = to_dev(x, "f32"), []
+    for q in (256, 24):
+        y = torch.full_like(x_, float("nan"))
+        m.forward(q, None, x_, y)
+        torch.cuda.synchronize()
+        outs.append(y)
+    m.destroy()
+    assert_close(from_dev(outs[0]), y_ref, "f32", "y", roundings=8)
+    assert torch.equal(bits(outs[0]), bits(outs[1]))
