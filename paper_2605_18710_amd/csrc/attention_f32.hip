@@ -479,10 +479,11 @@ bool four_columns(int d, const void* a, const void* b, const void* c, const void
 
 // Four sums to an item where the items are few (with 1024 waves every SIMD of the device has one): a function of the shape, because the
 // order of the additions follows it.  How many waves form them follows the share of the CUs as well.  Forward: four while four to a SIMD hold
-// all items.  Backward: four where both gradients then fit side by side, or the rows are long.  Otherwise one wave to an item: waves that
+// all items, and beyond where the rows are long (B2 N192 H6 d32 causal on 16 CUs 20.2 / 17.4 / 22.9 us).  Backward: four where both gradients then fit side by side, or the rows are long.  Otherwise one wave to an item: waves that
 // wait for each other at few steps a wave cost more than they hide.  One sum / four waves / four sums by one wave, us: B8 N48 H8 d64
 // causal on 16 CUs 11.8 / 22.3 / 14.1, backward 38.5 / 69.8 / 42.2; B1 N64 H64 d16 on 64 backward 14.7 / 17.0 / 16.5, on 128 6.4 / 10.9 / 8.0; B4 N256 H4
-// d64 causal on 64 32.5 / 23.3 / -, backward 97 / 71 / -, on 16 65.6 / 81.5 / 72.2 and 230 / 263 / 235.
+// d64 causal on 64 32.5 / 23.3 / -, backward 97 / 71 / -, on 16 65.6 / 81.5 / 72.2 and 230 / 263 / 235;
+// B1 N200 H4 d32 on 32 backward 25.0 / 23.9 / 25.8, B2 N128 H4 d64 22.6 / 26.0 / 24.1.
 bool split_items(const AttnArgs& p) { return p.N > 32 && p.d <= 64 && (int64_t)p.B * p.H * p.tiles <= 256; }
 
 template <typename T, int DB, bool VEC>
@@ -491,7 +492,8 @@ mosaic_status fwd_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv
   bool split = false;
   if constexpr (std::is_same<T, float>::value && DB <= 4) {
     split = split_items(p);
-    if (split && items <= 4 * (int64_t)quota) attn_fwd_f32<T, DB, VEC, 4, 4><<<grid_for(quota, 4, items), 256, 0, s>>>((const T*)qkv, (T*)O, lse, p);
+    const int64_t fit = (p.N < 192 ? 4 : DB <= 2 ? 16 : 6) * (int64_t)quota;
+    if (split && items <= fit) attn_fwd_f32<T, DB, VEC, 4, 4><<<grid_for(quota, 4, items), 256, 0, s>>>((const T*)qkv, (T*)O, lse, p);
     else if (split) attn_fwd_f32<T, DB, VEC, 4, 1><<<grid_for(quota, 8, items), 64, 0, s>>>((const T*)qkv, (T*)O, lse, p);
   }
   if (!split) attn_fwd_f32<T, DB, VEC, 1, 1><<<grid_for(quota, 8, items), 64, 0, s>>>((const T*)qkv, (T*)O, lse, p);
@@ -524,7 +526,7 @@ mosaic_status bwd_t(hipStream_t s, int quota, const AttnArgs& p, const void* qkv
                     void* dqkv, float* delta) {
   if constexpr (std::is_same<T, float>::value && DB <= 4) {
     const int64_t ndq = (int64_t)p.B * p.H * p.tiles, ndkv = (int64_t)p.B * p.Hkv * p.tiles;
-    const bool four = 4 * (ndq + ndkv) <= 8 * (int64_t)quota || (p.N >= 256 && ndq <= 4 * (int64_t)quota);
+    const bool four = 4 * (ndq + ndkv) <= 8 * (int64_t)quota || (p.N >= 192 && ndq <= 4 * (int64_t)quota);
     if (split_items(p) && four) return bwd_split_t<T, DB, VEC, 4, 4>(s, quota, p, qkv, O, lse, dO, dqkv, delta);
     if (split_items(p)) return bwd_split_t<T, DB, VEC, 4, 1>(s, quota, p, qkv, O, lse, dO, dqkv, delta);
   }
